@@ -814,12 +814,12 @@ int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const C
         if (want_gram) {
             int cus = 0;
             GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-            const int slices = gram_slices(rows, B, cus);
-            if (int rc = grow(ws.gram, (size_t)slices * rows * rows * sizeof(float))) return rc;
+            const GramPlan plan = gram_plan(rows, B, cus);
+            if (int rc = grow(ws.gram, (size_t)plan.slices * rows * rows * sizeof(float))) return rc;
             float *C = reinterpret_cast<float *>(ws.gram.ptr);
             {
                 Span span(3, stream);
-                gram_matrix(rows, B, slices, Y, G, C, stream);
+                gram_matrix(rows, B, plan, Y, G, C, stream);
                 GIVENS_HIP(hipGetLastError());
             }
             int rc = backward_chunks<T>(ws, dev, fam.carousel, pb, rows, coefs, C, nullptr, nullptr, dtheta, stream, 1);

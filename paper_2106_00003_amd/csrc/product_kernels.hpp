@@ -1,0 +1,233 @@
+// Dense products on the matrix cores in float32 precision: D = A X for a matrix A that many columns share (U itself,
+// or U^T) and a row-major operand X of B columns.
+//
+// Precision.  The fastest matrix instructions of the chip take bf16 operands; a float32 value is exactly the sum of
+// three bf16 values (8 + 8 + 8 significand bits: x = h + m + l, h = x cut to bf16, m = x - h rounded to bf16,
+// l = x - h - m, which fits).  A product of two float32 values is therefore the sum of nine exact bf16 products, of
+// which the six largest are formed (hh, hm, mh, hl, lh, mm); what is left out (ml, lm, ll) is below 2^-24 of the
+// product.  Sums are float32, sixteen products at a time.  So operands keep their 24 bits and the accumulation its
+// float32, and six bf16 instructions of 16-deep contraction still take 1/2.7 of the time of the eight float32 ones
+// (2-deep) they replace.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace givens {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Eight float32 values as three rows of eight bf16 values with h + m + l == x (exact for every finite x whose last
+// bits are normal numbers).
+struct Split8 {
+    u32x4 h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)
+{
+    const bf16x2 v = __builtin_convertvector((f32x2){a, b}, bf16x2);   // round to nearest even
+    return __builtin_bit_cast(unsigned, v);
+}
+__device__ __forceinline__ Split8 split8(const float (&x)[8])
+{
+    Split8 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
+        // the leading piece is cut, not rounded: it cannot overflow, whatever x is
+        s.h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        const float ra = x[2 * i] - __uint_as_float(a & 0xffff0000u), rb = x[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
+        const unsigned m = pack_bf16(ra, rb);
+        s.m[i] = m;
+        s.l[i] = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+    }
+    return s;
+}
+
+// acc += a b over 16 contraction indices, float32 operands given as their pieces, smallest products first
+__device__ __forceinline__ f32x16 mfma_split(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16 acc)
+{
+    auto mm = [](u32x4 x, u32x4 y, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0,
+                                                       0, 0);
+    };
+    acc = mm(a[2], b[0], acc);
+    acc = mm(a[0], b[2], acc);
+    acc = mm(a[1], b[1], acc);
+    acc = mm(a[1], b[0], acc);
+    acc = mm(a[0], b[1], acc);
+    return mm(a[0], b[0], acc);
+}
+
+// ---- the shared matrix in operand order.  Fragment (i, k) holds rows 32 i .. + 31 and contraction indices
+// 16 k .. + 15 of A; lane l of a wavefront keeps row l % 32, indices 8 (l / 32) .. + 7 as 16 bytes per piece, so a
+// wavefront loads a piece of a fragment as 1 KB of consecutive memory.  Rows and indices beyond the matrix are zero.
+constexpr int kProductStep = 32;   // contraction indices per step of the product kernel (two fragments)
+inline long long product_k16(int k) { return (long long)((k + kProductStep - 1) / kProductStep) * 2; }
+inline long long product_pieces(int m, int k)   // 16-byte pieces of an m x k matrix, rows padded to 256
+{
+    return (long long)((m + 255) / 256) * 8 * product_k16(k) * 3 * 64;
+}
+
+// One wavefront per fragment.  TRANS: the matrix is the transpose of the array (A[i][k] = src[k * ld + i]).
+template <bool TRANS>
+__global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const float *__restrict__ src, long long ld,
+                                                           long long frags, int k16s, u32x4 *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const long long f = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (f >= frags) return;
+    const int row = (int)(f / k16s) * 32 + (lane & 31), k0 = (int)(f % k16s) * 16 + 8 * (lane >> 5);
+    float x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        x[j] = 0.f;
+        if (row < m && k0 + j < k) x[j] = TRANS ? src[(long long)(k0 + j) * ld + row] : src[(long long)row * ld + k0 + j];
+    }
+    const Split8 s = split8(x);
+    u32x4 *o = out + f * 3 * 64 + lane;
+    o[0] = s.h;
+    o[64] = s.m;
+    o[128] = s.l;
+}
+inline void split_matrix(int m, int k, const float *src, long long ld, bool trans, u32x4 *out, hipStream_t stream)
+{
+    const int k16s = (int)product_k16(k);
+    const long long frags = (long long)((m + 255) / 256) * 8 * k16s;
+    const dim3 grid((unsigned)((frags + 3) / 4)), block(256);
+    if (trans)
+        hipLaunchKernelGGL(split_matrix_kernel<true>, grid, block, 0, stream, m, k, src, ld, frags, k16s, out);
+    else
+        hipLaunchKernelGGL(split_matrix_kernel<false>, grid, block, 0, stream, m, k, src, ld, frags, k16s, out);
+}
+
+struct ProductArgs {
+    int m, k;             // rows of A (and D), contraction length (rows of X)
+    long long B;          // columns, and leading dimension of X and D
+    const u32x4 *A;       // split_matrix's output
+    const float *X;
+    float *D;
+    int mblocks;          // row blocks of the launch
+};
+
+// MW x NW wavefronts of (32 MF) x (32 NF) results each.
+template <int MW, int NW, int MF, int NF>
+__global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
+{
+    constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW;
+    constexpr int OCT = BN * 4 / T;                    // octets (8 rows x 1 column of X) a thread brings per step
+    static_assert(OCT >= 1 && T % BN == 0 || BN % T == 0, "whole octets per thread");
+    __shared__ u32x4 panel[2][4][3][BN];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave % MW, wn = wave / MW;
+    // workgroups reach the XCDs in turn: those of one XCD take all row blocks of a column block one after the other, so
+    // that the column block is read into one L2
+    const unsigned xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+    const int mb = local % a.mblocks;
+    const long long n0 = ((long long)(local / a.mblocks) * 8 + xcd) * BN;
+    if (n0 >= a.B) return;
+
+    // staging: thread t brings column t % BN, octets t / BN + i * (T / BN)   (or columns t + T i when BN > T)
+    constexpr int ROWS_PER = T >= BN ? T / BN : 1;
+    float xr[OCT][8];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < OCT; ++i) {
+            const int c = T >= BN ? (int)threadIdx.x % BN : (int)threadIdx.x + T * (i % (BN / T > 0 ? BN / T : 1));
+            const int o = T >= BN ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / BN) + ROWS_PER * i
+                                  : i / (BN / T > 0 ? BN / T : 1);
+            long long col = n0 + c;
+            col = col < a.B ? col : a.B - 1;           // past the last column: any column, its results are not stored
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                int r = k0 + 8 * o + j;
+                r = r < a.k ? r : a.k - 1;             // past the last row: A is zero there
+                xr[i][j] = (a.X + (long long)r * a.B)[col];
+            }
+        }
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < OCT; ++i) {
+            const int c = T >= BN ? (int)threadIdx.x % BN : (int)threadIdx.x + T * (i % (BN / T > 0 ? BN / T : 1));
+            const int o = T >= BN ? (int)threadIdx.x / BN + ROWS_PER * i : i / (BN / T > 0 ? BN / T : 1);
+            const Split8 s = split8(xr[i]);
+            panel[buf][o][0][c] = s.h;
+            panel[buf][o][1][c] = s.m;
+            panel[buf][o][2][c] = s.l;
+        }
+    };
+
+    const int steps = (a.k + kProductStep - 1) / kProductStep, k16s = 2 * steps;
+    const u32x4 *ap[MF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+        ap[i] = a.A + (long long)(mb * (BM / 32) + wm * MF + i) * k16s * 192 + lane;
+    u32x4 fa[2][MF][3];
+    auto load_a = [&](int set, int k16) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) fa[set][i][p] = ap[i][(long long)k16 * 192 + 64 * p];
+    };
+
+    f32x16 acc[MF][NF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    fetch(0);
+    load_a(0, 0);
+    stash(0);
+    for (int step = 0; step < steps; ++step) {
+        const int buf = step & 1;
+        __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
+        if (step + 1 < steps) fetch((step + 1) * kProductStep);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int next = 2 * step + ks + 1;
+            load_a(ks ^ 1, next < k16s ? next : k16s - 1);
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                u32x4 fb[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) fb[p] = panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * j + (lane & 31)];
+#pragma unroll
+                for (int i = 0; i < MF; ++i) acc[i][j] = mfma_split(fa[ks][i], fb, acc[i][j]);
+            }
+        }
+        if (step + 1 < steps) stash(buf ^ 1);
+    }
+
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+        const long long col = n0 + wn * 32 * NF + 32 * j + (lane & 31);
+        if (col >= a.B) continue;
+#pragma unroll
+        for (int i = 0; i < MF; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = mb * BM + wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                if (row < a.m) a.D[(long long)row * a.B + col] = acc[i][j][v];
+            }
+    }
+}
+
+template <int MW, int NW, int MF, int NF>
+inline void launch_product(ProductArgs a, hipStream_t stream)
+{
+    constexpr int BM = 32 * MF * MW, BN = 32 * NF * NW;
+    a.mblocks = (a.m + BM - 1) / BM;
+    const long long nblocks = (a.B + BN - 1) / BN;
+    const unsigned grid = (unsigned)((nblocks + 7) / 8 * 8 * a.mblocks);
+    hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+}
+
+} // namespace givens
