@@ -130,7 +130,8 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
  * givens_forward_noalloc -- givens_forward for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels
  * and bit-identical results, but the coefficient tables (cos/sin or scaled / lifted coefficients, row
- * factors, renormalisation rows, the range-check flag) are written to a static device array of
+ * factors, renormalisation rows, the range-check flag) and what a wide batch needs (U, and a copy of some
+ * columns when Y is X) are written to a static device array of
  * GIVENS_NOALLOC_BYTES bytes inside the library instead of the hipMalloc'ed workspace, so the call makes
  * no hipMalloc, hipFree or other allocating call.  Every GPU the library runs on holds that array until
  * the process ends.
@@ -142,7 +143,7 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
  *   Per-kernel timing (givens_set_timing) is not recorded for this call.
  */
 #define GIVENS_NOALLOC_MAX_N 1024
-#define GIVENS_NOALLOC_BYTES 8446208 /* flag words, table, row factors, renormalisation rows at n = 1024 */
+#define GIVENS_NOALLOC_BYTES 21029120 /* n = 1024: flag words, table, row factors, renormalisation rows; U, its pieces, a copy of 512 columns */
 int givens_forward_noalloc(int n, int64_t B, const float *theta, const float *X, float *Y, void *stream);
 
 /*
@@ -176,9 +177,8 @@ int givens_backward_ex(int n, int m, int64_t B, const float *theta, const float 
  * than the tables were built for returns GIVENS_ERR_STALE and launches nothing: call the plain entry point
  * instead.  The token must be used on the stream it was prepared on.
  *   directions : GIVENS_PREPARE_FORWARD, GIVENS_PREPARE_BACKWARD or both (or-ed).  GIVENS_PREPARE_BACKWARD_WIDE
- *     (implies _BACKWARD) also builds the tables of the forward-type sweep that computes dX in the Gram form,
- *     which the backward call takes for B >= 2 n; without it givens_backward_prepared runs the two-stage sweep
- *     over all B columns whatever B is (and returns GIVENS_ERR_STALE if the Gram form is forced).
+ *     (implies _BACKWARD) lets givens_backward_prepared take the Gram form for B >= 2 n; without it it runs the
+ *     two-stage sweep over all B columns whatever B is (and returns GIVENS_ERR_STALE if the Gram form is forced).
  *   n, m, B, X, Y, U, G, dX, dtheta : as for the plain calls; n and m are those of givens_prepare.
  */
 #define GIVENS_PREPARE_FORWARD 1

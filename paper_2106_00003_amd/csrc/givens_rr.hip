@@ -15,6 +15,7 @@
 #include "coef_kernels.hpp"
 #include "gram_kernels.hpp"
 #include "lds_kernels.hpp"
+#include "product_kernels.hpp"
 #include "rr_index.h"
 #include "unitary_kernels.hpp"
 
@@ -27,6 +28,8 @@ constexpr size_t kLdsBudgetBytes = 144 * 1024;                 // of the 160 KB 
 constexpr long long kReduceSplitMaxAngles = 1 << 18;           // below this the second stage splits the rows too
 constexpr size_t kPartialCapBytes = size_t(24) << 30;          // cap on one chunk of strip partials
 constexpr int kMaxRows = 36864;                                // largest n any kernel family takes (one float column in LDS)
+constexpr size_t kColumnsCapBytes = size_t(128) << 20;         // copied columns of an operand that its product overwrites
+constexpr long long kProductMinRatio = 2, kProductMinB = 2048; // batches whose application goes through U (wants_product)
 constexpr size_t kFlagBytes = 256;                             // the flag words of a workspace
 
 struct Buffer {
@@ -45,10 +48,10 @@ struct CoefSet {
 struct Prepared {
     int64_t token = 0;       // 0: nothing prepared
     int rows = 0, m = 0;
-    bool fwd = false, rev = false, mirrored = false;
+    bool fwd = false, rev = false, wide = false;
     // whether each set was built with the device-side choice of the rotation form (float carousel kernels
     // only can read such a set; a set built without it holds the standard form, which every family reads)
-    bool fwd_forms = false, rev_forms = false, mirrored_forms = false;
+    bool fwd_forms = false, rev_forms = false;
     float scaled_max = 0.f;
 };
 
@@ -62,7 +65,6 @@ struct Workspace {
     int flag_turn = 0;  // which of [0], [1] the next range check uses
     Buffer scale;       // scaled / lifted forms: row factors d, float [n-1][n] (scratch of the coefficient kernels)
     CoefSet fwd, rev;   // forward sweep, reverse sweep
-    CoefSet mirrored;   // forward-type sweep that computes dX = U^T G in the Gram form
     Buffer partial;     // per-workgroup (carousel) or per-strip (LDS family) dtheta partial sums
     Buffer zeros;       // N floats that are zeroed when allocated and never written again
     Buffer sink;        // N + 8192 floats: where idle lanes of the carousel reverse sweep put their sums
@@ -70,6 +72,9 @@ struct Workspace {
     Buffer chain_flags; // one cache line per workgroup and block: tag of the launch and pass that finished it;
                         // last word: the launch counter
     Buffer gram;        // Gram form: slices of C = Y G^T, rows x rows floats each
+    Buffer matrix;      // wide batches: U or U^T, rows x rows floats
+    Buffer pieces;      // ... and its pieces in operand order (product_kernels.hpp)
+    Buffer columns;     // ... and a copy of the columns at work when a result overwrites its operand
     Buffer map;         // restricted parametrisation / odd n: index in theta of every entry of E, or -1
     Buffer map_counts;  // free pairs per block (scratch of the map kernels)
     // unitary extension, carousel family: phase inputs and reduced phase angles (fixed point), rotation signs, the two
@@ -78,7 +83,7 @@ struct Workspace {
     int map_rows = 0, map_m = 0; // the (row count, m) the map was built for
     Prepared prepared;
     Buffer *all[25] = {&flag, &scale, &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
-                       &mirrored.table, &mirrored.renorm, &mirrored.factor, &partial, &zeros, &sink, &gram, &map,
+                       &matrix, &pieces, &columns, &partial, &zeros, &sink, &gram, &map,
                        &u_q, &u_psi, &u_sgn, &u_rot, &u_phs, &u_orient, &u_fin, &chain, &chain_flags};
 };
 
@@ -404,7 +409,31 @@ int workspace_coef_storage(Workspace &ws, CoefSet &set, int n, bool want_factor,
     return GIVENS_OK;
 }
 
+// What a wide batch needs beside the coefficients: U (or U^T), its pieces in operand order, and room for the columns at
+// work when the result overwrites its operand.
+struct ProductStorage {
+    float *matrix = nullptr;
+    u32x4 *pieces = nullptr;
+    float *copy = nullptr;
+    long long copy_cols = 0;
+};
+int workspace_product_storage(Workspace &ws, int rows, long long B, bool in_place, ProductStorage *out)
+{
+    if (int rc = grow(ws.matrix, (size_t)rows * rows * sizeof(float))) return rc;
+    if (int rc = grow(ws.pieces, (size_t)product_pieces(rows, rows) * sizeof(u32x4))) return rc;
+    out->matrix = reinterpret_cast<float *>(ws.matrix.ptr);
+    out->pieces = reinterpret_cast<u32x4 *>(ws.pieces.ptr);
+    if (in_place) {
+        out->copy_cols = std::max<long long>(512, (long long)(kColumnsCapBytes / sizeof(float)) / rows);
+        out->copy_cols = std::min(out->copy_cols, B);
+        if (int rc = grow(ws.columns, (size_t)out->copy_cols * rows * sizeof(float))) return rc;
+        out->copy = reinterpret_cast<float *>(ws.columns.ptr);
+    }
+    return GIVENS_OK;
+}
+
 // ---- the entry point that allocates nothing: its coefficient tables live in a static device array.
+constexpr long long kNoAllocCopyCols = 512;
 constexpr int kNoAllocMaxN = GIVENS_NOALLOC_MAX_N;
 constexpr size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr size_t noalloc_bytes(int n)
@@ -413,7 +442,10 @@ constexpr size_t noalloc_bytes(int n)
     return round_up_256(N * sizeof(float2))                                                // the table
            + round_up_256((size_t)(n - 1) * n * sizeof(float))                             // row factors
            + round_up_256((size_t)((n - 1 + kRenormPeriod - 1) / kRenormPeriod) * (n / 2) * sizeof(float2))
-           + kFlagBytes;                                                                   // flag words
+           + kFlagBytes                                                                    // flag words
+           + round_up_256((size_t)n * n * sizeof(float))                                   // U
+           + round_up_256((size_t)product_pieces(n, n) * sizeof(u32x4))                    // ... its pieces
+           + round_up_256((size_t)n * kNoAllocCopyCols * sizeof(float));                   // columns of an in-place call
 }
 constexpr size_t kNoAllocBytes = noalloc_bytes(kNoAllocMaxN);
 static_assert(kNoAllocBytes == GIVENS_NOALLOC_BYTES, "the header states the size of the static array");
@@ -423,7 +455,7 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 unsigned char *g_scratch_ptr[kMaxDevices] = {};
 int g_scratch_turn[kMaxDevices] = {};   // which of the array's two flag words the next call uses
 
-int static_coef_storage(int dev, int n, CoefStorage<float> *out)
+int static_storage(int dev, int n, CoefStorage<float> *out, ProductStorage *prod)
 {
     if (n > kNoAllocMaxN) return GIVENS_ERR_UNSUPPORTED;
     if (!g_scratch_ptr[dev]) {
@@ -448,6 +480,10 @@ int static_coef_storage(int dev, int n, CoefStorage<float> *out)
     out->scale = reinterpret_cast<float *>(take((size_t)(n - 1) * n * sizeof(float)));
     out->renorm = reinterpret_cast<float *>(take((size_t)renorm_periods(n) * (n / 2) * sizeof(float2)));
     out->factor = nullptr;
+    prod->matrix = reinterpret_cast<float *>(take((size_t)n * n * sizeof(float)));
+    prod->pieces = reinterpret_cast<u32x4 *>(take((size_t)product_pieces(n, n) * sizeof(u32x4)));
+    prod->copy = reinterpret_cast<float *>(take((size_t)n * kNoAllocCopyCols * sizeof(float)));
+    prod->copy_cols = kNoAllocCopyCols;
     return (size_t)(at - g_scratch_ptr[dev]) <= kNoAllocBytes ? GIVENS_OK : GIVENS_ERR_UNSUPPORTED;
 }
 
@@ -594,6 +630,70 @@ int run_forward_sweep(const Problem &pb, long long B, const Coefs<T> &coefs, Fam
         t_state.last_kernel = GIVENS_KERNEL_LDS;
     }
     return rc;
+}
+
+// Wide batches.  Applying U to B columns as a sweep costs n^2 / 2 rotations of two to four vector instructions per
+// column; building U costs the same for its own n columns only, and the dense product U X then runs on the matrix
+// cores at several times the sweep's rate.  Measured, sweep against product in us: n = 256, B = 2048 30 / 30, 4096
+// 42 / 31, 65536 327 / 69; n = 1024, B = 1536 196 / 223, 2048 301 / 225, 65536 2958 / 808; n = 2048, B = 2048
+// 720 / 837, 4096 1311 / 896; n = 4096, B = 4096 2997 / 3418, 8192 5867 / 4002; n = 1002 (5 slots per lane), B = 2004
+// 266 / 275, 4008 447 / 290.  The column family's sweep (n <= 128) takes one time, that of the chain through its n - 1
+// blocks, whatever the batch up to 65536, so there the product never pays.
+template <typename T>
+bool wants_product(const Families &fam, int rows, long long B)
+{
+    return std::is_same<T, float>::value && !fam.column && B >= kProductMinRatio * rows && B >= kProductMinB;
+}
+// columns that the sweep of a forward-type call runs over
+template <typename T>
+long long swept_columns(const Families &fam, int rows, long long B)
+{
+    return wants_product<T>(fam, rows, B) ? rows : B;
+}
+
+// Y = A X for the rows x rows matrix A = st.matrix; Y may be X.
+int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const float *X, float *Y, hipStream_t stream)
+{
+    int cus = 0;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    Span span(1, stream);
+    split_matrix(rows, rows, st.matrix, st.pieces, stream);
+    const long long chunk = X == Y ? st.copy_cols : B;   // a result that overwrites its operand: from copies
+    for (long long c0 = 0; c0 < B; c0 += chunk) {
+        const long long cols = std::min(chunk, B - c0);
+        ProductArgs a{rows, rows, cols, st.pieces, X + c0, B, Y + c0, B, 0};
+        if (X == Y) {
+            hipLaunchKernelGGL(copy_columns_kernel, dim3((unsigned)((cols + 255) / 256), (unsigned)std::min(rows, 256)),
+                               dim3(256), 0, stream, rows, cols, X + c0, B, st.copy, cols);
+            a.X = st.copy;
+            a.ldx = cols;
+        }
+        product(a, cus, stream);
+    }
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+
+// A forward-type application, coefficients given: the sweep, or for a wide batch the sweep that builds U (or U^T)
+// followed by the product.  `ws`: where the product's storage comes from, unless `given` is that of a call that may not
+// allocate.
+template <typename T>
+int run_forward(Workspace *ws, int dev, const Problem &pb, long long B, const Coefs<T> &coefs, Families fam, const T *X,
+                T *Y, int identity, int transpose, hipStream_t stream, const ProductStorage *given = nullptr)
+{
+    if constexpr (std::is_same<T, float>::value) {
+        if (!identity && wants_product<T>(fam, pb.rows, B)) {
+            ProductStorage st;
+            if (given)
+                st = *given;
+            else if (int rc = workspace_product_storage(*ws, pb.rows, B, X == Y, &st))
+                return rc;
+            if (int rc = run_forward_sweep<float>(pb, pb.rows, coefs, fam, nullptr, st.matrix, 1, transpose, stream))
+                return rc;
+            return apply_matrix(st, dev, pb.rows, B, X, Y, stream);
+        }
+    }
+    return run_forward_sweep<T>(pb, B, coefs, fam, X, Y, identity, transpose, stream);
 }
 
 // Reverse sweep and the reduction of its partial sums into dtheta.  LDS family: chunks of strips, one
@@ -780,26 +880,37 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
     Families fam;
     if (int rc = pick_forward_family<T>(n, B, opt.kernel, &fam)) return rc;
     Coefs<T> coefs;
-    const FormPolicy policy = form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, B));
+    const long long swept = identity ? B : swept_columns<T>(fam, rows, B);
+    const FormPolicy policy =
+        form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept));
     if (no_alloc) {
         if constexpr (std::is_same<T, float>::value) {
             CoefStorage<float> st;
-            if (int rc = static_coef_storage(dev, n, &st)) return rc;
+            ProductStorage prod;
+            if (int rc = static_storage(dev, n, &st, &prod)) return rc;
             if (int rc = build_coefs<float>(st, pb, theta, true, policy, stream, &coefs, transpose)) return rc;
+            return run_forward<float>(nullptr, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream, &prod);
         }
     } else {
         invalidate_prepared(*ws, true, false);
         if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose)) return rc;
     }
-    return run_forward_sweep<T>(pb, B, coefs, fam, X, Y, identity, transpose, stream);
+    return run_forward<T>(ws, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream);
 }
 
-// The reverse sweep of one call, reverse-direction coefficients given; `mirrored_for_dx` builds (or returns) the
-// forward-type coefficients of the mirrored problem when the Gram form needs them for dX.
-template <typename T, typename MirroredFn>
+// Whether a backward call takes the Gram form (below): the batch is wide, unless the caller has chosen.
+template <typename T>
+bool wants_gram(int n, long long B, int reduction)
+{
+    if (!std::is_same<T, float>::value) return false;
+    const bool wide = B >= 2LL * n;   // measured break-even is near B = 1.6 n
+    return reduction == GIVENS_REDUCTION_GRAM || (reduction == GIVENS_REDUCTION_AUTO && wide);
+}
+
+// The reverse sweep of one call, coefficients given.
+template <typename T>
 int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const Coefs<T> &coefs, Families fam,
-                 CallOptions opt, const T *Y, const T *G, T *dX, T *dtheta, hipStream_t stream,
-                 MirroredFn &&mirrored_for_dx)
+                 CallOptions opt, const T *Y, const T *G, T *dX, T *dtheta, hipStream_t stream)
 {
     const int n = pb.n, rows = pb.rows;
     t_state.last_kernel = fam.carousel ? GIVENS_KERNEL_CAROUSEL : GIVENS_KERNEL_LDS;
@@ -807,11 +918,9 @@ int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const C
         // Gram-matrix form for wide batches.  With C = Y G^T (rows x rows) the sums of the reverse sweep
         // are those of the same sweep run on the operand C with the identity as upstream gradient:
         // z_k gbar_k^T = A_k C A_k^T for the product A_k of the transposed blocks so far, and the sweep on
-        // (C, I) carries A_k C and A_k.  So dtheta costs one contraction over B plus a rows-column sweep, and
-        // dX = U^T G one forward-type sweep over B (mirrored tables), instead of a two-strip sweep over B.
-        const bool wide = B >= 2LL * n;   // measured break-even is near B = 1.6 n
-        const bool want_gram = opt.reduction == GIVENS_REDUCTION_GRAM || (opt.reduction == GIVENS_REDUCTION_AUTO && wide);
-        if (want_gram) {
+        // (C, I) carries A_k C and A_k.  So dtheta costs one contraction over B plus a rows-column sweep; and since
+        // the second strip ends as A = U^T, dX = U^T G is one product with what the sweep leaves behind.
+        if (wants_gram<T>(n, B, opt.reduction)) {
             int cus = 0;
             GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             const GramPlan plan = gram_plan(rows, B, cus);
@@ -822,15 +931,11 @@ int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const C
                 gram_matrix(rows, B, plan, Y, G, C, stream);
                 GIVENS_HIP(hipGetLastError());
             }
-            int rc = backward_chunks<T>(ws, dev, fam.carousel, pb, rows, coefs, C, nullptr, nullptr, dtheta, stream, 1);
-            if (rc == GIVENS_OK && dX) {
-                Coefs<T> mirrored;
-                Families dx_fam;
-                dx_fam.column = fam.column;
-                dx_fam.carousel = !fam.column && fam.carousel;
-                rc = mirrored_for_dx(dx_fam, &mirrored);
-                if (rc == GIVENS_OK) rc = run_forward_sweep<T>(pb, B, mirrored, dx_fam, G, dX, 0, 1, stream);
-            }
+            ProductStorage st;
+            if (dX)
+                if (int rc = workspace_product_storage(ws, rows, B, G == dX, &st)) return rc;
+            int rc = backward_chunks<T>(ws, dev, fam.carousel, pb, rows, coefs, C, nullptr, st.matrix, dtheta, stream, 1);
+            if (rc == GIVENS_OK && dX) rc = apply_matrix(st, dev, rows, B, G, dX, stream);
             t_state.last_reduction = GIVENS_REDUCTION_GRAM;
             if (fam.column) t_state.last_kernel = GIVENS_KERNEL_COLUMN;
             else t_state.last_kernel = fam.carousel ? GIVENS_KERNEL_CAROUSEL : GIVENS_KERNEL_LDS;
@@ -862,16 +967,12 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
     if (int rc = pick_backward_family<T>(n, B, opt.kernel, &fam)) return rc;
     invalidate_prepared(*ws, false, true);
     Coefs<T> coefs;
+    const long long swept = wants_gram<T>(n, B, opt.reduction) ? rows : B;
     if (int rc = build_coefs<T>(*ws, ws->rev, pb, theta, false,
-                                form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, B)),
+                                form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept)),
                                 stream, &coefs))
         return rc;
-    auto mirrored_for_dx = [&](Families dx_fam, Coefs<T> *out) {
-        return build_coefs<T>(*ws, ws->mirrored, pb, theta, true,
-                              form_policy(dx_fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, B)),
-                              stream, out, 1);
-    };
-    return run_backward<T>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream, mirrored_for_dx);
+    return run_backward<T>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream);
 }
 
 // ---- prepared coefficients (float): givens_prepare builds the tables of one theta once, in the workspace of
@@ -903,12 +1004,17 @@ int64_t prepare_impl(int rows, int m, const float *theta, int directions, void *
         if (int rc = pick_backward_family<float>(n, 1, opt.kernel, &bfam)) return rc;
     ws->prepared = Prepared{};
     Coefs<float> c;
-    bool range_known = false, mirrored_forms = false;
+    bool range_known = false;
+    const bool wide = (directions & GIVENS_PREPARE_BACKWARD_WIDE) != 0;
     // without a hint the batch is not known here and AUTO means GIVENS_FORM_RANGE
-    const double kAnyBatch = batch_hint > 0 ? sweep_updates(n, batch_hint) : 1.0e300;
-    const FormPolicy fpol = form_policy(ffam.carousel, n, opt.form, kAnyBatch), bpol = form_policy(bfam.carousel, n, opt.form, kAnyBatch);
+    double fwd_updates = 1.0e300, rev_updates = 1.0e300;
+    if (batch_hint > 0) {
+        fwd_updates = sweep_updates(n, swept_columns<float>(ffam, rows, batch_hint));
+        rev_updates = sweep_updates(n, wide && wants_gram<float>(n, batch_hint, opt.reduction) ? rows : batch_hint);
+    }
+    const FormPolicy fpol = form_policy(ffam.carousel, n, opt.form, fwd_updates), bpol = form_policy(bfam.carousel, n, opt.form, rev_updates);
     // one range check for all the sets, into the flag word that belongs to givens_prepare
-    auto build = [&](CoefSet &set, bool forward, FormPolicy pol, int mirror) {
+    auto build = [&](CoefSet &set, bool forward, FormPolicy pol) {
         if (pol.try_forms && !range_known) {
             if (!ws->flag.ptr) {
                 if (int rc = grow(ws->flag, kFlagBytes)) return rc;
@@ -916,24 +1022,14 @@ int64_t prepare_impl(int rows, int m, const float *theta, int directions, void *
             }
             hipLaunchKernelGGL(reset_flag_kernel, dim3(1), dim3(1), 0, stream, reinterpret_cast<unsigned *>(ws->flag.ptr) + 2);
         }
-        const int rc = build_coefs<float>(*ws, set, pb, theta, forward, pol, stream, &c, mirror, range_known, true);
+        const int rc = build_coefs<float>(*ws, set, pb, theta, forward, pol, stream, &c, 0, range_known, true);
         range_known = range_known || pol.try_forms;
         return rc;
     };
     if (fwd)
-        if (int rc = build(ws->fwd, true, fpol, 0)) return rc;
+        if (int rc = build(ws->fwd, true, fpol)) return rc;
     if (rev) {
-        if (int rc = build(ws->rev, false, bpol, 0)) return rc;
-    }
-    const bool wide = (directions & GIVENS_PREPARE_BACKWARD_WIDE) != 0;
-    if (wide) {
-        // the Gram form's dX sweep (wide batches) reads forward-type tables of the mirrored problem
-        Families dx_fam;
-        dx_fam.column = bfam.column;
-        dx_fam.carousel = !bfam.column && bfam.carousel;
-        const FormPolicy mpol = form_policy(dx_fam.carousel, n, opt.form, kAnyBatch);
-        if (int rc = build(ws->mirrored, true, mpol, 1)) return rc;
-        mirrored_forms = mpol.try_forms;
+        if (int rc = build(ws->rev, false, bpol)) return rc;
     }
     Prepared &p = ws->prepared;
     p.token = ++g_next_token;
@@ -941,11 +1037,10 @@ int64_t prepare_impl(int rows, int m, const float *theta, int directions, void *
     p.m = m;
     p.fwd = fwd;
     p.rev = rev;
-    p.mirrored = wide;
+    p.wide = wide;
     p.fwd_forms = fwd && fpol.try_forms;
     p.rev_forms = rev && bpol.try_forms;
-    p.mirrored_forms = wide && mirrored_forms;
-    p.scaled_max = form_policy(true, n, opt.form, kAnyBatch).scaled_max;
+    p.scaled_max = form_policy(true, n, opt.form, 1.0e300).scaled_max;
     return p.token;
 }
 
@@ -998,7 +1093,7 @@ int forward_prepared_impl(int64_t token, long long B, const float *X, float *Y, 
     if (int rc = pick_forward_family<float>(pb.n, B, opt.kernel, &fam)) return rc;
     if (ws->prepared.fwd_forms && !fam.carousel) return GIVENS_ERR_STALE; // another family than the one prepared for
     const Coefs<float> coefs = prepared_coefs(*ws, ws->fwd, false, ws->prepared.fwd_forms, ws->prepared.scaled_max);
-    return run_forward_sweep<float>(pb, B, coefs, fam, X, Y, identity, 0, stream);
+    return run_forward<float>(ws, dev, pb, B, coefs, fam, X, Y, identity, 0, stream);
 }
 
 int backward_prepared_impl(int64_t token, long long B, const float *Y, const float *G, float *dX, float *dtheta,
@@ -1021,18 +1116,13 @@ int backward_prepared_impl(int64_t token, long long B, const float *Y, const flo
     if (int rc = pick_backward_family<float>(pb.n, B, opt.kernel, &fam)) return rc;
     const Prepared prep = ws->prepared;
     if (prep.rev_forms && !fam.carousel) return GIVENS_ERR_STALE;         // another family than the one prepared for
-    if (!prep.mirrored) {
-        // no tables for the Gram form's dX sweep: the two-stage sweep over all B columns serves any B
+    if (!prep.wide) {
+        // not prepared for the Gram form: the two-stage sweep over all B columns serves any B
         if (opt.reduction == GIVENS_REDUCTION_GRAM) return GIVENS_ERR_STALE;
         opt.reduction = GIVENS_REDUCTION_TWO_STAGE;
     }
     const Coefs<float> coefs = prepared_coefs(*ws, ws->rev, true, prep.rev_forms, prep.scaled_max);
-    auto mirrored_for_dx = [&](Families dx_fam, Coefs<float> *out) {
-        if (prep.mirrored_forms && !dx_fam.carousel) return (int)GIVENS_ERR_STALE;
-        *out = prepared_coefs(*ws, ws->mirrored, false, prep.mirrored_forms, prep.scaled_max);
-        return (int)GIVENS_OK;
-    };
-    return run_backward<float>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream, mirrored_for_dx);
+    return run_backward<float>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream);
 }
 
 // ---- unitary extension (appendix): complex operands, LDS strip kernels

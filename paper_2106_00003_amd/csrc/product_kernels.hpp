@@ -67,16 +67,15 @@ __device__ __forceinline__ f32x16 mfma_split(const u32x4 (&a)[3], const u32x4 (&
 // 16 k .. + 15 of A; lane l of a wavefront keeps row l % 32, indices 8 (l / 32) .. + 7 as 16 bytes per piece, so a
 // wavefront loads a piece of a fragment as 1 KB of consecutive memory.  Rows and indices beyond the matrix are zero.
 constexpr int kProductStep = 32;   // contraction indices per step of the product kernel (two fragments)
-inline long long product_k16(int k) { return (long long)((k + kProductStep - 1) / kProductStep) * 2; }
-inline long long product_pieces(int m, int k)   // 16-byte pieces of an m x k matrix, rows padded to 256
+constexpr long long product_k16(int k) { return (long long)((k + kProductStep - 1) / kProductStep) * 2; }
+constexpr long long product_pieces(int m, int k)   // 16-byte pieces of an m x k matrix, rows padded to 256
 {
     return (long long)((m + 255) / 256) * 8 * product_k16(k) * 3 * 64;
 }
 
-// One wavefront per fragment.  TRANS: the matrix is the transpose of the array (A[i][k] = src[k * ld + i]).
-template <bool TRANS>
-__global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const float *__restrict__ src, long long ld,
-                                                           long long frags, int k16s, u32x4 *__restrict__ out)
+// One wavefront per fragment of the m x k array src (leading dimension k).
+__global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const float *__restrict__ src, long long frags,
+                                                           int k16s, u32x4 *__restrict__ out)
 {
     const int lane = threadIdx.x & 63;
     const long long f = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -86,7 +85,7 @@ __global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const f
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         x[j] = 0.f;
-        if (row < m && k0 + j < k) x[j] = TRANS ? src[(long long)(k0 + j) * ld + row] : src[(long long)row * ld + k0 + j];
+        if (row < m && k0 + j < k) x[j] = src[(long long)row * k + k0 + j];
     }
     const Split8 s = split8(x);
     u32x4 *o = out + f * 3 * 64 + lane;
@@ -94,33 +93,44 @@ __global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const f
     o[64] = s.m;
     o[128] = s.l;
 }
-inline void split_matrix(int m, int k, const float *src, long long ld, bool trans, u32x4 *out, hipStream_t stream)
+inline void split_matrix(int m, int k, const float *src, u32x4 *out, hipStream_t stream)
 {
     const int k16s = (int)product_k16(k);
     const long long frags = (long long)((m + 255) / 256) * 8 * k16s;
-    const dim3 grid((unsigned)((frags + 3) / 4)), block(256);
-    if (trans)
-        hipLaunchKernelGGL(split_matrix_kernel<true>, grid, block, 0, stream, m, k, src, ld, frags, k16s, out);
-    else
-        hipLaunchKernelGGL(split_matrix_kernel<false>, grid, block, 0, stream, m, k, src, ld, frags, k16s, out);
+    hipLaunchKernelGGL(split_matrix_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, stream, m, k, src, frags,
+                       k16s, out);
 }
 
 struct ProductArgs {
     int m, k;             // rows of A (and D), contraction length (rows of X)
-    long long B;          // columns, and leading dimension of X and D
+    long long B;          // columns
     const u32x4 *A;       // split_matrix's output
     const float *X;
+    long long ldx;
     float *D;
+    long long ldd;
     int mblocks;          // row blocks of the launch
 };
 
-// MW x NW wavefronts of (32 MF) x (32 NF) results each.
+// D = A X.  MW x NW wavefronts of (32 MF) x (32 NF) results each.
+//
+// The fragments of A go from memory to registers, one ahead of their use: wavefronts that differ in their rows read
+// different ones, and where a workgroup's rows are all its own (NW = 1) each is read once.  X is shared: per step of 32
+// rows a thread brings octets (8 rows of one column, so that a lane's 8 values are consecutive along the contraction;
+// consecutive lanes take consecutive columns, hence whole cache lines and no alignment to care for) into registers a
+// step ahead, cuts them into pieces and writes them to the LDS buffer of the step's parity; lanes write and read 16
+// consecutive bytes, without bank conflicts.  One barrier per step.
+//
+// Bound by the matrix cores.  256 x 128 per workgroup, four wavefronts of 64 x 128 (128 accumulator registers), two
+// workgroups per compute unit: n = 2048, B = 65536 in 2.76 ms = 199 TFLOP/s of float32 product (1190 of bf16; the
+// float32 matrix instructions reach about 129), 128 x 128 3.03 ms; n = B = 4096 0.69 ms against 0.83.
 template <int MW, int NW, int MF, int NF>
 __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 {
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW;
     constexpr int OCT = BN * 4 / T;                    // octets (8 rows x 1 column of X) a thread brings per step
-    static_assert(OCT >= 1 && T % BN == 0 || BN % T == 0, "whole octets per thread");
+    constexpr int PER_ROW = T / BN;                    // octets of one column that the threads take at once
+    static_assert(OCT >= 1 && T % BN == 0 && OCT * PER_ROW == 4, "whole octets per thread");
     __shared__ u32x4 panel[2][4][3][BN];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % MW, wn = wave / MW;
@@ -131,34 +141,29 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     const long long n0 = ((long long)(local / a.mblocks) * 8 + xcd) * BN;
     if (n0 >= a.B) return;
 
-    // staging: thread t brings column t % BN, octets t / BN + i * (T / BN)   (or columns t + T i when BN > T)
-    constexpr int ROWS_PER = T >= BN ? T / BN : 1;
+    // thread t brings column t % BN, octets t / BN + PER_ROW * i of a step (BN is a multiple of the wavefront's 64
+    // columns: the octet is the same for all lanes)
+    const int my_col = (int)threadIdx.x % BN, my_oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BN);
+    const long long col_in = n0 + my_col < a.B ? n0 + my_col : a.B - 1;  // past the end: its results are not stored
     float xr[OCT][8];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < OCT; ++i) {
-            const int c = T >= BN ? (int)threadIdx.x % BN : (int)threadIdx.x + T * (i % (BN / T > 0 ? BN / T : 1));
-            const int o = T >= BN ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / BN) + ROWS_PER * i
-                                  : i / (BN / T > 0 ? BN / T : 1);
-            long long col = n0 + c;
-            col = col < a.B ? col : a.B - 1;           // past the last column: any column, its results are not stored
+        for (int i = 0; i < OCT; ++i)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                int r = k0 + 8 * o + j;
+                int r = k0 + 8 * (my_oct + PER_ROW * i) + j;
                 r = r < a.k ? r : a.k - 1;             // past the last row: A is zero there
-                xr[i][j] = (a.X + (long long)r * a.B)[col];
+                xr[i][j] = (a.X + (long long)r * a.ldx)[col_in];
             }
-        }
     };
     auto stash = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < OCT; ++i) {
-            const int c = T >= BN ? (int)threadIdx.x % BN : (int)threadIdx.x + T * (i % (BN / T > 0 ? BN / T : 1));
-            const int o = T >= BN ? (int)threadIdx.x / BN + ROWS_PER * i : i / (BN / T > 0 ? BN / T : 1);
             const Split8 s = split8(xr[i]);
-            panel[buf][o][0][c] = s.h;
-            panel[buf][o][1][c] = s.m;
-            panel[buf][o][2][c] = s.l;
+            const int o = my_oct + PER_ROW * i;
+            panel[buf][o][0][my_col] = s.h;
+            panel[buf][o][1][my_col] = s.m;
+            panel[buf][o][2][my_col] = s.l;
         }
     };
 
@@ -215,7 +220,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = mb * BM + wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row < a.m) a.D[(long long)row * a.B + col] = acc[i][j][v];
+                if (row < a.m) a.D[(long long)row * a.ldd + col] = acc[i][j][v];
             }
     }
 }
@@ -228,6 +233,29 @@ inline void launch_product(ProductArgs a, hipStream_t stream)
     const long long nblocks = (a.B + BN - 1) / BN;
     const unsigned grid = (unsigned)((nblocks + 7) / 8 * 8 * a.mblocks);
     hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+}
+
+// The largest tile that still gives every compute unit a workgroup and a half, and for few rows one no taller than they
+// are.
+inline void product(const ProductArgs &a, int compute_units, hipStream_t stream)
+{
+    auto groups = [&](int bm, int bn) { return ((a.m + bm - 1) / bm) * ((a.B + bn - 1) / bn); };
+    const long long enough = 3LL * compute_units / 2;
+    if (a.m > 128 && groups(256, 128) >= enough)
+        launch_product<4, 1, 2, 4>(a, stream);
+    else if (a.m > 64 && groups(128, 128) >= enough)
+        launch_product<2, 2, 2, 2>(a, stream);
+    else
+        launch_product<2, 2, 1, 1>(a, stream);
+}
+
+// dst <- src, `cols` columns of each row (an operand that is its own result is multiplied from a copy)
+__global__ void copy_columns_kernel(int rows, long long cols, const float *__restrict__ src, long long lds,
+                                    float *__restrict__ dst, long long ldd)
+{
+    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= cols) return;
+    for (int r = blockIdx.y; r < rows; r += gridDim.y) dst[(long long)r * ldd + c] = src[(long long)r * lds + c];
 }
 
 } // namespace givens

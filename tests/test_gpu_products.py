@@ -40,3 +40,55 @@ def test_gram_contraction_at_the_edges_of_its_tiles(n, B):
     assert rel(dx, want_dx) <= TOL_G and rel(dth, want_dth) <= TOL_G
     again = binding.givens_backward_ex(th, y, g, reduction=binding.REDUCTION_GRAM)[1]
     assert torch.equal(again, dth)
+
+
+# applications through U: below and above the batch where they begin, one column past a tile, one row past and short of
+# the tiles of 64, 128 and 256 rows, both directions, odd sizes, results over their operands, no allocation
+@pytest.mark.parametrize("n,B", [(132, 2048), (192, 2049), (254, 2111), (256, 16385), (258, 40001), (302, 2050),
+                                 (514, 33000), (1024, 2048), (1026, 12345)])
+def test_wide_batches_go_through_u(n, B):
+    data = inputs.make_custom(n, B, seed=1400 + n)
+    print(f"[products] wide n={n} B={B}", flush=True)
+    th, x = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X"))
+    want = binding.givens_forward(th.double(), x.double())
+    y = binding.givens_forward(th, x)
+    assert rel(y, want) <= TOL_Y
+    assert rel(y[:, -3:], want[:, -3:]) <= TOL_Y
+    back = binding.givens_forward_transposed(th, y)
+    assert rel(back, x.double()) <= 3 * TOL_Y
+    buf = x.clone()
+    binding.givens_forward(th, buf, Y=buf)
+    assert torch.equal(buf, y)
+    if n <= binding.NOALLOC_MAX_N:
+        other = torch.full_like(x, float("nan"))
+        assert torch.equal(binding.givens_forward_noalloc(th, x, other), y)
+        buf.copy_(x)
+        assert torch.equal(binding.givens_forward_noalloc(th, buf, buf), y)
+    token = binding.givens_prepare(th, n, directions=binding.PREPARE_FORWARD)
+    assert torch.equal(binding.givens_forward_prepared(token, x), y)
+
+
+def test_wide_restricted_batch_with_an_odd_number_of_rows():
+    n, m, B = 257, 40, 4099
+    data = inputs.make_restricted(n, m, B, seed=1500)
+    th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    y = binding.givens_forward_restricted(th, x, m)
+    dx, dth = binding.givens_backward_restricted(th, y, g, m)
+    want_y = binding.givens_forward_restricted(th.double(), x.double(), m)
+    want_dx, want_dth = binding.givens_backward_restricted(th.double(), want_y, g.double(), m)
+    assert rel(y, want_y) <= TOL_Y and rel(dx, want_dx) <= TOL_G and rel(dth, want_dth) <= TOL_G
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30, 3.4e38])
+def test_products_keep_the_range_of_float32(scale):
+    """Operands near the ends of the exponent range: the leading piece may not overflow, the trailing ones may vanish
+    only where float32 itself has no bits left.  A column of U has norm 1, so results are of the operand's size."""
+    n, B = 256, 4096
+    data = inputs.make_custom(n, B, seed=1600)
+    th = torch.from_numpy(data["theta"]).cuda()
+    x = torch.zeros(n, B, device="cuda")
+    rows = torch.arange(B, device="cuda") % n
+    x[rows, torch.arange(B, device="cuda")] = scale
+    y = binding.givens_forward(th, x)
+    want = binding.givens_forward(th.double(), x.double())
+    assert torch.isfinite(y).all() and rel(y, want) <= TOL_Y
