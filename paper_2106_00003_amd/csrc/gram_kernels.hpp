@@ -17,7 +17,8 @@
 // of float32 product, 1190 of bf16 (with the float32 matrix instructions the same contraction took 4.25 ms,
 // 129 TFLOP/s); 256 x 256 with eight wavefronts 2.87 ms, 128 x 128 3.13 ms.  Few rows give too few tiles of that
 // size, and B is then cut into more slices of 64 x 64 tiles: n = 64, B = 65536 in 10 us (256 slices), where the
-// 128 x 128 tile takes 36.
+// 128 x 128 tile takes 36.  Rows of any length and alignment take the same 16-byte loads: n = 1002, B = 65536 in 0.76 ms
+// = 172 TFLOP/s (1.76 ms with element-by-element loads), B = 3001 in 71 us (166).
 //
 // Split-K: B is cut into slices, each slice writes its own rows x rows matrix and sum_slices_kernel adds them in slice
 // order, so the result does not depend on scheduling.
@@ -29,6 +30,7 @@
 namespace givens {
 
 constexpr int kGramK = 16;       // contraction columns per step
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 struct GramArgs {
     int rows;
@@ -38,9 +40,9 @@ struct GramArgs {
     int tiles_m, tiles_n;
 };
 
-// MW x NW wavefronts of (32 MF) x (32 NF) results each.  GUARD: rows beyond `rows` and columns beyond the slice read as
-// zero, element by element; without it every octet is two unconditional 16-byte loads (the launch has checked that
-// tiles and slices are full and rows 16-byte aligned).
+// MW x NW wavefronts of (32 MF) x (32 NF) results each.  GUARD: the tiles or the last
+// slice are not full; rows past the end repeat the last one, and only the step that reaches past the slice's end goes
+// element by element.
 template <int MW, int NW, int MF, int NF, bool GUARD>
 __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
 {
@@ -71,22 +73,21 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
             int r = of_y ? tile_i * BM + pr : tile_j * BN + (pr - BM);
             const float *src = of_y ? a.Y : a.G;
             const long long k = k0 + 8 * (c & 1);
-            if constexpr (!GUARD) {
-                const f32x4 *p = reinterpret_cast<const f32x4 *>(src + (long long)r * a.B + k);
-                const f32x4 u = p[0], w = p[1];
+            if constexpr (GUARD) r = r < a.rows ? r : a.rows - 1;    // (its results are not stored)
+            const float *p = src + (long long)r * a.B + k;
+            if (!GUARD || k0 + kGramK <= kend) {
+                // (a row may start at any multiple of four bytes: the loads take that)
+                const f32x4_any u = *reinterpret_cast<const f32x4_any *>(p), w = *reinterpret_cast<const f32x4_any *>(p + 4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     xr[i][j] = u[j];
                     xr[i][4 + j] = w[j];
                 }
             } else {
-                const bool live = r < a.rows;
-                r = live ? r : a.rows - 1;
-                const float *p = src + (long long)r * a.B;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const float v = p[k + j < kend ? k + j : kend - 1];
-                    xr[i][j] = (live && k + j < kend) ? v : 0.f;
+                    const float v = k + j < kend ? p[j] : src[(long long)r * a.B];
+                    xr[i][j] = k + j < kend ? v : 0.f;
                 }
             }
         }
@@ -102,13 +103,15 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
         }
     };
 
-    f32x16 acc[MF][NF];
+    // results in IB groups of rows, a group's operands at a time in registers
+    constexpr int IB = MF == 4 ? 2 : 1;
+    f32x16 acc[IB][MF / IB][NF];
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int j = 0; j < NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[i / (MF / IB)][i % (MF / IB)][j][v] = 0.f;
 
     if (kbeg < kend) {
         fetch(kbeg);
@@ -125,12 +128,14 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
 #pragma unroll
             for (int p = 0; p < 3; ++p) fb[j][p] = panel[buf][p][lane >> 5][BM + wn * 32 * NF + 32 * j + (lane & 31)];
 #pragma unroll
-        for (int i = 0; i < MF; ++i) {
-            u32x4 fa[3];
+        for (int i = 0; i < IB; ++i) {
+            u32x4 fa[MF / IB][3];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) fa[p] = panel[buf][p][lane >> 5][wm * 32 * MF + 32 * i + (lane & 31)];
+            for (int q = 0; q < MF / IB; ++q)
 #pragma unroll
-            for (int j = 0; j < NF; ++j) acc[i][j] = mfma_split(fa, fb[j], acc[i][j]);
+                for (int p = 0; p < 3; ++p)
+                    fa[q][p] = panel[buf][p][lane >> 5][wm * 32 * MF + 32 * (i * (MF / IB) + q) + (lane & 31)];
+            mfma_split(fa, fb, acc[i]);
         }
         if (more) stash(buf ^ 1);
     }
@@ -146,7 +151,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = tile_i * BM + wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row < a.rows && col < a.rows) out[(long long)row * a.rows + col] = acc[i][j][v];
+                if (row < a.rows && col < a.rows) out[(long long)row * a.rows + col] = acc[i / (MF / IB)][i % (MF / IB)][j][v];
             }
     }
 }
@@ -205,8 +210,7 @@ inline void launch_gram(GramArgs a, int slices, hipStream_t stream)
     constexpr int BM = 32 * MF * MW, BN = 32 * NF * NW;
     a.tiles_m = (a.rows + BM - 1) / BM;
     a.tiles_n = (a.rows + BN - 1) / BN;
-    const bool full = a.B % kGramK == 0 && a.rows % BM == 0 && a.rows % BN == 0 &&
-                      reinterpret_cast<uintptr_t>(a.Y) % 16 == 0 && reinterpret_cast<uintptr_t>(a.G) % 16 == 0;
+    const bool full = a.B % kGramK == 0 && a.rows % BM == 0 && a.rows % BN == 0;
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n * slices)), block(64 * MW * NW);
     if (full)
         hipLaunchKernelGGL((gram_tile_kernel<MW, NW, MF, NF, false>), grid, block, 0, stream, a);

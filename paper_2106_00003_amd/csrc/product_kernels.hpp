@@ -1,67 +1,13 @@
 // Dense products on the matrix cores in float32 precision: D = A X for a matrix A that many columns share (U itself,
 // or U^T) and a row-major operand X of B columns.
-//
-// Precision.  The fastest matrix instructions of the chip take bf16 operands; a float32 value is exactly the sum of
-// three bf16 values (8 + 8 + 8 significand bits: x = h + m + l, h = x cut to bf16, m = x - h rounded to bf16,
-// l = x - h - m, which fits).  A product of two float32 values is therefore the sum of nine exact bf16 products, of
-// which the six largest are formed (hh, hm, mh, hl, lh, mm); what is left out (ml, lm, ll) is below 2^-24 of the
-// product.  Sums are float32, sixteen products at a time.  So operands keep their 24 bits and the accumulation its
-// float32, and six bf16 instructions of 16-deep contraction still take 1/2.7 of the time of the eight float32 ones
-// (2-deep) they replace.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "split_bf16.hpp"
+
 namespace givens {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// Eight float32 values as three rows of eight bf16 values with h + m + l == x (exact for every finite x whose last
-// bits are normal numbers).
-struct Split8 {
-    u32x4 h, m, l;
-};
-__device__ __forceinline__ unsigned pack_bf16(float a, float b)
-{
-    const bf16x2 v = __builtin_convertvector((f32x2){a, b}, bf16x2);   // round to nearest even
-    return __builtin_bit_cast(unsigned, v);
-}
-__device__ __forceinline__ Split8 split8(const float (&x)[8])
-{
-    Split8 s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const unsigned a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
-        // the leading piece is cut, not rounded: it cannot overflow, whatever x is
-        s.h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-        const float ra = x[2 * i] - __uint_as_float(a & 0xffff0000u), rb = x[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
-        const unsigned m = pack_bf16(ra, rb);
-        s.m[i] = m;
-        s.l[i] = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
-    }
-    return s;
-}
-
-// acc += a b over 16 contraction indices, float32 operands given as their pieces, smallest products first
-__device__ __forceinline__ f32x16 mfma_split(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16 acc)
-{
-    auto mm = [](u32x4 x, u32x4 y, f32x16 c) {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0,
-                                                       0, 0);
-    };
-    acc = mm(a[2], b[0], acc);
-    acc = mm(a[0], b[2], acc);
-    acc = mm(a[1], b[1], acc);
-    acc = mm(a[1], b[0], acc);
-    acc = mm(a[0], b[1], acc);
-    return mm(a[0], b[0], acc);
-}
 
 // ---- the shared matrix in operand order.  Fragment (i, k) holds rows 32 i .. + 31 and contraction indices
 // 16 k .. + 15 of A; lane l of a wavefront keeps row l % 32, indices 8 (l / 32) .. + 7 as 16 bytes per piece, so a
@@ -180,13 +126,15 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
             for (int p = 0; p < 3; ++p) fa[set][i][p] = ap[i][(long long)k16 * 192 + 64 * p];
     };
 
-    f32x16 acc[MF][NF];
+    // results in JB groups of columns, a group's operands at a time in registers
+    constexpr int JB = NF == 4 ? 2 : 1;
+    f32x16 acc[JB][MF][NF / JB];
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int j = 0; j < NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[j / (NF / JB)][i][j % (NF / JB)][v] = 0.f;
 
     fetch(0);
     load_a(0, 0);
@@ -200,12 +148,14 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
             const int next = 2 * step + ks + 1;
             load_a(ks ^ 1, next < k16s ? next : k16s - 1);
 #pragma unroll
-            for (int j = 0; j < NF; ++j) {
-                u32x4 fb[3];
+            for (int j = 0; j < JB; ++j) {
+                u32x4 fb[NF / JB][3];
 #pragma unroll
-                for (int p = 0; p < 3; ++p) fb[p] = panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * j + (lane & 31)];
+                for (int q = 0; q < NF / JB; ++q)
 #pragma unroll
-                for (int i = 0; i < MF; ++i) acc[i][j] = mfma_split(fa[ks][i], fb, acc[i][j]);
+                    for (int p = 0; p < 3; ++p)
+                        fb[q][p] = panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * (j * (NF / JB) + q) + (lane & 31)];
+                mfma_split(fa[ks], fb, acc[j]);
             }
         }
         if (step + 1 < steps) stash(buf ^ 1);
@@ -220,7 +170,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = mb * BM + wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row < a.m) a.D[(long long)row * a.ldd + col] = acc[i][j][v];
+                if (row < a.m) a.D[(long long)row * a.ldd + col] = acc[j / (NF / JB)][i][j % (NF / JB)][v];
             }
     }
 }

@@ -1,0 +1,67 @@
+// Float32 products on the bf16 matrix cores.
+//
+// Precision.  The fastest matrix instructions of the chip take bf16 operands; a float32 value is exactly the sum of
+// three bf16 values (8 + 8 + 8 significand bits: x = h + m + l, h = x cut to bf16, m = x - h rounded to bf16,
+// l = x - h - m, which fits).  A product of two float32 values is therefore the sum of nine exact bf16 products, of
+// which the six largest are formed (hh, hm, mh, hl, lh, mm); what is left out (ml, lm, ll) is below 2^-24 of the
+// product.  Sums are float32, sixteen products at a time.  So operands keep their 24 bits and the accumulation its
+// float32, and six bf16 instructions of 16-deep contraction still take 1/2.7 of the time of the eight float32 ones
+// (2-deep) they replace.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace givens {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Eight float32 values as three rows of eight bf16 values with h + m + l == x (exact for every finite x whose last
+// bits are normal numbers).
+struct Split8 {
+    u32x4 h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)
+{
+    const bf16x2 v = __builtin_convertvector((f32x2){a, b}, bf16x2);   // round to nearest even
+    return __builtin_bit_cast(unsigned, v);
+}
+__device__ __forceinline__ Split8 split8(const float (&x)[8])
+{
+    Split8 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const unsigned a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
+        // the leading piece is cut, not rounded: it cannot overflow, whatever x is
+        s.h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+        const float ra = x[2 * i] - __uint_as_float(a & 0xffff0000u), rb = x[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
+        const unsigned m = pack_bf16(ra, rb);
+        s.m[i] = m;
+        s.l[i] = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+    }
+    return s;
+}
+
+// acc[i][j] += a[i] b[j] over 16 contraction indices, float32 operands given as their pieces, smallest products first.
+// Each of the six instructions of a result needs the one before it, so the results take turns: back to back on one
+// accumulator the matrix cores wait.
+template <int NA, int NB>
+__device__ __forceinline__ void mfma_split(const u32x4 (&a)[NA][3], const u32x4 (&b)[NB][3], f32x16 (&acc)[NA][NB])
+{
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int p = 0; p < 6; ++p)
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][pa[p]]),
+                                                                    __builtin_bit_cast(bf16x8, b[j][pb[p]]), acc[i][j], 0, 0, 0);
+}
+
+} // namespace givens

@@ -42,6 +42,19 @@ def test_gram_contraction_at_the_edges_of_its_tiles(n, B):
     assert torch.equal(again, dth)
 
 
+# operands that start at an odd multiple of four bytes, row lengths of every remainder: both tile sizes
+@pytest.mark.parametrize("n,B", [(66, 4097), (66, 4098), (514, 4099), (512, 4096)])
+def test_gram_contraction_of_unaligned_operands(n, B):
+    data = inputs.make_custom(n, B, seed=1350 + n)
+    th, y, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    shifted = [torch.empty(n * B + 1, device="cuda")[1:].view(n, B).copy_(t) for t in (y, g)]
+    _, want = binding.givens_backward_ex(th, y, g, reduction=binding.REDUCTION_GRAM)
+    _, got = binding.givens_backward_ex(th, *shifted, reduction=binding.REDUCTION_GRAM)
+    assert torch.equal(got, want)
+    _, want = binding.givens_backward(th.double(), y.double(), g.double())
+    assert rel(got, want) <= TOL_G
+
+
 # applications through U: below and above the batch where they begin, one column past a tile, one row past and short of
 # the tiles of 64, 128 and 256 rows, both directions, odd sizes, results over their operands, no allocation
 @pytest.mark.parametrize("n,B", [(132, 2048), (192, 2049), (254, 2111), (256, 16385), (258, 40001), (302, 2050),
