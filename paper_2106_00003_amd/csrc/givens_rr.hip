@@ -30,6 +30,8 @@ constexpr size_t kPartialCapBytes = size_t(24) << 30;          // cap on one chu
 constexpr int kMaxRows = 36864;                                // largest n any kernel family takes (one float column in LDS)
 constexpr size_t kColumnsCapBytes = size_t(128) << 20;         // copied columns of an operand that its product overwrites
 constexpr long long kProductMinRatio = 2, kProductMinB = 2048; // batches whose application goes through U (wants_product)
+constexpr long long kUnitaryMinRatio = 4;                      // the same for complex operands (unitary_wants_product)
+constexpr long long kUnitaryMinForward = 4096, kUnitaryMinBackward = 1024;
 constexpr size_t kFlagBytes = 256;                             // the flag words of a workspace
 
 struct Buffer {
@@ -417,15 +419,16 @@ struct ProductStorage {
     float *copy = nullptr;
     long long copy_cols = 0;
 };
-int workspace_product_storage(Workspace &ws, int rows, long long B, bool in_place, ProductStorage *out)
+int workspace_product_storage(Workspace &ws, int rows, long long B, bool in_place, ProductStorage *out, bool cplx = false)
 {
-    if (int rc = grow(ws.matrix, (size_t)rows * rows * sizeof(float))) return rc;
-    if (int rc = grow(ws.pieces, (size_t)product_pieces(rows, rows) * sizeof(u32x4))) return rc;
+    const int k = cplx ? 2 * rows : rows;
+    if (int rc = grow(ws.matrix, (size_t)rows * k * sizeof(float))) return rc;
+    if (int rc = grow(ws.pieces, (size_t)product_pieces(rows, k) * sizeof(u32x4))) return rc;
     out->matrix = reinterpret_cast<float *>(ws.matrix.ptr);
     out->pieces = reinterpret_cast<u32x4 *>(ws.pieces.ptr);
     if (in_place) {
         out->copy_cols = std::max<long long>(512, (long long)(kColumnsCapBytes / sizeof(float)) / rows);
-        out->copy_cols = std::min(out->copy_cols, B);
+        out->copy_cols = std::min(out->copy_cols / 2 * 2, B);   // (whole complex numbers)
         if (int rc = grow(ws.columns, (size_t)out->copy_cols * rows * sizeof(float))) return rc;
         out->copy = reinterpret_cast<float *>(ws.columns.ptr);
     }
@@ -651,17 +654,19 @@ long long swept_columns(const Families &fam, int rows, long long B)
     return wants_product<T>(fam, rows, B) ? rows : B;
 }
 
-// Y = A X for the rows x rows matrix A = st.matrix; Y may be X.
-int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const float *X, float *Y, hipStream_t stream)
+// Y = A X for the rows x rows matrix A = st.matrix; Y may be X.  cplx: complex operands, B real columns.
+int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const float *X, float *Y, hipStream_t stream,
+                 bool cplx = false)
 {
+    const int k = cplx ? 2 * rows : rows;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     Span span(1, stream);
-    split_matrix(rows, rows, st.matrix, st.pieces, stream);
+    split_matrix(rows, k, st.matrix, st.pieces, stream, cplx);
     const long long chunk = X == Y ? st.copy_cols : B;   // a result that overwrites its operand: from copies
     for (long long c0 = 0; c0 < B; c0 += chunk) {
         const long long cols = std::min(chunk, B - c0);
-        ProductArgs a{rows, rows, cols, st.pieces, X + c0, B, Y + c0, B, 0};
+        ProductArgs a{rows, k, cols, st.pieces, X + c0, B, Y + c0, B, 0, cplx};
         if (X == Y) {
             hipLaunchKernelGGL(copy_columns_kernel, dim3((unsigned)((cols + 255) / 256), (unsigned)std::min(rows, 256)),
                                dim3(256), 0, stream, rows, cols, X + c0, B, st.copy, cols);
@@ -1223,11 +1228,12 @@ int unitary_carousel_backward(Workspace &ws, int dev, int n, long long B, const 
     // Shape.  Two slots per lane with strips of 8 floats (four complex numbers) where n <= 2048 and the batch is
     // wide enough to keep the chip busy: half the rows of partial sums of the alternative, four slots per lane
     // with strips of 4 floats (or 2 for narrow batches), which a lane's registers limit to that width.
-    // (measured at n = 2048, B = 2048: sweep 8.6 -> 5.2 ms, second stage 1.9 -> 1.0 ms.)
+    // (measured at n = 2048, B = 2048: sweep 8.6 -> 5.2 ms, second stage 1.9 -> 1.0 ms; strips of 4 from 256 wavefronts
+    // on: n = B = 512 565 -> 452 us with half the rows of partial sums.)
     const bool two_slots = n <= 2048 && ((Breal + 7) / 8) * ((n / 4 + 63) / 64) >= 512;
     const int M = two_slots ? 2 : 4;
     const int waves = (n / (2 * M) + 63) / 64;
-    const int W = M == 2 ? 8 : ((((Breal + 3) / 4) * waves >= 512) ? 4 : 2);
+    const int W = M == 2 ? 8 : ((((Breal + 3) / 4) * waves >= 256) ? 4 : 2);
     const long long strips = (Breal + W - 1) / W;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1272,32 +1278,37 @@ int unitary_carousel_backward(Workspace &ws, int dev, int n, long long B, const 
     return GIVENS_OK;
 }
 
+// Wide batches (complex64).  As for real operands (wants_product, wants_gram): the forward call builds U by the sweep over
+// its n columns and multiplies; the backward call contracts C = Y G^H once and runs the reverse sweep on (C, I), whose
+// second strip ends as U^H, with which dX is one product.  Measured, sweep against product in us: forward n = 64, B = 2048
+// 36 / 39, 65536 283 / 57; n = 512, B = 2048 285 / 277, 8192 555 / 332; n = 1024, B = 2048 667 / 800, 4096 1023 / 870;
+// n = 2048, B = 8192 6223 / 3601.  Backward n = 64, B = 1024 182 / 70; n = 256, B = 1024 298 / 226; n = 512, B = 1024
+// 510 / 577, 2048 653 / 561; n = 1024, B = 4096 2800 / 1633; n = 2048, B = 8192 22174 / 8992.
 template <typename T>
-int unitary_forward_impl(int n, long long B, const T *theta, const T *phi, const T *X, T *Y, int identity,
-                         void *stream_v)
+bool unitary_wants_product(int n, long long B, long long min_b)
+{
+    return std::is_same<T, float>::value && B >= kUnitaryMinRatio * n && B >= min_b;
+}
+
+__global__ void complex_identity_kernel(int n, float2 *__restrict__ out)
+{
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    for (int r = blockIdx.y; r < n; r += gridDim.y) out[(long long)r * n + c] = make_float2(r == c ? 1.f : 0.f, 0.f);
+}
+
+// The sweep over B columns with the family that takes n, Y = U X.
+template <typename T>
+int unitary_forward_sweep(Workspace &ws, int n, long long B, const T *theta, const T *phi, const T *X, T *Y, int identity,
+                          hipStream_t stream)
 {
     using C = typename Cplx<T>::type;
-    if (int rc = check_n(n)) return rc;
-    if (B < 1) return GIVENS_ERR_BAD_B;
-    if (!theta || !phi || !Y || (!identity && !X)) return GIVENS_ERR_NULL;
-    hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
-    std::lock_guard<std::mutex> lock(g_mutex);
-    int dev = 0;
-    if (int rc = current_device(&dev)) return rc;
-    timing_begin_call();
-    Workspace *ws = nullptr;
-    if constexpr (std::is_same<T, float>::value) {
-        if (unitary_wants_carousel(n, g_kernel_choice)) {
-            if (int rc = workspace_for(dev, stream, &ws)) return rc;
-            return unitary_carousel_forward(*ws, n, B, theta, phi, X, Y, identity, stream);
-        }
-    }
-    if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+    if constexpr (std::is_same<T, float>::value)
+        if (unitary_wants_carousel(n, g_kernel_choice))
+            return unitary_carousel_forward(ws, n, B, theta, phi, X, Y, identity, stream);
     const int w = unitary_strip_width<T>(n, B, 1);
-    if (w == 0) return GIVENS_ERR_UNSUPPORTED;
     const typename Cplx<T>::quad *table = nullptr;
-    if (int rc = workspace_for(dev, stream, &ws)) return rc;
-    if (int rc = unitary_table<T>(*ws, n, theta, phi, stream, &table)) return rc;
+    if (int rc = unitary_table<T>(ws, n, theta, phi, stream, &table)) return rc;
     const size_t smem = (size_t)n * w * sizeof(C);
     auto kern = lds_wants_ahead(n) ? unitary_forward_kernel<T, kUnitaryAhead> : unitary_forward_kernel<T, 0>;
     GIVENS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -1311,32 +1322,46 @@ int unitary_forward_impl(int n, long long B, const T *theta, const T *phi, const
 }
 
 template <typename T>
-int unitary_backward_impl(int n, long long B, const T *theta, const T *phi, const T *Y, const T *G, T *dX,
-                          T *dtheta, T *dphi, void *stream_v)
+int unitary_forward_impl(int n, long long B, const T *theta, const T *phi, const T *X, T *Y, int identity,
+                         void *stream_v)
 {
-    using C = typename Cplx<T>::type;
     if (int rc = check_n(n)) return rc;
     if (B < 1) return GIVENS_ERR_BAD_B;
-    if (!theta || !phi || !Y || !G || !dtheta || !dphi) return GIVENS_ERR_NULL;
-    if (dX && (const void *)dX == (const void *)Y) return GIVENS_ERR_ALIAS;
+    if (!theta || !phi || !Y || (!identity && !X)) return GIVENS_ERR_NULL;
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
     std::lock_guard<std::mutex> lock(g_mutex);
     int dev = 0;
     if (int rc = current_device(&dev)) return rc;
     timing_begin_call();
-    Workspace *wsp = nullptr;
+    const bool carousel = std::is_same<T, float>::value && unitary_wants_carousel(n, g_kernel_choice);
+    if (!carousel) {
+        if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+        if (unitary_strip_width<T>(n, B, 1) == 0) return GIVENS_ERR_UNSUPPORTED;
+    }
+    Workspace *ws = nullptr;
+    if (int rc = workspace_for(dev, stream, &ws)) return rc;
     if constexpr (std::is_same<T, float>::value) {
-        if (unitary_wants_carousel(n, g_kernel_choice)) {
-            if (int rc = workspace_for(dev, stream, &wsp)) return rc;
-            return unitary_carousel_backward(*wsp, dev, n, B, theta, phi, Y, G, dX, dtheta, dphi, stream);
+        if (!identity && unitary_wants_product<T>(n, B, kUnitaryMinForward)) {
+            ProductStorage st;
+            if (int rc = workspace_product_storage(*ws, n, 2 * B, X == Y, &st, true)) return rc;
+            if (int rc = unitary_forward_sweep<T>(*ws, n, n, theta, phi, nullptr, st.matrix, 1, stream)) return rc;
+            return apply_matrix(st, dev, n, 2 * B, X, Y, stream, true);
         }
     }
-    if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+    return unitary_forward_sweep<T>(*ws, n, B, theta, phi, X, Y, identity, stream);
+}
+
+// The reverse sweep over B columns with the family that takes n.
+template <typename T>
+int unitary_backward_sweep(Workspace &ws, int dev, int n, long long B, const T *theta, const T *phi, const T *Y, const T *G,
+                           T *dX, T *dtheta, T *dphi, hipStream_t stream)
+{
+    using C = typename Cplx<T>::type;
+    if constexpr (std::is_same<T, float>::value)
+        if (unitary_wants_carousel(n, g_kernel_choice))
+            return unitary_carousel_backward(ws, dev, n, B, theta, phi, Y, G, dX, dtheta, dphi, stream);
     const int w = unitary_strip_width<T>(n, B, 2);
-    if (w == 0) return GIVENS_ERR_UNSUPPORTED;
     const typename Cplx<T>::quad *table = nullptr;
-    if (int rc = workspace_for(dev, stream, &wsp)) return rc;
-    Workspace &ws = *wsp;
     if (int rc = unitary_table<T>(ws, n, theta, phi, stream, &table)) return rc;
     const long long N = (long long)n * (n - 1) / 2;
     const long long strips = (B + w - 1) / w;
@@ -1373,6 +1398,54 @@ int unitary_backward_impl(int n, long long B, const T *theta, const T *phi, cons
     t_state.last_chains = 0;
     t_state.last_flag = nullptr;
     return GIVENS_OK;
+}
+
+template <typename T>
+int unitary_backward_impl(int n, long long B, const T *theta, const T *phi, const T *Y, const T *G, T *dX,
+                          T *dtheta, T *dphi, void *stream_v)
+{
+    if (int rc = check_n(n)) return rc;
+    if (B < 1) return GIVENS_ERR_BAD_B;
+    if (!theta || !phi || !Y || !G || !dtheta || !dphi) return GIVENS_ERR_NULL;
+    if (dX && (const void *)dX == (const void *)Y) return GIVENS_ERR_ALIAS;
+    hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    int dev = 0;
+    if (int rc = current_device(&dev)) return rc;
+    timing_begin_call();
+    const bool carousel = std::is_same<T, float>::value && unitary_wants_carousel(n, g_kernel_choice);
+    if (!carousel) {
+        if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+        if (unitary_strip_width<T>(n, B, 2) == 0) return GIVENS_ERR_UNSUPPORTED;
+    }
+    Workspace *ws = nullptr;
+    if (int rc = workspace_for(dev, stream, &ws)) return rc;
+    if constexpr (std::is_same<T, float>::value) {
+        const bool chosen = g_reduction_choice == GIVENS_REDUCTION_AUTO;
+        if (chosen && unitary_wants_product<T>(n, B, kUnitaryMinBackward)) {
+            int cus = 0;
+            GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+            const GramPlan plan = gram_plan(n, 2 * B, cus, true);
+            if (int rc = grow(ws->gram, (size_t)plan.slices * n * 2 * n * sizeof(float))) return rc;
+            ProductStorage st;
+            if (int rc = workspace_product_storage(*ws, n, 2 * B, dX && G == dX, &st, true)) return rc;
+            float *C = reinterpret_cast<float *>(ws->gram.ptr);
+            {
+                Span span(3, stream);
+                gram_matrix<true>(n, 2 * B, plan, Y, G, C, stream);
+                hipLaunchKernelGGL(complex_identity_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)std::min(n, 1024)),
+                                   dim3(256), 0, stream, n, reinterpret_cast<float2 *>(st.matrix));
+                GIVENS_HIP(hipGetLastError());
+            }
+            // (the sweep brings each strip in before it writes the strip's result over it)
+            if (int rc = unitary_backward_sweep<T>(*ws, dev, n, n, theta, phi, C, st.matrix, dX ? st.matrix : nullptr, dtheta,
+                                                   dphi, stream))
+                return rc;
+            t_state.last_reduction = GIVENS_REDUCTION_GRAM;
+            return dX ? apply_matrix(st, dev, n, 2 * B, G, dX, stream, true) : GIVENS_OK;
+        }
+    }
+    return unitary_backward_sweep<T>(*ws, dev, n, B, theta, phi, Y, G, dX, dtheta, dphi, stream);
 }
 
 } // namespace

@@ -20,6 +20,10 @@
 // 128 x 128 tile takes 36.  Rows of any length and alignment take the same 16-byte loads: n = 1002, B = 65536 in 0.76 ms
 // = 172 TFLOP/s (1.76 ms with element-by-element loads), B = 3001 in 71 us (166).
 //
+// Complex operands (interleaved): C = Y G^H has the real parts Y G^T and the imaginary parts Y (i G)^T of the real
+// rows x 2B arrays, where i G swaps the two columns of a complex number and negates the first: one contraction with
+// 2 rows result columns.
+//
 // Split-K: B is cut into slices, each slice writes its own rows x rows matrix and sum_slices_kernel adds them in slice
 // order, so the result does not depend on scheduling.
 #pragma once
@@ -36,14 +40,15 @@ struct GramArgs {
     int rows;
     long long B, slice_cols;
     const float *Y, *G;
-    float *C;                    // [slices][rows][rows]
+    float *C;                    // [slices][rows][cols]
     int tiles_m, tiles_n;
+    int cols;                    // rows, or for complex operands (B counts real columns) 2 rows
 };
 
 // MW x NW wavefronts of (32 MF) x (32 NF) results each.  GUARD: the tiles or the last
 // slice are not full; rows past the end repeat the last one, and only the step that reaches past the slice's end goes
 // element by element.
-template <int MW, int NW, int MF, int NF, bool GUARD>
+template <int MW, int NW, int MF, int NF, bool GUARD, bool CPLX>
 __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
 {
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW, BOTH = BM + BN;
@@ -73,7 +78,12 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
             int r = of_y ? tile_i * BM + pr : tile_j * BN + (pr - BM);
             const float *src = of_y ? a.Y : a.G;
             const long long k = k0 + 8 * (c & 1);
-            if constexpr (GUARD) r = r < a.rows ? r : a.rows - 1;    // (its results are not stored)
+            if constexpr (GUARD) {                     // past the end: its results are not stored
+                const int end = of_y || !CPLX ? a.rows : a.cols;
+                r = r < end ? r : end - 1;
+            }
+            const bool turned = CPLX && !of_y && r >= a.rows;
+            if (turned) r -= a.rows;
             const float *p = src + (long long)r * a.B + k;
             if (!GUARD || k0 + kGramK <= kend) {
                 // (a row may start at any multiple of four bytes: the loads take that)
@@ -90,6 +100,13 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
                     xr[i][j] = k + j < kend ? v : 0.f;
                 }
             }
+            if constexpr (CPLX)
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {
+                    const float re = xr[i][j], im = xr[i][j + 1];
+                    xr[i][j] = turned ? -im : re;
+                    xr[i][j + 1] = turned ? re : im;
+                }
         }
     };
     auto stash = [&](int buf) {
@@ -142,16 +159,18 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
 
     // accumulator layout of the 32 x 32 matrix instructions: register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
     // column l % 32 of the fragment
-    float *out = a.C + (long long)slice * a.rows * a.rows;
+    const int cols = CPLX ? a.cols : a.rows;
+    float *out = a.C + (long long)slice * a.rows * cols;
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
         const int col = tile_j * BN + wn * 32 * NF + 32 * j + (lane & 31);
+        const int at = !CPLX ? col : (col < a.rows ? 2 * col : 2 * (col - a.rows) + 1);
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = tile_i * BM + wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row < a.rows && col < a.rows) out[(long long)row * a.rows + col] = acc[i / (MF / IB)][i % (MF / IB)][j][v];
+                if (row < a.rows && col < cols) out[(long long)row * cols + at] = acc[i / (MF / IB)][i % (MF / IB)][j][v];
             }
     }
 }
@@ -184,9 +203,10 @@ struct GramPlan {
     bool large;
     int slices;
 };
-inline GramPlan gram_plan(int rows, long long B, int compute_units)
+inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = false)
 {
-    auto tiles = [&](int bm, int bn) { return (long long)((rows + bm - 1) / bm) * ((rows + bn - 1) / bn); };
+    const int cols = cplx ? 2 * rows : rows;
+    auto tiles = [&](int bm, int bn) { return (long long)((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
     auto slices_for = [&](long long t, long long want, long long cols) {
         long long s = (want + t - 1) / t;
         const long long by_cols = B / cols > 1 ? B / cols : 1;
@@ -204,31 +224,34 @@ inline long long gram_slice_cols(long long B, int slices)
     return ((B + slices - 1) / slices + kGramK - 1) / kGramK * kGramK;   // slices start on a step boundary
 }
 
-template <int MW, int NW, int MF, int NF>
+template <int MW, int NW, int MF, int NF, bool CPLX>
 inline void launch_gram(GramArgs a, int slices, hipStream_t stream)
 {
     constexpr int BM = 32 * MF * MW, BN = 32 * NF * NW;
     a.tiles_m = (a.rows + BM - 1) / BM;
-    a.tiles_n = (a.rows + BN - 1) / BN;
-    const bool full = a.B % kGramK == 0 && a.rows % BM == 0 && a.rows % BN == 0;
+    a.tiles_n = (a.cols + BN - 1) / BN;
+    const bool full = a.B % kGramK == 0 && a.rows % BM == 0 && a.cols % BN == 0;
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n * slices)), block(64 * MW * NW);
     if (full)
-        hipLaunchKernelGGL((gram_tile_kernel<MW, NW, MF, NF, false>), grid, block, 0, stream, a);
+        hipLaunchKernelGGL((gram_tile_kernel<MW, NW, MF, NF, false, CPLX>), grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((gram_tile_kernel<MW, NW, MF, NF, true>), grid, block, 0, stream, a);
+        hipLaunchKernelGGL((gram_tile_kernel<MW, NW, MF, NF, true, CPLX>), grid, block, 0, stream, a);
 }
 
 // Launches C = Y G^T; C must hold plan.slices * rows * rows floats; the result ends in the first rows * rows.
+// CPLX: C = Y G^H, interleaved, with B counting real columns and twice the floats.
+template <bool CPLX = false>
 inline void gram_matrix(int rows, long long B, const GramPlan &plan, const float *Y, const float *G, float *C,
                         hipStream_t stream)
 {
-    const GramArgs a{rows, B, gram_slice_cols(B, plan.slices), Y, G, C, 0, 0};
+    const int cols = CPLX ? 2 * rows : rows;
+    const GramArgs a{rows, B, gram_slice_cols(B, plan.slices), Y, G, C, 0, 0, cols};
     if (plan.large)
-        launch_gram<2, 2, 4, 2>(a, plan.slices, stream);
+        launch_gram<2, 2, 4, 2, CPLX>(a, plan.slices, stream);
     else
-        launch_gram<2, 2, 1, 1>(a, plan.slices, stream);
+        launch_gram<2, 2, 1, 1, CPLX>(a, plan.slices, stream);
     if (plan.slices > 1) {
-        const long long count = (long long)rows * rows;
+        const long long count = (long long)rows * cols;
         hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((count + 63) / 64)), dim3(64 * kSumGroups), 0, stream, count,
                            plan.slices, C);
     }

@@ -1,5 +1,8 @@
 // Dense products on the matrix cores in float32 precision: D = A X for a matrix A that many columns share (U itself,
 // or U^T) and a row-major operand X of B columns.
+//
+// Complex operands (interleaved, so X is a real k x 2B array): Re A X + Im A (i X), where i X swaps the two columns of a
+// complex number and negates the first, is one real product with the m x 2k matrix [Re A, Im A].
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -19,9 +22,10 @@ constexpr long long product_pieces(int m, int k)   // 16-byte pieces of an m x k
     return (long long)((m + 255) / 256) * 8 * product_k16(k) * 3 * 64;
 }
 
-// One wavefront per fragment of the m x k array src (leading dimension k).
-__global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const float *__restrict__ src, long long frags,
-                                                           int k16s, u32x4 *__restrict__ out)
+// One wavefront per fragment of the m x k array src (leading dimension k); cplx: src is a complex m x k/2 array, its real
+// parts are the first k/2 columns and its imaginary ones the others.
+__global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, int cplx, const float *__restrict__ src,
+                                                           long long frags, int k16s, u32x4 *__restrict__ out)
 {
     const int lane = threadIdx.x & 63;
     const long long f = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -31,7 +35,8 @@ __global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const f
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         x[j] = 0.f;
-        if (row < m && k0 + j < k) x[j] = src[(long long)row * k + k0 + j];
+        const int c = k0 + j, at = !cplx ? c : (c < k / 2 ? 2 * c : 2 * c - k + 1);
+        if (row < m && c < k) x[j] = src[(long long)row * k + at];
     }
     const Split8 s = split8(x);
     u32x4 *o = out + f * 3 * 64 + lane;
@@ -39,12 +44,12 @@ __global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, const f
     o[64] = s.m;
     o[128] = s.l;
 }
-inline void split_matrix(int m, int k, const float *src, u32x4 *out, hipStream_t stream)
+inline void split_matrix(int m, int k, const float *src, u32x4 *out, hipStream_t stream, bool cplx = false)
 {
     const int k16s = (int)product_k16(k);
     const long long frags = (long long)((m + 255) / 256) * 8 * k16s;
-    hipLaunchKernelGGL(split_matrix_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, stream, m, k, src, frags,
-                       k16s, out);
+    hipLaunchKernelGGL(split_matrix_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, stream, m, k, cplx ? 1 : 0,
+                       src, frags, k16s, out);
 }
 
 struct ProductArgs {
@@ -56,6 +61,7 @@ struct ProductArgs {
     float *D;
     long long ldd;
     int mblocks;          // row blocks of the launch
+    bool cplx;            // complex operands: m x 2 k_complex matrix, X of k / 2 rows and 2 B_complex columns
 };
 
 // D = A X.  MW x NW wavefronts of (32 MF) x (32 NF) results each.
@@ -70,7 +76,7 @@ struct ProductArgs {
 // Bound by the matrix cores.  256 x 128 per workgroup, four wavefronts of 64 x 128 (128 accumulator registers), two
 // workgroups per compute unit: n = 2048, B = 65536 in 2.76 ms = 199 TFLOP/s of float32 product (1190 of bf16; the
 // float32 matrix instructions reach about 129), 128 x 128 3.03 ms; n = B = 4096 0.69 ms against 0.83.
-template <int MW, int NW, int MF, int NF>
+template <int MW, int NW, int MF, int NF, bool CPLX>
 __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 {
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW;
@@ -99,7 +105,13 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
             for (int j = 0; j < 8; ++j) {
                 int r = k0 + 8 * (my_oct + PER_ROW * i) + j;
                 r = r < a.k ? r : a.k - 1;             // past the last row: A is zero there
-                xr[i][j] = (a.X + (long long)r * a.ldx)[col_in];
+                if constexpr (CPLX) {
+                    const bool turned = r >= a.k / 2;
+                    const float v = (a.X + (long long)(turned ? r - a.k / 2 : r) * a.ldx)[turned ? col_in ^ 1 : col_in];
+                    xr[i][j] = turned && !(my_col & 1) ? -v : v;
+                } else {
+                    xr[i][j] = (a.X + (long long)r * a.ldx)[col_in];
+                }
             }
     };
     auto stash = [&](int buf) {
@@ -182,7 +194,10 @@ inline void launch_product(ProductArgs a, hipStream_t stream)
     a.mblocks = (a.m + BM - 1) / BM;
     const long long nblocks = (a.B + BN - 1) / BN;
     const unsigned grid = (unsigned)((nblocks + 7) / 8 * 8 * a.mblocks);
-    hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+    if (a.cplx)
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, true>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+    else
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, false>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
 }
 
 // The largest tile that still gives every compute unit a workgroup and a half, and for few rows one no taller than they

@@ -105,3 +105,32 @@ def test_products_keep_the_range_of_float32(scale):
     y = binding.givens_forward(th, x)
     want = binding.givens_forward(th.double(), x.double())
     assert torch.isfinite(y).all() and rel(y, want) <= TOL_Y
+
+
+# complex operands: below and above the batch from which each direction goes through U, odd batches, sizes of both kernel
+# families, results over their operands
+@pytest.mark.parametrize("n,B", [(2, 1024), (16, 4097), (30, 4096), (66, 1023), (66, 1024), (128, 1025), (130, 4099),
+                                 (256, 4096), (272, 5001)])
+def test_wide_unitary_batches(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(1700 + n)
+    print(f"[products] unitary n={n} B={B}", flush=True)
+    th, ph = ((torch.rand(n * (n - 1) // 2, device="cuda", generator=gen) * 2 - 1) * np.pi for _ in range(2))
+    x, g = (torch.randn(n, B, dtype=torch.complex64, device="cuda", generator=gen) for _ in range(2))
+    y = binding.givens_unitary_forward(th, ph, x)
+    dx, dth, dph = binding.givens_unitary_backward(th, ph, y, g)
+
+    def far(got, want):
+        return float((got.to(want.dtype) - want).norm() / want.norm())
+
+    want_y = binding.givens_unitary_forward(th.double(), ph.double(), x.to(torch.complex128))
+    want = binding.givens_unitary_backward(th.double(), ph.double(), want_y, g.to(torch.complex128))
+    assert far(y, want_y) <= TOL_Y
+    assert all(far(a, b) <= TOL_G for a, b in zip((dx, dth, dph), want))
+    none, dth2, dph2 = binding.givens_unitary_backward(th, ph, y, g, want_dx=False)
+    assert none is None and torch.equal(dth2, dth) and torch.equal(dph2, dph)
+    buf = x.clone()
+    binding.givens_unitary_forward(th, ph, buf, Y=buf)
+    assert torch.equal(buf, y)
+    buf = g.clone()
+    binding.givens_unitary_backward(th, ph, y, buf, dX=buf)
+    assert torch.equal(buf, dx)
