@@ -56,7 +56,8 @@ extern "C" {
                                  /* n from 132, a multiple of 4 up to 4096 or of 8 up to 8192,  */
                                  /* or n = 2 M L with M in {7, 5, 3} and L <= 1024 (standard    */
                                  /* rotation form only, whatever givens_set_rotation_form says) */
-#define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs */
+#define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs, */
+                                 /* or from n = 16 on one wavefront per strip of columns         */
 
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */
@@ -276,9 +277,9 @@ const char *givens_error_string(int code);
 /* Selects the kernel family for subsequent calls (process-wide).  Returns the previous value,
  * or GIVENS_ERR_UNSUPPORTED for an unknown value.  With GIVENS_KERNEL_CAROUSEL or GIVENS_KERNEL_COLUMN a
  * call whose shape those kernels do not cover returns GIVENS_ERR_UNSUPPORTED instead of falling back.
- * The column family has a forward kernel only: its backward call uses the Gram-matrix reduction (see
- * givens_set_reduction) with the sweep on the n x n Gram matrix done by the LDS family, and the LDS
- * family outright when that reduction is not available or not selected. */
+ * Below n = 16 the column family has a forward kernel only: its backward call uses the Gram-matrix
+ * reduction (see givens_set_reduction) with the sweep on the n x n Gram matrix done by the LDS family, and
+ * the LDS family outright when that reduction is not available or not selected. */
 int givens_set_kernel(int which);
 
 /* Which family the last successful forward/build/backward call on this thread used

@@ -87,16 +87,18 @@ inline bool carousel_has_forms(int n)
 }
 
 // One-wavefront shapes whose exchange stays inside the wavefront (DPP shifts, no LDS, no barrier): the fewest slots
-// per lane in {2, 4, 8} with at most 64 lanes, so multiples of 8 up to 256, 512 and 1024.  A lane then has the least
-// work per block, and the block-to-block chain is what bounds the small sweeps these shapes are for.  max_slots: 8
-// for the forward sweep, 4 for the reverse sweep (with 8 slots and two strips per lane it does not beat the LDS
-// exchange).
+// per lane in {1, 2, 4, 8} with at most 64 lanes: every even n up to 128, then multiples of 8 up to 512 and of 16 up to
+// 1024.  A lane then has the least work per block, and the block-to-block chain is what bounds the small
+// sweeps these shapes are for.  max_slots: 8 for the forward sweep, 4 for the reverse sweep (with 8 slots and two strips
+// per lane it does not beat the LDS exchange).  From kCarouselMinN on they belong to the carousel family, below it to the
+// column family (column_wave), with one slot per lane and the standard rotation form only; the others need n to be a
+// multiple of 8 for the forms' renormalisation points (the kernels unroll 8 blocks).
+constexpr int kWaveMinN = 16;
 inline bool carousel_wave_shape_for(int n, int max_slots, CarouselShape *out)
 {
-    if (n < kCarouselMinN) return false;
-    if (n % 8) return false;   // the kernels unroll 8 blocks (ring of prefetched coefficients)
-    for (int m : {2, 4, 8})
-        if (m <= max_slots && n % (2 * m) == 0 && n / (2 * m) <= 64) {
+    if (n < kWaveMinN) return false;
+    for (int m : {1, 2, 4, 8})
+        if (m <= max_slots && n % (m == 1 ? 2 : m == 8 ? 16 : 8) == 0 && n / (2 * m) <= 64) {
             *out = {m, 1};
             return true;
         }
@@ -228,6 +230,16 @@ int unitary_carousel_backward_m2(const UnitaryCarouselBwdArgs &a, int waves, int
 // Column family (column_fwd.hip): forward sweep for even n <= 128, one lane per column, standard-form
 // table.  GIVENS_ERR_UNSUPPORTED for other n.
 constexpr int kColumnFamilyMaxN = 128;
+// Sizes whose forward sweep (up to some batch) and reverse sweep run on the wavefront shape (carousel_wave_shape_for): a
+// block is then one rotation per lane and a move between lanes, where the column kernel goes through all n / 2 rotations
+// in turn.  Measured, forward column kernel against it in us (10 us is what a call takes on the host): n = 128, B = 64
+// 115 / 10.6, n = 64, B = 1024 44 / 10.4, n = 28, B = 2000 13.9 / 10.5, 16384 13.8 / 13.7, 65536 14.6 / 34.4;
+// backward LDS family against it n = 128, B = 64 60 / 19, B = 1024 (Gram form) 229 / 42; n = 16, B = 65536 329 / 29.
+inline bool column_wave(int n)
+{
+    CarouselShape s;
+    return n <= kColumnFamilyMaxN && carousel_wave_shape_for(n, 4, &s);
+}
 int column_forward(int n, int rows, long long B, const float2 *table, const float *X, float *Y, int identity,
                    int mirror, hipStream_t stream);
 
@@ -260,10 +272,14 @@ int carousel_backward_wave(const CarouselBwdArgs &a, int M, int W);
 // table, and beyond about a thousand wavefronts that traffic (L2) sets the time.
 inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 {
-    if (!carousel_shape_for(n, &p->s)) return false;
-    p->W = carousel_width(B, p->s.WAVES, carousel_fwd_widest(p->s));
     p->wave = false;
     CarouselShape ws;
+    if (n >= kCarouselMinN) {
+        if (!carousel_shape_for(n, &p->s)) return false;
+        p->W = carousel_width(B, p->s.WAVES, carousel_fwd_widest(p->s));
+    } else if (!carousel_wave_shape_for(n, 8, &ws)) {
+        return false;
+    }
     if (carousel_wave_shape_for(n, 8, &ws)) {
         const long long single = ws.M == 8 ? 512 : 1024;     // widest batch of single-column strips
         *p = {ws, B <= single ? 1 : B <= 4 * single ? 2 : B <= 16 * single ? 4 : 8, true};
@@ -304,6 +320,12 @@ inline int carousel_forward(int n, int rows, long long B, const CarouselCoefs &c
 // the forward sweep's rule).
 inline bool carousel_bwd_plan(int n, long long B, CarouselPlan *p)
 {
+    CarouselShape ws;
+    if (n < kCarouselMinN) {
+        if (!carousel_wave_shape_for(n, 4, &ws)) return false;
+        *p = {ws, B <= 256 ? 1 : B <= 1024 ? 2 : 4, true};
+        return true;
+    }
     if (!carousel_bwd_shape_for(n, &p->s)) return false;
     p->wave = false;
     p->W = B > 1 ? 2 : 1;
@@ -314,7 +336,6 @@ inline bool carousel_bwd_plan(int n, long long B, CarouselPlan *p)
         }
     // wavefront exchange: n up to 512 and batches up to 4096 columns (measured 1.2 to 2.1 times faster, sweep and
     // second stage together; each strip costs a row of partial sums, hence wider strips sooner than forward)
-    CarouselShape ws;
     if (B <= 4096 && carousel_wave_shape_for(n, 4, &ws)) *p = {ws, B <= 256 ? 1 : B <= 1024 ? 2 : 4, true};
     return true;
 }

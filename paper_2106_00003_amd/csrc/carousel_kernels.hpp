@@ -49,9 +49,9 @@ enum { kExchangeLds = 0, kExchangeWave = 1 };
 // where the LDS exchange sets the pace of a block anyway, three or seven blocks ahead with the wavefront exchange,
 // whose blocks are shorter than a load's latency (a ring of 2 left those sweeps at one L2 latency per block: n = 256,
 // 64 columns, forward 38 us; ring of 4: 22 us; ring of 8: 15 us).
-// (ring slots are static, so the unrolled group has lcm(M, depth) copies and n must be a multiple of that: 8 here)
+// (ring slots are static, so the unrolled group has lcm(M, depth) copies: 8)
 constexpr int wave_ring_depth_fwd(int M) { return M == 8 ? 4 : 8; }
-constexpr int wave_ring_depth_bwd(int M) { return M == 2 ? 8 : 4; }
+constexpr int wave_ring_depth_bwd(int M) { return M <= 2 ? 8 : 4; }
 constexpr int carousel_lcm(int a, int b)
 {
     int x = a, y = b;
@@ -292,9 +292,15 @@ struct CarouselFwd {
             for (int x = 0; x < W; ++x) {
                 const float t_out = top[q][x], b_out = bot[qb][x], t_one = top[q1][x];
                 const float t_in = lane_from_next(b_out, t_out);
-                bot[qb][x] = lane_from_prev(t_one, b_out);
-                top[q][x] = far ? b_out : t_in;
-                top[q1][x] = (lane == 0) ? t_out : top[q1][x];
+                if constexpr (M == 1) {
+                    // slot 1 is the next lane's: what lane 0 receives turns round into its bottom slot
+                    bot[0][x] = lane_from_prev(t_in, b_out);
+                    top[0][x] = lane == 0 ? t_out : (far ? b_out : t_in);
+                } else {
+                    bot[qb][x] = lane_from_prev(t_one, b_out);
+                    top[q][x] = far ? b_out : t_in;
+                    top[q1][x] = (lane == 0) ? t_out : top[q1][x];
+                }
             }
         }
 
@@ -324,11 +330,22 @@ struct CarouselFwd {
         (step<Cs, Cs == kUnroll - 2, false, (kUnroll - 2 - Cs >= kDepth - 1)>(kUnroll - 2 - Cs), ...);
     }
 
-    // all n-1 blocks: n/kUnroll - 1 full groups, then the tail of kUnroll - 1
+    // One slot per lane: n is even and no more, so the first n mod kUnroll blocks go before the unrolled groups with
+    // coefficients fetched on the spot.
+    __device__ __forceinline__ int leading_blocks() const { return M == 1 ? n % kUnroll : 0; }
+    __device__ __forceinline__ void lead_in()
+    {
+        for (int k = n - 2; k > n - 2 - leading_blocks(); --k) {
+            load_coefs(k, cs[0]);
+            step<0, false, false, false>(k);
+        }
+    }
+
+    // the other n-1 blocks: whole groups, then the tail of kUnroll - 1
     __device__ __forceinline__ void sweep()
     {
         constexpr auto seq = std::make_integer_sequence<int, kUnroll>{};
-        int k = n - 2;
+        int k = n - 2 - leading_blocks();
         if constexpr (FORM == 0) {
             for (; k >= kUnroll - 1; k -= kUnroll) full_group<false>(k, seq);
         } else {
@@ -443,8 +460,9 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
         load_row<W>(st.bot[r], X, B, mirrored_row(n, rr_label(n, n - 2, n - 1 - p), mirror), my_rows, b0, wv, vec,
                     identity);
     }
+    if constexpr (M == 1) st.lead_in();
 #pragma unroll
-    for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(n - 2 - d, st.cs[d]);
+    for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(n - 2 - st.leading_blocks() - d, st.cs[d]);
 
     st.sweep();
 
@@ -468,8 +486,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES > 8 ? 1 : 2) void carousel_forwar
 {
     using Exchange = std::conditional_t<EX == kExchangeLds, CarouselExchange<W, WAVES>, NoExchange>;
     __shared__ Exchange sh;
-    if constexpr (kRenormPeriod % M != 0) {
-        // slot counts that do not divide the renormalisation period: standard form only (the host passes no flag)
+    if constexpr (kRenormPeriod % M != 0 || M == 1) {
+        // slot counts that do not divide the renormalisation period, and the shapes with one slot, which only small
+        // problems take: standard form only (the host passes no flag)
         carousel_forward_body<M, W, WAVES, kFormStandard, EX>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok,
                                                               mirror);
     } else {
@@ -701,9 +720,15 @@ struct CarouselBwd {
         for (int x = 0; x < W; ++x) {
             const float t_out = t[qt][x], b_out = b[qb][x], held = t[pf][x];
             const float b_in = lane_from_next(t_out, b_out);
-            t[qt][x] = lane_from_prev(held, t_out);
-            b[qb][x] = far ? t_out : b_in;
-            t[pf][x] = (lane == 0) ? b_out : held;
+            if constexpr (M == 1) {
+                // slot 1 is the next lane's: lane 0 hands it its bottom slot and keeps the held row
+                t[0][x] = lane_from_prev(t_out, lane == 0 ? b_out : t_out);
+                b[0][x] = far ? t_out : b_in;
+            } else {
+                t[qt][x] = lane_from_prev(held, t_out);
+                b[qb][x] = far ? t_out : b_in;
+                t[pf][x] = (lane == 0) ? b_out : held;
+            }
         }
     }
 
@@ -853,17 +878,28 @@ struct CarouselBwd {
         (step<Cs, Cs == kUnroll - 2, false, (kUnroll - 2 - Cs >= kDepth - 1)>(k_first + Cs), ...);
     }
 
-    // all n-1 blocks in the order b_1, b_2, ...: n/kUnroll - 1 full groups, then the tail of kUnroll - 1
+    // as in the forward kernel
+    __device__ __forceinline__ int leading_blocks() const { return M == 1 ? n % kUnroll : 0; }
+    __device__ __forceinline__ void lead_in()
+    {
+        for (int k = 0; k < leading_blocks(); ++k) {
+            load_coefs(k, cs[0]);
+            load_prior(k, prior[0]);
+            step<0, false, false, false>(k);
+        }
+    }
+
+    // the other n-1 blocks in the order b_1, b_2, ...: whole groups, then the tail of kUnroll - 1
     __device__ __forceinline__ void sweep()
     {
         constexpr auto seq = std::make_integer_sequence<int, kUnroll>{};
+        int k = leading_blocks();
         if constexpr (CHAIN) {
             polled = 0u;
         } else {
 #pragma unroll
-            for (int d = 0; d < kDepth - 1; ++d) load_prior(d, prior[d]);
+            for (int d = 0; d < kDepth - 1; ++d) load_prior(k + d, prior[d]);
         }
-        int k = 0;
         if constexpr (FORM == 0) {
             for (; k + kUnroll <= n - 1; k += kUnroll) full_group<false>(k, seq);
         } else {
@@ -991,8 +1027,9 @@ __device__ __forceinline__ void carousel_backward_body(Exchange &sh, int n, int 
             load_row<W>(st.gt[r], G, B, p, my_rows, b0, wv, vec, g_identity);   // g_identity: G = I_n, not read
             load_row<W>(st.gb[r], G, B, n - 1 - p, my_rows, b0, wv, vec, g_identity);
         }
+        if constexpr (M == 1) st.lead_in();
 #pragma unroll
-        for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(d, st.cs[d]);
+        for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(st.leading_blocks() + d, st.cs[d]);
 
         st.sweep();
 
@@ -1025,7 +1062,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES > 8 ? 1 : 2) void carousel_backwa
 {
     using Exchange = std::conditional_t<EX == kExchangeLds, CarouselExchangeBwd<W, WAVES>, NoExchange>;
     __shared__ Exchange sh;
-    if constexpr (kRenormPeriod % M != 0) {
+    if constexpr (kRenormPeriod % M != 0 || M == 1) {
         carousel_backward_body<M, W, WAVES, kFormStandard, EX, 0>(sh, n, rows, B, strip0, nstrips, table, renorm, Yin,
                                                                   G, dX, partial, zeros, sink, vec_ok, g_identity,
                                                                   CarouselChainArgs{});

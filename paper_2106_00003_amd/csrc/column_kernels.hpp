@@ -9,9 +9,8 @@
 // unrolled group of kGroup blocks the turn is a renaming of registers; after the group the ring is
 // turned physically (n-1 register moves per kGroup blocks).
 //
-// The reverse sweep of this family is not a kernel of its own: for the wide batches small n comes
-// with, the gradient goes through the Gram matrix (C = Y G^T by one GEMM, the reverse sweep on the
-// n x n operand C in the LDS family, dX by this forward kernel on the mirrored problem).
+// What remains for it: sizes below 16, and wide batches below 32; the family's other forward sweeps and its reverse sweeps
+// run on the one-wavefront carousel shapes (column_wave), its wide batches through U and the Gram matrix.
 #pragma once
 #include <hip/hip_runtime.h>
 

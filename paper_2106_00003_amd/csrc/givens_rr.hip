@@ -32,6 +32,8 @@ constexpr size_t kColumnsCapBytes = size_t(128) << 20;         // copied columns
 constexpr long long kProductMinRatio = 2, kProductMinB = 2048; // batches whose application goes through U (wants_product)
 constexpr long long kUnitaryMinRatio = 4;                      // the same for complex operands (unitary_wants_product)
 constexpr long long kUnitaryMinForward = 4096, kUnitaryMinBackward = 1024;
+constexpr int kColumnProductMinN = 32;                         // smallest n of the column family whose wide batches go through U
+constexpr long long kColumnWaveMaxB = 16384;                   // widest batch of its wavefront sweep below that size
 constexpr size_t kFlagBytes = 256;                             // the flag words of a workspace
 
 struct Buffer {
@@ -624,7 +626,9 @@ int run_forward_sweep(const Problem &pb, long long B, const Coefs<T> &coefs, Fam
     } else if (fam.column) {
         if constexpr (std::is_same<T, float>::value) {
             Span span(1, stream);
-            rc = column_forward(n, rows, B, coefs.table, X, Y, identity, transpose, stream);
+            rc = column_wave(n) && B <= kColumnWaveMaxB
+                     ? carousel_forward(n, rows, B, coefs.carousel(), X, Y, identity, transpose, stream)
+                     : column_forward(n, rows, B, coefs.table, X, Y, identity, transpose, stream);
             if (rc == GIVENS_OK && !hip_ok(hipGetLastError())) rc = GIVENS_ERR_HIP;
         }
         t_state.last_kernel = GIVENS_KERNEL_COLUMN;
@@ -639,13 +643,15 @@ int run_forward_sweep(const Problem &pb, long long B, const Coefs<T> &coefs, Fam
 // column; building U costs the same for its own n columns only, and the dense product U X then runs on the matrix
 // cores at several times the sweep's rate.  Measured, sweep against product in us: n = 256, B = 2048 30 / 30, 4096
 // 42 / 31, 65536 327 / 69; n = 1024, B = 1536 196 / 223, 2048 301 / 225, 65536 2958 / 808; n = 2048, B = 2048
-// 720 / 837, 4096 1311 / 896; n = 4096, B = 4096 2997 / 3418, 8192 5867 / 4002; n = 1002 (5 slots per lane), B = 2004
-// 266 / 275, 4008 447 / 290.  The column family's sweep (n <= 128) takes one time, that of the chain through its n - 1
-// blocks, whatever the batch up to 65536, so there the product never pays.
+// 720 / 837, 4096 1311 / 896; n = 4096, B = 4096 2997 / 3418, 8192 5867 / 4002; n = 1002 (3 slots per lane), B = 2004
+// 266 / 275, 4008 447 / 290.  In the column family U comes from the
+// wavefront sweep (column_wave): n = 34, B = 4096 column kernel 16.6 us, product 15.7; n = 64, B = 65536 44 / 20; n = 128,
+// B = 65536 126 / 34; n = 28, B = 4096 13.7 / 14.2.
 template <typename T>
 bool wants_product(const Families &fam, int rows, long long B)
 {
-    return std::is_same<T, float>::value && !fam.column && B >= kProductMinRatio * rows && B >= kProductMinB;
+    if (fam.column && !(column_wave(rows + (rows & 1)) && rows >= kColumnProductMinN)) return false;
+    return std::is_same<T, float>::value && B >= kProductMinRatio * rows && B >= kProductMinB;
 }
 // columns that the sweep of a forward-type call runs over
 template <typename T>
@@ -939,13 +945,17 @@ int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const C
             ProductStorage st;
             if (dX)
                 if (int rc = workspace_product_storage(ws, rows, B, G == dX, &st)) return rc;
-            int rc = backward_chunks<T>(ws, dev, fam.carousel, pb, rows, coefs, C, nullptr, st.matrix, dtheta, stream, 1);
+            int rc = backward_chunks<T>(ws, dev, fam.carousel || (fam.column && column_wave(n)), pb, rows, coefs, C, nullptr, st.matrix, dtheta, stream, 1);
             if (rc == GIVENS_OK && dX) rc = apply_matrix(st, dev, rows, B, G, dX, stream);
             t_state.last_reduction = GIVENS_REDUCTION_GRAM;
             if (fam.column) t_state.last_kernel = GIVENS_KERNEL_COLUMN;
             else t_state.last_kernel = fam.carousel ? GIVENS_KERNEL_CAROUSEL : GIVENS_KERNEL_LDS;
             return rc;
         }
+    }
+    if (fam.column && column_wave(n)) {
+        t_state.last_kernel = GIVENS_KERNEL_COLUMN;
+        return backward_chunks<T>(ws, dev, true, pb, B, coefs, Y, G, dX, dtheta, stream);
     }
     return backward_chunks<T>(ws, dev, fam.carousel, pb, B, coefs, Y, G, dX, dtheta, stream);
 }
