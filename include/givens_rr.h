@@ -196,6 +196,16 @@ int givens_build_prepared(int64_t token, float *U, void *stream);
 int givens_backward_prepared(int64_t token, int64_t B, const float *Y, const float *G, float *dX, float *dtheta,
                              void *stream);
 
+/*
+ * One matrix, many batches (float).  givens_pack lays an n x n matrix (say U of givens_build) out for the matrix cores in
+ * memory of the caller's: givens_packed_bytes(n) bytes on the device, 16-byte aligned, about 6 n^2.  givens_apply_packed
+ * then computes Y = U X, n x B, in float32 precision: for a theta that stays while the operands change.  Neither call uses
+ * the library's workspaces; Y must not be X (GIVENS_ERR_ALIAS).
+ */
+int64_t givens_packed_bytes(int n);                              /* or a negative error code */
+int givens_pack(int n, const float *U, void *packed, void *stream);
+int givens_apply_packed(int n, int64_t B, const void *packed, const float *X, float *Y, void *stream);
+
 /* float64 variants: same semantics, all arrays double. */
 int givens_forward_f64(int n, int64_t B, const double *theta, const double *X, double *Y, void *stream);
 int givens_build_f64(int n, const double *theta, double *U, void *stream);

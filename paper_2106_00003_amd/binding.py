@@ -77,6 +77,9 @@ def lib():
     L.givens_forward_prepared.argtypes = [i64, i64, vp, vp, vp]
     L.givens_build_prepared.argtypes = [i64, vp, vp]
     L.givens_backward_prepared.argtypes = [i64, i64, vp, vp, vp, vp, vp]
+    L.givens_packed_bytes.argtypes, L.givens_packed_bytes.restype = [i32], i64
+    L.givens_pack.argtypes = [i32, vp, vp, vp]
+    L.givens_apply_packed.argtypes = [i32, i64, vp, vp, vp, vp]
     L.givens_num_angles.argtypes = [i32, i32]
     L.rr_schedule_restricted.argtypes = [i32, i32, vp]
     for name in ("givens_forward_restricted", "givens_forward_restricted_f64"):
@@ -297,6 +300,40 @@ def givens_build(theta, n: int, U=None, stream=None):
     fn = getattr(lib(), "givens_build" + _suffix(theta))
     _check(fn(n, _dev(theta, "theta"), _dev(U, "U", theta.dtype), _stream_ptr(stream)), "givens_build")
     return U
+
+
+def givens_pack(U, packed=None, stream=None):
+    """The n x n float32 matrix U laid out for givens_apply_packed: a uint8 tensor of givens_packed_bytes(n) bytes."""
+    import torch
+    n = U.shape[0]
+    if U.dtype != torch.float32 or U.dim() != 2 or U.shape[1] != n:
+        raise ValueError("U must be a square float32 matrix")
+    size = lib().givens_packed_bytes(n)
+    if size < 0:
+        raise GivensError(size, "givens_packed_bytes")
+    if packed is None:
+        packed = torch.empty(size, dtype=torch.uint8, device=U.device)
+    if packed.numel() < size or packed.data_ptr() % 16:
+        raise ValueError("packed must have givens_packed_bytes(n) bytes, 16-byte aligned")
+    _check(lib().givens_pack(n, _dev(U, "U"), _dev(packed, "packed", torch.uint8), _stream_ptr(stream)), "givens_pack")
+    return packed
+
+
+def givens_apply_packed(packed, X, Y=None, stream=None):
+    """Y = U X for the matrix U that `packed` was made from (givens_pack)."""
+    import torch
+    n, B = X.shape
+    if X.dtype != torch.float32:
+        raise TypeError("givens_apply_packed takes float32 operands")
+    if packed.numel() < lib().givens_packed_bytes(n):
+        raise ValueError("packed is too small for X")
+    if Y is None:
+        Y = torch.empty_like(X)
+    if Y.shape != X.shape:
+        raise ValueError("Y must have the shape of X")
+    _check(lib().givens_apply_packed(n, B, _dev(packed, "packed", torch.uint8), _dev(X, "X"),
+                                     _dev(Y, "Y", torch.float32), _stream_ptr(stream)), "givens_apply_packed")
+    return Y
 
 
 def givens_backward(theta, Y, G, dX=None, dtheta=None, want_dx: bool = True, stream=None):

@@ -679,7 +679,7 @@ int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const
             a.X = st.copy;
             a.ldx = cols;
         }
-        product(a, cus, stream);
+        product(a, cus, stream, B);
     }
     GIVENS_HIP(hipGetLastError());
     return GIVENS_OK;
@@ -1140,6 +1140,30 @@ int backward_prepared_impl(int64_t token, long long B, const float *Y, const flo
     return run_backward<float>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream);
 }
 
+// ---- a matrix laid out once, in the caller's memory, and applied to many batches
+int pack_impl(int n, const float *U, void *packed, void *stream_v)
+{
+    if (n < 1) return GIVENS_ERR_BAD_N;
+    if (!U || !packed) return GIVENS_ERR_NULL;
+    split_matrix(n, n, U, static_cast<u32x4 *>(packed), reinterpret_cast<hipStream_t>(stream_v));
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+int apply_packed_impl(int n, long long B, const void *packed, const float *X, float *Y, void *stream_v)
+{
+    if (n < 1) return GIVENS_ERR_BAD_N;
+    if (B < 1) return GIVENS_ERR_BAD_B;
+    if (!packed || !X || !Y) return GIVENS_ERR_NULL;
+    if (X == Y) return GIVENS_ERR_ALIAS;
+    int dev = 0, cus = 0;
+    if (int rc = current_device(&dev)) return rc;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    product(ProductArgs{n, n, B, static_cast<const u32x4 *>(packed), X, B, Y, B, 0, false}, cus,
+            reinterpret_cast<hipStream_t>(stream_v));
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+
 // ---- unitary extension (appendix): complex operands, LDS strip kernels
 template <typename T>
 int unitary_strip_width(int n, long long B, int strips_in_lds)
@@ -1574,6 +1598,22 @@ int givens_backward_prepared(int64_t token, int64_t B, const float *Y, const flo
                              void *stream)
 {
     return givens::backward_prepared_impl(token, B, Y, G, dX, dtheta, stream, givens::default_options());
+}
+
+int64_t givens_packed_bytes(int n)
+{
+    if (n < 1 || n > givens::kMaxRows) return GIVENS_ERR_BAD_N;
+    return (int64_t)(givens::product_pieces(n, n) * sizeof(givens::u32x4));
+}
+int givens_pack(int n, const float *U, void *packed, void *stream)
+{
+    if (n > givens::kMaxRows) return GIVENS_ERR_UNSUPPORTED;
+    return givens::pack_impl(n, U, packed, stream);
+}
+int givens_apply_packed(int n, int64_t B, const void *packed, const float *X, float *Y, void *stream)
+{
+    if (n > givens::kMaxRows) return GIVENS_ERR_UNSUPPORTED;
+    return givens::apply_packed_impl(n, B, packed, X, Y, stream);
 }
 
 int64_t givens_num_angles(int n, int m)

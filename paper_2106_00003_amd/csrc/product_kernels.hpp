@@ -187,6 +187,70 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     }
 }
 
+// D = A X for few columns, where tiles of 64 x 64 leave most of the chip idle and each walks the whole contraction step by
+// step.  A workgroup takes 32 x 32 results, its eight wavefronts a part of the contraction each (operands straight from
+// memory: a lane's eight values of X are rows of one column), two fragments ahead; the parts are added through LDS in
+// wavefront order.  Bound by the latency of memory, for large matrices by reading A: n = 1024, B = 64 in 6.8 us (39 with
+// tiles; 10.2 with 32 x 64 results per workgroup), n = 4096, B = 64 in 25 us = 4.0 TB/s (182).
+constexpr int kNarrowWaves = 8;
+template <bool CPLX>
+__global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(ProductArgs a)
+{
+    __shared__ float part[kNarrowWaves][16][64];
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mb = blockIdx.x % a.mblocks;
+    const long long n0 = (long long)(blockIdx.x / a.mblocks) * 32;
+    const int k16s = 2 * ((a.k + kProductStep - 1) / kProductStep);
+    const int per = (k16s + kNarrowWaves - 1) / kNarrowWaves;
+    const int k_from = wave * per, k_to = k_from + per < k16s ? k_from + per : k16s;
+    const long long col = n0 + (lane & 31) < a.B ? n0 + (lane & 31) : a.B - 1;   // past the end: its results are not stored
+    const u32x4 *ap = a.A + (long long)mb * k16s * 192 + lane;
+    constexpr int DEPTH = 3;
+    u32x4 fa[DEPTH][1][3];
+    float xr[DEPTH][8];
+    auto load = [&](int set, int kf) {
+        if (kf >= k_to) return;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) fa[set][0][p] = ap[(long long)kf * 192 + 64 * p];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            int r = 16 * kf + 8 * half + q;
+            r = r < a.k ? r : a.k - 1;                 // past the last row: A is zero there
+            const bool turned = CPLX && r >= a.k / 2;
+            const float *row = a.X + (long long)(turned ? r - a.k / 2 : r) * a.ldx;
+            const float v = row[turned ? col ^ 1 : col];
+            xr[set][q] = turned && !(col & 1) ? -v : v;
+        }
+    };
+    f32x16 acc[1][1];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+    load(0, k_from);
+    load(1, k_from + 1);
+    for (int kf = k_from; kf < k_to; kf += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            load((d + DEPTH - 1) % DEPTH, kf + d + DEPTH - 1);
+            if (kf + d < k_to) {
+                const Split8 s = split8(xr[d]);
+                const u32x4 fb[1][3] = {{s.h, s.m, s.l}};
+                mfma_split(fa[d], fb, acc);
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) part[wave][v][lane] = acc[0][0][v];
+    __syncthreads();
+    for (int v = wave; v < 16; v += kNarrowWaves) {
+        float sum = part[0][v][lane];
+#pragma unroll
+        for (int w = 1; w < kNarrowWaves; ++w) sum += part[w][v][lane];
+        const int row = 32 * mb + 8 * (v >> 2) + 4 * half + (v & 3);
+        if (row < a.m && n0 + (lane & 31) < a.B) a.D[(long long)row * a.ldd + col] = sum;
+    }
+}
+
 template <int MW, int NW, int MF, int NF>
 inline void launch_product(ProductArgs a, hipStream_t stream)
 {
@@ -200,10 +264,23 @@ inline void launch_product(ProductArgs a, hipStream_t stream)
         hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, false>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
 }
 
-// The largest tile that still gives every compute unit a workgroup and a half, and for few rows one no taller than they
-// are.
-inline void product(const ProductArgs &a, int compute_units, hipStream_t stream)
+// Few results (up to six workgroups of the narrow kernel per compute unit; n = 1024, B = 1024 23 us against 41 with tiles,
+// 2048 42 / 46, 4096 88 / 68): the narrow kernel.  Else the largest tile that still gives every compute unit a workgroup
+// and a half, and for few rows one no taller than they are.  The
+// two kinds add in different orders: `all_columns`, where it is given, decides (the columns of the result of which a.B are
+// a part), so that a result does not depend on how it is cut.
+inline void product(ProductArgs a, int compute_units, hipStream_t stream, long long all_columns = 0)
 {
+    const long long narrow = (long long)((a.m + 31) / 32) * ((a.B + 31) / 32);
+    const long long all = all_columns ? (long long)((a.m + 31) / 32) * ((all_columns + 31) / 32) : narrow;
+    if (all <= 6LL * compute_units) {
+        a.mblocks = (a.m + 31) / 32;
+        if (a.cplx)
+            hipLaunchKernelGGL(product_narrow_kernel<true>, dim3((unsigned)narrow), dim3(64 * kNarrowWaves), 0, stream, a);
+        else
+            hipLaunchKernelGGL(product_narrow_kernel<false>, dim3((unsigned)narrow), dim3(64 * kNarrowWaves), 0, stream, a);
+        return;
+    }
     auto groups = [&](int bm, int bn) { return ((a.m + bm - 1) / bm) * ((a.B + bn - 1) / bn); };
     const long long enough = 3LL * compute_units / 2;
     if (a.m > 128 && groups(256, 128) >= enough)

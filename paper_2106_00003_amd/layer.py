@@ -141,26 +141,30 @@ class OrthogonalLinear(torch.nn.Module):
         count = binding.num_angles(n, m)
         self.theta = torch.nn.Parameter(init_std * torch.randn(count, device=device, dtype=dtype))
 
-        self._eval_tables = None  # (token, version of theta, stream) of tables prepared for evaluation
+        self._eval_matrix = None  # (version of theta, its address, stream), U laid out for evaluation
+        self._captured = []       # laid-out matrices that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
         if torch.is_grad_enabled() or self.theta.dtype != torch.float32:
             return givens_apply(self.theta, X, self.m)
-        # evaluation: the tables of the current theta are prepared once and reused until theta changes
-        key = (self.theta._version, self.theta.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        # evaluation: U of the current theta is built and laid out once, here and not in the workspace of the stream, which
+        # all layers share, and multiplied with until theta changes
         x = X.contiguous()
-        m = None if _plain(self.n, self.m) else (self.n - 1 if self.m is None else self.m)
-        for _ in range(2):
-            if self._eval_tables is None or self._eval_tables[1] != key:
-                token = binding.givens_prepare(self.theta.detach(), self.n, m, binding.PREPARE_FORWARD)
-                self._eval_tables = (token, key)
-            try:
-                return binding.givens_forward_prepared(self._eval_tables[0], x)
-            except binding.GivensError as err:
-                if err.code != binding.ERR_STALE:
-                    raise
-                self._eval_tables = None
-        raise RuntimeError("prepared tables were replaced twice in a row")
+        if x.dim() != 2 or x.shape[0] != self.n or x.shape[1] == 0 or x.dtype != torch.float32 or not x.is_cuda:
+            return givens_apply(self.theta, X, self.m)   # refused there
+        key = (self.theta._version, self.theta.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        kept = self._eval_matrix
+        capturing = torch.cuda.is_current_stream_capturing()
+        if kept is None or kept[0] != key:
+            kept = (key, binding.givens_pack(givens_matrix(self.theta, self.n, self.m)))
+            if not capturing:                # what a graph records is there when it is replayed
+                self._eval_matrix = kept
+        elif capturing:
+            self._captured.append(kept[1])   # and what it reads has to stay
+        return binding.givens_apply_packed(kept[1], x)
+
+    def __getstate__(self):
+        return {**self.__dict__, "_eval_matrix": None, "_captured": []}
 
     def matrix(self) -> torch.Tensor:
         return givens_matrix(self.theta, self.n, self.m)

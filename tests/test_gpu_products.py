@@ -134,3 +134,56 @@ def test_wide_unitary_batches(n, B):
     buf = g.clone()
     binding.givens_unitary_backward(th, ph, y, buf, dX=buf)
     assert torch.equal(buf, dx)
+
+
+# the kernel for few columns: one column, one past its 32, contractions that do not fill its eight parts, the last size
+# before the tiled kernels and the first after it
+@pytest.mark.parametrize("n,B", [(1, 1), (2, 33), (31, 5), (33, 64), (130, 31), (257, 1), (514, 100), (1002, 64),
+                                 (1024, 1536), (1024, 1537), (520, 4000)])
+def test_packed_matrix_applied_to_few_columns(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(1800 + n)
+    u, x = torch.randn(n, n, device="cuda", generator=gen), torch.randn(n, B, device="cuda", generator=gen)
+    packed = binding.givens_pack(u)
+    want = (u.double().cpu() @ x.double().cpu()).cuda()
+    got = binding.givens_apply_packed(packed, x)
+    # float32 operands and sums of n products: a few units in the last place
+    assert rel(got, want) <= 1e-6
+    with pytest.raises(binding.GivensError):
+        binding.givens_apply_packed(packed, x, Y=x)
+
+
+def test_layers_in_evaluation_keep_their_own_matrix():
+    from paper_2106_00003_amd import layer
+    nets = [layer.OrthogonalLinear(n, m) for n, m in ((130, None), (130, None), (129, 20))]
+    xs = [torch.randn(net.n, 40, device="cuda") for net in nets]
+
+    def check():
+        with torch.no_grad():
+            for net, x in zip(nets, xs):
+                want = layer.givens_apply(net.theta.double(), x.double(), net.m)
+                assert rel(net(x), want) <= TOL_Y
+
+    check()
+    check()
+    with torch.no_grad():
+        nets[1].theta.mul_(0.5)
+    check()
+    # a recorded evaluation reads the matrix of its time, also after the layer has gone on
+    net, x = nets[0], xs[0]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.no_grad(), torch.cuda.stream(side):
+        want = net(x).clone()
+        side.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            out = net(x)
+    with torch.no_grad():
+        net.theta.add_(0.1)
+        net(x)
+    for _ in range(3):
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
