@@ -59,6 +59,10 @@ extern "C" {
 #define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs, */
                                  /* or from n = 16 on one wavefront per strip of columns         */
 
+#define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix */
+                                 /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it where it is */
+                                 /* the faster one, and givens_last_kernel then still names the family of the shape    */
+
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */
                                /* coefficient work (n (n-1)/2 * B >= 1e9 updates; always in givens_prepare),    */
@@ -195,6 +199,10 @@ int givens_forward_prepared(int64_t token, int64_t B, const float *X, float *Y, 
 int givens_build_prepared(int64_t token, float *U, void *stream);
 int givens_backward_prepared(int64_t token, int64_t B, const float *Y, const float *G, float *dX, float *dtheta,
                              void *stream);
+
+/* 1 when a forward and a backward call on B columns gain by prepared tables, 0 when one of them is faster as a plain call
+ * (large sweeps that run as tiles on the matrix cores keep no tables), or a negative error code. */
+int givens_prepare_pays(int n, int m, int64_t B);
 
 /*
  * One matrix, many batches (float).  givens_pack lays an n x n matrix (say U of givens_build) out for the matrix cores in

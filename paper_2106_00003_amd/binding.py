@@ -14,7 +14,7 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgivens_rr.so")
 
-KERNEL_AUTO, KERNEL_LDS, KERNEL_CAROUSEL, KERNEL_COLUMN = 0, 1, 2, 3
+KERNEL_AUTO, KERNEL_LDS, KERNEL_CAROUSEL, KERNEL_COLUMN, KERNEL_TILES = 0, 1, 2, 3, 4
 FORM_AUTO, FORM_STANDARD, FORM_SCALED, FORM_LIFTED, FORM_RANGE = 0, 1, 2, 3, 4
 REDUCTION_AUTO, REDUCTION_TWO_STAGE, REDUCTION_GRAM = 0, 1, 3
 PREPARE_FORWARD, PREPARE_BACKWARD, PREPARE_BACKWARD_WIDE = 1, 2, 4
@@ -77,6 +77,7 @@ def lib():
     L.givens_forward_prepared.argtypes = [i64, i64, vp, vp, vp]
     L.givens_build_prepared.argtypes = [i64, vp, vp]
     L.givens_backward_prepared.argtypes = [i64, i64, vp, vp, vp, vp, vp]
+    L.givens_prepare_pays.argtypes = [i32, i32, i64]
     L.givens_packed_bytes.argtypes, L.givens_packed_bytes.restype = [i32], i64
     L.givens_pack.argtypes = [i32, vp, vp, vp]
     L.givens_apply_packed.argtypes = [i32, i64, vp, vp, vp, vp]
@@ -300,6 +301,14 @@ def givens_build(theta, n: int, U=None, stream=None):
     fn = getattr(lib(), "givens_build" + _suffix(theta))
     _check(fn(n, _dev(theta, "theta"), _dev(U, "U", theta.dtype), _stream_ptr(stream)), "givens_build")
     return U
+
+
+def givens_prepare_pays(n: int, m, B: int) -> bool:
+    """Whether a forward and a backward call on B columns gain by prepared tables (m None: unrestricted)."""
+    rc = lib().givens_prepare_pays(n, n - 1 if m is None else m, B)
+    if rc < 0:
+        raise GivensError(rc, "givens_prepare_pays")
+    return bool(rc)
 
 
 def givens_pack(U, packed=None, stream=None):

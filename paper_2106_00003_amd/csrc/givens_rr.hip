@@ -17,6 +17,7 @@
 #include "lds_kernels.hpp"
 #include "product_kernels.hpp"
 #include "rr_index.h"
+#include "tile_host.hpp"
 #include "unitary_kernels.hpp"
 
 namespace givens {
@@ -78,6 +79,7 @@ struct Workspace {
     Buffer gram;        // Gram form: slices of C = Y G^T, rows x rows floats each
     Buffer matrix;      // wide batches: U or U^T, rows x rows floats
     Buffer pieces;      // ... and its pieces in operand order (product_kernels.hpp)
+    Buffer tile_table, tile_matrices, tile_pieces, tile_s;   // tiled sweeps (tile_host.hpp)
     Buffer columns;     // ... and a copy of the columns at work when a result overwrites its operand
     Buffer map;         // restricted parametrisation / odd n: index in theta of every entry of E, or -1
     Buffer map_counts;  // free pairs per block (scratch of the map kernels)
@@ -86,7 +88,7 @@ struct Workspace {
     Buffer u_q, u_psi, u_sgn, u_rot, u_phs, u_orient, u_fin;
     int map_rows = 0, map_m = 0; // the (row count, m) the map was built for
     Prepared prepared;
-    Buffer *all[25] = {&flag, &scale, &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
+    Buffer *all[29] = {&tile_table, &tile_matrices, &tile_pieces, &tile_s, &flag, &scale, &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
                        &matrix, &pieces, &columns, &partial, &zeros, &sink, &gram, &map,
                        &u_q, &u_psi, &u_sgn, &u_rot, &u_phs, &u_orient, &u_fin, &chain, &chain_flags};
 };
@@ -582,6 +584,10 @@ int lds_forward(int n, int rows, long long B, const typename Pair2<T>::type *tab
 struct Families {
     bool carousel = false, column = false;  // neither: LDS strip family
 };
+int family_code(const Families &fam)
+{
+    return fam.carousel ? GIVENS_KERNEL_CAROUSEL : fam.column ? GIVENS_KERNEL_COLUMN : GIVENS_KERNEL_LDS;
+}
 template <typename T>
 int pick_forward_family(int n, long long B, int choice, Families *out)
 {
@@ -589,6 +595,7 @@ int pick_forward_family(int n, long long B, int choice, Families *out)
     const bool can_column = std::is_same<T, float>::value && n <= kColumnFamilyMaxN;
     if (choice == GIVENS_KERNEL_CAROUSEL && !can_carousel) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_COLUMN && !can_column) return GIVENS_ERR_UNSUPPORTED;
+    if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = !out->carousel && can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
@@ -600,6 +607,7 @@ int pick_backward_family(int n, long long B, int choice, Families *out)
     const bool can_column = std::is_same<T, float>::value && n <= kColumnFamilyMaxN;
     if (choice == GIVENS_KERNEL_CAROUSEL && !can_carousel) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_COLUMN && !can_column) return GIVENS_ERR_UNSUPPORTED;
+    if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
     // the family that sweeps (the n x n operand of the Gram form, or all B columns); the column family has
     // no reverse sweep of its own and borrows the LDS family's
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
@@ -849,7 +857,8 @@ int options_from(const givens_options *o, CallOptions *out)
     *out = default_options();
     if (!o) return GIVENS_OK;
     auto in = [](int v, std::initializer_list<int> ok) { return std::find(ok.begin(), ok.end(), v) != ok.end(); };
-    if (!in(o->kernel, {GIVENS_KERNEL_AUTO, GIVENS_KERNEL_LDS, GIVENS_KERNEL_CAROUSEL, GIVENS_KERNEL_COLUMN}) ||
+    if (!in(o->kernel, {GIVENS_KERNEL_AUTO, GIVENS_KERNEL_LDS, GIVENS_KERNEL_CAROUSEL, GIVENS_KERNEL_COLUMN,
+                        GIVENS_KERNEL_TILES}) ||
         !in(o->rotation_form, {GIVENS_FORM_AUTO, GIVENS_FORM_STANDARD, GIVENS_FORM_LIFTED, GIVENS_FORM_RANGE}) ||
         !in(o->reduction, {GIVENS_REDUCTION_AUTO, GIVENS_REDUCTION_TWO_STAGE, GIVENS_REDUCTION_GRAM}))
         return GIVENS_ERR_UNSUPPORTED;
@@ -863,6 +872,108 @@ void invalidate_prepared(Workspace &ws, bool fwd, bool rev)
     if (fwd) ws.prepared.fwd = false;
     if (rev) ws.prepared.rev = false;
     if (!ws.prepared.fwd && !ws.prepared.rev) ws.prepared.token = 0;
+}
+
+// ---- tiled sweeps (float): see tile_kernels.hpp
+// Whether a call takes them: chosen, or nothing chosen and its family's sweep is slower.  `swept`: columns that the family
+// would sweep.  Measured, family against tiles in us (the backward call with dX):
+//   no carousel shape: forward n = 514, B = 64 367 / 135, n = 1006, B = 64 912 / 182, n = 3002, B = 3002 13944 / 1449;
+//     backward n = 514, B = 64 368 / 389, 512 439 / 397, n = 1006, B = 64 878 / 538, n = 3002, B = 3002 43233 / 4117
+//   3, 5 or 7 slots per lane, or more than eight wavefronts: forward n = 1002, B = 64 205 / 181, 1002 236 / 203, n = 1022
+//     (7 slots), B = 1022 262 / 276, n = 2050, B = 2050 1088 / 784, n = 4098, B = 4096 4684 / 2909; backward n = 1002,
+//     B = 64 330 / 538, 1002 656 / 590, n = 2046, B = 512 1483 / 1565, n = 4098, B = 1024 6311 / 5979, 4096 19190 / 8186
+//   2, 4 or 8 slots: forward n = 1024, B = 1024 196 / 239, n = 2048, B = 2048 723 / 741, n = 4096, B = 4096 2328 / 2931;
+//     backward n = 1024, B = 64 351 / 569, 1024 690 / 647, n = 2048, B = 512 1528 / 1565, 2048 2293 / 1933, n = 4096,
+//     B = 1024 4405 / 5831, 4096 9068 / 7644
+bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
+{
+    if (opt.kernel == GIVENS_KERNEL_TILES) return true;
+    if (opt.kernel != GIVENS_KERNEL_AUTO || opt.form != GIVENS_FORM_AUTO) return false;
+    if (backward && opt.reduction == GIVENS_REDUCTION_TWO_STAGE) return false;
+    if (n < 400 || n > kTileMaxN) return false;
+    CarouselShape f{}, b{};
+    const bool has = carousel_shape_for(n, &f) && carousel_bwd_shape_for(n, &b);
+    if (!has) return !backward || n >= 700 || 10 * swept >= 9LL * n;
+    if (n < 900) return false;
+    const bool slow = f.M % 2 || f.WAVES > 8;
+    if (!backward) return slow && (f.M != 7 || n >= 1900);
+    if (slow) return 10 * swept >= 6LL * n;
+    return n <= 4096 && 10 * swept >= 9LL * n;
+}
+int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, TileBuffers *out)
+{
+    if (int rc = grow(ws.tile_table, tile_table_bytes(g))) return rc;
+    if (int rc = grow(ws.tile_matrices, tile_matrices_bytes(g))) return rc;
+    if (int rc = grow(ws.tile_pieces, tile_pieces_bytes(g))) return rc;
+    if (gradient)
+        if (int rc = grow(ws.tile_s, tile_s_bytes(g))) return rc;
+    *out = TileBuffers{reinterpret_cast<double2 *>(ws.tile_table.ptr), reinterpret_cast<float *>(ws.tile_matrices.ptr),
+                       ws.tile_pieces.ptr, reinterpret_cast<float *>(ws.tile_s.ptr)};
+    return GIVENS_OK;
+}
+// Y = U X or U^T X (forward = false) by the tiles' matrices, which are there; a wide batch through U itself
+int run_tiles_apply(Workspace &ws, int dev, const Problem &pb, const TilePlan &g, const TileBuffers &b, long long B,
+                    const float *X, float *Y, bool forward, hipStream_t stream)
+{
+    int cus = 0;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    if (X && B >= kProductMinRatio * pb.rows && B >= kProductMinB) {
+        ProductStorage st;
+        if (int rc = workspace_product_storage(ws, pb.rows, B, X == Y, &st)) return rc;
+        {
+            Span span(1, stream);
+            tiles_apply(g, cus, pb.rows, pb.m, pb.rows, b, nullptr, st.matrix, forward, stream);
+        }
+        return apply_matrix(st, dev, pb.rows, B, X, Y, stream);
+    }
+    Span span(1, stream);
+    tiles_apply(g, cus, pb.rows, pb.m, B, b, X, Y, forward, stream);
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+int tiles_forward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *X, float *Y,
+                  bool transpose, hipStream_t stream)
+{
+    if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
+    const TilePlan g = tile_plan(pb.n, kTilePad);
+    TileBuffers b;
+    if (int rc = tile_storage(ws, g, false, &b)) return rc;
+    {
+        Span span(0, stream);
+        tiles_build(g, theta, pb.map, pb.m, b, !transpose, stream);
+    }
+    t_state.last_flag = nullptr;
+    return run_tiles_apply(ws, dev, pb, g, b, B, X, Y, !transpose, stream);
+}
+int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *Y, const float *G,
+                   float *dX, float *dtheta, hipStream_t stream)
+{
+    if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
+    const TilePlan g = tile_plan(pb.n, kTilePad);
+    TileBuffers b;
+    if (int rc = tile_storage(ws, g, true, &b)) return rc;
+    int cus = 0;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const GramPlan plan = gram_plan(pb.rows, B, cus);
+    if (int rc = grow(ws.gram, (size_t)plan.slices * pb.rows * pb.rows * sizeof(float))) return rc;
+    float *C = reinterpret_cast<float *>(ws.gram.ptr);
+    {
+        Span span(0, stream);
+        tiles_build(g, theta, pb.map, pb.m, b, false, stream);
+    }
+    {
+        Span span(3, stream);
+        gram_matrix(pb.rows, B, plan, Y, G, C, stream);
+    }
+    {
+        Span span(2, stream);
+        tiles_gradient(g, pb.rows, pb.m, pb.map, b, C, dtheta, stream);
+        GIVENS_HIP(hipGetLastError());
+    }
+    t_state.last_flag = nullptr;
+    t_state.last_reduction = GIVENS_REDUCTION_GRAM;
+    t_state.last_chains = 0;
+    return dX ? run_tiles_apply(ws, dev, pb, g, b, B, G, dX, false, stream) : GIVENS_OK;
 }
 
 // rows, m: see Problem.  The unrestricted entry points pass an even rows and m = rows - 1.
@@ -889,9 +1000,17 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
     timing_begin_call();
     if (no_alloc) t_state.timing_valid = false; // event pairs are created on demand: not here
     Families fam;
-    if (int rc = pick_forward_family<T>(n, B, opt.kernel, &fam)) return rc;
+    if (opt.kernel != GIVENS_KERNEL_TILES)
+        if (int rc = pick_forward_family<T>(n, B, opt.kernel, &fam)) return rc;
     Coefs<T> coefs;
     const long long swept = identity ? B : swept_columns<T>(fam, rows, B);
+    if constexpr (std::is_same<T, float>::value) {
+        if (!no_alloc && wants_tiles(opt, n, swept, false)) {
+            t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
+            return tiles_forward(*ws, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream);
+        }
+    }
+    if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
     const FormPolicy policy =
         form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept));
     if (no_alloc) {
@@ -979,10 +1098,18 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
     const int n = pb.n;
     timing_begin_call();
     Families fam;
-    if (int rc = pick_backward_family<T>(n, B, opt.kernel, &fam)) return rc;
+    if (opt.kernel != GIVENS_KERNEL_TILES)
+        if (int rc = pick_backward_family<T>(n, B, opt.kernel, &fam)) return rc;
+    const long long swept = wants_gram<T>(n, B, opt.reduction) ? rows : B;
+    if constexpr (std::is_same<T, float>::value) {
+        if (wants_tiles(opt, n, swept, true)) {
+            t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
+            return tiles_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
+        }
+    }
+    if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
     invalidate_prepared(*ws, false, true);
     Coefs<T> coefs;
-    const long long swept = wants_gram<T>(n, B, opt.reduction) ? rows : B;
     if (int rc = build_coefs<T>(*ws, ws->rev, pb, theta, false,
                                 form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept)),
                                 stream, &coefs))
@@ -1369,7 +1496,7 @@ int unitary_forward_impl(int n, long long B, const T *theta, const T *phi, const
     timing_begin_call();
     const bool carousel = std::is_same<T, float>::value && unitary_wants_carousel(n, g_kernel_choice);
     if (!carousel) {
-        if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+        if (g_kernel_choice != GIVENS_KERNEL_AUTO && g_kernel_choice != GIVENS_KERNEL_LDS) return GIVENS_ERR_UNSUPPORTED;
         if (unitary_strip_width<T>(n, B, 1) == 0) return GIVENS_ERR_UNSUPPORTED;
     }
     Workspace *ws = nullptr;
@@ -1449,7 +1576,7 @@ int unitary_backward_impl(int n, long long B, const T *theta, const T *phi, cons
     timing_begin_call();
     const bool carousel = std::is_same<T, float>::value && unitary_wants_carousel(n, g_kernel_choice);
     if (!carousel) {
-        if (g_kernel_choice == GIVENS_KERNEL_CAROUSEL || g_kernel_choice == GIVENS_KERNEL_COLUMN) return GIVENS_ERR_UNSUPPORTED;
+        if (g_kernel_choice != GIVENS_KERNEL_AUTO && g_kernel_choice != GIVENS_KERNEL_LDS) return GIVENS_ERR_UNSUPPORTED;
         if (unitary_strip_width<T>(n, B, 2) == 0) return GIVENS_ERR_UNSUPPORTED;
     }
     Workspace *ws = nullptr;
@@ -1600,6 +1727,21 @@ int givens_backward_prepared(int64_t token, int64_t B, const float *Y, const flo
     return givens::backward_prepared_impl(token, B, Y, G, dX, dtheta, stream, givens::default_options());
 }
 
+int givens_prepare_pays(int n, int m, int64_t B)
+{
+    using namespace givens;
+    if (int rc = check_restricted(n, m)) return rc;
+    if (B < 1) return GIVENS_ERR_BAD_B;
+    const int padded = n + (n & 1);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    const CallOptions opt = default_options();
+    Families fam;
+    if (opt.kernel == GIVENS_KERNEL_TILES) return 0;
+    if (pick_forward_family<float>(padded, B, opt.kernel, &fam)) return 1;   // (the calls themselves will say so)
+    return wants_tiles(opt, padded, swept_columns<float>(fam, n, B), false) ||
+           wants_tiles(opt, padded, wants_gram<float>(padded, B, opt.reduction) ? n : B, true) ? 0 : 1;
+}
+
 int64_t givens_packed_bytes(int n)
 {
     if (n < 1 || n > givens::kMaxRows) return GIVENS_ERR_BAD_N;
@@ -1733,7 +1875,7 @@ const char *givens_error_string(int code)
 int givens_set_kernel(int which)
 {
     if (which != GIVENS_KERNEL_AUTO && which != GIVENS_KERNEL_LDS && which != GIVENS_KERNEL_CAROUSEL &&
-        which != GIVENS_KERNEL_COLUMN)
+        which != GIVENS_KERNEL_COLUMN && which != GIVENS_KERNEL_TILES)
         return GIVENS_ERR_UNSUPPORTED;
     std::lock_guard<std::mutex> lock(givens::g_mutex);
     const int prev = givens::g_kernel_choice;

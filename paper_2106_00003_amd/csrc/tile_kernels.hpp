@@ -1,0 +1,975 @@
+// Tiled sweeps (float): the blocks of rotations regrouped into tiles that run on the matrix cores.
+//
+// Order.  Let m = n - 1 (odd).  Give ring label L >= 1 the index a with label(a) = n - 1 - 2a for a < n/2 and
+// 2m - 2a from there on (so the low half runs through the odd labels, the high half through the even ones).  Block k
+// of the circle method then pairs a and b with a + b = k (mod m), and row 0, which the circle method holds, with the a
+// of 2a = k (mod m).  Rotations that share no row commute, so any order in which every row meets its partners in block
+// order gives the same product.  Cut both halves into P pieces of s indices: the rotations between piece i and piece j
+// (i < j) are a tile, a + b <= m - 1 its late and a + b >= m its early part, and stage t = -2 (or -1) ... 2P - 1 holds
+// the late parts with i + j = t and the early parts with i + j = t + 2P: P tiles that share no row.  The pairs inside
+// piece i and inside piece i + P, whose rotations with row 0 alternate, are one special tile of stage 2i.
+//
+// A tile's rotations act on at most 2s + 1 <= PAD rows, so they are one PAD x PAD orthogonal matrix: built here with
+// one lane per column, in float64 (as fast as float32 on this chip), and applied to any number of columns as a product
+// of bf16 pieces (split_bf16.hpp).  A rotation then costs 8 operations per column on the matrix cores instead of
+// 2 to 4 vector instructions, and the chain of n - 1 dependent blocks becomes one of about n / s products.
+//
+// Gradient.  With S = Z G^T - G Z^T (antisymmetric) of the strips z and gbar before a tile, the share of a pair (i, j),
+// i < j, is S_ij in the frame of its rotation, and a rotation takes S to R S R^T.  So the reverse sweep needs neither
+// strip: it starts from S = C - C^T, C = Y G^T, takes S through the stages (S <- A S A^T, two products per pair of
+// tiles, half of them by antisymmetry) and leaves every tile's own PAD x PAD block behind; the sums of all tiles then
+// come from those blocks in one launch.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "rr_index.h"
+#include "small_trig.hpp"
+#include "split_bf16.hpp"
+#include "tile_host.hpp"
+
+namespace givens {
+
+enum { kTileLate = 0, kTileEarly = 1, kTileSpecial = 2, kTileNone = 3 };
+struct Tile {
+    int i, j, kind;
+    int a0, na, b0, nb;   // indices of the two pieces
+};
+__host__ __device__ inline void tile_piece(const TilePlan &g, int i, int *start, int *count)
+{
+    const int lo = i < g.P ? i * g.s : g.h + (i - g.P) * g.s, end = i < g.P ? g.h : g.m;
+    const int c = end - lo;
+    *start = lo;
+    *count = c < 0 ? 0 : (c < g.s ? c : g.s);
+}
+__host__ __device__ inline int tile_label(const TilePlan &g, int a) { return a < g.h ? g.n - 1 - 2 * a : 2 * g.m - 2 * a; }
+// tile u of stage number st (0-based).  kTileNone: the pieces P - 1 and 2P - 1, which stage -2 leaves alone.
+__host__ __device__ inline Tile tile_at(const TilePlan &g, int st, int u)
+{
+    Tile x;
+    const int t = st + g.first, I = 2 * g.P;
+    if (t < 0) {
+        x.i = u;
+        x.j = t + I - u;
+        x.kind = kTileEarly;
+        if (t == -2 && u == g.P - 1) {
+            x.j = I - 1;
+            x.kind = kTileNone;
+        }
+    } else if (!(t & 1) && u == 0) {
+        x.i = t / 2;
+        x.j = t / 2 + g.P;
+        x.kind = kTileSpecial;
+    } else {
+        const int v = (t & 1) ? u : u - 1, late = (t + 1) / 2;
+        x.kind = v < late ? kTileLate : kTileEarly;
+        x.i = v < late ? v : t + 1 + (v - late);
+        x.j = v < late ? t - v : I - 1 - (v - late);
+    }
+    tile_piece(g, x.i, &x.a0, &x.na);
+    tile_piece(g, x.j, &x.b0, &x.nb);
+    return x;
+}
+// Row (label) of local index r of tile u, or -1: piece i from 0, piece j from pad / 2, and at pad - 1 row 0, which goes
+// with tile 0 of every stage (an identity row of its matrix unless the tile is special).
+__host__ __device__ inline int tile_row(const TilePlan &g, const Tile &x, int u, int r)
+{
+    const int q = r - g.pad / 2;
+    if (q < 0) return r < x.na ? tile_label(g, x.a0 + r) : -1;
+    if (q < x.nb) return tile_label(g, x.b0 + q);
+    return r == g.pad - 1 && u == 0 ? 0 : -1;
+}
+// Restricted parametrisation (pairs (i, j), i < free_rows): does the tile hold no free pair?  (labels go down by 2 along
+// a piece)
+__host__ __device__ inline bool tile_is_identity(const TilePlan &g, const Tile &x, int free_rows)
+{
+    if (x.kind == kTileNone) return true;
+    if (x.kind == kTileSpecial) return false;
+    const int la = x.na ? tile_label(g, x.a0 + x.na - 1) : g.n, lb = x.nb ? tile_label(g, x.b0 + x.nb - 1) : g.n;
+    return la >= free_rows && lb >= free_rows;
+}
+
+// index in E of the pair (a, b), and of the pair of a with row 0
+__device__ __forceinline__ long long tile_pair_entry(const TilePlan &g, int a, int b)
+{
+    int k = a + b;
+    if (k >= g.m) k -= g.m;
+    const int d = a < b ? b - a : a - b, p = d < g.m - d ? d : g.m - d;
+    return (long long)k * g.h + p;
+}
+__device__ __forceinline__ long long tile_held_entry(const TilePlan &g, int a)
+{
+    int k = 2 * a;
+    if (k >= g.m) k -= g.m;
+    return (long long)k * g.h;
+}
+__device__ __forceinline__ bool tile_has_pair(const TilePlan &g, const Tile &x, int a, int b)
+{
+    return x.kind == kTileSpecial || (a + b >= g.m) == (x.kind == kTileEarly);
+}
+// cos and sine of an angle in float64, to 1e-16 up to 1e5 (reduced by multiples of pi / 2)
+__device__ __forceinline__ double2 tile_sincos(double th)
+{
+    double s, c;
+    if (fabs(th) <= 1.0e5) {
+        const double k = rint(th * 0.63661977236758134308);
+        const double r = fma(-k, 6.123233995736766036e-17, fma(-k, 1.5707963267948965580, th));
+        const double sr = sin_small(r), cr = cos_small(r);
+        const int quarter = (int)k & 3;
+        s = quarter & 1 ? cr : sr;
+        c = quarter & 1 ? sr : cr;
+        if (quarter & 2) s = -s;
+        if (quarter == 1 || quarter == 2) c = -c;
+    } else {
+        sincos(th, &s, &c);
+    }
+    double2 out;
+    out.x = c;
+    out.y = s;
+    return out;
+}
+
+// Coefficient table of the tiles, rows of 64 (S + 1 used) entries (cos, sine; the sine negated when the first row has the
+// larger label; (1, 0) for a pair that is bypassed or not in the tile).  Row r of an ordinary tile: row r of piece i with
+// every row of piece j, in order.  Row r of a special tile, for piece i and then (s rows further on) for piece i + P: with
+// the row slot + 1 places before it, and in the last of the S + 1 entries with row 0.  First the P special tiles with 2 s
+// rows each, then all tiles with s rows each (those of the special ones unused).
+__device__ __forceinline__ const double2 *tile_coef_table(const TilePlan &g, const double2 *table, int st, int u, bool special,
+                                                          int width)
+{
+    const size_t row = special ? (size_t)((st + g.first) / 2) * 2 * g.s : (size_t)g.s * (2 * g.P + (size_t)st * g.P + u);
+    return table + row * width;
+}
+__global__ __launch_bounds__(256) void tile_coef_kernel(TilePlan g, const float *__restrict__ theta,
+                                                        const int *__restrict__ map, int free_rows, long long entries,
+                                                        double2 *__restrict__ table)
+{
+    const int width = g.pad / 2;
+    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (id >= entries) return;
+    const int slot = (int)(id % width);
+    long long row = id / width;
+    const bool special = row < 2LL * g.P * g.s;
+    long long e = -1;
+    bool ordered = false;
+    if (special) {
+        const int i = (int)(row / (2 * g.s)), which = (int)(row % (2 * g.s)) / g.s, r = (int)(row % g.s);
+        int start, count;
+        tile_piece(g, i + which * g.P, &start, &count);
+        if (r < count) {
+            const int a = start + r;
+            if (slot == width - 1) {
+                e = tile_held_entry(g, a);             // row 0 has the smaller label
+            } else if (slot < r) {
+                e = tile_pair_entry(g, a, a - 1 - slot);
+                ordered = tile_label(g, a) < tile_label(g, a - 1 - slot);
+            }
+        }
+    } else {
+        row -= 2LL * g.P * g.s;
+        const int r = (int)(row % g.s), tile = (int)(row / g.s);
+        const Tile x = tile_at(g, tile / g.P, tile % g.P);
+        if (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows)) return;   // never read
+        if (r < x.na && slot < x.nb) {
+            const int a = x.a0 + r, b = x.b0 + slot;
+            if (tile_has_pair(g, x, a, b)) {
+                e = tile_pair_entry(g, a, b);
+                ordered = tile_label(g, a) < tile_label(g, b);
+            }
+        }
+    }
+    if (e >= 0 && map) e = map[e];
+    double2 out;
+    out.x = 1.0;
+    out.y = 0.0;
+    if (e >= 0) {
+        out = tile_sincos((double)theta[e]);
+        if (!ordered) out.y = -out.y;
+    }
+    table[id] = out;
+}
+
+// the transposed rotation of rows p, q: p' = c p + s q, q' = c q - s p
+template <typename T, typename R2>
+__device__ __forceinline__ void tile_rotate(T &p, T &q, const R2 &cs)
+{
+    const T a = p, b = q;
+    p = fma(cs.x, a, cs.y * b);
+    q = fma(cs.x, b, -(cs.y * a));
+}
+
+constexpr int kTileChunk = 16;   // rows of the outer loop whose coefficients are in LDS at a time
+// address spaces of the loads that go from memory to LDS
+typedef __attribute__((address_space(3))) void *lds_ptr;
+typedef __attribute__((address_space(1))) const void *global_ptr;
+constexpr int kWaitForLoads = 0x0f70;   // s_waitcnt vmcnt(0): this wavefront's loads into LDS are there
+// Matrices of the tiles: A = the tile's transposed rotations in block order (the reverse sweep's matrix; its transpose is
+// the forward sweep's), float64, rounded once at the end.  A lane holds a column.  Ordinary tile: a workgroup's wavefronts
+// take its column blocks; the rows of piece j stay in registers, a row of piece i is fresh in every pass of the outer loop
+// and finished at its end.  Special tile: one workgroup per column block, a wavefront for each piece; a pass takes row r of
+// the piece through the rows before it, oldest first (finished rows sit in registers by age, newest in slot 0, so the code
+// is the same for every pass), then through row 0, which the two wavefronts hand to each other through LDS.
+// Bound by the chain of the rotations of a row (two dependent float64 instructions each).  Workgroups: special tiles first,
+// they take longest.
+template <int PAD>
+__global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const double2 *__restrict__ table, int free_rows,
+                                                            float *__restrict__ matrices)
+{
+    constexpr int S = tile_slots(PAD), PARTS = PAD / 64;
+    static_assert(PARTS == 2, "two wavefronts per workgroup");
+    __shared__ double2 coef[2][2][kTileChunk][S + 1];   // [which of two chunks][piece]
+    __shared__ double row0[64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool special = (int)blockIdx.x < g.P * PARTS;
+    const int id = (int)blockIdx.x - g.P * PARTS;
+    const int st = special ? 2 * ((int)blockIdx.x / PARTS) - g.first : id / g.P, u = special ? 0 : id % g.P;
+    const Tile x = tile_at(g, st, u);
+    if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
+    float *A = matrices + ((size_t)st * g.P + u) * PAD * PAD;
+    const double2 *mine = tile_coef_table(g, table, st, u, special, S + 1);
+    // rows of the chunk at i0: a wavefront brings its piece's (special) or every second one
+    auto load = [&](int i0) {
+        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk, chunk = (i0 / kTileChunk) & 1;
+        for (int r = special ? 0 : wave; r < rows; r += special ? 1 : 2)
+            __builtin_amdgcn_global_load_lds(
+                (global_ptr)(mine + (size_t)((special ? wave * g.s : 0) + i0 + r) * (S + 1) + lane),
+                (lds_ptr)(coef[chunk][special ? wave : 0][r]), 16, 0, 0);
+    };
+    double q[S];
+    load(0);
+    if (special) {
+        const int c = lane + 64 * ((int)blockIdx.x % PARTS), base = wave * (PAD / 2);
+#pragma unroll
+        for (int b = 0; b < S; ++b) q[b] = 0.0;
+        if (wave == 0) row0[lane] = c == PAD - 1 ? 1.0 : 0.0;
+        for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
+            __builtin_amdgcn_s_waitcnt(kWaitForLoads);
+            __syncthreads();   // the chunk is in LDS
+            const double2(*now)[S + 1] = coef[(i0 / kTileChunk) & 1][wave];
+            if (i0 + kTileChunk < g.s) load(i0 + kTileChunk);
+            const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
+            for (int r = 0; r < rows; ++r) {
+                const int i = i0 + r;
+                double cur = c == base + i ? 1.0 : 0.0;
+#pragma unroll
+                for (int s0 = (S - 1) / 8 * 8; s0 >= 0; s0 -= 8)
+                    if (s0 < i) {
+                        double2 cs[8];   // read together: one LDS latency for eight rotations
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) cs[v] = now[r][s0 + v];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int v = 7; v >= 0; --v)
+                            if (s0 + v < S) tile_rotate(cur, q[s0 + v], cs[v]);
+                    }
+                const double2 cs = now[r][S];
+                for (int turn = 0; turn < 2; ++turn) {     // row 0: piece i, then piece i + P
+                    if (turn == wave) {
+                        double held = row0[lane];
+                        tile_rotate(cur, held, cs);
+                        row0[lane] = held;
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int b = S - 1; b > 0; --b) q[b] = q[b - 1];
+                q[0] = cur;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < S; ++b)
+            if (b < g.s) A[(base + g.s - 1 - b) * PAD + c] = (float)q[b];
+        for (int r = g.s; r < PAD / 2; ++r)
+            if (base + r < PAD - 1) A[(base + r) * PAD + c] = 0.f;
+        if (wave == 1) A[(PAD - 1) * PAD + c] = (float)row0[lane];
+        return;
+    }
+    const int c = lane + 64 * wave;
+#pragma unroll
+    for (int b = 0; b < S; ++b) q[b] = (c == PAD / 2 + b && b < g.s) ? 1.0 : 0.0;
+    for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
+        __builtin_amdgcn_s_waitcnt(kWaitForLoads);
+        __syncthreads();
+        const double2(*now)[S + 1] = coef[(i0 / kTileChunk) & 1][0];
+        if (i0 + kTileChunk < g.s) load(i0 + kTileChunk);
+        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
+        double2 cs[2][8];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) cs[0][v] = now[0][v];
+        for (int r = 0; r < rows; ++r) {
+            double cur = c == i0 + r ? 1.0 : 0.0;
+            // eight rotations' coefficients are read while the eight before them run
+#pragma unroll
+            for (int b0 = 0; b0 < S + 1; b0 += 8) {
+                const double2(*next)[S + 1] = now + (b0 + 8 < S + 1 ? r : (r + 1 < rows ? r + 1 : r));
+#pragma unroll
+                for (int v = 0; v < 8; ++v) cs[(b0 / 8 + 1) & 1][v] = next[0][(b0 + 8) % (S + 1) + v];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int v = 0; v < 8; ++v)
+                    if (b0 + v < S) tile_rotate(cur, q[b0 + v], cs[(b0 / 8) & 1][v]);
+            }
+            A[(i0 + r) * PAD + c] = (float)cur;
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < S; ++b) A[(PAD / 2 + b) * PAD + c] = (float)q[b];
+    for (int r = g.s; r < PAD / 2; ++r) A[r * PAD + c] = 0.f;
+    A[(PAD - 1) * PAD + c] = (u == 0 && c == PAD - 1) ? 1.f : 0.f;
+}
+
+// A fragment of a tile's matrix: rows 32 f .. + 31, contraction indices 16 k .. + 15, as in product_kernels.hpp but with
+// the indices of a half wavefront in the order in which the matrix instructions leave their results in registers, so that
+// a result can be the next product's operand without a move between lanes.
+__device__ __forceinline__ int tile_k(int half, int j) { return (j & 3) + 4 * half + 8 * (j >> 2); }
+
+// matrices -> pieces, one wavefront per fragment; transposed: of the transposed matrices
+// (and one identity, behind the last tile, that all tiles without a free pair share)
+template <int PAD>
+__global__ __launch_bounds__(256) void tile_split_kernel(TilePlan g, int free_rows, const float *__restrict__ matrices,
+                                                         u32x4 *__restrict__ out, int transposed)
+{
+    constexpr int PER = (PAD / 32) * (PAD / 16);
+    const int lane = threadIdx.x & 63;
+    const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int tile = (int)(id / PER), f = (int)(id % PER), tiles = g.stages * g.P;
+    if (tile > tiles) return;
+    const bool identity = tile == tiles;
+    if (!identity && tile_is_identity(g, tile_at(g, tile / g.P, tile % g.P), free_rows)) return;
+    const float *A = matrices + (size_t)tile * PAD * PAD;
+    const int row = (f / (PAD / 16)) * 32 + (lane & 31), k0 = (f % (PAD / 16)) * 16;
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int k = k0 + tile_k(lane >> 5, j);
+        v[j] = identity ? (row == k ? 1.f : 0.f) : (transposed ? A[k * PAD + row] : A[row * PAD + k]);
+    }
+    const Split8 sp = split8(v);
+    u32x4 *o = out + id * 192 + lane;
+    o[0] = sp.h;
+    o[64] = sp.m;
+    o[128] = sp.l;
+}
+
+// where a tile's pieces are (in tiles)
+__device__ __forceinline__ size_t tile_piece_index(const TilePlan &g, int st, int u, bool identity)
+{
+    return identity ? (size_t)g.stages * g.P : (size_t)st * g.P + u;
+}
+
+struct TileApplyArgs {
+    TilePlan g;
+    int stage, rows, free_rows;
+    long long B;
+    const u32x4 *pieces;
+    const float *X;      // nullptr: the identity
+    float *Y;            // X, or another array: then every row is written (first stage of a sweep)
+    long long chunk;     // columns per workgroup
+};
+
+// One stage on B columns: rows of each tile <- matrix * rows.  A workgroup takes one tile and a run of columns, a wavefront
+// 32 rows of the result with its part of the matrix in registers throughout.  Per step of 32 NF columns a wavefront brings
+// 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange), a step ahead,
+// and puts the pieces into LDS as fragments.
+template <int PAD, int NF>
+__global__ __launch_bounds__(2 * PAD, 2) void tile_apply_kernel(TileApplyArgs a)
+{
+    constexpr int KF = PAD / 16, BN = 32 * NF, GROUPS = 64 / BN, ROWS = 32 / GROUPS;
+    __shared__ u32x4 panel[KF][NF][3][64];
+    const TilePlan &g = a.g;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int u = blockIdx.x % g.P;
+    const long long n0 = (long long)(blockIdx.x / g.P) * a.chunk, n1 = n0 + a.chunk < a.B ? n0 + a.chunk : a.B;
+    const Tile x = tile_at(g, a.stage, u);
+    const bool identity = tile_is_identity(g, x, a.free_rows);
+    if (n0 >= a.B || (a.X == a.Y && identity)) return;
+    // this wavefront's 32 rows: labels first, first - 2, ...; `count` of them are there, row 0 may stand at the end
+    const int local = 32 * wave, in_piece = local % (PAD / 2);
+    const bool second = local >= PAD / 2;
+    const int count = (second ? x.nb : x.na) - in_piece;
+    const int first = tile_label(g, (second ? x.b0 : x.a0)) - 2 * in_piece;
+    const bool has_held = u == 0 && local == PAD - 32;
+    const int skip = first >= a.rows ? 1 : 0;          // the added row of an odd problem is the first of its piece
+
+    u32x4 fa[KF][1][3];
+    const u32x4 *ap = a.pieces + tile_piece_index(g, a.stage, u, identity) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+#pragma unroll
+    for (int kf = 0; kf < KF; ++kf)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) fa[kf][0][p] = ap[kf * 192 + 64 * p];
+
+    // a lane brings ROWS rows of one column: all 32 (BN = 64), or the 8 + 8 rows of its half (BN = 32)
+    float xr[ROWS];
+    auto row_in = [&](int q) { return GROUPS == 1 ? q : 16 * (q >> 3) + tile_k(half, q & 7); };
+    auto fetch = [&](long long c0) {
+        long long col = c0 + (lane & (BN - 1));
+        col = col < n1 ? col : n1 - 1;
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+            const int r = row_in(q);
+            const bool there = r < count && r >= skip, held = has_held && r == 31;
+            const int row = there ? first - 2 * r : 0;
+            const float v = a.X ? a.X[(long long)row * a.B + col] : (col == row ? 1.f : 0.f);
+            xr[q] = there || held ? v : 0.f;
+        }
+    };
+    auto stash = [&]() {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int h = 0; h < (GROUPS == 1 ? 2 : 1); ++h) {
+                float v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = xr[GROUPS == 1 ? 16 * f + tile_k(h, q) : 8 * f + q];
+                const Split8 sp = split8(v);
+                const int nf = GROUPS == 1 ? lane >> 5 : 0, at = GROUPS == 1 ? 32 * h + l32 : lane;
+                panel[2 * wave + f][nf][0][at] = sp.h;
+                panel[2 * wave + f][nf][1][at] = sp.m;
+                panel[2 * wave + f][nf][2][at] = sp.l;
+            }
+    };
+    fetch(n0);
+    for (long long c0 = n0; c0 < n1; c0 += BN) {
+        stash();
+        __syncthreads();
+        if (c0 + BN < n1) fetch(c0 + BN);
+        f32x16 acc[1][NF];
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
+#pragma unroll
+        for (int kf = 0; kf < KF; ++kf) {
+            u32x4 fb[NF][3];
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) fb[j][p] = panel[kf][j][p][lane];
+            mfma_split(fa[kf], fb, acc);
+        }
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const long long col = c0 + 32 * j + l32;
+            if (col < n1)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = 8 * (v >> 2) + 4 * half + (v & 3);
+                    if (r < count && r >= skip)
+                        a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][j][v];
+                    else if (has_held && r == 31)
+                        a.Y[col] = acc[0][j][v];
+                }
+        }
+        __syncthreads();
+    }
+}
+
+// ---- the gradient's matrix S: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on),
+// then row 0; places that hold no row are zero or never count.
+// S[p][q] = C[row p][row q] - C[row q][row p]; `second` (may be null): zeros, so that places without a row stay numbers
+__global__ __launch_bounds__(256) void tile_antisym_kernel(TilePlan g, int rows, const float *__restrict__ C,
+                                                           float *__restrict__ S, float *__restrict__ second)
+{
+    __shared__ float other[32][33];
+    const int ld = tile_ld(g);
+    const int p0 = blockIdx.y * 32, q0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    auto label = [&](int p) {
+        const int stride = tile_piece_stride(g), held = tile_held_place(g);
+        if (p >= held) return p == held ? 0 : -1;
+        int start, count;
+        tile_piece(g, p / stride, &start, &count);
+        const int r = p % stride;
+        if (r >= count) return -1;
+        const int l = tile_label(g, start + r);
+        return l < rows ? l : -1;
+    };
+    const int lp = label(p0 + tx), lq = label(q0 + tx);
+    for (int r = ty; r < 32; r += 8) {
+        const int lr = label(q0 + r);                       // other[r][tx] = C[row q0 + r][row p0 + tx]
+        other[r][tx] = (lr >= 0 && lp >= 0) ? C[(long long)lr * rows + lp] : 0.f;
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) {
+        const int lr = label(p0 + r);
+        const float mine = (lr >= 0 && lq >= 0) ? C[(long long)lr * rows + lq] : 0.f;
+        S[(long long)(p0 + r) * ld + q0 + tx] = mine - other[tx][r];
+        if (second) second[(long long)(p0 + r) * ld + q0 + tx] = 0.f;
+    }
+}
+
+struct TileTwoSidedArgs {
+    TilePlan g;
+    int stage, free_rows;
+    const u32x4 *pieces;   // of A (not transposed)
+    const float *in;       // S before the stage
+    float *out;            // S after it: the same array, or another one
+    float *blocks;         // [tile][PAD][PAD]: every tile's own block before its stage
+};
+
+// Places in S of the local rows of a pair's two tiles (-1: holds no row)
+template <int PAD>
+__device__ __forceinline__ void tile_places(const TilePlan &g, const Tile &x, const Tile &y, int ux, int uy, int (&place_x)[PAD],
+                                            int (&place_y)[PAD])
+{
+    const int stride = tile_piece_stride(g);
+    for (int r = threadIdx.x; r < 2 * PAD; r += 2 * PAD) {
+        const bool of_x = r < PAD;
+        const int q = r % PAD, u = of_x ? ux : uy, w = q - PAD / 2;
+        const int i = of_x ? x.i : y.i, j = of_x ? x.j : y.j;
+        int p = -1;
+        if (q < g.s) p = i * stride + q;
+        else if (w >= 0 && w < g.s) p = j * stride + w;
+        else if (q == PAD - 1 && u == 0) p = tile_held_place(g);
+        (of_x ? place_x : place_y)[q] = p;
+    }
+}
+// Rows 32 wave .. + 31 of a result R for columns of tile y, place cp: to (x, y) and, negated and transposed, to (y, x)
+template <int PAD>
+__device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, const f32x16 &R, int wave, int half, int cp,
+                                                bool own, bool first, const int (&place_x)[PAD])
+{
+    const int held = tile_held_place(g), ld = tile_ld(g);
+    if (cp < 0) return;
+#pragma unroll
+    for (int v = 0; v < 16; v += 4) {
+        const int r0 = 32 * wave + 8 * (v >> 2) + 4 * half;
+        const int p0 = place_x[r0];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int p = place_x[r0 + q];
+            if (p >= 0) S[(long long)p * ld + cp] = R[v + q];
+        }
+        if (!own) {
+            float *o = S + (long long)cp * ld;
+            if (p0 >= 0) {   // (a piece starts at a multiple of four places and owns whole groups of four)
+                f32x4 neg;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) neg[q] = -R[v + q];
+                *reinterpret_cast<f32x4 *>(o + p0) = neg;
+            }
+            if (r0 == PAD - 4 && first) o[held] = -R[v + 3];
+        }
+    }
+}
+
+// One stage of S <- A S A^T: a workgroup per pair of tiles (x, y), x <= y, in place.  First V = S A_y^T, a wavefront taking
+// 32 of its columns (its part of A_y in registers) and all rows, then R = A_x V, a wavefront taking 32 of its rows (its
+// part of A_x in registers).  The other operand of both products is cut into pieces once and shared through LDS, half the
+// contraction at a time: S as rows of eight values (a lane's are two groups of four consecutive columns), V as its
+// accumulators are.  Pairs without a rotation are left alone.  n = 4096: 40 to 48 us a stage.
+template <int PAD>
+__global__ __launch_bounds__(2 * PAD, 2) void tile_two_sided_kernel(TileTwoSidedArgs a)
+{
+    constexpr int MF = PAD / 32, KF = PAD / 16, KH = KF / 2;
+    __shared__ u32x4 panel[KH][MF][3][64];
+    __shared__ int place_x[PAD], place_y[PAD];
+    const TilePlan &g = a.g;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int ux = 0, uy = blockIdx.x;
+    while (uy >= g.P - ux) uy -= g.P - ux++;
+    uy += ux;
+    const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
+    const bool own = ux == uy;
+    const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
+    if (idx && idy) return;
+    const int stride = tile_piece_stride(g), ld = tile_ld(g);
+    tile_places<PAD>(g, x, y, ux, uy, place_x, place_y);
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+    __syncthreads();
+
+    // S: a wavefront brings 32 rows; a row that is none: A_x has zeros in its column
+    const int p_row = place_x[32 * wave + l32];
+    const float *row = a.in + (long long)(p_row < 0 ? 0 : p_row) * ld;
+    float *block = a.blocks + ((size_t)a.stage * g.P + ux) * PAD * PAD + (32 * wave + l32) * PAD;
+    f32x4 sr[KH][2];
+    auto fetch = [&](int h) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            const int local = 16 * (KH * h + k) + 4 * half;                 // half h of the contraction is piece i or j
+            const float *src = row + (h ? y.j : y.i) * stride + local - h * (PAD / 2);
+            sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
+            sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
+            if (h == 1 && k == KH - 1 && uy == 0) {
+                const float v = row[tile_held_place(g)];
+                if (half) sr[k][1][3] = v;
+            }
+        }
+    };
+    auto stash = [&](int k, const float(&v)[8]) {
+        const Split8 sp = split8(v);
+        panel[k][wave][0][lane] = sp.h;
+        panel[k][wave][1][lane] = sp.m;
+        panel[k][wave][2][lane] = sp.l;
+    };
+    auto stash_s = [&](int h) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            if (own) {
+                float *o = block + 16 * (KH * h + k) + 4 * half;
+                *reinterpret_cast<f32x4 *>(o) = sr[k][0];
+                *reinterpret_cast<f32x4 *>(o + 8) = sr[k][1];
+            }
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = sr[k][0][q];
+                v[4 + q] = sr[k][1][q];
+            }
+            stash(k, v);
+        }
+    };
+    u32x4 fm[KH][1][3];
+    auto load_matrix = [&](const u32x4 *p, int h) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) fm[k][0][q] = p[(KH * h + k) * 192 + 64 * q];
+    };
+    f32x16 V[MF][1], R[1][MF];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) V[i][0][v] = R[0][i][v] = 0.f;
+    fetch(0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        load_matrix(py, h);
+        stash_s(h);
+        __syncthreads();
+        if (h == 0) fetch(1);
+#pragma unroll
+        for (int k = 0; k < KH; ++k)
+#pragma unroll
+            for (int i = 0; i < MF; i += 2) {
+                u32x4 fs[2][3];
+#pragma unroll
+                for (int w = 0; w < 2; ++w)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) fs[w][q] = panel[k][i + w][q][lane];
+                f32x16(&pair)[2][1] = reinterpret_cast<f32x16(&)[2][1]>(V[i]);
+                mfma_split(fs, fm[k], pair);
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        load_matrix(px, h);
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            float v[8];
+            const int kf = KH * h + k;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = V[kf / 2][0][8 * (kf & 1) + q];
+            stash(k, v);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            u32x4 fv[MF][3];
+#pragma unroll
+            for (int j = 0; j < MF; ++j)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) fv[j][q] = panel[k][j][q][lane];
+            mfma_split(fm[k], fv, R);
+        }
+        if (h == 0) __syncthreads();
+    }
+    // (every wavefront has read its part of S by now: the barriers above)
+#pragma unroll
+    for (int j = 0; j < MF; ++j)
+        tile_store_both<PAD>(g, a.out, R[0][j], wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
+}
+
+// The same for few tiles, where a pair per workgroup leaves compute units idle: a workgroup takes 32 columns of tile y, a
+// wavefront 32 rows of tile x, and only V's pieces go through LDS.  The other workgroups of a pair still read what one
+// writes, so the result goes to another array, all of it.  Bound by latency: everything a product needs is on its way
+// before it starts.  n = 1024: 12 us a stage (19.7 with a pair per workgroup).
+template <int PAD>
+__global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileTwoSidedArgs a)
+{
+    constexpr int MF = PAD / 32, KF = PAD / 16;
+    __shared__ u32x4 panel[KF][3][64];
+    __shared__ int place_x[PAD], place_y[PAD];
+    const TilePlan &g = a.g;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = blockIdx.x % MF;
+    int ux = 0, uy = blockIdx.x / MF;
+    while (uy >= g.P - ux) uy -= g.P - ux++;
+    uy += ux;
+    const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
+    const bool own = ux == uy;
+    const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * tile_piece_words(PAD) + (size_t)part * KF * 192 + lane;
+    u32x4 fm[KF][1][3];
+#pragma unroll
+    for (int k = 0; k < KF; ++k)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) fm[k][0][q] = py[k * 192 + 64 * q];
+    tile_places<PAD>(g, x, y, ux, uy, place_x, place_y);
+    __syncthreads();
+
+    // this wavefront's rows of S (one that is none: A_x has zeros in its column)
+    const int stride = tile_piece_stride(g), ld = tile_ld(g);
+    const int p_row = place_x[32 * wave + l32];
+    const float *row = a.in + (long long)(p_row < 0 ? 0 : p_row) * ld;
+    f32x4 sr[KF][2];
+#pragma unroll
+    for (int k = 0; k < KF; ++k) {
+        const int local = 16 * k + 4 * half;
+        const float *src = row + (16 * k < PAD / 2 ? y.i * stride + local : y.j * stride + local - PAD / 2);
+        sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
+        sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
+    }
+    if (uy == 0) {
+        const float v = row[tile_held_place(g)];
+        if (half) sr[KF - 1][1][3] = v;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (own && part == 0) {
+        float *block = a.blocks + ((size_t)a.stage * g.P + ux) * PAD * PAD + (32 * wave + l32) * PAD + 4 * half;
+#pragma unroll
+        for (int k = 0; k < KF; ++k) {
+            *reinterpret_cast<f32x4 *>(block + 16 * k) = sr[k][0];
+            *reinterpret_cast<f32x4 *>(block + 16 * k + 8) = sr[k][1];
+        }
+    }
+    // two accumulators, even and odd fragments: one chain would wait for itself
+    f32x16 acc[2][1][1];
+    auto clear = [&]() {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][0][0][v] = acc[1][0][0][v] = 0.f;
+    };
+    clear();
+#pragma unroll
+    for (int k = 0; k < KF; ++k) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v[q] = sr[k][0][q];
+            v[4 + q] = sr[k][1][q];
+        }
+        const Split8 sp = split8(v);
+        const u32x4 fs[1][3] = {{sp.h, sp.m, sp.l}};
+        mfma_split(fs, fm[k], acc[k & 1]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < KF; ++k)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) fm[k][0][q] = px[k * 192 + 64 * q];
+    __builtin_amdgcn_sched_barrier(0);
+    // V as operand of the second product: these 32 rows are contraction indices 32 wave .. + 31 of it
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = acc[0][0][0][8 * f + q] + acc[1][0][0][8 * f + q];
+        const Split8 sp = split8(v);
+        panel[2 * wave + f][0][lane] = sp.h;
+        panel[2 * wave + f][1][lane] = sp.m;
+        panel[2 * wave + f][2][lane] = sp.l;
+    }
+    __syncthreads();
+    clear();
+#pragma unroll
+    for (int k = 0; k < KF; ++k) {
+        const u32x4 fv[1][3] = {{panel[k][0][lane], panel[k][1][lane], panel[k][2][lane]}};
+        mfma_split(fm[k], fv, acc[k & 1]);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[0][0][0][v] += acc[1][0][0][v];
+    tile_store_both<PAD>(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
+}
+
+// 64 values per lane -> lane l has the sum over all lanes of value l
+__device__ __forceinline__ float tile_reduce64(float (&v)[64])
+{
+    const int lane = threadIdx.x & 63;
+    float w[32];
+#pragma unroll
+    for (int r = 0; r < 32; ++r) {
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 32]), false, false);
+        w[r] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[r]), __float_as_uint(w[r + 16]), false, false);
+        w[r] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    }
+    // within a row of 16 lanes: keep one value of a pair, hand the other to the lane that keeps it
+    auto step = [&](auto ctrl, int bit, int count) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            if (r < count) {
+                const bool up = (lane & bit) != 0;
+                const float keep = up ? w[r + count] : w[r], give = up ? w[r] : w[r + count];
+                w[r] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), decltype(ctrl)::value, 0xf, 0xf, true));
+            }
+    };
+    step(std::integral_constant<int, 0x128>{}, 8, 8);   // row_ror:8: lane ^ 8
+    step(std::integral_constant<int, 0x141>{}, 4, 4);   // row_half_mirror: lane ^ 7
+    step(std::integral_constant<int, 0x1b>{}, 2, 2);    // quad_perm 3 2 1 0: lane ^ 3
+    step(std::integral_constant<int, 0xb1>{}, 1, 1);    // quad_perm 1 0 3 2: lane ^ 1
+    return w[0];
+}
+
+// The sums of all tiles' pairs from the blocks the stages have left: the reverse sweep of a tile on the strips
+// W = A S and A (columns of the block, one per lane); the share of rows a, b is W_a . A_b, summed over the lanes.  A
+// workgroup is two groups of PAD threads: two ordinary tiles, or the two pieces of a special one (which hand row 0 to each
+// other as in the build kernel).
+template <int PAD>
+__global__ __launch_bounds__(2 * PAD, 1) void tile_gradient_kernel(TilePlan g, const double2 *__restrict__ table,
+                                                                   const int *__restrict__ map, int free_rows,
+                                                                   const float *__restrict__ blocks, float *__restrict__ dtheta)
+{
+    constexpr int S = tile_slots(PAD), WAVES = PAD / 64;
+    __shared__ float2 coefs[2][kTileChunk][S + 1];
+    __shared__ float sums[2][kTileChunk][WAVES][64];
+    __shared__ float2 row0[PAD];
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / PAD);
+    const bool special = (int)blockIdx.x < g.P;
+    const int id = special ? 0 : 2 * ((int)blockIdx.x - g.P) + group, tiles = g.stages * g.P;
+    const int st = special ? 2 * (int)blockIdx.x - g.first : id / g.P, u = special ? 0 : id % g.P;
+    const Tile x = tile_at(g, id < tiles ? st : 0, u);
+    const bool active = special || (id < tiles && x.kind != kTileSpecial && !tile_is_identity(g, x, free_rows));
+    if (__syncthreads_or(active ? 1 : 0) == 0) return;
+    const float *blk = blocks + (active ? ((size_t)st * g.P + u) * PAD * PAD : 0);
+    const int c = threadIdx.x % PAD, lane = c & 63, wave = c >> 6;
+    const double2 *mine = tile_coef_table(g, table, active ? st : 2 - g.first, active ? u : 0, special || !active, S + 1) +
+                          (special ? (size_t)group * g.s * (S + 1) : 0);
+    float2(*coef)[S + 1] = coefs[group];
+    auto load = [&](int i0) {
+        constexpr int PER = kTileChunk * (S + 1) / PAD;
+        double2 v[PER];
+        const double2 *src = mine + (size_t)i0 * (S + 1);
+        const int last = (g.s - i0) * (S + 1) - 1;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) v[q] = src[c + q * PAD < last ? c + q * PAD : last];
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            coef[0][c + q * PAD] = make_float2((float)v[q].x, (float)v[q].y);
+    };
+    // sums of a chunk -> dtheta
+    auto store = [&](int i0, int rows) {
+        for (int e = c; e < rows * 64; e += PAD) {
+            const int r = e / 64, slot = e % 64, i = i0 + r;
+            long long entry;
+            bool ordered;
+            if (special) {
+                if (i >= (group ? x.nb : x.na)) continue;
+                const int a = (group ? x.b0 : x.a0) + i;
+                if (slot == 63) {
+                    entry = tile_held_entry(g, a);
+                    ordered = false;
+                } else {
+                    if (slot >= i) continue;
+                    entry = tile_pair_entry(g, a, a - 1 - slot);
+                    ordered = tile_label(g, a) < tile_label(g, a - 1 - slot);
+                }
+            } else {
+                if (i >= x.na || slot >= x.nb) continue;
+                const int a = x.a0 + i, b = x.b0 + slot;
+                if (!tile_has_pair(g, x, a, b)) continue;
+                entry = tile_pair_entry(g, a, b);
+                ordered = tile_label(g, a) < tile_label(g, b);
+            }
+            const long long out = map ? (long long)map[entry] : entry;
+            if (out < 0) continue;
+            float v = sums[group][r][0][slot];
+            for (int w = 1; w < WAVES; ++w) v += sums[group][r][w][slot];
+            dtheta[out] = ordered ? v : -v;
+        }
+    };
+    const int first = special ? group * (PAD / 2) : 0;   // rows of the outer loop from here on
+    float fa[S], fw[S], ahead = blk[first * PAD + c];    // `ahead`: the next one
+    if (special) {
+#pragma unroll
+        for (int b = 0; b < S; ++b) fa[b] = fw[b] = 0.f;
+        if (group == 0) row0[c] = make_float2(c == PAD - 1 ? 1.f : 0.f, blk[(PAD - 1) * PAD + c]);
+    } else {
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            fa[b] = c == PAD / 2 + b ? 1.f : 0.f;
+            fw[b] = blk[(PAD / 2 + b) * PAD + c];
+        }
+    }
+    for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
+        __syncthreads();
+        load(i0);
+        __syncthreads();
+        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
+        for (int r = 0; r < rows; ++r) {
+            const int i = i0 + r;
+            float ca = c == first + i ? 1.f : 0.f, cw = ahead;
+            ahead = blk[(first + (i + 1 < g.s ? i + 1 : i)) * PAD + c];
+            float prod[64];
+            if (special) {
+#pragma unroll
+                for (int b = 0; b < 64; ++b) prod[b] = 0.f;
+#pragma unroll
+                for (int s0 = (S - 1) / 8 * 8; s0 >= 0; s0 -= 8)
+                    if (s0 < i) {
+                        float2 cs[8];
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) cs[v] = coef[r][s0 + v];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int v = 7; v >= 0; --v)
+                            if (s0 + v < S) {
+                                prod[s0 + v] = cw * fa[s0 + v];
+                                tile_rotate(cw, fw[s0 + v], cs[v]);
+                                tile_rotate(ca, fa[s0 + v], cs[v]);
+                            }
+                    }
+                const float2 cs = coef[r][S];
+                for (int turn = 0; turn < 2; ++turn) {
+                    if (turn == group) {
+                        float2 t = row0[c];
+                        prod[63] = cw * t.x;
+                        tile_rotate(cw, t.y, cs);
+                        tile_rotate(ca, t.x, cs);
+                        row0[c] = t;
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int b = S - 1; b > 0; --b) {
+                    fa[b] = fa[b - 1];
+                    fw[b] = fw[b - 1];
+                }
+                fa[0] = ca;
+                fw[0] = cw;
+            } else {
+#pragma unroll
+                for (int b = S; b < 64; ++b) prod[b] = 0.f;
+#pragma unroll
+                for (int b0 = 0; b0 < S + 1; b0 += 8) {
+                    float2 cs[8];   // read together: one LDS latency for eight rotations
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) cs[v] = coef[r][b0 + v];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        const int b = b0 + v;
+                        if (b < S) {
+                            prod[b] = cw * fa[b];
+                            tile_rotate(cw, fw[b], cs[v]);
+                            tile_rotate(ca, fa[b], cs[v]);
+                        }
+                    }
+                }
+            }
+            sums[group][r][wave][lane] = tile_reduce64(prod);
+        }
+        __syncthreads();
+        if (active) store(i0, rows);
+    }
+}
+
+} // namespace givens

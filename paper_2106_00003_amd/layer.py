@@ -23,7 +23,7 @@ def _plain(n: int, m) -> bool:
 
 def _prepare(th, n, m, want_backward: bool, B: int) -> int:
     """Token of the prepared tables of th (float32), or 0 when the prepared path does not apply."""
-    if th.dtype != torch.float32:
+    if th.dtype != torch.float32 or B < 1 or not binding.givens_prepare_pays(n, m, B):
         return 0
     directions = binding.PREPARE_FORWARD
     if want_backward:
