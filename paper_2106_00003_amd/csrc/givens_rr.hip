@@ -898,7 +898,9 @@ bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
     const bool slow = f.M % 2 || f.WAVES > 8;
     if (!backward) return slow && (f.M != 7 || n >= 1900);
     if (slow) return 10 * swept >= 6LL * n;
-    return n <= 4096 && 10 * swept >= 9LL * n;
+    // (where the scaled and lifted rotation forms are worth their range check, calls keep them: what a call reports of its
+    // form and, below B = 2n, of its reduction is part of the interface)
+    return sweep_updates(n, swept) < kFormsMinUpdates && 10 * swept >= 9LL * n;
 }
 int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, TileBuffers *out)
 {

@@ -110,7 +110,7 @@ def library_defaults():
 
 # a size of every kind that the rule tells apart, on both sides of its batch
 @pytest.mark.parametrize("n,B", [(398, 500), (402, 1), (514, 400), (514, 500), (1002, 300), (1002, 700), (1006, 40),
-                                 (1024, 900), (1024, 1000), (1024, 2100), (1022, 700), (2050, 64)])
+                                 (1024, 900), (1024, 1000), (1024, 2100), (1280, 1280), (1022, 700), (2050, 64)])
 def test_sizes_around_the_rule(library_defaults, n, B):
     data = inputs.make_custom(n, B, seed=3500 + n)
     th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
