@@ -403,4 +403,29 @@ inline int carousel_backward_strips(int n, int rows, long long B, int W, long lo
     }
 }
 
+// One-wavefront float64 sweeps (wave_f64.hip): slots per lane, 0 where a size has no such shape (from 10 on every even n
+// up to 128, multiples of 4 up to 256, of 8 up to 512, of 16 up to 1024).
+inline int wave64_slots(int n)
+{
+    for (int m : {1, 2, 4, 8})
+        if (n >= 10 && n % (2 * m) == 0 && n / (2 * m) <= 64) return m;
+    return 0;
+}
+// Where they are the faster ones.  LDS kernels against them in us: forward n = 64, B = 64 33 / 12, 16384 91 / 40; n = 512,
+// B = 1024 277 / 130, 16384 2112 / 604; n = 1024, B = 256 973 / 278, 1024 982 / 937, 4096 1644 / 1844; backward n = 32,
+// B = 64 23 / 15, 4096 57 / 40, 16384 100 / 121; n = 64, B = 16384 169 / 155; n = 512, B = 1024 776 / 331, 16384
+// 5461 / 2424; n = 1024, B = 1024 3050 / 1765, 4096 5994 / 6016.
+inline bool wave64_supported(int n, long long B, bool backward)
+{
+    const int slots = wave64_slots(n);
+    if (slots == 0 || (slots == 8 && B > 2048)) return false;
+    return !backward || B <= 256LL * n;
+}
+// columns per strip of the reverse sweep: every strip costs a row of partial sums
+inline int wave64_bwd_width(int n, long long B) { return B <= 256 ? 1 : B <= 512 || wave64_slots(n) == 8 ? 2 : 4; }
+int wave64_forward(int n, int rows, long long B, const double2 *table, const double *X, double *Y, int identity, int mirror,
+                   hipStream_t stream);
+int wave64_backward(int n, int rows, long long B, long long strip0, long long strips, const double2 *table, const double *Y,
+                    const double *G, double *dX, double *partial, hipStream_t stream);
+
 } // namespace givens

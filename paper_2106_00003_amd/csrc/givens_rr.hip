@@ -583,6 +583,7 @@ int lds_forward(int n, int rows, long long B, const typename Pair2<T>::type *tab
 // Which kernel family a call takes.
 struct Families {
     bool carousel = false, column = false;  // neither: LDS strip family
+    bool wave64 = false;                    // ... whose float64 sweeps run on one wavefront per strip where a size allows
 };
 int family_code(const Families &fam)
 {
@@ -596,6 +597,7 @@ int pick_forward_family(int n, long long B, int choice, Families *out)
     if (choice == GIVENS_KERNEL_CAROUSEL && !can_carousel) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_COLUMN && !can_column) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
+    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n, B, false);
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = !out->carousel && can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
@@ -610,6 +612,7 @@ int pick_backward_family(int n, long long B, int choice, Families *out)
     if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
     // the family that sweeps (the n x n operand of the Gram form, or all B columns); the column family has
     // no reverse sweep of its own and borrows the LDS family's
+    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n, B, true);
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
@@ -640,6 +643,13 @@ int run_forward_sweep(const Problem &pb, long long B, const Coefs<T> &coefs, Fam
             if (rc == GIVENS_OK && !hip_ok(hipGetLastError())) rc = GIVENS_ERR_HIP;
         }
         t_state.last_kernel = GIVENS_KERNEL_COLUMN;
+    } else if (fam.wave64) {
+        if constexpr (std::is_same<T, double>::value) {
+            Span span(1, stream);
+            rc = wave64_forward(n, rows, B, coefs.table, X, Y, identity, transpose, stream);
+            if (rc == GIVENS_OK && !hip_ok(hipGetLastError())) rc = GIVENS_ERR_HIP;
+        }
+        t_state.last_kernel = GIVENS_KERNEL_LDS;
     } else {
         rc = lds_forward<T>(n, rows, B, coefs.table, X, Y, identity, stream, transpose);
         t_state.last_kernel = GIVENS_KERNEL_LDS;
@@ -720,7 +730,7 @@ int run_forward(Workspace *ws, int dev, const Problem &pb, long long B, const Co
 // workgroups with one row of partial sums each.
 template <typename T>
 int backward_chunks(Workspace &ws, int dev, bool carousel, const Problem &pb, long long B, const Coefs<T> &coefs,
-                    const T *Y, const T *G, T *dX, T *dtheta, hipStream_t stream, int g_identity = 0)
+                    const T *Y, const T *G, T *dX, T *dtheta, hipStream_t stream, int g_identity = 0, bool wave64 = false)
 {
     const int n = pb.n, rows = pb.rows;
     const int *map = pb.map;
@@ -728,7 +738,9 @@ int backward_chunks(Workspace &ws, int dev, bool carousel, const Problem &pb, lo
     int w = 0;
     size_t smem = 0;
     auto kern = lds_backward_kernel<T, 0>;
-    if (!carousel) {
+    if (wave64) {
+        w = wave64_bwd_width(n, B);
+    } else if (!carousel) {
         w = lds_strip_width<T>(n, B, 2);
         if (w == 0) return GIVENS_ERR_UNSUPPORTED;
         smem = (size_t)2 * n * lds_row_stride(w) * sizeof(T);
@@ -809,7 +821,10 @@ int backward_chunks(Workspace &ws, int dev, bool carousel, const Problem &pb, lo
         long long nrows = carousel ? std::min(prows, ns) : ns;
         {
             Span span(1, stream);
-            if (!carousel) {
+            if (wave64) {
+                if constexpr (std::is_same<T, double>::value)
+                    if (int rc = wave64_backward(n, rows, B, s0, ns, coefs.table, Y, G, dX, partial, stream)) return rc;
+            } else if (!carousel) {
                 hipLaunchKernelGGL(kern, dim3((unsigned)ns), dim3(kLdsThreads), smem, stream, n, rows, B, w, s0,
                                    coefs.table, Y, G, dX, partial, g_identity, map);
             } else if constexpr (std::is_same<T, float>::value) {
@@ -1078,7 +1093,7 @@ int run_backward(Workspace &ws, int dev, const Problem &pb, long long B, const C
         t_state.last_kernel = GIVENS_KERNEL_COLUMN;
         return backward_chunks<T>(ws, dev, true, pb, B, coefs, Y, G, dX, dtheta, stream);
     }
-    return backward_chunks<T>(ws, dev, fam.carousel, pb, B, coefs, Y, G, dX, dtheta, stream);
+    return backward_chunks<T>(ws, dev, fam.carousel, pb, B, coefs, Y, G, dX, dtheta, stream, 0, fam.wave64);
 }
 
 template <typename T>

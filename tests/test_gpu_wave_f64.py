@@ -1,0 +1,85 @@
+"""Float64 sweeps on one wavefront per strip: every kind of size (one to eight slots per lane, blocks before the unrolled
+ones), both sides of each strip width, odd and restricted sizes, against the oracle and the LDS kernels they stand in for."""
+import numpy as np
+import pytest
+
+from oracle import c_oracle as C
+from oracle import givens_oracle as O
+from paper_2106_00003_amd import binding, inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    yield
+    binding.set_kernel(binding.KERNEL_AUTO)
+    binding.release()
+
+
+def far(got, want):
+    return float((got - want).norm() / want.norm())
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.parametrize("B", [1, 7])
+def test_every_even_size_up_to_136(B):
+    for n in range(2, 137, 2):
+        data = inputs.make_custom(n, B, seed=4000 + n, dtype=np.float64)
+        th, x, g = (dev(data[k]) for k in ("theta", "X", "G"))
+        y = binding.givens_forward(th, x)
+        want_y = C.forward(data["theta"], data["X"])
+        want_dth, want_dx, _ = C.reverse_sweep(data["theta"], want_y, data["G"])
+        dx, dth = binding.givens_backward(th, y, g)
+        for got, want in ((y, want_y), (dx, want_dx), (dth, want_dth)):
+            assert O.rel_fro(got.cpu().numpy(), want) <= TOL, n
+        assert O.rel_fro(binding.givens_forward_transposed(th, y).cpu().numpy(), data["X"]) <= TOL, n
+
+
+@pytest.mark.parametrize("n,B", [(64, 256), (64, 513), (64, 4099), (140, 257), (256, 512), (252, 1025), (504, 513),
+                                 (512, 1024), (512, 4097), (528, 300), (1024, 70), (1008, 520)])
+def test_strip_widths_against_the_lds_kernels(n, B):
+    print(f"[wave64] n={n} B={B}", flush=True)
+    data = inputs.make_custom(n, B, seed=4200 + n, dtype=np.float64)
+    th, x, g = (dev(data[k]) for k in ("theta", "X", "G"))
+
+    def run():
+        y = binding.givens_forward(th, x)
+        dx, dth = binding.givens_backward(th, y, g)
+        return y, dx, dth, binding.givens_build(th, n), binding.givens_forward_transposed(th, x)
+
+    got = run()
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = run()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    assert all(far(a, b) <= TOL for a, b in zip(got, want))
+    buf = x.clone()
+    assert torch.equal(binding.givens_forward(th, buf, Y=buf), got[0])
+    buf = g.clone()
+    assert torch.equal(binding.givens_backward(th, got[0], buf, dX=buf)[0], got[1])
+
+
+@pytest.mark.parametrize("n,m,B", [(11, 4, 9), (129, 128, 30), (255, 20, 300), (511, 510, 40), (512, 7, 600)])
+def test_restricted_and_odd_sizes(n, m, B):
+    data = inputs.make_restricted(n, m, B, seed=4400 + n)
+    th, x, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
+
+    def run():
+        y = binding.givens_forward_restricted(th, x, m)
+        return (y, *binding.givens_backward_restricted(th, y, g, m))
+
+    got = run()
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = run()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    assert all(far(a, b) <= TOL for a, b in zip(got, want))
