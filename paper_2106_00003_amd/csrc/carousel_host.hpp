@@ -412,7 +412,7 @@ inline int wave64_slots(int n)
     return 0;
 }
 // Where they are the faster ones.  LDS kernels against them in us: forward n = 64, B = 64 33 / 12, 16384 91 / 40; n = 512,
-// B = 1024 277 / 130, 16384 2112 / 604; n = 1024, B = 256 973 / 278, 1024 982 / 937, 4096 1644 / 1844; backward n = 32,
+// B = 1024 277 / 103, 16384 2112 / 557; n = 1024, B = 256 973 / 278, 1024 982 / 467, 4096 1644 / 1844; backward n = 32,
 // B = 64 23 / 15, 4096 57 / 40, 16384 100 / 121; n = 64, B = 16384 169 / 155; n = 512, B = 1024 776 / 331, 16384
 // 5461 / 2424; n = 1024, B = 1024 3050 / 1765, 4096 5994 / 6016.
 inline bool wave64_supported(int n, long long B, bool backward)
@@ -420,6 +420,14 @@ inline bool wave64_supported(int n, long long B, bool backward)
     const int slots = wave64_slots(n);
     if (slots == 0 || (slots == 8 && B > 2048)) return false;
     return !backward || B <= 256LL * n;
+}
+// columns per strip of the forward sweep: every strip reads the whole coefficient table, so wide strips soon pay where
+// that is long (n = 512, B = 1024: one column 133 us, two 103; B = 4096: two 264, four 160; n = 256, B = 1024 39 / 43)
+inline int wave64_fwd_width(int n, long long B)
+{
+    const int slots = wave64_slots(n);
+    if (B <= (slots <= 2 ? 1024 : 512)) return 1;
+    return B <= 2048 || slots == 8 ? 2 : 4;
 }
 // columns per strip of the reverse sweep: every strip costs a row of partial sums
 inline int wave64_bwd_width(int n, long long B) { return B <= 256 ? 1 : B <= 512 || wave64_slots(n) == 8 ? 2 : 4; }

@@ -48,7 +48,7 @@ int backward_widths(int W, int n, int rows, long long B, long long strip0, long 
 int wave64_forward(int n, int rows, long long B, const double2 *table, const double *X, double *Y, int identity, int mirror,
                    hipStream_t stream)
 {
-    const int M = wave64_slots(n), W = B <= 1024 ? 1 : B <= 4096 ? 2 : 4;
+    const int M = wave64_slots(n), W = wave64_fwd_width(n, B);
     switch (M) {
     case 1: return forward_widths<1>(W, n, rows, B, table, X, Y, identity, mirror, stream);
     case 2: return forward_widths<2>(W, n, rows, B, table, X, Y, identity, mirror, stream);
