@@ -26,7 +26,8 @@ EXPORTS = [
     "givens_forward_transposed", "givens_forward_transposed_f64", "givens_forward_noalloc",
     "givens_forward_ex", "givens_backward_ex",
     "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex", "givens_forward_prepared", "givens_build_prepared",
-    "givens_backward_prepared",
+    "givens_backward_prepared", "givens_prepare_pays",
+    "givens_packed_bytes", "givens_pack", "givens_apply_packed",
     "givens_release", "givens_last_hip_error", "givens_error_string",
     "givens_set_kernel", "givens_last_kernel", "givens_set_timing", "givens_last_timing",
     "givens_set_rotation_form", "givens_last_rotation_form",
@@ -78,7 +79,7 @@ def lib():
     L.givens_build_prepared.argtypes = [i64, vp, vp]
     L.givens_backward_prepared.argtypes = [i64, i64, vp, vp, vp, vp, vp]
     L.givens_prepare_pays.argtypes = [i32, i32, i64]
-    L.givens_packed_bytes.argtypes, L.givens_packed_bytes.restype = [i32], i64
+    L.givens_packed_bytes.argtypes = [i32]
     L.givens_pack.argtypes = [i32, vp, vp, vp]
     L.givens_apply_packed.argtypes = [i32, i64, vp, vp, vp, vp]
     L.givens_num_angles.argtypes = [i32, i32]
@@ -104,9 +105,10 @@ def lib():
     L.givens_last_timing.argtypes = [ctypes.POINTER(ctypes.c_float)]
     for name in EXPORTS:
         if name not in ("givens_error_string", "givens_num_angles", "givens_prepare", "givens_prepare_restricted",
-                        "givens_prepare_ex"):
+                        "givens_prepare_ex", "givens_packed_bytes"):
             getattr(L, name).restype = i32
-    for name in ("givens_num_angles", "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex"):
+    for name in ("givens_num_angles", "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex",
+                 "givens_packed_bytes"):
         getattr(L, name).restype = i64
     _lib = L
     return L
