@@ -214,6 +214,20 @@ int64_t givens_packed_bytes(int n);                              /* or a negativ
 int givens_pack(int n, const float *U, void *packed, void *stream);
 int givens_apply_packed(int n, int64_t B, const void *packed, const float *X, float *Y, void *stream);
 
+/*
+ * The same for the U of a theta that may change unseen (a layer in evaluation, whose angles a training program writes
+ * where it likes).  givens_keep lays U = U(theta) (m: as in the restricted entry points, n - 1 for all pairs) out at the
+ * start of `kept`, givens_kept_bytes(n, m) bytes of the caller's on the device, 16-byte aligned, about 12 n^2, beside a
+ * copy of theta, and returns a positive id (or a negative error code).  givens_apply_kept then computes Y = U(theta) X for
+ * the theta it is given: it compares theta with the copy on the device, multiplies with the matrix, and where they
+ * differ runs the sweep of the LDS family over X instead.  That is right and slow; as soon as the host has learnt of it,
+ * calls with this id return GIVENS_ERR_STALE and launch nothing: build U and call givens_keep again.  Y must not be X.
+ */
+int64_t givens_kept_bytes(int n, int m);
+int64_t givens_keep(int n, int m, const float *theta, const float *U, void *kept, void *stream);
+int givens_apply_kept(int64_t id, int n, int m, int64_t B, const float *theta, void *kept, const float *X, float *Y,
+                      void *stream);
+
 /* float64 variants: same semantics, all arrays double. */
 int givens_forward_f64(int n, int64_t B, const double *theta, const double *X, double *Y, void *stream);
 int givens_build_f64(int n, const double *theta, double *U, void *stream);

@@ -27,7 +27,7 @@ EXPORTS = [
     "givens_forward_ex", "givens_backward_ex",
     "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex", "givens_forward_prepared", "givens_build_prepared",
     "givens_backward_prepared", "givens_prepare_pays",
-    "givens_packed_bytes", "givens_pack", "givens_apply_packed",
+    "givens_packed_bytes", "givens_pack", "givens_apply_packed", "givens_kept_bytes", "givens_keep", "givens_apply_kept",
     "givens_release", "givens_last_hip_error", "givens_error_string",
     "givens_set_kernel", "givens_last_kernel", "givens_set_timing", "givens_last_timing",
     "givens_set_rotation_form", "givens_last_rotation_form",
@@ -82,6 +82,9 @@ def lib():
     L.givens_packed_bytes.argtypes = [i32]
     L.givens_pack.argtypes = [i32, vp, vp, vp]
     L.givens_apply_packed.argtypes = [i32, i64, vp, vp, vp, vp]
+    L.givens_kept_bytes.argtypes = [i32, i32]
+    L.givens_keep.argtypes = [i32, i32, vp, vp, vp, vp]
+    L.givens_apply_kept.argtypes = [i64, i32, i32, i64, vp, vp, vp, vp, vp]
     L.givens_num_angles.argtypes = [i32, i32]
     L.rr_schedule_restricted.argtypes = [i32, i32, vp]
     for name in ("givens_forward_restricted", "givens_forward_restricted_f64"):
@@ -105,10 +108,10 @@ def lib():
     L.givens_last_timing.argtypes = [ctypes.POINTER(ctypes.c_float)]
     for name in EXPORTS:
         if name not in ("givens_error_string", "givens_num_angles", "givens_prepare", "givens_prepare_restricted",
-                        "givens_prepare_ex", "givens_packed_bytes"):
+                        "givens_prepare_ex", "givens_packed_bytes", "givens_kept_bytes", "givens_keep"):
             getattr(L, name).restype = i32
     for name in ("givens_num_angles", "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex",
-                 "givens_packed_bytes"):
+                 "givens_packed_bytes", "givens_kept_bytes", "givens_keep"):
         getattr(L, name).restype = i64
     _lib = L
     return L
@@ -344,6 +347,43 @@ def givens_apply_packed(packed, X, Y=None, stream=None):
         raise ValueError("Y must have the shape of X")
     _check(lib().givens_apply_packed(n, B, _dev(packed, "packed", torch.uint8), _dev(X, "X"),
                                      _dev(Y, "Y", torch.float32), _stream_ptr(stream)), "givens_apply_packed")
+    return Y
+
+
+class Kept:
+    """U of the angles theta, laid out for givens_apply_kept; `packed` is its matrix for givens_apply_packed."""
+
+    def __init__(self, theta, U, m=None, stream=None):
+        import torch
+        self.n = U.shape[0]
+        self.m = self.n - 1 if m is None else m
+        self.count = num_angles(self.n, self.m)
+        if U.shape != (self.n, self.n) or theta.numel() != self.count:
+            raise ValueError("U must be n x n and theta its angles")
+        size = lib().givens_kept_bytes(self.n, self.m)
+        if size < 0:
+            raise GivensError(size, "givens_kept_bytes")
+        self.block = torch.empty(size, dtype=torch.uint8, device=U.device)
+        self.packed = self.block[:lib().givens_packed_bytes(self.n)]
+        self.id = lib().givens_keep(self.n, self.m, _dev(theta, "theta", torch.float32), _dev(U, "U", torch.float32),
+                                    _dev(self.block, "block"), _stream_ptr(stream))
+        if self.id < 0:
+            raise GivensError(self.id, "givens_keep")
+
+
+def givens_apply_kept(kept, theta, X, Y=None, stream=None):
+    """Y = U(theta) X, fast for the theta that `kept` was made from; raises ERR_STALE once another one was seen."""
+    import torch
+    n, B = X.shape
+    if n != kept.n or theta.numel() != kept.count:
+        raise ValueError("X and theta must be of the kept matrix's size")
+    if Y is None:
+        Y = torch.empty_like(X)
+    if Y.shape != X.shape:
+        raise ValueError("Y must have the shape of X")
+    _check(lib().givens_apply_kept(kept.id, n, kept.m, B, _dev(theta, "theta", torch.float32), _dev(kept.block, "block"),
+                                   _dev(X, "X", torch.float32), _dev(Y, "Y", torch.float32), _stream_ptr(stream)),
+           "givens_apply_kept")
     return Y
 
 

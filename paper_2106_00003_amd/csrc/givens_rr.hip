@@ -14,6 +14,7 @@
 #include "carousel_host.hpp"
 #include "coef_kernels.hpp"
 #include "gram_kernels.hpp"
+#include "kept_kernels.hpp"
 #include "lds_kernels.hpp"
 #include "product_kernels.hpp"
 #include "rr_index.h"
@@ -564,18 +565,19 @@ inline bool lds_wants_ahead(int n) { return n >= 2048; }
 
 template <typename T>
 int lds_forward(int n, int rows, long long B, const typename Pair2<T>::type *table, const T *X, T *Y,
-                int identity, hipStream_t stream, int mirror = 0)
+                int identity, hipStream_t stream, int mirror = 0, const int *only_if = nullptr)
 {
     const int w = lds_strip_width<T>(n, B, 1);
     if (w == 0) return GIVENS_ERR_UNSUPPORTED;
     const size_t smem = (size_t)n * lds_row_stride(w) * sizeof(T);
     auto kern = lds_wants_ahead(n) ? lds_forward_kernel<T, kLdsAhead> : lds_forward_kernel<T, 0>;
-    GIVENS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+    if (smem > 64 * 1024)   // (what a launch may ask for by itself)
+        GIVENS_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
     const long long strips = (B + w - 1) / w;
     Span span(1, stream);
     hipLaunchKernelGGL(kern, dim3((unsigned)strips), dim3(kLdsThreads), smem, stream, n, rows, B, w, table, X,
-                       Y, identity, mirror);
+                       Y, identity, mirror, only_if);
     GIVENS_HIP(hipGetLastError());
     return GIVENS_OK;
 }
@@ -1308,6 +1310,97 @@ int apply_packed_impl(int n, long long B, const void *packed, const float *X, fl
     return GIVENS_OK;
 }
 
+// ---- a matrix kept for a theta that stays, in the caller's memory: the laid-out matrix, the standard-form table and a
+// copy of the angles, and the word that says whether they were found changed
+struct KeptLayout {
+    size_t table, copy, changed, bytes;
+};
+KeptLayout kept_layout(int rows, int m)
+{
+    const int n = rows + (rows & 1);
+    KeptLayout k;
+    k.table = round_up_256((size_t)product_pieces(rows, rows) * sizeof(u32x4));
+    k.copy = k.table + round_up_256((size_t)(n - 1) * (n / 2) * sizeof(float2));
+    k.changed = k.copy + round_up_256((size_t)count_free_angles(rows, m) * sizeof(float));
+    k.bytes = k.changed + 256;
+    return k;
+}
+// Host memory in which the device notes the kept matrices whose angles it found changed: the slot of id holds it then.
+// (A note that another id of the same slot overwrites is made again by the next call.)  Kept until the process ends.
+constexpr int kNoteSlots = 256;
+volatile int64_t *g_notes = nullptr;
+int64_t g_next_kept = 0;
+
+KeptAngles kept_angles_of(const Problem &pb, const float *theta, unsigned char *kept, int64_t id)
+{
+    const KeptLayout k = kept_layout(pb.rows, pb.m);
+    return KeptAngles{pb.n, theta, pb.map, reinterpret_cast<float *>(kept + k.copy), reinterpret_cast<float2 *>(kept + k.table),
+                      reinterpret_cast<int *>(kept + k.changed), (long long)id,
+                      reinterpret_cast<long long *>(const_cast<int64_t *>(g_notes)) + id % kNoteSlots};
+}
+unsigned kept_angles_blocks(int n, int threads)
+{
+    return (unsigned)std::min<long long>(((long long)n * (n - 1) / 2 + threads - 1) / threads, 2048);
+}
+int64_t keep_impl(int rows, int m, const float *theta, const float *U, void *kept, void *stream_v)
+{
+    if (int rc = check_restricted(rows, m)) return rc;
+    if (!theta || !U || !kept) return GIVENS_ERR_NULL;
+    hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    int dev = 0;
+    if (int rc = current_device(&dev)) return rc;
+    Workspace *ws = nullptr;
+    if (int rc = workspace_for(dev, stream, &ws)) return rc;
+    Problem pb;
+    if (int rc = resolve_problem(ws, rows, m, stream, &pb)) return rc;
+    if (!g_notes) {
+        void *p = nullptr;
+        GIVENS_HIP(hipHostMalloc(&p, kNoteSlots * sizeof(int64_t), hipHostMallocPortable | hipHostMallocMapped));
+        g_notes = static_cast<volatile int64_t *>(p);
+        for (int i = 0; i < kNoteSlots; ++i) g_notes[i] = 0;
+    }
+    split_matrix(rows, rows, U, static_cast<u32x4 *>(kept), stream);
+    const int64_t id = ++g_next_kept;
+    hipLaunchKernelGGL(kept_angles_kernel<true>, dim3(kept_angles_blocks(pb.n, 256)), dim3(256), 0, stream,
+                       kept_angles_of(pb, theta, static_cast<unsigned char *>(kept), id));
+    GIVENS_HIP(hipGetLastError());
+    return id;
+}
+int apply_kept_impl(int64_t id, int rows, int m, long long B, const float *theta, void *kept, const float *X, float *Y,
+                    void *stream_v)
+{
+    if (int rc = check_restricted(rows, m)) return rc;
+    if (B < 1) return GIVENS_ERR_BAD_B;
+    if (!theta || !kept || !X || !Y) return GIVENS_ERR_NULL;
+    if (X == Y) return GIVENS_ERR_ALIAS;
+    hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    if (id < 1 || id > g_next_kept || g_notes[id % kNoteSlots] == id) return GIVENS_ERR_STALE;
+    int dev = 0, cus = 0;
+    if (int rc = current_device(&dev)) return rc;
+    Workspace *ws = nullptr;
+    if (int rc = workspace_for(dev, stream, &ws)) return rc;
+    Problem pb;
+    if (int rc = resolve_problem(ws, rows, m, stream, &pb)) return rc;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    unsigned char *block = static_cast<unsigned char *>(kept);
+    const KeptAngles k = kept_angles_of(pb, theta, block, id);
+    ProductArgs a{rows, rows, B, reinterpret_cast<const u32x4 *>(block), X, B, Y, B, 0, false};
+    if (product_is_narrow(rows, B, cus)) {
+        const unsigned blocks = (unsigned)product_narrow_blocks(rows, B), threads = 64 * kNarrowWaves;
+        a.mblocks = (rows + 31) / 32;
+        hipLaunchKernelGGL(product_narrow_kept_kernel, dim3(blocks + kept_angles_blocks(pb.n, threads)), dim3(threads), 0,
+                           stream, a, blocks, k);
+    } else {
+        hipLaunchKernelGGL(kept_angles_kernel<false>, dim3(kept_angles_blocks(pb.n, 256)), dim3(256), 0, stream, k);
+        product(a, cus, stream);
+    }
+    GIVENS_HIP(hipGetLastError());
+    // over it, where the angles are not those of the matrix
+    return lds_forward<float>(pb.n, rows, B, k.table, X, Y, 0, stream, 0, k.changed);
+}
+
 // ---- unitary extension (appendix): complex operands, LDS strip kernels
 template <typename T>
 int unitary_strip_width(int n, long long B, int strips_in_lds)
@@ -1773,6 +1866,22 @@ int givens_apply_packed(int n, int64_t B, const void *packed, const float *X, fl
 {
     if (n > givens::kMaxRows) return GIVENS_ERR_UNSUPPORTED;
     return givens::apply_packed_impl(n, B, packed, X, Y, stream);
+}
+
+int64_t givens_kept_bytes(int n, int m)
+{
+    if (int rc = givens::check_restricted(n, m)) return rc;
+    if (n > givens::kMaxRows) return GIVENS_ERR_UNSUPPORTED;
+    return (int64_t)givens::kept_layout(n, m).bytes;
+}
+int64_t givens_keep(int n, int m, const float *theta, const float *U, void *kept, void *stream)
+{
+    return givens::keep_impl(n, m, theta, U, kept, stream);
+}
+int givens_apply_kept(int64_t id, int n, int m, int64_t B, const float *theta, void *kept, const float *X, float *Y,
+                      void *stream)
+{
+    return givens::apply_kept_impl(id, n, m, B, theta, kept, X, Y, stream);
 }
 
 int64_t givens_num_angles(int n, int m)

@@ -26,8 +26,9 @@ __host__ __device__ inline int lds_row_stride(int w) { return w | 1; }
 template <typename T, int AHEAD>
 __global__ __launch_bounds__(kLdsThreads) void lds_forward_kernel(
     int n, int rows, long long B, int w, const typename Pair2<T>::type *__restrict__ table,
-    const T *X, T *Y, int identity, int mirror)
+    const T *X, T *Y, int identity, int mirror, const int *__restrict__ only_if)
 {
+    if (only_if && *only_if == 0) return;               // nullptr: runs
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *strip = reinterpret_cast<T *>(smem_raw);
     const int H = n >> 1;

@@ -194,9 +194,8 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 // tiles; 10.2 with 32 x 64 results per workgroup), n = 4096, B = 64 in 25 us = 4.0 TB/s (182).
 constexpr int kNarrowWaves = 8;
 template <bool CPLX>
-__global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(ProductArgs a)
+__device__ __forceinline__ void product_narrow(const ProductArgs &a, float (&part)[kNarrowWaves][16][64])
 {
-    __shared__ float part[kNarrowWaves][16][64];
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int mb = blockIdx.x % a.mblocks;
@@ -251,6 +250,13 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(Pr
     }
 }
 
+template <bool CPLX>
+__global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(ProductArgs a)
+{
+    __shared__ float part[kNarrowWaves][16][64];
+    product_narrow<CPLX>(a, part);
+}
+
 template <int MW, int NW, int MF, int NF>
 inline void launch_product(ProductArgs a, hipStream_t stream)
 {
@@ -269,11 +275,15 @@ inline void launch_product(ProductArgs a, hipStream_t stream)
 // and a half, and for few rows one no taller than they are.  The
 // two kinds add in different orders: `all_columns`, where it is given, decides (the columns of the result of which a.B are
 // a part), so that a result does not depend on how it is cut.
+constexpr long long product_narrow_blocks(int m, long long B) { return (long long)((m + 31) / 32) * ((B + 31) / 32); }
+constexpr bool product_is_narrow(int m, long long B, int compute_units)
+{
+    return product_narrow_blocks(m, B) <= 6LL * compute_units;
+}
 inline void product(ProductArgs a, int compute_units, hipStream_t stream, long long all_columns = 0)
 {
-    const long long narrow = (long long)((a.m + 31) / 32) * ((a.B + 31) / 32);
-    const long long all = all_columns ? (long long)((a.m + 31) / 32) * ((all_columns + 31) / 32) : narrow;
-    if (all <= 6LL * compute_units) {
+    const long long narrow = product_narrow_blocks(a.m, a.B);
+    if (product_is_narrow(a.m, all_columns ? all_columns : a.B, compute_units)) {
         a.mblocks = (a.m + 31) / 32;
         if (a.cplx)
             hipLaunchKernelGGL(product_narrow_kernel<true>, dim3((unsigned)narrow), dim3(64 * kNarrowWaves), 0, stream, a);

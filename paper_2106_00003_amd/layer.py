@@ -141,27 +141,41 @@ class OrthogonalLinear(torch.nn.Module):
         count = binding.num_angles(n, m)
         self.theta = torch.nn.Parameter(init_std * torch.randn(count, device=device, dtype=dtype))
 
-        self._eval_matrix = None  # (version of theta, its address, stream), U laid out for evaluation
+        self._eval_matrix = None  # (version of theta, stream), theta, U laid out for evaluation
         self._captured = []       # laid-out matrices that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
         if torch.is_grad_enabled() or self.theta.dtype != torch.float32:
             return givens_apply(self.theta, X, self.m)
-        # evaluation: U of the current theta is built and laid out once, here and not in the workspace of the stream, which
-        # all layers share, and multiplied with until theta changes
         x = X.contiguous()
         if x.dim() != 2 or x.shape[0] != self.n or x.shape[1] == 0 or x.dtype != torch.float32 or not x.is_cuda:
             return givens_apply(self.theta, X, self.m)   # refused there
-        key = (self.theta._version, self.theta.data_ptr(), torch.cuda.current_stream().cuda_stream)
-        kept = self._eval_matrix
+        # evaluation: U of the current theta is built and laid out once, here and not in the workspace of the stream, which
+        # all layers share, and multiplied with until theta changes.  The version counter tells most changes; writes that it
+        # does not count (through .data, by a replayed graph) are seen on the device, which compares the angles.  (Holding
+        # theta holds its memory: no other angles can come to lie at its address.)
+        theta = self.theta.detach()
+        th = theta.contiguous()
+        key = (theta._version, torch.cuda.current_stream().cuda_stream)
         capturing = torch.cuda.is_current_stream_capturing()
-        if kept is None or kept[0] != key:
-            kept = (key, binding.givens_pack(givens_matrix(self.theta, self.n, self.m)))
-            if not capturing:                # what a graph records is there when it is replayed
+        for _ in range(2):
+            kept = self._eval_matrix
+            same = kept is not None and kept[0] == key and kept[1].data_ptr() == theta.data_ptr()
+            if capturing:
+                if not same:                     # what a graph records is there when it is replayed
+                    return binding.givens_apply_packed(binding.givens_pack(givens_matrix(theta, self.n, self.m)), x)
+                self._captured.append(kept[2])   # and what it reads has to stay
+                return binding.givens_apply_packed(kept[2].packed, x)
+            if not same:
+                kept = (key, theta, binding.Kept(th, givens_matrix(th, self.n, self.m), self.m))
                 self._eval_matrix = kept
-        elif capturing:
-            self._captured.append(kept[1])   # and what it reads has to stay
-        return binding.givens_apply_packed(kept[1], x)
+            try:
+                return binding.givens_apply_kept(kept[2], th, x)
+            except binding.GivensError as err:
+                if err.code != binding.ERR_STALE:
+                    raise
+                self._eval_matrix = None
+        return givens_apply(self.theta, X, self.m)
 
     def __getstate__(self):
         return {**self.__dict__, "_eval_matrix": None, "_captured": []}
