@@ -56,8 +56,8 @@ extern "C" {
                                  /* n from 132, a multiple of 4 up to 4096 or of 8 up to 8192,  */
                                  /* or n = 2 M L with M in {7, 5, 3} and L <= 1024 (standard    */
                                  /* rotation form only, whatever givens_set_rotation_form says) */
-#define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs, */
-                                 /* or from n = 16 on one wavefront per strip of columns         */
+#define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs  */
+                                 /* (n <= 32), or from n = 16 on one wavefront per strip         */
 
 #define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix */
                                  /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it where it is */

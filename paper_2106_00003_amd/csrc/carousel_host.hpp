@@ -227,8 +227,8 @@ int unitary_carousel_forward_m8(const UnitaryCarouselFwdArgs &a, int waves, int 
 int unitary_carousel_backward_m4(const UnitaryCarouselBwdArgs &a, int waves, int W);
 int unitary_carousel_backward_m2(const UnitaryCarouselBwdArgs &a, int waves, int W);
 
-// Column family (column_fwd.hip): forward sweep for even n <= 128, one lane per column, standard-form
-// table.  GIVENS_ERR_UNSUPPORTED for other n.
+// Column family (float, n <= 128): column_fwd.hip, forward sweep for even n <= 32, one lane per column, standard-form table
+// (GIVENS_ERR_UNSUPPORTED for other n), and the wavefront shape below.
 constexpr int kColumnFamilyMaxN = 128;
 // Sizes whose forward sweep (up to some batch) and reverse sweep run on the wavefront shape (carousel_wave_shape_for): a
 // block is then one rotation per lane and a move between lanes, where the column kernel goes through all n / 2 rotations

@@ -1,4 +1,4 @@
-// Column forward kernels (small n): one instance per even n up to kColumnMaxN.
+// Column forward kernels: one instance per even n up to kColumnMaxN.
 #include "carousel_host.hpp"
 #include "column_kernels.hpp"
 

@@ -1,4 +1,4 @@
-// Column kernels (float): the forward family for small n (n <= 128).
+// Column kernels (float): the forward sweep of the smallest sizes (n <= 32).
 //
 // One lane owns one column of the operand and keeps all n of its rows in VGPRs, so a block of
 // Algorithm 2 (Section 3: n/2 disjoint pairs) is n/2 rotations inside the lane with no exchange at
@@ -9,8 +9,8 @@
 // unrolled group of kGroup blocks the turn is a renaming of registers; after the group the ring is
 // turned physically (n-1 register moves per kGroup blocks).
 //
-// What remains for it: sizes below 16, and wide batches below 32; the family's other forward sweeps and its reverse sweeps
-// run on the one-wavefront carousel shapes (column_wave), its wide batches through U and the Gram matrix.
+// It runs sizes below 16, and batches beyond kColumnWaveMaxB columns up to 32; the family's other forward sweeps and its
+// reverse sweeps run on the one-wavefront carousel shapes (column_wave), its wide batches through U and the Gram matrix.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -21,7 +21,7 @@
 namespace givens {
 
 constexpr int kColumnThreads = 256;
-constexpr int kColumnMaxN = 128;
+constexpr int kColumnMaxN = 32;
 
 template <int N>
 struct ColumnFwd {
@@ -81,10 +81,8 @@ struct ColumnFwd {
 // table: standard-form (cos, sin) per angle of the n-dimensional problem in E order (of the mirrored
 // problem when `mirror` is set, see carousel_forward_kernel).  rows: the operand's row count (n, or
 // n - 1 when n pads an odd problem).
-// launch bound: three wavefronts per SIMD for 64 < n <= 112 (the scheduler otherwise spends registers on
-// overlapping more rotations than the issue rate can use)
 template <int N>
-__global__ __launch_bounds__(kColumnThreads, N > 112 ? 2 : (N > 64 ? 3 : 4)) void column_forward_kernel(
+__global__ __launch_bounds__(kColumnThreads, 4) void column_forward_kernel(
     int rows, long long B, const float2 *__restrict__ table, const float *X, float *Y, int identity, int mirror)
 {
     using State = ColumnFwd<N>;

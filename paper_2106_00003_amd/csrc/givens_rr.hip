@@ -954,7 +954,7 @@ int tiles_forward(Workspace &ws, int dev, const Problem &pb, long long B, const 
                   bool transpose, hipStream_t stream)
 {
     if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
-    const TilePlan g = tile_plan(pb.n, kTilePad);
+    const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
     if (int rc = tile_storage(ws, g, false, &b)) return rc;
     {
@@ -968,7 +968,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
                    float *dX, float *dtheta, hipStream_t stream)
 {
     if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
-    const TilePlan g = tile_plan(pb.n, kTilePad);
+    const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
     if (int rc = tile_storage(ws, g, true, &b)) return rc;
     int cus = 0;

@@ -9,7 +9,7 @@
 // the late parts with i + j = t and the early parts with i + j = t + 2P: P tiles that share no row.  The pairs inside
 // piece i and inside piece i + P, whose rotations with row 0 alternate, are one special tile of stage 2i.
 //
-// A tile's rotations act on at most 2s + 1 <= PAD rows, so they are one PAD x PAD orthogonal matrix: built here with
+// A tile's rotations act on at most 2s + 1 <= kTilePad rows, so they are one kTilePad x kTilePad orthogonal matrix: built here with
 // one lane per column, in float64 (as fast as float32 on this chip), and applied to any number of columns as a product
 // of bf16 pieces (split_bf16.hpp).  A rotation then costs 8 operations per column on the matrix cores instead of
 // 2 to 4 vector instructions, and the chain of n - 1 dependent blocks becomes one of about n / s products.
@@ -17,7 +17,7 @@
 // Gradient.  With S = Z G^T - G Z^T (antisymmetric) of the strips z and gbar before a tile, the share of a pair (i, j),
 // i < j, is S_ij in the frame of its rotation, and a rotation takes S to R S R^T.  So the reverse sweep needs neither
 // strip: it starts from S = C - C^T, C = Y G^T, takes S through the stages (S <- A S A^T, two products per pair of
-// tiles, half of them by antisymmetry) and leaves every tile's own PAD x PAD block behind; the sums of all tiles then
+// tiles, half of them by antisymmetry) and leaves every tile's own kTilePad x kTilePad block behind; the sums of all tiles then
 // come from those blocks in one launch.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -71,14 +71,14 @@ __host__ __device__ inline Tile tile_at(const TilePlan &g, int st, int u)
     tile_piece(g, x.j, &x.b0, &x.nb);
     return x;
 }
-// Row (label) of local index r of tile u, or -1: piece i from 0, piece j from pad / 2, and at pad - 1 row 0, which goes
+// Row (label) of local index r of tile u, or -1: piece i from 0, piece j from kTilePad / 2, and at kTilePad - 1 row 0, which goes
 // with tile 0 of every stage (an identity row of its matrix unless the tile is special).
 __host__ __device__ inline int tile_row(const TilePlan &g, const Tile &x, int u, int r)
 {
-    const int q = r - g.pad / 2;
+    const int q = r - kTilePad / 2;
     if (q < 0) return r < x.na ? tile_label(g, x.a0 + r) : -1;
     if (q < x.nb) return tile_label(g, x.b0 + q);
-    return r == g.pad - 1 && u == 0 ? 0 : -1;
+    return r == kTilePad - 1 && u == 0 ? 0 : -1;
 }
 // Restricted parametrisation (pairs (i, j), i < free_rows): does the tile hold no free pair?  (labels go down by 2 along
 // a piece)
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void tile_coef_kernel(TilePlan g, const float 
                                                         const int *__restrict__ map, int free_rows, long long entries,
                                                         double2 *__restrict__ table)
 {
-    const int width = g.pad / 2;
+    const int width = kTilePad / 2;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
     if (id >= entries) return;
     const int slot = (int)(id % width);
@@ -212,12 +212,10 @@ constexpr int kWaitForLoads = 0x0f70;   // s_waitcnt vmcnt(0): this wavefront's 
 // is the same for every pass), then through row 0, which the two wavefronts hand to each other through LDS.
 // Bound by the chain of the rotations of a row (two dependent float64 instructions each).  Workgroups: special tiles first,
 // they take longest.
-template <int PAD>
 __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const double2 *__restrict__ table, int free_rows,
                                                             float *__restrict__ matrices)
 {
-    constexpr int S = tile_slots(PAD), PARTS = PAD / 64;
-    static_assert(PARTS == 2, "two wavefronts per workgroup");
+    constexpr int S = kTileSlots, PARTS = kTilePad / 64;
     __shared__ double2 coef[2][2][kTileChunk][S + 1];   // [which of two chunks][piece]
     __shared__ double row0[64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -226,7 +224,7 @@ __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const do
     const int st = special ? 2 * ((int)blockIdx.x / PARTS) - g.first : id / g.P, u = special ? 0 : id % g.P;
     const Tile x = tile_at(g, st, u);
     if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
-    float *A = matrices + ((size_t)st * g.P + u) * PAD * PAD;
+    float *A = matrices + ((size_t)st * g.P + u) * kTilePad * kTilePad;
     const double2 *mine = tile_coef_table(g, table, st, u, special, S + 1);
     // rows of the chunk at i0: a wavefront brings its piece's (special) or every second one
     auto load = [&](int i0) {
@@ -239,10 +237,10 @@ __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const do
     double q[S];
     load(0);
     if (special) {
-        const int c = lane + 64 * ((int)blockIdx.x % PARTS), base = wave * (PAD / 2);
+        const int c = lane + 64 * ((int)blockIdx.x % PARTS), base = wave * (kTilePad / 2);
 #pragma unroll
         for (int b = 0; b < S; ++b) q[b] = 0.0;
-        if (wave == 0) row0[lane] = c == PAD - 1 ? 1.0 : 0.0;
+        if (wave == 0) row0[lane] = c == kTilePad - 1 ? 1.0 : 0.0;
         for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
             __builtin_amdgcn_s_waitcnt(kWaitForLoads);
             __syncthreads();   // the chunk is in LDS
@@ -279,15 +277,15 @@ __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const do
         }
 #pragma unroll
         for (int b = 0; b < S; ++b)
-            if (b < g.s) A[(base + g.s - 1 - b) * PAD + c] = (float)q[b];
-        for (int r = g.s; r < PAD / 2; ++r)
-            if (base + r < PAD - 1) A[(base + r) * PAD + c] = 0.f;
-        if (wave == 1) A[(PAD - 1) * PAD + c] = (float)row0[lane];
+            if (b < g.s) A[(base + g.s - 1 - b) * kTilePad + c] = (float)q[b];
+        for (int r = g.s; r < kTilePad / 2; ++r)
+            if (base + r < kTilePad - 1) A[(base + r) * kTilePad + c] = 0.f;
+        if (wave == 1) A[(kTilePad - 1) * kTilePad + c] = (float)row0[lane];
         return;
     }
     const int c = lane + 64 * wave;
 #pragma unroll
-    for (int b = 0; b < S; ++b) q[b] = (c == PAD / 2 + b && b < g.s) ? 1.0 : 0.0;
+    for (int b = 0; b < S; ++b) q[b] = (c == kTilePad / 2 + b && b < g.s) ? 1.0 : 0.0;
     for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
         __builtin_amdgcn_s_waitcnt(kWaitForLoads);
         __syncthreads();
@@ -310,13 +308,13 @@ __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const do
                 for (int v = 0; v < 8; ++v)
                     if (b0 + v < S) tile_rotate(cur, q[b0 + v], cs[(b0 / 8) & 1][v]);
             }
-            A[(i0 + r) * PAD + c] = (float)cur;
+            A[(i0 + r) * kTilePad + c] = (float)cur;
         }
     }
 #pragma unroll
-    for (int b = 0; b < S; ++b) A[(PAD / 2 + b) * PAD + c] = (float)q[b];
-    for (int r = g.s; r < PAD / 2; ++r) A[r * PAD + c] = 0.f;
-    A[(PAD - 1) * PAD + c] = (u == 0 && c == PAD - 1) ? 1.f : 0.f;
+    for (int b = 0; b < S; ++b) A[(kTilePad / 2 + b) * kTilePad + c] = (float)q[b];
+    for (int r = g.s; r < kTilePad / 2; ++r) A[r * kTilePad + c] = 0.f;
+    A[(kTilePad - 1) * kTilePad + c] = (u == 0 && c == kTilePad - 1) ? 1.f : 0.f;
 }
 
 // A fragment of a tile's matrix: rows 32 f .. + 31, contraction indices 16 k .. + 15, as in product_kernels.hpp but with
@@ -326,24 +324,23 @@ __device__ __forceinline__ int tile_k(int half, int j) { return (j & 3) + 4 * ha
 
 // matrices -> pieces, one wavefront per fragment; transposed: of the transposed matrices
 // (and one identity, behind the last tile, that all tiles without a free pair share)
-template <int PAD>
 __global__ __launch_bounds__(256) void tile_split_kernel(TilePlan g, int free_rows, const float *__restrict__ matrices,
                                                          u32x4 *__restrict__ out, int transposed)
 {
-    constexpr int PER = (PAD / 32) * (PAD / 16);
+    constexpr int PER = (kTilePad / 32) * (kTilePad / 16);
     const int lane = threadIdx.x & 63;
     const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int tile = (int)(id / PER), f = (int)(id % PER), tiles = g.stages * g.P;
     if (tile > tiles) return;
     const bool identity = tile == tiles;
     if (!identity && tile_is_identity(g, tile_at(g, tile / g.P, tile % g.P), free_rows)) return;
-    const float *A = matrices + (size_t)tile * PAD * PAD;
-    const int row = (f / (PAD / 16)) * 32 + (lane & 31), k0 = (f % (PAD / 16)) * 16;
+    const float *A = matrices + (size_t)tile * kTilePad * kTilePad;
+    const int row = (f / (kTilePad / 16)) * 32 + (lane & 31), k0 = (f % (kTilePad / 16)) * 16;
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int k = k0 + tile_k(lane >> 5, j);
-        v[j] = identity ? (row == k ? 1.f : 0.f) : (transposed ? A[k * PAD + row] : A[row * PAD + k]);
+        v[j] = identity ? (row == k ? 1.f : 0.f) : (transposed ? A[k * kTilePad + row] : A[row * kTilePad + k]);
     }
     const Split8 sp = split8(v);
     u32x4 *o = out + id * 192 + lane;
@@ -358,6 +355,7 @@ __device__ __forceinline__ size_t tile_piece_index(const TilePlan &g, int st, in
     return identity ? (size_t)g.stages * g.P : (size_t)st * g.P + u;
 }
 
+constexpr int kTileCols = 32;   // columns per step of the apply kernel
 struct TileApplyArgs {
     TilePlan g;
     int stage, rows, free_rows;
@@ -369,14 +367,13 @@ struct TileApplyArgs {
 };
 
 // One stage on B columns: rows of each tile <- matrix * rows.  A workgroup takes one tile and a run of columns, a wavefront
-// 32 rows of the result with its part of the matrix in registers throughout.  Per step of 32 NF columns a wavefront brings
+// 32 rows of the result with its part of the matrix in registers throughout.  Per step of kTileCols columns a wavefront brings
 // 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange), a step ahead,
 // and puts the pieces into LDS as fragments.
-template <int PAD, int NF>
-__global__ __launch_bounds__(2 * PAD, 2) void tile_apply_kernel(TileApplyArgs a)
+__global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyArgs a)
 {
-    constexpr int KF = PAD / 16, BN = 32 * NF, GROUPS = 64 / BN, ROWS = 32 / GROUPS;
-    __shared__ u32x4 panel[KF][NF][3][64];
+    constexpr int KF = kTilePad / 16;
+    __shared__ u32x4 panel[KF][3][64];
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -386,29 +383,28 @@ __global__ __launch_bounds__(2 * PAD, 2) void tile_apply_kernel(TileApplyArgs a)
     const bool identity = tile_is_identity(g, x, a.free_rows);
     if (n0 >= a.B || (a.X == a.Y && identity)) return;
     // this wavefront's 32 rows: labels first, first - 2, ...; `count` of them are there, row 0 may stand at the end
-    const int local = 32 * wave, in_piece = local % (PAD / 2);
-    const bool second = local >= PAD / 2;
+    const int local = 32 * wave, in_piece = local % (kTilePad / 2);
+    const bool second = local >= kTilePad / 2;
     const int count = (second ? x.nb : x.na) - in_piece;
     const int first = tile_label(g, (second ? x.b0 : x.a0)) - 2 * in_piece;
-    const bool has_held = u == 0 && local == PAD - 32;
+    const bool has_held = u == 0 && local == kTilePad - 32;
     const int skip = first >= a.rows ? 1 : 0;          // the added row of an odd problem is the first of its piece
 
     u32x4 fa[KF][1][3];
-    const u32x4 *ap = a.pieces + tile_piece_index(g, a.stage, u, identity) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+    const u32x4 *ap = a.pieces + tile_piece_index(g, a.stage, u, identity) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
 #pragma unroll
     for (int kf = 0; kf < KF; ++kf)
 #pragma unroll
         for (int p = 0; p < 3; ++p) fa[kf][0][p] = ap[kf * 192 + 64 * p];
 
-    // a lane brings ROWS rows of one column: all 32 (BN = 64), or the 8 + 8 rows of its half (BN = 32)
-    float xr[ROWS];
-    auto row_in = [&](int q) { return GROUPS == 1 ? q : 16 * (q >> 3) + tile_k(half, q & 7); };
+    // a lane brings 16 rows of one column, those of its half of the fragments
+    float xr[16];
     auto fetch = [&](long long c0) {
-        long long col = c0 + (lane & (BN - 1));
+        long long col = c0 + l32;
         col = col < n1 ? col : n1 - 1;
 #pragma unroll
-        for (int q = 0; q < ROWS; ++q) {
-            const int r = row_in(q);
+        for (int q = 0; q < 16; ++q) {
+            const int r = 16 * (q >> 3) + tile_k(half, q & 7);
             const bool there = r < count && r >= skip, held = has_held && r == 31;
             const int row = there ? first - 2 * r : 0;
             const float v = a.X ? a.X[(long long)row * a.B + col] : (col == row ? 1.f : 0.f);
@@ -417,51 +413,39 @@ __global__ __launch_bounds__(2 * PAD, 2) void tile_apply_kernel(TileApplyArgs a)
     };
     auto stash = [&]() {
 #pragma unroll
-        for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < 2; ++f) {
+            float v[8];
 #pragma unroll
-            for (int h = 0; h < (GROUPS == 1 ? 2 : 1); ++h) {
-                float v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = xr[GROUPS == 1 ? 16 * f + tile_k(h, q) : 8 * f + q];
-                const Split8 sp = split8(v);
-                const int nf = GROUPS == 1 ? lane >> 5 : 0, at = GROUPS == 1 ? 32 * h + l32 : lane;
-                panel[2 * wave + f][nf][0][at] = sp.h;
-                panel[2 * wave + f][nf][1][at] = sp.m;
-                panel[2 * wave + f][nf][2][at] = sp.l;
-            }
+            for (int q = 0; q < 8; ++q) v[q] = xr[8 * f + q];
+            const Split8 sp = split8(v);
+            panel[2 * wave + f][0][lane] = sp.h;
+            panel[2 * wave + f][1][lane] = sp.m;
+            panel[2 * wave + f][2][lane] = sp.l;
+        }
     };
     fetch(n0);
-    for (long long c0 = n0; c0 < n1; c0 += BN) {
+    for (long long c0 = n0; c0 < n1; c0 += kTileCols) {
         stash();
         __syncthreads();
-        if (c0 + BN < n1) fetch(c0 + BN);
-        f32x16 acc[1][NF];
+        if (c0 + kTileCols < n1) fetch(c0 + kTileCols);
+        f32x16 acc[1][1];
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
 #pragma unroll
         for (int kf = 0; kf < KF; ++kf) {
-            u32x4 fb[NF][3];
-#pragma unroll
-            for (int j = 0; j < NF; ++j)
-#pragma unroll
-                for (int p = 0; p < 3; ++p) fb[j][p] = panel[kf][j][p][lane];
+            const u32x4 fb[1][3] = {{panel[kf][0][lane], panel[kf][1][lane], panel[kf][2][lane]}};
             mfma_split(fa[kf], fb, acc);
         }
+        const long long col = c0 + l32;
+        if (col < n1)
 #pragma unroll
-        for (int j = 0; j < NF; ++j) {
-            const long long col = c0 + 32 * j + l32;
-            if (col < n1)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int r = 8 * (v >> 2) + 4 * half + (v & 3);
-                    if (r < count && r >= skip)
-                        a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][j][v];
-                    else if (has_held && r == 31)
-                        a.Y[col] = acc[0][j][v];
-                }
-        }
+            for (int v = 0; v < 16; ++v) {
+                const int r = 8 * (v >> 2) + 4 * half + (v & 3);
+                if (r < count && r >= skip)
+                    a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][0][v];
+                else if (has_held && r == 31)
+                    a.Y[col] = acc[0][0][v];
+            }
         __syncthreads();
     }
 }
@@ -505,30 +489,28 @@ struct TileTwoSidedArgs {
     const u32x4 *pieces;   // of A (not transposed)
     const float *in;       // S before the stage
     float *out;            // S after it: the same array, or another one
-    float *blocks;         // [tile][PAD][PAD]: every tile's own block before its stage
+    float *blocks;         // [tile][kTilePad][kTilePad]: every tile's own block before its stage
 };
 
 // Places in S of the local rows of a pair's two tiles (-1: holds no row)
-template <int PAD>
-__device__ __forceinline__ void tile_places(const TilePlan &g, const Tile &x, const Tile &y, int ux, int uy, int (&place_x)[PAD],
-                                            int (&place_y)[PAD])
+__device__ __forceinline__ void tile_places(const TilePlan &g, const Tile &x, const Tile &y, int ux, int uy, int (&place_x)[kTilePad],
+                                            int (&place_y)[kTilePad])
 {
     const int stride = tile_piece_stride(g);
-    for (int r = threadIdx.x; r < 2 * PAD; r += 2 * PAD) {
-        const bool of_x = r < PAD;
-        const int q = r % PAD, u = of_x ? ux : uy, w = q - PAD / 2;
+    for (int r = threadIdx.x; r < 2 * kTilePad; r += 2 * kTilePad) {
+        const bool of_x = r < kTilePad;
+        const int q = r % kTilePad, u = of_x ? ux : uy, w = q - kTilePad / 2;
         const int i = of_x ? x.i : y.i, j = of_x ? x.j : y.j;
         int p = -1;
         if (q < g.s) p = i * stride + q;
         else if (w >= 0 && w < g.s) p = j * stride + w;
-        else if (q == PAD - 1 && u == 0) p = tile_held_place(g);
+        else if (q == kTilePad - 1 && u == 0) p = tile_held_place(g);
         (of_x ? place_x : place_y)[q] = p;
     }
 }
 // Rows 32 wave .. + 31 of a result R for columns of tile y, place cp: to (x, y) and, negated and transposed, to (y, x)
-template <int PAD>
 __device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, const f32x16 &R, int wave, int half, int cp,
-                                                bool own, bool first, const int (&place_x)[PAD])
+                                                bool own, bool first, const int (&place_x)[kTilePad])
 {
     const int held = tile_held_place(g), ld = tile_ld(g);
     if (cp < 0) return;
@@ -549,7 +531,7 @@ __device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, con
                 for (int q = 0; q < 4; ++q) neg[q] = -R[v + q];
                 *reinterpret_cast<f32x4 *>(o + p0) = neg;
             }
-            if (r0 == PAD - 4 && first) o[held] = -R[v + 3];
+            if (r0 == kTilePad - 4 && first) o[held] = -R[v + 3];
         }
     }
 }
@@ -559,12 +541,11 @@ __device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, con
 // part of A_x in registers).  The other operand of both products is cut into pieces once and shared through LDS, half the
 // contraction at a time: S as rows of eight values (a lane's are two groups of four consecutive columns), V as its
 // accumulators are.  Pairs without a rotation are left alone.  n = 4096: 40 to 48 us a stage.
-template <int PAD>
-__global__ __launch_bounds__(2 * PAD, 2) void tile_two_sided_kernel(TileTwoSidedArgs a)
+__global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwoSidedArgs a)
 {
-    constexpr int MF = PAD / 32, KF = PAD / 16, KH = KF / 2;
+    constexpr int MF = kTilePad / 32, KF = kTilePad / 16, KH = KF / 2;
     __shared__ u32x4 panel[KH][MF][3][64];
-    __shared__ int place_x[PAD], place_y[PAD];
+    __shared__ int place_x[kTilePad], place_y[kTilePad];
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -576,21 +557,21 @@ __global__ __launch_bounds__(2 * PAD, 2) void tile_two_sided_kernel(TileTwoSided
     const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
     if (idx && idy) return;
     const int stride = tile_piece_stride(g), ld = tile_ld(g);
-    tile_places<PAD>(g, x, y, ux, uy, place_x, place_y);
-    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
-    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
+    tile_places(g, x, y, ux, uy, place_x, place_y);
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
     __syncthreads();
 
     // S: a wavefront brings 32 rows; a row that is none: A_x has zeros in its column
     const int p_row = place_x[32 * wave + l32];
     const float *row = a.in + (long long)(p_row < 0 ? 0 : p_row) * ld;
-    float *block = a.blocks + ((size_t)a.stage * g.P + ux) * PAD * PAD + (32 * wave + l32) * PAD;
+    float *block = a.blocks + ((size_t)a.stage * g.P + ux) * kTilePad * kTilePad + (32 * wave + l32) * kTilePad;
     f32x4 sr[KH][2];
     auto fetch = [&](int h) {
 #pragma unroll
         for (int k = 0; k < KH; ++k) {
             const int local = 16 * (KH * h + k) + 4 * half;                 // half h of the contraction is piece i or j
-            const float *src = row + (h ? y.j : y.i) * stride + local - h * (PAD / 2);
+            const float *src = row + (h ? y.j : y.i) * stride + local - h * (kTilePad / 2);
             sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
             sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
             if (h == 1 && k == KH - 1 && uy == 0) {
@@ -681,19 +662,18 @@ __global__ __launch_bounds__(2 * PAD, 2) void tile_two_sided_kernel(TileTwoSided
     // (every wavefront has read its part of S by now: the barriers above)
 #pragma unroll
     for (int j = 0; j < MF; ++j)
-        tile_store_both<PAD>(g, a.out, R[0][j], wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
+        tile_store_both(g, a.out, R[0][j], wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
 }
 
 // The same for few tiles, where a pair per workgroup leaves compute units idle: a workgroup takes 32 columns of tile y, a
 // wavefront 32 rows of tile x, and only V's pieces go through LDS.  The other workgroups of a pair still read what one
 // writes, so the result goes to another array, all of it.  Bound by latency: everything a product needs is on its way
 // before it starts.  n = 1024: 12 us a stage (19.7 with a pair per workgroup).
-template <int PAD>
-__global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileTwoSidedArgs a)
+__global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(TileTwoSidedArgs a)
 {
-    constexpr int MF = PAD / 32, KF = PAD / 16;
+    constexpr int MF = kTilePad / 32, KF = kTilePad / 16;
     __shared__ u32x4 panel[KF][3][64];
-    __shared__ int place_x[PAD], place_y[PAD];
+    __shared__ int place_x[kTilePad], place_y[kTilePad];
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -704,14 +684,14 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileT
     const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
     const bool own = ux == uy;
     const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
-    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * tile_piece_words(PAD) + (size_t)wave * KF * 192 + lane;
-    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * tile_piece_words(PAD) + (size_t)part * KF * 192 + lane;
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * kTilePieceWords + (size_t)part * KF * 192 + lane;
     u32x4 fm[KF][1][3];
 #pragma unroll
     for (int k = 0; k < KF; ++k)
 #pragma unroll
         for (int q = 0; q < 3; ++q) fm[k][0][q] = py[k * 192 + 64 * q];
-    tile_places<PAD>(g, x, y, ux, uy, place_x, place_y);
+    tile_places(g, x, y, ux, uy, place_x, place_y);
     __syncthreads();
 
     // this wavefront's rows of S (one that is none: A_x has zeros in its column)
@@ -722,7 +702,7 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileT
 #pragma unroll
     for (int k = 0; k < KF; ++k) {
         const int local = 16 * k + 4 * half;
-        const float *src = row + (16 * k < PAD / 2 ? y.i * stride + local : y.j * stride + local - PAD / 2);
+        const float *src = row + (16 * k < kTilePad / 2 ? y.i * stride + local : y.j * stride + local - kTilePad / 2);
         sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
         sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
     }
@@ -732,7 +712,7 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileT
     }
     __builtin_amdgcn_sched_barrier(0);
     if (own && part == 0) {
-        float *block = a.blocks + ((size_t)a.stage * g.P + ux) * PAD * PAD + (32 * wave + l32) * PAD + 4 * half;
+        float *block = a.blocks + ((size_t)a.stage * g.P + ux) * kTilePad * kTilePad + (32 * wave + l32) * kTilePad + 4 * half;
 #pragma unroll
         for (int k = 0; k < KF; ++k) {
             *reinterpret_cast<f32x4 *>(block + 16 * k) = sr[k][0];
@@ -784,7 +764,7 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_two_sided_narrow_kernel(TileT
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][0][0][v] += acc[1][0][0][v];
-    tile_store_both<PAD>(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
+    tile_store_both(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
 }
 
 // 64 values per lane -> lane l has the sum over all lanes of value l
@@ -821,43 +801,42 @@ __device__ __forceinline__ float tile_reduce64(float (&v)[64])
 
 // The sums of all tiles' pairs from the blocks the stages have left: the reverse sweep of a tile on the strips
 // W = A S and A (columns of the block, one per lane); the share of rows a, b is W_a . A_b, summed over the lanes.  A
-// workgroup is two groups of PAD threads: two ordinary tiles, or the two pieces of a special one (which hand row 0 to each
+// workgroup is two groups of kTilePad threads: two ordinary tiles, or the two pieces of a special one (which hand row 0 to each
 // other as in the build kernel).
-template <int PAD>
-__global__ __launch_bounds__(2 * PAD, 1) void tile_gradient_kernel(TilePlan g, const double2 *__restrict__ table,
+__global__ __launch_bounds__(2 * kTilePad, 1) void tile_gradient_kernel(TilePlan g, const double2 *__restrict__ table,
                                                                    const int *__restrict__ map, int free_rows,
                                                                    const float *__restrict__ blocks, float *__restrict__ dtheta)
 {
-    constexpr int S = tile_slots(PAD), WAVES = PAD / 64;
+    constexpr int S = kTileSlots, WAVES = kTilePad / 64;
     __shared__ float2 coefs[2][kTileChunk][S + 1];
     __shared__ float sums[2][kTileChunk][WAVES][64];
-    __shared__ float2 row0[PAD];
-    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / PAD);
+    __shared__ float2 row0[kTilePad];
+    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / kTilePad);
     const bool special = (int)blockIdx.x < g.P;
     const int id = special ? 0 : 2 * ((int)blockIdx.x - g.P) + group, tiles = g.stages * g.P;
     const int st = special ? 2 * (int)blockIdx.x - g.first : id / g.P, u = special ? 0 : id % g.P;
     const Tile x = tile_at(g, id < tiles ? st : 0, u);
     const bool active = special || (id < tiles && x.kind != kTileSpecial && !tile_is_identity(g, x, free_rows));
     if (__syncthreads_or(active ? 1 : 0) == 0) return;
-    const float *blk = blocks + (active ? ((size_t)st * g.P + u) * PAD * PAD : 0);
-    const int c = threadIdx.x % PAD, lane = c & 63, wave = c >> 6;
+    const float *blk = blocks + (active ? ((size_t)st * g.P + u) * kTilePad * kTilePad : 0);
+    const int c = threadIdx.x % kTilePad, lane = c & 63, wave = c >> 6;
     const double2 *mine = tile_coef_table(g, table, active ? st : 2 - g.first, active ? u : 0, special || !active, S + 1) +
                           (special ? (size_t)group * g.s * (S + 1) : 0);
     float2(*coef)[S + 1] = coefs[group];
     auto load = [&](int i0) {
-        constexpr int PER = kTileChunk * (S + 1) / PAD;
+        constexpr int PER = kTileChunk * (S + 1) / kTilePad;
         double2 v[PER];
         const double2 *src = mine + (size_t)i0 * (S + 1);
         const int last = (g.s - i0) * (S + 1) - 1;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) v[q] = src[c + q * PAD < last ? c + q * PAD : last];
+        for (int q = 0; q < PER; ++q) v[q] = src[c + q * kTilePad < last ? c + q * kTilePad : last];
 #pragma unroll
         for (int q = 0; q < PER; ++q)
-            coef[0][c + q * PAD] = make_float2((float)v[q].x, (float)v[q].y);
+            coef[0][c + q * kTilePad] = make_float2((float)v[q].x, (float)v[q].y);
     };
     // sums of a chunk -> dtheta
     auto store = [&](int i0, int rows) {
-        for (int e = c; e < rows * 64; e += PAD) {
+        for (int e = c; e < rows * 64; e += kTilePad) {
             const int r = e / 64, slot = e % 64, i = i0 + r;
             long long entry;
             bool ordered;
@@ -886,17 +865,17 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_gradient_kernel(TilePlan g, c
             dtheta[out] = ordered ? v : -v;
         }
     };
-    const int first = special ? group * (PAD / 2) : 0;   // rows of the outer loop from here on
-    float fa[S], fw[S], ahead = blk[first * PAD + c];    // `ahead`: the next one
+    const int first = special ? group * (kTilePad / 2) : 0;   // rows of the outer loop from here on
+    float fa[S], fw[S], ahead = blk[first * kTilePad + c];    // `ahead`: the next one
     if (special) {
 #pragma unroll
         for (int b = 0; b < S; ++b) fa[b] = fw[b] = 0.f;
-        if (group == 0) row0[c] = make_float2(c == PAD - 1 ? 1.f : 0.f, blk[(PAD - 1) * PAD + c]);
+        if (group == 0) row0[c] = make_float2(c == kTilePad - 1 ? 1.f : 0.f, blk[(kTilePad - 1) * kTilePad + c]);
     } else {
 #pragma unroll
         for (int b = 0; b < S; ++b) {
-            fa[b] = c == PAD / 2 + b ? 1.f : 0.f;
-            fw[b] = blk[(PAD / 2 + b) * PAD + c];
+            fa[b] = c == kTilePad / 2 + b ? 1.f : 0.f;
+            fw[b] = blk[(kTilePad / 2 + b) * kTilePad + c];
         }
     }
     for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
@@ -907,7 +886,7 @@ __global__ __launch_bounds__(2 * PAD, 1) void tile_gradient_kernel(TilePlan g, c
         for (int r = 0; r < rows; ++r) {
             const int i = i0 + r;
             float ca = c == first + i ? 1.f : 0.f, cw = ahead;
-            ahead = blk[(first + (i + 1 < g.s ? i + 1 : i)) * PAD + c];
+            ahead = blk[(first + (i + 1 < g.s ? i + 1 : i)) * kTilePad + c];
             float prod[64];
             if (special) {
 #pragma unroll

@@ -6,27 +6,24 @@
 namespace givens {
 namespace {
 
-template <int PAD>
 inline void tile_build(const TilePlan &g, const float *theta, const int *map, int free_rows, double2 *table, float *matrices,
                        u32x4 *pieces, bool transposed, hipStream_t stream)
 {
     const long long tiles = tile_count(g), entries = tile_coef_entries(g);
     hipLaunchKernelGGL(tile_coef_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, stream, g, theta, map,
                        free_rows, entries, table);
-    hipLaunchKernelGGL(tile_build_kernel<PAD>, dim3((unsigned)(g.P * (PAD / 64) + tiles)), dim3(128), 0, stream, g, table,
+    hipLaunchKernelGGL(tile_build_kernel, dim3((unsigned)(g.P * (kTilePad / 64) + tiles)), dim3(128), 0, stream, g, table,
                        free_rows, matrices);
-    const long long frags = (tiles + 1) * (PAD / 32) * (PAD / 16);
-    hipLaunchKernelGGL(tile_split_kernel<PAD>, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, stream, g, free_rows,
+    const long long frags = (tiles + 1) * (kTilePad / 32) * (kTilePad / 16);
+    hipLaunchKernelGGL(tile_split_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, stream, g, free_rows,
                        matrices, pieces, transposed ? 1 : 0);
 }
 // Y <- U X (forward, pieces of the transposed matrices) or U^T X; X may be Y, nullptr means I
-template <int PAD, int NF>
 inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const u32x4 *pieces,
                        const float *X, float *Y, bool forward, hipStream_t stream)
 {
-    constexpr long long BN = 32 * NF;
     // at most what the chip holds at once (eight wavefronts per compute unit)
-    const long long resident = (long long)compute_units * 8 / (PAD / 32), steps = (B + BN - 1) / BN;
+    const long long resident = (long long)compute_units * 8 / (kTilePad / 32), steps = (B + kTileCols - 1) / kTileCols;
     for (int i = 0; i < g.stages; ++i) {
         const int st = forward ? g.stages - 1 - i : i;
         const bool copies = i == 0 && X != Y;          // the first stage writes every row
@@ -39,11 +36,10 @@ inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_
         long long runs = resident / active > 1 ? resident / active : 1;
         const long long per = (steps + runs - 1) / runs;
         runs = (steps + per - 1) / per;
-        const TileApplyArgs a{g, st, rows, free_rows, B, pieces, i ? Y : X, Y, per * BN};
-        hipLaunchKernelGGL((tile_apply_kernel<PAD, NF>), dim3((unsigned)(runs * g.P)), dim3(2 * PAD), 0, stream, a);
+        const TileApplyArgs a{g, st, rows, free_rows, B, pieces, i ? Y : X, Y, per * kTileCols};
+        hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
     }
 }
-template <int PAD>
 inline void tile_gradient(const TilePlan &g, int rows, int free_rows, const double2 *table, const int *map, const u32x4 *pieces,
                           const float *C, float *S, float *blocks, float *dtheta, hipStream_t stream)
 {
@@ -55,12 +51,12 @@ inline void tile_gradient(const TilePlan &g, int rows, int free_rows, const doub
     for (int st = 0; st < g.stages; ++st) {
         const TileTwoSidedArgs a{g, st, free_rows, pieces, in, out, blocks};
         if (second)
-            hipLaunchKernelGGL(tile_two_sided_narrow_kernel<PAD>, dim3(pairs * (PAD / 32)), dim3(2 * PAD), 0, stream, a);
+            hipLaunchKernelGGL(tile_two_sided_narrow_kernel, dim3(pairs * (kTilePad / 32)), dim3(2 * kTilePad), 0, stream, a);
         else
-            hipLaunchKernelGGL(tile_two_sided_kernel<PAD>, dim3(pairs), dim3(2 * PAD), 0, stream, a);
+            hipLaunchKernelGGL(tile_two_sided_kernel, dim3(pairs), dim3(2 * kTilePad), 0, stream, a);
         if (second) std::swap(in, out);
     }
-    hipLaunchKernelGGL(tile_gradient_kernel<PAD>, dim3((unsigned)(g.P + (tile_count(g) + 1) / 2)), dim3(2 * PAD), 0, stream, g,
+    hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(g.P + (tile_count(g) + 1) / 2)), dim3(2 * kTilePad), 0, stream, g,
                        table, map, free_rows, blocks, dtheta);
 }
 } // namespace
@@ -68,17 +64,17 @@ inline void tile_gradient(const TilePlan &g, int rows, int free_rows, const doub
 void tiles_build(const TilePlan &g, const float *theta, const int *map, int free_rows, const TileBuffers &b, bool forward,
                  hipStream_t stream)
 {
-    tile_build<kTilePad>(g, theta, map, free_rows, b.table, b.matrices, static_cast<u32x4 *>(b.pieces), forward, stream);
+    tile_build(g, theta, map, free_rows, b.table, b.matrices, static_cast<u32x4 *>(b.pieces), forward, stream);
 }
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const TileBuffers &b,
                  const float *X, float *Y, bool forward, hipStream_t stream)
 {
-    tile_apply<kTilePad, 1>(g, compute_units, rows, free_rows, B, static_cast<const u32x4 *>(b.pieces), X, Y, forward, stream);
+    tile_apply(g, compute_units, rows, free_rows, B, static_cast<const u32x4 *>(b.pieces), X, Y, forward, stream);
 }
 void tiles_gradient(const TilePlan &g, int rows, int free_rows, const int *map, const TileBuffers &b, const float *C,
                     float *dtheta, hipStream_t stream)
 {
-    tile_gradient<kTilePad>(g, rows, free_rows, b.table, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.matrices, dtheta,
+    tile_gradient(g, rows, free_rows, b.table, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.matrices, dtheta,
                             stream);
 }
 
