@@ -80,7 +80,7 @@ struct Workspace {
     Buffer gram;        // Gram form: slices of C = Y G^T, rows x rows floats each
     Buffer matrix;      // wide batches: U or U^T, rows x rows floats
     Buffer pieces;      // ... and its pieces in operand order (product_kernels.hpp)
-    Buffer tile_table, tile_matrices, tile_pieces, tile_s;   // tiled sweeps (tile_host.hpp)
+    Buffer tile_table, tile_matrices, tile_pieces, tile_s, tile_tops;   // tiled sweeps (tile_host.hpp)
     Buffer columns;     // ... and a copy of the columns at work when a result overwrites its operand
     Buffer map;         // restricted parametrisation / odd n: index in theta of every entry of E, or -1
     Buffer map_counts;  // free pairs per block (scratch of the map kernels)
@@ -89,7 +89,8 @@ struct Workspace {
     Buffer u_q, u_psi, u_sgn, u_rot, u_phs, u_orient, u_fin;
     int map_rows = 0, map_m = 0; // the (row count, m) the map was built for
     Prepared prepared;
-    Buffer *all[29] = {&tile_table, &tile_matrices, &tile_pieces, &tile_s, &flag, &scale, &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
+    Buffer *all[30] = {&tile_table, &tile_matrices, &tile_pieces, &tile_s, &tile_tops, &flag, &scale,
+                       &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
                        &matrix, &pieces, &columns, &partial, &zeros, &sink, &gram, &map,
                        &u_q, &u_psi, &u_sgn, &u_rot, &u_phs, &u_orient, &u_fin, &chain, &chain_flags};
 };
@@ -919,15 +920,25 @@ bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
     // form and, below B = 2n, of its reduction is part of the interface)
     return sweep_updates(n, swept) < kFormsMinUpdates && 10 * swept >= 9LL * n;
 }
-int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, TileBuffers *out)
+// Whether the tiles are applied to I, to build U, and X multiplied with that.
+bool tiles_by_product(int rows, long long B) { return B >= kProductMinRatio * rows && B >= kProductMinB; }
+// operand_cols: of the operand the tiles are applied to (0: none, or I)
+int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, long long operand_cols, TileBuffers *out)
 {
     if (int rc = grow(ws.tile_table, tile_table_bytes(g))) return rc;
     if (int rc = grow(ws.tile_matrices, tile_matrices_bytes(g))) return rc;
     if (int rc = grow(ws.tile_pieces, tile_pieces_bytes(g))) return rc;
-    if (gradient)
-        if (int rc = grow(ws.tile_s, tile_s_bytes(g))) return rc;
     *out = TileBuffers{reinterpret_cast<double2 *>(ws.tile_table.ptr), reinterpret_cast<float *>(ws.tile_matrices.ptr),
-                       ws.tile_pieces.ptr, reinterpret_cast<float *>(ws.tile_s.ptr)};
+                       ws.tile_pieces.ptr, nullptr, nullptr, nullptr};
+    if (operand_cols) {
+        if (int rc = grow(ws.tile_tops, (size_t)operand_cols * sizeof(unsigned))) return rc;
+        out->tops = reinterpret_cast<unsigned *>(ws.tile_tops.ptr);
+    }
+    if (gradient) {
+        if (int rc = grow(ws.tile_s, tile_s_bytes(g))) return rc;
+        out->S = reinterpret_cast<float *>(ws.tile_s.ptr);
+        out->range = reinterpret_cast<int *>(static_cast<unsigned char *>(ws.tile_s.ptr) + tile_range_offset(g));
+    }
     return GIVENS_OK;
 }
 // Y = U X or U^T X (forward = false) by the tiles' matrices, which are there; a wide batch through U itself
@@ -936,7 +947,7 @@ int run_tiles_apply(Workspace &ws, int dev, const Problem &pb, const TilePlan &g
 {
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    if (X && B >= kProductMinRatio * pb.rows && B >= kProductMinB) {
+    if (X && tiles_by_product(pb.rows, B)) {
         ProductStorage st;
         if (int rc = workspace_product_storage(ws, pb.rows, B, X == Y, &st)) return rc;
         {
@@ -956,10 +967,11 @@ int tiles_forward(Workspace &ws, int dev, const Problem &pb, long long B, const 
     if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
     const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
-    if (int rc = tile_storage(ws, g, false, &b)) return rc;
+    const float *swept = X && !tiles_by_product(pb.rows, B) ? X : nullptr;
+    if (int rc = tile_storage(ws, g, false, swept ? B : 0, &b)) return rc;
     {
         Span span(0, stream);
-        tiles_build(g, theta, pb.map, pb.m, b, !transpose, stream);
+        tiles_build(g, theta, pb.map, pb.m, b, !transpose, pb.rows, B, swept, stream);
     }
     t_state.last_flag = nullptr;
     return run_tiles_apply(ws, dev, pb, g, b, B, X, Y, !transpose, stream);
@@ -970,7 +982,8 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
     const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
-    if (int rc = tile_storage(ws, g, true, &b)) return rc;
+    const float *swept = dX && !tiles_by_product(pb.rows, B) ? G : nullptr;
+    if (int rc = tile_storage(ws, g, true, swept ? B : 0, &b)) return rc;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const GramPlan plan = gram_plan(pb.rows, B, cus);
@@ -978,7 +991,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     float *C = reinterpret_cast<float *>(ws.gram.ptr);
     {
         Span span(0, stream);
-        tiles_build(g, theta, pb.map, pb.m, b, false, stream);
+        tiles_build(g, theta, pb.map, pb.m, b, false, pb.rows, B, swept, stream);
     }
     {
         Span span(3, stream);

@@ -29,6 +29,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "product_kernels.hpp"
 
 namespace givens {
@@ -55,6 +57,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     constexpr int PER = BOTH * 2 / T;                  // octets per thread and step
     static_assert(BOTH * 2 % T == 0, "whole octets per thread");
     __shared__ u32x4 panel[2][3][2][BOTH];             // [buffer][piece][octet of the step][row of Y, then of G]
+    __shared__ float tops[BOTH];                       // largest magnitude of every row in this slice
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % MW, wn = wave / MW;
     // Workgroups are handed to the eight XCDs (each with an L2 of its own) in turn.  The list of (slice, tile row, tile
@@ -109,10 +112,20 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
                 }
         }
     };
-    auto stash = [&](int buf) {
+    float top[PER], scale[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) top[i] = 0.f;
+    // SCALED: the second run, of rows out of the middle range
+    auto stash = [&](auto scaled, int buf) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int c = (int)threadIdx.x + T * i;
+            if constexpr (scaled()) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) xr[i][j] *= scale[i];
+            } else {
+                top[i] = range_top(top[i], xr[i]);
+            }
             const Split8 s = split8(xr[i]);
             panel[buf][0][c & 1][c >> 1] = s.h;
             panel[buf][1][c & 1][c >> 1] = s.m;
@@ -123,39 +136,56 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     // results in IB groups of rows, a group's operands at a time in registers
     constexpr int IB = MF == 4 ? 2 : 1;
     f32x16 acc[IB][MF / IB][NF];
+    auto run = [&](auto scaled) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+        for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
+            for (int j = 0; j < NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i / (MF / IB)][i % (MF / IB)][j][v] = 0.f;
-
-    if (kbeg < kend) {
-        fetch(kbeg);
-        stash(0);
-    }
-    int buf = 0;
-    for (long long k0 = kbeg; k0 < kend; k0 += kGramK, buf ^= 1) {
-        __syncthreads();   // this step's panels are whole; the other buffer is free (its readers passed this barrier)
-        const bool more = k0 + kGramK < kend;
-        if (more) fetch(k0 + kGramK);
-        u32x4 fb[NF][3];
-#pragma unroll
-        for (int j = 0; j < NF; ++j)
-#pragma unroll
-            for (int p = 0; p < 3; ++p) fb[j][p] = panel[buf][p][lane >> 5][BM + wn * 32 * NF + 32 * j + (lane & 31)];
-#pragma unroll
-        for (int i = 0; i < IB; ++i) {
-            u32x4 fa[MF / IB][3];
-#pragma unroll
-            for (int q = 0; q < MF / IB; ++q)
-#pragma unroll
-                for (int p = 0; p < 3; ++p)
-                    fa[q][p] = panel[buf][p][lane >> 5][wm * 32 * MF + 32 * (i * (MF / IB) + q) + (lane & 31)];
-            mfma_split(fa, fb, acc[i]);
+                for (int v = 0; v < 16; ++v) acc[i / (MF / IB)][i % (MF / IB)][j][v] = 0.f;
+        if (kbeg < kend) {
+            fetch(kbeg);
+            stash(scaled, 0);
         }
-        if (more) stash(buf ^ 1);
+        int buf = 0;
+        for (long long k0 = kbeg; k0 < kend; k0 += kGramK, buf ^= 1) {
+            __syncthreads();   // this step's panels are whole; the other buffer is free (its readers passed this barrier)
+            const bool more = k0 + kGramK < kend;
+            if (more) fetch(k0 + kGramK);
+            u32x4 fb[NF][3];
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) fb[j][p] = panel[buf][p][lane >> 5][BM + wn * 32 * NF + 32 * j + (lane & 31)];
+#pragma unroll
+            for (int i = 0; i < IB; ++i) {
+                u32x4 fa[MF / IB][3];
+#pragma unroll
+                for (int q = 0; q < MF / IB; ++q)
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        fa[q][p] = panel[buf][p][lane >> 5][wm * 32 * MF + 32 * (i * (MF / IB) + q) + (lane & 31)];
+                mfma_split(fa, fb, acc[i]);
+            }
+            if (more) stash(scaled, buf ^ 1);
+        }
+    };
+    run(std::false_type{});
+
+    // the rows' largest magnitudes: every wavefront looks at all of them and comes to the same result
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = (int)threadIdx.x + T * i;
+        top[i] = range_top(top[i], __shfl_xor(top[i], 1), 0.f);   // (two threads share a row)
+        scale[i] = range_scale(top[i]);
+        tops[c >> 1] = top[i];
     }
+    __syncthreads();
+    bool odd = false;
+#pragma unroll
+    for (int r = 0; r < BOTH; r += 64) odd = odd || range_scale(tops[r + lane]) != 1.f;
+    const bool again = __any(odd);
+    if (again) run(std::true_type{});
 
     // accumulator layout of the 32 x 32 matrix instructions: register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
     // column l % 32 of the fragment
@@ -165,6 +195,17 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     for (int j = 0; j < NF; ++j) {
         const int col = tile_j * BN + wn * 32 * NF + 32 * j + (lane & 31);
         const int at = !CPLX ? col : (col < a.rows ? 2 * col : 2 * (col - a.rows) + 1);
+        if (again) {
+            const float undo = range_unscale(range_scale(tops[BM + wn * 32 * NF + 32 * j + (lane & 31)]));
+#pragma unroll
+            for (int i = 0; i < MF; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                    const float x = acc[i / (MF / IB)][i % (MF / IB)][j][v] * undo;
+                    acc[i / (MF / IB)][i % (MF / IB)][j][v] = x * range_unscale(range_scale(tops[r]));
+                }
+        }
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll

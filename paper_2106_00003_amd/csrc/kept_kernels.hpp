@@ -59,12 +59,12 @@ __global__ __launch_bounds__(256) void kept_angles_kernel(KeptAngles a)
 __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kept_kernel(ProductArgs a, unsigned product_blocks,
                                                                                   KeptAngles k)
 {
-    __shared__ float part[kNarrowWaves][16][64];
+    __shared__ NarrowShared sh;
     if (blockIdx.x >= product_blocks)
         kept_angles<false>(k, (long long)(blockIdx.x - product_blocks) * (64 * kNarrowWaves) + threadIdx.x,
                            (long long)(gridDim.x - product_blocks) * (64 * kNarrowWaves));
     else
-        product_narrow<false>(a, part);
+        product_narrow<false>(a, sh);
 }
 
 } // namespace givens

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "split_bf16.hpp"
 
@@ -84,6 +85,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     constexpr int PER_ROW = T / BN;                    // octets of one column that the threads take at once
     static_assert(OCT >= 1 && T % BN == 0 && OCT * PER_ROW == 4, "whole octets per thread");
     __shared__ u32x4 panel[2][4][3][BN];
+    __shared__ float tops[T / BN][BN];                 // largest magnitude of every column, by the threads that share it
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % MW, wn = wave / MW;
     // workgroups reach the XCDs in turn: those of one XCD take all row blocks of a column block one after the other, so
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     // thread t brings column t % BN, octets t / BN + PER_ROW * i of a step (BN is a multiple of the wavefront's 64
     // columns: the octet is the same for all lanes)
     const int my_col = (int)threadIdx.x % BN, my_oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BN);
-    const long long col_in = n0 + my_col < a.B ? n0 + my_col : a.B - 1;  // past the end: its results are not stored
+    long long col_in = n0 + my_col < a.B ? n0 + my_col : a.B - 1;  // past the end: its results are not stored
     float xr[OCT][8];
     auto fetch = [&](int k0) {
 #pragma unroll
@@ -114,9 +116,17 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
                 }
             }
     };
-    auto stash = [&](int buf) {
+    float top = 0.f, scale = 1.f;
+    // SCALED: the second run, of columns out of the middle range
+    auto stash = [&](auto scaled, int buf) {
 #pragma unroll
         for (int i = 0; i < OCT; ++i) {
+            if constexpr (scaled()) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) xr[i][j] *= scale;
+            } else {
+                top = range_top(top, xr[i]);
+            }
             const Split8 s = split8(xr[i]);
             const int o = my_oct + PER_ROW * i;
             panel[buf][o][0][my_col] = s.h;
@@ -141,41 +151,73 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     // results in JB groups of columns, a group's operands at a time in registers
     constexpr int JB = NF == 4 ? 2 : 1;
     f32x16 acc[JB][MF][NF / JB];
+    auto run = [&](auto scaled) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < MF; ++i)
+        for (int i = 0; i < MF; ++i)
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
+            for (int j = 0; j < NF; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j / (NF / JB)][i][j % (NF / JB)][v] = 0.f;
-
-    fetch(0);
-    load_a(0, 0);
-    stash(0);
-    for (int step = 0; step < steps; ++step) {
-        const int buf = step & 1;
-        __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
-        if (step + 1 < steps) fetch((step + 1) * kProductStep);
+                for (int v = 0; v < 16; ++v) acc[j / (NF / JB)][i][j % (NF / JB)][v] = 0.f;
+        fetch(0);
+        load_a(0, 0);
+        stash(scaled, 0);
+        for (int step = 0; step < steps; ++step) {
+            const int buf = step & 1;
+            __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
+            if (step + 1 < steps) fetch((step + 1) * kProductStep);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int next = 2 * step + ks + 1;
-            load_a(ks ^ 1, next < k16s ? next : k16s - 1);
+            for (int ks = 0; ks < 2; ++ks) {
+                const int next = 2 * step + ks + 1;
+                load_a(ks ^ 1, next < k16s ? next : k16s - 1);
 #pragma unroll
-            for (int j = 0; j < JB; ++j) {
-                u32x4 fb[NF / JB][3];
+                for (int j = 0; j < JB; ++j) {
+                    u32x4 fb[NF / JB][3];
 #pragma unroll
-                for (int q = 0; q < NF / JB; ++q)
+                    for (int q = 0; q < NF / JB; ++q)
 #pragma unroll
-                    for (int p = 0; p < 3; ++p)
-                        fb[q][p] = panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * (j * (NF / JB) + q) + (lane & 31)];
-                mfma_split(fa[ks], fb, acc[j]);
+                        for (int p = 0; p < 3; ++p)
+                            fb[q][p] =
+                                panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * (j * (NF / JB) + q) + (lane & 31)];
+                    mfma_split(fa[ks], fb, acc[j]);
+                }
             }
+            if (step + 1 < steps) stash(scaled, buf ^ 1);
         }
-        if (step + 1 < steps) stash(buf ^ 1);
+    };
+    run(std::false_type{});
+
+    // the columns' largest magnitudes: every wavefront looks at all of them and comes to the same result
+    auto top_of = [&](int c) {
+        float t = tops[0][c];
+#pragma unroll
+        for (int g = 1; g < T / BN; ++g) t = t > tops[g][c] ? t : tops[g][c];
+        return t;
+    };
+    tops[threadIdx.x / BN][my_col] = top;
+    __syncthreads();
+    bool odd = false;
+#pragma unroll
+    for (int c = 0; c < BN; c += 64) odd = odd || range_scale(top_of(c + lane)) != 1.f;
+    const bool again = __any(odd);
+    if (again) {
+        scale = range_scale(top_of(my_col));
+        // (nothing that only this run needs is to be computed, and kept in registers, before the first one)
+        asm volatile("" : "+v"(col_in));
+#pragma unroll
+        for (int i = 0; i < MF; ++i) asm volatile("" : "+v"(ap[i]));
+        run(std::true_type{});
     }
 
 #pragma unroll
     for (int j = 0; j < NF; ++j) {
         const long long col = n0 + wn * 32 * NF + 32 * j + (lane & 31);
+        if (again) {
+            const float undo = range_unscale(range_scale(top_of(wn * 32 * NF + 32 * j + (lane & 31))));
+#pragma unroll
+            for (int i = 0; i < MF; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j / (NF / JB)][i][j % (NF / JB)][v] *= undo;
+        }
         if (col >= a.B) continue;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
@@ -193,8 +235,12 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 // wavefront order.  Bound by the latency of memory, for large matrices by reading A: n = 1024, B = 64 in 6.8 us (39 with
 // tiles; 10.2 with 32 x 64 results per workgroup), n = 4096, B = 64 in 25 us = 4.0 TB/s (182).
 constexpr int kNarrowWaves = 8;
+struct NarrowShared {
+    float part[kNarrowWaves][16][64];
+    float tops[kNarrowWaves][32];      // largest magnitude of every column in each wavefront's part of the contraction
+};
 template <bool CPLX>
-__device__ __forceinline__ void product_narrow(const ProductArgs &a, float (&part)[kNarrowWaves][16][64])
+__device__ __forceinline__ void product_narrow(const ProductArgs &a, NarrowShared &sh)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -223,28 +269,50 @@ __device__ __forceinline__ void product_narrow(const ProductArgs &a, float (&par
         }
     };
     f32x16 acc[1][1];
+    float top = 0.f, scale = 1.f;
+    auto run = [&](auto scaled) __attribute__((always_inline)) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
-    load(0, k_from);
-    load(1, k_from + 1);
-    for (int kf = k_from; kf < k_to; kf += DEPTH) {
+        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+        load(0, k_from);
+        load(1, k_from + 1);
+        for (int kf = k_from; kf < k_to; kf += DEPTH) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            load((d + DEPTH - 1) % DEPTH, kf + d + DEPTH - 1);
-            if (kf + d < k_to) {
-                const Split8 s = split8(xr[d]);
-                const u32x4 fb[1][3] = {{s.h, s.m, s.l}};
-                mfma_split(fa[d], fb, acc);
+            for (int d = 0; d < DEPTH; ++d) {
+                load((d + DEPTH - 1) % DEPTH, kf + d + DEPTH - 1);
+                if (kf + d < k_to) {
+                    if constexpr (scaled()) {
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) xr[d][q] *= scale;
+                    } else {
+                        top = range_top(top, xr[d]);
+                    }
+                    const Split8 s = split8(xr[d]);
+                    const u32x4 fb[1][3] = {{s.h, s.m, s.l}};
+                    mfma_split(fa[d], fb, acc);
+                }
             }
         }
-    }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) part[wave][v][lane] = acc[0][0][v];
+        for (int v = 0; v < 16; ++v) sh.part[wave][v][lane] = acc[0][0][v];
+    };
+    run(std::false_type{});
+    top = range_top(top, __shfl_xor(top, 32), 0.f);
+    if (half == 0) sh.tops[wave][lane] = top;
     __syncthreads();
-    for (int v = wave; v < 16; v += kNarrowWaves) {
-        float sum = part[0][v][lane];
 #pragma unroll
-        for (int w = 1; w < kNarrowWaves; ++w) sum += part[w][v][lane];
+    for (int w = 0; w < kNarrowWaves; ++w) top = range_top(top, sh.tops[w][lane & 31], 0.f);
+    scale = range_scale(top);
+    if (__any(scale != 1.f)) {         // (the same in every wavefront)
+        __syncthreads();
+        run(std::true_type{});
+        __syncthreads();
+    }
+    const float undo = range_unscale(scale);
+    for (int v = wave; v < 16; v += kNarrowWaves) {
+        float sum = sh.part[0][v][lane];
+#pragma unroll
+        for (int w = 1; w < kNarrowWaves; ++w) sum += sh.part[w][v][lane];
+        sum *= undo;
         const int row = 32 * mb + 8 * (v >> 2) + 4 * half + (v & 3);
         if (row < a.m && n0 + (lane & 31) < a.B) a.D[(long long)row * a.ldd + col] = sum;
     }
@@ -253,8 +321,8 @@ __device__ __forceinline__ void product_narrow(const ProductArgs &a, float (&par
 template <bool CPLX>
 __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(ProductArgs a)
 {
-    __shared__ float part[kNarrowWaves][16][64];
-    product_narrow<CPLX>(a, part);
+    __shared__ NarrowShared sh;
+    product_narrow<CPLX>(a, sh);
 }
 
 template <int MW, int NW, int MF, int NF>

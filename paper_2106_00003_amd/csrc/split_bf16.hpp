@@ -47,6 +47,32 @@ __device__ __forceinline__ Split8 split8(const float (&x)[8])
     return s;
 }
 
+// Range.  The trailing pieces of a value below 2^-110 fall below the smallest bf16 numbers, so an operand whose columns
+// (for the contraction: rows) are that small as a whole would be multiplied with fewer bits than it has.  The kernels
+// therefore keep the largest magnitude of every column they bring, and where one is far from the middle of float32's range
+// (range_scale) they do their work once more with such columns scaled by a power of two, which they take out of the
+// results.  Small elements of a column that has larger ones do not count: what they lose is below 2^-134, and 2^-34 of the
+// column.  (The upper end leaves room for a column's norm to gather in one element.)
+constexpr float kRangeSmall = 0x1p-100f, kRangeLarge = 0x1p120f;
+__device__ __forceinline__ float range_scale(float top)
+{
+    return top >= kRangeLarge ? 0x1p-8f : (top < kRangeSmall && top > 0.f) ? 0x1p100f : 1.f;
+}
+__device__ __forceinline__ float range_unscale(float scale) { return scale > 1.f ? 0x1p-100f : scale < 1.f ? 0x1p8f : 1.f; }
+// the larger of top and |a|, |b| (NaN counts as nothing; the instruction by name: the compiler would quieten every operand
+// first)
+__device__ __forceinline__ float range_top(float top, float a, float b)
+{
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(top) : "v"(a), "v"(b));
+    return top;
+}
+__device__ __forceinline__ float range_top(float top, const float (&x)[8])
+{
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) top = range_top(top, x[i], x[i + 1]);
+    return top;
+}
+
 // acc[i][j] += a[i] b[j] over 16 contraction indices, float32 operands given as their pieces, smallest products first.
 // Each of the six instructions of a result needs the one before it, so the results take turns: back to back on one
 // accumulator the matrix cores wait.

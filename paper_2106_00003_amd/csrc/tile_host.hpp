@@ -46,17 +46,21 @@ struct TileBuffers {
     double2 *table;      // cos and sine of every rotation, in the order in which the tiles take them
     float *matrices;     // the tiles' matrices; later the blocks that the gradient's stages leave
     void *pieces;        // ... cut into bf16 pieces, in operand order
-    float *S;            // gradient only
+    float *S;            // gradient only (forward: null)
+    int *range;          // the same: the range of S's elements, behind it
+    unsigned *tops;      // of an operand's columns, one word each; null where the tiles are applied to I only
 };
 inline size_t tile_table_bytes(const TilePlan &g) { return (size_t)tile_coef_entries(g) * sizeof(double2); }
 inline size_t tile_matrices_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
 inline size_t tile_pieces_bytes(const TilePlan &g) { return (size_t)(tile_count(g) + 1) * kTilePieceWords * 16; }
-inline size_t tile_s_bytes(const TilePlan &g) { return 2 * tile_s_floats(g) * sizeof(float); }
+inline size_t tile_range_offset(const TilePlan &g) { return 2 * tile_s_floats(g) * sizeof(float); }
+inline size_t tile_s_bytes(const TilePlan &g) { return tile_range_offset(g) + 256; }
 
 // free_rows: pairs (i, j) with i < free_rows rotate (n - 1: all of them); rows: of the operand, n or n - 1.
 // Matrices of all tiles, cut into pieces: of U's side (forward) or of U^T's, which the gradient takes too.
+// X (may be null): the rows x B operand that tiles_apply is going to take, whose columns' range is looked at beside.
 void tiles_build(const TilePlan &g, const float *theta, const int *map, int free_rows, const TileBuffers &b, bool forward,
-                 hipStream_t stream);
+                 int rows, long long B, const float *X, hipStream_t stream);
 // Y <- U X or U^T X on B columns; X may be Y, nullptr means I
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const TileBuffers &b,
                  const float *X, float *Y, bool forward, hipStream_t stream);

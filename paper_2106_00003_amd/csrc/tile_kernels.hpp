@@ -130,6 +130,14 @@ __device__ __forceinline__ double2 tile_sincos(double th)
     return out;
 }
 
+// The range (split_bf16.hpp) of the gradient's matrix S, one for all of it: the stages keep its norm.  Words that the coefficient kernel clears
+// and the antisymmetric part's sets, 1 each: an element other than zero, one of the middle range or above, one above it.
+enum { kTileAny = 0, kTileMiddle = 1, kTileLarge = 2, kTileRangeWords = 3 };
+__device__ __forceinline__ float tile_scale(const int *range)
+{
+    return range[kTileLarge] ? range_scale(kRangeLarge) : range[kTileMiddle] || !range[kTileAny] ? 1.f : range_scale(kRangeSmall / 2);
+}
+
 // Coefficient table of the tiles, rows of 64 (S + 1 used) entries (cos, sine; the sine negated when the first row has the
 // larger label; (1, 0) for a pair that is bypassed or not in the tile).  Row r of an ordinary tile: row r of piece i with
 // every row of piece j, in order.  Row r of a special tile, for piece i and then (s rows further on) for piece i + P: with
@@ -143,10 +151,13 @@ __device__ __forceinline__ const double2 *tile_coef_table(const TilePlan &g, con
 }
 __global__ __launch_bounds__(256) void tile_coef_kernel(TilePlan g, const float *__restrict__ theta,
                                                         const int *__restrict__ map, int free_rows, long long entries,
-                                                        double2 *__restrict__ table)
+                                                        double2 *__restrict__ table, int *__restrict__ range,
+                                                        long long columns, unsigned *__restrict__ tops)
 {
     const int width = kTilePad / 2;
     const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (range && id < kTileRangeWords) range[id] = 0;
+    for (long long i = id; i < columns; i += (long long)gridDim.x * 256) tops[i] = 0u;
     if (id >= entries) return;
     const int slot = (int)(id % width);
     long long row = id / width;
@@ -322,11 +333,42 @@ __global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const do
 // a result can be the next product's operand without a move between lanes.
 __device__ __forceinline__ int tile_k(int half, int j) { return (j & 3) + 4 * half + 8 * (j >> 2); }
 
-// matrices -> pieces, one wavefront per fragment; transposed: of the transposed matrices
-// (and one identity, behind the last tile, that all tiles without a free pair share)
-__global__ __launch_bounds__(256) void tile_split_kernel(TilePlan g, int free_rows, const float *__restrict__ matrices,
-                                                         u32x4 *__restrict__ out, int transposed)
+// What the apply stages have to know of their operand's columns: tops (cleared by the coefficient kernel) takes the bits of
+// their largest magnitudes.  A workgroup takes 256 columns and kTileTopRows rows.
+constexpr int kTileTopRows = 32;
+struct TileTops {
+    int rows;
+    long long B;
+    const float *X;      // null: nothing to do
+    unsigned *tops;
+};
+inline long long tile_top_blocks(const TileTops &t)
 {
+    return t.X ? (t.B + 255) / 256 * ((t.rows + kTileTopRows - 1) / kTileTopRows) : 0;
+}
+__device__ __forceinline__ void tile_tops(const TileTops &t, long long block)
+{
+    const long long per = (t.B + 255) / 256, col = block % per * 256 + threadIdx.x;
+    const int r0 = (int)(block / per) * kTileTopRows;
+    if (col >= t.B) return;
+    float x[kTileTopRows], top = 0.f;
+#pragma unroll
+    for (int r = 0; r < kTileTopRows; ++r) x[r] = t.X[(long long)(r0 + r < t.rows ? r0 + r : r0) * t.B + col];
+#pragma unroll
+    for (int r = 0; r < kTileTopRows; r += 2) top = range_top(top, x[r], x[r + 1]);
+    if (__float_as_uint(top) > t.tops[col]) atomicMax(t.tops + col, __float_as_uint(top));
+}
+// matrices -> pieces, one wavefront per fragment; transposed: of the transposed matrices
+// (and one identity, behind the last tile, that all tiles without a free pair share).  The workgroups from `split_blocks`
+// on look at the operand.
+__global__ __launch_bounds__(256) void tile_split_kernel(TilePlan g, int free_rows, const float *__restrict__ matrices,
+                                                         u32x4 *__restrict__ out, int transposed, unsigned split_blocks,
+                                                         TileTops tops)
+{
+    if (blockIdx.x >= split_blocks) {
+        tile_tops(tops, blockIdx.x - split_blocks);
+        return;
+    }
     constexpr int PER = (kTilePad / 32) * (kTilePad / 16);
     const int lane = threadIdx.x & 63;
     const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -364,6 +406,8 @@ struct TileApplyArgs {
     const float *X;      // nullptr: the identity
     float *Y;            // X, or another array: then every row is written (first stage of a sweep)
     long long chunk;     // columns per workgroup
+    const unsigned *tops;   // largest magnitude of every column at the sweep's start, as bits (its stages keep a column's
+                            // norm: split_bf16.hpp, "Range"); null: all of the middle range
 };
 
 // One stage on B columns: rows of each tile <- matrix * rows.  A workgroup takes one tile and a run of columns, a wavefront
@@ -399,9 +443,11 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
 
     // a lane brings 16 rows of one column, those of its half of the fragments
     float xr[16];
+    unsigned top = 0u;
     auto fetch = [&](long long c0) {
         long long col = c0 + l32;
         col = col < n1 ? col : n1 - 1;
+        if (a.tops) top = a.tops[col];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int r = 16 * (q >> 3) + tile_k(half, q & 7);
@@ -411,12 +457,15 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
             xr[q] = there || held ? v : 0.f;
         }
     };
+    float undo = 1.f;   // of the columns in the panel
     auto stash = [&]() {
+        const float scale = range_scale(__uint_as_float(top));
+        undo = range_unscale(scale);
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
             float v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = xr[8 * f + q];
+            for (int q = 0; q < 8; ++q) v[q] = xr[8 * f + q] * scale;
             const Split8 sp = split8(v);
             panel[2 * wave + f][0][lane] = sp.h;
             panel[2 * wave + f][1][lane] = sp.m;
@@ -442,9 +491,9 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
             for (int v = 0; v < 16; ++v) {
                 const int r = 8 * (v >> 2) + 4 * half + (v & 3);
                 if (r < count && r >= skip)
-                    a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][0][v];
+                    a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][0][v] * undo;
                 else if (has_held && r == 31)
-                    a.Y[col] = acc[0][0][v];
+                    a.Y[col] = acc[0][0][v] * undo;
             }
         __syncthreads();
     }
@@ -454,7 +503,8 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
 // then row 0; places that hold no row are zero or never count.
 // S[p][q] = C[row p][row q] - C[row q][row p]; `second` (may be null): zeros, so that places without a row stay numbers
 __global__ __launch_bounds__(256) void tile_antisym_kernel(TilePlan g, int rows, const float *__restrict__ C,
-                                                           float *__restrict__ S, float *__restrict__ second)
+                                                           float *__restrict__ S, float *__restrict__ second,
+                                                           int *__restrict__ range)
 {
     __shared__ float other[32][33];
     const int ld = tile_ld(g);
@@ -475,12 +525,22 @@ __global__ __launch_bounds__(256) void tile_antisym_kernel(TilePlan g, int rows,
         other[r][tx] = (lr >= 0 && lp >= 0) ? C[(long long)lr * rows + lp] : 0.f;
     }
     __syncthreads();
+    float top = 0.f;
     for (int r = ty; r < 32; r += 8) {
         const int lr = label(p0 + r);
         const float mine = (lr >= 0 && lq >= 0) ? C[(long long)lr * rows + lq] : 0.f;
-        S[(long long)(p0 + r) * ld + q0 + tx] = mine - other[tx][r];
+        const float v = mine - other[tx][r];
+        S[(long long)(p0 + r) * ld + q0 + tx] = v;
         if (second) second[(long long)(p0 + r) * ld + q0 + tx] = 0.f;
+        top = range_top(top, v, 0.f);
     }
+    // (each word is written by the first wavefronts that get there: they all write the same)
+    auto set = [&](bool on, int word) {
+        if (__any(on) && (threadIdx.x & 63) == 0 && range[word] == 0) range[word] = 1;
+    };
+    set(top > 0.f, kTileAny);
+    set(top >= kRangeSmall, kTileMiddle);
+    set(top >= kRangeLarge, kTileLarge);
 }
 
 struct TileTwoSidedArgs {
@@ -490,6 +550,7 @@ struct TileTwoSidedArgs {
     const float *in;       // S before the stage
     float *out;            // S after it: the same array, or another one
     float *blocks;         // [tile][kTilePad][kTilePad]: every tile's own block before its stage
+    const int *range;      // of S
 };
 
 // Places in S of the local rows of a pair's two tiles (-1: holds no row)
@@ -556,6 +617,7 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwo
     const bool own = ux == uy;
     const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
     if (idx && idy) return;
+    const float scale = tile_scale(a.range), undo = range_unscale(scale);
     const int stride = tile_piece_stride(g), ld = tile_ld(g);
     tile_places(g, x, y, ux, uy, place_x, place_y);
     const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
@@ -597,8 +659,8 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwo
             float v[8];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                v[q] = sr[k][0][q];
-                v[4 + q] = sr[k][1][q];
+                v[q] = sr[k][0][q] * scale;
+                v[4 + q] = sr[k][1][q] * scale;
             }
             stash(k, v);
         }
@@ -662,7 +724,7 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwo
     // (every wavefront has read its part of S by now: the barriers above)
 #pragma unroll
     for (int j = 0; j < MF; ++j)
-        tile_store_both(g, a.out, R[0][j], wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
+        tile_store_both(g, a.out, R[0][j] * undo, wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
 }
 
 // The same for few tiles, where a pair per workgroup leaves compute units idle: a workgroup takes 32 columns of tile y, a
@@ -684,6 +746,7 @@ __global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(
     const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
     const bool own = ux == uy;
     const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
+    const float scale = tile_scale(a.range), undo = range_unscale(scale);
     const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
     const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * kTilePieceWords + (size_t)part * KF * 192 + lane;
     u32x4 fm[KF][1][3];
@@ -731,8 +794,8 @@ __global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(
         float v[8];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            v[q] = sr[k][0][q];
-            v[4 + q] = sr[k][1][q];
+            v[q] = sr[k][0][q] * scale;
+            v[4 + q] = sr[k][1][q] * scale;
         }
         const Split8 sp = split8(v);
         const u32x4 fs[1][3] = {{sp.h, sp.m, sp.l}};
@@ -763,7 +826,7 @@ __global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(
         mfma_split(fm[k], fv, acc[k & 1]);
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][0][0][v] += acc[1][0][0][v];
+    for (int v = 0; v < 16; ++v) acc[0][0][0][v] = (acc[0][0][0][v] + acc[1][0][0][v]) * undo;
     tile_store_both(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
 }
 
