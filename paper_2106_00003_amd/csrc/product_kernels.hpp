@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void split_matrix_kernel(int m, int k, int cpl
         const int c = k0 + j, at = !cplx ? c : (c < k / 2 ? 2 * c : 2 * c - k + 1);
         if (row < m && c < k) x[j] = src[(long long)row * k + at];
     }
-    const Split8 s = split8(x);
+    const Split8 s = split8<true>(x);
     u32x4 *o = out + f * 3 * 64 + lane;
     o[0] = s.h;
     o[64] = s.m;

@@ -1,12 +1,13 @@
 // Float32 products on the bf16 matrix cores.
 //
 // Precision.  The fastest matrix instructions of the chip take bf16 operands; a float32 value is exactly the sum of
-// three bf16 values (8 + 8 + 8 significand bits: x = h + m + l, h = x cut to bf16, m = x - h rounded to bf16,
+// three bf16 values (8 + 8 + 8 significand bits: x = h + m + l, h = x rounded to bf16, m = x - h rounded to bf16,
 // l = x - h - m, which fits).  A product of two float32 values is therefore the sum of nine exact bf16 products, of
-// which the six largest are formed (hh, hm, mh, hl, lh, mm); what is left out (ml, lm, ll) is below 2^-24 of the
-// product.  Sums are float32, sixteen products at a time.  So operands keep their 24 bits and the accumulation its
-// float32, and six bf16 instructions of 16-deep contraction still take 1/2.7 of the time of the eight float32 ones
-// (2-deep) they replace.
+// which the six largest are formed (hh, hm, mh, hl, lh, mm).  With x and y at least 2^e and 2^f, m is at most 2^(e-8) and
+// l at most 2^(e-17), so what is left out (ml, lm, ll) is at most 2^-24 of the product: what rounding it to float32 may
+// cost.  (Were h cut instead, m could be twice, l twice and the error four times as large.)  Sums are float32, sixteen
+// products at a time.  So operands keep their 24 bits and the accumulation its float32, and six bf16 instructions of
+// 16-deep contraction still take 1/2.7 of the time of the eight float32 ones (2-deep) they replace.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -21,8 +22,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// Eight float32 values as three rows of eight bf16 values with h + m + l == x (exact for every finite x whose last
-// bits are normal numbers).
+// Eight float32 values as three rows of eight bf16 values with h + m + l == x (exact for every x whose last bits are
+// normal numbers, up to the largest bf16 number, 2^128 - 2^120).
 struct Split8 {
     u32x4 h, m, l;
 };
@@ -31,15 +32,20 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
     const bf16x2 v = __builtin_convertvector((f32x2){a, b}, bf16x2);   // round to nearest even
     return __builtin_bit_cast(unsigned, v);
 }
+// CLAMP: of every finite x (h stays finite)
+template <bool CLAMP = false>
 __device__ __forceinline__ Split8 split8(const float (&x)[8])
 {
+    constexpr float kLargest = 0x1.fep127f;
     Split8 s;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const unsigned a = __float_as_uint(x[2 * i]), b = __float_as_uint(x[2 * i + 1]);
-        // the leading piece is cut, not rounded: it cannot overflow, whatever x is
-        s.h[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-        const float ra = x[2 * i] - __uint_as_float(a & 0xffff0000u), rb = x[2 * i + 1] - __uint_as_float(b & 0xffff0000u);
+        const float a = x[2 * i], b = x[2 * i + 1];
+        const unsigned h = CLAMP ? pack_bf16(__builtin_amdgcn_fmed3f(a, -kLargest, kLargest),
+                                             __builtin_amdgcn_fmed3f(b, -kLargest, kLargest))
+                                 : pack_bf16(a, b);
+        s.h[i] = h;
+        const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
         const unsigned m = pack_bf16(ra, rb);
         s.m[i] = m;
         s.l[i] = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));

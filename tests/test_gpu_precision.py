@@ -93,3 +93,44 @@ def test_small_complex_operands(n, B):
         dx, dth, dph = binding.givens_unitary_backward(th, ph, y, gg)
         want = binding.givens_unitary_backward(*wide, y.to(torch.complex128), gg.to(torch.complex128))
         assert worst_column(dx, want[0]) <= TOL_G and rel(dth, want[1]) <= TOL_G and rel(dph, want[2]) <= TOL_G
+
+
+def patterns(count):
+    """Values whose pieces are awkward: every bit pattern near the middle between two bf16 values and near the end of the
+    middle piece (where a cut leading piece leaves the largest remainders), and random ones."""
+    high = np.array([0x3f80, 0x3f81, 0x3fc0, 0x3ffe, 0x3fff, 0x4000, 0xbf80, 0x2f80], dtype=np.uint32)
+    low = np.array([0xff7f, 0x7fff, 0x8000, 0x8001, 0xfeff, 0xff80, 0xffff, 0x7f7f, 0x8080, 0x0001], dtype=np.uint32)
+    values = ((high[:, None] << np.uint32(16)) | low[None, :]).ravel()
+    random = np.random.default_rng(5).integers(0x3f800000, 0x40000000, size=max(0, count - values.size), dtype=np.uint32)
+    return torch.from_numpy(np.concatenate([values, random])[:count].view(np.float32).copy()).cuda()
+
+
+# One product per result: six piece products, three left out (2^-24 of the product), and the sums: the last one at most
+# 2^-23 (the matrix instructions do not round every sum to nearest), those before it on terms 2^-7 of it and smaller.
+ONE_PRODUCT = (2.0 ** -24 + 2.0 ** -23) * (1 + 2.0 ** -5)
+
+
+@pytest.mark.parametrize("B", [200, 20000])
+def test_one_product_of_every_pattern(B):
+    n = 256
+    u, x = patterns(n), patterns(B)
+    matrix = torch.diag(u)
+    operand = x.repeat(n, 1).contiguous()
+    want = u.double()[:, None] * x.double()[None, :]
+    got = binding.givens_apply_packed(binding.givens_pack(matrix), operand)
+    assert float(((got.double() - want) / want).abs().max()) <= ONE_PRODUCT
+
+
+# with all angles zero and one column, dtheta of a pair (i, j), i < n/2 <= j, is the product y_i g_j; both tile sizes
+@pytest.mark.parametrize("n,B", [(96, 200), (1024, 16384)])
+def test_contraction_of_every_pattern(n, B):
+    y, g = torch.zeros(n, B, device="cuda"), torch.zeros(n, B, device="cuda")
+    y[: n // 2, 5] = patterns(n // 2)
+    g[n // 2:, 5] = patterns(n // 2)
+    theta = torch.zeros(n * (n - 1) // 2, device="cuda")
+    _, dth = binding.givens_backward_ex(theta, y, g, reduction=binding.REDUCTION_GRAM)
+    assert binding.last_reduction() == binding.REDUCTION_GRAM
+    pairs = torch.from_numpy(binding.rr_schedule(n).reshape(-1, 2).astype(np.int64)).cuda()
+    across = (pairs[:, 0] < n // 2) & (pairs[:, 1] >= n // 2)
+    want = y[pairs[across, 0], 5].double() * g[pairs[across, 1], 5].double()
+    assert float(((dth[across].double() - want) / want).abs().max()) <= ONE_PRODUCT
