@@ -240,6 +240,12 @@ __global__ __launch_bounds__(64 * kSumGroups) void sum_slices_kernel(long long c
 
 // Tile and number of slices of a contraction.  Large tiles where they give every compute unit its two workgroups with
 // slices of at least 1024 columns, else 64 x 64 tiles and slices of at least 256 columns; at most 256 slices.
+//
+// A result's error grows with the square root of the additions behind it, six for every sixteen columns here, where the
+// float32 matrix instructions made eight.  Slices of at most 4096 columns keep it below theirs: n = 2048, B = 65536, normal
+// operands 2.5e-6 with slices of 16384, 1.3e-6 with 4096 (float32 instructions 2.3e-6), contraction 2.70 and 2.82 ms;
+// n = 1024, B = 131072 2.2e-6 with 8192, 1.6e-6 with 4096 (1.6e-6).
+constexpr long long kGramMaxSlice = 4096;
 struct GramPlan {
     bool large;
     int slices;
@@ -250,8 +256,9 @@ inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = 
     auto tiles = [&](int bm, int bn) { return (long long)((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
     auto slices_for = [&](long long t, long long want, long long cols) {
         long long s = (want + t - 1) / t;
-        const long long by_cols = B / cols > 1 ? B / cols : 1;
+        const long long by_cols = B / cols > 1 ? B / cols : 1, least = (B + kGramMaxSlice - 1) / kGramMaxSlice;
         s = s < by_cols ? s : by_cols;
+        s = s > least ? s : least;
         s = s < 256 ? s : 256;
         return (int)(s > 1 ? s : 1);
     };

@@ -134,3 +134,21 @@ def test_contraction_of_every_pattern(n, B):
     across = (pairs[:, 0] < n // 2) & (pairs[:, 1] >= n // 2)
     want = y[pairs[across, 0], 5].double() * g[pairs[across, 1], 5].double()
     assert float(((dth[across].double() - want) / want).abs().max()) <= ONE_PRODUCT
+
+
+# Sums over many columns, of one sign and of both: the error of a slice's sum is a walk of six roundings per 16 columns
+# of at most 2^-23 each, relative to sums that are 1/sqrt(3) of the last one in the mean square, so 2^-23 sqrt(6 4096 / 16)
+# / sqrt(3) / 2 = 1.3e-6 for roundings spread evenly; sums of one sign gather half of that and no drift.
+@pytest.mark.parametrize("n,B", [(64, 300000), (1024, 131072), (2048, 65536)])
+def test_long_contractions(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(4300 + n)
+    theta = torch.zeros(n * (n - 1) // 2, device="cuda")
+    pairs = torch.from_numpy(binding.rr_schedule(n).reshape(-1, 2).astype(np.int64)).cuda()
+    across = (pairs[:, 0] < n // 2) & (pairs[:, 1] >= n // 2)
+    i, j = pairs[across, 0], pairs[across, 1] - n // 2
+    for draw, most in ((torch.rand, 6e-7), (torch.randn, 1.8e-6)):
+        y, g = torch.zeros(n, B, device="cuda"), torch.zeros(n, B, device="cuda")
+        y[: n // 2], g[n // 2:] = (draw(n // 2, B, device="cuda", generator=gen) for _ in range(2))
+        _, dth = binding.givens_backward_ex(theta, y, g, want_dx=False, reduction=binding.REDUCTION_GRAM)
+        c = sum(y[: n // 2, k: k + 8192].double() @ g[n // 2:, k: k + 8192].double().T for k in range(0, B, 8192))
+        assert rel(dth[across], c[i, j]) <= most
