@@ -135,8 +135,8 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
  * givens_forward_noalloc -- givens_forward for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels
  * and bit-identical results, but the coefficient tables (cos/sin or scaled / lifted coefficients, row
- * factors, renormalisation rows, the range-check flag) and what a wide batch needs (U, and a copy of some
- * columns when Y is X) are written to a static device array of
+ * factors, renormalisation rows, the range-check flag; or the tiles' matrices) and what a wide batch needs
+ * (U, and a copy of some columns when Y is X) are written to a static device array of
  * GIVENS_NOALLOC_BYTES bytes inside the library instead of the hipMalloc'ed workspace, so the call makes
  * no hipMalloc, hipFree or other allocating call.  Every GPU the library runs on holds that array until
  * the process ends.
@@ -148,7 +148,8 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
  *   Per-kernel timing (givens_set_timing) is not recorded for this call.
  */
 #define GIVENS_NOALLOC_MAX_N 1024
-#define GIVENS_NOALLOC_BYTES 21029120 /* n = 1024: flag words, table, row factors, renormalisation rows; U, its pieces, a copy of 512 columns */
+#define GIVENS_NOALLOC_BYTES 53737728 /* n = 1024: flag words; tables of a sweep, or tables, matrices and pieces of 180 tiles; */
+                                      /* U, its pieces, a copy of 512 columns                                              */
 int givens_forward_noalloc(int n, int64_t B, const float *theta, const float *X, float *Y, void *stream);
 
 /*

@@ -445,18 +445,38 @@ int workspace_product_storage(Workspace &ws, int rows, long long B, bool in_plac
 constexpr long long kNoAllocCopyCols = 512;
 constexpr int kNoAllocMaxN = GIVENS_NOALLOC_MAX_N;
 constexpr size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
-constexpr size_t noalloc_bytes(int n)
+// Parts of the array for a problem of n dimensions.  The tables are the family's sweep's or the tiles', never both.
+constexpr size_t noalloc_sweep_bytes(int n)
 {
-    const size_t N = (size_t)n * (n - 1) / 2;
+    const long long N = (long long)n * (n - 1) / 2;
     return round_up_256(N * sizeof(float2))                                                // the table
            + round_up_256((size_t)(n - 1) * n * sizeof(float))                             // row factors
-           + round_up_256((size_t)((n - 1 + kRenormPeriod - 1) / kRenormPeriod) * (n / 2) * sizeof(float2))
-           + kFlagBytes                                                                    // flag words
+           + round_up_256((size_t)((n - 1 + kRenormPeriod - 1) / kRenormPeriod) * (n / 2) * sizeof(float2));
+}
+// widest operand that the tiles take without the product: tiles_by_product
+constexpr long long noalloc_tile_cols(int n) { return std::max<long long>(kProductMinRatio * n, kProductMinB); }
+constexpr size_t noalloc_tile_bytes(int n)
+{
+    if (n < kTileMinN) return 0;
+    const TilePlan g = tile_plan(n);
+    return round_up_256(tile_table_bytes(g)) + round_up_256(tile_matrices_bytes(g)) + round_up_256(tile_pieces_bytes(g)) +
+           round_up_256(noalloc_tile_cols(n) * sizeof(unsigned));
+}
+constexpr size_t noalloc_tables_bytes(int n) { return std::max(noalloc_sweep_bytes(n), noalloc_tile_bytes(n)); }
+constexpr size_t noalloc_bytes(int n)
+{
+    return kFlagBytes + noalloc_tables_bytes(n)
            + round_up_256((size_t)n * n * sizeof(float))                                   // U
            + round_up_256((size_t)product_pieces(n, n) * sizeof(u32x4))                    // ... its pieces
            + round_up_256((size_t)n * kNoAllocCopyCols * sizeof(float));                   // columns of an in-place call
 }
-constexpr size_t kNoAllocBytes = noalloc_bytes(kNoAllocMaxN);
+constexpr size_t noalloc_most_bytes()
+{
+    size_t most = 0;
+    for (int n = 2; n <= kNoAllocMaxN; n += 2) most = std::max(most, noalloc_bytes(n));
+    return most;
+}
+constexpr size_t kNoAllocBytes = noalloc_most_bytes();
 static_assert(kNoAllocBytes == GIVENS_NOALLOC_BYTES, "the header states the size of the static array");
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 // Address of `scratch` on each device (every GPU holds its own copy of the array): looked up once per
@@ -464,7 +484,7 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 unsigned char *g_scratch_ptr[kMaxDevices] = {};
 int g_scratch_turn[kMaxDevices] = {};   // which of the array's two flag words the next call uses
 
-int static_storage(int dev, int n, CoefStorage<float> *out, ProductStorage *prod)
+int static_storage(int dev, int n, CoefStorage<float> *out, TileBuffers *tiles, ProductStorage *prod)
 {
     if (n > kNoAllocMaxN) return GIVENS_ERR_UNSUPPORTED;
     if (!g_scratch_ptr[dev]) {
@@ -485,10 +505,20 @@ int static_storage(int dev, int n, CoefStorage<float> *out, ProductStorage *prod
     out->flag = words + g_scratch_turn[dev];
     out->next_flag = words + (g_scratch_turn[dev] ^ 1);
     g_scratch_turn[dev] ^= 1;
+    unsigned char *const tables = at;
     out->table = reinterpret_cast<float2 *>(take(N * sizeof(float2)));
     out->scale = reinterpret_cast<float *>(take((size_t)(n - 1) * n * sizeof(float)));
     out->renorm = reinterpret_cast<float *>(take((size_t)renorm_periods(n) * (n / 2) * sizeof(float2)));
     out->factor = nullptr;
+    at = tables;
+    if (n >= kTileMinN) {
+        const TilePlan g = tile_plan(n);
+        tiles->table = reinterpret_cast<double2 *>(take(tile_table_bytes(g)));
+        tiles->matrices = reinterpret_cast<float *>(take(tile_matrices_bytes(g)));
+        tiles->pieces = take(tile_pieces_bytes(g));
+        tiles->tops = reinterpret_cast<unsigned *>(take(noalloc_tile_cols(n) * sizeof(unsigned)));
+    }
+    at = tables + noalloc_tables_bytes(n);
     prod->matrix = reinterpret_cast<float *>(take((size_t)n * n * sizeof(float)));
     prod->pieces = reinterpret_cast<u32x4 *>(take((size_t)product_pieces(n, n) * sizeof(u32x4)));
     prod->copy = reinterpret_cast<float *>(take((size_t)n * kNoAllocCopyCols * sizeof(float)));
@@ -941,15 +971,19 @@ int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, long long oper
     }
     return GIVENS_OK;
 }
-// Y = U X or U^T X (forward = false) by the tiles' matrices, which are there; a wide batch through U itself
-int run_tiles_apply(Workspace &ws, int dev, const Problem &pb, const TilePlan &g, const TileBuffers &b, long long B,
-                    const float *X, float *Y, bool forward, hipStream_t stream)
+// Y = U X or U^T X (forward = false) by the tiles' matrices, which are there; a wide batch through U itself.  `ws`, `given`:
+// as for run_forward.
+int run_tiles_apply(Workspace *ws, int dev, const Problem &pb, const TilePlan &g, const TileBuffers &b, long long B,
+                    const float *X, float *Y, bool forward, hipStream_t stream, const ProductStorage *given = nullptr)
 {
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (X && tiles_by_product(pb.rows, B)) {
         ProductStorage st;
-        if (int rc = workspace_product_storage(ws, pb.rows, B, X == Y, &st)) return rc;
+        if (given)
+            st = *given;
+        else if (int rc = workspace_product_storage(*ws, pb.rows, B, X == Y, &st))
+            return rc;
         {
             Span span(1, stream);
             tiles_apply(g, cus, pb.rows, pb.m, pb.rows, b, nullptr, st.matrix, forward, stream);
@@ -961,20 +995,25 @@ int run_tiles_apply(Workspace &ws, int dev, const Problem &pb, const TilePlan &g
     GIVENS_HIP(hipGetLastError());
     return GIVENS_OK;
 }
-int tiles_forward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *X, float *Y,
-                  bool transpose, hipStream_t stream)
+// storage, given: of a call that may not allocate
+int tiles_forward(Workspace *ws, int dev, const Problem &pb, long long B, const float *theta, const float *X, float *Y,
+                  bool transpose, hipStream_t stream, const TileBuffers *storage = nullptr,
+                  const ProductStorage *given = nullptr)
 {
     if (pb.n < kTileMinN || pb.n > kTileMaxN) return GIVENS_ERR_UNSUPPORTED;
     const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
     const float *swept = X && !tiles_by_product(pb.rows, B) ? X : nullptr;
-    if (int rc = tile_storage(ws, g, false, swept ? B : 0, &b)) return rc;
+    if (storage)
+        b = *storage;
+    else if (int rc = tile_storage(*ws, g, false, swept ? B : 0, &b))
+        return rc;
     {
         Span span(0, stream);
         tiles_build(g, theta, pb.map, pb.m, b, !transpose, pb.rows, B, swept, stream);
     }
     t_state.last_flag = nullptr;
-    return run_tiles_apply(ws, dev, pb, g, b, B, X, Y, !transpose, stream);
+    return run_tiles_apply(ws, dev, pb, g, b, B, X, Y, !transpose, stream, given);
 }
 int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *Y, const float *G,
                    float *dX, float *dtheta, hipStream_t stream)
@@ -1005,7 +1044,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     t_state.last_flag = nullptr;
     t_state.last_reduction = GIVENS_REDUCTION_GRAM;
     t_state.last_chains = 0;
-    return dX ? run_tiles_apply(ws, dev, pb, g, b, B, G, dX, false, stream) : GIVENS_OK;
+    return dX ? run_tiles_apply(&ws, dev, pb, g, b, B, G, dX, false, stream) : GIVENS_OK;
 }
 
 // rows, m: see Problem.  The unrestricted entry points pass an even rows and m = rows - 1.
@@ -1036,20 +1075,24 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
         if (int rc = pick_forward_family<T>(n, B, opt.kernel, &fam)) return rc;
     Coefs<T> coefs;
     const long long swept = identity ? B : swept_columns<T>(fam, rows, B);
-    if constexpr (std::is_same<T, float>::value) {
-        if (!no_alloc && wants_tiles(opt, n, swept, false)) {
-            t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
-            return tiles_forward(*ws, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream);
-        }
-    }
-    if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
+    bool tiles = false;
+    if constexpr (std::is_same<T, float>::value) tiles = wants_tiles(opt, n, swept, false);
+    if (!tiles && opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
+    if (tiles) t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
     const FormPolicy policy =
-        form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept));
+        form_policy(!tiles && fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept));
+    if constexpr (std::is_same<T, float>::value)
+        if (tiles && !no_alloc)
+            return tiles_forward(ws, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream);
     if (no_alloc) {
         if constexpr (std::is_same<T, float>::value) {
             CoefStorage<float> st;
+            TileBuffers tile_buffers{};
             ProductStorage prod;
-            if (int rc = static_storage(dev, n, &st, &prod)) return rc;
+            if (int rc = static_storage(dev, n, &st, &tile_buffers, &prod)) return rc;
+            if (tiles)
+                return tiles_forward(nullptr, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream,
+                                     &tile_buffers, &prod);
             if (int rc = build_coefs<float>(st, pb, theta, true, policy, stream, &coefs, transpose)) return rc;
             return run_forward<float>(nullptr, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream, &prod);
         }

@@ -14,7 +14,7 @@ struct TilePlan {
 constexpr int kTilePad = 128;                 // rows of a tile's matrix (64: n = 4096 applied in 4.6 ms against 2.7)
 constexpr int kTileSlots = kTilePad / 2 - 1;  // longest piece: 2 s + 1 <= kTilePad
 constexpr int kTileMinN = 8, kTileMaxN = 8192;
-inline TilePlan tile_plan(int n)
+constexpr TilePlan tile_plan(int n)
 {
     TilePlan p{};
     p.n = n;
@@ -27,9 +27,9 @@ inline TilePlan tile_plan(int n)
     p.stages = 2 * p.P - p.first;
     return p;
 }
-inline long long tile_count(const TilePlan &p) { return (long long)p.stages * p.P; }
+constexpr long long tile_count(const TilePlan &p) { return (long long)p.stages * p.P; }
 constexpr int kTilePieceWords = kTilePad * kTilePad * 3 / 8;   // u32x4 per tile
-inline long long tile_coef_entries(const TilePlan &g) { return (long long)g.s * (2 * g.P + tile_count(g)) * (kTilePad / 2); }
+constexpr long long tile_coef_entries(const TilePlan &g) { return (long long)g.s * (2 * g.P + tile_count(g)) * (kTilePad / 2); }
 
 // the gradient's matrix: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on), then row 0
 inline __host__ __device__ int tile_piece_stride(const TilePlan &g) { return (g.s + 3) / 4 * 4; }
@@ -50,9 +50,9 @@ struct TileBuffers {
     int *range;          // the same: the range of S's elements, behind it
     unsigned *tops;      // of an operand's columns, one word each; null where the tiles are applied to I only
 };
-inline size_t tile_table_bytes(const TilePlan &g) { return (size_t)tile_coef_entries(g) * sizeof(double2); }
-inline size_t tile_matrices_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
-inline size_t tile_pieces_bytes(const TilePlan &g) { return (size_t)(tile_count(g) + 1) * kTilePieceWords * 16; }
+constexpr size_t tile_table_bytes(const TilePlan &g) { return (size_t)tile_coef_entries(g) * sizeof(double2); }
+constexpr size_t tile_matrices_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
+constexpr size_t tile_pieces_bytes(const TilePlan &g) { return (size_t)(tile_count(g) + 1) * kTilePieceWords * 16; }
 inline size_t tile_range_offset(const TilePlan &g) { return 2 * tile_s_floats(g) * sizeof(float); }
 inline size_t tile_s_bytes(const TilePlan &g) { return tile_range_offset(g) + 256; }
 

@@ -73,3 +73,24 @@ def test_sizes_beyond_the_static_array_are_rejected():
     assert info.value.code == -5
     torch.cuda.synchronize()
     assert float(y_d.abs().max()) == 0.0   # nothing was launched
+
+
+# under the library's defaults, where some sizes take the tiles by themselves: their smallest, sizes without a carousel
+# shape, with one of 3, 5 and 7 slots, and the largest; narrow, below and above the batch that goes through U
+@pytest.mark.parametrize("n", [402, 514, 882, 998, 1002, 1006, 1010, 1022, 1024])
+def test_equal_under_the_library_defaults(n):
+    binding.set_rotation_form(binding.FORM_AUTO)
+    binding.set_kernel(binding.KERNEL_AUTO)
+    for B in (1, 33, 700, 2047, 2100):
+        data = inputs.make_custom(n, B, seed=410 + n)
+        th, x = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X"))
+        print(f"[noalloc] defaults n={n} B={B}", flush=True)
+        want = binding.givens_forward(th, x)
+        family = binding.last_kernel()
+        y = torch.full_like(x, float("nan"))
+        binding.givens_forward_noalloc(th, x, y)
+        assert binding.last_kernel() == family
+        assert torch.equal(y, want)
+        buf = x.clone()
+        binding.givens_forward_noalloc(th, buf, buf)
+        assert torch.equal(buf, want)
