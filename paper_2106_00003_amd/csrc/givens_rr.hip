@@ -484,7 +484,8 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 unsigned char *g_scratch_ptr[kMaxDevices] = {};
 int g_scratch_turn[kMaxDevices] = {};   // which of the array's two flag words the next call uses
 
-int static_storage(int dev, int n, CoefStorage<float> *out, TileBuffers *tiles, ProductStorage *prod)
+// try_forms: the call makes the range check (only then do the flag words take turns)
+int static_storage(int dev, int n, bool try_forms, CoefStorage<float> *out, TileBuffers *tiles, ProductStorage *prod)
 {
     if (n > kNoAllocMaxN) return GIVENS_ERR_UNSUPPORTED;
     if (!g_scratch_ptr[dev]) {
@@ -502,9 +503,11 @@ int static_storage(int dev, int n, CoefStorage<float> *out, TileBuffers *tiles, 
     // the flag words come first: their place must not depend on n, because the word a call uses has to be zero
     // when the call starts and it is the call before that puts it to zero (a fresh array is all zero)
     unsigned *words = reinterpret_cast<unsigned *>(take(kFlagBytes));
-    out->flag = words + g_scratch_turn[dev];
-    out->next_flag = words + (g_scratch_turn[dev] ^ 1);
-    g_scratch_turn[dev] ^= 1;
+    if (try_forms) {
+        out->flag = words + g_scratch_turn[dev];
+        out->next_flag = words + (g_scratch_turn[dev] ^ 1);
+        g_scratch_turn[dev] ^= 1;
+    }
     unsigned char *const tables = at;
     out->table = reinterpret_cast<float2 *>(take(N * sizeof(float2)));
     out->scale = reinterpret_cast<float *>(take((size_t)(n - 1) * n * sizeof(float)));
@@ -1089,7 +1092,7 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
             CoefStorage<float> st;
             TileBuffers tile_buffers{};
             ProductStorage prod;
-            if (int rc = static_storage(dev, n, &st, &tile_buffers, &prod)) return rc;
+            if (int rc = static_storage(dev, n, policy.try_forms, &st, &tile_buffers, &prod)) return rc;
             if (tiles)
                 return tiles_forward(nullptr, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream,
                                      &tile_buffers, &prod);

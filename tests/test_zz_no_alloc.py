@@ -94,3 +94,23 @@ def test_equal_under_the_library_defaults(n):
         buf = x.clone()
         binding.givens_forward_noalloc(th, buf, buf)
         assert torch.equal(buf, want)
+
+
+def test_the_range_check_after_calls_without_one():
+    """The flag words take turns among the calls that make a range check, whatever runs between them."""
+    n, B = 512, 40
+    th, x = torch.empty(n * (n - 1) // 2, device="cuda"), torch.randn(n, B, device="cuda")
+    y = torch.empty_like(x)
+    for large, small in ((3.0, 0.1), (3.0, 0.1)):
+        for between in (0, 1, 2):
+            th.fill_(large)
+            binding.set_rotation_form(binding.FORM_RANGE)
+            binding.givens_forward_noalloc(th, x, y)
+            assert binding.last_rotation_form() == binding.FORM_LIFTED
+            binding.set_rotation_form(binding.FORM_STANDARD)
+            for _ in range(between):
+                binding.givens_forward_noalloc(th, x, y)
+            binding.set_rotation_form(binding.FORM_RANGE)
+            th.fill_(small)
+            binding.givens_forward_noalloc(th, x, y)
+            assert binding.last_rotation_form() == binding.FORM_SCALED
