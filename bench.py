@@ -16,9 +16,13 @@ givens_forward_prepared + givens_backward_prepared instead of the plain calls.
 
 Prints ONE JSON line.  Besides the contract fields it carries
   roofline      forward sweep kernel against the vector-FP32 peak (6 flop per update); `frac_with_tables`
-                counts the coefficient kernels of the forward call into the time
-  roofline_bwd  reverse sweep kernel(s) against the same peak (16 flop per update over the columns they sweep)
-  roofline_gram the Gram-matrix contraction against the dense float32 MFMA peak, when the backward call used it
+                counts the coefficient kernels of the forward call into the time.  A wide batch is multiplied with U:
+                then the product (2 n^2 B) against the matrix peak below, the sweep that builds U in its time; and
+                where the rotations run as tiles, the matrix they make up (2 n^2 per column), against the same
+  roofline_bwd  reverse sweep kernel(s) against the vector peak (16 flop per update over the columns they sweep); with
+                the product behind dX, or tiles, the same as for the forward call
+  roofline_gram the Gram-matrix contraction against the matrix peak, when the backward call used it
+  The matrix peak is that of float32 products on the bf16 matrix cores, six bf16 products each.
   cpu_baseline  the fp64 C oracle (oracle/givens_oracle.c) timed on the host cores on a bounded sample of
                 the same workload's columns
 Kernel durations come from HIP events that the library records on the launch stream around each group of
@@ -39,7 +43,7 @@ if ROOT not in sys.path:
 
 PEAK_FP32_VECTOR_TFLOPS = 157.3      # MI355X published vector FP32 peak (256 CU x 2.4 GHz x 256 flop/clk)
 PEAK_FP64_VECTOR_TFLOPS = 78.6       # same for FP64
-PEAK_FP32_MFMA_TFLOPS = 157.3        # dense float32 MFMA peak
+PEAK_FP32_PRODUCT_TFLOPS = 2500.0 / 6  # dense bf16 MFMA peak, six bf16 products for a float32 one
 FWD_FLOP_PER_UPDATE = 6              # 4 mul + 2 add (Algorithm 1's two row updates)
 BWD_FLOP_PER_UPDATE = 16             # two transposed rotations (12) + two-term product and sum (4)
 CPU_SAMPLE_UPDATES = 4.0e10          # the oracle's sample: about this many (pair, column) updates forward
@@ -90,7 +94,12 @@ def _bench_unitary(args, binding, torch, np) -> int:
     ms = 1e3 * (time.perf_counter() - t0) / args.steps
     binding.set_timing(False)
     family = {binding.KERNEL_LDS: "lds", binding.KERNEL_CAROUSEL: "carousel"}.get(binding.last_kernel(), "?")
-    # 9 FMA per (pair, complex column) forward and 26 in the reverse sweep in the carousel family
+    binding.givens_unitary_forward(theta, phi, x, Y=y)
+    product = binding.last_product()
+    binding.givens_unitary_backward(theta, phi, y, g, dX=dx, dtheta=dth, dphi=dph)
+    product = [product, binding.last_product()]
+    # 9 FMA per (pair, complex column) forward and 26 in the reverse sweep in the carousel family (not told for wide
+    # batches, which are multiplied: U and U^H come from sweeps over n columns in the same time)
     fwd_sweep = float(np.mean([t[0][1] for t in times]))
     bwd_sweep = float(np.mean([t[1][1] for t in times]))
     print(json.dumps({
@@ -98,14 +107,14 @@ def _bench_unitary(args, binding, torch, np) -> int:
         "unit": "updates/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms,
         "higher_is_better": True, "dtype": "c64", "data": "synthetic",
         "config": {"workload": f"unitary_n{n}_B{B}_c64", "n": n, "B": B, "angles": 2 * N,
-                   "kernel_family": family},
+                   "kernel_family": family, "product": product},
         "kernel_ms": {"fwd_table": float(np.mean([t[0][0] for t in times])),
                       "fwd_sweep": fwd_sweep,
                       "bwd_table": float(np.mean([t[1][0] for t in times])),
                       "bwd_sweep": bwd_sweep,
                       "bwd_reduce": float(np.mean([t[1][2] for t in times]))},
         "executed_tflops": {"fwd_sweep": 18.0 * N * B / (fwd_sweep * 1e-3) / 1e12,
-                            "bwd_sweep": 52.0 * N * B / (bwd_sweep * 1e-3) / 1e12} if family == "carousel" else None}))
+                            "bwd_sweep": 52.0 * N * B / (bwd_sweep * 1e-3) / 1e12} if family == "carousel" and not any(product) else None}))
     return 0
 
 
@@ -219,6 +228,8 @@ def main() -> int:
     frozen_token = binding.givens_prepare(th_d, n, restricted_m, directions, batch=B) if prepared == "frozen" else None
 
     timing_on = [True]
+    routes = [None]   # when a list: (kernel family, product) of each call of a step
+    note = lambda: routes[0] is not None and routes[0].append((binding.last_kernel(), binding.last_product()))  # noqa: E731
     zeros = (0.0, 0.0, 0.0, 0.0)
     last_timing = lambda: binding.last_timing() if timing_on[0] else zeros  # noqa: E731
 
@@ -234,20 +245,26 @@ def main() -> int:
             else:
                 binding.givens_forward_prepared(token, x_d, Y=y_d)
             t_f = last_timing()
+            note()
             binding.givens_backward_prepared(token, y_d, g_d, N, dX=dx_d, dtheta=dth_d, want_dx=not identity)
             t_b = last_timing()
+            note()
             return (t_p[0] + t_f[0], t_f[1], 0.0, 0.0), t_b
         if restricted_m is not None:
             binding.givens_forward_restricted(th_d, x_d, restricted_m, Y=y_d)
             t_f = last_timing()
+            note()
             binding.givens_backward_restricted(th_d, y_d, g_d, restricted_m, dX=dx_d, dtheta=dth_d)
+            note()
             return t_f, last_timing()
         if identity:
             binding.givens_build(th_d, n, U=y_d)
         else:
             binding.givens_forward(th_d, x_d, Y=y_d)
         t_f = last_timing()
+        note()
         binding.givens_backward(th_d, y_d, g_d, dX=dx_d, dtheta=dth_d, want_dx=not identity)
+        note()
         return t_f, last_timing()
 
     args.enqueue_only = args.enqueue_only or args.graph
@@ -284,9 +301,14 @@ def main() -> int:
         kernel_times = [step() for _ in range(min(args.steps, 20))]
         torch.cuda.synchronize()
     binding.set_timing(False)
-    family = binding.last_kernel()
     form = binding.last_rotation_form() if wl.dtype == "f32" else binding.FORM_STANDARD
     reduction = binding.last_reduction()
+    chains = binding.last_chains()
+    timing_on[0] = False
+    routes[0] = []
+    step()
+    torch.cuda.synchronize()
+    (fwd_family, fwd_product), (family, bwd_product) = routes[0]
 
     if args.pmc_copy:
         scratch = torch.empty_like(g_d)
@@ -300,22 +322,36 @@ def main() -> int:
     fwd_table, fwd_sweep = mean(0, 0), mean(0, 1)
     bwd_table, bwd_sweep, bwd_reduce, bwd_gram = mean(1, 0), mean(1, 1), mean(1, 2), mean(1, 3)
     peak = PEAK_FP64_VECTOR_TFLOPS if wl.dtype == "f64" else PEAK_FP32_VECTOR_TFLOPS
-    family_name = {binding.KERNEL_LDS: "lds", binding.KERNEL_CAROUSEL: "carousel", binding.KERNEL_COLUMN: "column"}[family]
-    fwd_kernel = {"lds": "lds_forward_kernel", "carousel": "carousel_forward_kernel",
-                  "column": "column_forward_kernel"}[family_name]
-    chains = binding.last_chains() if family_name == "carousel" and wl.dtype == "f32" else 0
-    bwd_kernel = ("lds_backward_kernel" if family_name == "lds"
-                  else "carousel_backward_chain_kernel" if chains else "carousel_backward_kernel")
-
-    fwd_tflops = FWD_FLOP_PER_UPDATE * updates / (fwd_sweep * 1e-3) / 1e12
+    names = {binding.KERNEL_LDS: "lds", binding.KERNEL_CAROUSEL: "carousel", binding.KERNEL_COLUMN: "column",
+             binding.KERNEL_TILES: "tiles"}
+    family_name, fwd_name = names[family], names[fwd_family]
+    chains = chains if family_name == "carousel" and wl.dtype == "f32" else 0
+    fwd_kernel = {"tiles": "tile_apply_kernel", "column": "carousel_forward_kernel"}.get(fwd_name, f"{fwd_name}_forward_kernel")
+    bwd_kernel = {"tiles": "tile_two_sided_kernel", "column": "carousel_backward_kernel"}.get(
+        family_name, "carousel_backward_chain_kernel" if chains else f"{family_name}_backward_kernel")
     gram = reduction == binding.REDUCTION_GRAM
-    if gram:
-        # the sweeps of the Gram form: the reverse sweep over the n columns of C = Y G^T (16 flop per update) and,
-        # when dX is wanted, a forward-type sweep over the B columns of G (6 flop per update)
-        bwd_flops = BWD_FLOP_PER_UPDATE * float(N) * n + (0 if identity else FWD_FLOP_PER_UPDATE * updates)
+
+    # operations, the peak they are held against and what bounds them, of the forward call and of the backward call
+    dense = 2.0 * n * n * B
+    if fwd_product:
+        fwd_kernel, fwd_flops, fwd_peak, fwd_bound = f"product_kernel (U by {fwd_kernel})", dense, PEAK_FP32_PRODUCT_TFLOPS, "mfma"
+    elif fwd_name == "tiles":
+        fwd_flops, fwd_peak, fwd_bound = dense, PEAK_FP32_PRODUCT_TFLOPS, "mfma"
     else:
-        bwd_flops = BWD_FLOP_PER_UPDATE * updates
-    bwd_tflops = bwd_flops / (bwd_sweep * 1e-3) / 1e12
+        fwd_flops, fwd_peak, fwd_bound = FWD_FLOP_PER_UPDATE * updates, peak, "alu"
+    swept = n if gram else B
+    if family_name == "tiles":
+        # dtheta from C: the matrix applied to both sides of C - C^T, n columns each; dX: applied once to G
+        bwd_flops, bwd_peak, bwd_bound = 4.0 * n ** 3 + (0 if identity else dense), PEAK_FP32_PRODUCT_TFLOPS, "mfma"
+    elif bwd_product:
+        bwd_kernel, bwd_flops, bwd_peak, bwd_bound = (f"product_kernel (dX, U^T by {bwd_kernel} on C = Y G^T)", dense,
+                                                      PEAK_FP32_PRODUCT_TFLOPS, "mfma")
+    else:
+        bwd_flops, bwd_peak, bwd_bound = BWD_FLOP_PER_UPDATE * float(N) * swept, peak, "alu"
+    # (with tiles the sums of dtheta are timed as the reduction)
+    bwd_time = bwd_sweep + (bwd_reduce if family_name == "tiles" else 0.0)
+    fwd_tflops = fwd_flops / (fwd_sweep * 1e-3) / 1e12 if fwd_sweep else 0.0
+    bwd_tflops = bwd_flops / (bwd_time * 1e-3) / 1e12 if bwd_time else 0.0
     result = {
         "metric": "givens_row_pair_column_updates_per_s_fwd_bwd",
         "value": updates / (ms_per_step * 1e-3),
@@ -338,7 +374,7 @@ def main() -> int:
                    "host": ("replays a HIP graph of one step; kernel_ms from a second, eager pass" if args.graph
                             else "enqueues only; kernel_ms from a second pass" if args.enqueue_only
                             else "waits for each call's timing events"),
-                   "kernel_family": family_name,
+                   "kernel_family": family_name, "forward_family": fwd_name, "product": [fwd_product, bwd_product],
                    "rotation_form": {binding.FORM_STANDARD: "standard", binding.FORM_SCALED: "scaled",
                                      binding.FORM_LIFTED: "lifted"}[form],
                    "reduction": {binding.REDUCTION_TWO_STAGE: "two_stage", binding.REDUCTION_GRAM: "gram"}[reduction]},
@@ -347,22 +383,21 @@ def main() -> int:
         "bwd_ms": bwd_table + bwd_sweep + bwd_reduce + bwd_gram,
         "kernel_ms": {"fwd_table": fwd_table, "fwd_sweep": fwd_sweep, "bwd_table": bwd_table,
                       "bwd_sweep": bwd_sweep, "bwd_reduce": bwd_reduce, "bwd_gram": bwd_gram},
-        "roofline": {"kernel": fwd_kernel, "bound": "alu", "achieved": fwd_tflops,
-                     "peak": peak, "unit": "TFLOP/s", "frac": fwd_tflops / peak,
-                     "frac_with_tables": FWD_FLOP_PER_UPDATE * updates / ((fwd_table + fwd_sweep) * 1e-3) / 1e12 / peak,
+        "roofline": {"kernel": fwd_kernel, "bound": fwd_bound, "achieved": fwd_tflops,
+                     "peak": fwd_peak, "unit": "TFLOP/s", "frac": fwd_tflops / fwd_peak,
+                     "frac_with_tables": fwd_flops / ((fwd_table + fwd_sweep) * 1e-3) / 1e12 / fwd_peak,
                      "traffic": _traffic_from_profiles(f"{fwd_kernel.replace('_kernel', '')}_{name}")},
-        "roofline_bwd": {"kernel": bwd_kernel + (" (on C = Y G^T) + " + fwd_kernel + " (dX)" if gram and not identity
-                                                 else (" (on C = Y G^T)" if gram else "")),
-                         "bound": "alu", "achieved": bwd_tflops, "peak": peak, "unit": "TFLOP/s",
-                         "frac": bwd_tflops / peak,
+        "roofline_bwd": {"kernel": bwd_kernel + (" (on C = Y G^T)" if gram and bwd_bound == "alu" else ""),
+                         "bound": bwd_bound, "achieved": bwd_tflops, "peak": bwd_peak, "unit": "TFLOP/s",
+                         "frac": bwd_tflops / bwd_peak,
                          "traffic": _traffic_from_profiles(
                              f"{bwd_kernel.replace('_chain', '').replace('_kernel', '')}_{name}")},
     }
     if gram and bwd_gram > 0:
         gram_tflops = 2.0 * n * n * B / (bwd_gram * 1e-3) / 1e12
         result["roofline_gram"] = {"kernel": "gram_tile_kernel", "bound": "mfma", "achieved": gram_tflops,
-                                   "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                                   "frac": gram_tflops / PEAK_FP32_MFMA_TFLOPS,
+                                   "peak": PEAK_FP32_PRODUCT_TFLOPS, "unit": "TFLOP/s",
+                                   "frac": gram_tflops / PEAK_FP32_PRODUCT_TFLOPS,
                                    "traffic": _traffic_from_profiles(f"gram_tile_{name}")}
 
     if not args.no_cpu_baseline:

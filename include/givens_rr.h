@@ -49,9 +49,10 @@ extern "C" {
 #define GIVENS_ERR_STALE (-8)       /* prepared calls: the token's tables are gone      */
 
 /* Kernel families (givens_set_kernel). */
-#define GIVENS_KERNEL_AUTO 0     /* column kernels for n <= 128, register carousel where the  */
-                                 /* shape allows, else LDS strip                              */
-#define GIVENS_KERNEL_LDS 1      /* strip of the operand held in LDS; any even n that fits   */
+#define GIVENS_KERNEL_AUTO 0     /* column kernels for n <= 128, tiles where they are faster (below), register  */
+                                 /* carousel where the shape allows, else LDS strip                             */
+#define GIVENS_KERNEL_LDS 1      /* strip of the operand held in LDS; any even n that fits.  Chosen by AUTO for */
+                                 /* float64, n = 10 .. 1024: one wavefront per strip where the size allows it   */
 #define GIVENS_KERNEL_CAROUSEL 2 /* strip held in VGPRs in circle-method position order: float, */
                                  /* n from 132, a multiple of 4 up to 4096 or of 8 up to 8192,  */
                                  /* or n = 2 M L with M in {7, 5, 3} and L <= 1024 (standard    */
@@ -59,9 +60,12 @@ extern "C" {
 #define GIVENS_KERNEL_COLUMN 3   /* float, n <= 128: one lane per column, all rows in its VGPRs  */
                                  /* (n <= 32), or from n = 16 on one wavefront per strip         */
 
-#define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix */
-                                 /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it where it is */
-                                 /* the faster one, and givens_last_kernel then still names the family of the shape    */
+#define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix    */
+                                 /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it, with      */
+                                 /* GIVENS_FORM_AUTO and unless TWO_STAGE is chosen, for n from 400 without a carousel */
+                                 /* shape and from 900 with one of 3, 5 or 7 slots or more than eight wavefronts, and  */
+                                 /* in the backward call from B = 0.6 n to 0.9 n on for these, 0.9 n for the others    */
+                                 /* below 1e9 updates (n (n-1)/2 * B), where it is the faster one                      */
 
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */
@@ -80,8 +84,8 @@ extern "C" {
                                      /* are chained and add their sums into shared rows, in a fixed order too;   */
                                      /* should a workgroup's bounded wait for its predecessor ever run out, the  */
                                      /* call cannot report it, being asynchronous: dtheta is then all NaN)       */
-#define GIVENS_REDUCTION_GRAM 3      /* C = Y G^T by the library's float32 MFMA kernel, then the sweep on the    */
-                                     /* n x n operand C; dX by a forward-type sweep (float entry points)        */
+#define GIVENS_REDUCTION_GRAM 3      /* C = Y G^T on the matrix cores, then the sweep on the n x n operand C;   */
+                                     /* dX = U^T G by a dense product (float and complex64 entry points)        */
 
 /*
  * rr_schedule -- the round-robin sequence by the circle method (Section 3; the worked n = 6
@@ -181,7 +185,9 @@ int givens_backward_ex(int n, int m, int64_t B, const float *theta, const float 
  * both; givens_release drops everything.  A *_prepared call whose token is no longer the workspace's, whose
  * direction was not prepared or lost, or which asks (through givens_set_kernel) for another kernel family
  * than the tables were built for returns GIVENS_ERR_STALE and launches nothing: call the plain entry point
- * instead.  The token must be used on the stream it was prepared on.
+ * instead.  The token must be used on the stream it was prepared on.  The prepared calls always sweep: they give the
+ * bits of the plain calls except where those run as tiles, whose results agree with theirs to rounding and which are
+ * the faster ones there (givens_prepare_pays).
  *   directions : GIVENS_PREPARE_FORWARD, GIVENS_PREPARE_BACKWARD or both (or-ed).  GIVENS_PREPARE_BACKWARD_WIDE
  *     (implies _BACKWARD) lets givens_backward_prepared take the Gram form for B >= 2 n; without it it runs the
  *     two-stage sweep over all B columns whatever B is (and returns GIVENS_ERR_STALE if the Gram form is forced).
@@ -317,8 +323,11 @@ const char *givens_error_string(int code);
 int givens_set_kernel(int which);
 
 /* Which family the last successful forward/build/backward call on this thread used
- * (GIVENS_KERNEL_LDS, GIVENS_KERNEL_CAROUSEL or GIVENS_KERNEL_COLUMN; 0 before any call). */
+ * (GIVENS_KERNEL_LDS, GIVENS_KERNEL_CAROUSEL, GIVENS_KERNEL_COLUMN or GIVENS_KERNEL_TILES; 0 before any call). */
 int givens_last_kernel(void);
+/* 1 when that call ran its family over n columns only, to get U or U^T, and multiplied the batch with it as a dense
+ * product on the matrix cores (AUTO and every forced family, float: B >= 2 n and B >= 2048, complex64: B >= 4 n), else 0. */
+int givens_last_product(void);
 
 /*
  * The float carousel kernels have three arithmetically equivalent forms of the same Givens update
@@ -342,9 +351,10 @@ int givens_last_rotation_form(void);
  * (at most 256 rows on this chip: 8.6 GB at n = 4096, whatever B is) or per strip of the LDS family,
  * capped at 24 GiB per chunk, and gives bit-identical dtheta from run to run.  GRAM replaces the sweep
  * over B columns by the Gram matrix C = Y G^T (the sums of the sweep are those of the same sweep on the
- * operand C with upstream gradient I_n), contracted over B by the library's own float32 MFMA kernel in a
- * fixed order (reproducible as well), and computes dX = U^T G by a forward-type sweep.  AUTO means GRAM for
- * every float kernel family when B >= 2 n, TWO_STAGE otherwise; the f64 entry points always use TWO_STAGE.
+ * operand C with upstream gradient I_n), contracted over B on the matrix cores in float32 precision and in a
+ * fixed order (reproducible as well), and computes dX = U^T G by a product with what the sweep leaves of I_n.
+ * AUTO means GRAM for every float kernel family when B >= 2 n and wherever the call runs as tiles
+ * (GIVENS_KERNEL_TILES, also below 2 n), TWO_STAGE otherwise; the f64 entry points always use TWO_STAGE.
  * givens_last_reduction() reports what the last backward call on this thread did.
  */
 int givens_set_reduction(int which);

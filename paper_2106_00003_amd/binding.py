@@ -29,7 +29,7 @@ EXPORTS = [
     "givens_backward_prepared", "givens_prepare_pays",
     "givens_packed_bytes", "givens_pack", "givens_apply_packed", "givens_kept_bytes", "givens_keep", "givens_apply_kept",
     "givens_release", "givens_last_hip_error", "givens_error_string",
-    "givens_set_kernel", "givens_last_kernel", "givens_set_timing", "givens_last_timing",
+    "givens_set_kernel", "givens_last_kernel", "givens_last_product", "givens_set_timing", "givens_last_timing",
     "givens_set_rotation_form", "givens_last_rotation_form",
     "givens_set_reduction", "givens_last_reduction", "givens_last_chains",
     "givens_num_angles", "rr_schedule_restricted",
@@ -540,6 +540,11 @@ def set_kernel(which: int) -> int:
 
 def last_kernel() -> int:
     return lib().givens_last_kernel()
+
+
+def last_product() -> bool:
+    """Whether the last call on this thread applied U to its batch as a dense product."""
+    return bool(lib().givens_last_product())
 
 
 def set_rotation_form(which: int) -> int:

@@ -128,6 +128,7 @@ struct ThreadState {
     int last_hip_error = 0;
     int last_kernel = 0;
     int last_reduction = 0;
+    int last_product = 0;                // the last call multiplied its operand by U (or U^T) as a dense product
     int last_chains = 0;                 // chains of workgroups in the last two-stage carousel reverse sweep (0: none)
     const unsigned *last_flag = nullptr; // device flag of the last call when the form was chosen on the device
     float last_scaled_max = 0.f;         // that call's threshold for the scaled form
@@ -235,6 +236,7 @@ void timing_begin_call()
     }
     ts.spans.clear();
     ts.timing_valid = g_timing_on != 0;
+    ts.last_product = 0;
 }
 
 // RAII: records an event pair around the launches made while it is alive.
@@ -621,10 +623,6 @@ struct Families {
     bool carousel = false, column = false;  // neither: LDS strip family
     bool wave64 = false;                    // ... whose float64 sweeps run on one wavefront per strip where a size allows
 };
-int family_code(const Families &fam)
-{
-    return fam.carousel ? GIVENS_KERNEL_CAROUSEL : fam.column ? GIVENS_KERNEL_COLUMN : GIVENS_KERNEL_LDS;
-}
 template <typename T>
 int pick_forward_family(int n, long long B, int choice, Families *out)
 {
@@ -721,6 +719,7 @@ int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const
     const int k = cplx ? 2 * rows : rows;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    t_state.last_product = 1;
     Span span(1, stream);
     split_matrix(rows, k, st.matrix, st.pieces, stream, cplx);
     const long long chunk = X == Y ? st.copy_cols : B;   // a result that overwrites its operand: from copies
@@ -949,8 +948,9 @@ bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
     const bool slow = f.M % 2 || f.WAVES > 8;
     if (!backward) return slow && (f.M != 7 || n >= 1900);
     if (slow) return 10 * swept >= 6LL * n;
-    // (where the scaled and lifted rotation forms are worth their range check, calls keep them: what a call reports of its
-    // form and, below B = 2n, of its reduction is part of the interface)
+    // From 1e9 updates on such calls keep the sweep, though the tiles are the faster ones there (n = B = 2048 1933 against
+    // 2293 us, 4096 7644 / 9068): their scaled and lifted rotation forms and, below B = 2n, the two-stage reduction are
+    // what the interface lets a caller see and choose at these sizes, and the tests hold them to it.
     return sweep_updates(n, swept) < kFormsMinUpdates && 10 * swept >= 9LL * n;
 }
 // Whether the tiles are applied to I, to build U, and X multiplied with that.
@@ -1015,6 +1015,7 @@ int tiles_forward(Workspace *ws, int dev, const Problem &pb, long long B, const 
         Span span(0, stream);
         tiles_build(g, theta, pb.map, pb.m, b, !transpose, pb.rows, B, swept, stream);
     }
+    t_state.last_kernel = GIVENS_KERNEL_TILES;
     t_state.last_flag = nullptr;
     return run_tiles_apply(ws, dev, pb, g, b, B, X, Y, !transpose, stream, given);
 }
@@ -1044,6 +1045,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
         tiles_gradient(g, pb.rows, pb.m, pb.map, b, C, dtheta, stream);
         GIVENS_HIP(hipGetLastError());
     }
+    t_state.last_kernel = GIVENS_KERNEL_TILES;
     t_state.last_flag = nullptr;
     t_state.last_reduction = GIVENS_REDUCTION_GRAM;
     t_state.last_chains = 0;
@@ -1081,7 +1083,6 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
     bool tiles = false;
     if constexpr (std::is_same<T, float>::value) tiles = wants_tiles(opt, n, swept, false);
     if (!tiles && opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
-    if (tiles) t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
     const FormPolicy policy =
         form_policy(!tiles && fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept));
     if constexpr (std::is_same<T, float>::value)
@@ -1179,12 +1180,8 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
     if (opt.kernel != GIVENS_KERNEL_TILES)
         if (int rc = pick_backward_family<T>(n, B, opt.kernel, &fam)) return rc;
     const long long swept = wants_gram<T>(n, B, opt.reduction) ? rows : B;
-    if constexpr (std::is_same<T, float>::value) {
-        if (wants_tiles(opt, n, swept, true)) {
-            t_state.last_kernel = opt.kernel == GIVENS_KERNEL_TILES ? GIVENS_KERNEL_TILES : family_code(fam);
-            return tiles_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
-        }
-    }
+    if constexpr (std::is_same<T, float>::value)
+        if (wants_tiles(opt, n, swept, true)) return tiles_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
     if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
     invalidate_prepared(*ws, false, true);
     Coefs<T> coefs;
@@ -2081,6 +2078,7 @@ int givens_set_reduction(int which)
 }
 
 int givens_last_reduction(void) { return givens::t_state.last_reduction; }
+int givens_last_product(void) { return givens::t_state.last_product; }
 int givens_last_chains(void) { return givens::t_state.last_chains; }
 
 

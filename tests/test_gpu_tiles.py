@@ -108,15 +108,25 @@ def library_defaults():
     binding.set_rotation_form(binding.FORM_RANGE)
 
 
-# a size of every kind that the rule tells apart, on both sides of its batch
-@pytest.mark.parametrize("n,B", [(398, 500), (402, 1), (514, 400), (514, 500), (1002, 300), (1002, 700), (1006, 40),
-                                 (1024, 900), (1024, 1000), (1024, 2100), (1280, 1280), (1022, 700), (2050, 64)])
-def test_sizes_around_the_rule(library_defaults, n, B):
+# a size of every kind that the rule tells apart, on both sides of its batch: whether the forward and the backward call run
+# as tiles, and whether each multiplies
+@pytest.mark.parametrize("n,B,forward,backward,product", [
+    (398, 500, False, False, False), (402, 1, False, False, False), (514, 400, True, False, False),
+    (514, 500, True, True, False), (514, 2048, True, True, True), (706, 20, True, True, False),
+    (1002, 300, True, False, False), (1002, 700, True, True, False), (1006, 40, True, True, False),
+    (1024, 900, False, False, False), (1024, 1000, False, True, False), (1024, 2100, False, True, True),
+    (1280, 1280, False, False, False), (1022, 700, False, True, False), (2050, 64, True, False, False),
+    (898, 898, True, True, False), (896, 896, False, False, False), (2048, 1950, False, False, False)])
+def test_sizes_around_the_rule(library_defaults, n, B, forward, backward, product):
     data = inputs.make_custom(n, B, seed=3500 + n)
     th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
     y = binding.givens_forward(th, x)
+    assert (binding.last_kernel() == binding.KERNEL_TILES) == forward and binding.last_product() == product
     dx, dth = binding.givens_backward(th, y, g)
+    assert (binding.last_kernel() == binding.KERNEL_TILES) == backward and binding.last_product() == product
+    assert binding.last_reduction() == (binding.REDUCTION_GRAM if backward or B >= 2 * n else binding.REDUCTION_TWO_STAGE)
     want_y = binding.givens_forward(th.double(), x.double())
+    assert binding.last_kernel() != binding.KERNEL_TILES and not binding.last_product()
     want_dx, want_dth = binding.givens_backward(th.double(), want_y, g.double())
     assert far(y, want_y) <= 1e-5 and far(dx, want_dx) <= 1e-4 and far(dth, want_dth) <= 1e-4
 
