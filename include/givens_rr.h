@@ -354,7 +354,8 @@ int givens_last_rotation_form(void);
  * operand C with upstream gradient I_n), contracted over B on the matrix cores in float32 precision and in a
  * fixed order (reproducible as well), and computes dX = U^T G by a product with what the sweep leaves of I_n.
  * AUTO means GRAM for every float kernel family when B >= 2 n and wherever the call runs as tiles
- * (GIVENS_KERNEL_TILES, also below 2 n), TWO_STAGE otherwise; the f64 entry points always use TWO_STAGE.
+ * (GIVENS_KERNEL_TILES, also below 2 n), TWO_STAGE otherwise; for givens_unitary_backward GRAM (C = Y G^H) when
+ * B >= 4 n and B >= 1024, TWO_STAGE otherwise; the f64 entry points always use TWO_STAGE.
  * givens_last_reduction() reports what the last backward call on this thread did.
  */
 int givens_set_reduction(int which);

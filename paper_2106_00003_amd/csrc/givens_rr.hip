@@ -1748,8 +1748,9 @@ int unitary_backward_impl(int n, long long B, const T *theta, const T *phi, cons
     Workspace *ws = nullptr;
     if (int rc = workspace_for(dev, stream, &ws)) return rc;
     if constexpr (std::is_same<T, float>::value) {
-        const bool chosen = g_reduction_choice == GIVENS_REDUCTION_AUTO;
-        if (chosen && unitary_wants_product<T>(n, B, kUnitaryMinBackward)) {
+        const bool gram = g_reduction_choice == GIVENS_REDUCTION_GRAM ||
+                          (g_reduction_choice == GIVENS_REDUCTION_AUTO && unitary_wants_product<T>(n, B, kUnitaryMinBackward));
+        if (gram) {
             int cus = 0;
             GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             const GramPlan plan = gram_plan(n, 2 * B, cus, true);

@@ -136,6 +136,28 @@ def test_wide_unitary_batches(n, B):
     assert torch.equal(buf, dx)
 
 
+# the reduction a caller chooses, on both sides of the batch from which AUTO contracts, in both families; float64 has the sweep
+@pytest.mark.parametrize("n,B", [(6, 3), (30, 200), (64, 1024), (128, 40), (144, 1024)])
+def test_unitary_reductions_that_are_chosen(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(1750 + n)
+    th, ph = ((torch.rand(n * (n - 1) // 2, device="cuda", generator=gen) * 2 - 1) * np.pi for _ in range(2))
+    y, g = (torch.randn(n, B, dtype=torch.complex64, device="cuda", generator=gen) for _ in range(2))
+    want = binding.givens_unitary_backward(th.double(), ph.double(), y.to(torch.complex128), g.to(torch.complex128))
+    wide = B >= 4 * n and B >= 1024
+    gram, sweep = binding.REDUCTION_GRAM, binding.REDUCTION_TWO_STAGE
+    try:
+        for chosen, runs in ((binding.REDUCTION_AUTO, gram if wide else sweep), (gram, gram), (sweep, sweep)):
+            binding.set_reduction(chosen)
+            got = binding.givens_unitary_backward(th, ph, y, g)
+            assert binding.last_reduction() == runs and binding.last_product() == (runs == gram)
+            for a, b in zip(got, want):
+                assert float((a.to(b.dtype) - b).norm() / b.norm()) <= TOL_G
+            binding.givens_unitary_backward(th.double(), ph.double(), y.to(torch.complex128), g.to(torch.complex128))
+            assert binding.last_reduction() == sweep
+    finally:
+        binding.set_reduction(binding.REDUCTION_AUTO)
+
+
 # the kernel for few columns: one column, one past its 32, contractions that do not fill its eight parts, the last size
 # before the tiled kernels and the first after it
 @pytest.mark.parametrize("n,B", [(1, 1), (2, 33), (31, 5), (33, 64), (130, 31), (257, 1), (514, 100), (1002, 64),
