@@ -128,6 +128,25 @@ def givens_matrix(theta: torch.Tensor, n: int, m: int | None = None) -> torch.Te
     return _GivensMatrix.apply(theta, n, m)
 
 
+class _KeptMatrix:
+    """U of the present angles laid out for evaluation, for use on any stream: made on one, which others wait for."""
+
+    def __init__(self, theta, th, n, m, stream):
+        # holding theta holds its memory: no other angles can come to lie at its address
+        self.theta, self.version, self.stream = theta, theta._version, stream
+        self.matrix = binding.Kept(th, givens_matrix(th, n, m), m)
+        self.ready = stream.record_event()
+
+    def of(self, theta) -> bool:
+        return theta._version == self.version and theta.data_ptr() == self.theta.data_ptr()
+
+    def apply(self, th, x, stream):
+        if stream != self.stream:
+            stream.wait_event(self.ready)
+            self.matrix.block.record_stream(stream)
+        return binding.givens_apply_kept(self.matrix, th, x, stream=stream)
+
+
 class OrthogonalLinear(torch.nn.Module):
     """Orthogonal layer y = U(theta) x on column batches (n, B), with the free angles as its parameters in
     the round-robin order E (Section 3): n(n-1)/2 of them, or m n - m(m+1)/2 with the parametrisation
@@ -141,7 +160,7 @@ class OrthogonalLinear(torch.nn.Module):
         count = binding.num_angles(n, m)
         self.theta = torch.nn.Parameter(init_std * torch.randn(count, device=device, dtype=dtype))
 
-        self._eval_matrix = None  # (version of theta, stream), theta, U laid out for evaluation
+        self._eval_matrix = None  # U laid out for evaluation, a _KeptMatrix
         self._captured = []       # laid-out matrices that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
@@ -152,25 +171,23 @@ class OrthogonalLinear(torch.nn.Module):
             return givens_apply(self.theta, X, self.m)   # refused there
         # evaluation: U of the current theta is built and laid out once, here and not in the workspace of the stream, which
         # all layers share, and multiplied with until theta changes.  The version counter tells most changes; writes that it
-        # does not count (through .data, by a replayed graph) are seen on the device, which compares the angles.  (Holding
-        # theta holds its memory: no other angles can come to lie at its address.)
+        # does not count (through .data, by a replayed graph) are seen on the device, which compares the angles.
         theta = self.theta.detach()
         th = theta.contiguous()
-        key = (theta._version, torch.cuda.current_stream().cuda_stream)
+        stream = torch.cuda.current_stream()
         capturing = torch.cuda.is_current_stream_capturing()
         for _ in range(2):
             kept = self._eval_matrix
-            same = kept is not None and kept[0] == key and kept[1].data_ptr() == theta.data_ptr()
+            same = kept is not None and kept.of(theta)
             if capturing:
-                if not same:                     # what a graph records is there when it is replayed
+                if not same:                       # what a graph records is there when it is replayed
                     return binding.givens_apply_packed(binding.givens_pack(givens_matrix(theta, self.n, self.m)), x)
-                self._captured.append(kept[2])   # and what it reads has to stay
-                return binding.givens_apply_packed(kept[2].packed, x)
+                self._captured.append(kept)        # and what it reads has to stay
+                return binding.givens_apply_packed(kept.matrix.packed, x)
             if not same:
-                kept = (key, theta, binding.Kept(th, givens_matrix(th, self.n, self.m), self.m))
-                self._eval_matrix = kept
+                self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
             try:
-                return binding.givens_apply_kept(kept[2], th, x)
+                return kept.apply(th, x, stream)
             except binding.GivensError as err:
                 if err.code != binding.ERR_STALE:
                     raise

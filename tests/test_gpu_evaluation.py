@@ -104,3 +104,44 @@ def test_angles_updated_by_a_replayed_graph():
             assert wrong(net, x, net(x)) <= TOL_Y
             graph.replay()
             assert wrong(net, x, net(x)) <= TOL_Y
+
+
+@pytest.fixture
+def built(monkeypatch):
+    """How often a layer has built and laid out its matrix."""
+    count = [0]
+    kept = binding.Kept
+
+    def counted(*args, **kwargs):
+        count[0] += 1
+        return kept(*args, **kwargs)
+
+    monkeypatch.setattr(binding, "Kept", counted)
+    return count
+
+
+def test_streams_share_the_matrix(built):
+    net = _layer().OrthogonalLinear(514)
+    x = torch.randn(514, 64, device="cuda")
+    streams = [torch.cuda.current_stream()] + [torch.cuda.Stream() for _ in range(3)]
+    with torch.no_grad():
+        for change in range(3):
+            net.theta.add_(0.01)
+            torch.cuda.synchronize()
+            outs = []
+            for _ in range(4):
+                for stream in streams:
+                    with torch.cuda.stream(stream):
+                        outs.append(net(x))
+            torch.cuda.synchronize()
+            assert all(wrong(net, x, y) <= TOL_Y for y in outs)
+            assert built[0] == change + 1
+        # changed unseen: whichever stream comes first
+        net.theta.data.mul_(0.5)
+        torch.cuda.synchronize()
+        outs = []
+        for stream in streams[::-1]:
+            with torch.cuda.stream(stream):
+                outs += [net(x), net(x)]
+        torch.cuda.synchronize()
+        assert all(wrong(net, x, y) <= TOL_Y for y in outs)
