@@ -161,6 +161,7 @@ class OrthogonalLinear(torch.nn.Module):
         self.theta = torch.nn.Parameter(init_std * torch.randn(count, device=device, dtype=dtype))
 
         self._eval_matrix = None  # U laid out for evaluation, a _KeptMatrix
+        self._eval_plain = None   # version of theta, theta, plain batches evaluated with it
         self._captured = []       # laid-out matrices that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
@@ -175,27 +176,33 @@ class OrthogonalLinear(torch.nn.Module):
         theta = self.theta.detach()
         th = theta.contiguous()
         stream = torch.cuda.current_stream()
-        capturing = torch.cuda.is_current_stream_capturing()
-        for _ in range(2):
-            kept = self._eval_matrix
-            same = kept is not None and kept.of(theta)
-            if capturing:
-                if not same:                       # what a graph records is there when it is replayed
-                    return binding.givens_apply_packed(binding.givens_pack(givens_matrix(theta, self.n, self.m)), x)
-                self._captured.append(kept)        # and what it reads has to stay
-                return binding.givens_apply_packed(kept.matrix.packed, x)
+        kept = self._eval_matrix
+        same = kept is not None and kept.of(theta)
+        if torch.cuda.is_current_stream_capturing():
             if not same:
-                self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
+                return givens_apply(self.theta, X, self.m)
+            self._captured.append(kept)            # what a graph reads has to stay
+            return binding.givens_apply_packed(kept.matrix.packed, x)
+        if same:
             try:
                 return kept.apply(th, x, stream)
             except binding.GivensError as err:
                 if err.code != binding.ERR_STALE:
                     raise
-                self._eval_matrix = None
-        return givens_apply(self.theta, X, self.m)
+                self._eval_matrix = self._eval_plain = None
+        # The first batches of a theta are plain calls.  Building and laying out U costs as much as 1.5 of them with few
+        # columns up to n = 2048, two at 4096 and four at 8192 (measured, B = 64: n = 1024 123 and 187 us, 2048 508 / 709,
+        # 4096 1212 / 2430, 8192 5.5 / 22 ms), so that many have come before it pays.
+        plain = self._eval_plain
+        batches = plain[2] if plain is not None and plain[0] == theta._version and plain[1].data_ptr() == theta.data_ptr() else 0
+        if batches < max(1, self.n // 2048):
+            self._eval_plain = (theta._version, theta, batches + 1)
+            return givens_apply(self.theta, X, self.m)
+        self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
+        return kept.apply(th, x, stream)
 
     def __getstate__(self):
-        return {**self.__dict__, "_eval_matrix": None, "_captured": []}
+        return {**self.__dict__, "_eval_matrix": None, "_eval_plain": None, "_captured": []}
 
     def matrix(self) -> torch.Tensor:
         return givens_matrix(self.theta, self.n, self.m)

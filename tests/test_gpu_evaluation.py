@@ -145,3 +145,51 @@ def test_streams_share_the_matrix(built):
                 outs += [net(x), net(x)]
         torch.cuda.synchronize()
         assert all(wrong(net, x, y) <= TOL_Y for y in outs)
+
+
+@pytest.mark.parametrize("n,plain", [(64, 1), (1006, 1), (2048, 1), (4096, 2)])
+def test_first_batches_are_plain_calls(built, n, plain):
+    net = _layer().OrthogonalLinear(n)
+    x = torch.randn(n, 8, device="cuda")
+    with torch.no_grad():
+        for _ in range(3):                                  # one batch per change of theta: never a matrix
+            net.theta.mul_(0.9)
+            assert wrong(net, x, net(x)) <= TOL_Y
+        assert built[0] == 0
+        for _ in range(plain - 1):
+            net(x)
+        assert built[0] == 0
+        for _ in range(3):
+            assert wrong(net, x, net(x)) <= TOL_Y
+        assert built[0] == 1
+        net.theta.data.mul_(0.9)                            # unseen: right at once, and a plain call once it is known
+        assert wrong(net, x, net(x)) <= TOL_Y
+        torch.cuda.synchronize()
+        for _ in range(plain):
+            assert wrong(net, x, net(x)) <= TOL_Y
+        assert built[0] == 1
+        assert wrong(net, x, net(x)) <= TOL_Y
+        assert built[0] == 2
+
+
+def test_a_recorded_first_batch_follows_the_angles(built):
+    """A graph recorded before the layer has its matrix holds the plain call, not one that builds U."""
+    net = _layer().OrthogonalLinear(256)
+    x = torch.randn(256, 64, device="cuda")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.no_grad():
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            net(x)                                          # the workspace of the stream
+            net.theta.mul_(0.9)
+            side.synchronize()
+            with torch.cuda.graph(graph, stream=side):
+                y = net(x)
+        assert built[0] == 0
+        for _ in range(3):
+            net.theta.mul_(0.9)
+            y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert wrong(net, x, y) <= TOL_Y
