@@ -235,6 +235,7 @@ int64_t givens_kept_bytes(int n, int m);
 int64_t givens_keep(int n, int m, const float *theta, const float *U, void *kept, void *stream);
 int givens_apply_kept(int64_t id, int n, int m, int64_t B, const float *theta, void *kept, const float *X, float *Y,
                       void *stream);
+int givens_kept_changed(int64_t id); /* 1 once such a call was seen (or for no id of givens_keep's), else 0 */
 
 /* float64 variants: same semantics, all arrays double. */
 int givens_forward_f64(int n, int64_t B, const double *theta, const double *X, double *Y, void *stream);

@@ -28,6 +28,7 @@ EXPORTS = [
     "givens_prepare", "givens_prepare_restricted", "givens_prepare_ex", "givens_forward_prepared", "givens_build_prepared",
     "givens_backward_prepared", "givens_prepare_pays",
     "givens_packed_bytes", "givens_pack", "givens_apply_packed", "givens_kept_bytes", "givens_keep", "givens_apply_kept",
+    "givens_kept_changed",
     "givens_release", "givens_last_hip_error", "givens_error_string",
     "givens_set_kernel", "givens_last_kernel", "givens_last_product", "givens_set_timing", "givens_last_timing",
     "givens_set_rotation_form", "givens_last_rotation_form",
@@ -85,6 +86,7 @@ def lib():
     L.givens_kept_bytes.argtypes = [i32, i32]
     L.givens_keep.argtypes = [i32, i32, vp, vp, vp, vp]
     L.givens_apply_kept.argtypes = [i64, i32, i32, i64, vp, vp, vp, vp, vp]
+    L.givens_kept_changed.argtypes = [i64]
     L.givens_num_angles.argtypes = [i32, i32]
     L.rr_schedule_restricted.argtypes = [i32, i32, vp]
     for name in ("givens_forward_restricted", "givens_forward_restricted_f64"):
@@ -369,6 +371,10 @@ class Kept:
                                     _dev(self.block, "block"), _stream_ptr(stream))
         if self.id < 0:
             raise GivensError(self.id, "givens_keep")
+
+    def changed(self) -> bool:
+        """Whether a call is known to have been given other angles."""
+        return bool(lib().givens_kept_changed(self.id))
 
 
 def givens_apply_kept(kept, theta, X, Y=None, stream=None):

@@ -1387,6 +1387,8 @@ constexpr int kNoteSlots = 256;
 volatile int64_t *g_notes = nullptr;
 int64_t g_next_kept = 0;
 
+bool kept_changed(int64_t id) { return id < 1 || id > g_next_kept || g_notes[id % kNoteSlots] == id; }
+
 KeptAngles kept_angles_of(const Problem &pb, const float *theta, unsigned char *kept, int64_t id)
 {
     const KeptLayout k = kept_layout(pb.rows, pb.m);
@@ -1432,7 +1434,7 @@ int apply_kept_impl(int64_t id, int rows, int m, long long B, const float *theta
     if (X == Y) return GIVENS_ERR_ALIAS;
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
     std::lock_guard<std::mutex> lock(g_mutex);
-    if (id < 1 || id > g_next_kept || g_notes[id % kNoteSlots] == id) return GIVENS_ERR_STALE;
+    if (kept_changed(id)) return GIVENS_ERR_STALE;
     int dev = 0, cus = 0;
     if (int rc = current_device(&dev)) return rc;
     Workspace *ws = nullptr;
@@ -1939,6 +1941,12 @@ int givens_apply_kept(int64_t id, int n, int m, int64_t B, const float *theta, v
                       void *stream)
 {
     return givens::apply_kept_impl(id, n, m, B, theta, kept, X, Y, stream);
+}
+
+int givens_kept_changed(int64_t id)
+{
+    std::lock_guard<std::mutex> lock(givens::g_mutex);
+    return givens::kept_changed(id) ? 1 : 0;
 }
 
 int64_t givens_num_angles(int n, int m)

@@ -162,7 +162,7 @@ class OrthogonalLinear(torch.nn.Module):
 
         self._eval_matrix = None  # U laid out for evaluation, a _KeptMatrix
         self._eval_plain = None   # version of theta, theta, plain batches evaluated with it
-        self._captured = []       # laid-out matrices that recorded graphs read
+        self._captured = []       # those that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
         if torch.is_grad_enabled() or self.theta.dtype != torch.float32:
@@ -179,10 +179,11 @@ class OrthogonalLinear(torch.nn.Module):
         kept = self._eval_matrix
         same = kept is not None and kept.of(theta)
         if torch.cuda.is_current_stream_capturing():
-            if not same:
+            if not same or kept.matrix.changed():
                 return givens_apply(self.theta, X, self.m)
-            self._captured.append(kept)            # what a graph reads has to stay
-            return binding.givens_apply_packed(kept.matrix.packed, x)
+            if not any(kept is k for k in self._captured):   # what a graph reads has to stay
+                self._captured.append(kept)
+            return binding.givens_apply_packed(kept.matrix.packed, x, stream=stream)
         if same:
             try:
                 return kept.apply(th, x, stream)
@@ -203,6 +204,11 @@ class OrthogonalLinear(torch.nn.Module):
 
     def __getstate__(self):
         return {**self.__dict__, "_eval_matrix": None, "_eval_plain": None, "_captured": []}
+
+    def forget_recorded(self) -> None:
+        """Gives up the matrices that graphs recorded in evaluation read (one for every theta that was recorded).  Only
+        when none of these graphs is going to be replayed; without it they stay as long as the layer."""
+        self._captured = []
 
     def matrix(self) -> torch.Tensor:
         return givens_matrix(self.theta, self.n, self.m)

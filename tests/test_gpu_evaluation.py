@@ -193,3 +193,47 @@ def test_a_recorded_first_batch_follows_the_angles(built):
             graph.replay()
             torch.cuda.synchronize()
             assert wrong(net, x, y) <= TOL_Y
+
+
+def test_matrices_of_recorded_graphs():
+    """One is held for every theta that was recorded, however many calls a graph has; angles known to have changed unseen
+    are not recorded as they were."""
+    net = _layer().OrthogonalLinear(256)
+    x = torch.randn(256, 64, device="cuda")
+    side = torch.cuda.Stream()
+    with torch.no_grad():
+        for change in range(3):
+            net.theta.mul_(0.9)
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(side):
+                for _ in range(2):
+                    net(x)
+                side.synchronize()
+                with torch.cuda.graph(graph, stream=side):
+                    for _ in range(5):
+                        y = net(x)
+            assert len(net._captured) == change + 1
+        for _ in range(3):
+            y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert wrong(net, x, y) <= TOL_Y
+        del graph, y
+        torch.cuda.synchronize()
+        net.forget_recorded()
+        assert net._captured == []
+        net.theta.data.mul_(0.5)
+        with torch.cuda.stream(side):
+            net(x)
+            side.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                y = net(x)
+        for _ in range(3):
+            y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert wrong(net, x, y) <= TOL_Y
