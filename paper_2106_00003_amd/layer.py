@@ -160,6 +160,9 @@ class OrthogonalLinear(torch.nn.Module):
         count = binding.num_angles(n, m)
         self.theta = torch.nn.Parameter(init_std * torch.randn(count, device=device, dtype=dtype))
 
+        self._start_evaluation()
+
+    def _start_evaluation(self) -> None:
         self._eval_matrix = None  # U laid out for evaluation, a _KeptMatrix
         self._eval_plain = None   # version of theta, theta, plain batches evaluated with it
         self._captured = []       # those that recorded graphs read
@@ -202,8 +205,13 @@ class OrthogonalLinear(torch.nn.Module):
         self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
         return kept.apply(th, x, stream)
 
+    # what evaluation keeps stays with the object: a copy starts anew, from whichever version of this class it was pickled
     def __getstate__(self):
-        return {**self.__dict__, "_eval_matrix": None, "_eval_plain": None, "_captured": []}
+        return {k: v for k, v in self.__dict__.items() if k not in ("_eval_matrix", "_eval_plain", "_captured")}
+
+    def __setstate__(self, state):
+        super().__setstate__({k: v for k, v in state.items() if k != "_eval_tables"})
+        self._start_evaluation()
 
     def forget_recorded(self) -> None:
         """Gives up the matrices that graphs recorded in evaluation read (one for every theta that was recorded).  Only

@@ -237,3 +237,25 @@ def test_matrices_of_recorded_graphs():
             graph.replay()
             torch.cuda.synchronize()
             assert wrong(net, x, y) <= TOL_Y
+
+
+def test_copies_and_pickles():
+    L = _layer()
+    net = L.OrthogonalLinear(130, 20)
+    x = torch.randn(130, 40, device="cuda")
+    with torch.no_grad():
+        for _ in range(3):
+            want = net(x)
+        old = {**net.__dict__, "_eval_tables": (7, (0, net.theta.data_ptr(), 0))}   # as pickled by earlier versions
+        for name in ("_eval_matrix", "_eval_plain", "_captured"):
+            del old[name]
+        from_old = L.OrthogonalLinear.__new__(L.OrthogonalLinear)
+        from_old.__setstate__(pickle.loads(pickle.dumps(old)))
+        for other in (copy.deepcopy(net), pickle.loads(pickle.dumps(net)), from_old):
+            assert other._eval_matrix is None and not hasattr(other, "_eval_tables")
+            for _ in range(3):
+                y = other(x)
+                assert wrong(other, x, y) <= TOL_Y
+            assert torch.equal(y, want)
+            other.theta.mul_(0.5)
+            assert torch.equal(net(x), want)
