@@ -213,7 +213,8 @@ int givens_prepare_pays(int n, int m, int64_t B);
 
 /*
  * One matrix, many batches (float).  givens_pack lays an n x n matrix (say U of givens_build) out for the matrix cores in
- * memory of the caller's: givens_packed_bytes(n) bytes on the device, 16-byte aligned, about 6 n^2.  givens_apply_packed
+ * memory of the caller's: givens_packed_bytes(n) bytes on the device (another number for every n), 16-byte aligned (else
+ * GIVENS_ERR_UNSUPPORTED), about 6 n^2.  givens_apply_packed
  * then computes Y = U X, n x B, in float32 precision: for a theta that stays while the operands change.  Neither call uses
  * the library's workspaces; Y must not be X (GIVENS_ERR_ALIAS).  (Elements of the matrix below 2^-110 keep fewer than 24
  * bits, which an orthogonal matrix does not notice; X may be of any size.)

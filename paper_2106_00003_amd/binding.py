@@ -332,17 +332,22 @@ def givens_pack(U, packed=None, stream=None):
     if packed.numel() < size or packed.data_ptr() % 16:
         raise ValueError("packed must have givens_packed_bytes(n) bytes, 16-byte aligned")
     _check(lib().givens_pack(n, _dev(U, "U"), _dev(packed, "packed", torch.uint8), _stream_ptr(stream)), "givens_pack")
+    packed._givens_rows = n
     return packed
 
 
 def givens_apply_packed(packed, X, Y=None, stream=None):
-    """Y = U X for the matrix U that `packed` was made from (givens_pack)."""
+    """Y = U X for the matrix U that `packed` was made from (givens_pack).  A tensor that givens_pack was not given or did
+    not return (a view, a copy) tells the matrix's size by its own, which no two share."""
     import torch
     n, B = X.shape
     if X.dtype != torch.float32:
         raise TypeError("givens_apply_packed takes float32 operands")
-    if packed.numel() < lib().givens_packed_bytes(n):
-        raise ValueError("packed is too small for X")
+    rows = getattr(packed, "_givens_rows", None)
+    if (rows != n) if rows is not None else (packed.numel() != lib().givens_packed_bytes(n)):
+        raise ValueError("packed holds a matrix of another size than X's rows")
+    if packed.data_ptr() % 16:
+        raise ValueError("packed must be 16-byte aligned")
     if Y is None:
         Y = torch.empty_like(X)
     if Y.shape != X.shape:

@@ -1343,10 +1343,15 @@ int backward_prepared_impl(int64_t token, long long B, const float *Y, const flo
 }
 
 // ---- a matrix laid out once, in the caller's memory, and applied to many batches
+// bytes: the pieces, whose rows are padded to whole fragments, and a trailer that is never read, so that no two n have the
+// same size
+int64_t packed_bytes(int n) { return (int64_t)product_pieces(n, n) * sizeof(u32x4) + 16 * (n % kProductStep); }
+bool misaligned(const void *p) { return reinterpret_cast<uintptr_t>(p) % 16 != 0; }
 int pack_impl(int n, const float *U, void *packed, void *stream_v)
 {
     if (n < 1) return GIVENS_ERR_BAD_N;
     if (!U || !packed) return GIVENS_ERR_NULL;
+    if (misaligned(packed)) return GIVENS_ERR_UNSUPPORTED;
     split_matrix(n, n, U, static_cast<u32x4 *>(packed), reinterpret_cast<hipStream_t>(stream_v));
     GIVENS_HIP(hipGetLastError());
     return GIVENS_OK;
@@ -1356,6 +1361,7 @@ int apply_packed_impl(int n, long long B, const void *packed, const float *X, fl
     if (n < 1) return GIVENS_ERR_BAD_N;
     if (B < 1) return GIVENS_ERR_BAD_B;
     if (!packed || !X || !Y) return GIVENS_ERR_NULL;
+    if (misaligned(packed)) return GIVENS_ERR_UNSUPPORTED;
     if (X == Y) return GIVENS_ERR_ALIAS;
     int dev = 0, cus = 0;
     if (int rc = current_device(&dev)) return rc;
@@ -1375,7 +1381,7 @@ KeptLayout kept_layout(int rows, int m)
 {
     const int n = rows + (rows & 1);
     KeptLayout k;
-    k.table = round_up_256((size_t)product_pieces(rows, rows) * sizeof(u32x4));
+    k.table = round_up_256((size_t)packed_bytes(rows));
     k.copy = k.table + round_up_256((size_t)(n - 1) * (n / 2) * sizeof(float2));
     k.changed = k.copy + round_up_256((size_t)count_free_angles(rows, m) * sizeof(float));
     k.bytes = k.changed + 256;
@@ -1404,6 +1410,7 @@ int64_t keep_impl(int rows, int m, const float *theta, const float *U, void *kep
 {
     if (int rc = check_restricted(rows, m)) return rc;
     if (!theta || !U || !kept) return GIVENS_ERR_NULL;
+    if (misaligned(kept)) return GIVENS_ERR_UNSUPPORTED;
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
     std::lock_guard<std::mutex> lock(g_mutex);
     int dev = 0;
@@ -1431,6 +1438,7 @@ int apply_kept_impl(int64_t id, int rows, int m, long long B, const float *theta
     if (int rc = check_restricted(rows, m)) return rc;
     if (B < 1) return GIVENS_ERR_BAD_B;
     if (!theta || !kept || !X || !Y) return GIVENS_ERR_NULL;
+    if (misaligned(kept)) return GIVENS_ERR_UNSUPPORTED;
     if (X == Y) return GIVENS_ERR_ALIAS;
     hipStream_t stream = reinterpret_cast<hipStream_t>(stream_v);
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -1914,7 +1922,7 @@ int givens_prepare_pays(int n, int m, int64_t B)
 int64_t givens_packed_bytes(int n)
 {
     if (n < 1 || n > givens::kMaxRows) return GIVENS_ERR_BAD_N;
-    return (int64_t)(givens::product_pieces(n, n) * sizeof(givens::u32x4));
+    return givens::packed_bytes(n);
 }
 int givens_pack(int n, const float *U, void *packed, void *stream)
 {

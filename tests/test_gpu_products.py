@@ -174,6 +174,25 @@ def test_packed_matrix_applied_to_few_columns(n, B):
         binding.givens_apply_packed(packed, x, Y=x)
 
 
+def test_packed_matrices_of_another_size_are_refused():
+    x = torch.randn(1000, 40, device="cuda")
+    u = torch.randn(1002, 1002, device="cuda")
+    packed = binding.givens_pack(u)
+    for matrix in (packed, packed.clone(), packed[:binding.lib().givens_packed_bytes(1000)].clone()[:-16]):
+        with pytest.raises(ValueError):
+            binding.givens_apply_packed(matrix, x)
+    # a longer buffer, and views and copies of the right size, do
+    longer = torch.empty(packed.numel() + 4096, dtype=torch.uint8, device="cuda")
+    same = binding.givens_pack(u, packed=longer)
+    y = torch.randn(1002, 40, device="cuda")
+    want = binding.givens_apply_packed(packed, y)
+    for matrix in (same, longer, longer[:packed.numel()], packed.clone()):
+        assert torch.equal(binding.givens_apply_packed(matrix, y), want)
+    with pytest.raises(ValueError):
+        binding.givens_apply_packed(longer[8: 8 + packed.numel()], y)
+    assert len({binding.lib().givens_packed_bytes(n) for n in range(1, 1200)}) == 1199
+
+
 def test_layers_in_evaluation_keep_their_own_matrix():
     from paper_2106_00003_amd import layer
     nets = [layer.OrthogonalLinear(n, m) for n, m in ((130, None), (130, None), (129, 20))]

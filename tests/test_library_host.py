@@ -110,3 +110,17 @@ def test_restricted_argument_errors():
     assert L.givens_forward_restricted(9, 4, 4, None, None, None, None) == -3
     assert L.givens_backward_restricted(9, 4, 4, None, None, None, None, None, None) == -3
     assert b"m must" in L.givens_error_string(-7)
+
+
+def test_packed_matrices_must_be_aligned():
+    L = binding.lib()
+    memory = ctypes.create_string_buffer(64)
+    at = ctypes.addressof(memory) // 16 * 16 + 16
+    p, odd = ctypes.c_void_p(at), ctypes.c_void_p(at + 4)
+    assert L.givens_pack(8, p, odd, None) == -5
+    assert L.givens_apply_packed(8, 1, odd, p, ctypes.c_void_p(at + 16), None) == -5
+    assert L.givens_keep(8, 7, p, p, odd, None) == -5
+    assert L.givens_apply_kept(1, 8, 7, 1, p, odd, p, ctypes.c_void_p(at + 16), None) == -5
+    assert L.givens_kept_changed(0) == 1
+    assert L.givens_apply_kept(10 ** 9, 8, 7, 1, p, p, p, ctypes.c_void_p(at + 16), None) == -8
+    assert L.givens_kept_bytes(1, 1) == -1 and L.givens_kept_bytes(8, 8) == -7 and L.givens_kept_bytes(40000, 5) == -5
