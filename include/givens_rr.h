@@ -69,7 +69,8 @@ extern "C" {
 
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */
-                               /* coefficient work (n (n-1)/2 * B >= 1e9 updates; always in givens_prepare),    */
+                               /* coefficient work (n (n-1)/2 * B >= 1e9 updates, B the columns swept: n of a    */
+                               /* batch that is multiplied with U; always in givens_prepare), and                */
                                /* GIVENS_FORM_STANDARD below that                                               */
 #define GIVENS_FORM_STANDARD 1 /* r_i = c U_i - s U_j, r_j = s U_i + c U_j exactly as in Algorithm 1         */
 #define GIVENS_FORM_SCALED 2   /* same rotations on rows kept divided by their accumulated cosines (2 FMAs)  */

@@ -128,13 +128,46 @@ def givens_matrix(theta: torch.Tensor, n: int, m: int | None = None) -> torch.Te
     return _GivensMatrix.apply(theta, n, m)
 
 
+# Evaluation.  Building and laying out U costs as much as 1.5 plain calls with few columns up to n = 2048, two at 4096 and
+# four at 8192 (B = 64: n = 1024 116 and 190 us, 2048 490 / 710, 4096 1190 / 2430, 8192 4.8 / 22 ms; below 512 host work
+# decides, and a batch gains little by it).  So a layer whose last theta saw fewer batches than pay for a matrix (one batch
+# per training step) evaluates the next one by plain calls.  The two differ in rounding, and batches of one theta should
+# not differ with their number: a theta that is begun one way stays with it, up to a number of batches (times n / 2048)
+# that only a layer in service again sees.  Up to n = 128 a plain call is as fast as a product with a kept matrix
+# (n = 64, B = 64: 18 and 20 us).
+_MATRIX_MIN_N = 129
+_PLAIN_BATCHES = 32
+
+
+def _worth_a_matrix(n: int) -> int:
+    return 8 if n < 512 else max(2, n // 2048 + 1)
+
+
+def _evaluate(th, x, m):
+    """Y = U(th) x by a plain call."""
+    n = x.shape[0]
+    if _plain(n, m):
+        return binding.givens_forward(th, x)
+    return binding.givens_forward_restricted(th, x, n - 1 if m is None else m)
+
+
+class _Run:
+    """The batches evaluated with one theta (held, so that no other angles can come to lie at its address)."""
+
+    def __init__(self, theta, plain):
+        self.theta, self.version, self.plain, self.batches = theta, theta._version, plain, 0
+
+    def of(self, theta) -> bool:
+        return theta._version == self.version and theta.data_ptr() == self.theta.data_ptr()
+
+
 class _KeptMatrix:
     """U of the present angles laid out for evaluation, for use on any stream: made on one, which others wait for."""
 
     def __init__(self, theta, th, n, m, stream):
-        # holding theta holds its memory: no other angles can come to lie at its address
         self.theta, self.version, self.stream = theta, theta._version, stream
-        self.matrix = binding.Kept(th, givens_matrix(th, n, m), m)
+        U = binding.givens_build(th, n) if _plain(n, m) else binding.givens_build_restricted(th, n, n - 1 if m is None else m)
+        self.matrix = binding.Kept(th, U, m)
         self.ready = stream.record_event()
 
     def of(self, theta) -> bool:
@@ -164,7 +197,7 @@ class OrthogonalLinear(torch.nn.Module):
 
     def _start_evaluation(self) -> None:
         self._eval_matrix = None  # U laid out for evaluation, a _KeptMatrix
-        self._eval_plain = None   # version of theta, theta, plain batches evaluated with it
+        self._eval_run = None     # the batches evaluated with the present theta, a _Run
         self._captured = []       # those that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
@@ -178,36 +211,37 @@ class OrthogonalLinear(torch.nn.Module):
         # does not count (through .data, by a replayed graph) are seen on the device, which compares the angles.
         theta = self.theta.detach()
         th = theta.contiguous()
+        if self.n < _MATRIX_MIN_N:
+            return _evaluate(th, x, self.m)
         stream = torch.cuda.current_stream()
         kept = self._eval_matrix
         same = kept is not None and kept.of(theta)
         if torch.cuda.is_current_stream_capturing():
             if not same or kept.matrix.changed():
-                return givens_apply(self.theta, X, self.m)
+                return _evaluate(th, x, self.m)
             if not any(kept is k for k in self._captured):   # what a graph reads has to stay
                 self._captured.append(kept)
             return binding.givens_apply_packed(kept.matrix.packed, x, stream=stream)
-        if same:
-            try:
-                return kept.apply(th, x, stream)
-            except binding.GivensError as err:
-                if err.code != binding.ERR_STALE:
-                    raise
-                self._eval_matrix = self._eval_plain = None
-        # The first batches of a theta are plain calls.  Building and laying out U costs as much as 1.5 of them with few
-        # columns up to n = 2048, two at 4096 and four at 8192 (measured, B = 64: n = 1024 123 and 187 us, 2048 508 / 709,
-        # 4096 1212 / 2430, 8192 5.5 / 22 ms), so that many have come before it pays.
-        plain = self._eval_plain
-        batches = plain[2] if plain is not None and plain[0] == theta._version and plain[1].data_ptr() == theta.data_ptr() else 0
-        if batches < max(1, self.n // 2048):
-            self._eval_plain = (theta._version, theta, batches + 1)
-            return givens_apply(self.theta, X, self.m)
-        self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
-        return kept.apply(th, x, stream)
+        run = self._eval_run
+        if run is None or not run.of(theta) or (same and kept.matrix.changed()):
+            # a new theta: by plain calls if the last one did not see enough batches to be worth a matrix
+            run = self._eval_run = _Run(theta, run is not None and run.batches < _worth_a_matrix(self.n))
+            same = False
+        run.batches += 1
+        if run.plain and run.batches <= _PLAIN_BATCHES * max(1, self.n // 2048):
+            return _evaluate(th, x, self.m)
+        if not same:
+            self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
+        try:
+            return kept.apply(th, x, stream)
+        except binding.GivensError as err:
+            if err.code != binding.ERR_STALE:      # (known to have changed by now: the next batch is a new theta's)
+                raise
+            return _evaluate(th, x, self.m)
 
     # what evaluation keeps stays with the object: a copy starts anew, from whichever version of this class it was pickled
     def __getstate__(self):
-        return {k: v for k, v in self.__dict__.items() if k not in ("_eval_matrix", "_eval_plain", "_captured")}
+        return {k: v for k, v in self.__dict__.items() if k not in ("_eval_matrix", "_eval_run", "_captured")}
 
     def __setstate__(self, state):
         super().__setstate__({k: v for k, v in state.items() if k != "_eval_tables"})

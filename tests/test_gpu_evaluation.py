@@ -147,28 +147,50 @@ def test_streams_share_the_matrix(built):
         assert all(wrong(net, x, y) <= TOL_Y for y in outs)
 
 
-@pytest.mark.parametrize("n,plain", [(64, 1), (1006, 1), (2048, 1), (4096, 2)])
-def test_first_batches_are_plain_calls(built, n, plain):
+@pytest.mark.parametrize("n,enough", [(256, 8), (1006, 2), (2048, 2), (4096, 3)])
+def test_one_batch_per_change_is_a_plain_call(built, n, enough):
+    """The first theta gets a matrix; the next ones do when the last one saw enough batches.  The batches of one theta have
+    the same bits, whichever it is."""
     net = _layer().OrthogonalLinear(n)
     x = torch.randn(n, 8, device="cuda")
+
+    def batches(count):
+        ys = [net(x) for _ in range(count)]
+        assert wrong(net, x, ys[0]) <= TOL_Y and all(torch.equal(y, ys[0]) for y in ys)
+
     with torch.no_grad():
-        for _ in range(3):                                  # one batch per change of theta: never a matrix
-            net.theta.mul_(0.9)
-            assert wrong(net, x, net(x)) <= TOL_Y
-        assert built[0] == 0
-        for _ in range(plain - 1):
-            net(x)
-        assert built[0] == 0
-        for _ in range(3):
-            assert wrong(net, x, net(x)) <= TOL_Y
+        batches(1)
         assert built[0] == 1
-        net.theta.data.mul_(0.9)                            # unseen: right at once, and a plain call once it is known
+        for _ in range(3):
+            net.theta.mul_(0.9)
+            batches(1)
+        assert built[0] == 1
+        net.theta.mul_(0.9)
+        batches(enough)                                     # begun by plain calls and so on
+        assert built[0] == 1
+        net.theta.mul_(0.9)
+        batches(9)
+        assert built[0] == 2
+        net.theta.data.mul_(0.9)                            # unseen: right at once, and a new theta once it is known
         assert wrong(net, x, net(x)) <= TOL_Y
         torch.cuda.synchronize()
-        for _ in range(plain):
-            assert wrong(net, x, net(x)) <= TOL_Y
+        batches(enough)
+        assert built[0] == 3
+        net.theta.mul_(0.9)
+        batches(1)
+        assert built[0] == 4
+
+
+def test_a_layer_that_goes_back_into_service_has_its_matrix(built):
+    net = _layer().OrthogonalLinear(256)
+    x = torch.randn(256, 8, device="cuda")
+    with torch.no_grad():
+        for _ in range(3):
+            net.theta.mul_(0.9)
+            net(x)
         assert built[0] == 1
-        assert wrong(net, x, net(x)) <= TOL_Y
+        for _ in range(40):
+            assert wrong(net, x, net(x)) <= TOL_Y
         assert built[0] == 2
 
 
@@ -180,12 +202,13 @@ def test_a_recorded_first_batch_follows_the_angles(built):
     with torch.no_grad():
         torch.cuda.synchronize()
         with torch.cuda.stream(side):
-            net(x)                                          # the workspace of the stream
-            net.theta.mul_(0.9)
+            for _ in range(2):                              # (and the workspace of the stream)
+                net(x)
+                net.theta.mul_(0.9)
             side.synchronize()
             with torch.cuda.graph(graph, stream=side):
                 y = net(x)
-        assert built[0] == 0
+        assert built[0] == 1
         for _ in range(3):
             net.theta.mul_(0.9)
             y.fill_(float("nan"))
@@ -207,7 +230,7 @@ def test_matrices_of_recorded_graphs():
             torch.cuda.synchronize()
             graph = torch.cuda.CUDAGraph()
             with torch.cuda.stream(side):
-                for _ in range(2):
+                for _ in range(8):
                     net(x)
                 side.synchronize()
                 with torch.cuda.graph(graph, stream=side):
@@ -247,7 +270,7 @@ def test_copies_and_pickles():
         for _ in range(3):
             want = net(x)
         old = {**net.__dict__, "_eval_tables": (7, (0, net.theta.data_ptr(), 0))}   # as pickled by earlier versions
-        for name in ("_eval_matrix", "_eval_plain", "_captured"):
+        for name in ("_eval_matrix", "_eval_run", "_captured"):
             del old[name]
         from_old = L.OrthogonalLinear.__new__(L.OrthogonalLinear)
         from_old.__setstate__(pickle.loads(pickle.dumps(old)))

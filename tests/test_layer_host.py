@@ -16,7 +16,7 @@ def test_layers_are_copied_and_pickled_without_what_evaluation_keeps():
     from_old = layer.OrthogonalLinear.__new__(layer.OrthogonalLinear)
     from_old.__setstate__(old)
     for other in (copy.deepcopy(net), pickle.loads(pickle.dumps(net)), from_old):
-        assert other._eval_matrix is None and other._eval_plain is None and other._captured == []
+        assert other._eval_matrix is None and other._eval_run is None and other._captured == []
         assert not hasattr(other, "_eval_tables")
         assert torch.equal(other.theta, net.theta) and (other.n, other.m) == (6, None)
     assert net._captured == ["a matrix"]
