@@ -18,7 +18,7 @@
 // 129 TFLOP/s); 256 x 256 with eight wavefronts 2.87 ms, 128 x 128 3.13 ms.  Few rows give too few tiles of that
 // size, and B is then cut into more slices of 64 x 64 tiles: n = 64, B = 65536 in 10 us (256 slices), where the
 // 128 x 128 tile takes 36.  Rows of any length and alignment take the same 16-byte loads: n = 1002, B = 65536 in 0.76 ms
-// = 172 TFLOP/s (1.76 ms with element-by-element loads), B = 3001 in 71 us (166).
+// = 172 TFLOP/s (1.76 ms with element-by-element loads), B = 3001 in 58 us (166).
 //
 // Complex operands (interleaved): C = Y G^H has the real parts Y G^T and the imaginary parts Y (i G)^T of the real
 // rows x 2B arrays, where i G swaps the two columns of a complex number and negates the first: one contraction with

@@ -5,8 +5,8 @@ Section 2 — "forward" builds or applies U, "backward" turns dL/dY into dL/dthe
 Marshalling only.  forward() is one givens_forward / givens_build call; backward() is one
 givens_backward call on the saved *output* (the reverse sweep undoes the rotations, so no
 activations other than Y are kept).  For float32 the forward pass prepares the coefficient tables of both
-sweep directions once (givens_prepare) and the backward pass reuses them -- theta cannot change in
-between; if another call on the stream has replaced the tables meanwhile, the backward pass falls back to
+sweep directions once (givens_prepare, where givens_prepare_pays) and the backward pass reuses them -- theta cannot
+change in between; if another call on the stream has replaced the tables meanwhile, the backward pass falls back to
 the plain call, which rebuilds them.  There is no CPU path: tensors must live on the GPU.
 """
 from __future__ import annotations
@@ -27,7 +27,7 @@ def _prepare(th, n, m, want_backward: bool, B: int) -> int:
         return 0
     directions = binding.PREPARE_FORWARD
     if want_backward:
-        # wide batches take the Gram form, whose dX sweep needs tables of its own
+        # wide batches take the Gram form, which a token has to be prepared for
         directions |= binding.PREPARE_BACKWARD_WIDE if B >= 2 * (n + n % 2) else binding.PREPARE_BACKWARD
     return binding.givens_prepare(th, n, m, directions, batch=B)
 

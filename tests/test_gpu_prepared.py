@@ -1,6 +1,6 @@
 """Prepared coefficients (givens_prepare + *_prepared), per-call options (*_ex) and calls on several streams,
-through the C ABI.  The prepared calls run the same kernels on the same tables as the plain calls, so their
-results must be bit-identical to those; the plain calls are compared with the oracle here as elsewhere.
+through the C ABI.  The prepared calls run the same kernels on the same tables as the plain calls (these tests run with
+a rotation form chosen, under which no size runs as tiles by itself), so their results must be bit-identical to those; the plain calls are compared with the oracle here as elsewhere.
 """
 import numpy as np
 import pytest
