@@ -57,7 +57,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     constexpr int PER = BOTH * 2 / T;                  // octets per thread and step
     static_assert(BOTH * 2 % T == 0, "whole octets per thread");
     __shared__ u32x4 panel[2][3][2][BOTH];             // [buffer][piece][octet of the step][row of Y, then of G]
-    __shared__ float tops[BOTH];                       // largest magnitude of every row in this slice
+    __shared__ float tops[BOTH][2];                    // largest magnitude of every row in this slice, by its two threads
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % MW, wn = wave / MW;
     // Workgroups are handed to the eight XCDs (each with an L2 of its own) in turn.  The list of (slice, tile row, tile
@@ -143,9 +143,19 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
             for (int j = 0; j < NF; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i / (MF / IB)][i % (MF / IB)][j][v] = 0.f;
+        auto note = [&](long long k0) {   // with the last panel, whose barrier is the last one
+            if constexpr (!scaled())
+                if (k0 + kGramK >= kend)
+#pragma unroll
+                    for (int i = 0; i < PER; ++i) {
+                        const int c = (int)threadIdx.x + T * i;
+                        tops[c >> 1][c & 1] = top[i];
+                    }
+        };
         if (kbeg < kend) {
             fetch(kbeg);
             stash(scaled, 0);
+            note(kbeg);
         }
         int buf = 0;
         for (long long k0 = kbeg; k0 < kend; k0 += kGramK, buf ^= 1) {
@@ -167,25 +177,27 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
                         fa[q][p] = panel[buf][p][lane >> 5][wm * 32 * MF + 32 * (i * (MF / IB) + q) + (lane & 31)];
                 mfma_split(fa, fb, acc[i]);
             }
-            if (more) stash(scaled, buf ^ 1);
+            if (more) {
+                stash(scaled, buf ^ 1);
+                note(k0 + kGramK);
+            }
         }
     };
     run(std::false_type{});
 
     // the rows' largest magnitudes: every wavefront looks at all of them and comes to the same result
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const int c = (int)threadIdx.x + T * i;
-        top[i] = range_top(top[i], __shfl_xor(top[i], 1), 0.f);   // (two threads share a row)
-        scale[i] = range_scale(top[i]);
-        tops[c >> 1] = top[i];
-    }
-    __syncthreads();
+    auto scale_of = [&](int r) { return range_scale(tops[r][0] > tops[r][1] ? tops[r][0] : tops[r][1]); };
     bool odd = false;
+    if (kbeg < kend)                       // (an empty slice has none)
 #pragma unroll
-    for (int r = 0; r < BOTH; r += 64) odd = odd || range_scale(tops[r + lane]) != 1.f;
+        for (int r = 0; r < BOTH; r += 64) odd = odd || scale_of(r + lane) != 1.f;
     const bool again = __any(odd);
-    if (again) run(std::true_type{});
+    if (again) {
+        __syncthreads();                   // the last step's panels have been read
+#pragma unroll
+        for (int i = 0; i < PER; ++i) scale[i] = scale_of(((int)threadIdx.x + T * i) >> 1);
+        run(std::true_type{});
+    }
 
     // accumulator layout of the 32 x 32 matrix instructions: register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
     // column l % 32 of the fragment
@@ -196,14 +208,14 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
         const int col = tile_j * BN + wn * 32 * NF + 32 * j + (lane & 31);
         const int at = !CPLX ? col : (col < a.rows ? 2 * col : 2 * (col - a.rows) + 1);
         if (again) {
-            const float undo = range_unscale(range_scale(tops[BM + wn * 32 * NF + 32 * j + (lane & 31)]));
+            const float undo = range_unscale(scale_of(BM + wn * 32 * NF + 32 * j + (lane & 31)));
 #pragma unroll
             for (int i = 0; i < MF; ++i)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int r = wm * 32 * MF + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                     const float x = acc[i / (MF / IB)][i % (MF / IB)][j][v] * undo;
-                    acc[i / (MF / IB)][i % (MF / IB)][j][v] = x * range_unscale(range_scale(tops[r]));
+                    acc[i / (MF / IB)][i % (MF / IB)][j][v] = x * range_unscale(scale_of(r));
                 }
         }
 #pragma unroll

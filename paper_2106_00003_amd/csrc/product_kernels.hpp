@@ -133,6 +133,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
             panel[buf][o][1][my_col] = s.m;
             panel[buf][o][2][my_col] = s.l;
         }
+        if constexpr (!scaled()) tops[threadIdx.x / BN][my_col] = top;   // (read after the last step's barrier)
     };
 
     const int steps = (a.k + kProductStep - 1) / kProductStep, k16s = 2 * steps;
@@ -193,13 +194,12 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
         for (int g = 1; g < T / BN; ++g) t = t > tops[g][c] ? t : tops[g][c];
         return t;
     };
-    tops[threadIdx.x / BN][my_col] = top;
-    __syncthreads();
     bool odd = false;
 #pragma unroll
     for (int c = 0; c < BN; c += 64) odd = odd || range_scale(top_of(c + lane)) != 1.f;
     const bool again = __any(odd);
     if (again) {
+        __syncthreads();   // the last step's panel has been read
         scale = range_scale(top_of(my_col));
         // (nothing that only this run needs is to be computed, and kept in registers, before the first one)
         asm volatile("" : "+v"(col_in));
