@@ -329,7 +329,9 @@ int givens_set_kernel(int which);
  * (GIVENS_KERNEL_LDS, GIVENS_KERNEL_CAROUSEL, GIVENS_KERNEL_COLUMN or GIVENS_KERNEL_TILES; 0 before any call). */
 int givens_last_kernel(void);
 /* 1 when that call ran its family over n columns only, to get U or U^T, and multiplied the batch with it as a dense
- * product on the matrix cores (AUTO and every forced family, float: B >= 2 n and B >= 2048, complex64: B >= 4 n), else 0. */
+ * product on the matrix cores, whichever family was chosen, else 0.  Forward calls do so for float from n = 32, B >= 2 n
+ * and B >= 2048 on and for complex64 from B >= 4 n and B >= 4096 on; backward calls for dX whenever they take the Gram
+ * form, and where they run as tiles from B >= 2 n and B >= 2048 on. */
 int givens_last_product(void);
 
 /*

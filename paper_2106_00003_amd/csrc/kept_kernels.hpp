@@ -43,10 +43,12 @@ __device__ __forceinline__ void kept_angles(const KeptAngles &a, long long threa
     }
     if (FIRST) {
         if (thread == 0) *a.changed = 0;
-    } else if (differ || all) {
-        *a.changed = 1;
-        *a.note = a.id;
+        return;
     }
+    // one store over the bus: of the first wavefront that sees a change, and later of the first thread (the note may have
+    // gone to another matrix since)
+    if (__any(differ) && (threadIdx.x & 63) == 0 && atomicExch(a.changed, 1) == 0) *a.note = a.id;
+    if (all && thread == 0) *a.note = a.id;
 }
 // Bound by reading theta and its copy: n = 1024 (4 MB) in 3.2 us.
 template <bool FIRST>
