@@ -228,25 +228,29 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     }
 }
 
-// c[0] += c[1] + ... + c[slices-1] element by element: 64 elements per workgroup, kSumGroups threads for each, thread g
-// adding the slices g, g + kSumGroups, ... and the first one the sums, in that order (a single thread per element
-// leaves most of the chip idle for small matrices and waits for one load after the other).
-constexpr int kSumGroups = 8;
+// c[0] += c[1] + ... + c[slices-1] element by element: 64 elements at a time per workgroup, kSumGroups threads for each,
+// thread g adding the slices g, g + kSumGroups, ... and the first one the sums, in that order (a single thread per element
+// leaves most of the chip idle for small matrices and waits for one load after the other).  Workgroups take turns: one
+// for every 64 elements would be more threads than a launch may have for the largest matrices.
+constexpr int kSumGroups = 8, kSumBlocks = 16384;
 __global__ __launch_bounds__(64 * kSumGroups) void sum_slices_kernel(long long count, int slices, float *__restrict__ c)
 {
     __shared__ float part[kSumGroups][64];
     const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long long i = (long long)blockIdx.x * 64 + lane;
-    float acc = 0.f;
-    if (i < count) {
+    for (long long i0 = (long long)blockIdx.x * 64; i0 < count; i0 += (long long)gridDim.x * 64) {
+        const long long i = i0 + lane;
+        float acc = 0.f;
+        if (i < count) {
 #pragma unroll 4
-        for (int s = g; s < slices; s += kSumGroups) acc += c[(long long)s * count + i];
-    }
-    part[g][lane] = acc;
-    __syncthreads();
-    if (g == 0 && i < count) {
-        for (int q = 1; q < kSumGroups; ++q) acc += part[q][lane];
-        c[i] = acc;
+            for (int s = g; s < slices; s += kSumGroups) acc += c[(long long)s * count + i];
+        }
+        part[g][lane] = acc;
+        __syncthreads();
+        if (g == 0 && i < count) {
+            for (int q = 1; q < kSumGroups; ++q) acc += part[q][lane];
+            c[i] = acc;
+        }
+        __syncthreads();
     }
 }
 
@@ -256,21 +260,22 @@ __global__ __launch_bounds__(64 * kSumGroups) void sum_slices_kernel(long long c
 // A result's error grows with the square root of the additions behind it, six for every sixteen columns here, where the
 // float32 matrix instructions made eight.  Slices of at most 4096 columns keep it below theirs: n = 2048, B = 65536, normal
 // operands 2.5e-6 with slices of 16384, 1.3e-6 with 4096 (float32 instructions 2.3e-6), contraction 2.70 and 2.82 ms;
-// n = 1024, B = 131072 2.2e-6 with 8192, 1.6e-6 with 4096 (1.6e-6).
-constexpr long long kGramMaxSlice = 4096;
+// n = 1024, B = 131072 2.2e-6 with 8192, 1.6e-6 with 4096 (1.6e-6).  As far as the slices fit 4 GiB (n = 8192: sixteen).
+constexpr long long kGramMaxSlice = 4096, kGramSliceBytes = 1LL << 32;
 struct GramPlan {
     bool large;
     int slices;
 };
 inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = false)
 {
-    const int cols = cplx ? 2 * rows : rows;
-    auto tiles = [&](int bm, int bn) { return (long long)((rows + bm - 1) / bm) * ((cols + bn - 1) / bn); };
+    const int result_cols = cplx ? 2 * rows : rows;
+    auto tiles = [&](int bm, int bn) { return (long long)((rows + bm - 1) / bm) * ((result_cols + bn - 1) / bn); };
     auto slices_for = [&](long long t, long long want, long long cols) {
         long long s = (want + t - 1) / t;
-        const long long by_cols = B / cols > 1 ? B / cols : 1, least = (B + kGramMaxSlice - 1) / kGramMaxSlice;
+        const long long by_cols = B / cols > 1 ? B / cols : 1, fit = kGramSliceBytes / (4LL * rows * result_cols);
+        const long long least = (B + kGramMaxSlice - 1) / kGramMaxSlice;
         s = s < by_cols ? s : by_cols;
-        s = s > least ? s : least;
+        s = s > least || s > fit ? s : (least < fit ? least : fit);
         s = s < 256 ? s : 256;
         return (int)(s > 1 ? s : 1);
     };
@@ -312,8 +317,8 @@ inline void gram_matrix(int rows, long long B, const GramPlan &plan, const float
         launch_gram<2, 2, 1, 1, CPLX>(a, plan.slices, stream);
     if (plan.slices > 1) {
         const long long count = (long long)rows * cols;
-        hipLaunchKernelGGL(sum_slices_kernel, dim3((unsigned)((count + 63) / 64)), dim3(64 * kSumGroups), 0, stream, count,
-                           plan.slices, C);
+        const unsigned blocks = (unsigned)((count + 63) / 64 < kSumBlocks ? (count + 63) / 64 : kSumBlocks);
+        hipLaunchKernelGGL(sum_slices_kernel, dim3(blocks), dim3(64 * kSumGroups), 0, stream, count, plan.slices, C);
     }
 }
 
