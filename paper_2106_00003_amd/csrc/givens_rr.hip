@@ -989,12 +989,12 @@ int run_tiles_apply(Workspace *ws, int dev, const Problem &pb, const TilePlan &g
             return rc;
         {
             Span span(1, stream);
-            tiles_apply(g, cus, pb.rows, pb.m, pb.rows, b, nullptr, st.matrix, forward, stream);
+            tiles_apply(g, cus, pb.rows, pb.m, b, TileOperand{pb.rows, nullptr, st.matrix}, forward, stream);
         }
         return apply_matrix(st, dev, pb.rows, B, X, Y, stream);
     }
     Span span(1, stream);
-    tiles_apply(g, cus, pb.rows, pb.m, B, b, X, Y, forward, stream);
+    tiles_apply(g, cus, pb.rows, pb.m, b, TileOperand{B, X, Y}, forward, stream);
     GIVENS_HIP(hipGetLastError());
     return GIVENS_OK;
 }
@@ -1032,6 +1032,12 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     const GramPlan plan = gram_plan(pb.rows, B, cus);
     if (int rc = grow(ws.gram, (size_t)plan.slices * pb.rows * pb.rows * sizeof(float))) return rc;
     float *C = reinterpret_cast<float *>(ws.gram.ptr);
+    // dX = U^T G: the stages take G along, or I for the product of a wide batch with U^T
+    const bool multiplies = dX && !swept;
+    ProductStorage st;
+    if (multiplies)
+        if (int rc = workspace_product_storage(ws, pb.rows, B, G == dX, &st)) return rc;
+    const TileOperand op = multiplies ? TileOperand{pb.rows, nullptr, st.matrix} : TileOperand{B, G, dX};
     {
         Span span(0, stream);
         tiles_build(g, theta, pb.map, pb.m, b, false, pb.rows, B, swept, stream);
@@ -1042,14 +1048,14 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     }
     {
         Span span(2, stream);
-        tiles_gradient(g, pb.rows, pb.m, pb.map, b, C, dtheta, stream);
+        tiles_gradient(g, cus, pb.rows, pb.m, pb.map, b, C, dtheta, op, stream);
         GIVENS_HIP(hipGetLastError());
     }
     t_state.last_kernel = GIVENS_KERNEL_TILES;
     t_state.last_flag = nullptr;
     t_state.last_reduction = GIVENS_REDUCTION_GRAM;
     t_state.last_chains = 0;
-    return dX ? run_tiles_apply(&ws, dev, pb, g, b, B, G, dX, false, stream) : GIVENS_OK;
+    return multiplies ? apply_matrix(st, dev, pb.rows, B, G, dX, stream) : GIVENS_OK;
 }
 
 // rows, m: see Problem.  The unrestricted entry points pass an even rows and m = rows - 1.

@@ -61,11 +61,16 @@ inline size_t tile_s_bytes(const TilePlan &g) { return tile_range_offset(g) + 25
 // X (may be null): the rows x B operand that tiles_apply is going to take, whose columns' range is looked at beside.
 void tiles_build(const TilePlan &g, const float *theta, const int *map, int free_rows, const TileBuffers &b, bool forward,
                  int rows, long long B, const float *X, hipStream_t stream);
-// Y <- U X or U^T X on B columns; X may be Y, nullptr means I
-void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const TileBuffers &b,
-                 const float *X, float *Y, bool forward, hipStream_t stream);
-// dtheta from C = Y G^T (leading dimension `rows`); the pieces are U^T's
-void tiles_gradient(const TilePlan &g, int rows, int free_rows, const int *map, const TileBuffers &b, const float *C,
-                    float *dtheta, hipStream_t stream);
+// What the tiles are applied to: Y <- U X or U^T X on B columns; X may be Y, nullptr means I
+struct TileOperand {
+    long long B;
+    const float *X;
+    float *Y;            // null: nothing to apply to
+};
+void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
+                 bool forward, hipStream_t stream);
+// dtheta from C = Y G^T (leading dimension `rows`); the pieces are U^T's.  Beside it, U^T is applied to `op`.
+void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const int *map, const TileBuffers &b,
+                    const float *C, float *dtheta, const TileOperand &op, hipStream_t stream);
 
 } // namespace givens

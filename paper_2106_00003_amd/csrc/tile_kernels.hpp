@@ -414,15 +414,18 @@ struct TileApplyArgs {
 // 32 rows of the result with its part of the matrix in registers throughout.  Per step of kTileCols columns a wavefront brings
 // 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange), a step ahead,
 // and puts the pieces into LDS as fragments.
-__global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyArgs a)
+struct TileApplyShared {
+    u32x4 panel[kTilePad / 16][3][64];
+};
+__device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned block, TileApplyShared &sh)
 {
     constexpr int KF = kTilePad / 16;
-    __shared__ u32x4 panel[KF][3][64];
+    auto &panel = sh.panel;
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int u = blockIdx.x % g.P;
-    const long long n0 = (long long)(blockIdx.x / g.P) * a.chunk, n1 = n0 + a.chunk < a.B ? n0 + a.chunk : a.B;
+    const int u = block % g.P;
+    const long long n0 = (long long)(block / g.P) * a.chunk, n1 = n0 + a.chunk < a.B ? n0 + a.chunk : a.B;
     const Tile x = tile_at(g, a.stage, u);
     const bool identity = tile_is_identity(g, x, a.free_rows);
     if (n0 >= a.B || (a.X == a.Y && identity)) return;
@@ -497,6 +500,11 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
             }
         __syncthreads();
     }
+}
+__global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyArgs a)
+{
+    __shared__ TileApplyShared sh;
+    tile_apply(a, blockIdx.x, sh);
 }
 
 // ---- the gradient's matrix S: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on),
@@ -602,15 +610,19 @@ __device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, con
 // part of A_x in registers).  The other operand of both products is cut into pieces once and shared through LDS, half the
 // contraction at a time: S as rows of eight values (a lane's are two groups of four consecutive columns), V as its
 // accumulators are.  Pairs without a rotation are left alone.  n = 4096: 40 to 48 us a stage.
-__global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwoSidedArgs a)
+struct TileTwoSidedShared {
+    u32x4 panel[kTilePad / 32][kTilePad / 32][3][64];
+    int place_x[kTilePad], place_y[kTilePad];
+};
+__device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsigned block_id, TileTwoSidedShared &sh)
 {
     constexpr int MF = kTilePad / 32, KF = kTilePad / 16, KH = KF / 2;
-    __shared__ u32x4 panel[KH][MF][3][64];
-    __shared__ int place_x[kTilePad], place_y[kTilePad];
+    auto &panel = sh.panel;
+    auto &place_x = sh.place_x, &place_y = sh.place_y;
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int ux = 0, uy = blockIdx.x;
+    int ux = 0, uy = block_id;
     while (uy >= g.P - ux) uy -= g.P - ux++;
     uy += ux;
     const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
@@ -731,16 +743,20 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_two_sided_kernel(TileTwo
 // wavefront 32 rows of tile x, and only V's pieces go through LDS.  The other workgroups of a pair still read what one
 // writes, so the result goes to another array, all of it.  Bound by latency: everything a product needs is on its way
 // before it starts.  n = 1024: 12 us a stage (19.7 with a pair per workgroup).
-__global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(TileTwoSidedArgs a)
+struct TileNarrowShared {
+    u32x4 panel[kTilePad / 16][3][64];
+    int place_x[kTilePad], place_y[kTilePad];
+};
+__device__ __forceinline__ void tile_two_sided_narrow(const TileTwoSidedArgs &a, unsigned block_id, TileNarrowShared &sh)
 {
     constexpr int MF = kTilePad / 32, KF = kTilePad / 16;
-    __shared__ u32x4 panel[KF][3][64];
-    __shared__ int place_x[kTilePad], place_y[kTilePad];
+    auto &panel = sh.panel;
+    auto &place_x = sh.place_x, &place_y = sh.place_y;
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int part = blockIdx.x % MF;
-    int ux = 0, uy = blockIdx.x / MF;
+    const int part = block_id % MF;
+    int ux = 0, uy = block_id / MF;
     while (uy >= g.P - ux) uy -= g.P - ux++;
     uy += ux;
     const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
@@ -828,6 +844,33 @@ __global__ __launch_bounds__(2 * kTilePad, 1) void tile_two_sided_narrow_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[0][0][0][v] = (acc[0][0][0][v] + acc[1][0][0][v]) * undo;
     tile_store_both(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
+}
+
+// One launch per stage of the reverse sweep: the workgroups before `pair_blocks` take S through it, the others (OPERAND) what
+// dX comes from (G, or I where U^T is wanted).  Neither reads what the other writes, and alone each leaves compute units
+// idle.  Per stage, launches of their own against this one: n = 1002 with I 11.2 + 6.9 and 13 us, n = 1024 with I 12.2 + 8.4
+// and 13.5, n = 4097, m = 512, B = 4096 with G 29 + 21 and 45.
+struct TileStageArgs {
+    TileTwoSidedArgs s;
+    TileApplyArgs a;
+    unsigned pair_blocks;
+};
+template <bool NARROW, bool OPERAND>
+__global__ __launch_bounds__(2 * kTilePad, NARROW && !OPERAND ? 1 : 2) void tile_stage_kernel(TileStageArgs a)
+{
+    __shared__ union {
+        std::conditional_t<NARROW, TileNarrowShared, TileTwoSidedShared> s;
+        TileApplyShared a;
+    } sh;
+    if constexpr (OPERAND)
+        if (blockIdx.x >= a.pair_blocks) {
+            tile_apply(a.a, blockIdx.x - a.pair_blocks, sh.a);
+            return;
+        }
+    if constexpr (NARROW)
+        tile_two_sided_narrow(a.s, blockIdx.x, sh.s);
+    else
+        tile_two_sided(a.s, blockIdx.x, sh.s);
 }
 
 // 64 values per lane -> lane l has the sum over all lanes of value l

@@ -1,6 +1,7 @@
 // Launches of the tiled sweeps (tile_kernels.hpp).
 #include "tile_kernels.hpp"
 
+#include <algorithm>
 #include <utility>
 
 namespace givens {
@@ -19,42 +20,60 @@ inline void tile_build(const TilePlan &g, const float *theta, const int *map, in
     hipLaunchKernelGGL(tile_split_kernel, dim3(split_blocks + (unsigned)tile_top_blocks(tops)), dim3(256), 0, stream, g,
                        free_rows, matrices, pieces, transposed ? 1 : 0, split_blocks, tops);
 }
-// Y <- U X (forward, pieces of the transposed matrices) or U^T X; X may be Y, nullptr means I
-inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const u32x4 *pieces,
-                       const unsigned *tops, const float *X, float *Y, bool forward, hipStream_t stream)
+// Stage st of Y <- U X or U^T X, the `first` one from X (nullptr: I), the others in place.  `runs` of column blocks for each
+// tile; 0: no tile of the stage has a free pair.  `resident`: workgroups to aim at.
+inline long long tile_apply_stage(const TilePlan &g, long long resident, int st, bool first, int rows, int free_rows,
+                                  const TileOperand &op, const u32x4 *pieces, const unsigned *tops, TileApplyArgs *out)
+{
+    const bool copies = first && op.X != op.Y;          // the first stage writes every row
+    int active = g.P;
+    if (!copies && free_rows < g.n - 1) {
+        active = 0;
+        for (int u = 0; u < g.P; ++u) active += tile_is_identity(g, tile_at(g, st, u), free_rows) ? 0 : 1;
+        if (active == 0) return 0;
+    }
+    const long long steps = (op.B + kTileCols - 1) / kTileCols;
+    long long runs = resident / active > 1 ? resident / active : 1;
+    const long long per = (steps + runs - 1) / runs;
+    runs = (steps + per - 1) / per;
+    *out = TileApplyArgs{g, st, rows, free_rows, op.B, pieces, first ? op.X : op.Y, op.Y, per * kTileCols,
+                         op.X ? tops : nullptr};
+    return runs;
+}
+// Y <- U X (forward, pieces of the transposed matrices) or U^T X
+inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileOperand &op,
+                       const u32x4 *pieces, const unsigned *tops, bool forward, hipStream_t stream)
 {
     // at most what the chip holds at once (eight wavefronts per compute unit)
-    const long long resident = (long long)compute_units * 8 / (kTilePad / 32), steps = (B + kTileCols - 1) / kTileCols;
+    const long long resident = (long long)compute_units * 8 / (kTilePad / 32);
     for (int i = 0; i < g.stages; ++i) {
-        const int st = forward ? g.stages - 1 - i : i;
-        const bool copies = i == 0 && X != Y;          // the first stage writes every row
-        int active = g.P;
-        if (!copies && free_rows < g.n - 1) {
-            active = 0;
-            for (int u = 0; u < g.P; ++u) active += tile_is_identity(g, tile_at(g, st, u), free_rows) ? 0 : 1;
-            if (active == 0) continue;
-        }
-        long long runs = resident / active > 1 ? resident / active : 1;
-        const long long per = (steps + runs - 1) / runs;
-        runs = (steps + per - 1) / per;
-        const TileApplyArgs a{g, st, rows, free_rows, B, pieces, i ? Y : X, Y, per * kTileCols, X ? tops : nullptr};
-        hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
+        TileApplyArgs a;
+        const long long runs = tile_apply_stage(g, resident, forward ? g.stages - 1 - i : i, i == 0, rows, free_rows, op,
+                                                pieces, tops, &a);
+        if (runs)
+            hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
     }
 }
-inline void tile_gradient(const TilePlan &g, int rows, int free_rows, const double2 *table, const int *map, const u32x4 *pieces,
-                          const float *C, float *S, float *blocks, int *range, float *dtheta, hipStream_t stream)
+inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const double2 *table, const int *map,
+                          const u32x4 *pieces, const float *C, float *S, float *blocks, int *range, const unsigned *tops,
+                          float *dtheta, const TileOperand &op, hipStream_t stream)
 {
     const int t = tile_ld(g) / 32;
-    const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2);
-    float *second = tile_gradient_narrow(g, free_rows) ? S + tile_s_floats(g) : nullptr;
+    const bool narrow = tile_gradient_narrow(g, free_rows);
+    const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2) * (narrow ? kTilePad / 32 : 1);
+    float *second = narrow ? S + tile_s_floats(g) : nullptr;
     hipLaunchKernelGGL(tile_antisym_kernel, dim3(t, t), dim3(256), 0, stream, g, rows, C, S, second, range);
+    const long long slots = (long long)compute_units * 8 / (kTilePad / 32);
     float *in = S, *out = second ? second : S;
     for (int st = 0; st < g.stages; ++st) {
-        const TileTwoSidedArgs a{g, st, free_rows, pieces, in, out, blocks, range};
-        if (second)
-            hipLaunchKernelGGL(tile_two_sided_narrow_kernel, dim3(pairs * (kTilePad / 32)), dim3(2 * kTilePad), 0, stream, a);
-        else
-            hipLaunchKernelGGL(tile_two_sided_kernel, dim3(pairs), dim3(2 * kTilePad), 0, stream, a);
+        TileStageArgs a{TileTwoSidedArgs{g, st, free_rows, pieces, in, out, blocks, range}, {}, pairs};
+        long long runs = 0;
+        if (op.Y)
+            runs = tile_apply_stage(g, std::max(slots - (long long)pairs, slots / 2), st, st == 0, rows, free_rows, op, pieces,
+                                    tops, &a.a);
+        const auto kernel = narrow ? (runs ? tile_stage_kernel<true, true> : tile_stage_kernel<true, false>)
+                                   : (runs ? tile_stage_kernel<false, true> : tile_stage_kernel<false, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(pairs + runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
         if (second) std::swap(in, out);
     }
     hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(g.P + (tile_count(g) + 1) / 2)), dim3(2 * kTilePad), 0, stream, g,
@@ -68,17 +87,16 @@ void tiles_build(const TilePlan &g, const float *theta, const int *map, int free
     tile_build(g, theta, map, free_rows, b.table, b.matrices, static_cast<u32x4 *>(b.pieces), b.range,
                TileTops{rows, B, X, b.tops}, forward, stream);
 }
-void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, long long B, const TileBuffers &b,
-                 const float *X, float *Y, bool forward, hipStream_t stream)
+void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
+                 bool forward, hipStream_t stream)
 {
-    tile_apply(g, compute_units, rows, free_rows, B, static_cast<const u32x4 *>(b.pieces), b.tops, X, Y, forward,
-               stream);
+    tile_apply(g, compute_units, rows, free_rows, op, static_cast<const u32x4 *>(b.pieces), b.tops, forward, stream);
 }
-void tiles_gradient(const TilePlan &g, int rows, int free_rows, const int *map, const TileBuffers &b, const float *C,
-                    float *dtheta, hipStream_t stream)
+void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const int *map, const TileBuffers &b,
+                    const float *C, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
-    tile_gradient(g, rows, free_rows, b.table, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.matrices, b.range, dtheta,
-                            stream);
+    tile_gradient(g, compute_units, rows, free_rows, b.table, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.matrices,
+                  b.range, b.tops, dtheta, op, stream);
 }
 
 } // namespace givens
