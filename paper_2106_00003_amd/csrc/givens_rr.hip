@@ -80,7 +80,7 @@ struct Workspace {
     Buffer gram;        // Gram form: slices of C = Y G^T, rows x rows floats each
     Buffer matrix;      // wide batches: U or U^T, rows x rows floats
     Buffer pieces;      // ... and its pieces in operand order (product_kernels.hpp)
-    Buffer tile_table, tile_matrices, tile_pieces, tile_s, tile_tops;   // tiled sweeps (tile_host.hpp)
+    Buffer tile_pieces, tile_blocks, tile_s, tile_tops;   // tiled sweeps (tile_host.hpp)
     Buffer columns;     // ... and a copy of the columns at work when a result overwrites its operand
     Buffer map;         // restricted parametrisation / odd n: index in theta of every entry of E, or -1
     Buffer map_counts;  // free pairs per block (scratch of the map kernels)
@@ -89,7 +89,7 @@ struct Workspace {
     Buffer u_q, u_psi, u_sgn, u_rot, u_phs, u_orient, u_fin;
     int map_rows = 0, map_m = 0; // the (row count, m) the map was built for
     Prepared prepared;
-    Buffer *all[30] = {&tile_table, &tile_matrices, &tile_pieces, &tile_s, &tile_tops, &flag, &scale,
+    Buffer *all[29] = {&tile_pieces, &tile_blocks, &tile_s, &tile_tops, &flag, &scale,
                        &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
                        &matrix, &pieces, &columns, &partial, &zeros, &sink, &gram, &map,
                        &u_q, &u_psi, &u_sgn, &u_rot, &u_phs, &u_orient, &u_fin, &chain, &chain_flags};
@@ -461,8 +461,7 @@ constexpr size_t noalloc_tile_bytes(int n)
 {
     if (n < kTileMinN) return 0;
     const TilePlan g = tile_plan(n);
-    return round_up_256(tile_table_bytes(g)) + round_up_256(tile_matrices_bytes(g)) + round_up_256(tile_pieces_bytes(g)) +
-           round_up_256(noalloc_tile_cols(n) * sizeof(unsigned));
+    return round_up_256(tile_pieces_bytes(g)) + round_up_256(noalloc_tile_cols(n) * sizeof(unsigned));
 }
 constexpr size_t noalloc_tables_bytes(int n) { return std::max(noalloc_sweep_bytes(n), noalloc_tile_bytes(n)); }
 constexpr size_t noalloc_bytes(int n)
@@ -518,8 +517,6 @@ int static_storage(int dev, int n, bool try_forms, CoefStorage<float> *out, Tile
     at = tables;
     if (n >= kTileMinN) {
         const TilePlan g = tile_plan(n);
-        tiles->table = reinterpret_cast<double2 *>(take(tile_table_bytes(g)));
-        tiles->matrices = reinterpret_cast<float *>(take(tile_matrices_bytes(g)));
         tiles->pieces = take(tile_pieces_bytes(g));
         tiles->tops = reinterpret_cast<unsigned *>(take(noalloc_tile_cols(n) * sizeof(unsigned)));
     }
@@ -958,19 +955,21 @@ bool tiles_by_product(int rows, long long B) { return B >= kProductMinRatio * ro
 // operand_cols: of the operand the tiles are applied to (0: none, or I)
 int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, long long operand_cols, TileBuffers *out)
 {
-    if (int rc = grow(ws.tile_table, tile_table_bytes(g))) return rc;
-    if (int rc = grow(ws.tile_matrices, tile_matrices_bytes(g))) return rc;
     if (int rc = grow(ws.tile_pieces, tile_pieces_bytes(g))) return rc;
-    *out = TileBuffers{reinterpret_cast<double2 *>(ws.tile_table.ptr), reinterpret_cast<float *>(ws.tile_matrices.ptr),
-                       ws.tile_pieces.ptr, nullptr, nullptr, nullptr};
+    *out = TileBuffers{};
+    out->pieces = ws.tile_pieces.ptr;
     if (operand_cols) {
         if (int rc = grow(ws.tile_tops, (size_t)operand_cols * sizeof(unsigned))) return rc;
         out->tops = reinterpret_cast<unsigned *>(ws.tile_tops.ptr);
     }
     if (gradient) {
+        if (int rc = grow(ws.tile_blocks, tile_blocks_bytes(g))) return rc;
         if (int rc = grow(ws.tile_s, tile_s_bytes(g))) return rc;
+        out->blocks = reinterpret_cast<float *>(ws.tile_blocks.ptr);
         out->S = reinterpret_cast<float *>(ws.tile_s.ptr);
-        out->range = reinterpret_cast<int *>(static_cast<unsigned char *>(ws.tile_s.ptr) + tile_range_offset(g));
+        unsigned char *const s = static_cast<unsigned char *>(ws.tile_s.ptr);
+        out->range = reinterpret_cast<int *>(s + tile_range_offset(g));
+        out->halves = reinterpret_cast<float *>(s + tile_halves_offset(g));
     }
     return GIVENS_OK;
 }
@@ -1048,7 +1047,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     }
     {
         Span span(2, stream);
-        tiles_gradient(g, cus, pb.rows, pb.m, pb.map, b, C, dtheta, op, stream);
+        tiles_gradient(g, cus, pb.rows, pb.m, theta, pb.map, b, C, dtheta, op, stream);
         GIVENS_HIP(hipGetLastError());
     }
     t_state.last_kernel = GIVENS_KERNEL_TILES;

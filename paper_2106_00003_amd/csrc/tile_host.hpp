@@ -29,7 +29,6 @@ constexpr TilePlan tile_plan(int n)
 }
 constexpr long long tile_count(const TilePlan &p) { return (long long)p.stages * p.P; }
 constexpr int kTilePieceWords = kTilePad * kTilePad * 3 / 8;   // u32x4 per tile
-constexpr long long tile_coef_entries(const TilePlan &g) { return (long long)g.s * (2 * g.P + tile_count(g)) * (kTilePad / 2); }
 
 // the gradient's matrix: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on), then row 0
 inline __host__ __device__ int tile_piece_stride(const TilePlan &g) { return (g.s + 3) / 4 * 4; }
@@ -43,18 +42,22 @@ inline bool tile_gradient_narrow(const TilePlan &g, int free_rows) { return free
 
 // What the calls on one problem need: bytes of each buffer.
 struct TileBuffers {
-    double2 *table;      // cos and sine of every rotation, in the order in which the tiles take them
-    float *matrices;     // the tiles' matrices; later the blocks that the gradient's stages leave
-    void *pieces;        // ... cut into bf16 pieces, in operand order
-    float *S;            // gradient only (forward: null)
-    int *range;          // the same: the range of S's elements, behind it
+    void *pieces;        // the tiles' matrices, cut into bf16 pieces, in operand order
+    float *blocks;       // gradient only (forward: null): the tiles' own blocks of S, which its stages leave
+    float *S;            // the same
+    int *range;          // the same: the range of S's elements and counts of the gradient kernel, behind it
+    float *halves;       // the same: sums of special tiles, behind those
     unsigned *tops;      // of an operand's columns, one word each; null where the tiles are applied to I only
 };
-constexpr size_t tile_table_bytes(const TilePlan &g) { return (size_t)tile_coef_entries(g) * sizeof(double2); }
-constexpr size_t tile_matrices_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
+constexpr size_t tile_blocks_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
 constexpr size_t tile_pieces_bytes(const TilePlan &g) { return (size_t)(tile_count(g) + 1) * kTilePieceWords * 16; }
 inline size_t tile_range_offset(const TilePlan &g) { return 2 * tile_s_floats(g) * sizeof(float); }
-inline size_t tile_s_bytes(const TilePlan &g) { return tile_range_offset(g) + 256; }
+// behind S: its range and the counts (one page), and the sums of the special tiles' two halves
+inline size_t tile_halves_offset(const TilePlan &g) { return tile_range_offset(g) + 1024; }
+inline size_t tile_s_bytes(const TilePlan &g)
+{
+    return tile_halves_offset(g) + (size_t)g.P * 4 * kTileSlots * (kTilePad / 2) * sizeof(float);
+}
 
 // free_rows: pairs (i, j) with i < free_rows rotate (n - 1: all of them); rows: of the operand, n or n - 1.
 // Matrices of all tiles, cut into pieces: of U's side (forward) or of U^T's, which the gradient takes too.
@@ -70,7 +73,7 @@ struct TileOperand {
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
                  bool forward, hipStream_t stream);
 // dtheta from C = Y G^T (leading dimension `rows`); the pieces are U^T's.  Beside it, U^T is applied to `op`.
-void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const int *map, const TileBuffers &b,
-                    const float *C, float *dtheta, const TileOperand &op, hipStream_t stream);
+void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
+                    const TileBuffers &b, const float *C, float *dtheta, const TileOperand &op, hipStream_t stream);
 
 } // namespace givens

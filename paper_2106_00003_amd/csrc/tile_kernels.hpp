@@ -9,10 +9,10 @@
 // the late parts with i + j = t and the early parts with i + j = t + 2P: P tiles that share no row.  The pairs inside
 // piece i and inside piece i + P, whose rotations with row 0 alternate, are one special tile of stage 2i.
 //
-// A tile's rotations act on at most 2s + 1 <= kTilePad rows, so they are one kTilePad x kTilePad orthogonal matrix: built here with
-// one lane per column, in float64 (as fast as float32 on this chip), and applied to any number of columns as a product
-// of bf16 pieces (split_bf16.hpp).  A rotation then costs 8 operations per column on the matrix cores instead of
-// 2 to 4 vector instructions, and the chain of n - 1 dependent blocks becomes one of about n / s products.
+// A tile's rotations act on at most 2s + 1 <= kTilePad rows, so they are one kTilePad x kTilePad orthogonal matrix: built here
+// in float64, column by column, and applied to any number of columns as a product of bf16 pieces (split_bf16.hpp).  A rotation
+// then costs 8 operations per column on the matrix cores instead of 2 to 4 vector instructions, and the chain of n - 1
+// dependent blocks becomes one of about n / s products.
 //
 // Gradient.  With S = Z G^T - G Z^T (antisymmetric) of the strips z and gbar before a tile, the share of a pair (i, j),
 // i < j, is S_ij in the frame of its rotation, and a rotation takes S to R S R^T.  So the reverse sweep needs neither
@@ -130,75 +130,107 @@ __device__ __forceinline__ double2 tile_sincos(double th)
     return out;
 }
 
-// The range (split_bf16.hpp) of the gradient's matrix S, one for all of it: the stages keep its norm.  Words that the coefficient kernel clears
+// The range (split_bf16.hpp) of the gradient's matrix S, one for all of it: the stages keep its norm.  Words that the build kernel clears
 // and the antisymmetric part's sets, 1 each: an element other than zero, one of the middle range or above, one above it.
+// Behind them, cleared with them, a count for every special tile (tile_gradient_kernel).
 enum { kTileAny = 0, kTileMiddle = 1, kTileLarge = 2, kTileRangeWords = 3 };
 __device__ __forceinline__ float tile_scale(const int *range)
 {
     return range[kTileLarge] ? range_scale(kRangeLarge) : range[kTileMiddle] || !range[kTileAny] ? 1.f : range_scale(kRangeSmall / 2);
 }
 
-// Coefficient table of the tiles, rows of 64 (S + 1 used) entries (cos, sine; the sine negated when the first row has the
-// larger label; (1, 0) for a pair that is bypassed or not in the tile).  Row r of an ordinary tile: row r of piece i with
-// every row of piece j, in order.  Row r of a special tile, for piece i and then (s rows further on) for piece i + P: with
-// the row slot + 1 places before it, and in the last of the S + 1 entries with row 0.  First the P special tiles with 2 s
-// rows each, then all tiles with s rows each (those of the special ones unused).
-__device__ __forceinline__ const double2 *tile_coef_table(const TilePlan &g, const double2 *table, int st, int u, bool special,
-                                                          int width)
+// A tile's rotations as a table of s x 64 entries, row by row in order.  Row r of an ordinary tile: row r of piece i with every
+// row of piece j.  Row r of a special tile, for piece i and for piece i + P: with the rows before it, oldest first, and in the
+// last entry with row 0.  Places without a rotation: -1.
+constexpr int kTileTable = kTilePad / 2;   // entries in a row of the table
+constexpr int kTileThreads = 512;          // of the kernels that go rotation by rotation
+struct TileEntry {
+    int e;            // in E
+    bool ordered;     // the first row has the smaller label
+};
+__device__ __forceinline__ TileEntry tile_entry(const TilePlan &g, const Tile &x, bool special, int which, int r, int slot)
 {
-    const size_t row = special ? (size_t)((st + g.first) / 2) * 2 * g.s : (size_t)g.s * (2 * g.P + (size_t)st * g.P + u);
-    return table + row * width;
-}
-__global__ __launch_bounds__(256) void tile_coef_kernel(TilePlan g, const float *__restrict__ theta,
-                                                        const int *__restrict__ map, int free_rows, long long entries,
-                                                        double2 *__restrict__ table, int *__restrict__ range,
-                                                        long long columns, unsigned *__restrict__ tops)
-{
-    const int width = kTilePad / 2;
-    const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (range && id < kTileRangeWords) range[id] = 0;
-    for (long long i = id; i < columns; i += (long long)gridDim.x * 256) tops[i] = 0u;
-    if (id >= entries) return;
-    const int slot = (int)(id % width);
-    long long row = id / width;
-    const bool special = row < 2LL * g.P * g.s;
-    long long e = -1;
-    bool ordered = false;
+    TileEntry t{-1, false};
     if (special) {
-        const int i = (int)(row / (2 * g.s)), which = (int)(row % (2 * g.s)) / g.s, r = (int)(row % g.s);
-        int start, count;
-        tile_piece(g, i + which * g.P, &start, &count);
-        if (r < count) {
-            const int a = start + r;
-            if (slot == width - 1) {
-                e = tile_held_entry(g, a);             // row 0 has the smaller label
-            } else if (slot < r) {
-                e = tile_pair_entry(g, a, a - 1 - slot);
-                ordered = tile_label(g, a) < tile_label(g, a - 1 - slot);
-            }
+        const int start = which ? x.b0 : x.a0, a = start + r;
+        if (r >= (which ? x.nb : x.na)) return t;
+        if (slot == kTileTable - 1) {
+            t.e = (int)tile_held_entry(g, a);
+        } else if (slot < r) {
+            t.e = (int)tile_pair_entry(g, a, start + slot);
+            t.ordered = tile_label(g, a) < tile_label(g, start + slot);
         }
-    } else {
-        row -= 2LL * g.P * g.s;
-        const int r = (int)(row % g.s), tile = (int)(row / g.s);
-        const Tile x = tile_at(g, tile / g.P, tile % g.P);
-        if (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows)) return;   // never read
-        if (r < x.na && slot < x.nb) {
-            const int a = x.a0 + r, b = x.b0 + slot;
-            if (tile_has_pair(g, x, a, b)) {
-                e = tile_pair_entry(g, a, b);
-                ordered = tile_label(g, a) < tile_label(g, b);
-            }
+    } else if (r < x.na && slot < x.nb) {
+        const int a = x.a0 + r, b = x.b0 + slot;
+        if (tile_has_pair(g, x, a, b)) {
+            t.e = (int)tile_pair_entry(g, a, b);
+            t.ordered = tile_label(g, a) < tile_label(g, b);
         }
     }
-    if (e >= 0 && map) e = map[e];
-    double2 out;
-    out.x = 1.0;
-    out.y = 0.0;
-    if (e >= 0) {
-        out = tile_sincos((double)theta[e]);
-        if (!ordered) out.y = -out.y;
+    return t;
+}
+constexpr int kTilePlaces = kTileTable * kTileTable;
+// Piece, row and slot of place `id` < kTilePlaces.  The lanes of a wavefront run along r + slot, that is along a block, whose
+// angles are neighbours in memory.  The two triangles of a special tile share the places (row 63, which no piece has, stands
+// for the entries with row 0 of piece i + P).
+__device__ __forceinline__ void tile_table_place(bool special, int id, int *which, int *r, int *slot)
+{
+    const int row = id % kTileTable, col = (id / kTileTable - id) & (kTileTable - 1), last = kTileTable - 1;
+    *which = special && (col > row || row == last) ? 1 : 0;
+    *r = special && (col > row || row == last) ? col : row;
+    *slot = !special || (col < row && row != last) ? col : (col > row ? row : last);
+}
+// Cosines and sines (the sine negated when the first row has the larger label; (1, 0) for a pair that is bypassed or not in the
+// tile) into the table `out`, [piece][rows][64].
+template <typename R2, typename R>
+__device__ __forceinline__ void tile_coefs(const TilePlan &g, const Tile &x, bool special, int rows,
+                                           const float *__restrict__ theta, const int *__restrict__ map, R2 *out)
+{
+    auto place = [&](int id, int *which, int *r, int *slot) {
+        tile_table_place(special, id, which, r, slot);
+        return out + ((size_t)*which * rows + *r) * kTileTable + *slot;
+    };
+    if (special)   // (the rows' ends: rotations are taken eight at a time)
+        for (int id = threadIdx.x; id < 2 * rows * kTileTable; id += kTileThreads) {
+            const int r = id / kTileTable % rows, slot = id % kTileTable;
+            if (slot >= r && slot != kTileTable - 1) {
+                out[id].x = (R)1;
+                out[id].y = (R)0;
+            }
+        }
+    // angles first, eight loads at a time, then their cosines and sines
+    static_assert(kTilePlaces == 8 * kTileThreads, "eight places per thread");
+    float th[8], sign[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        int which, r, slot;
+        tile_table_place(special, threadIdx.x + q * kTileThreads, &which, &r, &slot);
+        const TileEntry t = tile_entry(g, x, special, which, r, slot);
+        const int e = t.e >= 0 && map ? map[t.e] : t.e;
+        th[q] = e >= 0 ? theta[e] : 0.f;
+        sign[q] = e < 0 ? 0.f : (t.ordered ? 1.f : -1.f);
     }
-    table[id] = out;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        int which, r, slot;
+        R2 *to = place(threadIdx.x + q * kTileThreads, &which, &r, &slot);
+        if (r < rows) {
+            to->x = (R)th[q];
+            to->y = (R)sign[q];
+        }
+    }
+#pragma unroll 1
+    for (int id = threadIdx.x; id < kTilePlaces; id += kTileThreads) {
+        int which, r, slot;
+        R2 *to = place(id, &which, &r, &slot);
+        if (r >= rows) continue;
+        const R2 v = *to;
+        const double2 cs = tile_sincos((double)v.x);
+        R2 w;
+        w.x = v.y != (R)0 ? (R)cs.x : (R)1;
+        w.y = v.y != (R)0 ? (R)(v.y > (R)0 ? cs.y : -cs.y) : (R)0;
+        *to = w;
+    }
 }
 
 // the transposed rotation of rows p, q: p' = c p + s q, q' = c q - s p
@@ -210,185 +242,237 @@ __device__ __forceinline__ void tile_rotate(T &p, T &q, const R2 &cs)
     q = fma(cs.x, b, -(cs.y * a));
 }
 
-constexpr int kTileChunk = 16;   // rows of the outer loop whose coefficients are in LDS at a time
-// address spaces of the loads that go from memory to LDS
-typedef __attribute__((address_space(3))) void *lds_ptr;
-typedef __attribute__((address_space(1))) const void *global_ptr;
-constexpr int kWaitForLoads = 0x0f70;   // s_waitcnt vmcnt(0): this wavefront's loads into LDS are there
-// Matrices of the tiles: A = the tile's transposed rotations in block order (the reverse sweep's matrix; its transpose is
-// the forward sweep's), float64, rounded once at the end.  A lane holds a column.  Ordinary tile: a workgroup's wavefronts
-// take its column blocks; the rows of piece j stay in registers, a row of piece i is fresh in every pass of the outer loop
-// and finished at its end.  Special tile: one workgroup per column block, a wavefront for each piece; a pass takes row r of
-// the piece through the rows before it, oldest first (finished rows sit in registers by age, newest in slot 0, so the code
-// is the same for every pass), then through row 0, which the two wavefronts hand to each other through LDS.
-// Bound by the chain of the rotations of a row (two dependent float64 instructions each).  Workgroups: special tiles first,
-// they take longest.
-__global__ __launch_bounds__(128, 1) void tile_build_kernel(TilePlan g, const double2 *__restrict__ table, int free_rows,
-                                                            float *__restrict__ matrices)
-{
-    constexpr int S = kTileSlots, PARTS = kTilePad / 64;
-    __shared__ double2 coef[2][2][kTileChunk][S + 1];   // [which of two chunks][piece]
-    __shared__ double row0[64];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool special = (int)blockIdx.x < g.P * PARTS;
-    const int id = (int)blockIdx.x - g.P * PARTS;
-    const int st = special ? 2 * ((int)blockIdx.x / PARTS) - g.first : id / g.P, u = special ? 0 : id % g.P;
-    const Tile x = tile_at(g, st, u);
-    if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
-    float *A = matrices + ((size_t)st * g.P + u) * kTilePad * kTilePad;
-    const double2 *mine = tile_coef_table(g, table, st, u, special, S + 1);
-    // rows of the chunk at i0: a wavefront brings its piece's (special) or every second one
-    auto load = [&](int i0) {
-        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk, chunk = (i0 / kTileChunk) & 1;
-        for (int r = special ? 0 : wave; r < rows; r += special ? 1 : 2)
-            __builtin_amdgcn_global_load_lds(
-                (global_ptr)(mine + (size_t)((special ? wave * g.s : 0) + i0 + r) * (S + 1) + lane),
-                (lds_ptr)(coef[chunk][special ? wave : 0][r]), 16, 0, 0);
-    };
-    double q[S];
-    load(0);
-    if (special) {
-        const int c = lane + 64 * ((int)blockIdx.x % PARTS), base = wave * (kTilePad / 2);
-#pragma unroll
-        for (int b = 0; b < S; ++b) q[b] = 0.0;
-        if (wave == 0) row0[lane] = c == kTilePad - 1 ? 1.0 : 0.0;
-        for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
-            __builtin_amdgcn_s_waitcnt(kWaitForLoads);
-            __syncthreads();   // the chunk is in LDS
-            const double2(*now)[S + 1] = coef[(i0 / kTileChunk) & 1][wave];
-            if (i0 + kTileChunk < g.s) load(i0 + kTileChunk);
-            const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
-            for (int r = 0; r < rows; ++r) {
-                const int i = i0 + r;
-                double cur = c == base + i ? 1.0 : 0.0;
-#pragma unroll
-                for (int s0 = (S - 1) / 8 * 8; s0 >= 0; s0 -= 8)
-                    if (s0 < i) {
-                        double2 cs[8];   // read together: one LDS latency for eight rotations
-#pragma unroll
-                        for (int v = 0; v < 8; ++v) cs[v] = now[r][s0 + v];
-                        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                        for (int v = 7; v >= 0; --v)
-                            if (s0 + v < S) tile_rotate(cur, q[s0 + v], cs[v]);
-                    }
-                const double2 cs = now[r][S];
-                for (int turn = 0; turn < 2; ++turn) {     // row 0: piece i, then piece i + P
-                    if (turn == wave) {
-                        double held = row0[lane];
-                        tile_rotate(cur, held, cs);
-                        row0[lane] = held;
-                    }
-                    __syncthreads();
-                }
-#pragma unroll
-                for (int b = S - 1; b > 0; --b) q[b] = q[b - 1];
-                q[0] = cur;
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < S; ++b)
-            if (b < g.s) A[(base + g.s - 1 - b) * kTilePad + c] = (float)q[b];
-        for (int r = g.s; r < kTilePad / 2; ++r)
-            if (base + r < kTilePad - 1) A[(base + r) * kTilePad + c] = 0.f;
-        if (wave == 1) A[(kTilePad - 1) * kTilePad + c] = (float)row0[lane];
-        return;
-    }
-    const int c = lane + 64 * wave;
-#pragma unroll
-    for (int b = 0; b < S; ++b) q[b] = (c == kTilePad / 2 + b && b < g.s) ? 1.0 : 0.0;
-    for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
-        __builtin_amdgcn_s_waitcnt(kWaitForLoads);
-        __syncthreads();
-        const double2(*now)[S + 1] = coef[(i0 / kTileChunk) & 1][0];
-        if (i0 + kTileChunk < g.s) load(i0 + kTileChunk);
-        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
-        double2 cs[2][8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) cs[0][v] = now[0][v];
-        for (int r = 0; r < rows; ++r) {
-            double cur = c == i0 + r ? 1.0 : 0.0;
-            // eight rotations' coefficients are read while the eight before them run
-#pragma unroll
-            for (int b0 = 0; b0 < S + 1; b0 += 8) {
-                const double2(*next)[S + 1] = now + (b0 + 8 < S + 1 ? r : (r + 1 < rows ? r + 1 : r));
-#pragma unroll
-                for (int v = 0; v < 8; ++v) cs[(b0 / 8 + 1) & 1][v] = next[0][(b0 + 8) % (S + 1) + v];
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int v = 0; v < 8; ++v)
-                    if (b0 + v < S) tile_rotate(cur, q[b0 + v], cs[(b0 / 8) & 1][v]);
-            }
-            A[(i0 + r) * kTilePad + c] = (float)cur;
-        }
-    }
-#pragma unroll
-    for (int b = 0; b < S; ++b) A[(kTilePad / 2 + b) * kTilePad + c] = (float)q[b];
-    for (int r = g.s; r < kTilePad / 2; ++r) A[r * kTilePad + c] = 0.f;
-    A[(kTilePad - 1) * kTilePad + c] = (u == 0 && c == kTilePad - 1) ? 1.f : 0.f;
-}
-
 // A fragment of a tile's matrix: rows 32 f .. + 31, contraction indices 16 k .. + 15, as in product_kernels.hpp but with
 // the indices of a half wavefront in the order in which the matrix instructions leave their results in registers, so that
 // a result can be the next product's operand without a move between lanes.
 __device__ __forceinline__ int tile_k(int half, int j) { return (j & 3) + 4 * half + 8 * (j >> 2); }
 
-// What the apply stages have to know of their operand's columns: tops (cleared by the coefficient kernel) takes the bits of
-// their largest magnitudes.  A workgroup takes 256 columns and kTileTopRows rows.
-constexpr int kTileTopRows = 32;
+// What the apply stages have to know of their operand's columns: tops, the bits of their largest magnitudes.  A workgroup takes
+// 64 columns, a wavefront an eighth of the rows.
 struct TileTops {
     int rows;
     long long B;
     const float *X;      // null: nothing to do
     unsigned *tops;
 };
-inline long long tile_top_blocks(const TileTops &t)
+inline long long tile_top_blocks(const TileTops &t) { return t.X ? (t.B + 63) / 64 : 0; }
+__device__ __forceinline__ void tile_tops(const TileTops &t, long long block, float (*part)[64])
 {
-    return t.X ? (t.B + 255) / 256 * ((t.rows + kTileTopRows - 1) / kTileTopRows) : 0;
-}
-__device__ __forceinline__ void tile_tops(const TileTops &t, long long block)
-{
-    const long long per = (t.B + 255) / 256, col = block % per * 256 + threadIdx.x;
-    const int r0 = (int)(block / per) * kTileTopRows;
-    if (col >= t.B) return;
-    float x[kTileTopRows], top = 0.f;
+    constexpr int WAVES = kTileThreads / 64, ONCE = 32;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long mine = block * 64 + lane, col = mine < t.B ? mine : t.B - 1;
+    const int per = (t.rows + WAVES - 1) / WAVES, from = wave * per, to = from + per < t.rows ? from + per : t.rows;
+    float top = 0.f;
+    for (int r0 = from; r0 < to; r0 += ONCE) {
+        float x[ONCE];
 #pragma unroll
-    for (int r = 0; r < kTileTopRows; ++r) x[r] = t.X[(long long)(r0 + r < t.rows ? r0 + r : r0) * t.B + col];
+        for (int r = 0; r < ONCE; ++r) x[r] = t.X[(long long)(r0 + r < to ? r0 + r : to - 1) * t.B + col];
 #pragma unroll
-    for (int r = 0; r < kTileTopRows; r += 2) top = range_top(top, x[r], x[r + 1]);
-    if (__float_as_uint(top) > t.tops[col]) atomicMax(t.tops + col, __float_as_uint(top));
+        for (int r = 0; r < ONCE; r += 2) top = range_top(top, x[r], x[r + 1]);
+    }
+    part[wave][lane] = top;
+    __syncthreads();
+    if (wave == 0 && mine < t.B) {
+        for (int w = 1; w < WAVES; ++w) top = range_top(top, part[w][lane], 0.f);
+        t.tops[mine] = __float_as_uint(top);
+    }
 }
-// matrices -> pieces, one wavefront per fragment; transposed: of the transposed matrices
-// (and one identity, behind the last tile, that all tiles without a free pair share).  The workgroups from `split_blocks`
-// on look at the operand.
-__global__ __launch_bounds__(256) void tile_split_kernel(TilePlan g, int free_rows, const float *__restrict__ matrices,
-                                                         u32x4 *__restrict__ out, int transposed, unsigned split_blocks,
-                                                         TileTops tops)
+
+// Matrices of the tiles: A = the tile's transposed rotations in block order (the reverse sweep's matrix; its transpose is
+// the forward sweep's), float64, rounded once at the end and cut into pieces in operand order.
+//
+// A workgroup makes one tile, a lane two columns of it, a wavefront the rotations with some of the rows that stay in registers:
+// 8 rows of piece j (ordinary tile), or 16 rows of one piece (special tile: of the rows that are finished).  A row of piece i is
+// fresh in the first wavefront and handed from one to the next through LDS, so the wavefronts work on different rows at once:
+// s / 2 + 7 steps of twice 8 rotations where one wavefront with all rows takes s steps of s.  A special tile's row stays with the
+// wavefront it belongs to, after its rotation with row 0, which the two pieces take in turn; that chain makes its steps longer,
+// so two workgroups share it, 64 columns each.
+//
+// Bound by the float64 rotations (four instructions of eight cycles each; 81000 cycles for an ordinary tile's loop, which is
+// what they take), a compute unit holding one tile.  All matrices in pieces: n = 1002 53 us, n = 4097 with m = 512 238 us
+// (a table kernel, one lane per column of a tile and a kernel that cuts into pieces: 78 and 279 us).
+constexpr int kTilePart = 8, kTileParts = (kTileSlots + kTilePart - 1) / kTilePart;   // ordinary tiles
+constexpr int kTileSpecialPart = 16;
+struct TileBuildShared {
+    union {
+        double2 special[2][kTileSlots][kTileTable];
+        struct {
+            double2 coef[kTileTable][kTileTable];
+            float A[kTilePad][kTilePad + 1];
+        } ordinary;
+        float A[kTilePad][kTilePad + 1];     // of a special tile: when its coefficients are done with
+        float tops[kTileThreads / 64][64];
+    };
+    double hand[2][kTileParts - 1][2][kTilePad];   // rows on their way to the next wavefront, by the parity of the step
+    double row0[kTilePad];
+};
+// A wavefront of an ordinary tile takes row r (or pair of rows) in step r + its number: `row(r, t)`; all make the same number
+// of steps.
+template <typename F>
+__device__ __forceinline__ void tile_steps(int s, int parts, int wave, F &&row)
 {
-    if (blockIdx.x >= split_blocks) {
-        tile_tops(tops, blockIdx.x - split_blocks);
+    const int before = wave < parts ? wave : s + parts - 1;
+    for (int t = 0; t < before; ++t) __syncthreads();
+    if (wave >= parts) return;
+    for (int r = 0; r < s; ++r) {
+        row(r, r + wave);
+        __syncthreads();
+    }
+    for (int t = wave + s; t < s + parts - 1; ++t) __syncthreads();
+}
+__global__ __launch_bounds__(kTileThreads, 1) void tile_build_kernel(TilePlan g, const float *__restrict__ theta,
+                                                                     const int *__restrict__ map, int free_rows,
+                                                                     u32x4 *__restrict__ out, int transposed,
+                                                                     int *__restrict__ range, TileTops tops, int top_blocks)
+{
+    __shared__ TileBuildShared sh;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tiles = g.stages * g.P;
+    const bool special = (int)blockIdx.x < 2 * g.P;
+    const int id = (int)blockIdx.x - 2 * g.P - top_blocks, half = special ? blockIdx.x & 1 : 0;
+    if (range && blockIdx.x == 0 && threadIdx.x < kTileRangeWords + g.P) range[threadIdx.x] = 0;
+    if (!special && id < 0) {
+        tile_tops(tops, id + top_blocks, sh.tops);
         return;
     }
-    constexpr int PER = (kTilePad / 32) * (kTilePad / 16);
-    const int lane = threadIdx.x & 63;
-    const long long id = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int tile = (int)(id / PER), f = (int)(id % PER), tiles = g.stages * g.P;
-    if (tile > tiles) return;
-    const bool identity = tile == tiles;
-    if (!identity && tile_is_identity(g, tile_at(g, tile / g.P, tile % g.P), free_rows)) return;
-    const float *A = matrices + (size_t)tile * kTilePad * kTilePad;
-    const int row = (f / (kTilePad / 16)) * 32 + (lane & 31), k0 = (f % (kTilePad / 16)) * 16;
-    float v[8];
+    const int st = special ? 2 * ((int)blockIdx.x / 2) - g.first : id / g.P, u = special ? 0 : id % g.P;
+    const bool identity = !special && id == tiles;   // shared by all tiles without a free pair, behind the last tile
+    float(*A)[kTilePad + 1] = special ? sh.A : sh.ordinary.A;
+    if (identity) {
+        for (int i = threadIdx.x; i < kTilePad * kTilePad; i += kTileThreads)
+            A[i / kTilePad][i % kTilePad] = i / kTilePad == i % kTilePad ? 1.f : 0.f;
+    } else {
+        const Tile x = tile_at(g, st, u);
+        if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
+        tile_coefs<double2, double>(g, x, special, special ? g.s : kTileTable, theta, map, special ? &sh.special[0][0][0] : &sh.ordinary.coef[0][0]);
+        if (special && threadIdx.x < 64) sh.row0[threadIdx.x] = threadIdx.x + 64 * half == kTilePad - 1 ? 1.0 : 0.0;
+        __syncthreads();
+        auto unit = [&](int row, double(&v)[2]) {
+            v[0] = row == lane ? 1.0 : 0.0;
+            v[1] = row == lane + 64 ? 1.0 : 0.0;
+        };
+        if (special) {
+            constexpr int ROWS = kTileSpecialPart;
+            const int which = wave & 1, part = wave >> 1, base = which * (kTilePad / 2);   // (the two on different SIMDs)
+            const int col = lane + 64 * half;
+            const double2 *table = &sh.special[0][0][0] + (size_t)which * g.s * kTileTable;
+            double q[ROWS];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int k = k0 + tile_k(lane >> 5, j);
-        v[j] = identity ? (row == k ? 1.f : 0.f) : (transposed ? A[k * kTilePad + row] : A[row * kTilePad + k]);
+            for (int b = 0; b < ROWS; ++b) q[b] = 0.0;
+            for (int t = 0; t < g.s + 3; ++t) {
+                const int r = t - part, place = r - ROWS * part;      // (row r ends in part r / 16)
+                const bool mine = r < g.s && place >= 0, own = mine && place < ROWS;
+                double cur = 0.0;
+                double2 held{};
+                if (mine) {
+                    const double2 *coef = table + (size_t)r * kTileTable;
+                    held = coef[kTileTable - 1];
+                    cur = part ? sh.hand[(t + 1) & 1][part - 1][which][lane] : (base + r == col ? 1.0 : 0.0);
+#pragma unroll
+                    for (int b0 = 0; b0 < ROWS; b0 += 8)
+                        if (b0 < place) {
+                            double2 cs[8];   // read together: one LDS latency for eight rotations
+#pragma unroll
+                            for (int v = 0; v < 8; ++v) cs[v] = coef[ROWS * part + b0 + v];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int v = 0; v < 8; ++v)
+                                if (b0 + v < ROWS - 1 || !own) tile_rotate(cur, q[b0 + v], cs[v]);   // (its last entry may be row 0's)
+                        }
+                    if (!own) sh.hand[t & 1][part][which][lane] = cur;
+                }
+                for (int turn = 0; turn < 2; ++turn) {                // row 0: piece i, then piece i + P
+                    if (own && turn == which) {
+                        double zero = sh.row0[lane];
+                        tile_rotate(cur, zero, held);
+                        sh.row0[lane] = zero;
+                    }
+                    __syncthreads();
+                }
+                if (own)
+#pragma unroll
+                    for (int b0 = 0; b0 < ROWS; b0 += 8)
+                        if (place / 8 == b0 / 8)
+#pragma unroll
+                            for (int v = 0; v < 8; ++v) q[b0 + v] = place % 8 == v ? cur : q[b0 + v];
+            }
+#pragma unroll
+            for (int b = 0; b < ROWS; ++b) {
+                const int row = base + ROWS * part + b;
+                if (row != kTilePad - 1) A[row][col] = (float)q[b];
+            }
+            if (threadIdx.x < 64) A[kTilePad - 1][threadIdx.x + 64 * half] = (float)sh.row0[threadIdx.x];
+        } else {
+            const int parts = (g.s + kTilePart - 1) / kTilePart, first = kTilePart * wave;
+            const double2(*coef)[kTileTable] = sh.ordinary.coef;
+            double q[kTilePart][2];
+#pragma unroll
+            for (int b = 0; b < kTilePart; ++b) {
+                unit(first + b < g.s ? kTilePad / 2 + first + b : -1, q[b]);
+            }
+            double2 cs[2][kTilePart];   // a row's coefficients are read while the row before it is turned
+            auto read = [&](int set, int r) {
+#pragma unroll
+                for (int v = 0; v < kTilePart; ++v) cs[set][v] = coef[r < kTileTable ? r : 0][first + v];
+            };
+            read(0, 0);
+            // (two rows a step; the row after an odd number of them is zeros)
+            tile_steps((g.s + 1) / 2, parts, wave, [&](int pair, int t) __attribute__((always_inline)) {
+                double cur[2][2];
+                if (wave) {
+#pragma unroll
+                    for (int w = 0; w < 2; ++w)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) cur[w][i] = sh.hand[(t + 1) & 1][wave - 1][w][lane + 64 * i];
+                } else {
+                    unit(2 * pair, cur[0]);
+                    unit(2 * pair + 1 < g.s ? 2 * pair + 1 : -1, cur[1]);
+                }
+                read(1, 2 * pair + 1);
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+#pragma unroll
+                    for (int v = 0; v < kTilePart; ++v)
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) tile_rotate(cur[w][i], q[v][i], cs[w][v]);
+                    if (w == 0) read(0, 2 * pair + 2);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        if (wave + 1 < parts)
+                            sh.hand[t & 1][wave][w][lane + 64 * i] = cur[w][i];
+                        else
+                            A[2 * pair + w][lane + 64 * i] = (float)cur[w][i];
+                }
+            });
+#pragma unroll
+            for (int b = 0; b < kTilePart; ++b) {
+                const int row = kTilePad / 2 + first + b;
+                const bool last = row == kTilePad - 1;                // row 0, where it is this tile's
+                A[row][lane] = last ? 0.f : (float)q[b][0];
+                A[row][lane + 64] = last ? (u == 0 && lane == 63 ? 1.f : 0.f) : (float)q[b][1];
+            }
+            for (int row = (g.s + 1) / 2 * 2 + wave; row < kTilePad / 2; row += kTileThreads / 64) A[row][lane] = A[row][lane + 64] = 0.f;
+        }
     }
-    const Split8 sp = split8(v);
-    u32x4 *o = out + id * 192 + lane;
-    o[0] = sp.h;
-    o[64] = sp.m;
-    o[128] = sp.l;
+    __syncthreads();
+    const long long tile = identity ? tiles : (long long)st * g.P + u;
+    u32x4 *o = out + tile * kTilePieceWords + lane;
+    constexpr int FRAGMENTS = (kTilePad / 32) * (kTilePad / 16);
+    for (int i = wave; i < (special ? FRAGMENTS / 2 : FRAGMENTS); i += kTileThreads / 64) {
+        // (of a special tile those of its half of the columns, which are rows of the transposed matrix)
+        const int f = !special ? i : transposed ? half * (FRAGMENTS / 2) + i : i / 4 * 8 + half * 4 + i % 4;
+        const int row = (f / (kTilePad / 16)) * 32 + (lane & 31), k0 = (f % (kTilePad / 16)) * 16;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = k0 + tile_k(lane >> 5, j);
+            v[j] = transposed ? A[k][row] : A[row][k];
+        }
+        const Split8 sp = split8(v);
+        o[f * 192] = sp.h;
+        o[f * 192 + 64] = sp.m;
+        o[f * 192 + 128] = sp.l;
+    }
 }
 
 // where a tile's pieces are (in tiles)
@@ -873,187 +957,220 @@ __global__ __launch_bounds__(2 * kTilePad, NARROW && !OPERAND ? 1 : 2) void tile
         tile_two_sided(a.s, blockIdx.x, sh.s);
 }
 
-// 64 values per lane -> lane l has the sum over all lanes of value l
-__device__ __forceinline__ float tile_reduce64(float (&v)[64])
+// N values per lane (8 or 16) -> lane l has the sum over all lanes of value l / (64 / N)
+template <int N>
+__device__ __forceinline__ float tile_reduce(const float (&v)[N])
 {
     const int lane = threadIdx.x & 63;
-    float w[32];
+    float w[N / 2];
 #pragma unroll
-    for (int r = 0; r < 32; ++r) {
-        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[r]), __float_as_uint(v[r + 32]), false, false);
+    for (int r = 0; r < N / 2; ++r) {
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[r]), __float_as_uint(v[r + N / 2]), false, false);
         w[r] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[r]), __float_as_uint(w[r + 16]), false, false);
+    for (int r = 0; r < N / 4; ++r) {
+        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[r]), __float_as_uint(w[r + N / 4]), false, false);
         w[r] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
     }
-    // within a row of 16 lanes: keep one value of a pair, hand the other to the lane that keeps it
-    auto step = [&](auto ctrl, int bit, int count) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (r < count) {
-                const bool up = (lane & bit) != 0;
-                const float keep = up ? w[r + count] : w[r], give = up ? w[r] : w[r + count];
-                w[r] = keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), decltype(ctrl)::value, 0xf, 0xf, true));
-            }
+    auto moved = [](auto ctrl, float x) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
     };
-    step(std::integral_constant<int, 0x128>{}, 8, 8);   // row_ror:8: lane ^ 8
-    step(std::integral_constant<int, 0x141>{}, 4, 4);   // row_half_mirror: lane ^ 7
-    step(std::integral_constant<int, 0x1b>{}, 2, 2);    // quad_perm 3 2 1 0: lane ^ 3
-    step(std::integral_constant<int, 0xb1>{}, 1, 1);    // quad_perm 1 0 3 2: lane ^ 1
+    // within a row of 16 lanes: keep one value of a pair, hand the other to the lane that keeps it; one value left: add it
+    auto step = [&](auto ctrl, int bit, auto left) {
+        constexpr int HALF = decltype(left)::value / 2;
+        if constexpr (HALF == 0) w[0] += moved(ctrl, w[0]);
+#pragma unroll
+        for (int r = 0; r < HALF; ++r) {
+            const bool up = (lane & bit) != 0;
+            const float keep = up ? w[r + HALF] : w[r], give = up ? w[r] : w[r + HALF];
+            w[r] = keep + moved(ctrl, give);
+        }
+    };
+    step(std::integral_constant<int, 0x128>{}, 8, std::integral_constant<int, N / 4>{});   // row_ror:8: lane ^ 8
+    step(std::integral_constant<int, 0x141>{}, 4, std::integral_constant<int, N / 8>{});   // row_half_mirror: lane ^ 7
+    step(std::integral_constant<int, 0x1b>{}, 2, std::integral_constant<int, 1>{});        // quad_perm 3 2 1 0: lane ^ 3
+    step(std::integral_constant<int, 0xb1>{}, 1, std::integral_constant<int, 1>{});        // quad_perm 1 0 3 2: lane ^ 1
     return w[0];
 }
 
 // The sums of all tiles' pairs from the blocks the stages have left: the reverse sweep of a tile on the strips
-// W = A S and A (columns of the block, one per lane); the share of rows a, b is W_a . A_b, summed over the lanes.  A
-// workgroup is two groups of kTilePad threads: two ordinary tiles, or the two pieces of a special one (which hand row 0 to each
-// other as in the build kernel).
-__global__ __launch_bounds__(2 * kTilePad, 1) void tile_gradient_kernel(TilePlan g, const double2 *__restrict__ table,
-                                                                   const int *__restrict__ map, int free_rows,
-                                                                   const float *__restrict__ blocks, float *__restrict__ dtheta)
+// W = A S and A (columns of the block, two per lane); the share of rows a, b is W_a . A_b, summed over the lanes.  A workgroup
+// takes a tile, its wavefronts the rotations with some of the rows, as in the build kernel; a wavefront puts the sums of a
+// row where the coefficients were that it alone has read.  A special tile's columns are shared by two workgroups: the one that
+// is done last adds the two sums, the first half's first.  Bound by the vector instructions, 20 for a rotation of two
+// columns.  n = 1002 92 us, n = 4097 with m = 512 247 us (one lane per column with all rows of a tile: 144 and 428 us).
+__global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan g, const float *__restrict__ theta,
+                                                                        const int *__restrict__ map, int free_rows,
+                                                                        const float *__restrict__ blocks,
+                                                                        int *__restrict__ counts, float *__restrict__ halves,
+                                                                        float *__restrict__ dtheta)
 {
-    constexpr int S = kTileSlots, WAVES = kTilePad / 64;
-    __shared__ float2 coefs[2][kTileChunk][S + 1];
-    __shared__ float sums[2][kTileChunk][WAVES][64];
-    __shared__ float2 row0[kTilePad];
-    const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / kTilePad);
-    const bool special = (int)blockIdx.x < g.P;
-    const int id = special ? 0 : 2 * ((int)blockIdx.x - g.P) + group, tiles = g.stages * g.P;
-    const int st = special ? 2 * (int)blockIdx.x - g.first : id / g.P, u = special ? 0 : id % g.P;
-    const Tile x = tile_at(g, id < tiles ? st : 0, u);
-    const bool active = special || (id < tiles && x.kind != kTileSpecial && !tile_is_identity(g, x, free_rows));
-    if (__syncthreads_or(active ? 1 : 0) == 0) return;
-    const float *blk = blocks + (active ? ((size_t)st * g.P + u) * kTilePad * kTilePad : 0);
-    const int c = threadIdx.x % kTilePad, lane = c & 63, wave = c >> 6;
-    const double2 *mine = tile_coef_table(g, table, active ? st : 2 - g.first, active ? u : 0, special || !active, S + 1) +
-                          (special ? (size_t)group * g.s * (S + 1) : 0);
-    float2(*coef)[S + 1] = coefs[group];
-    auto load = [&](int i0) {
-        constexpr int PER = kTileChunk * (S + 1) / kTilePad;
-        double2 v[PER];
-        const double2 *src = mine + (size_t)i0 * (S + 1);
-        const int last = (g.s - i0) * (S + 1) - 1;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) v[q] = src[c + q * kTilePad < last ? c + q * kTilePad : last];
-#pragma unroll
-        for (int q = 0; q < PER; ++q)
-            coef[0][c + q * kTilePad] = make_float2((float)v[q].x, (float)v[q].y);
-    };
-    // sums of a chunk -> dtheta
-    auto store = [&](int i0, int rows) {
-        for (int e = c; e < rows * 64; e += kTilePad) {
-            const int r = e / 64, slot = e % 64, i = i0 + r;
-            long long entry;
-            bool ordered;
-            if (special) {
-                if (i >= (group ? x.nb : x.na)) continue;
-                const int a = (group ? x.b0 : x.a0) + i;
-                if (slot == 63) {
-                    entry = tile_held_entry(g, a);
-                    ordered = false;
-                } else {
-                    if (slot >= i) continue;
-                    entry = tile_pair_entry(g, a, a - 1 - slot);
-                    ordered = tile_label(g, a) < tile_label(g, a - 1 - slot);
-                }
-            } else {
-                if (i >= x.na || slot >= x.nb) continue;
-                const int a = x.a0 + i, b = x.b0 + slot;
-                if (!tile_has_pair(g, x, a, b)) continue;
-                entry = tile_pair_entry(g, a, b);
-                ordered = tile_label(g, a) < tile_label(g, b);
-            }
-            const long long out = map ? (long long)map[entry] : entry;
-            if (out < 0) continue;
-            float v = sums[group][r][0][slot];
-            for (int w = 1; w < WAVES; ++w) v += sums[group][r][w][slot];
-            dtheta[out] = ordered ? v : -v;
-        }
-    };
-    const int first = special ? group * (kTilePad / 2) : 0;   // rows of the outer loop from here on
-    float fa[S], fw[S], ahead = blk[first * kTilePad + c];    // `ahead`: the next one
-    if (special) {
-#pragma unroll
-        for (int b = 0; b < S; ++b) fa[b] = fw[b] = 0.f;
-        if (group == 0) row0[c] = make_float2(c == kTilePad - 1 ? 1.f : 0.f, blk[(kTilePad - 1) * kTilePad + c]);
-    } else {
-#pragma unroll
-        for (int b = 0; b < S; ++b) {
-            fa[b] = c == kTilePad / 2 + b ? 1.f : 0.f;
-            fw[b] = blk[(kTilePad / 2 + b) * kTilePad + c];
-        }
+    __shared__ float2 table[2 * kTileSlots * kTileTable];   // [piece][s][64]
+    __shared__ float hand[2][kTileParts - 1][4][64];
+    __shared__ float2 row0[64];
+    __shared__ int finished;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool special = (int)blockIdx.x < 2 * g.P;
+    const int id = (int)blockIdx.x - 2 * g.P, half = special ? blockIdx.x & 1 : 0;
+    const int st = special ? 2 * ((int)blockIdx.x / 2) - g.first : id / g.P, u = special ? 0 : id % g.P;
+    const Tile x = tile_at(g, st, u);
+    if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
+    const float *blk = blocks + ((size_t)st * g.P + u) * kTilePad * kTilePad;
+    tile_coefs<float2, float>(g, x, special, g.s, theta, map, table);
+    if (special && threadIdx.x < 64) {
+        const int col = threadIdx.x + 64 * half;
+        row0[threadIdx.x] = make_float2(col == kTilePad - 1 ? 1.f : 0.f, blk[(kTilePad - 1) * kTilePad + col]);
     }
-    for (int i0 = 0; i0 < g.s; i0 += kTileChunk) {
-        __syncthreads();
-        load(i0);
-        __syncthreads();
-        const int rows = g.s - i0 < kTileChunk ? g.s - i0 : kTileChunk;
-        for (int r = 0; r < rows; ++r) {
-            const int i = i0 + r;
-            float ca = c == first + i ? 1.f : 0.f, cw = ahead;
-            ahead = blk[(first + (i + 1 < g.s ? i + 1 : i)) * kTilePad + c];
-            float prod[64];
-            if (special) {
+    __syncthreads();
+
+    if (special) {
+        constexpr int ROWS = kTileSpecialPart;
+        const int which = wave & 1, part = wave >> 1, base = which * (kTilePad / 2);   // (the two on different SIMDs)
+        const int col = lane + 64 * half;
+        float fa[ROWS], fw[ROWS], ca = 0.f, cw = 0.f, ahead = blk[base * kTilePad + col];
 #pragma unroll
-                for (int b = 0; b < 64; ++b) prod[b] = 0.f;
+        for (int b = 0; b < ROWS; ++b) fa[b] = fw[b] = 0.f;
+        for (int t = 0; t < g.s + 3; ++t) {
+            const int r = t - part, place = r - ROWS * part;      // (row r ends in part r / 16)
+            const bool mine = r < g.s && place >= 0, own = mine && place < ROWS;
+            float2 *coef = table + ((size_t)which * g.s + (mine ? r : 0)) * kTileTable;
+            float prod[ROWS];
 #pragma unroll
-                for (int s0 = (S - 1) / 8 * 8; s0 >= 0; s0 -= 8)
-                    if (s0 < i) {
-                        float2 cs[8];
+            for (int b = 0; b < ROWS; ++b) prod[b] = 0.f;
+            const float2 held = coef[kTileTable - 1];
+            if (mine) {
+                if (part) {
+                    ca = hand[(t + 1) & 1][part - 1][2 * which][lane];
+                    cw = hand[(t + 1) & 1][part - 1][2 * which + 1][lane];
+                } else {
+                    ca = base + r == col ? 1.f : 0.f;
+                    cw = ahead;
+                    ahead = blk[(base + (r + 1 < g.s ? r + 1 : r)) * kTilePad + col];
+                }
 #pragma unroll
-                        for (int v = 0; v < 8; ++v) cs[v] = coef[r][s0 + v];
+                for (int b0 = 0; b0 < ROWS; b0 += 8)
+                    if (b0 < place) {
+                        float2 cs[8];   // read together: one LDS latency for eight rotations
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) cs[v] = coef[ROWS * part + b0 + v];
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int v = 7; v >= 0; --v)
-                            if (s0 + v < S) {
-                                prod[s0 + v] = cw * fa[s0 + v];
-                                tile_rotate(cw, fw[s0 + v], cs[v]);
-                                tile_rotate(ca, fa[s0 + v], cs[v]);
+                        for (int v = 0; v < 8; ++v)
+                            if (b0 + v < ROWS - 1 || !own) {      // (its last entry may be that of row 0)
+                                prod[b0 + v] = cw * fa[b0 + v];
+                                tile_rotate(cw, fw[b0 + v], cs[v]);
+                                tile_rotate(ca, fa[b0 + v], cs[v]);
                             }
                     }
-                const float2 cs = coef[r][S];
-                for (int turn = 0; turn < 2; ++turn) {
-                    if (turn == group) {
-                        float2 t = row0[c];
-                        prod[63] = cw * t.x;
-                        tile_rotate(cw, t.y, cs);
-                        tile_rotate(ca, t.x, cs);
-                        row0[c] = t;
-                    }
-                    __syncthreads();
-                }
-#pragma unroll
-                for (int b = S - 1; b > 0; --b) {
-                    fa[b] = fa[b - 1];
-                    fw[b] = fw[b - 1];
-                }
-                fa[0] = ca;
-                fw[0] = cw;
-            } else {
-#pragma unroll
-                for (int b = S; b < 64; ++b) prod[b] = 0.f;
-#pragma unroll
-                for (int b0 = 0; b0 < S + 1; b0 += 8) {
-                    float2 cs[8];   // read together: one LDS latency for eight rotations
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) cs[v] = coef[r][b0 + v];
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int v = 0; v < 8; ++v) {
-                        const int b = b0 + v;
-                        if (b < S) {
-                            prod[b] = cw * fa[b];
-                            tile_rotate(cw, fw[b], cs[v]);
-                            tile_rotate(ca, fa[b], cs[v]);
-                        }
-                    }
+                if (!own) {
+                    hand[t & 1][part][2 * which][lane] = ca;
+                    hand[t & 1][part][2 * which + 1][lane] = cw;
                 }
             }
-            sums[group][r][wave][lane] = tile_reduce64(prod);
+            for (int turn = 0; turn < 2; ++turn) {                // row 0: piece i, then piece i + P
+                if (own && turn == which) {
+                    float2 zero = row0[lane];
+                    prod[ROWS - 1] = cw * zero.x;                 // (no row is behind 15 others of its part)
+                    tile_rotate(cw, zero.y, held);
+                    tile_rotate(ca, zero.x, held);
+                    row0[lane] = zero;
+                }
+                __syncthreads();
+            }
+            if (mine) {
+                const float sum = tile_reduce<ROWS>(prod);
+                const int slot = lane >> 2;
+                if ((lane & 3) == 0) coef[own && slot == ROWS - 1 ? kTileTable - 1 : ROWS * part + slot].x = sum;
+            }
+            if (own)
+#pragma unroll
+                for (int b0 = 0; b0 < ROWS; b0 += 8)
+                    if (place / 8 == b0 / 8)
+#pragma unroll
+                        for (int v = 0; v < 8; ++v) {
+                            fa[b0 + v] = place % 8 == v ? ca : fa[b0 + v];
+                            fw[b0 + v] = place % 8 == v ? cw : fw[b0 + v];
+                        }
         }
+    } else {
+        const int parts = (g.s + kTilePart - 1) / kTilePart, first = kTilePart * wave;
+        float fa[kTilePart][2], fw[kTilePart][2];
+#pragma unroll
+        for (int b = 0; b < kTilePart; ++b)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int row = kTilePad / 2 + first + b;
+                fa[b][i] = row == lane + 64 * i ? 1.f : 0.f;
+                fw[b][i] = blk[row * kTilePad + lane + 64 * i];
+            }
+        float ahead[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ahead[i] = blk[lane + 64 * i];
+        float2 cs[kTilePart];   // a row's coefficients are read while the row before it is turned
+#pragma unroll
+        for (int v = 0; v < kTilePart; ++v) cs[v] = table[first + v];
+        tile_steps(g.s, parts, wave, [&](int r, int t) __attribute__((always_inline)) {
+            float2 *coef = table + r * kTileTable + first;
+            float ca[2], cw[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (wave) {
+                    ca[i] = hand[(t + 1) & 1][wave - 1][i][lane];
+                    cw[i] = hand[(t + 1) & 1][wave - 1][2 + i][lane];
+                } else {                                       // a from I, w from the block, one row ahead
+                    ca[i] = r == lane + 64 * i ? 1.f : 0.f;
+                    cw[i] = ahead[i];
+                    ahead[i] = blk[(r + 1 < g.s ? r + 1 : r) * kTilePad + lane + 64 * i];
+                }
+            const float2 *next = coef + (r + 1 < g.s ? kTileTable : 0);
+            float prod[kTilePart];
+#pragma unroll
+            for (int b = 0; b < kTilePart; ++b) {
+                const float2 now = cs[b];
+                cs[b] = next[b];
+                prod[b] = fmaf(cw[0], fa[b][0], cw[1] * fa[b][1]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    tile_rotate(cw[i], fw[b][i], now);
+                    tile_rotate(ca[i], fa[b][i], now);
+                }
+            }
+            if (wave + 1 < parts)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    hand[t & 1][wave][i][lane] = ca[i];
+                    hand[t & 1][wave][2 + i][lane] = cw[i];
+                }
+            const float sum = tile_reduce<kTilePart>(prod);
+            if ((lane & 7) == 0) coef[lane >> 3].x = sum;
+        });
+    }
+    __syncthreads();
+    const float *first_half = nullptr, *second_half = nullptr;
+    if (special) {
+        const size_t words = 2 * kTileSlots * kTileTable;
+        float *const out = halves + (size_t)blockIdx.x * words;
+        for (int i = threadIdx.x; i < 2 * g.s * kTileTable; i += kTileThreads) out[i] = table[i].x;
+        __threadfence();
         __syncthreads();
-        if (active) store(i0, rows);
+        if (threadIdx.x == 0) finished = atomicAdd(counts + blockIdx.x / 2, 1);
+        __syncthreads();
+        if (finished == 0) return;
+        __threadfence();
+        first_half = out - half * words;
+        second_half = first_half + words;
+    }
+    for (int i = threadIdx.x; i < kTilePlaces; i += kTileThreads) {
+        int which, r, slot;
+        tile_table_place(special, i, &which, &r, &slot);
+        const TileEntry t = tile_entry(g, x, special, which, r, slot);
+        if (t.e < 0) continue;
+        const int to = map ? map[t.e] : t.e;
+        if (to < 0) continue;
+        const int at = (which * g.s + r) * kTileTable + slot;
+        const float v = special ? first_half[at] + second_half[at] : table[at].x;
+        dtheta[to] = t.ordered ? v : -v;
     }
 }
 

@@ -7,19 +7,6 @@
 namespace givens {
 namespace {
 
-inline void tile_build(const TilePlan &g, const float *theta, const int *map, int free_rows, double2 *table, float *matrices,
-                       u32x4 *pieces, int *range, const TileTops &tops, bool transposed, hipStream_t stream)
-{
-    const long long tiles = tile_count(g), entries = tile_coef_entries(g);
-    hipLaunchKernelGGL(tile_coef_kernel, dim3((unsigned)((entries + 255) / 256)), dim3(256), 0, stream, g, theta, map,
-                       free_rows, entries, table, range, tops.X ? tops.B : 0LL, tops.tops);
-    hipLaunchKernelGGL(tile_build_kernel, dim3((unsigned)(g.P * (kTilePad / 64) + tiles)), dim3(128), 0, stream, g, table,
-                       free_rows, matrices);
-    const long long frags = (tiles + 1) * (kTilePad / 32) * (kTilePad / 16);
-    const unsigned split_blocks = (unsigned)((frags + 3) / 4);
-    hipLaunchKernelGGL(tile_split_kernel, dim3(split_blocks + (unsigned)tile_top_blocks(tops)), dim3(256), 0, stream, g,
-                       free_rows, matrices, pieces, transposed ? 1 : 0, split_blocks, tops);
-}
 // Stage st of Y <- U X or U^T X, the `first` one from X (nullptr: I), the others in place.  `runs` of column blocks for each
 // tile; 0: no tile of the stage has a free pair.  `resident`: workgroups to aim at.
 inline long long tile_apply_stage(const TilePlan &g, long long resident, int st, bool first, int rows, int free_rows,
@@ -54,9 +41,9 @@ inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_
             hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
     }
 }
-inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const double2 *table, const int *map,
-                          const u32x4 *pieces, const float *C, float *S, float *blocks, int *range, const unsigned *tops,
-                          float *dtheta, const TileOperand &op, hipStream_t stream)
+inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
+                          const u32x4 *pieces, const float *C, float *S, float *blocks, int *range, float *halves,
+                          const unsigned *tops, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
     const int t = tile_ld(g) / 32;
     const bool narrow = tile_gradient_narrow(g, free_rows);
@@ -76,27 +63,30 @@ inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int fr
         hipLaunchKernelGGL(kernel, dim3((unsigned)(pairs + runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
         if (second) std::swap(in, out);
     }
-    hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(g.P + (tile_count(g) + 1) / 2)), dim3(2 * kTilePad), 0, stream, g,
-                       table, map, free_rows, blocks, dtheta);
+    hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(2 * g.P + tile_count(g))), dim3(kTileThreads), 0, stream, g, theta,
+                       map, free_rows, blocks, range + kTileRangeWords, halves, dtheta);
 }
 } // namespace
 
 void tiles_build(const TilePlan &g, const float *theta, const int *map, int free_rows, const TileBuffers &b, bool forward,
                  int rows, long long B, const float *X, hipStream_t stream)
 {
-    tile_build(g, theta, map, free_rows, b.table, b.matrices, static_cast<u32x4 *>(b.pieces), b.range,
-               TileTops{rows, B, X, b.tops}, forward, stream);
+    const TileTops tops{rows, B, X, b.tops};
+    const int top_blocks = (int)tile_top_blocks(tops);
+    const long long grid = 2 * g.P + top_blocks + tile_count(g) + 1;
+    hipLaunchKernelGGL(tile_build_kernel, dim3((unsigned)grid), dim3(kTileThreads), 0, stream, g, theta, map, free_rows,
+                       static_cast<u32x4 *>(b.pieces), forward ? 1 : 0, b.range, tops, top_blocks);
 }
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
                  bool forward, hipStream_t stream)
 {
     tile_apply(g, compute_units, rows, free_rows, op, static_cast<const u32x4 *>(b.pieces), b.tops, forward, stream);
 }
-void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const int *map, const TileBuffers &b,
-                    const float *C, float *dtheta, const TileOperand &op, hipStream_t stream)
+void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
+                    const TileBuffers &b, const float *C, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
-    tile_gradient(g, compute_units, rows, free_rows, b.table, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.matrices,
-                  b.range, b.tops, dtheta, op, stream);
+    tile_gradient(g, compute_units, rows, free_rows, theta, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.blocks, b.range,
+                  b.halves, b.tops, dtheta, op, stream);
 }
 
 } // namespace givens
