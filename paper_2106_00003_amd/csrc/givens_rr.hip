@@ -1043,11 +1043,11 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     }
     {
         Span span(3, stream);
-        gram_matrix(pb.rows, B, plan, Y, G, C, stream);
+        gram_slices(pb.rows, B, plan, Y, G, C, stream);
     }
     {
         Span span(2, stream);
-        tiles_gradient(g, cus, pb.rows, pb.m, theta, pb.map, b, C, dtheta, op, stream);
+        tiles_gradient(g, cus, pb.rows, pb.m, theta, pb.map, b, C, plan.slices, dtheta, op, stream);
         GIVENS_HIP(hipGetLastError());
     }
     t_state.last_kernel = GIVENS_KERNEL_TILES;

@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -67,17 +68,17 @@ struct ProductArgs {
 
 // D = A X.  MW x NW wavefronts of (32 MF) x (32 NF) results each.
 //
-// The fragments of A go from memory to registers, one ahead of their use: wavefronts that differ in their rows read
+// The fragments of A go from memory to registers, 2 DEPTH - 1 ahead of their use: wavefronts that differ in their rows read
 // different ones, and where a workgroup's rows are all its own (NW = 1) each is read once.  X is shared: per step of 32
 // rows a thread brings octets (8 rows of one column, so that a lane's 8 values are consecutive along the contraction;
-// consecutive lanes take consecutive columns, hence whole cache lines and no alignment to care for) into registers a
-// step ahead, cuts them into pieces and writes them to the LDS buffer of the step's parity; lanes write and read 16
+// consecutive lanes take consecutive columns, hence whole cache lines and no alignment to care for) into registers DEPTH
+// steps ahead, cuts them into pieces and writes them to the LDS buffer of the step's parity; lanes write and read 16
 // consecutive bytes, without bank conflicts.  One barrier per step.
 //
 // Bound by the matrix cores.  256 x 128 per workgroup, four wavefronts of 64 x 128 (128 accumulator registers), two
 // workgroups per compute unit: n = 2048, B = 65536 in 2.76 ms = 199 TFLOP/s of float32 product (1190 of bf16; the
 // float32 matrix instructions reach about 129), 128 x 128 3.03 ms; n = B = 4096 0.69 ms against 0.83.
-template <int MW, int NW, int MF, int NF, bool CPLX>
+template <int MW, int NW, int MF, int NF, int DEPTH, bool CPLX>
 __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 {
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW;
@@ -99,8 +100,8 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     // columns: the octet is the same for all lanes)
     const int my_col = (int)threadIdx.x % BN, my_oct = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BN);
     long long col_in = n0 + my_col < a.B ? n0 + my_col : a.B - 1;  // past the end: its results are not stored
-    float xr[OCT][8];
-    auto fetch = [&](int k0) {
+    float xr[DEPTH][OCT][8];
+    auto fetch = [&](int set, int k0) {
 #pragma unroll
         for (int i = 0; i < OCT; ++i)
 #pragma unroll
@@ -110,24 +111,24 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
                 if constexpr (CPLX) {
                     const bool turned = r >= a.k / 2;
                     const float v = (a.X + (long long)(turned ? r - a.k / 2 : r) * a.ldx)[turned ? col_in ^ 1 : col_in];
-                    xr[i][j] = turned && !(my_col & 1) ? -v : v;
+                    xr[set][i][j] = turned && !(my_col & 1) ? -v : v;
                 } else {
-                    xr[i][j] = (a.X + (long long)r * a.ldx)[col_in];
+                    xr[set][i][j] = (a.X + (long long)r * a.ldx)[col_in];
                 }
             }
     };
     float top = 0.f, scale = 1.f;
     // SCALED: the second run, of columns out of the middle range
-    auto stash = [&](auto scaled, int buf) {
+    auto stash = [&](auto scaled, int set, int buf) {
 #pragma unroll
         for (int i = 0; i < OCT; ++i) {
             if constexpr (scaled()) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) xr[i][j] *= scale;
+                for (int j = 0; j < 8; ++j) xr[set][i][j] *= scale;
             } else {
-                top = range_top(top, xr[i]);
+                top = range_top(top, xr[set][i]);
             }
-            const Split8 s = split8(xr[i]);
+            const Split8 s = split8(xr[set][i]);
             const int o = my_oct + PER_ROW * i;
             panel[buf][o][0][my_col] = s.h;
             panel[buf][o][1][my_col] = s.m;
@@ -141,12 +142,14 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
 #pragma unroll
     for (int i = 0; i < MF; ++i)
         ap[i] = a.A + (long long)(mb * (BM / 32) + wm * MF + i) * k16s * 192 + lane;
-    u32x4 fa[2][MF][3];
+    constexpr int SETS = 2 * DEPTH;
+    u32x4 fa[SETS][MF][3];
     auto load_a = [&](int set, int k16) {
+        const long long at = (long long)(k16 < k16s ? k16 : k16s - 1) * 192;
 #pragma unroll
         for (int i = 0; i < MF; ++i)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) fa[set][i][p] = ap[i][(long long)k16 * 192 + 64 * p];
+            for (int p = 0; p < 3; ++p) fa[set][i][p] = ap[i][at + 64 * p];
     };
 
     // results in JB groups of columns, a group's operands at a time in registers
@@ -159,31 +162,36 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
             for (int j = 0; j < NF; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[j / (NF / JB)][i][j % (NF / JB)][v] = 0.f;
-        fetch(0);
-        load_a(0, 0);
-        stash(scaled, 0);
-        for (int step = 0; step < steps; ++step) {
-            const int buf = step & 1;
-            __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
-            if (step + 1 < steps) fetch((step + 1) * kProductStep);
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const int next = 2 * step + ks + 1;
-                load_a(ks ^ 1, next < k16s ? next : k16s - 1);
+        for (int d = 0; d < DEPTH; ++d)
+            if (d == 0 || d < steps) fetch(d, d * kProductStep);
 #pragma unroll
-                for (int j = 0; j < JB; ++j) {
-                    u32x4 fb[NF / JB][3];
+        for (int d = 0; d < SETS - 1; ++d) load_a(d, d);
+        stash(scaled, 0, 0);
+        for (int step0 = 0; step0 < steps; step0 += DEPTH)
 #pragma unroll
-                    for (int q = 0; q < NF / JB; ++q)
+            for (int d = 0; d < DEPTH; ++d) {
+                const int step = step0 + d, buf = step & 1;
+                if (d > 0 && step >= steps) break;
+                __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
+                if (step + DEPTH < steps) fetch(d, (step + DEPTH) * kProductStep);
 #pragma unroll
-                        for (int p = 0; p < 3; ++p)
-                            fb[q][p] =
-                                panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * (j * (NF / JB) + q) + (lane & 31)];
-                    mfma_split(fa[ks], fb, acc[j]);
+                for (int ks = 0; ks < 2; ++ks) {
+                    load_a((2 * d + ks + SETS - 1) % SETS, 2 * step + ks + SETS - 1);
+#pragma unroll
+                    for (int j = 0; j < JB; ++j) {
+                        u32x4 fb[NF / JB][3];
+#pragma unroll
+                        for (int q = 0; q < NF / JB; ++q)
+#pragma unroll
+                            for (int p = 0; p < 3; ++p)
+                                fb[q][p] =
+                                    panel[buf][2 * ks + (lane >> 5)][p][wn * 32 * NF + 32 * (j * (NF / JB) + q) + (lane & 31)];
+                        mfma_split(fa[2 * d + ks], fb, acc[j]);
+                    }
                 }
+                if (step + 1 < steps) stash(scaled, (d + 1) % DEPTH, buf ^ 1);
             }
-            if (step + 1 < steps) stash(scaled, buf ^ 1);
-        }
     };
     run(std::false_type{});
 
@@ -325,24 +333,48 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(Pr
     product_narrow<CPLX>(a, sh);
 }
 
-template <int MW, int NW, int MF, int NF>
+// DEPTH: of real operands whose contraction is long enough; complex ones have no registers to spare for more than one step
+// (n = 1024, B = 4096 440 us with two, 235 with one), and two steps are all there is for n = 64 (11.0 against 9.5 us).
+constexpr int kProductDeepK = 256;
+template <int MW, int NW, int MF, int NF, int DEPTH>
 inline void launch_product(ProductArgs a, hipStream_t stream)
 {
     constexpr int BM = 32 * MF * MW, BN = 32 * NF * NW;
     a.mblocks = (a.m + BM - 1) / BM;
     const long long nblocks = (a.B + BN - 1) / BN;
-    const unsigned grid = (unsigned)((nblocks + 7) / 8 * 8 * a.mblocks);
+    const dim3 grid((unsigned)((nblocks + 7) / 8 * 8 * a.mblocks)), block(64 * MW * NW);
     if (a.cplx)
-        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, true>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, 1, true>), grid, block, 0, stream, a);
+    else if (DEPTH == 1 || a.k < kProductDeepK)
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, 1, false>), grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, false>), dim3(grid), dim3(64 * MW * NW), 0, stream, a);
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, DEPTH, false>), grid, block, 0, stream, a);
+}
+
+// Time in us of a launch of a tiled product or contraction, from what its workgroups take per step of the contraction where the
+// chip is full of them (`full`, with `slots` per compute unit) and where a compute unit has one (`alone`), and `ends` for a
+// round's first loads and last stores.  The last round is as long as it is filled.
+struct TileCost {
+    int bm, bn, slots;
+    double full, alone, ends;
+};
+inline double tile_time(const TileCost &t, long long groups, long long steps, int compute_units)
+{
+    const long long room = (long long)t.slots * compute_units, rounds = groups / room, rest = groups % room;
+    const double last = rest ? std::max(t.alone, t.full * (double)rest / (double)room) : 0.0;
+    return (double)steps * ((double)rounds * t.full + last) + t.ends * (double)(rounds + (rest ? 1 : 0));
 }
 
 // Few results (up to six workgroups of the narrow kernel per compute unit; n = 1024, B = 1024 23 us against 41 with tiles,
-// 2048 42 / 46, 4096 88 / 68): the narrow kernel.  Else the largest tile that still gives every compute unit a workgroup
-// and a half, and for few rows one no taller than they are.  The
-// two kinds add in different orders: `all_columns`, where it is given, decides (the columns of the result of which a.B are
+// 2048 42 / 46, 4096 88 / 68): the narrow kernel.  Else the tile whose launch is shortest by tile_time, for which the loads run
+// a step ahead of the products, or two where the registers allow that.  Times measured in us, 64 x 64 / 128 x 64 / 128 x 128 /
+// 256 x 128: n = 256, B = 65536 79 / 69 / 60 / 52, n = 1002, B = 3001 46 / 49 / 60 / 96, n = 1024, B = 4096 59 / 53 / 61 / 95,
+// B = 16384 225 / 194 / 173 / 148, n = 2048, B = 4096 242 / 202 / 176 / 192, n = 4097, B = 4096 974 / 969 / 829 / 901.  (With
+// the loads one step ahead 64 x 64 takes 52 us at n = 1002, 128 x 128 196 us at n = 2048, B = 4096.)  All tiles add in the same
+// order; the narrow kernel in another: `all_columns`, where it is given, decides (the columns of the result of which a.B are
 // a part), so that a result does not depend on how it is cut.
+constexpr TileCost kProductTiles[4] = {{64, 64, 4, 1.79, 0.9, 4.0}, {128, 64, 2, 1.63, 1.3, 6.0},
+                                       {128, 128, 2, 2.71, 1.9, 9.0}, {256, 128, 2, 4.6, 3.0, 15.0}};
 constexpr long long product_narrow_blocks(int m, long long B) { return (long long)((m + 31) / 32) * ((B + 31) / 32); }
 constexpr bool product_is_narrow(int m, long long B, int compute_units)
 {
@@ -359,14 +391,25 @@ inline void product(ProductArgs a, int compute_units, hipStream_t stream, long l
             hipLaunchKernelGGL(product_narrow_kernel<false>, dim3((unsigned)narrow), dim3(64 * kNarrowWaves), 0, stream, a);
         return;
     }
-    auto groups = [&](int bm, int bn) { return ((a.m + bm - 1) / bm) * ((a.B + bn - 1) / bn); };
-    const long long enough = 3LL * compute_units / 2;
-    if (a.m > 128 && groups(256, 128) >= enough)
-        launch_product<4, 1, 2, 4>(a, stream);
-    else if (a.m > 64 && groups(128, 128) >= enough)
-        launch_product<2, 2, 2, 2>(a, stream);
+    int best = 0;
+    double least = 0.0;
+    for (int i = 0; i < 4; ++i) {
+        const TileCost &t = kProductTiles[i];
+        const long long groups = (long long)((a.m + t.bm - 1) / t.bm) * ((a.B + t.bn - 1) / t.bn);
+        const double us = tile_time(t, groups, (a.k + kProductStep - 1) / kProductStep, compute_units);
+        if (i == 0 || us < least) {
+            best = i;
+            least = us;
+        }
+    }
+    if (best == 3)
+        launch_product<4, 1, 2, 4, 1>(a, stream);
+    else if (best == 2)
+        launch_product<2, 2, 2, 2, 2>(a, stream);
+    else if (best == 1)
+        launch_product<2, 2, 2, 1, 2>(a, stream);
     else
-        launch_product<2, 2, 1, 1>(a, stream);
+        launch_product<2, 2, 1, 1, 2>(a, stream);
 }
 
 // dst <- src, `cols` columns of each row (an operand that is its own result is multiplied from a copy)

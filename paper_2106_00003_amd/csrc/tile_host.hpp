@@ -72,8 +72,8 @@ struct TileOperand {
 };
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
                  bool forward, hipStream_t stream);
-// dtheta from C = Y G^T (leading dimension `rows`); the pieces are U^T's.  Beside it, U^T is applied to `op`.
+// dtheta from the slices of C = Y G^T (leading dimension `rows`), whose sum it is; the pieces are U^T's.  Beside it, U^T is applied to `op`.
 void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
-                    const TileBuffers &b, const float *C, float *dtheta, const TileOperand &op, hipStream_t stream);
+                    const TileBuffers &b, const float *C, int slices, float *dtheta, const TileOperand &op, hipStream_t stream);
 
 } // namespace givens

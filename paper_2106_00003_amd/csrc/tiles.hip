@@ -42,14 +42,15 @@ inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_
     }
 }
 inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
-                          const u32x4 *pieces, const float *C, float *S, float *blocks, int *range, float *halves,
+                          const u32x4 *pieces, const float *C, int slices, float *S, float *blocks, int *range, float *halves,
                           const unsigned *tops, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
     const int t = tile_ld(g) / 32;
     const bool narrow = tile_gradient_narrow(g, free_rows);
     const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2) * (narrow ? kTilePad / 32 : 1);
     float *second = narrow ? S + tile_s_floats(g) : nullptr;
-    hipLaunchKernelGGL(tile_antisym_kernel, dim3(t, t), dim3(256), 0, stream, g, rows, C, S, second, range);
+    hipLaunchKernelGGL(tile_antisym_kernel, dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, stream, g, rows, slices, C, S, second,
+                       range);
     const long long slots = (long long)compute_units * 8 / (kTilePad / 32);
     float *in = S, *out = second ? second : S;
     for (int st = 0; st < g.stages; ++st) {
@@ -83,9 +84,9 @@ void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, 
     tile_apply(g, compute_units, rows, free_rows, op, static_cast<const u32x4 *>(b.pieces), b.tops, forward, stream);
 }
 void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
-                    const TileBuffers &b, const float *C, float *dtheta, const TileOperand &op, hipStream_t stream)
+                    const TileBuffers &b, const float *C, int slices, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
-    tile_gradient(g, compute_units, rows, free_rows, theta, map, static_cast<const u32x4 *>(b.pieces), C, b.S, b.blocks, b.range,
+    tile_gradient(g, compute_units, rows, free_rows, theta, map, static_cast<const u32x4 *>(b.pieces), C, slices, b.S, b.blocks, b.range,
                   b.halves, b.tops, dtheta, op, stream);
 }
 

@@ -42,6 +42,21 @@ def test_gram_contraction_at_the_edges_of_its_tiles(n, B):
     assert torch.equal(again, dth)
 
 
+# the tiles between: contractions of 128 x 128, products of 64 x 64, 128 x 64 and 128 x 128 with loads two steps ahead, odd and
+# even numbers of steps, ragged in both directions
+@pytest.mark.parametrize("n,B", [(288, 12001), (386, 9001), (770, 5001), (800, 4999), (1002, 3001), (1056, 4501)])
+def test_tiles_of_middle_sizes(n, B):
+    data = inputs.make_custom(n, B, seed=1330 + n)
+    print(f"[products] middle n={n} B={B}", flush=True)
+    th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    want = binding.givens_forward(th.double(), x.double())
+    y = binding.givens_forward(th, x)
+    assert rel(y, want) <= TOL_Y and rel(y[-3:, -3:], want[-3:, -3:]) <= TOL_Y
+    dx, dth = binding.givens_backward_ex(th, y, g, reduction=binding.REDUCTION_GRAM)
+    want_dx, want_dth = binding.givens_backward(th.double(), want, g.double())
+    assert rel(dx, want_dx) <= TOL_G and rel(dth, want_dth) <= TOL_G
+
+
 # operands that start at an odd multiple of four bytes, row lengths of every remainder: both tile sizes
 @pytest.mark.parametrize("n,B", [(66, 4097), (66, 4098), (514, 4099), (512, 4096)])
 def test_gram_contraction_of_unaligned_operands(n, B):
