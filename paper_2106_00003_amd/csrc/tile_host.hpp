@@ -30,12 +30,13 @@ constexpr TilePlan tile_plan(int n)
 constexpr long long tile_count(const TilePlan &p) { return (long long)p.stages * p.P; }
 constexpr int kTilePieceWords = kTilePad * kTilePad * 3 / 8;   // u32x4 per tile
 
-// the gradient's matrix: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on), then row 0
-inline __host__ __device__ int tile_piece_stride(const TilePlan &g) { return (g.s + 3) / 4 * 4; }
-inline __host__ __device__ int tile_held_place(const TilePlan &g) { return 2 * g.P * tile_piece_stride(g); }
-inline __host__ __device__ int tile_ld(const TilePlan &g) { return (tile_held_place(g) + 1 + 31) / 32 * 32; }
-// floats of S: a tile's loads run up to half a tile past a piece's start
-inline size_t tile_s_floats(const TilePlan &g) { return (size_t)tile_ld(g) * tile_ld(g) + (size_t)kTilePad * 2; }
+// The gradient's matrix S: a row and column for every one of the kTileHalf slots of each of the 2P pieces (those past a piece's end
+// are zeros), as blocks of piece by piece in the order of tile_block_at, and behind the blocks row 0 (S is antisymmetric, so its
+// column is not kept).
+constexpr int kTileHalf = kTilePad / 2;
+constexpr int kTileBlock = kTileHalf * kTileHalf;
+inline __host__ __device__ size_t tile_held_offset(const TilePlan &g) { return (size_t)4 * g.P * g.P * kTileBlock; }
+inline __host__ __device__ size_t tile_s_floats(const TilePlan &g) { return tile_held_offset(g) + (size_t)2 * g.P * kTileHalf; }
 // whether the gradient's stages run with 32 columns of a pair of tiles per workgroup (tile_two_sided_narrow_kernel); with
 // restricted parametrisations most pairs have nothing to do, which only the other kernel leaves alone
 inline bool tile_gradient_narrow(const TilePlan &g, int free_rows) { return free_rows >= g.n - 2 && g.P <= 24; }

@@ -242,10 +242,35 @@ __device__ __forceinline__ void tile_rotate(T &p, T &q, const R2 &cs)
     q = fma(cs.x, b, -(cs.y * a));
 }
 
+// address spaces of the loads that go from memory to LDS
+typedef __attribute__((address_space(3))) void *lds_ptr;
+typedef __attribute__((address_space(1))) const void *global_ptr;
+constexpr int kWaitForLoads = 0x0f70;   // s_waitcnt vmcnt(0): this wavefront's loads into LDS are there
+
 // A fragment of a tile's matrix: rows 32 f .. + 31, contraction indices 16 k .. + 15, as in product_kernels.hpp but with
 // the indices of a half wavefront in the order in which the matrix instructions leave their results in registers, so that
 // a result can be the next product's operand without a move between lanes.
 __device__ __forceinline__ int tile_k(int half, int j) { return (j & 3) + 4 * half + 8 * (j >> 2); }
+// Place of element (row, col) in a block of float32 fragments of such an order, `columns` / 16 of them beside one another: a lane's
+// eight values of a fragment are consecutive, a wavefront loads or stores one as 2 KB.
+__device__ __forceinline__ int tile_block_at(int columns, int row, int col)
+{
+    return ((row >> 5) * (columns / 16) + (col >> 4)) * 512 + ((row & 31) + 32 * ((col >> 2) & 1)) * 8 + (col & 3) +
+           4 * ((col >> 3) & 1);
+}
+// a b over 16 contraction indices added to large + small, operands given as pieces: the largest products in one accumulator,
+// those below 2^-16 of them in the other.  The two take turns, since a matrix instruction has to wait for the one before it on
+// its accumulator; and half of the roundings are those of small sums.
+__device__ __forceinline__ void tile_mfma(const u32x4 (&a)[3], const u32x4 (&b)[3], f32x16 &large, f32x16 &small)
+{
+    constexpr int pa[6] = {2, 1, 0, 0, 1, 0}, pb[6] = {0, 0, 2, 1, 1, 0};
+#pragma unroll
+    for (int p = 0; p < 6; ++p) {
+        f32x16 &acc = p & 1 ? large : small;
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[pa[p]]), __builtin_bit_cast(bf16x8, b[pb[p]]),
+                                                      acc, 0, 0, 0);
+    }
+}
 
 // What the apply stages have to know of their operand's columns: tops, the bits of their largest magnitudes.  A workgroup takes
 // 64 columns, a wavefront an eighth of the rows.
@@ -496,23 +521,24 @@ struct TileApplyArgs {
 
 // One stage on B columns: rows of each tile <- matrix * rows.  A workgroup takes one tile and a run of columns, a wavefront
 // 32 rows of the result with its part of the matrix in registers throughout.  Per step of kTileCols columns a wavefront brings
-// 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange), a step ahead,
-// and puts the pieces into LDS as fragments.
+// 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange) and puts the pieces
+// into LDS as fragments, into the buffer of the step's parity: while a step's products run, the next one's rows are cut and the
+// rows after that are on their way.  (An operand of the tiles has less than 4 GiB: fewer than max(2n, 2048) columns.)
+// MEASURED_APPLY
 struct TileApplyShared {
-    u32x4 panel[kTilePad / 16][3][64];
+    u32x4 panel[2][kTilePad / 16][3][64];
 };
 __device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned block, TileApplyShared &sh)
 {
     constexpr int KF = kTilePad / 16;
-    auto &panel = sh.panel;
     const TilePlan &g = a.g;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int u = block % g.P;
-    const long long n0 = (long long)(block / g.P) * a.chunk, n1 = n0 + a.chunk < a.B ? n0 + a.chunk : a.B;
+    const unsigned B = (unsigned)a.B, n0 = block / g.P * (unsigned)a.chunk, n1 = n0 + (unsigned)a.chunk < B ? n0 + (unsigned)a.chunk : B;
     const Tile x = tile_at(g, a.stage, u);
     const bool identity = tile_is_identity(g, x, a.free_rows);
-    if (n0 >= a.B || (a.X == a.Y && identity)) return;
+    if (n0 >= B || (a.X == a.Y && identity)) return;
     // this wavefront's 32 rows: labels first, first - 2, ...; `count` of them are there, row 0 may stand at the end
     const int local = 32 * wave, in_piece = local % (kTilePad / 2);
     const bool second = local >= kTilePad / 2;
@@ -520,70 +546,80 @@ __device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned bloc
     const int first = tile_label(g, (second ? x.b0 : x.a0)) - 2 * in_piece;
     const bool has_held = u == 0 && local == kTilePad - 32;
     const int skip = first >= a.rows ? 1 : 0;          // the added row of an odd problem is the first of its piece
-
-    u32x4 fa[KF][1][3];
-    const u32x4 *ap = a.pieces + tile_piece_index(g, a.stage, u, identity) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
-#pragma unroll
-    for (int kf = 0; kf < KF; ++kf)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) fa[kf][0][p] = ap[kf * 192 + 64 * p];
+    // byte offset of row first - 2 (4 half); the rows below it are 8 B bytes apart
+    const unsigned row_of_half = (unsigned)(first - 8 * half) * B;
 
     // a lane brings 16 rows of one column, those of its half of the fragments
     float xr[16];
     unsigned top = 0u;
-    auto fetch = [&](long long c0) {
-        long long col = c0 + l32;
-        col = col < n1 ? col : n1 - 1;
+    auto fetch = [&](unsigned c0) {
+        const unsigned col = c0 + l32 < n1 ? c0 + l32 : n1 - 1;
         if (a.tops) top = a.tops[col];
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
-            const int r = 16 * (q >> 3) + tile_k(half, q & 7);
+            const int r = 16 * (q >> 3) + tile_k(half, q & 7), below = 16 * (q >> 3) + tile_k(0, q & 7);
             const bool there = r < count && r >= skip, held = has_held && r == 31;
-            const int row = there ? first - 2 * r : 0;
-            const float v = a.X ? a.X[(long long)row * a.B + col] : (col == row ? 1.f : 0.f);
+            const unsigned at = there ? (row_of_half - 2 * below * B + col) * 4u : col * 4u;
+            const float v = a.X ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.X) + at)
+                                : ((int)col == (there ? first - 2 * r : 0) ? 1.f : 0.f);
             xr[q] = there || held ? v : 0.f;
         }
     };
-    float undo = 1.f;   // of the columns in the panel
-    auto stash = [&]() {
+    float undo[2] = {1.f, 1.f};   // of the columns in the panels
+    auto stash = [&](int buf) {
         const float scale = range_scale(__uint_as_float(top));
-        undo = range_unscale(scale);
+        undo[buf] = range_unscale(scale);
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
             float v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = xr[8 * f + q] * scale;
             const Split8 sp = split8(v);
-            panel[2 * wave + f][0][lane] = sp.h;
-            panel[2 * wave + f][1][lane] = sp.m;
-            panel[2 * wave + f][2][lane] = sp.l;
+            sh.panel[buf][2 * wave + f][0][lane] = sp.h;
+            sh.panel[buf][2 * wave + f][1][lane] = sp.m;
+            sh.panel[buf][2 * wave + f][2][lane] = sp.l;
         }
     };
     fetch(n0);
-    for (long long c0 = n0; c0 < n1; c0 += kTileCols) {
-        stash();
-        __syncthreads();
-        if (c0 + kTileCols < n1) fetch(c0 + kTileCols);
-        f32x16 acc[1][1];
+    u32x4 fa[KF][3];
+    const u32x4 *ap = a.pieces + tile_piece_index(g, a.stage, u, identity) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] = 0.f;
+    for (int kf = 0; kf < KF; ++kf)
 #pragma unroll
-        for (int kf = 0; kf < KF; ++kf) {
-            const u32x4 fb[1][3] = {{panel[kf][0][lane], panel[kf][1][lane], panel[kf][2][lane]}};
-            mfma_split(fa[kf], fb, acc);
-        }
-        const long long col = c0 + l32;
-        if (col < n1)
+        for (int p = 0; p < 3; ++p) fa[kf][p] = ap[kf * 192 + 64 * p];
+    stash(0);
+    if (n0 + kTileCols < n1) fetch(n0 + kTileCols);
+    for (unsigned at = n0; at < n1; at += 2 * kTileCols)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 8 * (v >> 2) + 4 * half + (v & 3);
-                if (r < count && r >= skip)
-                    a.Y[(long long)(first - 2 * r) * a.B + col] = acc[0][0][v] * undo;
-                else if (has_held && r == 31)
-                    a.Y[col] = acc[0][0][v] * undo;
+        for (int buf = 0; buf < 2; ++buf) {
+            const unsigned c0 = at + buf * kTileCols;
+            if (buf && c0 >= n1) break;
+            __syncthreads();   // this step's panel is whole; the other one is free (its readers passed this barrier)
+            f32x16 acc, small;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = small[v] = 0.f;
+#pragma unroll
+            for (int kf = 0; kf < KF; ++kf) {
+                const u32x4 fb[3] = {sh.panel[buf][kf][0][lane], sh.panel[buf][kf][1][lane], sh.panel[buf][kf][2][lane]};
+                tile_mfma(fa[kf], fb, acc, small);
             }
-        __syncthreads();
-    }
+            if (c0 + kTileCols < n1) {
+                stash(buf ^ 1);
+                if (c0 + 2 * kTileCols < n1) fetch(c0 + 2 * kTileCols);
+            }
+            const unsigned col = c0 + l32;
+            if (col < n1)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = 8 * (v >> 2) + 4 * half + (v & 3), below = 8 * (v >> 2) + (v & 3);
+                    const float y = (acc[v] + small[v]) * undo[buf];
+                    char *const to = reinterpret_cast<char *>(a.Y);
+                    if (r < count && r >= skip)
+                        *reinterpret_cast<float *>(to + (row_of_half - 2 * below * B + col) * 4u) = y;
+                    else if (has_held && r == 31)
+                        a.Y[col] = y;
+                }
+        }
 }
 __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyArgs a)
 {
@@ -591,60 +627,78 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
     tile_apply(a, blockIdx.x, sh);
 }
 
-// ---- the gradient's matrix S: rows and columns in the order piece 0, 1, ..., 2P - 1 (each from a multiple of four on),
-// then row 0; places that hold no row are zero or never count.
-// S[p][q] = C[row p][row q] - C[row q][row p] for C the sum of its slices; `second` (may be null): zeros, so that places without a
-// row stay numbers.  A workgroup takes two 32 x 32 blocks that mirror each other and reads each slice of them once.  Bound by
-// memory (labels go by two, so half of a line is another block's): n = 1002 with 7 slices 19 us, n = 4097 61 us (a kernel that
-// summed the slices first, and one that read C twice: 15 + 10 us with 4 slices, 83 us).
+// ---- the gradient's matrix S (tile_s_floats).
+// S[p][q] = C[row p][row q] - C[row q][row p] for C the sum of its slices.  A workgroup takes two 32 x 32 blocks that mirror each
+// other and reads each slice of them once; the last ones take row 0.  Bound by memory (labels go by two, so half of a line is
+// another block's): MEASURED_ANTISYM
+inline unsigned tile_antisym_blocks(const TilePlan &g)
+{
+    const int t = 2 * g.P * (kTileHalf / 32);
+    return (unsigned)(t * (t + 1) / 2 + (2 * g.P * kTileHalf + 255) / 256);
+}
 __global__ __launch_bounds__(256) void tile_antisym_kernel(TilePlan g, int rows, int slices, const float *__restrict__ C,
-                                                           float *__restrict__ S, float *__restrict__ second,
-                                                           int *__restrict__ range)
+                                                           float *__restrict__ S, int *__restrict__ range)
 {
     __shared__ float block[2][32][33];
-    const int ld = tile_ld(g), t = ld / 32;
-    int bi = 0, bj = blockIdx.x;
-    while (bj >= t - bi) bj -= t - bi++;
-    bj += bi;
-    const int p0 = bi * 32, q0 = bj * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int t = 2 * g.P * (kTileHalf / 32), pairs = t * (t + 1) / 2;
     auto label = [&](int p) {
-        const int stride = tile_piece_stride(g), held = tile_held_place(g);
-        if (p >= held) return p == held ? 0 : -1;
         int start, count;
-        tile_piece(g, p / stride, &start, &count);
-        const int r = p % stride;
+        tile_piece(g, p / kTileHalf, &start, &count);
+        const int r = p % kTileHalf;
         if (r >= count) return -1;
         const int l = tile_label(g, start + r);
         return l < rows ? l : -1;
     };
-    const int lp = label(p0 + tx), lq = label(q0 + tx);
     const size_t slice = (size_t)rows * rows;
-    size_t at[8];          // rows ty, ty + 8, ... of block (p, q), then of block (q, p)
-    bool there[8];
-    float sum[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int lr = label((i < 4 ? p0 : q0) + ty + 8 * (i & 3)), lc = i < 4 ? lq : lp;
-        there[i] = lr >= 0 && lc >= 0;
-        at[i] = there[i] ? (size_t)lr * rows + lc : 0;
-        sum[i] = 0.f;
-    }
-#pragma unroll 4
-    for (int s = 0; s < slices; ++s)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) sum[i] += C[s * slice + at[i]];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) block[i >> 2][ty + 8 * (i & 3)][tx] = there[i] ? sum[i] : 0.f;
-    __syncthreads();
     float top = 0.f;
+    if ((int)blockIdx.x < pairs) {
+        int bi = 0, bj = blockIdx.x;
+        while (bj >= t - bi) bj -= t - bi++;
+        bj += bi;
+        const int p0 = bi * 32, q0 = bj * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+        const int lp = label(p0 + tx), lq = label(q0 + tx);
+        size_t at[8];          // rows ty, ty + 8, ... of block (p, q), then of block (q, p)
+        bool there[8];
+        float sum[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int which = i >> 2, r = ty + 8 * (i & 3);
-        const float v = block[which][r][tx] - block[which ^ 1][tx][r];
-        const size_t to = (size_t)((which ? q0 : p0) + r) * ld + (which ? p0 : q0) + tx;
-        S[to] = v;
-        if (second) second[to] = 0.f;
-        top = range_top(top, v, 0.f);
+        for (int i = 0; i < 8; ++i) {
+            const int lr = label((i < 4 ? p0 : q0) + ty + 8 * (i & 3)), lc = i < 4 ? lq : lp;
+            there[i] = lr >= 0 && lc >= 0;
+            at[i] = there[i] ? (size_t)lr * rows + lc : 0;
+            sum[i] = 0.f;
+        }
+#pragma unroll 4
+        for (int s = 0; s < slices; ++s)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] += C[s * slice + at[i]];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) block[i >> 2][ty + 8 * (i & 3)][tx] = there[i] ? sum[i] : 0.f;
+        __syncthreads();
+        // four consecutive columns of a row: half of a lane's values of a fragment
+        const int r = threadIdx.x / 2 % 32, c = threadIdx.x / 128 * 16 + threadIdx.x / 64 % 2 * 4 + threadIdx.x % 2 * 8;
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            f32x4 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = block[which][r][c + q] - block[which ^ 1][c + q][r];
+            const int row0 = which ? q0 : p0, col0 = which ? p0 : q0;
+            float *to = S + (size_t)(row0 / kTileHalf * 2 * g.P + col0 / kTileHalf) * kTileBlock;
+            *reinterpret_cast<f32x4 *>(to + tile_block_at(kTileHalf, row0 % kTileHalf + r, col0 % kTileHalf + c)) = v;
+            top = range_top(range_top(top, v[0], v[1]), v[2], v[3]);
+        }
+    } else {
+        const int p = ((int)blockIdx.x - pairs) * 256 + threadIdx.x;
+        if (p < 2 * g.P * kTileHalf) {
+            const int l = label(p);
+            float of_row = 0.f, of_col = 0.f;
+            if (l >= 0)
+                for (int s = 0; s < slices; ++s) {
+                    of_row += C[s * slice + l];
+                    of_col += C[s * slice + (size_t)l * rows];
+                }
+            S[tile_held_offset(g) + p] = of_row - of_col;
+            top = range_top(top, of_row - of_col, 0.f);
+        }
     }
     // (each word is written by the first wavefronts that get there: they all write the same)
     auto set = [&](bool on, int word) {
@@ -661,102 +715,137 @@ struct TileTwoSidedArgs {
     const u32x4 *pieces;   // of A (not transposed)
     const float *in;       // S before the stage
     float *out;            // S after it: the same array, or another one
-    float *blocks;         // [tile][kTilePad][kTilePad]: every tile's own block before its stage
+    float *blocks;         // every tile's own block before its stage, in the order of tile_block_at
     const int *range;      // of S
 };
-
-// Places in S of the local rows of a pair's two tiles (-1: holds no row)
-__device__ __forceinline__ void tile_places(const TilePlan &g, const Tile &x, const Tile &y, int ux, int uy, int (&place_x)[kTilePad],
-                                            int (&place_y)[kTilePad])
+struct TilePair {
+    Tile x, y;
+    int ux, uy;
+    bool idx, idy;         // identities
+};
+__device__ __forceinline__ TilePair tile_pair(const TileTwoSidedArgs &a, unsigned id)
 {
-    const int stride = tile_piece_stride(g);
-    for (int r = threadIdx.x; r < 2 * kTilePad; r += 2 * kTilePad) {
-        const bool of_x = r < kTilePad;
-        const int q = r % kTilePad, u = of_x ? ux : uy, w = q - kTilePad / 2;
-        const int i = of_x ? x.i : y.i, j = of_x ? x.j : y.j;
-        int p = -1;
-        if (q < g.s) p = i * stride + q;
-        else if (w >= 0 && w < g.s) p = j * stride + w;
-        else if (q == kTilePad - 1 && u == 0) p = tile_held_place(g);
-        (of_x ? place_x : place_y)[q] = p;
+    const TilePlan &g = a.g;
+    TilePair t;
+    t.ux = 0;
+    t.uy = id;
+    while (t.uy >= g.P - t.ux) t.uy -= g.P - t.ux++;
+    t.uy += t.ux;
+    t.x = tile_at(g, a.stage, t.ux);
+    t.y = tile_at(g, a.stage, t.uy);
+    t.idx = tile_is_identity(g, t.x, a.free_rows);
+    t.idy = tile_is_identity(g, t.y, a.free_rows);
+    return t;
+}
+__device__ __forceinline__ size_t tile_s_block(const TilePlan &g, int i, int j) { return ((size_t)i * 2 * g.P + j) * kTileBlock; }
+
+// Rows 32 wave .. + 31 of S for the columns of fragment kf, a lane's eight values (S of the pair's two tiles; row 0, which stands in
+// the last row of tile 0, from behind the blocks)
+__device__ __forceinline__ void tile_load_s(const TileTwoSidedArgs &a, const TilePair &t, int wave, int kf, f32x4 (&v)[2])
+{
+    const int lane = threadIdx.x & 63;
+    const int i = wave < 2 ? t.x.i : t.x.j, j = kf < 4 ? t.y.i : t.y.j;
+    const float *src = a.in + tile_s_block(a.g, i, j) + ((wave & 1) * 4 + (kf & 3)) * 512 + lane * 8;
+    v[0] = *reinterpret_cast<const f32x4 *>(src);
+    v[1] = *reinterpret_cast<const f32x4 *>(src + 4);
+}
+__device__ __forceinline__ void tile_load_held(const TileTwoSidedArgs &a, const TilePair &t, int wave, int kf, f32x4 (&v)[2])
+{
+    if (t.ux != 0 || wave != 3) return;
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const float *held = a.in + tile_held_offset(a.g);
+    if ((lane & 31) == 31) {
+        const float *src = held + (kf < 4 ? t.y.i : t.y.j) * kTileHalf + (kf & 3) * 16 + 4 * half;
+        v[0] = *reinterpret_cast<const f32x4 *>(src);
+        v[1] = *reinterpret_cast<const f32x4 *>(src + 8);
     }
 }
-// Rows 32 wave .. + 31 of a result R for columns of tile y, place cp: to (x, y) and, negated and transposed, to (y, x)
-__device__ __forceinline__ void tile_store_both(const TilePlan &g, float *S, const f32x16 &R, int wave, int half, int cp,
-                                                bool own, bool first, const int (&place_x)[kTilePad])
+// (the column of row 0, in tile 0's own pair)
+__device__ __forceinline__ void tile_load_held_column(const TileTwoSidedArgs &a, const TilePair &t, int wave, f32x4 (&v)[2])
 {
-    const int held = tile_held_place(g), ld = tile_ld(g);
-    if (cp < 0) return;
+    if (t.uy != 0) return;
+    const int lane = threadIdx.x & 63, row = (wave & 1) * 32 + (lane & 31);
+    if (lane >= 32) {
+        const float held = a.in[tile_held_offset(a.g) + (wave < 2 ? t.x.i : t.x.j) * kTileHalf + row];
+        v[1][3] = wave == 3 && row == kTileHalf - 1 ? 0.f : -held;
+    }
+}
+// Rows 32 wave .. + 31 and columns 32 part .. + 31 of a result R as the matrix instructions leave it: to (x, y), turned in LDS, and
+// as it stands, negated, to (y, x)
+typedef float TileTurn[32][36];
+__device__ __forceinline__ void tile_store_both(const TileTwoSidedArgs &a, const TilePair &t, f32x16 R, int wave, int part,
+                                                TileTurn &turn)
+{
+    const TilePlan &g = a.g;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int i = wave < 2 ? t.x.i : t.x.j, j = part < 2 ? t.y.i : t.y.j;
+    const int row0 = (wave & 1) * 32, col = (part & 1) * 32 + l32;
+    if (t.ux == 0 && wave == 3 && half == 1) a.out[tile_held_offset(g) + j * kTileHalf + col] = col < g.s ? R[15] : 0.f;
+    if (row0 + 31 >= g.s || (part & 1) * 32 + 31 >= g.s)      // places without a row stay zeros
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = row0 + 8 * (v >> 2) + 4 * half + (v & 3);
+            R[v] = row < g.s && col < g.s ? R[v] : 0.f;
+        }
+    float *mirror = a.out + tile_s_block(g, j, i) + (part & 1) * 2048 + (wave & 1) * 1024 + lane * 8;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            f32x4 neg;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) neg[w] = -R[8 * f + 4 * q + w];
+            *reinterpret_cast<f32x4 *>(mirror + 512 * f + 4 * q) = neg;
+        }
+    if (t.ux == t.uy) return;                                 // (its own mirror)
 #pragma unroll
     for (int v = 0; v < 16; v += 4) {
-        const int r0 = 32 * wave + 8 * (v >> 2) + 4 * half;
-        const int p0 = place_x[r0];
+        f32x4 four;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int p = place_x[r0 + q];
-            if (p >= 0) S[(long long)p * ld + cp] = R[v + q];
-        }
-        if (!own) {
-            float *o = S + (long long)cp * ld;
-            if (p0 >= 0) {   // (a piece starts at a multiple of four places and owns whole groups of four)
-                f32x4 neg;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) neg[q] = -R[v + q];
-                *reinterpret_cast<f32x4 *>(o + p0) = neg;
-            }
-            if (r0 == kTilePad - 4 && first) o[held] = -R[v + 3];
-        }
+        for (int w = 0; w < 4; ++w) four[w] = R[v + w];
+        *reinterpret_cast<f32x4 *>(&turn[l32][8 * (v >> 2) + 4 * half]) = four;
     }
+    float *to = a.out + tile_s_block(g, i, j) + (wave & 1) * 2048 + (part & 1) * 1024 + lane * 8;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            f32x4 four;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) four[w] = turn[16 * f + tile_k(half, 4 * q + w)][l32];
+            *reinterpret_cast<f32x4 *>(to + 512 * f + 4 * q) = four;
+        }
 }
 
 // One stage of S <- A S A^T: a workgroup per pair of tiles (x, y), x <= y, in place.  First V = S A_y^T, a wavefront taking
 // 32 of its columns (its part of A_y in registers) and all rows, then R = A_x V, a wavefront taking 32 of its rows (its
 // part of A_x in registers).  The other operand of both products is cut into pieces once and shared through LDS, half the
-// contraction at a time: S as rows of eight values (a lane's are two groups of four consecutive columns), V as its
-// accumulators are.  Pairs without a rotation are left alone.  n = 4096: 40 to 48 us a stage.
+// contraction at a time: S as its fragments, V as its accumulators are.  Pairs without a rotation are left alone.
+// MEASURED_WIDE
 struct TileTwoSidedShared {
     u32x4 panel[kTilePad / 32][kTilePad / 32][3][64];
-    int place_x[kTilePad], place_y[kTilePad];
+    TileTurn turn[kTilePad / 32];
 };
 __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsigned block_id, TileTwoSidedShared &sh)
 {
     constexpr int MF = kTilePad / 32, KF = kTilePad / 16, KH = KF / 2;
     auto &panel = sh.panel;
-    auto &place_x = sh.place_x, &place_y = sh.place_y;
     const TilePlan &g = a.g;
-    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int ux = 0, uy = block_id;
-    while (uy >= g.P - ux) uy -= g.P - ux++;
-    uy += ux;
-    const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
-    const bool own = ux == uy;
-    const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
-    if (idx && idy) return;
-    const float scale = tile_scale(a.range), undo = range_unscale(scale);
-    const int stride = tile_piece_stride(g), ld = tile_ld(g);
-    tile_places(g, x, y, ux, uy, place_x, place_y);
-    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
-    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
-    __syncthreads();
+    const TilePair t = tile_pair(a, block_id);
+    const bool own = t.ux == t.uy;
+    if (t.idx && t.idy) return;
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, t.ux, t.idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, t.uy, t.idy) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
 
-    // S: a wavefront brings 32 rows; a row that is none: A_x has zeros in its column
-    const int p_row = place_x[32 * wave + l32];
-    const float *row = a.in + (long long)(p_row < 0 ? 0 : p_row) * ld;
-    float *block = a.blocks + ((size_t)a.stage * g.P + ux) * kTilePad * kTilePad + (32 * wave + l32) * kTilePad;
     f32x4 sr[KH][2];
     auto fetch = [&](int h) {
 #pragma unroll
-        for (int k = 0; k < KH; ++k) {
-            const int local = 16 * (KH * h + k) + 4 * half;                 // half h of the contraction is piece i or j
-            const float *src = row + (h ? y.j : y.i) * stride + local - h * (kTilePad / 2);
-            sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
-            sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
-            if (h == 1 && k == KH - 1 && uy == 0) {
-                const float v = row[tile_held_place(g)];
-                if (half) sr[k][1][3] = v;
-            }
-        }
+        for (int k = 0; k < KH; ++k) tile_load_s(a, t, wave, KH * h + k, sr[k]);
+#pragma unroll
+        for (int k = 0; k < KH; ++k) tile_load_held(a, t, wave, KH * h + k, sr[k]);
+        if (h == 1) tile_load_held_column(a, t, wave, sr[KH - 1]);
     };
     auto stash = [&](int k, const float(&v)[8]) {
         const Split8 sp = split8(v);
@@ -764,13 +853,23 @@ __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsign
         panel[k][wave][1][lane] = sp.m;
         panel[k][wave][2][lane] = sp.l;
     };
+    u32x4 fm[KH][1][3];
+    auto load_matrix = [&](const u32x4 *p, int h) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) fm[k][0][q] = p[(KH * h + k) * 192 + 64 * q];
+    };
+    fetch(0);
+    load_matrix(py, 0);
+    const float scale = tile_scale(a.range), undo = range_unscale(scale);
     auto stash_s = [&](int h) {
 #pragma unroll
         for (int k = 0; k < KH; ++k) {
             if (own) {
-                float *o = block + 16 * (KH * h + k) + 4 * half;
+                float *o = a.blocks + ((size_t)a.stage * g.P + t.ux) * kTilePad * kTilePad + (wave * KF + KH * h + k) * 512 + lane * 8;
                 *reinterpret_cast<f32x4 *>(o) = sr[k][0];
-                *reinterpret_cast<f32x4 *>(o + 8) = sr[k][1];
+                *reinterpret_cast<f32x4 *>(o + 4) = sr[k][1];
             }
             float v[8];
 #pragma unroll
@@ -781,22 +880,14 @@ __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsign
             stash(k, v);
         }
     };
-    u32x4 fm[KH][1][3];
-    auto load_matrix = [&](const u32x4 *p, int h) {
-#pragma unroll
-        for (int k = 0; k < KH; ++k)
-#pragma unroll
-            for (int q = 0; q < 3; ++q) fm[k][0][q] = p[(KH * h + k) * 192 + 64 * q];
-    };
     f32x16 V[MF][1], R[1][MF];
 #pragma unroll
     for (int i = 0; i < MF; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) V[i][0][v] = R[0][i][v] = 0.f;
-    fetch(0);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        load_matrix(py, h);
+        if (h) load_matrix(py, h);
         stash_s(h);
         __syncthreads();
         if (h == 0) fetch(1);
@@ -839,74 +930,61 @@ __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsign
     }
     // (every wavefront has read its part of S by now: the barriers above)
 #pragma unroll
-    for (int j = 0; j < MF; ++j)
-        tile_store_both(g, a.out, R[0][j] * undo, wave, half, place_y[32 * j + l32], own, ux == 0, place_x);
+    for (int j = 0; j < MF; ++j) tile_store_both(a, t, R[0][j] * undo, wave, j, sh.turn[wave]);
 }
 
 // The same for few tiles, where a pair per workgroup leaves compute units idle: a workgroup takes 32 columns of tile y, a
-// wavefront 32 rows of tile x, and only V's pieces go through LDS.  The other workgroups of a pair still read what one
-// writes, so the result goes to another array, all of it.  Bound by latency: everything a product needs is on its way
-// before it starts.  n = 1024: 12 us a stage (19.7 with a pair per workgroup).
+// wavefront 32 rows of tile x, and only V's pieces and the part of A_y, which all wavefronts need, go through LDS.  The other
+// workgroups of a pair still read what one writes, so the result goes to another array, all of it.  Bound by latency:
+// everything that the first product needs is on its way before it starts, and A_x while it runs.  MEASURED_NARROW
 struct TileNarrowShared {
-    u32x4 panel[kTilePad / 16][3][64];
-    int place_x[kTilePad], place_y[kTilePad];
+    u32x4 panel[kTilePad / 16][3][64];   // V
+    u32x4 matrix[kTilePad / 16][3][64];  // the part of A_y
+    TileTurn turn[kTilePad / 32];
 };
 __device__ __forceinline__ void tile_two_sided_narrow(const TileTwoSidedArgs &a, unsigned block_id, TileNarrowShared &sh)
 {
     constexpr int MF = kTilePad / 32, KF = kTilePad / 16;
     auto &panel = sh.panel;
-    auto &place_x = sh.place_x, &place_y = sh.place_y;
     const TilePlan &g = a.g;
-    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int part = block_id % MF;
-    int ux = 0, uy = block_id / MF;
-    while (uy >= g.P - ux) uy -= g.P - ux++;
-    uy += ux;
-    const Tile x = tile_at(g, a.stage, ux), y = tile_at(g, a.stage, uy);
-    const bool own = ux == uy;
-    const bool idx = tile_is_identity(g, x, a.free_rows), idy = tile_is_identity(g, y, a.free_rows);
+    const TilePair t = tile_pair(a, block_id / MF);
+    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, t.uy, t.idy) * kTilePieceWords + (size_t)part * KF * 192 + lane;
+    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, t.ux, t.idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
+#pragma unroll
+    for (int k = 0; k < KF / 4; ++k)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            __builtin_amdgcn_global_load_lds((global_ptr)(py + (KF / 4 * wave + k) * 192 + 64 * q),
+                                             (lds_ptr)(sh.matrix[KF / 4 * wave + k][q]), 16, 0, 0);
+    f32x4 sr[KF][2];
+#pragma unroll
+    for (int k = 0; k < KF; ++k) tile_load_s(a, t, wave, k, sr[k]);
+#pragma unroll
+    for (int k = 0; k < KF; ++k) tile_load_held(a, t, wave, k, sr[k]);
+    tile_load_held_column(a, t, wave, sr[KF - 1]);
+    u32x4 fm[KF][3];
     const float scale = tile_scale(a.range), undo = range_unscale(scale);
-    const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, ux, idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
-    const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, uy, idy) * kTilePieceWords + (size_t)part * KF * 192 + lane;
-    u32x4 fm[KF][1][3];
+    __builtin_amdgcn_s_waitcnt(kWaitForLoads);
+    __syncthreads();       // the part of A_y is in LDS
 #pragma unroll
     for (int k = 0; k < KF; ++k)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) fm[k][0][q] = py[k * 192 + 64 * q];
-    tile_places(g, x, y, ux, uy, place_x, place_y);
-    __syncthreads();
-
-    // this wavefront's rows of S (one that is none: A_x has zeros in its column)
-    const int stride = tile_piece_stride(g), ld = tile_ld(g);
-    const int p_row = place_x[32 * wave + l32];
-    const float *row = a.in + (long long)(p_row < 0 ? 0 : p_row) * ld;
-    f32x4 sr[KF][2];
-#pragma unroll
-    for (int k = 0; k < KF; ++k) {
-        const int local = 16 * k + 4 * half;
-        const float *src = row + (16 * k < kTilePad / 2 ? y.i * stride + local : y.j * stride + local - kTilePad / 2);
-        sr[k][0] = *reinterpret_cast<const f32x4 *>(src);
-        sr[k][1] = *reinterpret_cast<const f32x4 *>(src + 8);
-    }
-    if (uy == 0) {
-        const float v = row[tile_held_place(g)];
-        if (half) sr[KF - 1][1][3] = v;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (own && part == 0) {
-        float *block = a.blocks + ((size_t)a.stage * g.P + ux) * kTilePad * kTilePad + (32 * wave + l32) * kTilePad + 4 * half;
+        for (int q = 0; q < 3; ++q) fm[k][q] = px[k * 192 + 64 * q];
+    if (t.ux == t.uy && part == 0) {
+        float *block = a.blocks + ((size_t)a.stage * g.P + t.ux) * kTilePad * kTilePad + wave * KF * 512 + lane * 8;
 #pragma unroll
         for (int k = 0; k < KF; ++k) {
-            *reinterpret_cast<f32x4 *>(block + 16 * k) = sr[k][0];
-            *reinterpret_cast<f32x4 *>(block + 16 * k + 8) = sr[k][1];
+            *reinterpret_cast<f32x4 *>(block + 512 * k) = sr[k][0];
+            *reinterpret_cast<f32x4 *>(block + 512 * k + 4) = sr[k][1];
         }
     }
-    // two accumulators, even and odd fragments: one chain would wait for itself
-    f32x16 acc[2][1][1];
+    f32x16 acc, small;
     auto clear = [&]() {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][0][v] = acc[1][0][0][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[v] = small[v] = 0.f;
     };
     clear();
 #pragma unroll
@@ -918,21 +996,15 @@ __device__ __forceinline__ void tile_two_sided_narrow(const TileTwoSidedArgs &a,
             v[4 + q] = sr[k][1][q] * scale;
         }
         const Split8 sp = split8(v);
-        const u32x4 fs[1][3] = {{sp.h, sp.m, sp.l}};
-        mfma_split(fs, fm[k], acc[k & 1]);
+        const u32x4 fs[3] = {sp.h, sp.m, sp.l}, fy[3] = {sh.matrix[k][0][lane], sh.matrix[k][1][lane], sh.matrix[k][2][lane]};
+        tile_mfma(fs, fy, acc, small);
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int k = 0; k < KF; ++k)
-#pragma unroll
-        for (int q = 0; q < 3; ++q) fm[k][0][q] = px[k * 192 + 64 * q];
-    __builtin_amdgcn_sched_barrier(0);
     // V as operand of the second product: these 32 rows are contraction indices 32 wave .. + 31 of it
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
         float v[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = acc[0][0][0][8 * f + q] + acc[1][0][0][8 * f + q];
+        for (int q = 0; q < 8; ++q) v[q] = acc[8 * f + q] + small[8 * f + q];
         const Split8 sp = split8(v);
         panel[2 * wave + f][0][lane] = sp.h;
         panel[2 * wave + f][1][lane] = sp.m;
@@ -942,12 +1014,10 @@ __device__ __forceinline__ void tile_two_sided_narrow(const TileTwoSidedArgs &a,
     clear();
 #pragma unroll
     for (int k = 0; k < KF; ++k) {
-        const u32x4 fv[1][3] = {{panel[k][0][lane], panel[k][1][lane], panel[k][2][lane]}};
-        mfma_split(fm[k], fv, acc[k & 1]);
+        const u32x4 fv[3] = {panel[k][0][lane], panel[k][1][lane], panel[k][2][lane]};
+        tile_mfma(fm[k], fv, acc, small);
     }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[0][0][0][v] = (acc[0][0][0][v] + acc[1][0][0][v]) * undo;
-    tile_store_both(g, a.out, acc[0][0][0], wave, half, place_y[32 * part + l32], own, ux == 0, place_x);
+    tile_store_both(a, t, (acc + small) * undo, wave, part, sh.turn[wave]);
 }
 
 // One launch per stage of the reverse sweep: the workgroups before `pair_blocks` take S through it, the others (OPERAND) what
@@ -1037,10 +1107,11 @@ __global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan
     const Tile x = tile_at(g, st, u);
     if (!special && (x.kind == kTileSpecial || tile_is_identity(g, x, free_rows))) return;
     const float *blk = blocks + ((size_t)st * g.P + u) * kTilePad * kTilePad;
+    auto at = [&](int row, int col) { return blk[tile_block_at(kTilePad, row, col)]; };
     tile_coefs<float2, float>(g, x, special, g.s, theta, map, table);
     if (special && threadIdx.x < 64) {
         const int col = threadIdx.x + 64 * half;
-        row0[threadIdx.x] = make_float2(col == kTilePad - 1 ? 1.f : 0.f, blk[(kTilePad - 1) * kTilePad + col]);
+        row0[threadIdx.x] = make_float2(col == kTilePad - 1 ? 1.f : 0.f, at(kTilePad - 1, col));
     }
     __syncthreads();
 
@@ -1048,7 +1119,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan
         constexpr int ROWS = kTileSpecialPart;
         const int which = wave & 1, part = wave >> 1, base = which * (kTilePad / 2);   // (the two on different SIMDs)
         const int col = lane + 64 * half;
-        float fa[ROWS], fw[ROWS], ca = 0.f, cw = 0.f, ahead = blk[base * kTilePad + col];
+        float fa[ROWS], fw[ROWS], ca = 0.f, cw = 0.f, ahead = at(base, col);
 #pragma unroll
         for (int b = 0; b < ROWS; ++b) fa[b] = fw[b] = 0.f;
         for (int t = 0; t < g.s + 3; ++t) {
@@ -1066,7 +1137,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan
                 } else {
                     ca = base + r == col ? 1.f : 0.f;
                     cw = ahead;
-                    ahead = blk[(base + (r + 1 < g.s ? r + 1 : r)) * kTilePad + col];
+                    ahead = at(base + (r + 1 < g.s ? r + 1 : r), col);
                 }
 #pragma unroll
                 for (int b0 = 0; b0 < ROWS; b0 += 8)
@@ -1122,11 +1193,11 @@ __global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan
             for (int i = 0; i < 2; ++i) {
                 const int row = kTilePad / 2 + first + b;
                 fa[b][i] = row == lane + 64 * i ? 1.f : 0.f;
-                fw[b][i] = blk[row * kTilePad + lane + 64 * i];
+                fw[b][i] = at(row, lane + 64 * i);
             }
         float ahead[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) ahead[i] = blk[lane + 64 * i];
+        for (int i = 0; i < 2; ++i) ahead[i] = at(0, lane + 64 * i);
         float2 cs[kTilePart];   // a row's coefficients are read while the row before it is turned
 #pragma unroll
         for (int v = 0; v < kTilePart; ++v) cs[v] = table[first + v];
@@ -1141,7 +1212,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void tile_gradient_kernel(TilePlan
                 } else {                                       // a from I, w from the block, one row ahead
                     ca[i] = r == lane + 64 * i ? 1.f : 0.f;
                     cw[i] = ahead[i];
-                    ahead[i] = blk[(r + 1 < g.s ? r + 1 : r) * kTilePad + lane + 64 * i];
+                    ahead[i] = at(r + 1 < g.s ? r + 1 : r, lane + 64 * i);
                 }
             const float2 *next = coef + (r + 1 < g.s ? kTileTable : 0);
             float prod[kTilePart];

@@ -44,7 +44,8 @@ def test_gram_contraction_at_the_edges_of_its_tiles(n, B):
 
 # the tiles between: contractions of 128 x 128, products of 64 x 64, 128 x 64 and 128 x 128 with loads two steps ahead, odd and
 # even numbers of steps, ragged in both directions
-@pytest.mark.parametrize("n,B", [(288, 12001), (386, 9001), (770, 5001), (800, 4999), (1002, 3001), (1056, 4501)])
+@pytest.mark.parametrize("n,B", [(288, 12001), (386, 9001), (768, 5000), (770, 5001), (800, 4999), (1002, 3001),
+                                 (1056, 4501)])
 def test_tiles_of_middle_sizes(n, B):
     data = inputs.make_custom(n, B, seed=1330 + n)
     print(f"[products] middle n={n} B={B}", flush=True)
