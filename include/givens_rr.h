@@ -153,7 +153,7 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
  *   Per-kernel timing (givens_set_timing) is not recorded for this call.
  */
 #define GIVENS_NOALLOC_MAX_N 1024
-#define GIVENS_NOALLOC_BYTES 30384384 /* n = 1024: flag words; tables of a sweep, or pieces of the matrices of 180 tiles;   */
+#define GIVENS_NOALLOC_BYTES 39829760 /* n = 1024: flag words; tables of a sweep, or pieces of the matrices of 180 tiles;   */
                                       /* U, its pieces, a copy of 512 columns                                              */
 int givens_forward_noalloc(int n, int64_t B, const float *theta, const float *X, float *Y, void *stream);
 

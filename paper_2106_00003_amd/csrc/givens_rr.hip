@@ -80,7 +80,7 @@ struct Workspace {
     Buffer gram;        // Gram form: slices of C = Y G^T, rows x rows floats each
     Buffer matrix;      // wide batches: U or U^T, rows x rows floats
     Buffer pieces;      // ... and its pieces in operand order (product_kernels.hpp)
-    Buffer tile_pieces, tile_blocks, tile_s, tile_tops;   // tiled sweeps (tile_host.hpp)
+    Buffer tile_pieces, tile_blocks, tile_s, tile_operand, tile_tops;   // tiled sweeps (tile_host.hpp)
     Buffer columns;     // ... and a copy of the columns at work when a result overwrites its operand
     Buffer map;         // restricted parametrisation / odd n: index in theta of every entry of E, or -1
     Buffer map_counts;  // free pairs per block (scratch of the map kernels)
@@ -89,7 +89,7 @@ struct Workspace {
     Buffer u_q, u_psi, u_sgn, u_rot, u_phs, u_orient, u_fin;
     int map_rows = 0, map_m = 0; // the (row count, m) the map was built for
     Prepared prepared;
-    Buffer *all[29] = {&tile_pieces, &tile_blocks, &tile_s, &tile_tops, &flag, &scale,
+    Buffer *all[30] = {&tile_pieces, &tile_blocks, &tile_s, &tile_operand, &tile_tops, &flag, &scale,
                        &fwd.table, &fwd.renorm, &fwd.factor, &rev.table, &rev.renorm, &rev.factor,
                        &matrix, &pieces, &columns, &partial, &zeros, &sink, &gram, &map,
                        &u_q, &u_psi, &u_sgn, &u_rot, &u_phs, &u_orient, &u_fin, &chain, &chain_flags};
@@ -461,7 +461,8 @@ constexpr size_t noalloc_tile_bytes(int n)
 {
     if (n < kTileMinN) return 0;
     const TilePlan g = tile_plan(n);
-    return round_up_256(tile_pieces_bytes(g)) + round_up_256(noalloc_tile_cols(n) * sizeof(unsigned));
+    return round_up_256(tile_pieces_bytes(g)) + round_up_256(tile_operand_floats(g, noalloc_tile_cols(n)) * sizeof(float)) +
+           round_up_256(noalloc_tile_cols(n) * sizeof(unsigned));
 }
 constexpr size_t noalloc_tables_bytes(int n) { return std::max(noalloc_sweep_bytes(n), noalloc_tile_bytes(n)); }
 constexpr size_t noalloc_bytes(int n)
@@ -518,6 +519,7 @@ int static_storage(int dev, int n, bool try_forms, CoefStorage<float> *out, Tile
     if (n >= kTileMinN) {
         const TilePlan g = tile_plan(n);
         tiles->pieces = take(tile_pieces_bytes(g));
+        tiles->operand = reinterpret_cast<float *>(take(tile_operand_floats(g, noalloc_tile_cols(n)) * sizeof(float)));
         tiles->tops = reinterpret_cast<unsigned *>(take(noalloc_tile_cols(n) * sizeof(unsigned)));
     }
     at = tables + noalloc_tables_bytes(n);
@@ -952,14 +954,18 @@ bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
 }
 // Whether the tiles are applied to I, to build U, and X multiplied with that.
 bool tiles_by_product(int rows, long long B) { return B >= kProductMinRatio * rows && B >= kProductMinB; }
-// operand_cols: of the operand the tiles are applied to (0: none, or I)
-int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, long long operand_cols, TileBuffers *out)
+// columns: of the operand the tiles are applied to, or of I (0: neither); swept: an operand's
+int tile_storage(Workspace &ws, const TilePlan &g, bool gradient, long long columns, bool swept, TileBuffers *out)
 {
     if (int rc = grow(ws.tile_pieces, tile_pieces_bytes(g))) return rc;
     *out = TileBuffers{};
     out->pieces = ws.tile_pieces.ptr;
-    if (operand_cols) {
-        if (int rc = grow(ws.tile_tops, (size_t)operand_cols * sizeof(unsigned))) return rc;
+    if (columns) {
+        if (int rc = grow(ws.tile_operand, tile_operand_floats(g, columns) * sizeof(float))) return rc;
+        out->operand = reinterpret_cast<float *>(ws.tile_operand.ptr);
+    }
+    if (swept) {
+        if (int rc = grow(ws.tile_tops, (size_t)columns * sizeof(unsigned))) return rc;
         out->tops = reinterpret_cast<unsigned *>(ws.tile_tops.ptr);
     }
     if (gradient) {
@@ -1008,7 +1014,7 @@ int tiles_forward(Workspace *ws, int dev, const Problem &pb, long long B, const 
     const float *swept = X && !tiles_by_product(pb.rows, B) ? X : nullptr;
     if (storage)
         b = *storage;
-    else if (int rc = tile_storage(*ws, g, false, swept ? B : 0, &b))
+    else if (int rc = tile_storage(*ws, g, false, !X || swept ? B : pb.rows, swept != nullptr, &b))
         return rc;
     {
         Span span(0, stream);
@@ -1025,7 +1031,7 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     const TilePlan g = tile_plan(pb.n);
     TileBuffers b;
     const float *swept = dX && !tiles_by_product(pb.rows, B) ? G : nullptr;
-    if (int rc = tile_storage(ws, g, true, swept ? B : 0, &b)) return rc;
+    if (int rc = tile_storage(ws, g, true, swept ? B : dX ? pb.rows : 0, swept != nullptr, &b)) return rc;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     const GramPlan plan = gram_plan(pb.rows, B, cus);

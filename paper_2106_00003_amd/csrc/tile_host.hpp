@@ -37,9 +37,17 @@ constexpr int kTileHalf = kTilePad / 2;
 constexpr int kTileBlock = kTileHalf * kTileHalf;
 inline __host__ __device__ size_t tile_held_offset(const TilePlan &g) { return (size_t)4 * g.P * g.P * kTileBlock; }
 inline __host__ __device__ size_t tile_s_floats(const TilePlan &g) { return tile_held_offset(g) + (size_t)2 * g.P * kTileHalf; }
-// whether the gradient's stages run with 32 columns of a pair of tiles per workgroup (tile_two_sided_narrow_kernel); with
-// restricted parametrisations most pairs have nothing to do, which only the other kernel leaves alone
-inline bool tile_gradient_narrow(const TilePlan &g, int free_rows) { return free_rows >= g.n - 2 && g.P <= 24; }
+// What the stages of an operand of B columns work on: 64 x 32 blocks, those of a piece one after the other, and row 0 behind them
+constexpr int kTileCols = 32;   // columns per step of the apply kernel
+constexpr size_t tile_operand_floats(const TilePlan &g, long long B)
+{
+    return (size_t)((B + kTileCols - 1) / kTileCols) * kTileCols * (2 * g.P * kTileHalf + 1);
+}
+// Whether the gradient's stages run with 32 columns of a pair of tiles per workgroup (tile_two_sided_narrow_kernel): where that
+// gives at most two workgroups per compute unit of 256 (measured, 32 columns against a pair per workgroup: P = 8 8.0 and 14.9 us,
+// P = 17 20.6 and 17.7, P = 24 33.9 and 26.6).  With restricted parametrisations most pairs have nothing to do, which only the
+// other kernel leaves alone.
+inline bool tile_gradient_narrow(const TilePlan &g, int free_rows) { return free_rows >= g.n - 2 && g.P <= 15; }
 
 // What the calls on one problem need: bytes of each buffer.
 struct TileBuffers {
@@ -48,7 +56,8 @@ struct TileBuffers {
     float *S;            // the same
     int *range;          // the same: the range of S's elements and counts of the gradient kernel, behind it
     float *halves;       // the same: sums of special tiles, behind those
-    unsigned *tops;      // of an operand's columns, one word each; null where the tiles are applied to I only
+    float *operand;      // null: there is none
+    unsigned *tops;      // of its columns, one word each; null where the tiles are applied to I only
 };
 constexpr size_t tile_blocks_bytes(const TilePlan &g) { return (size_t)tile_count(g) * kTilePad * kTilePad * sizeof(float); }
 constexpr size_t tile_pieces_bytes(const TilePlan &g) { return (size_t)(tile_count(g) + 1) * kTilePieceWords * 16; }

@@ -506,15 +506,16 @@ __device__ __forceinline__ size_t tile_piece_index(const TilePlan &g, int st, in
     return identity ? (size_t)g.stages * g.P : (size_t)st * g.P + u;
 }
 
-constexpr int kTileCols = 32;   // columns per step of the apply kernel
 struct TileApplyArgs {
     TilePlan g;
     int stage, rows, free_rows;
     long long B;
     const u32x4 *pieces;
-    const float *X;      // nullptr: the identity
-    float *Y;            // X, or another array: then every row is written (first stage of a sweep)
-    long long chunk;     // columns per workgroup
+    bool from_rows, to_rows;   // first and last stage of a sweep, which take every row
+    const float *X;      // the first stage's operand, row by row; nullptr: the identity
+    float *W;            // what the stages work on (tile_operand_floats)
+    float *Y;            // the last stage's result, row by row
+    unsigned chunk;      // columns per workgroup
     const unsigned *tops;   // largest magnitude of every column at the sweep's start, as bits (its stages keep a column's
                             // norm: split_bf16.hpp, "Range"); null: all of the middle range
 };
@@ -523,8 +524,10 @@ struct TileApplyArgs {
 // 32 rows of the result with its part of the matrix in registers throughout.  Per step of kTileCols columns a wavefront brings
 // 32 of the tile's rows (a lane has its values of a column, so cutting them into pieces needs no exchange) and puts the pieces
 // into LDS as fragments, into the buffer of the step's parity: while a step's products run, the next one's rows are cut and the
-// rows after that are on their way.  (An operand of the tiles has less than 4 GiB: fewer than max(2n, 2048) columns.)
-// MEASURED_APPLY
+// rows after that are on their way.  Between a sweep's first and last stage the rows lie in the order in which the wavefronts
+// take and leave them, 32 consecutive bytes a lane: as rows, 16 loads of 4 bytes a lane took a wavefront 1800 cycles to issue
+// and its stores 1000, the 48 matrix instructions of a step 1770.  (An operand of the tiles has fewer than max(2n, 2048)
+// columns, less than 4 GiB.)
 struct TileApplyShared {
     u32x4 panel[2][kTilePad / 16][3][64];
 };
@@ -535,19 +538,23 @@ __device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned bloc
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int u = block % g.P;
-    const unsigned B = (unsigned)a.B, n0 = block / g.P * (unsigned)a.chunk, n1 = n0 + (unsigned)a.chunk < B ? n0 + (unsigned)a.chunk : B;
+    const unsigned B = (unsigned)a.B, n0 = block / g.P * a.chunk, n1 = n0 + a.chunk < B ? n0 + a.chunk : B;
     const Tile x = tile_at(g, a.stage, u);
     const bool identity = tile_is_identity(g, x, a.free_rows);
-    if (n0 >= B || (a.X == a.Y && identity)) return;
+    if (n0 >= B || (!a.from_rows && !a.to_rows && identity)) return;
     // this wavefront's 32 rows: labels first, first - 2, ...; `count` of them are there, row 0 may stand at the end
-    const int local = 32 * wave, in_piece = local % (kTilePad / 2);
-    const bool second = local >= kTilePad / 2;
+    const int local = 32 * wave, in_piece = local % kTileHalf;
+    const bool second = local >= kTileHalf;
     const int count = (second ? x.nb : x.na) - in_piece;
     const int first = tile_label(g, (second ? x.b0 : x.a0)) - 2 * in_piece;
     const bool has_held = u == 0 && local == kTilePad - 32;
     const int skip = first >= a.rows ? 1 : 0;          // the added row of an odd problem is the first of its piece
     // byte offset of row first - 2 (4 half); the rows below it are 8 B bytes apart
     const unsigned row_of_half = (unsigned)(first - 8 * half) * B;
+    // ... and where they are in W
+    const unsigned blocks = (B + kTileCols - 1) / kTileCols;
+    float *const mine = a.W + (size_t)((second ? x.j : x.i) * blocks) * (kTileHalf * kTileCols) + (wave & 1) * 1024;
+    float *const held_row = a.W + (size_t)(2 * g.P) * blocks * (kTileHalf * kTileCols);
 
     // a lane brings 16 rows of one column, those of its half of the fragments
     float xr[16];
@@ -555,14 +562,28 @@ __device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned bloc
     auto fetch = [&](unsigned c0) {
         const unsigned col = c0 + l32 < n1 ? c0 + l32 : n1 - 1;
         if (a.tops) top = a.tops[col];
+        if (a.from_rows) {
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int r = 16 * (q >> 3) + tile_k(half, q & 7), below = 16 * (q >> 3) + tile_k(0, q & 7);
-            const bool there = r < count && r >= skip, held = has_held && r == 31;
-            const unsigned at = there ? (row_of_half - 2 * below * B + col) * 4u : col * 4u;
-            const float v = a.X ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.X) + at)
-                                : ((int)col == (there ? first - 2 * r : 0) ? 1.f : 0.f);
-            xr[q] = there || held ? v : 0.f;
+            for (int q = 0; q < 16; ++q) {
+                const int r = 16 * (q >> 3) + tile_k(half, q & 7), below = 16 * (q >> 3) + tile_k(0, q & 7);
+                const bool there = r < count && r >= skip, held = has_held && r == 31;
+                const unsigned at = there ? (row_of_half - 2 * below * B + col) * 4u : col * 4u;
+                const float v = a.X ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(a.X) + at)
+                                    : ((int)col == (there ? first - 2 * r : 0) ? 1.f : 0.f);
+                xr[q] = there || held ? v : 0.f;
+            }
+        } else {
+            const float *src = mine + c0 / kTileCols * (kTileHalf * kTileCols) + lane * 8;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = *reinterpret_cast<const f32x4 *>(src + (q >> 1) * 512 + (q & 1) * 4);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) xr[4 * q + w] = v[w];
+            }
+            if (has_held) {                            // (its place in the block is nobody's)
+                const float v = held_row[c0 + l32];
+                xr[15] = half ? v : xr[15];
+            }
         }
     };
     float undo[2] = {1.f, 1.f};   // of the columns in the panels
@@ -607,18 +628,30 @@ __device__ __forceinline__ void tile_apply(const TileApplyArgs &a, unsigned bloc
                 stash(buf ^ 1);
                 if (c0 + 2 * kTileCols < n1) fetch(c0 + 2 * kTileCols);
             }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[v] = (acc[v] + small[v]) * undo[buf];
             const unsigned col = c0 + l32;
-            if (col < n1)
+            if (!a.to_rows) {
+                float *to = mine + c0 / kTileCols * (kTileHalf * kTileCols) + lane * 8;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) v[w] = acc[4 * q + w];
+                    *reinterpret_cast<f32x4 *>(to + (q >> 1) * 512 + (q & 1) * 4) = v;
+                }
+                if (has_held && half) held_row[col] = acc[15];
+            } else if (col < n1) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int r = 8 * (v >> 2) + 4 * half + (v & 3), below = 8 * (v >> 2) + (v & 3);
-                    const float y = (acc[v] + small[v]) * undo[buf];
                     char *const to = reinterpret_cast<char *>(a.Y);
                     if (r < count && r >= skip)
-                        *reinterpret_cast<float *>(to + (row_of_half - 2 * below * B + col) * 4u) = y;
+                        *reinterpret_cast<float *>(to + (row_of_half - 2 * below * B + col) * 4u) = acc[v];
                     else if (has_held && r == 31)
-                        a.Y[col] = y;
+                        a.Y[col] = acc[v];
                 }
+            }
         }
 }
 __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyArgs a)
@@ -630,7 +663,8 @@ __global__ __launch_bounds__(2 * kTilePad, 2) void tile_apply_kernel(TileApplyAr
 // ---- the gradient's matrix S (tile_s_floats).
 // S[p][q] = C[row p][row q] - C[row q][row p] for C the sum of its slices.  A workgroup takes two 32 x 32 blocks that mirror each
 // other and reads each slice of them once; the last ones take row 0.  Bound by memory (labels go by two, so half of a line is
-// another block's): MEASURED_ANTISYM
+// another block's): n = 1002 with 7 slices 18 us, n = 4097
+// 50 us (a kernel that summed the slices first, and one that read C twice: 15 + 10 us with 4 slices, 83 us).
 inline unsigned tile_antisym_blocks(const TilePlan &g)
 {
     const int t = 2 * g.P * (kTileHalf / 32);
@@ -821,7 +855,7 @@ __device__ __forceinline__ void tile_store_both(const TileTwoSidedArgs &a, const
 // 32 of its columns (its part of A_y in registers) and all rows, then R = A_x V, a wavefront taking 32 of its rows (its
 // part of A_x in registers).  The other operand of both products is cut into pieces once and shared through LDS, half the
 // contraction at a time: S as its fragments, V as its accumulators are.  Pairs without a rotation are left alone.
-// MEASURED_WIDE
+// n = 3002: 26.6 us a stage.
 struct TileTwoSidedShared {
     u32x4 panel[kTilePad / 32][kTilePad / 32][3][64];
     TileTurn turn[kTilePad / 32];
@@ -936,7 +970,8 @@ __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsign
 // The same for few tiles, where a pair per workgroup leaves compute units idle: a workgroup takes 32 columns of tile y, a
 // wavefront 32 rows of tile x, and only V's pieces and the part of A_y, which all wavefronts need, go through LDS.  The other
 // workgroups of a pair still read what one writes, so the result goes to another array, all of it.  Bound by latency:
-// everything that the first product needs is on its way before it starts, and A_x while it runs.  MEASURED_NARROW
+// everything that the first product needs is on its way before it starts, and A_x while it runs.  n = 1024: 10.2 us a
+// stage (12.2 with S row by row and one accumulator).
 struct TileNarrowShared {
     u32x4 panel[kTilePad / 16][3][64];   // V
     u32x4 matrix[kTilePad / 16][3][64];  // the part of A_y
@@ -1022,8 +1057,8 @@ __device__ __forceinline__ void tile_two_sided_narrow(const TileTwoSidedArgs &a,
 
 // One launch per stage of the reverse sweep: the workgroups before `pair_blocks` take S through it, the others (OPERAND) what
 // dX comes from (G, or I where U^T is wanted).  Neither reads what the other writes, and alone each leaves compute units
-// idle.  Per stage, launches of their own against this one: n = 1002 with I 11.2 + 6.9 and 13 us, n = 1024 with I 12.2 + 8.4
-// and 13.5, n = 4097, m = 512, B = 4096 with G 29 + 21 and 45.
+// idle.  Per stage, launches of their own against this one: n = 1002 with I 8.0 + 5.4 and 9.2 us, n = 2050, B = 2050 with G
+// 17.7 + 11.8 and 26.8, n = 4097, m = 512, B = 4096 with G 25.3 + 13.8 and 32.
 struct TileStageArgs {
     TileTwoSidedArgs s;
     TileApplyArgs a;

@@ -7,8 +7,6 @@
 namespace givens {
 namespace {
 
-// Stage st of Y <- U X or U^T X, the `first` one from X (nullptr: I), the others in place.  `runs` of column blocks for each
-// tile; 0: no tile of the stage has a free pair.  `resident`: workgroups to aim at.
 inline int tile_active(const TilePlan &g, int st, int free_rows)
 {
     if (free_rows >= g.n - 1) return g.P;
@@ -16,59 +14,60 @@ inline int tile_active(const TilePlan &g, int st, int free_rows)
     for (int u = 0; u < g.P; ++u) active += tile_is_identity(g, tile_at(g, st, u), free_rows) ? 0 : 1;
     return active;
 }
-inline long long tile_apply_stage(const TilePlan &g, long long resident, int st, bool first, int rows,
-                                  int free_rows, const TileOperand &op, const u32x4 *pieces, const unsigned *tops,
-                                  TileApplyArgs *out)
+// Stage st of Y <- U X or U^T X: the `first` one takes X, the last one leaves Y.  Returns the runs of column blocks for each tile
+// (0: no tile of the stage has a free pair).  A tile's matrix is worth loading for three steps where there are workgroups
+// enough, for one where the chip holds all of those, and beside `pairs` workgroups of the gradient for two where it holds all,
+// or three where each has a compute unit of its own.  Measured in us, alone with 1, 2, 3, 4, 8 steps: n = 1002 5.4, 6.6, 7.9, 9.2,
+// 15.1, n = 1700 10.1, 9.4, 9.2, 10.4, 15.9, n = 2050 13.3, 13.4, 11.8, 13.4, 16.4, n = 4098, m = 512 17.6, 15.0, 13.8, 14.3, 20.0;
+// beside pairs: n = 1002 10.0, 9.9, 9.2, 10.2, 15.8, n = 1024 10.8, 10.5, 11.2, 10.5, 16.0, n = 4098 36.6, 33.0, 32.2, 32.9, 37.1.
+inline long long tile_apply_stage(const TilePlan &g, int compute_units, long long pairs, int st, bool first, bool last, int rows,
+                                  int free_rows, const TileOperand &op, const TileBuffers &b, TileApplyArgs *out)
 {
-    const int active = first && op.X != op.Y ? g.P : tile_active(g, st, free_rows);   // the first stage writes every row
+    const int active = first || last ? g.P : tile_active(g, st, free_rows);
     if (active == 0) return 0;
     const long long steps = (op.B + kTileCols - 1) / kTileCols;
-    const long long most = std::max(1LL, resident / active);
-    const long long per = (steps + most - 1) / most;
-    *out = TileApplyArgs{g, st, rows, free_rows, op.B, pieces, first ? op.X : op.Y, op.Y, per * kTileCols,
-                         op.X ? tops : nullptr};
+    auto groups = [&](long long per) { return pairs + active * ((steps + per - 1) / per); };
+    long long per = 3;
+    if (!pairs && groups(1) <= 2LL * compute_units) per = 1;
+    if (pairs && groups(3) > compute_units && groups(2) <= 2LL * compute_units) per = 2;
+    *out = TileApplyArgs{g, st, rows, free_rows, op.B, static_cast<const u32x4 *>(b.pieces), first, last, op.X, b.operand, op.Y,
+                         (unsigned)(per * kTileCols), op.X ? b.tops : nullptr};
     return (steps + per - 1) / per;
 }
 // Y <- U X (forward, pieces of the transposed matrices) or U^T X
-inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileOperand &op,
-                       const u32x4 *pieces, const unsigned *tops, bool forward, hipStream_t stream)
+inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileOperand &op, const TileBuffers &b,
+                       bool forward, hipStream_t stream)
 {
-    // at most what the chip holds at once (eight wavefronts per compute unit)
-    const long long resident = (long long)compute_units * 8 / (kTilePad / 32);
     for (int i = 0; i < g.stages; ++i) {
         TileApplyArgs a;
-        const long long runs = tile_apply_stage(g, resident, forward ? g.stages - 1 - i : i, i == 0, rows, free_rows,
-                                                op, pieces, tops, &a);
+        const long long runs = tile_apply_stage(g, compute_units, 0, forward ? g.stages - 1 - i : i, i == 0,
+                                                i == g.stages - 1, rows, free_rows, op, b, &a);
         if (runs)
             hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
     }
 }
 inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
-                          const u32x4 *pieces, const float *C, int slices, float *S, float *blocks, int *range, float *halves,
-                          const unsigned *tops, float *dtheta, const TileOperand &op, hipStream_t stream)
+                          const TileBuffers &b, const float *C, int slices, float *dtheta, const TileOperand &op,
+                          hipStream_t stream)
 {
+    const u32x4 *pieces = static_cast<const u32x4 *>(b.pieces);
     const bool narrow = tile_gradient_narrow(g, free_rows);
     const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2) * (narrow ? kTilePad / 32 : 1);
-    float *second = narrow ? S + tile_s_floats(g) : nullptr;
-    hipLaunchKernelGGL(tile_antisym_kernel, dim3(tile_antisym_blocks(g)), dim3(256), 0, stream, g, rows, slices, C, S, range);
-    const long long slots = (long long)compute_units * 8 / (kTilePad / 32);
-    float *in = S, *out = second ? second : S;
+    float *second = narrow ? b.S + tile_s_floats(g) : nullptr;
+    hipLaunchKernelGGL(tile_antisym_kernel, dim3(tile_antisym_blocks(g)), dim3(256), 0, stream, g, rows, slices, C, b.S, b.range);
+    float *in = b.S, *out = second ? second : b.S;
     for (int st = 0; st < g.stages; ++st) {
-        TileStageArgs a{TileTwoSidedArgs{g, st, free_rows, pieces, in, out, blocks, range}, {}, pairs};
+        TileStageArgs a{TileTwoSidedArgs{g, st, free_rows, pieces, in, out, b.blocks, b.range}, {}, pairs};
         long long runs = 0;
-        if (op.Y) {   // beside the pairs that have something to do
-            const long long idle = g.P - tile_active(g, st, free_rows);
-            const long long busy = narrow ? pairs : pairs - idle * (idle + 1) / 2, room = slots - busy;
-            runs = tile_apply_stage(g, std::max(room, slots / 2), st, st == 0, rows, free_rows, op, pieces, tops,
-                                    &a.a);
-        }
+        if (op.Y)
+            runs = tile_apply_stage(g, compute_units, pairs, st, st == 0, st == g.stages - 1, rows, free_rows, op, b, &a.a);
         const auto kernel = narrow ? (runs ? tile_stage_kernel<true, true> : tile_stage_kernel<true, false>)
                                    : (runs ? tile_stage_kernel<false, true> : tile_stage_kernel<false, false>);
         hipLaunchKernelGGL(kernel, dim3((unsigned)(pairs + runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
         if (second) std::swap(in, out);
     }
     hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(2 * g.P + tile_count(g))), dim3(kTileThreads), 0, stream, g, theta,
-                       map, free_rows, blocks, range + kTileRangeWords, halves, dtheta);
+                       map, free_rows, b.blocks, b.range + kTileRangeWords, b.halves, dtheta);
 }
 } // namespace
 
@@ -84,13 +83,12 @@ void tiles_build(const TilePlan &g, const float *theta, const int *map, int free
 void tiles_apply(const TilePlan &g, int compute_units, int rows, int free_rows, const TileBuffers &b, const TileOperand &op,
                  bool forward, hipStream_t stream)
 {
-    tile_apply(g, compute_units, rows, free_rows, op, static_cast<const u32x4 *>(b.pieces), b.tops, forward, stream);
+    tile_apply(g, compute_units, rows, free_rows, op, b, forward, stream);
 }
 void tiles_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
                     const TileBuffers &b, const float *C, int slices, float *dtheta, const TileOperand &op, hipStream_t stream)
 {
-    tile_gradient(g, compute_units, rows, free_rows, theta, map, static_cast<const u32x4 *>(b.pieces), C, slices, b.S, b.blocks, b.range,
-                  b.halves, b.tops, dtheta, op, stream);
+    tile_gradient(g, compute_units, rows, free_rows, theta, map, b, C, slices, dtheta, op, stream);
 }
 
 } // namespace givens
