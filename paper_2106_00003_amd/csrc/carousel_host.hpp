@@ -411,29 +411,35 @@ inline int wave64_slots(int n)
         if (n >= 10 && n % (2 * m) == 0 && n / (2 * m) <= 64) return m;
     return 0;
 }
-// Where they are the faster ones.  LDS kernels against them in us: forward n = 64, B = 64 33 / 12, 16384 91 / 40; n = 512,
-// B = 1024 277 / 103, 16384 2112 / 557; n = 1024, B = 256 973 / 278, 1024 982 / 467, 4096 1644 / 1844; backward n = 32,
-// B = 64 23 / 15, 4096 57 / 40, 16384 100 / 121; n = 64, B = 16384 169 / 155; n = 512, B = 1024 776 / 331, 16384
-// 5461 / 2424; n = 1024, B = 1024 3050 / 1765, 4096 5994 / 6016.
-inline bool wave64_supported(int n, long long B, bool backward)
-{
-    const int slots = wave64_slots(n);
-    if (slots == 0 || (slots == 8 && B > 2048)) return false;
-    return !backward || B <= 256LL * n;
-}
-// columns per strip of the forward sweep: every strip reads the whole coefficient table, so wide strips soon pay where
-// that is long (n = 512, B = 1024: one column 133 us, two 103; B = 4096: two 264, four 160; n = 256, B = 1024 39 / 43)
+// They are the faster ones throughout.  LDS kernels against them in us: forward n = 64, B = 64 33 / 11, 65536 118 / 106; n = 512,
+// B = 1024 277 / 92; n = 1024, B = 256 973 / 199, 4096 1632 / 616; backward n = 32, B = 64 23 / 15, 65536 292 / 201; n = 64,
+// B = 65536 484 / 314; n = 512, B = 1024 776 / 208; n = 1024, B = 1024 3050 / 769, 9000 17466 / 4542.
+inline bool wave64_supported(int n) { return wave64_slots(n) != 0; }
+// Columns per strip of the forward sweep, and strips per workgroup: every strip reads the whole coefficient table, so wide
+// strips and shared L1s soon pay where that is long.  Measured in us, one strip and four per workgroup: n = 512, B = 64 73 / 105,
+// 512 88 / 98, 1024 98 / 89 (two columns 92 / 100), 4000 with four columns 134 in fours; n = 1024, B = 256 201 / 259, 1024 with
+// two columns 248 / 262, 2000 295 in fours; n = 256, B = 2000 47 / 39 (two columns 45 / 41).
+constexpr int kWave64Strips = 4;
 inline int wave64_fwd_width(int n, long long B)
 {
     const int slots = wave64_slots(n);
-    if (B <= (slots <= 2 ? 1024 : 512)) return 1;
+    if (B <= (slots == 8 ? 512 : 1024)) return 1;
     return B <= 2048 || slots == 8 ? 2 : 4;
 }
-// columns per strip of the reverse sweep: every strip costs a row of partial sums
-inline int wave64_bwd_width(int n, long long B) { return B <= 256 ? 1 : B <= 512 || wave64_slots(n) == 8 ? 2 : 4; }
+inline int wave64_fwd_strips(long long strips) { return strips > 512 ? kWave64Strips : 1; }
+// Columns per row of partial sums of the reverse sweep: those of a workgroup's strips.  Measured in us with the second stage,
+// one, two and four columns a strip: n = 512, B = 1024 213 / 221 / 321, 4000 749 / 452 / 355, n = 256, B = 1024 70 / 78 / 115,
+// 4096 183 / 140 / 135, n = 64, B = 16384 156 / 115 / 97, n = 1024, B = 256 522 / 643, 1024 879 / 763; a strip per workgroup and row:
+// n = 512, B = 64 132 us against 143.
+inline int wave64_bwd_strips(long long B) { return B <= 128 ? 1 : kWave64Strips; }
+inline int wave64_bwd_width(int n, long long B)
+{
+    const bool eight = wave64_slots(n) == 8;
+    return wave64_bwd_strips(B) * (B <= (eight ? 768 : 1024) ? 1 : B <= 2048 || eight ? 2 : 4);
+}
 int wave64_forward(int n, int rows, long long B, const double2 *table, const double *X, double *Y, int identity, int mirror,
                    hipStream_t stream);
-int wave64_backward(int n, int rows, long long B, long long strip0, long long strips, const double2 *table, const double *Y,
+int wave64_backward(int n, int rows, long long B, long long group0, long long groups, const double2 *table, const double *Y,
                     const double *G, double *dX, double *partial, hipStream_t stream);
 
 } // namespace givens

@@ -213,7 +213,7 @@ __global__ void scaled_scan_kernel(int n, const float *__restrict__ theta, const
 //     the forward sweep does a -= T b, b += S a, a -= T b on the stored values, the reverse sweep the same
 //     with the signs flipped.
 template <typename T>
-__global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int *__restrict__ map, int mirror,
+__global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int *__restrict__ map, int mirror, int slots,
                                   const unsigned *flag, float scaled_max, const float *__restrict__ D,
                                   typename Pair2<T>::type *__restrict__ table, T *__restrict__ factor)
 {
@@ -251,7 +251,8 @@ __global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int 
                 out.y = (T)(fac * s);
             }
         }
-        table[e] = out;
+        // slots of a lane of the sweep that reads the table (wave_f64_kernels.hpp): first slots of 64 lanes, second slots, ...
+        table[slots ? ((long long)k * slots + p % slots) * 64 + p / slots : e] = out;
         if (factor) factor[e] = (T)fac;
     }
 }

@@ -386,12 +386,12 @@ struct CoefStorage {
 inline int renorm_periods(int n) { return (n - 1 + kRenormPeriod - 1) / kRenormPeriod; }
 
 template <typename T>
-int workspace_coef_storage(Workspace &ws, CoefSet &set, int n, bool want_factor, bool try_forms, hipStream_t stream,
+int workspace_coef_storage(Workspace &ws, CoefSet &set, int n, bool want_factor, bool try_forms, int slots, hipStream_t stream,
                            CoefStorage<T> *out, bool for_prepare)
 {
     using P2 = typename Pair2<T>::type;
     const long long N = (long long)n * (n - 1) / 2;
-    if (int rc = grow(set.table, (size_t)N * sizeof(P2))) return rc;
+    if (int rc = grow(set.table, (size_t)(slots ? (n - 1) * 64LL * slots : N) * sizeof(P2))) return rc;
     out->table = reinterpret_cast<P2 *>(set.table.ptr);
     if (want_factor) {
         if (int rc = grow(set.factor, (size_t)N * sizeof(T))) return rc;
@@ -532,10 +532,11 @@ int static_storage(int dev, int n, bool try_forms, CoefStorage<float> *out, Tile
 
 // Launches the coefficient kernels of one sweep direction.  `forward` picks the direction of the scaled /
 // lifted forms' row factors; `policy.try_forms` adds those forms (range check unless `range_known`: the
-// flag already holds max |theta| of this theta).
+// flag already holds max |theta| of this theta).  slots: per lane of the sweep that is to read the table, where it wants it in
+// the order of its lanes (coef_table_kernel), else 0.
 template <typename T>
 int build_coefs(const CoefStorage<T> &st, const Problem &pb, const T *theta, bool forward, FormPolicy policy,
-                hipStream_t stream, Coefs<T> *out, int mirror = 0, bool range_known = false)
+                hipStream_t stream, Coefs<T> *out, int mirror = 0, int slots = 0, bool range_known = false)
 {
     const int n = pb.n;
     const int *map = pb.map;
@@ -564,7 +565,7 @@ int build_coefs(const CoefStorage<T> &st, const Problem &pb, const T *theta, boo
             out->renorm = reinterpret_cast<const float2 *>(st.renorm);
         }
     }
-    hipLaunchKernelGGL(coef_table_kernel<T>, dim3(blocks), dim3(threads), 0, stream, n, theta, map, mirror,
+    hipLaunchKernelGGL(coef_table_kernel<T>, dim3(blocks), dim3(threads), 0, stream, n, theta, map, mirror, slots,
                        static_cast<const unsigned *>(flag), policy.scaled_max, static_cast<const float *>(st.scale),
                        st.table, forward ? nullptr : st.factor);
     GIVENS_HIP(hipGetLastError());
@@ -583,13 +584,13 @@ int build_coefs(const CoefStorage<T> &st, const Problem &pb, const T *theta, boo
 // (range_known: an earlier build of the same givens_prepare call has made the range check already)
 template <typename T>
 int build_coefs(Workspace &ws, CoefSet &set, const Problem &pb, const T *theta, bool forward, FormPolicy policy,
-                hipStream_t stream, Coefs<T> *out, int mirror = 0, bool range_known = false, bool for_prepare = false)
+                hipStream_t stream, Coefs<T> *out, int mirror = 0, int slots = 0, bool range_known = false, bool for_prepare = false)
 {
     CoefStorage<T> st;
     const bool forms = policy.try_forms && std::is_same<T, float>::value;
-    if (int rc = workspace_coef_storage<T>(ws, set, pb.n, !forward, forms, stream, &st, for_prepare))
+    if (int rc = workspace_coef_storage<T>(ws, set, pb.n, !forward, forms, slots, stream, &st, for_prepare))
         return rc;
-    return build_coefs<T>(st, pb, theta, forward, policy, stream, out, mirror, range_known);
+    return build_coefs<T>(st, pb, theta, forward, policy, stream, out, mirror, slots, range_known);
 }
 
 // From n = 2048 on (four or more arcs per thread and block) the LDS-family kernels run the instance that fetches
@@ -630,7 +631,7 @@ int pick_forward_family(int n, long long B, int choice, Families *out)
     if (choice == GIVENS_KERNEL_CAROUSEL && !can_carousel) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_COLUMN && !can_column) return GIVENS_ERR_UNSUPPORTED;
     if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
-    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n, B, false);
+    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n);
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = !out->carousel && can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
@@ -645,7 +646,7 @@ int pick_backward_family(int n, long long B, int choice, Families *out)
     if (choice == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;   // (not by way of a family: tiles_* below)
     // the family that sweeps (the n x n operand of the Gram form, or all B columns); the column family has
     // no reverse sweep of its own and borrows the LDS family's
-    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n, B, true);
+    out->wave64 = std::is_same<T, double>::value && choice == GIVENS_KERNEL_AUTO && wave64_supported(n);
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
@@ -1113,7 +1114,9 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
         }
     } else {
         invalidate_prepared(*ws, true, false);
-        if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose)) return rc;
+        if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose,
+                                    fam.wave64 ? wave64_slots(n) : 0))
+            return rc;
     }
     return run_forward<T>(ws, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream);
 }
@@ -1198,7 +1201,7 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
     Coefs<T> coefs;
     if (int rc = build_coefs<T>(*ws, ws->rev, pb, theta, false,
                                 form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept)),
-                                stream, &coefs))
+                                stream, &coefs, 0, fam.wave64 ? wave64_slots(n) : 0))
         return rc;
     return run_backward<T>(*ws, dev, pb, B, coefs, fam, opt, Y, G, dX, dtheta, stream);
 }
@@ -1250,7 +1253,7 @@ int64_t prepare_impl(int rows, int m, const float *theta, int directions, void *
             }
             hipLaunchKernelGGL(reset_flag_kernel, dim3(1), dim3(1), 0, stream, reinterpret_cast<unsigned *>(ws->flag.ptr) + 2);
         }
-        const int rc = build_coefs<float>(*ws, set, pb, theta, forward, pol, stream, &c, 0, range_known, true);
+        const int rc = build_coefs<float>(*ws, set, pb, theta, forward, pol, stream, &c, 0, 0, range_known, true);
         range_known = range_known || pol.try_forms;
         return rc;
     };

@@ -8,13 +8,18 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
 #include <utility>
 
+#include "carousel_host.hpp"
 #include "rr_index.h"
 
 namespace givens {
 
 constexpr int kWave64Depth = 4;   // ring of coefficients, in blocks
+// Strips of a workgroup, one wavefront each, where there are many.  They read the same coefficients within a few blocks of each
+// other, so most come from the compute unit's L1, and in the reverse sweep they share a row of partial sums.  Where there are no
+// more strips than places for them each has a compute unit's L1 to itself (wave64_fwd_strips, wave64_bwd_strips).
 constexpr int wave64_unroll(int M) { return M > kWave64Depth ? M : kWave64Depth; }   // a multiple of both (powers of two)
 
 template <int CTRL>
@@ -28,16 +33,18 @@ __device__ __forceinline__ double wave64_shift(double incoming, double v)
 __device__ __forceinline__ double wave64_from_next(double incoming, double v) { return wave64_shift<0x130>(incoming, v); }
 __device__ __forceinline__ double wave64_from_prev(double incoming, double v) { return wave64_shift<0x138>(incoming, v); }
 
+// A row of the table lists the first slots of 64 lanes, then the second ones, and so on: a load of a wavefront is 1 KB of
+// consecutive memory (with a lane's slots side by side each load of eight-slot lanes touched 64 lines, and four wavefronts of a
+// compute unit had no use of its L1: n = 1024, B = 256 forward 904 us).
 template <int M>
 struct Wave64Coefs {
     double2 cs[kWave64Depth][M];
-    const double2 *lane;   // table + slots of this lane
-    int H;
+    const double2 *lane;   // table + first slot of this lane
     __device__ __forceinline__ void load(int k, int slot)
     {
-        const double2 *src = lane + (long long)k * H;
+        const double2 *src = lane + (long long)k * (64 * M);
 #pragma unroll
-        for (int r = 0; r < M; ++r) cs[slot][r] = src[r];
+        for (int r = 0; r < M; ++r) cs[slot][r] = src[64 * r];
     }
 };
 
@@ -110,18 +117,18 @@ struct Wave64Fwd {
 // rows: the operand's row count (n, or n - 1 when n pads an odd problem); mirror: rows relabelled r -> n - r, with mirrored
 // tables the launch applies U^T (carousel_kernels.hpp)
 template <int M, int W>
-__global__ __launch_bounds__(64, 1) void wave64_forward_kernel(int n, int rows, long long B, const double2 *__restrict__ table,
+__global__ __launch_bounds__(64 * kWave64Strips, 1) void wave64_forward_kernel(int n, int rows, long long B, const double2 *__restrict__ table,
                                                                const double *X, double *Y, int identity, int mirror)
 {
     using State = Wave64Fwd<M, W>;
     State st;
-    const int l = threadIdx.x, L = n / (2 * M);
+    const int l = threadIdx.x & 63, L = n / (2 * M);
     const bool idle = l >= L;
     st.lane = l;
     st.lanes = L;
-    st.co.H = n >> 1;
-    st.co.lane = table + (idle ? 0 : l * M);
-    const long long b0 = (long long)blockIdx.x * W;
+    st.co.lane = table + (idle ? 0 : l);
+    const long long b0 = ((long long)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * W;
+    if (b0 >= B) return;
     auto place = [&](int label) { return (mirror && label) ? n - label : label; };
     auto bring = [&](double(&v)[W], int row) {
 #pragma unroll
@@ -151,14 +158,40 @@ __global__ __launch_bounds__(64, 1) void wave64_forward_kernel(int n, int rows, 
     }
 }
 
-template <int M, int W>
+// Reverse sweep.  With several strips in a workgroup their sums of four blocks go to LDS, and after a barrier each wavefront adds
+// those of one block, in strip order, and stores them.  So a row of partial sums stands for 4 W columns, while a wavefront's
+// block has the arithmetic of W: n = 512, B = 1024 with the second stage 213 us, 332 with a wavefront of four columns per row;
+// n = 1024, B = 1024 763 and 1764 (two columns per row).
+template <int M, int W, int STRIPS>
 struct Wave64Bwd {
     static constexpr int kUnroll = wave64_unroll(M);
     double zt[M][W], zb[M][W], gt[M][W], gb[M][W];
     Wave64Coefs<M> co;
-    int lane, lanes;
+    int lane, lanes, wave, H;
     bool idle;
-    double *part;   // this strip's row of partial sums + slots of this lane
+    double *part;   // this workgroup's row of partial sums + slots of this lane
+    struct Sums {
+        double of[kWave64Depth][STRIPS][M][64];
+    };
+    Sums *sums_of;  // two of them, which take turns
+    int turn;
+    // sums of the `count` blocks from k0 on are in LDS
+    __device__ __forceinline__ void flush(int k0, int count)
+    {
+        if constexpr (STRIPS == 1) return;   // (stored by the blocks themselves)
+        __syncthreads();
+        const auto &s = sums_of[turn].of;
+        turn ^= 1;
+        if (wave >= count || idle) return;
+        double *dst = part + (long long)(k0 + wave) * H;
+#pragma unroll
+        for (int r = 0; r < M; ++r) {
+            double v = s[wave][0][r][lane];
+#pragma unroll
+            for (int w = 1; w < STRIPS; ++w) v += s[wave][w][r][lane];
+            dst[r] = v;
+        }
+    }
     template <int U>
     __device__ __forceinline__ void move(double (&t)[M][W], double (&b)[M][W])
     {
@@ -178,8 +211,9 @@ struct Wave64Bwd {
             }
         }
     }
+    // `place`: of this block's sums in LDS
     template <int C, bool LAST, bool AHEAD>
-    __device__ __forceinline__ void step(int k)
+    __device__ __forceinline__ void step(int k, int place = C % kWave64Depth)
     {
         constexpr int U = C % M, D = kWave64Depth;
         if constexpr (AHEAD) co.load(k + (D - 1), (C + D - 1) % D);
@@ -201,33 +235,43 @@ struct Wave64Bwd {
             }
             sums[r] = sum;
         }
-        if (!idle) {
-            double *dst = part + (long long)k * co.H;
+        if constexpr (STRIPS == 1) {
+            if (!idle)
 #pragma unroll
-            for (int r = 0; r < M; ++r) dst[r] = sums[r];
+                for (int r = 0; r < M; ++r) part[(long long)k * H + r] = sums[r];
+        } else {
+#pragma unroll
+            for (int r = 0; r < M; ++r) sums_of[turn].of[place][wave][r][lane] = sums[r];
         }
         if constexpr (!LAST) {
             move<U>(zt, zb);
             move<U>(gt, gb);
         }
     }
+    template <int C, bool LAST, bool AHEAD>
+    __device__ __forceinline__ void step_and_flush(int k)
+    {
+        step<C, LAST, AHEAD>(k);
+        if constexpr (C % kWave64Depth == kWave64Depth - 1 || LAST) flush(k - C % kWave64Depth, C % kWave64Depth + 1);
+    }
     template <int... Cs>
     __device__ __forceinline__ void group(int k, std::integer_sequence<int, Cs...>)
     {
-        (step<Cs, false, true>(k + Cs), ...);
+        (step_and_flush<Cs, false, true>(k + Cs), ...);
     }
     template <int... Cs>
     __device__ __forceinline__ void tail(int k, std::integer_sequence<int, Cs...>)
     {
-        (step<Cs, Cs == kUnroll - 2, (kUnroll - 2 - Cs >= kWave64Depth - 1)>(k + Cs), ...);
+        (step_and_flush<Cs, Cs == kUnroll - 2, (kUnroll - 2 - Cs >= kWave64Depth - 1)>(k + Cs), ...);
     }
     __device__ __forceinline__ void sweep(int n)
     {
         int k = 0;
-        for (; k < n % kUnroll; ++k) {
+        for (; k < n % kUnroll; ++k) {   // (one slot per lane only, three blocks at most)
             co.load(k, 0);
-            step<0, false, false>(k);
+            step<0, false, false>(k, k);
         }
+        if (k) flush(0, k);
 #pragma unroll
         for (int d = 0; d < kWave64Depth - 1; ++d)
             if (k + d <= n - 2) co.load(k + d, d);
@@ -236,23 +280,27 @@ struct Wave64Bwd {
     }
 };
 
-// strips strip0 + blockIdx.x of W columns; partial: [gridDim.x][N]
-template <int M, int W>
-__global__ __launch_bounds__(64, 1) void wave64_backward_kernel(int n, int rows, long long B, long long strip0,
+// strips of W columns, STRIPS of them per workgroup, from group strip0 + blockIdx.x on; partial: [gridDim.x][N]
+template <int M, int W, int STRIPS>
+__global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, int rows, long long B, long long strip0,
                                                                 const double2 *__restrict__ table, const double *Yin,
                                                                 const double *G, double *dX, double *__restrict__ partial)
 {
-    using State = Wave64Bwd<M, W>;
+    using State = Wave64Bwd<M, W, STRIPS>;
+    __shared__ std::conditional_t<STRIPS == 1, char, typename State::Sums> sums[2];
     State st;
-    const int l = threadIdx.x, L = n / (2 * M);
+    if constexpr (STRIPS > 1) st.sums_of = sums;
+    st.turn = 0;
+    st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = threadIdx.x & 63, L = n / (2 * M);
     const bool idle = l >= L;
     st.lane = l;
     st.lanes = L;
     st.idle = idle;
-    st.co.H = n >> 1;
-    st.co.lane = table + (idle ? 0 : l * M);
+    st.H = n >> 1;
+    st.co.lane = table + (idle ? 0 : l);
     st.part = partial + (long long)blockIdx.x * (n - 1) * (n >> 1) + (idle ? 0 : l * M);
-    const long long b0 = (strip0 + blockIdx.x) * W;
+    const long long b0 = ((strip0 + blockIdx.x) * STRIPS + st.wave) * W;   // (past the end: zeros)
     auto bring = [&](double(&v)[W], const double *src, int row) {
 #pragma unroll
         for (int x = 0; x < W; ++x) v[x] = !idle && row < rows && b0 + x < B ? src[(long long)row * B + b0 + x] : 0.0;

@@ -47,7 +47,8 @@ def test_every_even_size_up_to_136(B):
 
 
 @pytest.mark.parametrize("n,B", [(64, 256), (64, 513), (64, 4099), (140, 257), (256, 512), (252, 1025), (504, 513),
-                                 (512, 1024), (512, 4097), (528, 300), (1024, 70), (1008, 520)])
+                                 (512, 1024), (512, 4097), (528, 300), (1024, 70), (1008, 520), (32, 128), (32, 129),
+                                 (260, 1026), (32, 9001), (1024, 2401)])
 def test_strip_widths_against_the_lds_kernels(n, B):
     print(f"[wave64] n={n} B={B}", flush=True)
     data = inputs.make_custom(n, B, seed=4200 + n, dtype=np.float64)
