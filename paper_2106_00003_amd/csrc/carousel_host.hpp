@@ -219,10 +219,11 @@ struct UnitaryCarouselBwdArgs {
     hipStream_t stream;
 };
 // Defined in unitary_carousel_fwd.hip / unitary_carousel_bwd.hip.  unitary_carousel_coefficients runs the
-// phase pass and the table kernel for one sweep direction (q: N 8-byte words, turn: N 4-byte words of scratch; orient may be
-// null for the forward direction).
+// phase pass and the table kernel for one sweep direction (q: N 8-byte words, turn: N 4-byte words, scratch:
+// unitary_scan_bytes(n) of scratch; orient may be null for the forward direction).
+size_t unitary_scan_bytes(int n);
 int unitary_carousel_coefficients(int n, const float *theta, const float *phi, int reverse, uint2 *q, unsigned *turn,
-                                  float *sgn, float2 *rot, float2 *phs, float *orient, float2 *fin, hipStream_t stream);
+                                  void *scratch, float *sgn, float2 *rot, float2 *phs, float *orient, float2 *fin, hipStream_t stream);
 int unitary_carousel_forward_m8(const UnitaryCarouselFwdArgs &a, int waves, int W);
 int unitary_carousel_backward_m4(const UnitaryCarouselBwdArgs &a, int waves, int W);
 int unitary_carousel_backward_m2(const UnitaryCarouselBwdArgs &a, int waves, int W);

@@ -1524,7 +1524,8 @@ int unitary_carousel_coefs(Workspace &ws, int n, const float *theta, const float
     if (int rc = grow(ws.u_sgn, N * sizeof(float))) return rc;
     if (int rc = grow(ws.u_rot, N * sizeof(float2))) return rc;
     if (int rc = grow(ws.u_phs, N * sizeof(float2))) return rc;
-    if (int rc = grow(ws.u_fin, (size_t)n * sizeof(float2))) return rc;
+    const size_t fin_bytes = ((size_t)n * sizeof(float2) + 255) / 256 * 256;   // the phase pass's scratch behind it
+    if (int rc = grow(ws.u_fin, fin_bytes + unitary_scan_bytes(n))) return rc;
     if (reverse)
         if (int rc = grow(ws.u_orient, N * sizeof(float))) return rc;
     Span span(0, stream);
@@ -1532,6 +1533,7 @@ int unitary_carousel_coefs(Workspace &ws, int n, const float *theta, const float
     if (int rc = unitary_carousel_coefficients(n, theta, phi, reverse ? 1 : 0,
                                                reinterpret_cast<uint2 *>(ws.u_q.ptr),
                                                reinterpret_cast<unsigned *>(ws.u_psi.ptr),
+                                               static_cast<unsigned char *>(ws.u_fin.ptr) + fin_bytes,
                                                reinterpret_cast<float *>(ws.u_sgn.ptr),
                                                reinterpret_cast<float2 *>(ws.u_rot.ptr),
                                                reinterpret_cast<float2 *>(ws.u_phs.ptr), orient,

@@ -4,38 +4,41 @@
 
 namespace givens {
 
-template <bool REVERSE>
-static void launch_phase_scan(int n, const uint2 *q, unsigned *turn, float2 *fin, hipStream_t stream)
+template <bool REVERSE, int PER>
+static void launch_phase_scan(int n, int threads, const uint2 *q, unsigned *turn, const PhaseScan &scan, hipStream_t stream)
 {
-    // one thread per pair up to 1024 threads, then two pairs per thread (more pairs per thread measured slower: the pass is bound by the
-    // latency of its LDS round trip per pair, not by the barrier)
-    const int H = n / 2;
-    if (H <= kPhaseScanThreads)
-        hipLaunchKernelGGL((unitary_phase_scan_kernel<REVERSE, 1>), dim3(1), dim3((H + 63) / 64 * 64), 0, stream, n, q,
-                           turn, fin);
-    else
-        hipLaunchKernelGGL((unitary_phase_scan_kernel<REVERSE, 2>), dim3(1), dim3(kPhaseScanThreads), 0, stream, n, q,
-                           turn, fin);
+    hipLaunchKernelGGL((unitary_phase_scan_kernel<REVERSE, PER, true>), dim3(scan.chunks), dim3(threads), 0, stream, n, q, turn,
+                       scan);
+    hipLaunchKernelGGL((unitary_phase_scan_kernel<REVERSE, PER, false>), dim3(scan.chunks), dim3(threads), 0, stream, n, q, turn,
+                       scan);
 }
 
-int unitary_carousel_coefficients(int n, const float *theta, const float *phi, int reverse, uint2 *q, unsigned *turn,
+size_t unitary_scan_bytes(int n) { return (size_t)n * (2 * sizeof(unsigned) + phase_chunks(n) * sizeof(uint2)); }
+
+template <bool REVERSE>
+static void coefficients(int n, const float *theta, const float *phi, uint2 *q, unsigned *turn, void *scratch, float *sgn,
+                         float2 *rot, float2 *phs, float *orient, float2 *fin, hipStream_t stream)
+{
+    const long long N = (long long)n * (n - 1) / 2;
+    const int threads = 256, H = n / 2, chunks = phase_chunks(n);
+    const unsigned blocks = (unsigned)((N + threads - 1) / threads < 8192 ? (N + threads - 1) / threads : 8192);
+    uint2 *const maps = static_cast<uint2 *>(scratch);
+    unsigned *const flips = reinterpret_cast<unsigned *>(maps + (size_t)chunks * n);
+    const PhaseScan scan{chunks, maps, flips, flips + n};
+    hipLaunchKernelGGL(unitary_phase_input_kernel<REVERSE>, dim3(blocks), dim3(threads), 0, stream, n, theta, phi, q);
+    // one thread per pair up to 1024 threads, then two pairs per thread
+    if (H <= kPhaseScanThreads)
+        launch_phase_scan<REVERSE, 1>(n, (H + 63) / 64 * 64, q, turn, scan, stream);
+    else
+        launch_phase_scan<REVERSE, 2>(n, kPhaseScanThreads, q, turn, scan, stream);
+    hipLaunchKernelGGL(unitary_carousel_table_kernel<REVERSE>, dim3(blocks), dim3(threads), 0, stream, n, theta, turn, scan, sgn,
+                       rot, phs, orient, fin);
+}
+int unitary_carousel_coefficients(int n, const float *theta, const float *phi, int reverse, uint2 *q, unsigned *turn, void *scratch,
                                   float *sgn, float2 *rot, float2 *phs, float *orient, float2 *fin, hipStream_t stream)
 {
     if (!unitary_carousel_supported(n) || n / 2 > 2 * kPhaseScanThreads) return GIVENS_ERR_UNSUPPORTED;
-    const long long N = (long long)n * (n - 1) / 2;
-    const int threads = 256;
-    const unsigned blocks = (unsigned)((N + threads - 1) / threads < 8192 ? (N + threads - 1) / threads : 8192);
-    if (reverse) {
-        hipLaunchKernelGGL(unitary_phase_input_kernel<true>, dim3(blocks), dim3(threads), 0, stream, n, theta, phi, q);
-        launch_phase_scan<true>(n, q, turn, fin, stream);
-        hipLaunchKernelGGL(unitary_carousel_table_kernel<true>, dim3(blocks), dim3(threads), 0, stream, n, theta, turn,
-                           sgn, rot, phs, orient);
-    } else {
-        hipLaunchKernelGGL(unitary_phase_input_kernel<false>, dim3(blocks), dim3(threads), 0, stream, n, theta, phi, q);
-        launch_phase_scan<false>(n, q, turn, fin, stream);
-        hipLaunchKernelGGL(unitary_carousel_table_kernel<false>, dim3(blocks), dim3(threads), 0, stream, n, theta, turn,
-                           sgn, rot, phs, orient);
-    }
+    (reverse ? coefficients<true> : coefficients<false>)(n, theta, phi, q, turn, scratch, sgn, rot, phs, orient, fin, stream);
     return GIVENS_OK;
 }
 

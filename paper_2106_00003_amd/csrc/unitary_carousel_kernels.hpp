@@ -20,8 +20,8 @@
 // free of orientation-dependent code.
 //
 // The carried phases of a block depend on those of the block before through the partner row, so they are
-// produced by a sequential pass over the n-1 blocks (unitary_phase_kernels.hpp): one workgroup, phases in LDS as
-// 64-bit fixed-point fractions of a turn, one barrier per block; it writes psi' and the sign of the effective
+// produced by a pass over the n-1 blocks (unitary_phase_kernels.hpp): chunks of blocks side by side, phases in LDS as
+// 32-bit fixed-point fractions of a turn, one barrier per block; it writes psi' and the sign of the effective
 // rotation angle per pair, and a parallel kernel turns these into the coefficient tables
 //     rot[e] = (tan(theta'/2), sin theta'),   phs[e] = (tan(psi'/2), sin psi')
 // with theta' the effective rotation angle reduced by a multiple of pi.

@@ -167,6 +167,24 @@ def test_carousel_family_at_the_edges_of_the_angle_reductions():
     assert errs[0] <= 1e-5 and max(errs[1:]) <= 1e-4
 
 
+# The phase pass runs in chunks of blocks side by side, 8 of them below n = 256, 16 below 1024, then 32: sizes whose blocks
+# do not divide into them, so that the last chunk is shorter, in the forward order and in the reverse one.  Angles of
+# several turns, so that the rows' signs change in every chunk.
+@pytest.mark.parametrize("n,B,seed", [(144, 5, 461), (240, 8, 462), (496, 6, 463), (1008, 4, 464), (1040, 4, 465),
+                                      (2064, 3, 466)])
+def test_phase_pass_in_chunks(n, B, seed):
+    theta, phi, x, g = make(n, B, seed, np.float32, np.complex64)
+    theta, phi = np.float32(5) * theta, np.float32(-3) * phi
+    y_d = binding.givens_unitary_forward(dev(theta), dev(phi), dev(x))
+    assert binding.last_kernel() == binding.KERNEL_CAROUSEL
+    got = [y_d, *binding.givens_unitary_backward(dev(theta), dev(phi), y_d, dev(g))]
+    want_y = V.forward_blocks(theta, phi, x)
+    want_dth, want_dph, want_dx, _ = V.reverse_sweep_blocks(theta, phi, want_y, g)
+    errs = [V.rel_fro(host(a), b) for a, b in zip(got, (want_y, want_dx, want_dth, want_dph))]
+    print(f"[unitary] chunks n={n}: " + " ".join("%.2e" % e for e in errs), flush=True)
+    assert errs[0] <= 1e-5 and max(errs[1:]) <= 1e-4   # a lost or doubled sign or constant shows as an error near 1
+
+
 def test_carousel_family_at_a_benchmark_size():
     """n = B = 2048, the shape bench.py --unitary is quoted on: sampled columns of Y and dX against the oracle
     (columns do not interact), all of dtheta and dphi against the LDS family, which the small cases pin."""
