@@ -18,6 +18,7 @@
 #include "lds_kernels.hpp"
 #include "product_kernels.hpp"
 #include "rr_index.h"
+#include "small_kernels.hpp"
 #include "tile_host.hpp"
 #include "unitary_kernels.hpp"
 
@@ -1064,6 +1065,60 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     return multiplies ? apply_matrix(st, dev, pb.rows, B, G, dX, stream) : GIVENS_OK;
 }
 
+// Smallest problems (float64, nothing chosen): one kernel per call, or with several workgroups in the reverse sweep two
+// (small_kernels.hpp).  Measured in us, table and wavefront sweep against it: forward n = 24, B = 64 10.0 / 8.3, 1024 10.0 / 8.6,
+// n = 32, B = 4 10.0 / 8.2, 64 9.9 / 10.1; backward n = 16, B = 1024 13.4 / 11.3, n = 24, B = 4 13.2 / 9.1, 256 13.2 / 14.5,
+// n = 32, B = 4 13.2 / 11.3, 64 13.1 / 14.9.
+constexpr long long kSmallMaxB = 1024;
+template <typename T>
+bool wants_small(const CallOptions &opt, int n, long long B, bool backward)
+{
+    if (!std::is_same<T, double>::value || opt.kernel != GIVENS_KERNEL_AUTO || n > kSmallMaxN || B > kSmallMaxB) return false;
+    return n <= (backward ? 16 : 24) || B <= small_width(n, B, backward);
+}
+int small_forward(const Problem &pb, long long B, const double *theta, const double *X, double *Y, int identity, int mirror,
+                  hipStream_t stream)
+{
+    const int w = small_width(pb.n, B, false);
+    t_state.last_kernel = GIVENS_KERNEL_LDS;
+    t_state.last_flag = nullptr;
+    Span span(1, stream);
+    hipLaunchKernelGGL(small_forward_kernel, dim3((unsigned)((B + w - 1) / w)), dim3(small_threads(pb.n, w, false)), 0, stream,
+                       pb.n, pb.rows, B, w, theta, pb.map, X, Y, identity, mirror);
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+int small_backward(Workspace &ws, const Problem &pb, long long B, const double *theta, const double *Y, const double *G,
+                   double *dX, double *dtheta, hipStream_t stream)
+{
+    const int w = small_width(pb.n, B, true), N = pb.n * (pb.n - 1) / 2;
+    const long long groups = (B + w - 1) / w;
+    if (groups > 1)
+        if (int rc = grow(ws.partial, (size_t)groups * N * sizeof(double))) return rc;
+    double *partial = reinterpret_cast<double *>(ws.partial.ptr);
+    t_state.last_kernel = GIVENS_KERNEL_LDS;
+    t_state.last_flag = nullptr;
+    t_state.last_reduction = GIVENS_REDUCTION_TWO_STAGE;
+    t_state.last_chains = 0;
+    {
+        Span span(1, stream);
+        hipLaunchKernelGGL(small_backward_kernel, dim3((unsigned)groups), dim3(small_threads(pb.n, w, true)), 0, stream, pb.n,
+                           pb.rows, B, w, theta, pb.map, Y, G, dX, partial, dtheta);
+        GIVENS_HIP(hipGetLastError());
+    }
+    if (groups > 1) {
+        Span span(2, stream);
+        if (groups >= 4 * kReduceSplit)
+            hipLaunchKernelGGL(reduce_partials_split_kernel<double>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kReduceSplit), 0,
+                               stream, pb.n, groups, partial, (const double *)nullptr, pb.map, dtheta, 0);
+        else
+            hipLaunchKernelGGL(reduce_partials_kernel<double>, dim3((unsigned)((N + 63) / 64)), dim3(64), 0, stream, pb.n, groups,
+                               partial, (const double *)nullptr, pb.map, dtheta, 0, (const unsigned *)nullptr);
+        GIVENS_HIP(hipGetLastError());
+    }
+    return GIVENS_OK;
+}
+
 // rows, m: see Problem.  The unrestricted entry points pass an even rows and m = rows - 1.
 template <typename T>
 int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y, int identity, void *stream_v,
@@ -1114,6 +1169,8 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
         }
     } else {
         invalidate_prepared(*ws, true, false);
+        if constexpr (std::is_same<T, double>::value)
+            if (wants_small<T>(opt, n, B, false)) return small_forward(pb, B, theta, X, Y, identity, transpose, stream);
         if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose,
                                     fam.wave64 ? wave64_slots(n) : 0))
             return rc;
@@ -1198,6 +1255,8 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
         if (wants_tiles(opt, n, swept, true)) return tiles_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
     if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
     invalidate_prepared(*ws, false, true);
+    if constexpr (std::is_same<T, double>::value)
+        if (wants_small<T>(opt, n, B, true)) return small_backward(*ws, pb, B, theta, Y, G, dX, dtheta, stream);
     Coefs<T> coefs;
     if (int rc = build_coefs<T>(*ws, ws->rev, pb, theta, false,
                                 form_policy(fam.carousel && std::is_same<T, float>::value, n, opt.form, sweep_updates(n, swept)),

@@ -70,6 +70,37 @@ def test_strip_widths_against_the_lds_kernels(n, B):
     assert torch.equal(binding.givens_backward(th, got[0], buf, dX=buf)[0], got[1])
 
 
+# one kernel per call: strips that end with the batch, just past it and far before it, the largest batch and the next; both sides of
+# the sizes that take it.  Angles of 0 among the free ones, bypassed pairs, and odd sizes.  No more than some hundred roundings of
+# 1.1e-16 lie between the two, so 1e-12 has room.
+@pytest.mark.parametrize("n,m,B", [(2, 1, 128), (2, 1, 129), (8, 7, 32), (8, 7, 33), (7, 3, 64), (8, 7, 1024), (8, 7, 1025),
+                                   (15, 14, 17), (16, 5, 16), (16, 15, 1024), (18, 17, 14), (18, 17, 15), (24, 23, 21), (23, 9, 22),
+                                   (24, 2, 1024), (26, 25, 9), (26, 25, 10), (31, 30, 8), (32, 31, 8), (32, 31, 17), (32, 6, 16)])
+def test_smallest_problems_in_one_kernel(n, m, B):
+    print(f"[small64] n={n} m={m} B={B}", flush=True)
+    data = inputs.make_restricted(n, m, B, seed=4600 + n)
+    th, x, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
+    th[::3] = 0.0
+
+    def run():
+        y = binding.givens_forward_restricted(th, x, m)
+        out = [y, *binding.givens_backward_restricted(th, y, g, m), binding.givens_build_restricted(th, n, m)]
+        if n % 2 == 0 and m == n - 1:
+            out.append(binding.givens_forward_transposed(th, x))
+        return out
+
+    got = run()
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = run()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    assert all(far(a, b) <= TOL for a, b in zip(got, want))
+    buf = x.clone()
+    assert torch.equal(binding.givens_forward_restricted(th, buf, m, Y=buf), got[0])
+    buf = g.clone()
+    dx, dth = binding.givens_backward_restricted(th, got[0], buf, m, dX=buf)
+    assert torch.equal(dx, got[1]) and torch.equal(dth, got[2])
+
+
 @pytest.mark.parametrize("n,m,B", [(11, 4, 9), (129, 128, 30), (255, 20, 300), (511, 510, 40), (512, 7, 600)])
 def test_restricted_and_odd_sizes(n, m, B):
     data = inputs.make_restricted(n, m, B, seed=4400 + n)
