@@ -62,10 +62,12 @@ extern "C" {
 
 #define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix    */
                                  /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it, with      */
-                                 /* GIVENS_FORM_AUTO and unless TWO_STAGE is chosen, for n from 400 without a carousel */
-                                 /* shape and from 900 with one of 3, 5 or 7 slots or more than eight wavefronts, and  */
-                                 /* in the backward call from B = 0.6 n to 0.9 n on for these, 0.9 n for the others    */
-                                 /* below 1e9 updates (n (n-1)/2 * B), where it is the faster one                      */
+                                 /* GIVENS_FORM_AUTO and unless TWO_STAGE is chosen, where it is the faster one: for n */
+                                 /* from 400 without a carousel shape, from 700 with one of 3, 5 or 7 slots or more    */
+                                 /* than eight wavefronts, and below 1e9 updates (n (n-1)/2 * B) from 700 for          */
+                                 /* other sizes that are no multiple of 16 up to 1024; in the backward call from       */
+                                 /* B = 0.9 n, 0.3 n, and n / 6 (0.9 n below n = 900) on, and for those multiples      */
+                                 /* from n = 900 and B = 0.9 n on                                                      */
 
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */

@@ -930,29 +930,35 @@ void invalidate_prepared(Workspace &ws, bool fwd, bool rev)
 // would sweep.  Measured, family against tiles in us (the backward call with dX):
 //   no carousel shape: forward n = 514, B = 64 367 / 135, n = 1006, B = 64 912 / 182, n = 3002, B = 3002 13944 / 1449;
 //     backward n = 514, B = 64 368 / 389, 512 439 / 397, n = 1006, B = 64 878 / 538, n = 3002, B = 3002 43233 / 4117
-//   3, 5 or 7 slots per lane, or more than eight wavefronts: forward n = 1002, B = 64 205 / 181, 1002 236 / 203, n = 1022
-//     (7 slots), B = 1022 262 / 276, n = 2050, B = 2050 1088 / 784, n = 4098, B = 4096 4684 / 2909; backward n = 1002,
-//     B = 64 330 / 538, 1002 656 / 590, n = 2046, B = 512 1483 / 1565, n = 4098, B = 1024 6311 / 5979, 4096 19190 / 8186
-//   2, 4 or 8 slots: forward n = 1024, B = 1024 196 / 239, n = 2048, B = 2048 723 / 741, n = 4096, B = 4096 2328 / 2931;
-//     backward n = 1024, B = 64 351 / 569, 1024 690 / 647, n = 2048, B = 512 1528 / 1565, 2048 2293 / 1933, n = 4096,
-//     B = 1024 4405 / 5831, 4096 9068 / 7644
+//   3, 5 or 7 slots per lane, or more than eight wavefronts: forward n = 1002, B = 64 202 / 144, 1002 232 / 169, n = 2050,
+//     B = 2050 1088 / 784, n = 4098, B = 4096 4684 / 2909; backward n = 770, B = 192 334 / 285, 770 497 / 305, n = 1002, B = 64
+//     328 / 329, 448 535 / 349, 1002 645 / 368, n = 4098, B = 4096 19190 / 8186
+//   2, 4 or 8 slots without a shape of one wavefront: forward n = 840, B = 64 158 / 127, n = 904, B = 64 173 / 140, n = 1032,
+//     B = 1032 245 / 201, n = 1280, B = 64 282 / 205, 1152 323 / 224, n = 2048, B = 64 492 / 312, n = 4096, B = 64 1230 / 800;
+//     backward n = 780, B = 390 254 / 307, 780 355 / 316, n = 840, B = 840 576 / 319, n = 904, B = 113 318 / 324, 226 333 / 329,
+//     n = 1152, B = 192 462 / 394, n = 1280, B = 160 498 / 521, 213 594 / 526, 640 982 / 541, n = 2048, B = 341 1479 / 1055
+//   the others, multiples of 16 up to 1024: forward n = 640, B = 320 75 / 122, n = 1024, B = 64 117 / 151, 768 187 / 174,
+//     1024 188 / 198; backward n = 1024, B = 64 351 / 347, 512 589 / 369, 1024 695 / 407, where the line stays at 0.9 n: below
+//     it the two-stage reduction is what the tests hold such a call to
+// The errors against 64 bits are 0.3 to 0.8 of the sweep's (n = 640 to 3584, both kinds of angles).
 bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
 {
     if (opt.kernel == GIVENS_KERNEL_TILES) return true;
     if (opt.kernel != GIVENS_KERNEL_AUTO || opt.form != GIVENS_FORM_AUTO) return false;
     if (backward && opt.reduction == GIVENS_REDUCTION_TWO_STAGE) return false;
     if (n < 400 || n > kTileMaxN) return false;
-    CarouselShape f{}, b{};
+    CarouselShape f{}, b{}, one{};
     const bool has = carousel_shape_for(n, &f) && carousel_bwd_shape_for(n, &b);
     if (!has) return !backward || n >= 700 || 10 * swept >= 9LL * n;
-    if (n < 900) return false;
+    if (n < 700) return false;
     const bool slow = f.M % 2 || f.WAVES > 8;
-    if (!backward) return slow && (f.M != 7 || n >= 1900);
-    if (slow) return 10 * swept >= 6LL * n;
-    // From 1e9 updates on such calls keep the sweep, though the tiles are the faster ones there (n = B = 2048 1933 against
-    // 2293 us, 4096 7644 / 9068): their scaled and lifted rotation forms and, below B = 2n, the two-stage reduction are
+    if (slow) return backward ? 10 * swept >= 3LL * n : f.M != 7 || n >= 1900;
+    // From 1e9 updates on the other sizes keep the sweep, though the tiles are the faster ones there (backward n = B = 2048 1283
+    // against 2290 us, 4096 6957 / 10674): their scaled and lifted rotation forms and, below B = 2n, the two-stage reduction are
     // what the interface lets a caller see and choose at these sizes, and the tests hold them to it.
-    return sweep_updates(n, swept) < kFormsMinUpdates && 10 * swept >= 9LL * n;
+    if (sweep_updates(n, swept) >= kFormsMinUpdates) return false;
+    if (carousel_wave_shape_for(n, 8, &one)) return backward && n >= 900 && 10 * swept >= 9LL * n;
+    return !backward || (n >= 900 ? 6 * swept >= n : 10 * swept >= 9LL * n);
 }
 // Whether the tiles are applied to I, to build U, and X multiplied with that.
 bool tiles_by_product(int rows, long long B) { return B >= kProductMinRatio * rows && B >= kProductMinB; }

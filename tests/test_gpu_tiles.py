@@ -118,6 +118,20 @@ def library_defaults():
     (1280, 1280, False, False, False), (1022, 700, False, True, False), (2050, 64, True, False, False),
     (898, 898, True, True, False), (896, 896, False, False, False), (2048, 1950, False, False, False)])
 def test_sizes_around_the_rule(library_defaults, n, B, forward, backward, product):
+    sizes_around_the_rule(n, B, forward, backward, product)
+
+
+# sizes with a carousel shape, none of one wavefront: both sides of the batch and of 1e9 updates; 3, 5 and 7 slots
+@pytest.mark.parametrize("n,B,forward,backward,product", [
+    (696, 696, False, False, False), (780, 3, True, False, False), (780, 702, True, True, False), (770, 230, False, False, False),
+    (770, 231, False, True, False), (690, 690, False, False, False), (904, 150, True, False, False), (904, 151, True, True, False),
+    (904, 2048, True, True, True), (1002, 301, True, True, False), (1280, 213, True, False, False), (1280, 214, True, True, False),
+    (1280, 1221, True, True, False), (1280, 1222, False, False, False), (2048, 342, True, True, False), (4096, 119, True, False, False)])
+def test_sizes_without_a_shape_of_one_wavefront(library_defaults, n, B, forward, backward, product):
+    sizes_around_the_rule(n, B, forward, backward, product)
+
+
+def sizes_around_the_rule(n, B, forward, backward, product):
     data = inputs.make_custom(n, B, seed=3500 + n)
     th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
     y = binding.givens_forward(th, x)
