@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "product_kernels.hpp"
+#include "tile_choice.hpp"
 
 namespace givens {
 
@@ -60,12 +61,10 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     __shared__ float tops[BOTH][2];                    // largest magnitude of every row in this slice, by its two threads
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave % MW, wn = wave / MW;
-    // Workgroups are handed to the eight XCDs (each with an L2 of its own) in turn.  The list of (slice, tile row, tile
-    // column) is cut into eight consecutive parts, one per XCD, so that the workgroups that share an L2 at any time
-    // work on neighbouring tiles of one slice and reuse each other's panels.
-    unsigned id = blockIdx.x;
-    const unsigned total = gridDim.x;
-    if (total % 8 == 0) id = (id % 8) * (total / 8) + id / 8;
+    // The list of (slice, tile row, tile column) is cut into eight consecutive parts, one per XCD, so that the workgroups
+    // that share an L2 at any time work on neighbouring tiles of one slice and reuse each other's panels (64 x 64 tiles, handed
+    // out in turn and so, in us: n = 314, B = 15395 in 60 slices 69 and 37, n = 192, B = 55531 in 170 81 and 41).
+    const unsigned id = xcd_order(blockIdx.x, gridDim.x);
     const int tile_j = id % a.tiles_n, tile_i = (id / a.tiles_n) % a.tiles_m;
     const unsigned slice = id / (a.tiles_n * a.tiles_m);
     const long long kbeg = (long long)slice * a.slice_cols;
