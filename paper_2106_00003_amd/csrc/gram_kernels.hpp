@@ -32,11 +32,9 @@
 #include <type_traits>
 
 #include "product_kernels.hpp"
-#include "tile_choice.hpp"
 
 namespace givens {
 
-constexpr int kGramK = 16;       // contraction columns per step
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 struct GramArgs {
@@ -251,55 +249,6 @@ __global__ __launch_bounds__(64 * kSumGroups) void sum_slices_kernel(long long c
         }
         __syncthreads();
     }
-}
-
-// Tile and number of slices of a contraction: the shortest by tile_time and by the slices' sum, among slices of at least 256
-// columns (64 x 64 tiles), 384 or 768, at most 256 of them.  Times measured in us without the sum, 64 x 64 / 128 x 128 /
-// 256 x 128, slices in brackets: n = 256, B = 65536 70 (128) / 55 (128) / 53 (256), n = 514, B = 2048 17 (8) / 22 (8) / 28 (12),
-// n = 1002, B = 3001 55 (4) / 45 (8) / 51 (12), n = 1024, B = 4096 68 (4) / 54 (8) / 50 (16), n = 2048, B = 4096 241 (4) /
-// 173 (2) / 155 (4), n = 4097, B = 4096 1085 (2) / 775 (2) / 881 (2) or 1114 (1: 561 workgroups for 512 places).
-//
-// A result's error grows with the square root of the additions behind it, six for every sixteen columns here, where the
-// float32 matrix instructions made eight.  Slices of at most 4096 columns keep it below theirs: n = 2048, B = 65536, normal
-// operands 2.5e-6 with slices of 16384, 1.3e-6 with 4096 (float32 instructions 2.3e-6), contraction 2.70 and 2.82 ms;
-// n = 1024, B = 131072 2.2e-6 with 8192, 1.6e-6 with 4096 (1.6e-6).  As far as the slices fit 4 GiB (n = 8192: sixteen).
-constexpr long long kGramMaxSlice = 4096, kGramSliceBytes = 1LL << 32;
-constexpr TileCost kGramTiles[3] = {{64, 64, 6, 1.55, 0.56, 5.0}, {128, 128, 3, 2.24, 0.94, 9.0}, {256, 128, 2, 2.44, 1.4, 14.0}};
-constexpr long long kGramLeastSlice[3] = {256, 384, 768};
-constexpr double kGramSumRate = 4.0e6;   // bytes of slices that are read in a microsecond
-struct GramPlan {
-    int tile;                            // of kGramTiles
-    int slices;
-};
-inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = false)
-{
-    const int result_cols = cplx ? 2 * rows : rows;
-    const long long bytes = 4LL * rows * result_cols, fit = std::max(1LL, kGramSliceBytes / bytes);
-    const long long least = std::min((B + kGramMaxSlice - 1) / kGramMaxSlice, std::min(fit, 256LL));
-    GramPlan plan{0, 0};
-    double best = 0.0;
-    for (int i = 0; i < 3; ++i) {
-        const TileCost &t = kGramTiles[i];
-        if (i > 0 && rows <= t.bm / 2) continue;
-        const long long tiles = (long long)((rows + t.bm - 1) / t.bm) * ((result_cols + t.bn - 1) / t.bn);
-        const long long room = (long long)t.slots * compute_units;
-        const long long most = std::max(least, std::min(std::min(B / kGramLeastSlice[i], fit), 256LL));
-        // as few as there may be, and as many as one, two or three rounds hold
-        for (int rounds = 0; rounds <= 3; ++rounds) {
-            const long long s = rounds ? std::min(most, std::max(least, rounds * room / tiles)) : least;
-            const long long steps = ((B + s - 1) / s + kGramK - 1) / kGramK;
-            const double us = tile_time(t, tiles * s, steps, compute_units) + (s > 1 ? (double)(s * bytes) / kGramSumRate : 0.0);
-            if (!plan.slices || us < best) {
-                plan = GramPlan{i, (int)s};
-                best = us;
-            }
-        }
-    }
-    return plan;
-}
-inline long long gram_slice_cols(long long B, int slices)
-{
-    return ((B + slices - 1) / slices + kGramK - 1) / kGramK * kGramK;   // slices start on a step boundary
 }
 
 template <int MW, int NW, int MF, int NF, bool CPLX>

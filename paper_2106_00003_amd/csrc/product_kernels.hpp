@@ -11,13 +11,13 @@
 #include <type_traits>
 
 #include "split_bf16.hpp"
+#include "tile_choice.hpp"
 
 namespace givens {
 
 // ---- the shared matrix in operand order.  Fragment (i, k) holds rows 32 i .. + 31 and contraction indices
 // 16 k .. + 15 of A; lane l of a wavefront keeps row l % 32, indices 8 (l / 32) .. + 7 as 16 bytes per piece, so a
 // wavefront loads a piece of a fragment as 1 KB of consecutive memory.  Rows and indices beyond the matrix are zero.
-constexpr int kProductStep = 32;   // contraction indices per step of the product kernel (two fragments)
 constexpr long long product_k16(int k) { return (long long)((k + kProductStep - 1) / kProductStep) * 2; }
 constexpr long long product_pieces(int m, int k)   // 16-byte pieces of an m x k matrix, rows padded to 256
 {
@@ -336,45 +336,26 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(Pr
 // DEPTH: of real operands whose contraction is long enough; complex ones have no registers to spare for more than one step
 // (n = 1024, B = 4096 440 us with two, 235 with one), and two steps are all there is for n = 64 (11.0 against 9.5 us).
 constexpr int kProductDeepK = 256;
-template <int MW, int NW, int MF, int NF, int DEPTH>
+template <int MW, int NW, int MF, int NF, int DEPTH, bool CPLX = false>
 inline void launch_product(ProductArgs a, hipStream_t stream)
 {
+    static_assert(!CPLX || DEPTH == 1, "no registers for more");
     constexpr int BM = 32 * MF * MW, BN = 32 * NF * NW;
     a.mblocks = (a.m + BM - 1) / BM;
     const long long nblocks = (a.B + BN - 1) / BN;
     const dim3 grid((unsigned)((nblocks + 7) / 8 * 8 * a.mblocks)), block(64 * MW * NW);
-    if (a.cplx)
-        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, 1, true>), grid, block, 0, stream, a);
-    else if (DEPTH == 1 || a.k < kProductDeepK)
-        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, 1, false>), grid, block, 0, stream, a);
+    if (DEPTH == 1 || a.k < kProductDeepK)
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, 1, CPLX>), grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, DEPTH, false>), grid, block, 0, stream, a);
-}
-
-// Time in us of a launch of a tiled product or contraction, from what its workgroups take per step of the contraction where the
-// chip is full of them (`full`, with `slots` per compute unit) and where a compute unit has one (`alone`), and `ends` for a
-// round's first loads and last stores.  The last round is as long as it is filled.
-struct TileCost {
-    int bm, bn, slots;
-    double full, alone, ends;
-};
-inline double tile_time(const TileCost &t, long long groups, long long steps, int compute_units)
-{
-    const long long room = (long long)t.slots * compute_units, rounds = groups / room, rest = groups % room;
-    const double last = rest ? std::max(t.alone, t.full * (double)rest / (double)room) : 0.0;
-    return (double)steps * ((double)rounds * t.full + last) + t.ends * (double)(rounds + (rest ? 1 : 0));
+        hipLaunchKernelGGL((product_kernel<MW, NW, MF, NF, DEPTH, CPLX>), grid, block, 0, stream, a);
 }
 
 // Few results (up to six workgroups of the narrow kernel per compute unit; n = 1024, B = 1024 23 us against 41 with tiles,
-// 2048 42 / 46, 4096 88 / 68): the narrow kernel.  Else the tile whose launch is shortest by tile_time, for which the loads run
-// a step ahead of the products, or two where the registers allow that.  Times measured in us, 64 x 64 / 128 x 64 / 128 x 128 /
-// 256 x 128: n = 256, B = 65536 79 / 69 / 60 / 52, n = 1002, B = 3001 46 / 49 / 60 / 96, n = 1024, B = 4096 59 / 53 / 61 / 95,
-// B = 16384 225 / 194 / 173 / 148, n = 2048, B = 4096 242 / 202 / 176 / 192, n = 4097, B = 4096 974 / 969 / 829 / 901.  (With
-// the loads one step ahead 64 x 64 takes 52 us at n = 1002, 128 x 128 196 us at n = 2048, B = 4096.)  All tiles add in the same
-// order; the narrow kernel in another: `all_columns`, where it is given, decides (the columns of the result of which a.B are
-// a part), so that a result does not depend on how it is cut.
-constexpr TileCost kProductTiles[4] = {{64, 64, 4, 1.79, 0.9, 4.0}, {128, 64, 2, 1.63, 1.3, 6.0},
-                                       {128, 128, 2, 2.71, 1.9, 9.0}, {256, 128, 2, 4.6, 3.0, 15.0}};
+// 2048 42 / 46, 4096 88 / 68): the narrow kernel.  Else the tile of product_tile, for
+// which the loads run a step ahead of the products, or two where the registers allow that (with one, 64 x 64 takes 52 us at
+// n = 1002, B = 3001, with two 46; 128 x 128 196 and 176 at n = 2048, B = 4096).  The two kinds add in different orders:
+// `all_columns`, where it is given, decides (the columns of the result of which a.B are a part), so that a result does not
+// depend on how it is cut.
 constexpr long long product_narrow_blocks(int m, long long B) { return (long long)((m + 31) / 32) * ((B + 31) / 32); }
 constexpr bool product_is_narrow(int m, long long B, int compute_units)
 {
@@ -391,25 +372,23 @@ inline void product(ProductArgs a, int compute_units, hipStream_t stream, long l
             hipLaunchKernelGGL(product_narrow_kernel<false>, dim3((unsigned)narrow), dim3(64 * kNarrowWaves), 0, stream, a);
         return;
     }
-    int best = 0;
-    double least = 0.0;
-    for (int i = 0; i < 4; ++i) {
-        const TileCost &t = kProductTiles[i];
-        const long long groups = (long long)((a.m + t.bm - 1) / t.bm) * ((a.B + t.bn - 1) / t.bn);
-        const double us = tile_time(t, groups, (a.k + kProductStep - 1) / kProductStep, compute_units);
-        if (i == 0 || us < least) {
-            best = i;
-            least = us;
-        }
-    }
-    if (best == 3)
+    const int tile = product_tile(a.m, a.k, a.B, compute_units, a.cplx);
+    if (a.cplx) {
+        if (tile == 2)
+            launch_product<2, 2, 2, 2, 1, true>(a, stream);
+        else if (tile == 1)
+            launch_product<2, 2, 2, 1, 1, true>(a, stream);
+        else
+            launch_product<2, 2, 1, 1, 1, true>(a, stream);
+    } else if (tile == 3) {
         launch_product<4, 1, 2, 4, 1>(a, stream);
-    else if (best == 2)
+    } else if (tile == 2) {
         launch_product<2, 2, 2, 2, 2>(a, stream);
-    else if (best == 1)
+    } else if (tile == 1) {
         launch_product<2, 2, 2, 1, 2>(a, stream);
-    else
+    } else {
         launch_product<2, 2, 1, 1, 2>(a, stream);
+    }
 }
 
 // dst <- src, `cols` columns of each row (an operand that is its own result is multiplied from a copy)
