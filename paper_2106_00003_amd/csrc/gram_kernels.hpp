@@ -272,7 +272,7 @@ inline void gram_slices(int rows, long long B, const GramPlan &plan, const float
                         hipStream_t stream)
 {
     const int cols = CPLX ? 2 * rows : rows;
-    const GramArgs a{rows, B, gram_slice_cols(B, plan.slices), Y, G, C, 0, 0, cols};
+    const GramArgs a{rows, B, plan.cols, Y, G, C, 0, 0, cols};
     if (plan.tile == 2)
         launch_gram<2, 2, 4, 2, CPLX>(a, plan.slices, stream);
     else if (plan.tile == 1)

@@ -95,18 +95,15 @@ constexpr long long kGramLeastSlice[3] = {256, 384, 768};
 constexpr double kGramSumEnds = 2.5, kGramSumRate = 3.5e6;   // of the slices' sum: us, and bytes that are read in a microsecond
 struct GramPlan {
     int tile;                            // of kGramCost
-    int slices;
+    int slices;                          // none of them empty
+    long long cols;                      // ... of all but the last one: they start on a step boundary
 };
-inline long long gram_slice_cols(long long B, int slices)
-{
-    return ((B + slices - 1) / slices + kGramK - 1) / kGramK * kGramK;   // slices start on a step boundary
-}
 inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = false)
 {
     const int result_cols = cplx ? 2 * rows : rows;
     const long long bytes = 4LL * rows * result_cols, fit = std::max(1LL, kGramSliceBytes / bytes);
     const long long least = std::min((B + kGramMaxSlice - 1) / kGramMaxSlice, std::min(fit, 256LL));
-    GramPlan plan{0, 0};
+    GramPlan plan{0, 0, 0};
     double best = 0.0;
     for (int i = 0; i < 3; ++i) {
         const TileCost &t = kGramCost[cplx][i];
@@ -115,12 +112,12 @@ inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = 
         const long long most = std::max(least, std::min(std::min(B / kGramLeastSlice[i], fit), 256LL));
         // as few as there may be, and as many as give every compute unit one workgroup, two, ... two rounds of them
         for (int held = 0; held <= 2 * t.slots; ++held) {
-            const long long s = std::min(most, std::max(least, held * (long long)compute_units / tiles));
-            const long long steps = gram_slice_cols(B, (int)s) / kGramK;
-            const double us = tile_time(t, (tiles * s + 7) / 8, steps, compute_units) +
+            const long long want = std::min(most, std::max(least, held * (long long)compute_units / tiles));
+            const long long cols = ((B + want - 1) / want + kGramK - 1) / kGramK * kGramK, s = (B + cols - 1) / cols;
+            const double us = tile_time(t, (tiles * s + 7) / 8, cols / kGramK, compute_units) +
                               (s > 1 ? kGramSumEnds + (double)(s * bytes) / kGramSumRate : 0.0);
             if (!plan.slices || us < best) {
-                plan = GramPlan{i, (int)s};
+                plan = GramPlan{i, (int)s, cols};
                 best = us;
             }
         }

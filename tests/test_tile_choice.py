@@ -16,7 +16,13 @@ double contraction_us(int tile, int slices, int rows, long long B, int units)
 {
     const TileCost &t = kGramCost[0][tile];
     const long long tiles = (long long)((rows + t.bm - 1) / t.bm) * ((rows + t.bn - 1) / t.bn);
-    return tile_time(t, (tiles * slices + 7) / 8, gram_slice_cols(B, slices) / kGramK, units);
+    return tile_time(t, (tiles * slices + 7) / 8, ((B + slices - 1) / slices + kGramK - 1) / kGramK, units);
+}
+void plan(int rows, long long B, int units, int cplx, int *slices, long long *cols)
+{
+    const GramPlan p = gram_plan(rows, B, units, cplx != 0);
+    *slices = p.slices;
+    *cols = p.cols;
 }
 }
 """
@@ -86,3 +92,16 @@ def test_estimates_grow_with_the_work(choice, units):
                 us = choice.contraction_us(tile, slices, n, ctypes.c_longlong(512 * slices), units)
                 assert us >= 0.98 * last
                 last = us
+
+
+# n = 228, B = 53484 was cut into 139 slices of 400 columns, of which 134 hold the columns: the others ran tiles for nothing.
+@pytest.mark.parametrize("cplx", [False, True])
+@pytest.mark.parametrize("units", [64, 256, 304])
+def test_the_slices_of_a_contraction_hold_its_columns_and_none_is_empty(choice, units, cplx):
+    slices, cols = ctypes.c_int(), ctypes.c_longlong()
+    shapes = [(228, 53484), (118, 115206), (34, 6513), (8192, 70000), (2, 256), (40, 2 ** 40)]
+    shapes += [(n, 2 * n + 7 * n * k * k // 3) for n in range(34, 2300, 74) for k in range(24)]
+    for n, B in shapes:
+        choice.plan(n, ctypes.c_longlong(B), units, cplx, ctypes.byref(slices), ctypes.byref(cols))
+        assert cols.value % 16 == 0 and (slices.value - 1) * cols.value < B <= slices.value * cols.value, (n, B)
+        assert slices.value <= 256 and (cols.value <= 4096 or B > 4096 * 256 or slices.value * n * n * 4 > 2 ** 30)
