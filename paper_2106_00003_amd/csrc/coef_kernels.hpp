@@ -251,8 +251,10 @@ __global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int 
                 out.y = (T)(fac * s);
             }
         }
-        // slots of a lane of the sweep that reads the table (wave_f64_kernels.hpp): first slots of 64 lanes, second slots, ...
-        table[slots ? ((long long)k * slots + p % slots) * 64 + p / slots : e] = out;
+        // slots of a lane of the sweep that reads the table, a power of two (wave_f64_kernels.hpp): first slots of 64 lanes,
+        // second slots, ...
+        const int shift = __ffs(slots) - 1;
+        table[slots ? (((long long)k << shift) + (p & (slots - 1))) * 64 + (p >> shift) : e] = out;
         if (factor) factor[e] = (T)fac;
     }
 }

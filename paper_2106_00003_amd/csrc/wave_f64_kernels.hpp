@@ -20,6 +20,12 @@ constexpr int kWave64Depth = 4;   // ring of coefficients, in blocks
 // Strips of a workgroup, one wavefront each, where there are many.  They read the same coefficients within a few blocks of each
 // other, so most come from the compute unit's L1, and in the reverse sweep they share a row of partial sums.  Where there are no
 // more strips than places for them each has a compute unit's L1 to itself (wave64_fwd_strips, wave64_bwd_strips).
+// Whether the first loads of the ring stand under a condition, which always holds (n >= 10).  Where the compiler does not know
+// how many loads are on their way it waits for all of them in every fourth block: n = 448, B = 15 forward and backward 65 and 109 us
+// with the condition, 57 and 89 without, n = 512, B = 1024 90 and 198, 77 and 175.  Only the shortest blocks, which end before
+// their loads come back, are better off with that wait than with one in every block: one slot and four columns, n = 18, B = 2541
+// 11.0 and 16.0 us, 11.0 and 16.4, n = 28, B = 2204 11.1 and 18.1, 11.4 and 18.4.
+constexpr bool wave64_asks(int M, int W) { return M == 1 && W == 4; }
 constexpr int wave64_unroll(int M) { return M > kWave64Depth ? M : kWave64Depth; }   // a multiple of both (powers of two)
 
 template <int CTRL>
@@ -108,7 +114,7 @@ struct Wave64Fwd {
         }
 #pragma unroll
         for (int d = 0; d < kWave64Depth - 1; ++d)
-            if (k - d >= 0) co.load(k - d, d);
+            if (!wave64_asks(M, W) || k - d >= 0) co.load(k - d, d);
         for (; k >= kUnroll - 1; k -= kUnroll) group(k, std::make_integer_sequence<int, kUnroll>{});
         tail(std::make_integer_sequence<int, kUnroll - 1>{});
     }
@@ -274,7 +280,7 @@ struct Wave64Bwd {
         if (k) flush(0, k);
 #pragma unroll
         for (int d = 0; d < kWave64Depth - 1; ++d)
-            if (k + d <= n - 2) co.load(k + d, d);
+            if (!wave64_asks(M, W) || k + d <= n - 2) co.load(k + d, d);
         for (; k + kUnroll <= n - 1; k += kUnroll) group(k, std::make_integer_sequence<int, kUnroll>{});
         tail(k, std::make_integer_sequence<int, kUnroll - 1>{});
     }
