@@ -62,12 +62,21 @@ extern "C" {
 
 #define GIVENS_KERNEL_TILES 4    /* float, n from 8 to 8192: rotations grouped into tiles of 128 rows on the matrix    */
                                  /* cores; plain calls only, the reduction is the Gram form.  AUTO takes it, with      */
-                                 /* GIVENS_FORM_AUTO and unless TWO_STAGE is chosen, where it is the faster one: for n */
-                                 /* from 400 without a carousel shape, from 700 with one of 3, 5 or 7 slots or more    */
-                                 /* than eight wavefronts, and below 1e9 updates (n (n-1)/2 * B) from 700 for          */
-                                 /* other sizes that are no multiple of 16 up to 1024; in the backward call from       */
-                                 /* B = 0.9 n, 0.3 n, and n / 6 (0.9 n below n = 900) on, and for those multiples      */
-                                 /* from n = 900 and B = 0.9 n on                                                      */
+                                 /* GIVENS_FORM_AUTO and unless TWO_STAGE is chosen, by the size and the columns B that*/
+                                 /* a sweep would run over (n of a batch that is multiplied with U):                   */
+                                 /*  - no carousel shape: forward calls from n = 400, backward calls from n = 700, or  */
+                                 /*    from n = 400 and B = 0.9 n;                                                     */
+                                 /*  - 3, 5 or 7 slots per lane or more than eight wavefronts: forward from n = 700    */
+                                 /*    (7 slots: 1900), backward from n = 700 and B = 0.3 n (3 slots: 0.75 n below     */
+                                 /*    n = 900, 0.4 n below 960);                                                      */
+                                 /*  - the others but multiples of 16 up to 1024, below 1e9 updates (n (n-1)/2 * B):   */
+                                 /*    forward from n = 700, backward from n = 900 and B = n / 6 (multiples of 4 that  */
+                                 /*    are none of 8: 0.4 n below n = 960, 0.3 n below 1040, 0.25 n below 1200), or    */
+                                 /*    from n = 700 and B = 0.9 n;                                                     */
+                                 /*  - multiples of 16 up to 1024, below 1e9 updates: backward from n = 900 and        */
+                                 /*    B = 0.9 n.                                                                      */
+                                 /* In the last two classes the tiles are the faster ones beyond those lines too (see  */
+                                 /* wants_tiles in csrc/givens_rr.hip)                                                 */
 
 /* Rotation forms of the float carousel kernels (givens_set_rotation_form). */
 #define GIVENS_FORM_AUTO 0     /* GIVENS_FORM_RANGE where the sweeps are long enough to pay for its extra       */

@@ -932,11 +932,16 @@ void invalidate_prepared(Workspace &ws, bool fwd, bool rev)
 //     backward n = 514, B = 64 368 / 389, 512 439 / 397, n = 1006, B = 64 878 / 538, n = 3002, B = 3002 43233 / 4117
 //   3, 5 or 7 slots per lane, or more than eight wavefronts: forward n = 1002, B = 64 202 / 144, 1002 232 / 169, n = 2050,
 //     B = 2050 1088 / 784, n = 4098, B = 4096 4684 / 2909; backward n = 770, B = 192 334 / 285, 770 497 / 305, n = 1002, B = 64
-//     328 / 329, 448 535 / 349, 1002 645 / 368, n = 4098, B = 4096 19190 / 8186
+//     328 / 329, 448 535 / 349, 1002 645 / 368, n = 4098, B = 4096 19190 / 8186.  Three slots are the fastest of these sweeps:
+//     tiles by sweep n = 702, B = 421 1.15, 526 0.94, n = 774, B = 387 1.07, 464 0.92, n = 894, B = 268 1.02, 357 0.86, n = 942,
+//     B = 235 1.00, 282 0.91
 //   2, 4 or 8 slots without a shape of one wavefront: forward n = 840, B = 64 158 / 127, n = 904, B = 64 173 / 140, n = 1032,
 //     B = 1032 245 / 201, n = 1280, B = 64 282 / 205, 1152 323 / 224, n = 2048, B = 64 492 / 312, n = 4096, B = 64 1230 / 800;
 //     backward n = 780, B = 390 254 / 307, 780 355 / 316, n = 840, B = 840 576 / 319, n = 904, B = 113 318 / 324, 226 333 / 329,
-//     n = 1152, B = 192 462 / 394, n = 1280, B = 160 498 / 521, 213 594 / 526, 640 982 / 541, n = 2048, B = 341 1479 / 1055
+//     n = 1152, B = 192 462 / 394, n = 1280, B = 160 498 / 521, 213 594 / 526, 640 982 / 541, n = 2048, B = 341 1479 / 1055.  Two
+//     slots, multiples of 4 that are none of 8: tiles by sweep n = 900, B = 270 1.17, 360 0.89, n = 940, B = 235 1.14, 282 0.96,
+//     n = 964, B = 241 1.13, n = 980, B = 196 1.12, 294 0.84, n = 1060, B = 176 1.05, 212 0.88, n = 1148, B = 191 1.06, 229 0.76,
+//     n = 1252, B = 156 0.78
 //   the others, multiples of 16 up to 1024: forward n = 640, B = 320 75 / 122, n = 1024, B = 64 117 / 151, 768 187 / 174,
 //     1024 188 / 198; backward n = 1024, B = 64 351 / 347, 512 589 / 369, 1024 695 / 407, where the line stays at 0.9 n: below
 //     it the two-stage reduction is what the tests hold such a call to
@@ -952,13 +957,17 @@ bool wants_tiles(const CallOptions &opt, int n, long long swept, bool backward)
     if (!has) return !backward || n >= 700 || 10 * swept >= 9LL * n;
     if (n < 700) return false;
     const bool slow = f.M % 2 || f.WAVES > 8;
-    if (slow) return backward ? 10 * swept >= 3LL * n : f.M != 7 || n >= 1900;
+    if (slow && !backward) return f.M != 7 || n >= 1900;
+    auto from = [&](int twentieths) { return 20 * swept >= (long long)twentieths * n; };
+    if (slow) return from(f.M != 3 || n >= 960 ? 6 : n >= 900 ? 8 : 15);
     // From 1e9 updates on the other sizes keep the sweep, though the tiles are the faster ones there (backward n = B = 2048 1283
     // against 2290 us, 4096 6957 / 10674): their scaled and lifted rotation forms and, below B = 2n, the two-stage reduction are
     // what the interface lets a caller see and choose at these sizes, and the tests hold them to it.
     if (sweep_updates(n, swept) >= kFormsMinUpdates) return false;
-    if (carousel_wave_shape_for(n, 8, &one)) return backward && n >= 900 && 10 * swept >= 9LL * n;
-    return !backward || (n >= 900 ? 6 * swept >= n : 10 * swept >= 9LL * n);
+    if (carousel_wave_shape_for(n, 8, &one)) return backward && n >= 900 && from(18);
+    if (!backward) return true;
+    if (b.M == 2 && n < 1200) return from(n >= 1040 ? 5 : n >= 960 ? 6 : n >= 900 ? 8 : 18);
+    return n >= 900 ? 6 * swept >= n : from(18);
 }
 // Whether the tiles are applied to I, to build U, and X multiplied with that.
 bool tiles_by_product(int rows, long long B) { return B >= kProductMinRatio * rows && B >= kProductMinB; }

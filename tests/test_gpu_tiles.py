@@ -131,6 +131,17 @@ def test_sizes_without_a_shape_of_one_wavefront(library_defaults, n, B, forward,
     sizes_around_the_rule(n, B, forward, backward, product)
 
 
+# two and three slots, whose backward sweeps are the fastest: both sides of each line
+@pytest.mark.parametrize("n,B,forward,backward,product", [
+    (900, 271, True, False, False), (900, 359, True, False, False), (900, 360, True, True, False), (956, 382, True, False, False),
+    (964, 289, True, False, False), (964, 290, True, True, False), (1060, 264, True, False, False), (1060, 265, True, True, False),
+    (1196, 298, True, False, False), (1204, 201, True, True, False), (702, 526, True, False, False), (702, 527, True, True, False),
+    (894, 268, True, False, False), (894, 671, True, True, False), (942, 376, True, False, False), (942, 377, True, True, False),
+    (966, 290, False, True, False), (978, 293, True, False, False), (978, 294, True, True, False)])
+def test_sizes_of_two_and_three_slots(library_defaults, n, B, forward, backward, product):
+    sizes_around_the_rule(n, B, forward, backward, product)
+
+
 def sizes_around_the_rule(n, B, forward, backward, product):
     data = inputs.make_custom(n, B, seed=3500 + n)
     th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
