@@ -192,7 +192,8 @@ int carousel_backward_chain(const CarouselBwdArgs &a, const CarouselChainArgs &c
 
 // Unitary extension in the carousel family (unitary_carousel_kernels.hpp): complex64 operands seen as real
 // n x Breal arrays (Breal = 2 B), W real columns per lane (even).  Even n that is a multiple of 16, from
-// kUnitaryCarouselMinN up to 4096 (8 slots per lane forward, 4 reverse; the phase pass keeps n float64 in LDS).
+// kUnitaryCarouselMinN up to 4096 (8 slots per lane forward, 4 reverse; the phase pass keeps two words for each of n rows in
+// LDS, twice).
 constexpr int kUnitaryCarouselMinN = 128;
 inline bool unitary_carousel_supported(int n) { return n >= kUnitaryCarouselMinN && n <= 4096 && n % 16 == 0; }
 
@@ -412,14 +413,14 @@ inline int wave64_slots(int n)
         if (n >= 10 && n % (2 * m) == 0 && n / (2 * m) <= 64) return m;
     return 0;
 }
-// They are the faster ones throughout.  LDS kernels against them in us: forward n = 64, B = 64 33 / 11, 65536 118 / 106; n = 512,
-// B = 1024 277 / 92; n = 1024, B = 256 973 / 199, 4096 1632 / 616; backward n = 32, B = 64 23 / 15, 65536 292 / 201; n = 64,
-// B = 65536 484 / 314; n = 512, B = 1024 776 / 208; n = 1024, B = 1024 3050 / 769, 9000 17466 / 4542.
+// They are the faster ones throughout.  LDS kernels against them in us: forward n = 64, B = 64 32 / 11, 65536 264 / 111; n = 512,
+// B = 1024 272 / 76; n = 1024, B = 256 973 / 190, 4096 1616 / 560; backward n = 32, B = 64 23 / 14, 65536 289 / 198; n = 64,
+// B = 65536 475 / 314; n = 512, B = 1024 775 / 177; n = 1024, B = 1024 3038 / 763, 9000 17451 / 4502.
 inline bool wave64_supported(int n) { return wave64_slots(n) != 0; }
 // Columns per strip of the forward sweep, and strips per workgroup: every strip reads the whole coefficient table, so wide
-// strips and shared L1s soon pay where that is long.  Measured in us, one strip and four per workgroup: n = 512, B = 64 73 / 105,
-// 512 88 / 98, 1024 98 / 89 (two columns 92 / 100), 4000 with four columns 134 in fours; n = 1024, B = 256 201 / 259, 1024 with
-// two columns 248 / 262, 2000 295 in fours; n = 256, B = 2000 47 / 39 (two columns 45 / 41).
+// strips and shared L1s soon pay where that is long.  Sweeps measured in us, one strip and four per workgroup: n = 512, B = 64
+// 41 / 62, 512 54 / 66, 1024 76 / 71 (two columns 78 / 75), 4000 with four columns 136 / 131; n = 1024, B = 256 182 / 242, 1024
+// with two columns 227 / 253, 2000 287 / 272; n = 256, B = 2000 44 / 37 (two columns 44 / 29).
 constexpr int kWave64Strips = 4;
 inline int wave64_fwd_width(int n, long long B)
 {
@@ -428,10 +429,10 @@ inline int wave64_fwd_width(int n, long long B)
     return B <= 2048 || slots == 8 ? 2 : 4;
 }
 inline int wave64_fwd_strips(long long strips) { return strips > 512 ? kWave64Strips : 1; }
-// Columns per row of partial sums of the reverse sweep: those of a workgroup's strips.  Measured in us with the second stage,
-// one, two and four columns a strip: n = 512, B = 1024 213 / 221 / 321, 4000 749 / 452 / 355, n = 256, B = 1024 70 / 78 / 115,
-// 4096 183 / 140 / 135, n = 64, B = 16384 156 / 115 / 97, n = 1024, B = 256 522 / 643, 1024 879 / 763; a strip per workgroup and row:
-// n = 512, B = 64 132 us against 143.
+// Columns per row of partial sums of the reverse sweep: those of a workgroup's strips.  Sweep and second stage measured in us,
+// one, two and four columns a strip: n = 512, B = 768 152 / 202 / 319, 1024 219 / 207 / 319, 4000 735 / 439 / 353, n = 256,
+// B = 1024 60 / 71 / 113, 4096 179 / 121 / 124, n = 64, B = 16384 146 / 103 / 89, n = 1024, B = 256 548 / 640, 1024 871 / 785; a
+// strip per workgroup and row: n = 512, B = 64 102 us against 122.
 inline int wave64_bwd_strips(long long B) { return B <= 128 ? 1 : kWave64Strips; }
 inline int wave64_bwd_width(int n, long long B)
 {

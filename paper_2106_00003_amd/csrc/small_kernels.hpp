@@ -1,8 +1,8 @@
 // Sweeps of the smallest problems (n <= kSmallMaxN, float64): one kernel per call.  What bounds such a call is the number of
 // launches and the latency of each, not arithmetic, so a workgroup makes the coefficients itself, in LDS (at most 496 angles, two
-// per thread), instead of reading a table that a launch before it wrote; a thread owns one arc and one column of the
-// workgroup's strip, so a block is one rotation deep; and the reverse sweep keeps every rotation's contribution in LDS and sums
-// over the columns at the end, writing dtheta itself where one workgroup holds all columns.
+// per thread, four in the reverse sweep), instead of reading a table that a launch before it wrote; a thread owns one arc and one
+// column of the workgroup's strip, so a block is one rotation deep; and the reverse sweep keeps every rotation's contribution in
+// LDS and sums over the columns at the end, writing dtheta itself where one workgroup holds all columns.
 // Forward and backward calls in us, back to back, tables and sweeps of their own before and now: n = 8, B = 4 9.9 / 13.4 and
 // 7.9 / 8.5; n = 16, B = 64 10.1 / 13.1 and 8.2 / 11.4, 1024 10.0 / 13.4 and 8.0 / 11.3.
 #pragma once

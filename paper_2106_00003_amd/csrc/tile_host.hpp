@@ -43,11 +43,14 @@ constexpr size_t tile_operand_floats(const TilePlan &g, long long B)
 {
     return (size_t)((B + kTileCols - 1) / kTileCols) * kTileCols * (2 * g.P * kTileHalf + 1);
 }
-// Whether the gradient's stages run with 32 columns of a pair of tiles per workgroup (tile_two_sided_narrow_kernel): where that
-// gives at most two workgroups per compute unit of 256 (measured, 32 columns against a pair per workgroup: P = 8 8.0 and 14.9 us,
+// Whether the gradient's stages run with 32 columns of a pair of tiles per workgroup (tile_two_sided_narrow): where that gives at
+// most two workgroups per compute unit (measured on 256 of them, 32 columns against a pair per workgroup: P = 8 8.0 and 14.9 us,
 // P = 17 20.6 and 17.7, P = 24 33.9 and 26.6).  With restricted parametrisations most pairs have nothing to do, which only the
 // other kernel leaves alone.
-inline bool tile_gradient_narrow(const TilePlan &g, int free_rows) { return free_rows >= g.n - 2 && g.P <= 15; }
+inline bool tile_gradient_narrow(const TilePlan &g, int compute_units, int free_rows)
+{
+    return free_rows >= g.n - 2 && (kTilePad / 32) * (g.P * (g.P + 1) / 2) <= 2 * compute_units;
+}
 
 // What the calls on one problem need: bytes of each buffer.
 struct TileBuffers {

@@ -32,6 +32,8 @@
 namespace givens {
 
 enum { kTileLate = 0, kTileEarly = 1, kTileSpecial = 2, kTileNone = 3 };
+// The rows of a tile's matrix: those of piece i from 0, of piece j from kTilePad / 2, and at kTilePad - 1 row 0, which goes with
+// tile 0 of every stage (an identity row unless the tile is special).
 struct Tile {
     int i, j, kind;
     int a0, na, b0, nb;   // indices of the two pieces
@@ -70,15 +72,6 @@ __host__ __device__ inline Tile tile_at(const TilePlan &g, int st, int u)
     tile_piece(g, x.i, &x.a0, &x.na);
     tile_piece(g, x.j, &x.b0, &x.nb);
     return x;
-}
-// Row (label) of local index r of tile u, or -1: piece i from 0, piece j from kTilePad / 2, and at kTilePad - 1 row 0, which goes
-// with tile 0 of every stage (an identity row of its matrix unless the tile is special).
-__host__ __device__ inline int tile_row(const TilePlan &g, const Tile &x, int u, int r)
-{
-    const int q = r - kTilePad / 2;
-    if (q < 0) return r < x.na ? tile_label(g, x.a0 + r) : -1;
-    if (q < x.nb) return tile_label(g, x.b0 + q);
-    return r == kTilePad - 1 && u == 0 ? 0 : -1;
 }
 // Restricted parametrisation (pairs (i, j), i < free_rows): does the tile hold no free pair?  (labels go down by 2 along
 // a piece)

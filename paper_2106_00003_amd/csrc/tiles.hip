@@ -51,7 +51,7 @@ inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int fr
                           hipStream_t stream)
 {
     const u32x4 *pieces = static_cast<const u32x4 *>(b.pieces);
-    const bool narrow = tile_gradient_narrow(g, free_rows);
+    const bool narrow = tile_gradient_narrow(g, compute_units, free_rows);
     const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2) * (narrow ? kTilePad / 32 : 1);
     float *second = narrow ? b.S + tile_s_floats(g) : nullptr;
     hipLaunchKernelGGL(tile_antisym_kernel, dim3(tile_antisym_blocks(g)), dim3(256), 0, stream, g, rows, slices, C, b.S, b.range);

@@ -21,7 +21,7 @@ __device__ __forceinline__ int reduce_by_pi(double x, double *r)
     return (int)((long long)m & 1);
 }
 
-// Phases in the sequential pass are fixed-point numbers: an unsigned 32-bit integer x stands for the angle
+// Phases in the pass are fixed-point numbers: an unsigned 32-bit integer x stands for the angle
 // 2 pi x / 2^32, so that sums and differences wrap round modulo 2 pi by themselves and the pass needs integer
 // additions only.  Rounding phi to 2 pi / 2^32 = 1.5e-9 rad is a perturbation of the parameter far below
 // float32's resolution of the result.
@@ -80,8 +80,8 @@ __global__ void unitary_phase_input_kernel(int n, const float *__restrict__ thet
 // second kernel starts a chunk from zeros, notes which rows' bits it turns (`flips`, a bit per chunk), and the table kernel
 // turns u where the chunks before have turned an odd number of times.  n = 1024: 182 us for the pass in one workgroup,
 // 25 us for both kernels in 32 chunks (a step of B = 4096 2520 and 2237).
-constexpr int kPhaseChunksMost = 32;
-inline int phase_chunks(int n) { return n >= 1024 ? 32 : n >= 256 ? 16 : 8; }
+constexpr int kPhaseChunksMost = 32;   // a bit each of a word of `flips`
+inline int phase_chunks(int n) { return n >= 1024 ? kPhaseChunksMost : n >= 256 ? 16 : 8; }
 __host__ __device__ inline int phase_chunk_steps(int n, int chunks) { return (n - 1 + chunks - 1) / chunks; }
 struct PhaseScan {
     int chunks;

@@ -166,8 +166,8 @@ __global__ __launch_bounds__(64 * kWave64Strips, 1) void wave64_forward_kernel(i
 
 // Reverse sweep.  With several strips in a workgroup their sums of four blocks go to LDS, and after a barrier each wavefront adds
 // those of one block, in strip order, and stores them.  So a row of partial sums stands for 4 W columns, while a wavefront's
-// block has the arithmetic of W: n = 512, B = 1024 with the second stage 213 us, 332 with a wavefront of four columns per row;
-// n = 1024, B = 1024 763 and 1764 (two columns per row).
+// block has the arithmetic of W: n = 512, B = 1024 with the second stage 219 us, 645 with a wavefront of one column per row;
+// n = 1024, B = 1024 871 and 2667.
 template <int M, int W, int STRIPS>
 struct Wave64Bwd {
     static constexpr int kUnroll = wave64_unroll(M);
@@ -286,9 +286,9 @@ struct Wave64Bwd {
     }
 };
 
-// strips of W columns, STRIPS of them per workgroup, from group strip0 + blockIdx.x on; partial: [gridDim.x][N]
+// strips of W columns, STRIPS of them per workgroup, from group group0 + blockIdx.x on; partial: [gridDim.x][N]
 template <int M, int W, int STRIPS>
-__global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, int rows, long long B, long long strip0,
+__global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, int rows, long long B, long long group0,
                                                                 const double2 *__restrict__ table, const double *Yin,
                                                                 const double *G, double *dX, double *__restrict__ partial)
 {
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, 
     st.H = n >> 1;
     st.co.lane = table + (idle ? 0 : l);
     st.part = partial + (long long)blockIdx.x * (n - 1) * (n >> 1) + (idle ? 0 : l * M);
-    const long long b0 = ((strip0 + blockIdx.x) * STRIPS + st.wave) * W;   // (past the end: zeros)
+    const long long b0 = ((group0 + blockIdx.x) * STRIPS + st.wave) * W;   // (past the end: zeros)
     auto bring = [&](double(&v)[W], const double *src, int row) {
 #pragma unroll
         for (int x = 0; x < W; ++x) v[x] = !idle && row < rows && b0 + x < B ? src[(long long)row * B + b0 + x] : 0.0;
