@@ -86,6 +86,28 @@ def test_large_angles(scale):
         binding.set_kernel(binding.KERNEL_AUTO)
 
 
+# upstream gradients with infinities and NaN: dX of the other columns does not change, in stages of both kinds, with the operand swept
+# and with the product
+@pytest.mark.parametrize("n,B", [(258, 70), (258, 600), (1006, 90), (2050, 40)])
+def test_infinities_and_nan_in_the_backward_call(n, B):
+    print(f"[tiles] infinities n={n} B={B}", flush=True)
+    data = inputs.make_custom(n, B, seed=3600 + n)
+    th, y, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    bad = g.clone()
+    bad[1, 0], bad[n - 1, B // 2], bad[n // 2, B - 1] = float("nan"), float("inf"), -float("inf")
+    clean = torch.ones(B, dtype=torch.bool, device="cuda")
+    clean[[0, B // 2, B - 1]] = False
+    try:
+        binding.set_kernel(binding.KERNEL_TILES)
+        want, _ = binding.givens_backward(th, y, g)
+        dx, dth = binding.givens_backward(th, y, bad)
+        again, plain = binding.givens_backward(th, y, g)
+    finally:
+        binding.set_kernel(binding.KERNEL_AUTO)
+    assert torch.equal(dx[:, clean], want[:, clean]) and not torch.isfinite(dx[:, ~clean]).all(dim=0).any()
+    assert not torch.isfinite(dth).all() and torch.equal(again, want) and torch.isfinite(plain).all()
+
+
 def test_calls_that_tiles_do_not_take():
     th = torch.zeros(15, device="cuda")
     try:

@@ -115,3 +115,30 @@ def test_restricted_and_odd_sizes(n, m, B):
     want = run()
     binding.set_kernel(binding.KERNEL_AUTO)
     assert all(far(a, b) <= TOL for a, b in zip(got, want))
+
+
+# Infinities and NaN stay in the columns and the angles they reach, in one kernel per call (n <= 32), in strips of their own and in
+# strips that share a row of sums: where the LDS kernels' results are finite the values are close, elsewhere neither is finite.
+@pytest.mark.parametrize("n,B", [(2, 9), (8, 4), (15, 40), (16, 200), (24, 700), (32, 8), (32, 2000), (64, 64), (64, 513), (200, 129),
+                                 (512, 1025), (1008, 70), (1024, 800)])
+def test_infinities_and_nan_stay_where_they_belong(n, B):
+    print(f"[wave64] infinities n={n} B={B}", flush=True)
+    data = inputs.make_restricted(n, n - 1, B, seed=4700 + n)
+    th, x, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
+    y = binding.givens_forward_restricted(th, x, n - 1)
+    bad_x, bad_g = x.clone(), g.clone()
+    bad_x[0, 0], bad_x[n - 1, B // 2], bad_x[n // 2, B - 1] = float("nan"), float("inf"), -float("inf")
+    bad_g[n // 2, 1], bad_g[n - 1, B - 1] = float("inf"), float("nan")
+
+    def run():
+        return [binding.givens_forward_restricted(th, bad_x, n - 1), *binding.givens_backward_restricted(th, y, bad_g, n - 1)]
+
+    got = run()
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = run()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    for a, b in zip(got, want):
+        finite = torch.isfinite(b)
+        assert torch.equal(torch.isfinite(a), finite) and not finite.all()
+        if finite.any():
+            assert far(a[finite], b[finite]) <= TOL
