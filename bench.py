@@ -21,7 +21,8 @@ Prints ONE JSON line.  Besides the contract fields it carries
                 where the rotations run as tiles, the matrix they make up (2 n^2 per column), against the same
   roofline_bwd  reverse sweep kernel(s) against the vector peak (16 flop per update over the columns they sweep); with
                 the product behind dX, or tiles, the same as for the forward call
-  roofline_gram the Gram-matrix contraction against the matrix peak, when the backward call used it
+  roofline_gram the Gram-matrix contraction against the matrix peak, when the backward call used it (with tiles: without
+                the slices' sum, which is part of their stages)
   The matrix peak is that of float32 products on the bf16 matrix cores, six bf16 products each.
   cpu_baseline  the fp64 C oracle (oracle/givens_oracle.c) timed on the host cores on a bounded sample of
                 the same workload's columns

@@ -390,7 +390,10 @@ int givens_last_chains(void);
  * caller's stream around each group of kernels it launches.  givens_last_timing() waits for the events of
  * the last call on this thread and writes milliseconds: ms[0] = coefficient kernels (range check, tables),
  * ms[1] = sweep kernel(s), ms[2] = dtheta second-stage reduction, ms[3] = Gram-matrix contraction and its
- * slice sum (ms[2], ms[3]: 0 for forward/build).  Returns GIVENS_ERR_UNSUPPORTED if timing was off for that call.
+ * slice sum (ms[2], ms[3]: 0 for forward/build).  A call that ran as tiles (GIVENS_KERNEL_TILES): ms[0] = the tiles'
+ * matrices, ms[1] = forward their application, and the product of a wide batch (backward: only that), ms[2] = backward
+ * the slice sum, the stages that take Y G^T and what dX comes from along together, and the angles' sums, ms[3] = the
+ * contraction alone.  Returns GIVENS_ERR_UNSUPPORTED if timing was off for that call.
  */
 int givens_set_timing(int on);
 int givens_last_timing(float ms[4]);

@@ -592,7 +592,8 @@ def set_timing(on: bool) -> int:
 
 
 def last_timing():
-    """(table_ms, sweep_ms, reduce_ms, gram_ms) of the last call on this thread; waits for its events."""
+    """(table_ms, sweep_ms, reduce_ms, gram_ms) of the last call on this thread; waits for its events.  A backward call that
+    ran as tiles counts the slice sum and its stages, dX's among them, as reduce_ms (givens_rr.h)."""
     buf = (ctypes.c_float * 4)()
     _check(lib().givens_last_timing(buf), "givens_last_timing")
     return float(buf[0]), float(buf[1]), float(buf[2]), float(buf[3])
