@@ -863,6 +863,66 @@ struct TileTwoSidedShared {
     u32x4 panel[kTilePad / 32][kTilePad / 32][3][64];
     TileTurn turn[kTilePad / 32];
 };
+// The same for a pair of which one tile has no free pair (neither of them tile 0, with which row 0 goes): one product, R = A S of the
+// other tile's rows.  S is the operand that goes through LDS; its fragments are, negated, those of the mirrored block.
+// n = 4097, m = 512, where that is three pairs of four: 32.5 us a stage beside an operand of 4096 columns (both products, one of them
+// with the identity: 35.8).
+__device__ __forceinline__ void tile_one_sided(const TileTwoSidedArgs &a, const TilePair &pair, TileTwoSidedShared &sh)
+{
+    constexpr int MF = kTilePad / 32, KF = kTilePad / 16, KH = KF / 2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    TilePair t = pair;               // x: the tile that rotates
+    if (t.idx) {
+        t.x = pair.y;
+        t.y = pair.x;
+        t.ux = pair.uy;
+        t.uy = pair.ux;
+    }
+    TilePair mirror = t;
+    mirror.x = t.y;
+    mirror.y = t.x;
+    const u32x4 *px = a.pieces + tile_piece_index(a.g, a.stage, t.ux, false) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
+    const float scale = -tile_scale(a.range), undo = range_unscale(-scale);
+    f32x4 sr[KF][2];
+#pragma unroll
+    for (int k = 0; k < KF; ++k) tile_load_s(a, mirror, wave, k, sr[k]);
+    u32x4 fm[KH][1][3];
+    f32x16 R[1][MF];
+#pragma unroll
+    for (int j = 0; j < MF; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) R[0][j][v] = 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int k = 0; k < KH; ++k)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) fm[k][0][q] = px[(KH * h + k) * 192 + 64 * q];
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = sr[KH * h + k][q >> 2][q & 3] * scale;
+            const Split8 sp = split8(v);
+            sh.panel[k][wave][0][lane] = sp.h;
+            sh.panel[k][wave][1][lane] = sp.m;
+            sh.panel[k][wave][2][lane] = sp.l;
+        }
+        __syncthreads();   // (in the second half: every wavefront has read its part of S)
+#pragma unroll
+        for (int k = 0; k < KH; ++k) {
+            u32x4 fv[MF][3];
+#pragma unroll
+            for (int j = 0; j < MF; ++j)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) fv[j][q] = sh.panel[k][j][q][lane];
+            mfma_split(fm[k], fv, R);
+        }
+        if (h == 0) __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < MF; ++j) tile_store_both(a, t, R[0][j] * undo, wave, j, sh.turn[wave]);
+}
 __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsigned block_id, TileTwoSidedShared &sh)
 {
     constexpr int MF = kTilePad / 32, KF = kTilePad / 16, KH = KF / 2;
@@ -873,6 +933,7 @@ __device__ __forceinline__ void tile_two_sided(const TileTwoSidedArgs &a, unsign
     const TilePair t = tile_pair(a, block_id);
     const bool own = t.ux == t.uy;
     if (t.idx && t.idy) return;
+    if ((t.idx || t.idy) && t.ux != 0) return tile_one_sided(a, t, sh);
     const u32x4 *px = a.pieces + tile_piece_index(g, a.stage, t.ux, t.idx) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
     const u32x4 *py = a.pieces + tile_piece_index(g, a.stage, t.uy, t.idy) * kTilePieceWords + (size_t)wave * KF * 192 + lane;
 
