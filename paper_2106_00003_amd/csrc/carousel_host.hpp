@@ -24,6 +24,7 @@ struct CarouselCoefs {
     const float2 *renorm;
     const unsigned *flag;
     float scaled_max; // threshold of the scaled form (negative: never), see form_for_range
+    bool turned;      // the table's rows are in the order of turned_place
 };
 
 // n = 2 * M * L: M slots per lane in {8, 4, 2} (the scaled and lifted forms need a slot count that divides the
@@ -197,6 +198,17 @@ int carousel_backward_chain(const CarouselBwdArgs &a, const CarouselChainArgs &c
 constexpr int kUnitaryCarouselMinN = 128;
 inline bool unitary_carousel_supported(int n) { return n >= kUnitaryCarouselMinN && n <= 4096 && n % 16 == 0; }
 
+// Floats per lane of the forward sweep.  With several wavefronts as carousel_width has it, whole complex numbers.  Strips of one
+// wavefront, four of which are a workgroup: at most one per SIMD with two floats, two with four.  Phase passes, tables and sweep in us
+// with 2, 4 and 8 floats: n = 512, B = 1024 164 / 222 / 383, 1500 266 / 224 / 382, n = 1024, B = 1024 312 / 428 / 750, 1500 528 / 431 /
+// 756, 4000 1038 / 620 / 753 (a strip per workgroup, tables in the order of the angles, as carousel_width has it: n = 1024,
+// B = 16 302 (295), 1024 506, 1500 746, 4000 1085).
+inline int unitary_fwd_width(long long Breal, int waves)
+{
+    if (waves == 1) return Breal <= 2048 ? 2 : Breal <= 8192 ? 4 : 8;
+    const int W = carousel_width(Breal, waves);
+    return W < 2 ? 2 : W;
+}
 struct UnitaryCarouselFwdArgs {
     int n;
     long long Breal;
@@ -265,6 +277,9 @@ int carousel_backward_m5(const CarouselBwdArgs &a, int waves, int W);
 int carousel_backward_m3(const CarouselBwdArgs &a, int waves, int W);
 
 int carousel_forward_wave(const CarouselFwdArgs &a, int M, int W);
+// turned tables (M = 8): one wavefront per strip and `strips` of them per workgroup, and two to eight wavefronts per strip
+int carousel_forward_turned(const CarouselFwdArgs &a, int W, int strips);
+int carousel_forward_turned_lds(const CarouselFwdArgs &a, int waves, int W);
 int carousel_backward_wave(const CarouselBwdArgs &a, int M, int W);
 
 // Forward sweep.  A size with a one-wavefront shape always takes the wavefront exchange: measured against the LDS
@@ -289,6 +304,28 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
     return true;
 }
 
+// With eight slots per lane a row of the table is 4 KB, which every strip reads.  A strip that has its compute unit, or nearly, to
+// itself does well with a lane's slots side by side, and so does one of two columns with up to two others; beyond that the loads set
+// the time, unless the table is turned (turned_place in rr_index.h).  From four strips per compute unit on they are one
+// workgroup, whose wavefronts stay close enough to find their rows in the unit's L1.  Forward sweep and table in us, as they were (single
+// columns up to 512, then two) and turned, with single columns in workgroups of one and of four strips and with two columns in
+// workgroups of four: n = 528, B = 512 63 / 68, 528 92 / 65, 77, 792 96 / 81, 79; n = 768, B = 512 94 / 97, 768 137 / 100, 104, 1528
+// 139 / 169, 198, 148; n = 1024, B = 1024 182 / 149, 143, 1536 198 / 233, 265, 201, 2040 295 / 355, 314, 209.  (With the rows
+// brought to LDS once per workgroup: n = B = 1024 157.  Four slots per lane gain nothing: n = B = 512 38 / 45.)
+// Strips of several wavefronts, one or two columns: n = 1040, B = 1040 292 / 305, 1976 380 / 316, n = 1536, B = 1536 481 / 452,
+// n = 2048, B = 512 519 / 473, n = 3072, B = 512 1044 / 757, n = 4096, B = 512 1322 / 1182; wider ones have enough arithmetic per
+// row (n = B = 2048 730 / 784).
+constexpr int kTurnedSlots = 8, kTurnedStrips = 4;
+constexpr long long kTurnedSingleB = 1024;
+inline int turned_strips(long long B) { return B <= 768 ? 1 : kTurnedStrips; }
+inline bool carousel_turned(int n, long long B)
+{
+    CarouselPlan p;
+    if (!carousel_fwd_plan(n, B, &p) || p.s.M != kTurnedSlots) return false;
+    if (!p.wave) return p.W <= 2 && p.s.WAVES <= 8;
+    return (B > 512 && B <= kTurnedSingleB) || (B > 1536 && B <= 2048);
+}
+
 inline int carousel_forward(int n, int rows, long long B, const CarouselCoefs &coefs, const float *X, float *Y,
                             int identity, int mirror, hipStream_t stream)
 {
@@ -299,6 +336,9 @@ inline int carousel_forward(int n, int rows, long long B, const CarouselCoefs &c
     const bool aligned = (B % 4 == 0) && (reinterpret_cast<uintptr_t>(Y) % 16 == 0) &&
                          (identity || reinterpret_cast<uintptr_t>(X) % 16 == 0);
     const CarouselFwdArgs a{n, rows, B, coefs, X, Y, identity, aligned ? 1 : 0, mirror, stream};
+    if (coefs.turned)
+        return plan.wave ? carousel_forward_turned(a, B <= kTurnedSingleB ? 1 : 2, turned_strips(B))
+                         : carousel_forward_turned_lds(a, s.WAVES, W);
     if (plan.wave) return carousel_forward_wave(a, s.M, W);
     switch (s.M) {
     case 7: return carousel_forward_m7(a, s.WAVES, W);

@@ -138,12 +138,22 @@ __device__ __forceinline__ void lds_load_row(float (&dst)[W], const float *src)
     }
 }
 
+// Between a wavefront's stores to LDS and its other lanes' loads from there, or the other way round: its LDS operations run in order,
+// so this only holds the compiler to it.
+__device__ __forceinline__ void wavefront_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // FORM 0: standard rotation (2 MUL + 2 FMA per update, table holds cos and sin).
 // FORM 1: scaled rotation (2 FMA per update on values kept divided by their accumulated cosines,
 //         table holds alpha and beta, renormalisation every kRenormPeriod blocks; coef_kernels.hpp).
 // FORM 2: lifted rotation (3 dependent FMA per update: three shears; table holds tan(theta'/2) and
 //         sin(theta') with the carried signs folded in; same renormalisation points, factors +-1).
-template <int M, int W, int WAVES, int FORM, int EX = kExchangeLds>
+// TURNED: the table's rows are in the order of turned_place.
+template <int M, int W, int WAVES, int FORM, int EX = kExchangeLds, bool TURNED = false>
 struct CarouselFwd {
     static_assert(EX == kExchangeLds || WAVES == 1, "the DPP exchange stays inside one wavefront");
     // copies of the block body in one unrolled group: a multiple of M (static register map) and of the ring depth
@@ -159,15 +169,16 @@ struct CarouselFwd {
     float2 cs[kDepth][M];
     int n, H, lane, wave, tid;
     int lanes;              // L = n / (2 M): lanes that hold slots (wavefront exchange: where the far end is)
-    const float2 *tab_lane; // table + tid*M
+    const float2 *tab_lane; // table + tid*M (turned: + 2 tid)
     const float2 *rn_lane;  // renormalisation factors + tid*M (scaled form)
     // this lane's LDS addresses in exchange buffer 0 (buffer 1 is at a compile-time offset)
     float *out_top, *out_bot, *turn;
     const float *in_top, *in_bot;
     static constexpr int kBufFloats = (int)(sizeof(typename CarouselExchange<W, WAVES>::Buf) / sizeof(float));
 
-    __device__ __forceinline__ void load_coefs(int k, float2 (&dst)[M]) { load_row_of(tab_lane, k, dst); }
+    __device__ __forceinline__ void load_coefs(int k, float2 (&dst)[M]) { load_row_of<TURNED>(tab_lane, k, dst); }
 
+    template <bool TURN = false>
     __device__ __forceinline__ void load_row_of(const float2 *base, int row, float2 (&dst)[M])
     {
         const float2 *src = base + (long long)row * H;
@@ -175,7 +186,7 @@ struct CarouselFwd {
             const float4 *s4 = reinterpret_cast<const float4 *>(src);
 #pragma unroll
             for (int r = 0; r < M / 2; ++r) {
-                const float4 v = s4[r];
+                const float4 v = s4[TURN ? r * lanes : r];
                 dst[2 * r] = make_float2(v.x, v.y);
                 dst[2 * r + 1] = make_float2(v.z, v.w);
             }
@@ -417,26 +428,30 @@ __device__ __forceinline__ void store_row(const float (&src)[W], float *Y, long 
 // coefficient tables (theta_at in coef_kernels.hpp) the launch then computes U(theta)^T X.
 __device__ __forceinline__ int mirrored_row(int n, int r, int mirror) { return (mirror && r) ? n - r : r; }
 
-template <int M, int W, int WAVES, int FORM, int EX, typename Exchange>
+// TURNED with the exchange inside a wavefront: as many strips in a workgroup as it has wavefronts.
+template <int M, int W, int WAVES, int FORM, int EX, bool TURNED = false, typename Exchange>
 __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int rows, long long B,
                                                       const float2 *__restrict__ table,
                                                       const float2 *__restrict__ renorm, const float *X, float *Y,
                                                       int identity, int vec_ok, int mirror)
 {
-    using State = CarouselFwd<M, W, WAVES, FORM, EX>;
+    using State = CarouselFwd<M, W, WAVES, FORM, EX, TURNED>;
     State st;
+    constexpr bool kStrips = TURNED && EX == kExchangeWave;
     const int L = n / (2 * M);                  // lanes that hold slots; the rest of the last wavefront idles
     st.lanes = L;
-    const bool idle = (int)threadIdx.x >= L;
-    const int coef_lane = idle ? 0 : (int)threadIdx.x;
+    const int tid = kStrips ? (int)threadIdx.x & 63 : (int)threadIdx.x;
+    const bool idle = tid >= L;
+    const int coef_lane = idle ? 0 : tid;
     const int my_rows = idle ? 0 : rows;        // an idle lane loads zeros and stores nothing
     st.rn_lane = renorm + (long long)coef_lane * M;
     st.n = n;
     st.H = n >> 1;
-    st.tid = threadIdx.x;
+    st.tid = tid;
     st.lane = threadIdx.x & 63;
-    st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    st.tab_lane = table + (long long)coef_lane * M;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    st.wave = kStrips ? 0 : wave;
+    st.tab_lane = table + coef_lane * (TURNED ? 2 : M);
     if constexpr (EX == kExchangeLds) {
         constexpr int LMAX = 64 * WAVES;
         auto &b = sh.buf[0];
@@ -448,7 +463,8 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
         st.in_bot = (t > 0) ? b.bot_out.lane(t - 1) : b.top_out.lane(LMAX);      // near end: top[1] -> bot[0]
     }
 
-    const long long b0 = (long long)blockIdx.x * W;
+    const long long b0 = (kStrips ? (long long)blockIdx.x * (blockDim.x >> 6) + wave : (long long)blockIdx.x) * W;
+    if (kStrips && b0 >= B) return;
     const int wv = (B - b0) < W ? (int)(B - b0) : W;
     const bool vec = vec_ok && wv == W;
 
@@ -503,6 +519,24 @@ __global__ __launch_bounds__(64 * WAVES, WAVES > 8 ? 1 : 2) void carousel_forwar
             carousel_forward_body<M, W, WAVES, kFormStandard, EX>(sh, n, rows, B, table, renorm, X, Y, identity,
                                                                   vec_ok, mirror);
     }
+}
+
+// The same with a turned table (carousel_turned).
+template <int W, int WAVES, int EX>
+__global__ __launch_bounds__(EX == kExchangeWave ? 64 * kTurnedStrips : 64 * WAVES, 2) void carousel_forward_turned_kernel(
+    int n, int rows, long long B, const float2 *__restrict__ table, const float2 *__restrict__ renorm,
+    const unsigned *flag, float scaled_max, const float *X, float *Y, int identity, int vec_ok, int mirror)
+{
+    constexpr int M = kTurnedSlots;
+    using Exchange = std::conditional_t<EX == kExchangeLds, CarouselExchange<W, WAVES>, NoExchange>;
+    __shared__ Exchange sh;
+    const int form = __builtin_amdgcn_readfirstlane(selected_form(flag, scaled_max));
+    if (form == kFormScaled)
+        carousel_forward_body<M, W, WAVES, kFormScaled, EX, true>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror);
+    else if (form == kFormLifted)
+        carousel_forward_body<M, W, WAVES, kFormLifted, EX, true>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror);
+    else
+        carousel_forward_body<M, W, WAVES, kFormStandard, EX, true>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1248,6 +1282,24 @@ inline int carousel_forward_wave_slots(const CarouselFwdArgs &a, int W)
     case 1: carousel_launch_fwd_wave<M, 1>(a); return GIVENS_OK;
     default: return GIVENS_ERR_UNSUPPORTED;
     }
+}
+// turned tables: strips of one or two columns
+template <int W, int WAVES, int EX>
+inline void carousel_launch_fwd_turned(const CarouselFwdArgs &a, int strips)
+{
+    const long long columns = (long long)W * strips, groups = (a.B + columns - 1) / columns;
+    hipLaunchKernelGGL((carousel_forward_turned_kernel<W, WAVES, EX>), dim3((unsigned)groups), dim3(64 * WAVES * strips), 0,
+                       a.stream, a.n, a.rows, a.B, a.coefs.table, a.coefs.renorm, a.coefs.flag, a.coefs.scaled_max, a.X, a.Y,
+                       a.identity, a.vec_ok, a.mirror);
+}
+template <int WAVES>
+inline int carousel_forward_turned_widths(const CarouselFwdArgs &a, int W)
+{
+    if (W == 1)
+        carousel_launch_fwd_turned<1, WAVES, kExchangeLds>(a, 1);
+    else
+        carousel_launch_fwd_turned<2, WAVES, kExchangeLds>(a, 1);
+    return GIVENS_OK;
 }
 template <int M, int W>
 inline void carousel_launch_bwd_wave(const CarouselBwdArgs &a)

@@ -251,10 +251,14 @@ __global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int 
                 out.y = (T)(fac * s);
             }
         }
-        // slots of a lane of the sweep that reads the table, a power of two (wave_f64_kernels.hpp): first slots of 64 lanes,
-        // second slots, ...
+        // slots of a lane of the sweep that reads the table, a power of two: 16 bytes of every lane, then the next 16 (float64,
+        // wave_f64_kernels.hpp: of 64 lanes; float32: turned_place)
         const int shift = __ffs(slots) - 1;
-        table[slots ? (((long long)k << shift) + (p & (slots - 1))) * 64 + (p >> shift) : e] = out;
+        long long at = e;
+        if (slots)
+            at = std::is_same<T, float>::value ? (long long)k * H + turned_place(p, shift, H >> shift)
+                                               : (((long long)k << shift) + (p & (slots - 1))) * 64 + (p >> shift);
+        table[at] = out;
         if (factor) factor[e] = (T)fac;
     }
 }

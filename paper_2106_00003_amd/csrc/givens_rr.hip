@@ -345,9 +345,10 @@ struct Coefs {
     const float2 *renorm = nullptr;                 // scaled / lifted forms
     const unsigned *flag = nullptr;                 // nullptr: standard form, no range check was made
     float scaled_max = 0.f;
+    bool turned = false;                            // float: a table in the order of turned_place
     CarouselCoefs carousel() const
     {
-        return CarouselCoefs{reinterpret_cast<const float2 *>(table), renorm, flag, scaled_max};
+        return CarouselCoefs{reinterpret_cast<const float2 *>(table), renorm, flag, scaled_max, turned};
     }
 };
 
@@ -392,7 +393,7 @@ int workspace_coef_storage(Workspace &ws, CoefSet &set, int n, bool want_factor,
 {
     using P2 = typename Pair2<T>::type;
     const long long N = (long long)n * (n - 1) / 2;
-    if (int rc = grow(set.table, (size_t)(slots ? (n - 1) * 64LL * slots : N) * sizeof(P2))) return rc;
+    if (int rc = grow(set.table, (size_t)(slots && !std::is_same<T, float>::value ? (n - 1) * 64LL * slots : N) * sizeof(P2))) return rc;
     out->table = reinterpret_cast<P2 *>(set.table.ptr);
     if (want_factor) {
         if (int rc = grow(set.factor, (size_t)N * sizeof(T))) return rc;
@@ -574,6 +575,7 @@ int build_coefs(const CoefStorage<T> &st, const Problem &pb, const T *theta, boo
     out->factor = forward ? nullptr : st.factor;
     out->flag = flag;
     out->scaled_max = policy.scaled_max;
+    out->turned = std::is_same<T, float>::value && slots;
     t_state.last_flag = flag;
     t_state.last_scaled_max = policy.scaled_max;
     t_state.last_stream = stream;
@@ -651,6 +653,14 @@ int pick_backward_family(int n, long long B, int choice, Families *out)
     out->carousel = can_carousel && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_CAROUSEL);
     out->column = can_column && (choice == GIVENS_KERNEL_AUTO || choice == GIVENS_KERNEL_COLUMN);
     return GIVENS_OK;
+}
+
+// Slots per lane of the forward sweep that is to read the table in an order of its own, or 0.
+template <typename T>
+int forward_slots(const Families &fam, int n, long long swept)
+{
+    if (fam.wave64) return wave64_slots(n);
+    return std::is_same<T, float>::value && fam.carousel && carousel_turned(n, swept) ? kTurnedSlots : 0;
 }
 
 // The forward-type sweep of one call, coefficients given.
@@ -1179,7 +1189,9 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
             if (tiles)
                 return tiles_forward(nullptr, dev, pb, B, theta, identity ? nullptr : X, Y, transpose != 0, stream,
                                      &tile_buffers, &prod);
-            if (int rc = build_coefs<float>(st, pb, theta, true, policy, stream, &coefs, transpose)) return rc;
+            if (int rc = build_coefs<float>(st, pb, theta, true, policy, stream, &coefs, transpose,
+                                             forward_slots<float>(fam, n, swept)))
+                return rc;
             return run_forward<float>(nullptr, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream, &prod);
         }
     } else {
@@ -1187,7 +1199,7 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
         if constexpr (std::is_same<T, double>::value)
             if (wants_small<T>(opt, n, B, false)) return small_forward(pb, B, theta, X, Y, identity, transpose, stream);
         if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose,
-                                    fam.wave64 ? wave64_slots(n) : 0))
+                                    forward_slots<T>(fam, n, swept)))
             return rc;
     }
     return run_forward<T>(ws, dev, pb, B, coefs, fam, X, Y, identity, transpose, stream);
@@ -1632,8 +1644,7 @@ int unitary_carousel_forward(Workspace &ws, int n, long long B, const float *the
     if (int rc = unitary_carousel_coefs(ws, n, theta, phi, false, stream, &c)) return rc;
     const long long Breal = 2 * B;
     const int waves = (n / 16 + 63) / 64;
-    int W = carousel_width(Breal, waves);
-    if (W < 2) W = 2;
+    const int W = unitary_fwd_width(Breal, waves);
     const bool aligned = (Breal % 4 == 0) && (reinterpret_cast<uintptr_t>(Y) % 16 == 0) &&
                          (identity || reinterpret_cast<uintptr_t>(X) % 16 == 0);
     Span span(1, stream);

@@ -32,7 +32,7 @@ static void coefficients(int n, const float *theta, const float *phi, uint2 *q, 
     else
         launch_phase_scan<REVERSE, 2>(n, kPhaseScanThreads, q, turn, scan, stream);
     hipLaunchKernelGGL(unitary_carousel_table_kernel<REVERSE>, dim3(blocks), dim3(threads), 0, stream, n, theta, turn, scan, sgn,
-                       rot, phs, orient, fin);
+                       rot, phs, orient, fin, !REVERSE && n / 16 <= 64 ? 3 : 0);   // (forward sweeps of one wavefront: eight slots)
 }
 int unitary_carousel_coefficients(int n, const float *theta, const float *phi, int reverse, uint2 *q, unsigned *turn, void *scratch,
                                   float *sgn, float2 *rot, float2 *phs, float *orient, float2 *fin, hipStream_t stream)

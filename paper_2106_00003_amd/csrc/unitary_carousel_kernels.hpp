@@ -90,12 +90,14 @@ template <int M, int W, int WAVES>
 struct UnitaryCarouselFwd {
     static_assert(W % 2 == 0, "a lane holds whole complex numbers");
     static constexpr int kLastU = (2 * M - 2) % M;
+    static constexpr bool kTurned = WAVES == 1;   // strips of one wavefront: tables in the order of turned_place, workgroups of several strips
 
     float top[M][W];
     float bot[M][W];
     float2 rot[2][M], phs[2][M];
     int n, H, lane, wave, tid;
-    const float2 *rot_lane, *phs_lane; // tables + tid*M
+    const float2 *rot_lane, *phs_lane; // tables + tid*M (turned: + 2 tid)
+    int lanes;
     float *out_top, *out_bot, *turn;
     const float *in_top, *in_bot;
     static constexpr int kBufFloats = (int)(sizeof(typename CarouselExchange<W, WAVES>::Buf) / sizeof(float));
@@ -107,7 +109,7 @@ struct UnitaryCarouselFwd {
             const float4 *s4 = reinterpret_cast<const float4 *>(src);
 #pragma unroll
             for (int r = 0; r < M / 2; ++r) {
-                const float4 v = s4[r];
+                const float4 v = s4[kTurned ? r * lanes : r];
                 dst[2 * r] = make_float2(v.x, v.y);
                 dst[2 * r + 1] = make_float2(v.z, v.w);
             }
@@ -184,7 +186,10 @@ struct UnitaryCarouselFwd {
             rotate_inner<U, 2 + kInnerA>(cr, cp, std::make_integer_sequence<int, kInner - kInnerA>{});
 
         if constexpr (!LAST) {
-            __syncthreads();
+            if constexpr (kTurned)
+                wavefront_order();
+            else
+                __syncthreads();
             lds_load_row<W, WAVES>(top[q], in_top + par * kBufFloats);
             lds_load_row<W, WAVES>(bot[qb], in_bot + par * kBufFloats);
         }
@@ -211,35 +216,39 @@ struct UnitaryCarouselFwd {
 
 // X, Y: the complex operand as floats (row stride Breal = 2 B floats); fin: final phase per row.
 template <int M, int W, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 2) void unitary_carousel_forward_kernel(
+__global__ __launch_bounds__(64 * (WAVES == 1 ? kTurnedStrips : WAVES), 2) void unitary_carousel_forward_kernel(
     int n, long long Breal, const float2 *__restrict__ rot, const float2 *__restrict__ phs,
     const float2 *__restrict__ fin, const float *X, float *Y, int identity, int vec_ok)
 {
-    __shared__ CarouselExchange<W, WAVES> sh;
     using State = UnitaryCarouselFwd<M, W, WAVES>;
+    constexpr bool kTurned = State::kTurned;
+    __shared__ CarouselExchange<W, WAVES> exchange[kTurned ? kTurnedStrips : 1];
     State st;
-    const int L = n / (2 * M);
-    const bool idle = (int)threadIdx.x >= L;
-    const int coef_lane = idle ? 0 : (int)threadIdx.x;
+    const int L = n / (2 * M), tid = kTurned ? (int)threadIdx.x & 63 : (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), strip = kTurned ? wave : 0;
+    const bool idle = tid >= L;
+    const int coef_lane = idle ? 0 : tid;
     const int my_rows = idle ? 0 : n;
     st.n = n;
     st.H = n >> 1;
-    st.tid = threadIdx.x;
+    st.lanes = L;
+    st.tid = tid;
     st.lane = threadIdx.x & 63;
-    st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    st.rot_lane = rot + (long long)coef_lane * M;
-    st.phs_lane = phs + (long long)coef_lane * M;
+    st.wave = kTurned ? 0 : wave;
+    st.rot_lane = rot + coef_lane * (kTurned ? 2 : M);
+    st.phs_lane = phs + coef_lane * (kTurned ? 2 : M);
     {
         constexpr int LMAX = 64 * WAVES;
-        auto &b = sh.buf[0];
-        const int t = threadIdx.x;
+        auto &b = exchange[strip].buf[0];
+        const int t = tid;
         st.out_top = b.top_out.lane(t);
         st.out_bot = b.bot_out.lane(t);
         st.turn = b.top_out.lane(LMAX);
         st.in_top = (t < L - 1) ? b.top_out.lane(t + 1) : b.bot_out.lane(L - 1);
         st.in_bot = (t > 0) ? b.bot_out.lane(t - 1) : b.top_out.lane(LMAX);
     }
-    const long long b0 = (long long)blockIdx.x * W;
+    const long long b0 = (kTurned ? (long long)blockIdx.x * (blockDim.x >> 6) + strip : (long long)blockIdx.x) * W;
+    if (kTurned && b0 >= Breal) return;
     const int wv = (Breal - b0) < W ? (int)(Breal - b0) : W;
     const bool vec = vec_ok && wv == W;
 
@@ -561,8 +570,9 @@ __global__ __launch_bounds__(64 * WAVES, 2) void unitary_carousel_backward_kerne
 template <int M, int W, int WAVES>
 inline void unitary_carousel_launch_fwd(const UnitaryCarouselFwdArgs &a)
 {
-    const long long strips = (a.Breal + W - 1) / W;
-    hipLaunchKernelGGL((unitary_carousel_forward_kernel<M, W, WAVES>), dim3((unsigned)strips), dim3(64 * WAVES), 0,
+    constexpr int strips = WAVES == 1 ? kTurnedStrips : 1;
+    const long long columns = W * strips, groups = (a.Breal + columns - 1) / columns;
+    hipLaunchKernelGGL((unitary_carousel_forward_kernel<M, W, WAVES>), dim3((unsigned)groups), dim3(64 * WAVES * strips), 0,
                        a.stream, a.n, a.Breal, a.rot, a.phs, a.fin, a.X, a.Y, a.identity, a.vec_ok);
 }
 template <int M, int WAVES>

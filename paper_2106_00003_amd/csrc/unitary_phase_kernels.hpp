@@ -245,11 +245,13 @@ __device__ __forceinline__ unsigned phase_flip(const PhaseScan &scan, int row, i
 // the real rotation uses the angle sgn[e] * theta[e], reduced by a multiple of pi to theta' (and in the reverse
 // sweep sgn[e] is also the sign of the pair's dL/dtheta sum); with ORIENT, orient[e] = 1 when the top position of
 // the pair holds its smaller label (reverse sweep).
+// shift: log2 of the slots per lane of a sweep that reads rot and phs in the order of turned_place, or 0.
 // The first threads write fin[r], (cos, sin) of the phase row r ends with.
 template <bool ORIENT>
 __global__ void unitary_carousel_table_kernel(int n, const float *__restrict__ theta, const unsigned *__restrict__ turn,
                                               PhaseScan scan, float *__restrict__ sgn, float2 *__restrict__ rot,
-                                              float2 *__restrict__ phs, float *__restrict__ orient, float2 *__restrict__ fin)
+                                              float2 *__restrict__ phs, float *__restrict__ orient, float2 *__restrict__ fin,
+                                              int shift)
 {
     const int H = n >> 1, steps = phase_chunk_steps(n, scan.chunks);
     const long long N = (long long)(n - 1) * H;
@@ -271,9 +273,10 @@ __global__ void unitary_carousel_table_kernel(int n, const float *__restrict__ t
         reduce_by_pi((double)sg * (double)theta[e], &r);
         double s, c;
         sincos(0.5 * r, &s, &c);
-        rot[e] = make_float2((float)(s / c), (float)(2.0 * s * c));
+        const long long at = shift ? (long long)k * H + turned_place(p, shift, H >> shift) : e;
+        rot[at] = make_float2((float)(s / c), (float)(2.0 * s * c));
         sincos(0.5 * psi, &s, &c);
-        phs[e] = make_float2((float)(s / c), (float)(2.0 * s * c));
+        phs[at] = make_float2((float)(s / c), (float)(2.0 * s * c));
         sgn[e] = sg;
         if constexpr (ORIENT) orient[e] = i_on_top ? 1.f : 0.f;
     }
