@@ -41,6 +41,8 @@ EXPORTS = [
 ]
 
 _lib = None
+_entries = {}   # entry points by name and data type of the operand, as they are first used
+_raw_stream = _current_device = None
 
 
 class GivensError(RuntimeError):
@@ -124,10 +126,20 @@ def _check(rc: int, where: str):
         raise GivensError(rc, where)
 
 
+def current_stream_key():
+    """The current device and the address of its current stream (torch.cuda.current_stream() makes a Python object of it, which
+    takes longer than the rest of a call's marshalling)."""
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()     # (initialises)
+        _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    device = _current_device()
+    return device, _raw_stream(device)
+
+
 def _stream_ptr(stream):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return stream.cuda_stream if stream is not None else current_stream_key()[1]
 
 
 def _suffix(t) -> str:
@@ -139,6 +151,14 @@ def _suffix(t) -> str:
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+def _entry(name, t):
+    """The entry point `name` for operands of t's data type."""
+    fn = _entries.get((name, t.dtype))
+    if fn is None:
+        fn = _entries[name, t.dtype] = getattr(lib(), name + _suffix(t))
+    return fn
+
+
 def _dev(t, name, dtype=None):
     if t is None:
         return None
@@ -146,7 +166,7 @@ def _dev(t, name, dtype=None):
         raise ValueError(f"{name} must be a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} has dtype {t.dtype}, expected {dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def rr_schedule(n: int) -> np.ndarray:
@@ -160,13 +180,13 @@ def rr_schedule(n: int) -> np.ndarray:
 
 def givens_forward(theta, X, Y=None, stream=None):
     """Y = U(theta) X on the device.  Y=None allocates; Y may be X (in place)."""
-    import torch
     n, B = X.shape
     if theta.numel() != n * (n - 1) // 2:
         raise ValueError("theta must have n(n-1)/2 entries")
     if Y is None:
+        import torch
         Y = torch.empty_like(X)
-    fn = getattr(lib(), "givens_forward" + _suffix(X))
+    fn = _entry("givens_forward", X)
     _check(fn(n, B, _dev(theta, "theta", X.dtype), _dev(X, "X"), _dev(Y, "Y", X.dtype), _stream_ptr(stream)),
            "givens_forward")
     return Y
@@ -292,7 +312,7 @@ def givens_forward_transposed(theta, X, Y=None, stream=None):
         raise ValueError("theta must have n(n-1)/2 entries")
     if Y is None:
         Y = torch.empty_like(X)
-    fn = getattr(lib(), "givens_forward_transposed" + _suffix(X))
+    fn = _entry("givens_forward_transposed", X)
     _check(fn(n, B, _dev(theta, "theta", X.dtype), _dev(X, "X"), _dev(Y, "Y", X.dtype), _stream_ptr(stream)),
            "givens_forward_transposed")
     return Y
@@ -305,7 +325,7 @@ def givens_build(theta, n: int, U=None, stream=None):
         raise ValueError("theta must have n(n-1)/2 entries")
     if U is None:
         U = torch.empty((n, n), dtype=theta.dtype, device=theta.device)
-    fn = getattr(lib(), "givens_build" + _suffix(theta))
+    fn = _entry("givens_build", theta)
     _check(fn(n, _dev(theta, "theta"), _dev(U, "U", theta.dtype), _stream_ptr(stream)), "givens_build")
     return U
 
@@ -400,17 +420,18 @@ def givens_apply_kept(kept, theta, X, Y=None, stream=None):
 
 def givens_backward(theta, Y, G, dX=None, dtheta=None, want_dx: bool = True, stream=None):
     """Reverse sweep from the forward output Y and the upstream gradient G.  Returns (dX, dtheta)."""
-    import torch
     n, B = Y.shape
     if theta.numel() != n * (n - 1) // 2:
         raise ValueError("theta must have n(n-1)/2 entries")
     if G.shape != Y.shape:
         raise ValueError("G must have the shape of Y")
     if dX is None and want_dx:
+        import torch
         dX = torch.empty_like(G)
     if dtheta is None:
+        import torch
         dtheta = torch.empty_like(theta)
-    fn = getattr(lib(), "givens_backward" + _suffix(Y))
+    fn = _entry("givens_backward", Y)
     _check(fn(n, B, _dev(theta, "theta", Y.dtype), _dev(Y, "Y"), _dev(G, "G", Y.dtype),
               _dev(dX, "dX", Y.dtype), _dev(dtheta, "dtheta", Y.dtype), _stream_ptr(stream)),
            "givens_backward")
@@ -442,7 +463,7 @@ def givens_forward_restricted(theta, X, m: int, Y=None, stream=None):
         raise ValueError("theta must have m n - m (m + 1) / 2 entries")
     if Y is None:
         Y = torch.empty_like(X)
-    fn = getattr(lib(), "givens_forward_restricted" + _suffix(X))
+    fn = _entry("givens_forward_restricted", X)
     _check(fn(n, m, B, _dev(theta, "theta", X.dtype), _dev(X, "X"), _dev(Y, "Y", X.dtype), _stream_ptr(stream)),
            "givens_forward_restricted")
     return Y
@@ -454,7 +475,7 @@ def givens_build_restricted(theta, n: int, m: int, U=None, stream=None):
         raise ValueError("theta must have m n - m (m + 1) / 2 entries")
     if U is None:
         U = torch.empty((n, n), dtype=theta.dtype, device=theta.device)
-    fn = getattr(lib(), "givens_build_restricted" + _suffix(theta))
+    fn = _entry("givens_build_restricted", theta)
     _check(fn(n, m, _dev(theta, "theta"), _dev(U, "U", theta.dtype), _stream_ptr(stream)),
            "givens_build_restricted")
     return U
@@ -471,7 +492,7 @@ def givens_backward_restricted(theta, Y, G, m: int, dX=None, dtheta=None, want_d
         dX = torch.empty_like(G)
     if dtheta is None:
         dtheta = torch.empty_like(theta)
-    fn = getattr(lib(), "givens_backward_restricted" + _suffix(Y))
+    fn = _entry("givens_backward_restricted", Y)
     _check(fn(n, m, B, _dev(theta, "theta", Y.dtype), _dev(Y, "Y"), _dev(G, "G", Y.dtype),
               _dev(dX, "dX", Y.dtype), _dev(dtheta, "dtheta", Y.dtype), _stream_ptr(stream)),
            "givens_backward_restricted")

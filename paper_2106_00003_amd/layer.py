@@ -164,20 +164,21 @@ class _Run:
 class _KeptMatrix:
     """U of the present angles laid out for evaluation, for use on any stream: made on one, which others wait for."""
 
-    def __init__(self, theta, th, n, m, stream):
-        self.theta, self.version, self.stream = theta, theta._version, stream
+    def __init__(self, theta, th, n, m):
+        self.theta, self.version, self.stream = theta, theta._version, binding.current_stream_key()
         U = binding.givens_build(th, n) if _plain(n, m) else binding.givens_build_restricted(th, n, n - 1 if m is None else m)
         self.matrix = binding.Kept(th, U, m)
-        self.ready = stream.record_event()
+        self.ready = torch.cuda.current_stream().record_event()
 
     def of(self, theta) -> bool:
         return theta._version == self.version and theta.data_ptr() == self.theta.data_ptr()
 
-    def apply(self, th, x, stream):
-        if stream != self.stream:
+    def apply(self, th, x):
+        if binding.current_stream_key() != self.stream:
+            stream = torch.cuda.current_stream()
             stream.wait_event(self.ready)
             self.matrix.block.record_stream(stream)
-        return binding.givens_apply_kept(self.matrix, th, x, stream=stream)
+        return binding.givens_apply_kept(self.matrix, th, x)
 
 
 class OrthogonalLinear(torch.nn.Module):
@@ -201,19 +202,18 @@ class OrthogonalLinear(torch.nn.Module):
         self._captured = []       # those that recorded graphs read
 
     def forward(self, X: torch.Tensor) -> torch.Tensor:
-        if torch.is_grad_enabled() or self.theta.dtype != torch.float32:
-            return givens_apply(self.theta, X, self.m)
+        theta = self.theta
+        if torch.is_grad_enabled() or theta.dtype != torch.float32:
+            return givens_apply(theta, X, self.m)
         x = X.contiguous()
         if x.dim() != 2 or x.shape[0] != self.n or x.shape[1] == 0 or x.dtype != torch.float32 or not x.is_cuda:
-            return givens_apply(self.theta, X, self.m)   # refused there
+            return givens_apply(theta, X, self.m)   # refused there
         # evaluation: U of the current theta is built and laid out once, here and not in the workspace of the stream, which
         # all layers share, and multiplied with until theta changes.  The version counter tells most changes; writes that it
         # does not count (through .data, by a replayed graph) are seen on the device, which compares the angles.
-        theta = self.theta.detach()
         th = theta.contiguous()
         if self.n < _MATRIX_MIN_N:
             return _evaluate(th, x, self.m)
-        stream = torch.cuda.current_stream()
         kept = self._eval_matrix
         same = kept is not None and kept.of(theta)
         if torch.cuda.is_current_stream_capturing():
@@ -221,19 +221,19 @@ class OrthogonalLinear(torch.nn.Module):
                 return _evaluate(th, x, self.m)
             if not any(kept is k for k in self._captured):   # what a graph reads has to stay
                 self._captured.append(kept)
-            return binding.givens_apply_packed(kept.matrix.packed, x, stream=stream)
+            return binding.givens_apply_packed(kept.matrix.packed, x)
         run = self._eval_run
         if run is None or not run.of(theta) or (same and kept.matrix.changed()):
             # a new theta: by plain calls if the last one did not see enough batches to be worth a matrix
-            run = self._eval_run = _Run(theta, run is not None and run.batches < _worth_a_matrix(self.n))
+            run = self._eval_run = _Run(theta.detach(), run is not None and run.batches < _worth_a_matrix(self.n))
             same = False
         run.batches += 1
         if run.plain and run.batches <= _PLAIN_BATCHES * max(1, self.n // 2048):
             return _evaluate(th, x, self.m)
         if not same:
-            self._eval_matrix = kept = _KeptMatrix(theta, th, self.n, self.m, stream)
+            self._eval_matrix = kept = _KeptMatrix(theta.detach(), th, self.n, self.m)
         try:
-            return kept.apply(th, x, stream)
+            return kept.apply(th, x)
         except binding.GivensError as err:
             if err.code != binding.ERR_STALE:      # (known to have changed by now: the next batch is a new theta's)
                 raise
