@@ -7,12 +7,19 @@
 namespace givens {
 namespace {
 
-inline int tile_active(const TilePlan &g, int st, int free_rows)
+inline bool tile_restricted(const TilePlan &g, int free_rows) { return free_rows < g.n - 1; }
+inline TileList tile_list(const TilePlan &g, int st, int free_rows)
 {
-    if (free_rows >= g.n - 1) return g.P;
-    int active = 0;
-    for (int u = 0; u < g.P; ++u) active += tile_is_identity(g, tile_at(g, st, u), free_rows) ? 0 : 1;
-    return active;
+    TileList l;
+    l.active = 0;
+    for (int pass = 0, at = 0; pass < 2; ++pass)
+        for (int u = 0; u < g.P; ++u) {
+            const bool idle = tile_is_identity(g, tile_at(g, st, u), free_rows);
+            if (idle != (pass == 1)) continue;
+            l.tile[at++] = (unsigned char)u;
+            l.active = idle ? l.active : at;
+        }
+    return l;
 }
 // Stage st of Y <- U X or U^T X: the `first` one takes X, the last one leaves Y.  Returns the runs of column blocks for each tile
 // (0: no tile of the stage has a free pair).  A tile's matrix is worth loading for three steps where there are workgroups
@@ -20,10 +27,9 @@ inline int tile_active(const TilePlan &g, int st, int free_rows)
 // or three where each has a compute unit of its own.  Measured in us, alone with 1, 2, 3, 4, 8 steps: n = 1002 5.4, 6.6, 7.9, 9.2,
 // 15.1, n = 1700 10.1, 9.4, 9.2, 10.4, 15.9, n = 2050 13.3, 13.4, 11.8, 13.4, 16.4, n = 4098, m = 512 17.6, 15.0, 13.8, 14.3, 20.0;
 // beside pairs: n = 1002 10.0, 9.9, 9.2, 10.2, 15.8, n = 1024 10.8, 10.5, 11.2, 10.5, 16.0, n = 4098 36.6, 33.0, 32.2, 32.9, 37.1.
-inline long long tile_apply_stage(const TilePlan &g, int compute_units, long long pairs, int st, bool first, bool last, int rows,
-                                  int free_rows, const TileOperand &op, const TileBuffers &b, TileApplyArgs *out)
+inline long long tile_apply_stage(const TilePlan &g, int compute_units, long long pairs, int st, int active, bool first, bool last,
+                                  int rows, int free_rows, const TileOperand &op, const TileBuffers &b, TileApplyArgs *out)
 {
-    const int active = first || last ? g.P : tile_active(g, st, free_rows);
     if (active == 0) return 0;
     const long long steps = (op.B + kTileCols - 1) / kTileCols;
     auto groups = [&](long long per) { return pairs + active * ((steps + per - 1) / per); };
@@ -39,11 +45,19 @@ inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_
                        bool forward, hipStream_t stream)
 {
     for (int i = 0; i < g.stages; ++i) {
+        const int st = forward ? g.stages - 1 - i : i;
+        const bool first = i == 0, last = i == g.stages - 1;
+        TileList list{};
+        list.active = g.P;
+        const bool listed = tile_restricted(g, free_rows) && !first && !last;   // (those two take every tile)
+        if (listed) list = tile_list(g, st, free_rows);
         TileApplyArgs a;
-        const long long runs = tile_apply_stage(g, compute_units, 0, forward ? g.stages - 1 - i : i, i == 0,
-                                                i == g.stages - 1, rows, free_rows, op, b, &a);
-        if (runs)
-            hipLaunchKernelGGL(tile_apply_kernel, dim3((unsigned)(runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
+        const long long runs = tile_apply_stage(g, compute_units, 0, st, list.active, first, last, rows, free_rows, op, b, &a);
+        const dim3 grid((unsigned)(runs * list.active));
+        if (runs && listed)
+            hipLaunchKernelGGL(tile_apply_kernel<TileList>, grid, dim3(2 * kTilePad), 0, stream, a, list);
+        else if (runs)
+            hipLaunchKernelGGL(tile_apply_kernel<TileAll>, grid, dim3(2 * kTilePad), 0, stream, a, TileAll{});
     }
 }
 inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int free_rows, const float *theta, const int *map,
@@ -52,18 +66,29 @@ inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int fr
 {
     const u32x4 *pieces = static_cast<const u32x4 *>(b.pieces);
     const bool narrow = tile_gradient_narrow(g, compute_units, free_rows);
-    const unsigned pairs = (unsigned)(g.P * (g.P + 1) / 2) * (narrow ? kTilePad / 32 : 1);
     float *second = narrow ? b.S + tile_s_floats(g) : nullptr;
     hipLaunchKernelGGL(tile_antisym_kernel, dim3(tile_antisym_blocks(g)), dim3(256), 0, stream, g, rows, slices, C, b.S, b.range);
     float *in = b.S, *out = second ? second : b.S;
     for (int st = 0; st < g.stages; ++st) {
+        // (the narrow kernel leaves no pair out, since its result is another array, and the first and last stage of an operand no tile)
+        const bool first = st == 0, last = st == g.stages - 1, listed = tile_restricted(g, free_rows) && !narrow && !((first || last) && op.Y);
+        TileList list{};
+        list.active = g.P;
+        if (listed) list = tile_list(g, st, free_rows);
+        const int c = list.active;
+        const unsigned pairs = (unsigned)(c * (c + 1) / 2 + c * (g.P - c)) * (narrow ? kTilePad / 32 : 1);
         TileStageArgs a{TileTwoSidedArgs{g, st, free_rows, pieces, in, out, b.blocks, b.range}, {}, pairs};
         long long runs = 0;
-        if (op.Y)
-            runs = tile_apply_stage(g, compute_units, pairs, st, st == 0, st == g.stages - 1, rows, free_rows, op, b, &a.a);
-        const auto kernel = narrow ? (runs ? tile_stage_kernel<true, true> : tile_stage_kernel<true, false>)
-                                   : (runs ? tile_stage_kernel<false, true> : tile_stage_kernel<false, false>);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(pairs + runs * g.P)), dim3(2 * kTilePad), 0, stream, a);
+        if (op.Y) runs = tile_apply_stage(g, compute_units, pairs, st, c, first, last, rows, free_rows, op, b, &a.a);
+        const dim3 grid((unsigned)(pairs + runs * c)), block(2 * kTilePad);
+        if (listed && c) {
+            const auto kernel = runs ? tile_stage_kernel<false, true, TileList> : tile_stage_kernel<false, false, TileList>;
+            hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, list);
+        } else if (!listed) {
+            const auto kernel = narrow ? (runs ? tile_stage_kernel<true, true, TileAll> : tile_stage_kernel<true, false, TileAll>)
+                                       : (runs ? tile_stage_kernel<false, true, TileAll> : tile_stage_kernel<false, false, TileAll>);
+            hipLaunchKernelGGL(kernel, grid, block, 0, stream, a, TileAll{});
+        }
         if (second) std::swap(in, out);
     }
     hipLaunchKernelGGL(tile_gradient_kernel, dim3((unsigned)(2 * g.P + tile_count(g))), dim3(kTileThreads), 0, stream, g, theta,
