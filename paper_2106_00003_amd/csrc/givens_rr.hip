@@ -21,6 +21,7 @@
 #include "small_kernels.hpp"
 #include "tile_host.hpp"
 #include "unitary_kernels.hpp"
+#include "wide_small_kernels.hpp"
 
 namespace givens {
 namespace {
@@ -725,14 +726,14 @@ long long swept_columns(const Families &fam, int rows, long long B)
 
 // Y = A X for the rows x rows matrix A = st.matrix; Y may be X.  cplx: complex operands, B real columns.
 int apply_matrix(const ProductStorage &st, int dev, int rows, long long B, const float *X, float *Y, hipStream_t stream,
-                 bool cplx = false)
+                 bool cplx = false, bool split = false)   // split: st.pieces are there
 {
     const int k = cplx ? 2 * rows : rows;
     int cus = 0;
     GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     t_state.last_product = 1;
     Span span(1, stream);
-    split_matrix(rows, k, st.matrix, st.pieces, stream, cplx);
+    if (!split) split_matrix(rows, k, st.matrix, st.pieces, stream, cplx);
     const long long chunk = X == Y ? st.copy_cols : B;   // a result that overwrites its operand: from copies
     for (long long c0 = 0; c0 < B; c0 += chunk) {
         const long long cols = std::min(chunk, B - c0);
@@ -771,6 +772,21 @@ int run_forward(Workspace *ws, int dev, const Problem &pb, long long B, const Co
     return run_forward_sweep<T>(pb, B, coefs, fam, X, Y, identity, transpose, stream);
 }
 
+// The row of zeros and the sink of a carousel family's reverse sweep over N angles.
+int sweep_ends(Workspace &ws, long long N, hipStream_t stream, const float **zeros, float **sink)
+{
+    const size_t want = (size_t)N * sizeof(float);
+    if (ws.zeros.bytes < want) {
+        if (int rc = grow(ws.zeros, want)) return rc;
+        hipLaunchKernelGGL(fill_zero_kernel, dim3(2048), dim3(256), 0, stream, N, reinterpret_cast<float *>(ws.zeros.ptr));
+        GIVENS_HIP(hipGetLastError());
+    }
+    *zeros = reinterpret_cast<const float *>(ws.zeros.ptr);
+    if (int rc = grow(ws.sink, ((size_t)N + 8192) * sizeof(float))) return rc;
+    *sink = reinterpret_cast<float *>(ws.sink.ptr);
+    return GIVENS_OK;
+}
+
 // Reverse sweep and the reduction of its partial sums into dtheta.  LDS family: chunks of strips, one
 // partial sum per (strip, angle), folded into dtheta chunk by chunk.  Carousel family: persistent
 // workgroups with one row of partial sums each.
@@ -803,18 +819,8 @@ int backward_chunks(Workspace &ws, int dev, bool carousel, const Problem &pb, lo
     const float *zeros = nullptr;
     float *sink = nullptr;
     if constexpr (std::is_same<T, float>::value) {
-        if (carousel) {
-            const size_t want = (size_t)N * sizeof(float);
-            if (ws.zeros.bytes < want) {
-                if (int rc = grow(ws.zeros, want)) return rc;
-                hipLaunchKernelGGL(fill_zero_kernel, dim3(2048), dim3(256), 0, stream, N,
-                                   reinterpret_cast<float *>(ws.zeros.ptr));
-                GIVENS_HIP(hipGetLastError());
-            }
-            zeros = reinterpret_cast<const float *>(ws.zeros.ptr);
-            if (int rc = grow(ws.sink, ((size_t)N + 8192) * sizeof(float))) return rc;
-            sink = reinterpret_cast<float *>(ws.sink.ptr);
-        }
+        if (carousel)
+            if (int rc = sweep_ends(ws, N, stream, &zeros, &sink)) return rc;
     }
     t_state.last_reduction = GIVENS_REDUCTION_TWO_STAGE;
 
@@ -1090,6 +1096,86 @@ int tiles_backward(Workspace &ws, int dev, const Problem &pb, long long B, const
     return multiplies ? apply_matrix(st, dev, pb.rows, B, G, dX, stream) : GIVENS_OK;
 }
 
+// Smallest matrices on wide batches (wide_small_kernels.hpp): the column family's sizes up to kWideSmallMaxN, where the forward call
+// multiplies and the backward one takes the Gram form and wants dX in memory of its own.
+bool wide_small(const Families &fam, int n) { return fam.column && column_wave(n) && n <= kWideSmallMaxN; }
+int wide_small_forward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *X, float *Y,
+                       bool transpose, hipStream_t stream)
+{
+    ProductStorage st;
+    if (int rc = workspace_product_storage(ws, pb.rows, B, X == Y, &st)) return rc;
+    t_state.last_kernel = GIVENS_KERNEL_COLUMN;
+    t_state.last_flag = nullptr;
+    {
+        Span span(0, stream);
+        hipLaunchKernelGGL(small_matrix_kernel, dim3(small_matrix_blocks(pb.rows)), dim3(kSmallMatrixThreads), 0, stream,
+                           SmallMatrixArgs{pb.n, pb.rows, transpose ? 1 : 0, (int)product_k16(pb.rows), theta, pb.map, st.pieces});
+        GIVENS_HIP(hipGetLastError());
+    }
+    return apply_matrix(st, dev, pb.rows, B, X, Y, stream, false, true);
+}
+int wide_small_backward(Workspace &ws, int dev, const Problem &pb, long long B, const float *theta, const float *Y, const float *G,
+                        float *dX, float *dtheta, hipStream_t stream)
+{
+    const int n = pb.n, rows = pb.rows;
+    const long long N = (long long)n * (n - 1) / 2;
+    int cus = 0;
+    GIVENS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    GramPlan plan = gram_plan(rows, B, cus);
+    if (int rc = grow(ws.gram, (size_t)plan.slices * rows * rows * sizeof(float))) return rc;
+    float *C = reinterpret_cast<float *>(ws.gram.ptr);
+    CoefStorage<float> coefs;
+    if (int rc = workspace_coef_storage<float>(ws, ws.rev, n, true, false, 0, stream, &coefs, false)) return rc;
+    ProductStorage st;
+    if (int rc = workspace_product_storage(ws, rows, B, false, &st)) return rc;
+    if (int rc = grow(ws.partial, (size_t)rows * N * sizeof(float))) return rc;
+    const float *zeros = nullptr;
+    float *sink = nullptr;
+    if (int rc = sweep_ends(ws, N, stream, &zeros, &sink)) return rc;
+    float *partial = reinterpret_cast<float *>(ws.partial.ptr);
+    t_state.last_kernel = GIVENS_KERNEL_COLUMN;
+    t_state.last_flag = nullptr;
+    t_state.last_reduction = GIVENS_REDUCTION_GRAM;
+    t_state.last_chains = 0;
+    t_state.last_product = 1;
+    {
+        Span span(3, stream);
+        GramArgs g{rows, B, plan.cols, Y, G, C, 1, 1, rows};      // (one tile of 64 x 64 per slice)
+        const SmallMatrixArgs m{n, rows, 1, (int)product_k16(rows), theta, pb.map, st.pieces};
+        const unsigned extra = wide_small_extra(rows);
+        const auto kernel = B % kGramK == 0 && rows == 64 ? wide_small_gram_kernel<false> : wide_small_gram_kernel<true>;
+        hipLaunchKernelGGL(kernel, dim3(extra + plan.slices), dim3(256), 0, stream, g, m, small_matrix_blocks(rows), extra, coefs.table,
+                           coefs.factor);
+        sum_gram(rows, plan, C, stream);
+        GIVENS_HIP(hipGetLastError());
+    }
+    {
+        Span span(1, stream);
+        ProductArgs p{rows, rows, B, st.pieces, G, B, dX, B, 0, false};
+        const SmallSweepArgs s{n, rows, coefs.table, C, partial, zeros, sink};
+        const unsigned sweeps = (unsigned)(rows + 7) / 8 * 8;
+        if (product_is_narrow(rows, B, cus)) {
+            p.mblocks = (rows + 31) / 32;
+            hipLaunchKernelGGL(wide_small_narrow_kernel, dim3(sweeps + (unsigned)product_narrow_blocks(rows, B)),
+                               dim3(64 * kNarrowWaves), 0, stream, p, s, sweeps);
+        } else {
+            p.mblocks = 1;
+            hipLaunchKernelGGL(wide_small_product_kernel, dim3(sweeps + (unsigned)(((B + 63) / 64 + 7) / 8 * 8)), dim3(256), 0, stream,
+                               p, s, sweeps);
+        }
+        GIVENS_HIP(hipGetLastError());
+    }
+    Span span(2, stream);
+    if (rows >= 4 * kReduceSplit)
+        hipLaunchKernelGGL(reduce_partials_split_kernel<float>, dim3((unsigned)((N + 63) / 64)), dim3(64 * kReduceSplit), 0, stream, n,
+                           (long long)rows, partial, coefs.factor, pb.map, dtheta, 0);
+    else
+        hipLaunchKernelGGL(reduce_partials_kernel<float>, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, stream, n, (long long)rows,
+                           partial, coefs.factor, pb.map, dtheta, 0, (const unsigned *)nullptr);
+    GIVENS_HIP(hipGetLastError());
+    return GIVENS_OK;
+}
+
 // Smallest problems (float64, nothing chosen): one kernel per call, or with several workgroups in the reverse sweep two
 // (small_kernels.hpp).  Measured in us, table and wavefront sweep against it: forward n = 24, B = 64 10.0 / 8.3, 1024 10.0 / 8.6,
 // n = 32, B = 4 10.0 / 8.2, 64 9.9 / 10.1; backward n = 16, B = 1024 13.4 / 11.3, n = 24, B = 4 13.2 / 9.1, 256 13.2 / 14.5,
@@ -1196,6 +1282,9 @@ int forward_impl(int rows, int m, long long B, const T *theta, const T *X, T *Y,
         }
     } else {
         invalidate_prepared(*ws, true, false);
+        if constexpr (std::is_same<T, float>::value)
+            if (!identity && wide_small(fam, n) && wants_product<T>(fam, rows, B))
+                return wide_small_forward(*ws, dev, pb, B, theta, X, Y, transpose != 0, stream);
         if constexpr (std::is_same<T, double>::value)
             if (wants_small<T>(opt, n, B, false)) return small_forward(pb, B, theta, X, Y, identity, transpose, stream);
         if (int rc = build_coefs<T>(*ws, ws->fwd, pb, theta, true, policy, stream, &coefs, transpose,
@@ -1282,6 +1371,9 @@ int backward_impl(int rows, int m, long long B, const T *theta, const T *Y, cons
         if (wants_tiles(opt, n, swept, true)) return tiles_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
     if (opt.kernel == GIVENS_KERNEL_TILES) return GIVENS_ERR_UNSUPPORTED;
     invalidate_prepared(*ws, false, true);
+    if constexpr (std::is_same<T, float>::value)
+        if (wide_small(fam, n) && wants_gram<T>(n, B, opt.reduction) && dX && dX != G)
+            return wide_small_backward(*ws, dev, pb, B, theta, Y, G, dX, dtheta, stream);
     if constexpr (std::is_same<T, double>::value)
         if (wants_small<T>(opt, n, B, true)) return small_backward(*ws, pb, B, theta, Y, G, dX, dtheta, stream);
     Coefs<T> coefs;

@@ -50,8 +50,12 @@ struct GramArgs {
 // slice are not full; rows past the end repeat the last one, and only the step that reaches past the slice's end goes
 // element by element.
 template <int MW, int NW, int MF, int NF, bool GUARD, bool CPLX>
-__global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
+__device__ __forceinline__ void gram_tile(const GramArgs &args, unsigned block, unsigned blocks)
 {
+    // (values: a choice between two members would be one between their addresses)
+    const GramArgs a = args;
+    const float *const Y = a.Y, *const G = a.G;
+    const int y_rows = a.rows, g_rows = a.cols;
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW, BOTH = BM + BN;
     constexpr int PER = BOTH * 2 / T;                  // octets per thread and step
     static_assert(BOTH * 2 % T == 0, "whole octets per thread");
@@ -62,7 +66,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
     // The list of (slice, tile row, tile column) is cut into eight consecutive parts, one per XCD, so that the workgroups
     // that share an L2 at any time work on neighbouring tiles of one slice and reuse each other's panels (64 x 64 tiles, handed
     // out in turn and so, in us: n = 314, B = 15395 in 60 slices 69 and 37, n = 192, B = 55531 in 170 81 and 41).
-    const unsigned id = xcd_order(blockIdx.x, gridDim.x);
+    const unsigned id = xcd_order(block, blocks);
     const int tile_j = id % a.tiles_n, tile_i = (id / a.tiles_n) % a.tiles_m;
     const unsigned slice = id / (a.tiles_n * a.tiles_m);
     const long long kbeg = (long long)slice * a.slice_cols;
@@ -76,10 +80,10 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
             const int pr = c >> 1;                     // panel row
             const bool of_y = pr < BM;
             int r = of_y ? tile_i * BM + pr : tile_j * BN + (pr - BM);
-            const float *src = of_y ? a.Y : a.G;
+            const float *src = of_y ? Y : G;
             const long long k = k0 + 8 * (c & 1);
             if constexpr (GUARD) {                     // past the end: its results are not stored
-                const int end = of_y || !CPLX ? a.rows : a.cols;
+                const int end = of_y || !CPLX ? y_rows : g_rows;
                 r = r < end ? r : end - 1;
             }
             const bool turned = CPLX && !of_y && r >= a.rows;
@@ -224,6 +228,11 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
             }
     }
 }
+template <int MW, int NW, int MF, int NF, bool GUARD, bool CPLX>
+__global__ __launch_bounds__(64 * MW * NW, 2) void gram_tile_kernel(GramArgs a)
+{
+    gram_tile<MW, NW, MF, NF, GUARD, CPLX>(a, blockIdx.x, gridDim.x);
+}
 
 // c[0] += c[1] + ... + c[slices-1] element by element: 64 elements at a time per workgroup, kSumGroups threads for each,
 // thread g adding the slices g, g + kSumGroups, ... and the first one the sums, in that order (a single thread per element
@@ -281,16 +290,19 @@ inline void gram_slices(int rows, long long B, const GramPlan &plan, const float
         launch_gram<2, 2, 1, 1, CPLX>(a, plan.slices, stream);
 }
 // ... and their sum, into the first of them
+inline void sum_gram(int rows, const GramPlan &plan, float *C, hipStream_t stream, bool cplx = false)
+{
+    if (plan.slices <= 1) return;
+    const long long count = (long long)rows * (cplx ? 2 * rows : rows);
+    const unsigned blocks = (unsigned)((count + 63) / 64 < kSumBlocks ? (count + 63) / 64 : kSumBlocks);
+    hipLaunchKernelGGL(sum_slices_kernel, dim3(blocks), dim3(64 * kSumGroups), 0, stream, count, plan.slices, C);
+}
 template <bool CPLX = false>
 inline void gram_matrix(int rows, long long B, const GramPlan &plan, const float *Y, const float *G, float *C,
                         hipStream_t stream)
 {
     gram_slices<CPLX>(rows, B, plan, Y, G, C, stream);
-    if (plan.slices > 1) {
-        const long long count = (long long)rows * (CPLX ? 2 * rows : rows);
-        const unsigned blocks = (unsigned)((count + 63) / 64 < kSumBlocks ? (count + 63) / 64 : kSumBlocks);
-        hipLaunchKernelGGL(sum_slices_kernel, dim3(blocks), dim3(64 * kSumGroups), 0, stream, count, plan.slices, C);
-    }
+    sum_gram(rows, plan, C, stream, CPLX);
 }
 
 } // namespace givens

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kept_kern
         kept_angles<false>(k, (long long)(blockIdx.x - product_blocks) * (64 * kNarrowWaves) + threadIdx.x,
                            (long long)(gridDim.x - product_blocks) * (64 * kNarrowWaves));
     else
-        product_narrow<false>(a, sh);
+        product_narrow<false>(a, sh, blockIdx.x);
 }
 
 } // namespace givens

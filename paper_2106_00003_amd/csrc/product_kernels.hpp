@@ -79,7 +79,7 @@ struct ProductArgs {
 // workgroups per compute unit: n = 2048, B = 65536 in 2.76 ms = 199 TFLOP/s of float32 product (1190 of bf16; the
 // float32 matrix instructions reach about 129), 128 x 128 3.03 ms; n = B = 4096 0.69 ms against 0.83.
 template <int MW, int NW, int MF, int NF, int DEPTH, bool CPLX>
-__global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
+__device__ __forceinline__ void product_tiled(const ProductArgs &a, unsigned block)
 {
     constexpr int T = 64 * MW * NW, BM = 32 * MF * MW, BN = 32 * NF * NW;
     constexpr int OCT = BN * 4 / T;                    // octets (8 rows x 1 column of X) a thread brings per step
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     const int wm = wave % MW, wn = wave / MW;
     // workgroups reach the XCDs in turn: those of one XCD take all row blocks of a column block one after the other, so
     // that the column block is read into one L2
-    const unsigned xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+    const unsigned xcd = block % 8, local = block / 8;
     const int mb = local % a.mblocks;
     const long long n0 = ((long long)(local / a.mblocks) * 8 + xcd) * BN;
     if (n0 >= a.B) return;
@@ -237,6 +237,12 @@ __global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
     }
 }
 
+template <int MW, int NW, int MF, int NF, int DEPTH, bool CPLX>
+__global__ __launch_bounds__(64 * MW * NW, 2) void product_kernel(ProductArgs a)
+{
+    product_tiled<MW, NW, MF, NF, DEPTH, CPLX>(a, blockIdx.x);
+}
+
 // D = A X for few columns, where tiles of 64 x 64 leave most of the chip idle and each walks the whole contraction step by
 // step.  A workgroup takes 32 x 32 results, its eight wavefronts a part of the contraction each (operands straight from
 // memory: a lane's eight values of X are rows of one column), two fragments ahead; the parts are added through LDS in
@@ -248,12 +254,12 @@ struct NarrowShared {
     float tops[kNarrowWaves][32];      // largest magnitude of every column in each wavefront's part of the contraction
 };
 template <bool CPLX>
-__device__ __forceinline__ void product_narrow(const ProductArgs &a, NarrowShared &sh)
+__device__ __forceinline__ void product_narrow(const ProductArgs &a, NarrowShared &sh, unsigned block)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int mb = blockIdx.x % a.mblocks;
-    const long long n0 = (long long)(blockIdx.x / a.mblocks) * 32;
+    const int mb = block % a.mblocks;
+    const long long n0 = (long long)(block / a.mblocks) * 32;
     const int k16s = 2 * ((a.k + kProductStep - 1) / kProductStep);
     const int per = (k16s + kNarrowWaves - 1) / kNarrowWaves;
     const int k_from = wave * per, k_to = k_from + per < k16s ? k_from + per : k16s;
@@ -330,7 +336,7 @@ template <bool CPLX>
 __global__ __launch_bounds__(64 * kNarrowWaves, 1) void product_narrow_kernel(ProductArgs a)
 {
     __shared__ NarrowShared sh;
-    product_narrow<CPLX>(a, sh);
+    product_narrow<CPLX>(a, sh, blockIdx.x);
 }
 
 // DEPTH: of real operands whose contraction is long enough; complex ones have no registers to spare for more than one step

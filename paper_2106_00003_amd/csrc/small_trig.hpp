@@ -32,4 +32,26 @@ __device__ __forceinline__ double sin_small(double x)
     return fma(p * z, x, x);
 }
 
+// cos and sine of an angle in float64, to 1e-16 up to 1e5 (reduced by multiples of pi / 2)
+__device__ __forceinline__ double2 tile_sincos(double th)
+{
+    double s, c;
+    if (fabs(th) <= 1.0e5) {
+        const double k = rint(th * 0.63661977236758134308);
+        const double r = fma(-k, 6.123233995736766036e-17, fma(-k, 1.5707963267948965580, th));
+        const double sr = sin_small(r), cr = cos_small(r);
+        const int quarter = (int)k & 3;
+        s = quarter & 1 ? cr : sr;
+        c = quarter & 1 ? sr : cr;
+        if (quarter & 2) s = -s;
+        if (quarter == 1 || quarter == 2) c = -c;
+    } else {
+        sincos(th, &s, &c);
+    }
+    double2 out;
+    out.x = c;
+    out.y = s;
+    return out;
+}
+
 } // namespace givens

@@ -115,28 +115,6 @@ __device__ __forceinline__ bool tile_has_pair(const TilePlan &g, const Tile &x, 
 {
     return x.kind == kTileSpecial || (a + b >= g.m) == (x.kind == kTileEarly);
 }
-// cos and sine of an angle in float64, to 1e-16 up to 1e5 (reduced by multiples of pi / 2)
-__device__ __forceinline__ double2 tile_sincos(double th)
-{
-    double s, c;
-    if (fabs(th) <= 1.0e5) {
-        const double k = rint(th * 0.63661977236758134308);
-        const double r = fma(-k, 6.123233995736766036e-17, fma(-k, 1.5707963267948965580, th));
-        const double sr = sin_small(r), cr = cos_small(r);
-        const int quarter = (int)k & 3;
-        s = quarter & 1 ? cr : sr;
-        c = quarter & 1 ? sr : cr;
-        if (quarter & 2) s = -s;
-        if (quarter == 1 || quarter == 2) c = -c;
-    } else {
-        sincos(th, &s, &c);
-    }
-    double2 out;
-    out.x = c;
-    out.y = s;
-    return out;
-}
-
 // The range (split_bf16.hpp) of the gradient's matrix S, one for all of it: the stages keep its norm.  Words that the build kernel clears
 // and the antisymmetric part's sets, 1 each: an element other than zero, one of the middle range or above, one above it.
 // Behind them, cleared with them, a count for every special tile (tile_gradient_kernel).

@@ -1,0 +1,92 @@
+"""Smallest matrices on wide batches: every size of the range, odd ones and restricted parametrisations among them, batches on both
+sides of what the product takes narrow and of whole tiles and slices, in place, the transpose, graphs, against float64."""
+import pytest
+
+from paper_2106_00003_amd import binding
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.set_kernel(binding.KERNEL_AUTO)
+    yield
+    binding.release()
+
+
+def rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+def problem(n, m, B, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    th = (torch.rand(binding.num_angles(n, m), device="cuda", generator=gen) * 2 - 1) * 3.1
+    return th, *(torch.randn(n, B, device="cuda", generator=gen) for _ in range(2))
+
+
+def check(n, m, B):
+    th, x, g = problem(n, m, B, 11 * n + B)
+    want_y = binding.givens_forward_restricted(th.double(), x.double(), m)
+    want_dx, want_dth = binding.givens_backward_restricted(th.double(), want_y, g.double(), m)
+    y = binding.givens_forward_restricted(th, x, m)
+    assert binding.last_kernel() == binding.KERNEL_COLUMN
+    dx, dth = binding.givens_backward_restricted(th, y, g, m)
+    assert binding.last_kernel() == binding.KERNEL_COLUMN and binding.last_reduction() == binding.REDUCTION_GRAM and binding.last_product()
+    assert rel(y, want_y) <= 1e-5 and rel(dx, want_dx) <= 1e-4 and rel(dth, want_dth) <= 1e-4
+    buf = x.clone()
+    assert torch.equal(binding.givens_forward_restricted(th, buf, m, Y=buf), y)
+    buf = g.clone()                                                # in place: the calls of the other sizes
+    again_dx, again_dth = binding.givens_backward_restricted(th, y, buf, m, dX=buf)
+    assert rel(again_dx, dx.double()) <= 1e-6 and rel(again_dth, dth.double()) <= 2e-6
+    assert rel(binding.givens_backward_restricted(th, y, g, m, want_dx=False)[1], dth.double()) <= 2e-6
+
+
+@pytest.mark.parametrize("n", range(16, 67))
+def test_every_size(n):
+    check(n, n - 1, 2048 + 37 * n)
+
+
+@pytest.mark.parametrize("n,m,B", [(64, 63, 2048), (64, 63, 24576), (64, 63, 24577), (62, 61, 24609), (33, 32, 49153), (63, 5, 30000),
+                                   (17, 1, 65536), (48, 20, 40001), (64, 30, 65535)])
+def test_batches_and_restricted(n, m, B):
+    check(n, m, B)
+
+
+def test_gram_form_chosen_for_a_narrow_batch():
+    th, x, g = problem(40, 39, 7, 5)
+    want_y = binding.givens_forward(th.double(), x.double())
+    want_dx, want_dth = binding.givens_backward(th.double(), want_y, g.double())
+    dx, dth = binding.givens_backward_ex(th, want_y.float(), g, reduction=binding.REDUCTION_GRAM)
+    assert rel(dx, want_dx) <= 1e-4 and rel(dth, want_dth) <= 1e-4
+
+
+@pytest.mark.parametrize("n,B", [(16, 5000), (50, 30000), (64, 3000)])
+def test_transposed_and_recorded(n, B):
+    th, x, g = problem(n, n - 1, B, n)
+    y, dx, dth = torch.empty_like(x), torch.empty_like(x), torch.empty_like(th)
+
+    def step():
+        binding.givens_forward(th, x, Y=y)
+        binding.givens_backward(th, y, g, dX=dx, dtheta=dth)
+
+    step()
+    assert rel(binding.givens_forward_transposed(th, y), x.double()) <= 3e-5
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        step()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for seed in range(3):                                          # replays on new values, eager work between them
+        new = problem(n, n - 1, B, 100 + seed)
+        for old, value in zip((th, x, g), new):
+            old.copy_(value)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (y, dx, dth)]
+        step()
+        assert all(torch.equal(a, b) for a, b in zip(got, (y, dx, dth)))
