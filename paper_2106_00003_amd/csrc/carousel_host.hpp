@@ -471,13 +471,20 @@ inline int wave64_fwd_width(int n, long long B)
 inline int wave64_fwd_strips(long long strips) { return strips > 512 ? kWave64Strips : 1; }
 // Columns per row of partial sums of the reverse sweep: those of a workgroup's strips.  Sweep and second stage measured in us,
 // one, two and four columns a strip: n = 512, B = 768 152 / 202 / 319, 1024 219 / 207 / 319, 4000 735 / 439 / 353, n = 256,
-// B = 1024 60 / 71 / 113, 4096 179 / 121 / 124, n = 64, B = 16384 146 / 103 / 89, n = 1024, B = 256 548 / 640, 1024 871 / 785; a
-// strip per workgroup and row: n = 512, B = 64 102 us against 122.
-inline int wave64_bwd_strips(long long B) { return B <= 128 ? 1 : kWave64Strips; }
+// B = 1024 60 / 71 / 113, 4096 179 / 121 / 124, n = 64, B = 16384 146 / 103 / 89, n = 1024, B = 256 548 / 640, 1024 871 / 785.
+// A strip per workgroup runs faster, but four times the rows of sums go through memory, past 256 MB not through its cache.
+// Backward calls in us, one strip and four per workgroup: n = 1024, B = 64 334 / 462, 96 442 / 468, 128 548 / 473; n = 768, B = 128
+// 277 / 353, 192 366 / 358; n = 528, B = 192 191 / 247, 256 223 / 249; n = 512, B = 192 124 / 131, 256 148 / 133; n = 384, B = 128
+// 87 / 99, 256 100 / 101; n = 256, B = 256 52.1 / 54.7.  With one slot four are as fast or faster: n = 128, B = 4 23.6 / 23.1, 128
+// 28.4 / 24.1, n = 64, B = 4 14.9 / 14.6, 128 17.8 / 15.6.
+inline int wave64_bwd_strips(int n, long long B)
+{
+    return wave64_slots(n) > 1 && B <= 256 && B * n <= 105000 ? 1 : kWave64Strips;
+}
 inline int wave64_bwd_width(int n, long long B)
 {
     const bool eight = wave64_slots(n) == 8;
-    return wave64_bwd_strips(B) * (B <= (eight ? 768 : 1024) ? 1 : B <= 2048 || eight ? 2 : 4);
+    return wave64_bwd_strips(n, B) * (B <= (eight ? 768 : 1024) ? 1 : B <= 2048 || eight ? 2 : 4);
 }
 int wave64_forward(int n, int rows, long long B, const double2 *table, const double *X, double *Y, int identity, int mirror,
                    hipStream_t stream);

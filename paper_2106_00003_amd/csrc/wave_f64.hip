@@ -64,7 +64,7 @@ int wave64_forward(int n, int rows, long long B, const double2 *table, const dou
 int wave64_backward(int n, int rows, long long B, long long group0, long long groups, const double2 *table, const double *Y,
                     const double *G, double *dX, double *partial, hipStream_t stream)
 {
-    const int M = wave64_slots(n), strips = wave64_bwd_strips(B), W = wave64_bwd_width(n, B) / strips;
+    const int M = wave64_slots(n), strips = wave64_bwd_strips(n, B), W = wave64_bwd_width(n, B) / strips;
     switch (M) {
     case 1: return backward_widths<1>(W, strips, n, rows, B, group0, groups, table, Y, G, dX, partial, stream);
     case 2: return backward_widths<2>(W, strips, n, rows, B, group0, groups, table, Y, G, dX, partial, stream);

@@ -101,6 +101,20 @@ def test_smallest_problems_in_one_kernel(n, m, B):
     assert torch.equal(dx, got[1]) and torch.equal(dth, got[2])
 
 
+# both sides of the batch up to which a strip has a row of sums of its own, and single slots, where none has: dX has the
+# same arithmetic, dtheta its sums in another order
+@pytest.mark.parametrize("n,B", [(1024, 102), (1024, 103), (768, 136), (768, 137), (512, 205), (512, 206), (264, 256), (264, 257),
+                                 (128, 1), (128, 6), (64, 127), (40, 3)])
+def test_strips_with_and_without_a_row_of_their_own(n, B):
+    data = inputs.make_restricted(n, n - 1, B, seed=4700 + n)
+    th, y, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
+    got = binding.givens_backward(th, y, g)
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = binding.givens_backward(th, y, g)
+    binding.set_kernel(binding.KERNEL_AUTO)
+    assert all(far(a, b) <= TOL for a, b in zip(got, want))
+
+
 @pytest.mark.parametrize("n,m,B", [(11, 4, 9), (129, 128, 30), (255, 20, 300), (511, 510, 40), (512, 7, 600)])
 def test_restricted_and_odd_sizes(n, m, B):
     data = inputs.make_restricted(n, m, B, seed=4400 + n)
