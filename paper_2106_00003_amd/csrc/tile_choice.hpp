@@ -125,4 +125,24 @@ inline GramPlan gram_plan(int rows, long long B, int compute_units, bool cplx = 
     return plan;
 }
 
+// Restricted tiled sweeps: whether a stage, P tiles in `runs` runs of `per` steps, launches only the `active` ones, which hold a
+// free pair.  The others return at once: while the chip holds them all they cost nothing, and a list of the rest was up to 8 % slower
+// there (fewer workgroups, on other XCDs, whose tile comes from a load).  Beyond that the list is faster where its workgroups
+// have a compute unit each, where they fill most of a second round and others would be in their way, where nearly all launched ones
+// are idle, and early where a tile's number is an XCD's, since the few that rotate are then on few XCDs.  Forward calls in us, all
+// tiles launched and listed: n = 2050, m = 41, B = 8 219 / 229, m = 256, B = 2000 385 / 403; n = 2561, m = 51, B = 64 262 / 271,
+// B = 4500 506 / 427; n = 3001, m = 375, B = 1000 539 / 458; n = 3250, m = 406, B = 4500 928 / 977; n = 4097, m = 512, B = 1000
+// 765 / 795, B = 4096 1389 / 1293.
+inline bool tile_apply_listed(int P, int compute_units, long long runs, long long per, int active)
+{
+    const long long all = runs * P, wanted = runs * active, units = compute_units;
+    if (P % 8 == 0) return 10 * all >= 9 * units && 3 * wanted <= 2 * all;
+    if (10 * all < 11 * units) return false;
+    const bool filled = per > 1 ? 3 * wanted >= 5 * units : 8 * wanted >= 15 * units;
+    return wanted <= units || (filled && 10 * all >= 13 * wanted) || 3 * all >= 20 * units;
+}
+// ... and one of the gradient: where there are more pairs of tiles than compute units (time of listed ones, all of them 1: n = 706 to
+// 1250 1.007, 1500 to 2561 1.001, 3001 to 6100 0.945).
+inline bool tile_pairs_listed(int P, int compute_units) { return P * (P + 1) / 2 > compute_units; }
+
 } // namespace givens

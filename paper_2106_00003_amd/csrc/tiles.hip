@@ -1,4 +1,5 @@
 // Launches of the tiled sweeps (tile_kernels.hpp).
+#include "tile_choice.hpp"
 #include "tile_kernels.hpp"
 
 #include <algorithm>
@@ -49,12 +50,13 @@ inline void tile_apply(const TilePlan &g, int compute_units, int rows, int free_
         const bool first = i == 0, last = i == g.stages - 1;
         TileList list{};
         list.active = g.P;
-        const bool listed = tile_restricted(g, free_rows) && !first && !last;   // (those two take every tile)
-        if (listed) list = tile_list(g, st, free_rows);
+        const bool idle = tile_restricted(g, free_rows) && !first && !last;   // (those two take every tile)
+        if (idle) list = tile_list(g, st, free_rows);
         TileApplyArgs a;
         const long long runs = tile_apply_stage(g, compute_units, 0, st, list.active, first, last, rows, free_rows, op, b, &a);
-        const dim3 grid((unsigned)(runs * list.active));
-        if (runs && listed)
+        const bool listed = idle && runs && tile_apply_listed(g.P, compute_units, runs, a.chunk / kTileCols, list.active);
+        const dim3 grid((unsigned)(runs * (listed ? list.active : g.P)));
+        if (listed)
             hipLaunchKernelGGL(tile_apply_kernel<TileList>, grid, dim3(2 * kTilePad), 0, stream, a, list);
         else if (runs)
             hipLaunchKernelGGL(tile_apply_kernel<TileAll>, grid, dim3(2 * kTilePad), 0, stream, a, TileAll{});
@@ -71,15 +73,16 @@ inline void tile_gradient(const TilePlan &g, int compute_units, int rows, int fr
     float *in = b.S, *out = second ? second : b.S;
     for (int st = 0; st < g.stages; ++st) {
         // (the narrow kernel leaves no pair out, since its result is another array, and the first and last stage of an operand no tile)
-        const bool first = st == 0, last = st == g.stages - 1, listed = tile_restricted(g, free_rows) && !narrow && !((first || last) && op.Y);
+        const bool first = st == 0, last = st == g.stages - 1, restricted = tile_restricted(g, free_rows);
+        const bool listed = restricted && !narrow && !((first || last) && op.Y) && tile_pairs_listed(g.P, compute_units);
         TileList list{};
         list.active = g.P;
-        if (listed) list = tile_list(g, st, free_rows);
-        const int c = list.active;
+        if (restricted) list = tile_list(g, st, free_rows);
+        const int active = first || last ? g.P : list.active, c = listed ? list.active : g.P;
         const unsigned pairs = (unsigned)(c * (c + 1) / 2 + c * (g.P - c)) * (narrow ? kTilePad / 32 : 1);
         TileStageArgs a{TileTwoSidedArgs{g, st, free_rows, pieces, in, out, b.blocks, b.range}, {}, pairs};
         long long runs = 0;
-        if (op.Y) runs = tile_apply_stage(g, compute_units, pairs, st, c, first, last, rows, free_rows, op, b, &a.a);
+        if (op.Y) runs = tile_apply_stage(g, compute_units, pairs, st, active, first, last, rows, free_rows, op, b, &a.a);
         const dim3 grid((unsigned)(pairs + runs * c)), block(2 * kTilePad);
         if (listed && c) {
             const auto kernel = runs ? tile_stage_kernel<false, true, TileList> : tile_stage_kernel<false, false, TileList>;

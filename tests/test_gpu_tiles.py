@@ -68,6 +68,12 @@ def test_restricted_and_odd_sizes(n, m, B):
     check(n, m, B, 3100 + n)
 
 
+# stages that launch the tiles with a free pair only, in both calls, in the forward call and in the gradient (tile_choice.hpp)
+@pytest.mark.parametrize("n,m,B", [(2901, 60, 300), (1001, 60, 1000), (2050, 41, 1000), (2901, 300, 40)])
+def test_restricted_stages_that_leave_tiles_out(n, m, B):
+    check(n, m, B, 3150)
+
+
 def test_more_pieces_than_the_narrow_stages_take():
     check(3100, 3099, 48, 3200)
 

@@ -24,6 +24,8 @@ void plan(int rows, long long B, int units, int cplx, int *slices, long long *co
     *slices = p.slices;
     *cols = p.cols;
 }
+int listed(int P, int units, long long runs, long long per, int active) { return tile_apply_listed(P, units, runs, per, active); }
+int pairs_listed(int P, int units) { return tile_pairs_listed(P, units); }
 }
 """
 
@@ -105,3 +107,20 @@ def test_the_slices_of_a_contraction_hold_its_columns_and_none_is_empty(choice, 
         choice.plan(n, ctypes.c_longlong(B), units, cplx, ctypes.byref(slices), ctypes.byref(cols))
         assert cols.value % 16 == 0 and (slices.value - 1) * cols.value < B <= slices.value * cols.value, (n, B)
         assert slices.value <= 256 and (cols.value <= 4096 or B > 4096 * 256 or slices.value * n * n * 4 > 2 ** 30)
+
+
+# Restricted tiled sweeps: calls with every tile of a stage launched and with those that hold a free pair, in us, by the tiles, runs
+# and steps of most of their stages.  Listed everywhere, the small ones were slower by up to 8 %.
+@pytest.mark.parametrize("P,runs,per,active,all_us,listed_us", [
+    (17, 1, 1, 2, 219, 229), (21, 1, 1, 2, 252, 267), (21, 2, 1, 2, 262, 271), (15, 14, 1, 4, 257, 265), (17, 63, 1, 6, 385, 403),
+    (26, 47, 3, 8, 928, 977), (33, 32, 1, 10, 765, 795), (21, 32, 1, 12, 486, 510), (7, 25, 1, 5, 139.5, 143.5),
+    (21, 141, 1, 2, 506, 427), (24, 32, 1, 8, 539, 458), (33, 43, 3, 10, 1389, 1293), (8, 63, 1, 2, 193, 164), (21, 22, 3, 10, 687, 663),
+    (33, 21, 3, 25, 1930, 1770), (49, 63, 1, 8, 1518, 1300)])
+def test_restricted_stages_are_listed_where_that_is_faster(choice, P, runs, per, active, all_us, listed_us):
+    assert choice.listed(P, 256, ctypes.c_longlong(runs), ctypes.c_longlong(per), active) == (listed_us < all_us)
+
+
+@pytest.mark.parametrize("P,all_us,listed_us", [(7, 417.5, 422.1), (8, 438.4, 443.6), (10, 671.7, 678.0), (14, 778, 785), (24, 1539, 1384),
+                                                (33, 3375, 3287)])
+def test_pairs_of_restricted_stages_are_listed_where_that_is_faster(choice, P, all_us, listed_us):
+    assert choice.pairs_listed(P, 256) == (listed_us < all_us)
