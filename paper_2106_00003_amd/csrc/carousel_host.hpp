@@ -472,14 +472,21 @@ inline int wave64_fwd_strips(long long strips) { return strips > 512 ? kWave64St
 // Columns per row of partial sums of the reverse sweep: those of a workgroup's strips.  Sweep and second stage measured in us,
 // one, two and four columns a strip: n = 512, B = 768 152 / 202 / 319, 1024 219 / 207 / 319, 4000 735 / 439 / 353, n = 256,
 // B = 1024 60 / 71 / 113, 4096 179 / 121 / 124, n = 64, B = 16384 146 / 103 / 89, n = 1024, B = 256 548 / 640, 1024 871 / 785.
-// A strip per workgroup runs faster, but four times the rows of sums go through memory, past 256 MB not through its cache.
-// Backward calls in us, one strip and four per workgroup: n = 1024, B = 64 334 / 462, 96 442 / 468, 128 548 / 473; n = 768, B = 128
-// 277 / 353, 192 366 / 358; n = 528, B = 192 191 / 247, 256 223 / 249; n = 512, B = 192 124 / 131, 256 148 / 133; n = 384, B = 128
-// 87 / 99, 256 100 / 101; n = 256, B = 256 52.1 / 54.7.  With one slot four are as fast or faster: n = 128, B = 4 23.6 / 23.1, 128
-// 28.4 / 24.1, n = 64, B = 4 14.9 / 14.6, 128 17.8 / 15.6.
+// A strip per workgroup runs faster, but four times the rows of sums, 4 n^2 bytes each, go through memory.  With one slot four
+// strips are as fast or faster (n = 128, B = 4 23.6 / 23.1, 128 28.4 / 24.1, n = 64, B = 4 14.9 / 14.6, 128 17.8 / 15.6); beyond 256 columns a
+// strip has no compute unit to itself.  In between, a measured line of bytes for every number of slots.  Backward calls in us, one
+// strip and four per workgroup: two slots n = 140, B = 128 31.1 / 30.8, 192 33.5 / 31.7; n = 172, B = 192 38.7 / 37.8; n = 188, B = 256 41.7 /
+// 42.3; n = 252, B = 256 53.1 / 55.4; four slots n = 384, B = 256 99 / 102; n = 480, B = 224 121 / 124; n = 512, B = 192 124 / 132, 224 130 /
+// 133, 256 154 / 134; eight slots n = 528, B = 256 224 / 251, 272 277 / 251; n = 608, B = 224 270 / 285, 256 300 / 288; n = 704, B = 160
+// 299 / 329, 176 332 / 328; n = 768, B = 160 335 / 357, 192 379 / 360; n = 832, B = 128 351 / 384, 160 420 / 388; n = 896, B = 128
+// 400 / 417; n = 960, B = 96 431 / 439, 112 469 / 439; n = 1024, B = 96 456 / 468, 112 511 / 470.
 inline int wave64_bwd_strips(int n, long long B)
 {
-    return wave64_slots(n) > 1 && B <= 256 && B * n <= 105000 ? 1 : kWave64Strips;
+    const int slots = wave64_slots(n);
+    if (slots == 1 || B > 256) return kWave64Strips;
+    if (slots == 2) return B <= 128 || n > 176 ? 1 : kWave64Strips;
+    const double most = slots == 4 ? 230.0e6 : n <= 704 ? 335.0e6 : 412.0e6;
+    return 4.0 * n * n * (double)B <= most ? 1 : kWave64Strips;
 }
 inline int wave64_bwd_width(int n, long long B)
 {

@@ -104,7 +104,8 @@ def test_smallest_problems_in_one_kernel(n, m, B):
 # both sides of the batch up to which a strip has a row of sums of its own, and single slots, where none has: dX has the
 # same arithmetic, dtheta its sums in another order
 @pytest.mark.parametrize("n,B", [(1024, 102), (1024, 103), (768, 136), (768, 137), (512, 205), (512, 206), (264, 256), (264, 257),
-                                 (128, 1), (128, 6), (64, 127), (40, 3)])
+                                 (128, 1), (128, 6), (64, 127), (40, 3), (1024, 98), (1024, 99), (768, 174), (768, 175), (704, 168),
+                                 (704, 169), (512, 219), (512, 220), (176, 128), (176, 129), (180, 256), (180, 257)])
 def test_strips_with_and_without_a_row_of_their_own(n, B):
     data = inputs.make_restricted(n, n - 1, B, seed=4700 + n)
     th, y, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
