@@ -27,8 +27,8 @@ RR_HD inline int rr_label(int n, int k, int q)
     return 1 + v;
 }
 
-// Place of arc p in a row of the coefficient table for the one-wavefront sweeps of `lanes` lanes with 1 << shift slots each (2 or
-// more): two slots (16 bytes in float32) of every lane, then the next two.  A load of a wavefront is then consecutive memory; with a
+// Place of arc p in a row of the coefficient table for sweeps of `lanes` lanes (of all of a strip's wavefronts) with 1 << shift slots
+// each (2 or more): two slots (16 bytes in float32) of every lane, then the next two.  A load of a wavefront is then consecutive memory; with a
 // lane's slots side by side each load of eight-slot lanes touches 64 lines, and several wavefronts of a compute unit have
 // no use of its L1.
 RR_HD inline int turned_place(int p, int shift, int lanes)

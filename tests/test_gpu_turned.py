@@ -23,9 +23,9 @@ def rel(got, want):
     return float((got - want).norm() / want.norm())
 
 
-# one wavefront per strip (528: 33 lanes, 1024: all), then strips of 2, 3 and 8 wavefronts
+# one wavefront per strip (528: 33 lanes, 1024: all), then strips of 2, 3 and 8 wavefronts (test_launch_choice.py: which are turned)
 @pytest.mark.parametrize("n,B", [(528, 512), (528, 513), (528, 768), (528, 771), (1024, 1021), (1024, 1024), (1024, 1025),
-                                 (1024, 1537), (768, 1535), (1008, 2007), (1040, 1041), (1536, 30), (3072, 257), (4096, 131)])
+                                 (1024, 1537), (768, 1535), (1008, 2007), (1040, 1041), (1040, 1561), (1536, 30), (3072, 257), (4096, 131)])
 @pytest.mark.parametrize("form,scale", [(binding.FORM_STANDARD, 2.0), (binding.FORM_RANGE, 2.0), (binding.FORM_RANGE, 0.1)])
 def test_forward(n, B, form, scale):
     binding.set_rotation_form(form)

@@ -13,6 +13,7 @@ SOURCE = """
 using namespace givens;
 extern "C" {
 int wave64_strips(int n, long long B) { return wave64_bwd_strips(n, B); }
+int turned(int n, long long B) { return carousel_turned(n, B); }
 }
 """
 
@@ -41,3 +42,25 @@ def choice(tmp_path_factory):
     (1024, 64, 334.0, 462.0), (1024, 128, 552.7, 475.6), (128, 128, 28.4, 24.1), (64, 4, 14.9, 14.6)])
 def test_float64_rows_of_sums(choice, n, B, one, four):
     assert {1: one, 4: four}[choice.wave64_strips(n, ctypes.c_longlong(B))] <= 1.03 * min(one, four)
+
+
+# Forward sweeps with eight slots per lane in us, with the table in the order of the angles and turned; strips of one wavefront, then of
+# several, of which n = 1040 to 1232 with two columns and up to three strips per compute unit are up to 6 % slower turned.
+@pytest.mark.parametrize("n,B,plain,turned", [
+    (528, 512, 62.8, 63.5), (528, 513, 90.1, 64.3), (640, 768, 125.1, 80.8), (768, 1024, 141.2, 105.3), (768, 1025, 142.0, 145.6),
+    (896, 1536, 164.7, 174.8), (896, 1537, 202.0, 173.2), (1024, 2040, 261.3, 198.6), (1024, 400, 127.4, 126.8),
+    (1040, 1, 237.2, 230.5), (1040, 640, 281.7, 235.5), (1040, 1200, 291.6, 306.8), (1040, 1536, 298.2, 309.8), (1040, 1560, 375.1, 314.1),
+    (1072, 1400, 299.6, 316.6), (1104, 1100, 306.3, 324.6), (1104, 1536, 318.7, 327.5), (1104, 1700, 446.6, 359.2),
+    (1168, 1400, 333.5, 346.3), (1168, 1536, 383.5, 368.1), (1232, 1200, 356.1, 364.2), (1232, 1400, 402.0, 385.8),
+    (1264, 1025, 361.3, 343.1), (1264, 1200, 366.3, 370.7), (1264, 1300, 413.9, 395.2), (1328, 1200, 435.8, 410.8), (1536, 1200, 512.1, 468.0),
+    (2048, 1, 499.4, 457.4), (2048, 1976, 995.1, 682.0), (3072, 64, 790.8, 722.4), (4096, 512, 1387.2, 1242.3)])
+def test_turned_tables(choice, n, B, plain, turned):
+    assert (turned if choice.turned(n, ctypes.c_longlong(B)) else plain) <= 1.015 * min(plain, turned)
+
+
+# which of the sizes of tests/test_gpu_turned.py are turned, on both sides of every line
+@pytest.mark.parametrize("n,B,expected", [(528, 512, 0), (528, 513, 1), (528, 768, 1), (528, 771, 1), (1024, 1021, 1), (1024, 1024, 1),
+                                          (1024, 1025, 0), (1024, 1537, 1), (768, 1535, 0), (1008, 2007, 1), (1040, 1041, 0),
+                                          (1040, 1561, 1), (1536, 30, 1), (3072, 257, 1), (4096, 131, 1)])
+def test_sizes_that_are_turned(choice, n, B, expected):
+    assert choice.turned(n, ctypes.c_longlong(B)) == expected
