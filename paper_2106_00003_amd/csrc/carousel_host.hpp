@@ -198,17 +198,23 @@ int carousel_backward_chain(const CarouselBwdArgs &a, const CarouselChainArgs &c
 constexpr int kUnitaryCarouselMinN = 128;
 inline bool unitary_carousel_supported(int n) { return n >= kUnitaryCarouselMinN && n <= 4096 && n % 16 == 0; }
 
-// Floats per lane of the forward sweep.  With several wavefronts as carousel_width has it, whole complex numbers.  Strips of one
-// wavefront, four of which are a workgroup: at most one per SIMD with two floats, two with four.  Phase passes, tables and sweep in us
-// with 2, 4 and 8 floats: n = 512, B = 1024 164 / 222 / 383, 1500 266 / 224 / 382, n = 1024, B = 1024 312 / 428 / 750, 1500 528 / 431 /
-// 756, 4000 1038 / 620 / 753 (a strip per workgroup, tables in the order of the angles, as carousel_width has it: n = 1024,
-// B = 16 302 (295), 1024 506, 1500 746, 4000 1085).
+// Floats per lane of the forward sweep: with several wavefronts as carousel_width has it, whole complex numbers; strips of one wavefront
+// two or four.  Strips per workgroup of the latter: four find their rows of the tables in one L1, but fill the chip in steps of 1024.
+// Phase passes, tables and sweep in us, two floats with one strip per workgroup and four, four floats with one and four:
+// n = 144, B = 16 54.8 / 58.0, 73.3 / 73.4, 512 57.6 / 58.3, 73.3 / 74.1, 1024 60.8 / 59.4, 75.6 / 73.6, 1030 68.0 / 94.0, 75.3 / 74.7, 1500
+// 78.5 / 94.6, 76.3 / 75.1, 2060 114 / 130, 87.6 / 94.1, 3000 142 / 133, 90.6 / 96.5, 3600 163 / 168, 121 / 99.2; n = 512, B = 1024
+// 170 / 167, 224 / 215, 1200 185 / 265, 223 / 215, 2060 340 / 383, 259 / 258, 3600 487 / 501, 292 / 279; n = 1024, B = 16 286 / 300,
+// 412 / 414, 512 304 / 305, 416 / 419, 900 324 / 317, 431 / 424, 1030 357 / 565, 444 / 420.  (Strips of one workgroup each, tables in
+// the order of the angles, width as carousel_width has it: n = 144, B = 16 56.6, 1030 72.3, 2060 85.4, 3600 121; n = 512, B = 1024 208,
+// 2060 257, 3600 384; n = 1024, B = 16 308, 900 504, 1030 652.  Eight floats are slower throughout: n = 1024, B = 4090 743 / 646.)
 inline int unitary_fwd_width(long long Breal, int waves)
 {
-    if (waves == 1) return Breal <= 2048 ? 2 : Breal <= 8192 ? 4 : 8;
+    if (waves == 1) return Breal <= 2560 ? 2 : 4;
     const int W = carousel_width(Breal, waves);
     return W < 2 ? 2 : W;
 }
+constexpr int kTurnedStrips = 4;
+inline int unitary_fwd_strips(long long strips) { return strips <= 512 || (strips > 1024 && strips <= 1536) ? 1 : kTurnedStrips; }
 struct UnitaryCarouselFwdArgs {
     int n;
     long long Breal;
@@ -317,7 +323,7 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 // 1322 / 1198.  Not those of two columns and two wavefronts, the second of them short, while up to three have a compute unit: n = 1040,
 // B = 1200 292 / 307, 1536 298 / 310, 1560 375 / 314, n = 1168, B = 1400 333 / 346, 1536 383 / 368, n = 1264, B = 1025 361 / 343, 1200 366 / 371,
 // 1400 414 / 393, n = 1328, B = 1100 390 / 392, 1200 436 / 411.  Wider ones have enough arithmetic per row (n = B = 2048 730 / 784).
-constexpr int kTurnedSlots = 8, kTurnedStrips = 4;
+constexpr int kTurnedSlots = 8;
 constexpr long long kTurnedSingleB = 1024;
 inline int turned_strips(long long B) { return B <= 768 ? 1 : kTurnedStrips; }
 inline bool carousel_turned(int n, long long B)

@@ -86,30 +86,42 @@ __device__ __forceinline__ void unitary_load_row(float (&dst)[W], const float *X
 // ---------------------------------------------------------------------------------------------
 // forward sweep: the structure of CarouselFwd (carousel_kernels.hpp) with two coefficient pairs per slot
 // ---------------------------------------------------------------------------------------------
+constexpr int kBufferWords = 0x00027000;   // a buffer descriptor's last word: raw 32-bit data
 template <int M, int W, int WAVES>
 struct UnitaryCarouselFwd {
     static_assert(W % 2 == 0, "a lane holds whole complex numbers");
     static constexpr int kLastU = (2 * M - 2) % M;
+    typedef unsigned Words __attribute__((ext_vector_type(4)));
     static constexpr bool kTurned = WAVES == 1;   // strips of one wavefront: tables in the order of turned_place, workgroups of several strips
 
     float top[M][W];
     float bot[M][W];
     float2 rot[2][M], phs[2][M];
     int n, H, lane, wave, tid;
-    const float2 *rot_lane, *phs_lane; // tables + tid*M (turned: + 2 tid)
-    int lanes;
+    const float2 *rot_lane, *phs_lane; // tables + tid*M (not turned)
+    __amdgpu_buffer_rsrc_t rot_rows, phs_rows;   // tables (turned)
+    int lanes, lane_bytes;             // lanes that hold slots, offset of this one's 16 bytes
     float *out_top, *out_bot, *turn;
     const float *in_top, *in_bot;
     static constexpr int kBufFloats = (int)(sizeof(typename CarouselExchange<W, WAVES>::Buf) / sizeof(float));
 
-    __device__ __forceinline__ void load_pairs(const float2 *base, int k, float2 (&dst)[M])
+    // A turned row's 16 bytes per lane lie a row of lanes apart, which no load's constant offset reaches: by way of a buffer all but the
+    // lane's own offset is scalar.  With eight 64-bit additions per block instead the sweep of n = 144, B = 16 took 3 us of 57 more.
+    __device__ __forceinline__ void load_pairs(const float2 *base, __amdgpu_buffer_rsrc_t rows, int k, float2 (&dst)[M])
     {
         const float2 *src = base + (long long)k * H;
-        if constexpr (M % 2 == 0) {
+        if constexpr (kTurned) {
+#pragma unroll
+            for (int r = 0; r < M / 2; ++r) {
+                const Words v = __builtin_amdgcn_raw_buffer_load_b128(rows, lane_bytes, (k * H + 2 * r * lanes) * (int)sizeof(float2), 0);
+                dst[2 * r] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+                dst[2 * r + 1] = make_float2(__uint_as_float(v.z), __uint_as_float(v.w));
+            }
+        } else if constexpr (M % 2 == 0) {
             const float4 *s4 = reinterpret_cast<const float4 *>(src);
 #pragma unroll
             for (int r = 0; r < M / 2; ++r) {
-                const float4 v = s4[kTurned ? r * lanes : r];
+                const float4 v = s4[r];
                 dst[2 * r] = make_float2(v.x, v.y);
                 dst[2 * r + 1] = make_float2(v.z, v.w);
             }
@@ -120,8 +132,8 @@ struct UnitaryCarouselFwd {
     }
     __device__ __forceinline__ void load_coefs(int k, int buf)
     {
-        load_pairs(rot_lane, k, rot[buf]);
-        load_pairs(phs_lane, k, phs[buf]);
+        load_pairs(rot_lane, rot_rows, k, rot[buf]);
+        load_pairs(phs_lane, phs_rows, k, phs[buf]);
     }
 
     // logical slot R under the register map of unrolled copy U: phase turn of the top row, then the rotation
@@ -235,8 +247,14 @@ __global__ __launch_bounds__(64 * (WAVES == 1 ? kTurnedStrips : WAVES), 2) void 
     st.tid = tid;
     st.lane = threadIdx.x & 63;
     st.wave = kTurned ? 0 : wave;
-    st.rot_lane = rot + coef_lane * (kTurned ? 2 : M);
-    st.phs_lane = phs + coef_lane * (kTurned ? 2 : M);
+    st.rot_lane = rot + coef_lane * M;
+    st.phs_lane = phs + coef_lane * M;
+    if constexpr (kTurned) {
+        const int bytes = (n - 1) * (n >> 1) * (int)sizeof(float2);
+        st.rot_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(rot), 0, bytes, kBufferWords);
+        st.phs_rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2 *>(phs), 0, bytes, kBufferWords);
+        st.lane_bytes = 16 * coef_lane;
+    }
     {
         constexpr int LMAX = 64 * WAVES;
         auto &b = exchange[strip].buf[0];
@@ -570,7 +588,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void unitary_carousel_backward_kerne
 template <int M, int W, int WAVES>
 inline void unitary_carousel_launch_fwd(const UnitaryCarouselFwdArgs &a)
 {
-    constexpr int strips = WAVES == 1 ? kTurnedStrips : 1;
+    const int strips = WAVES == 1 ? unitary_fwd_strips((a.Breal + W - 1) / W) : 1;
     const long long columns = W * strips, groups = (a.Breal + columns - 1) / columns;
     hipLaunchKernelGGL((unitary_carousel_forward_kernel<M, W, WAVES>), dim3((unsigned)groups), dim3(64 * WAVES * strips), 0,
                        a.stream, a.n, a.Breal, a.rot, a.phs, a.fin, a.X, a.Y, a.identity, a.vec_ok);
@@ -578,8 +596,12 @@ inline void unitary_carousel_launch_fwd(const UnitaryCarouselFwdArgs &a)
 template <int M, int WAVES>
 inline int unitary_carousel_fwd_widths(int W, const UnitaryCarouselFwdArgs &a)
 {
+    if constexpr (WAVES > 1)
+        if (W == 8) {
+            unitary_carousel_launch_fwd<M, 8, WAVES>(a);
+            return GIVENS_OK;
+        }
     switch (W) {
-    case 8: unitary_carousel_launch_fwd<M, 8, WAVES>(a); return GIVENS_OK;
     case 4: unitary_carousel_launch_fwd<M, 4, WAVES>(a); return GIVENS_OK;
     case 2: unitary_carousel_launch_fwd<M, 2, WAVES>(a); return GIVENS_OK;
     default: return GIVENS_ERR_UNSUPPORTED;

@@ -52,9 +52,10 @@ def test_build(n, B):
     assert rel(u.double(), binding.givens_build(th.double(), n)) <= 1e-5
 
 
-# strips of 2, 4 and 8 floats, four of them per workgroup
+# strips of 2 and 4 floats, one and four of them per workgroup (both sides of each line), and of two wavefronts
 @pytest.mark.parametrize("n,B", [(128, 1), (144, 5), (512, 1023), (1024, 9), (1024, 1024), (1024, 1025), (640, 2047), (1024, 4090),
-                                 (1024, 4097), (1040, 33)])
+                                 (1024, 4097), (1040, 33), (128, 511), (272, 512), (272, 513), (336, 1280), (336, 1281), (512, 2048),
+                                 (528, 2049), (784, 3072), (784, 3073)])
 def test_unitary_forward(n, B):
     gen = torch.Generator(device="cuda").manual_seed(n + B)
     th, ph = ((torch.rand(n * (n - 1) // 2, device="cuda", generator=gen) * 2 - 1) * 3 for _ in range(2))

@@ -13,6 +13,8 @@ SOURCE = """
 using namespace givens;
 extern "C" {
 int wave64_strips(int n, long long B) { return wave64_bwd_strips(n, B); }
+int unitary_width(long long B) { return unitary_fwd_width(2 * B, 1); }
+int unitary_strips(long long B) { const int w = unitary_fwd_width(2 * B, 1); return unitary_fwd_strips((2 * B + w - 1) / w); }
 int turned(int n, long long B) { return carousel_turned(n, B); }
 }
 """
@@ -64,3 +66,20 @@ def test_turned_tables(choice, n, B, plain, turned):
                                           (1040, 1561, 1), (1536, 30, 1), (3072, 257, 1), (4096, 131, 1)])
 def test_sizes_that_are_turned(choice, n, B, expected):
     assert choice.turned(n, ctypes.c_longlong(B)) == expected
+
+
+# Unitary forward calls in us: strips of two floats, one and four per workgroup, and of four floats; and as they were before tables
+# were turned (a strip per workgroup), which some calls of few columns and some just above 1024 and 2048 were slower than.
+@pytest.mark.parametrize("n,B,two_1,two_4,four_1,four_4,plain", [
+    (128, 16, 49.0, 51.1, 66.7, 66.6, 50.4), (144, 16, 54.8, 58.0, 73.3, 73.4, 56.6), (144, 400, 56.8, 58.2, 73.8, 74.7, 58.2),
+    (144, 1024, 60.8, 59.4, 75.6, 73.6, 64.0), (144, 1030, 68.0, 94.0, 75.3, 74.7, 72.3), (144, 1200, 68.7, 95.2, 76.0, 74.4, 73.4),
+    (144, 1500, 78.5, 94.6, 76.3, 75.1, 83.6), (144, 2060, 114.1, 130.2, 87.6, 94.1, 85.4), (144, 3600, 162.9, 167.9, 120.7, 99.2, 121.4),
+    (336, 128, 105.5, 108.1, 147.0, 147.1, 106.6), (336, 1200, 129.0, 179.3, 152.3, 146.7, 158.4),
+    (336, 2400, 240.3, 257.0, 181.3, 180.5, 175.7), (336, 4090, 339.4, 336.6, 255.0, 193.0, 273.2),
+    (512, 1024, 170.2, 167.3, 223.7, 215.4, 208.2), (512, 2060, 340.2, 383.1, 259.0, 257.7, 256.9),
+    (640, 256, 204.9, 199.8, 265.6, 268.7, 202.3), (784, 2400, 585.8, 647.1, 405.3, 443.6, 447.7),
+    (896, 1800, 622.1, 482.2, 445.5, 379.6, 858.4), (1024, 16, 285.6, 300.0, 411.7, 414.4, 308.4), (1024, 900, 323.5, 317.1, 431.1, 423.6, 504.1)])
+def test_unitary_strips(choice, n, B, two_1, two_4, four_1, four_4, plain):
+    wide = ctypes.c_longlong(B)
+    us = {(2, 1): two_1, (2, 4): two_4, (4, 1): four_1, (4, 4): four_4}[choice.unitary_width(wide), choice.unitary_strips(wide)]
+    assert us <= 1.035 * min(two_1, two_4, four_1, four_4, plain)
