@@ -149,10 +149,10 @@ int givens_forward_transposed_f64(int n, int64_t B, const double *theta, const d
 
 /*
  * givens_forward_noalloc -- givens_forward for callers that cannot allocate device memory: code under
- * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels
- * and bit-identical results, but the coefficient tables (cos/sin or scaled / lifted coefficients, row
- * factors, renormalisation rows, the range-check flag; or the tiles' matrices) and what a wide batch needs
- * (U, and a copy of some columns when Y is X) are written to a static device array of
+ * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and bit-identical results
+ * (by the same kernels, except for n <= 64 where the plain call multiplies and has fewer launches), but the
+ * coefficient tables (cos/sin or scaled / lifted coefficients, row factors, renormalisation rows, the range-check
+ * flag; or the tiles' matrices) and what a wide batch needs (U, and a copy of some columns when Y is X) are written to a static device array of
  * GIVENS_NOALLOC_BYTES bytes inside the library instead of the hipMalloc'ed workspace, so the call makes
  * no hipMalloc, hipFree or other allocating call.  Every GPU the library runs on holds that array until
  * the process ends.
@@ -368,7 +368,8 @@ int givens_last_rotation_form(void);
  * capped at 24 GiB per chunk, and gives bit-identical dtheta from run to run.  GRAM replaces the sweep
  * over B columns by the Gram matrix C = Y G^T (the sums of the sweep are those of the same sweep on the
  * operand C with upstream gradient I_n), contracted over B on the matrix cores in float32 precision and in a
- * fixed order (reproducible as well), and computes dX = U^T G by a product with what the sweep leaves of I_n.
+ * fixed order (reproducible as well), and computes dX = U^T G by a product with what the sweep leaves of I_n, which is U^T
+ * (for n from 16 to 64 with dX in memory of its own U^T is made beside the contraction instead, of the same bits).
  * AUTO means GRAM for every float kernel family when B >= 2 n and wherever the call runs as tiles
  * (GIVENS_KERNEL_TILES, also below 2 n), TWO_STAGE otherwise; for givens_unitary_backward GRAM (C = Y G^H) when
  * B >= 4 n and B >= 1024, TWO_STAGE otherwise; the f64 entry points always use TWO_STAGE.
@@ -393,7 +394,10 @@ int givens_last_chains(void);
  * slice sum (ms[2], ms[3]: 0 for forward/build).  A call that ran as tiles (GIVENS_KERNEL_TILES): ms[0] = the tiles'
  * matrices, ms[1] = forward their application, and the product of a wide batch (backward: only that), ms[2] = backward
  * the slice sum, the stages that take Y G^T and what dX comes from along together, and the angles' sums, ms[3] = the
- * contraction alone.  Returns GIVENS_ERR_UNSUPPORTED if timing was off for that call.
+ * contraction alone.  A float call with n from 16 to 64 that multiplies: forward ms[0] = U with its table, cut for the product,
+ * ms[1] = the product; backward, with dX in memory of its own, ms[0] = 0, ms[3] = the contraction with the table and U^T
+ * beside it, and its slice sum, ms[1] = the product with dtheta's sweep beside it, ms[2] = the second stage.
+ * Returns GIVENS_ERR_UNSUPPORTED if timing was off for that call.
  */
 int givens_set_timing(int on);
 int givens_last_timing(float ms[4]);

@@ -200,6 +200,19 @@ __global__ void scaled_scan_kernel(int n, const float *__restrict__ theta, const
     renorm[2 * ((long long)g * H + p) + (q < H ? 0 : 1)] = (float)d;
 }
 
+// The standard form's entry for an angle: (cos, sin) with the orientation folded into the sine.  Every kernel that makes such entries calls
+// this, so that all entry points rotate by the same bits.
+template <typename T>
+__device__ __forceinline__ typename Pair2<T>::type standard_entry(double th, double orient)
+{
+    double s, c;
+    sincos(th, &s, &c);
+    typename Pair2<T>::type out;
+    out.x = (T)c;
+    out.y = (T)(orient * s);
+    return out;
+}
+
 // Step 2, and the only step of the standard form: the table of one sweep direction in E order, in the form
 // the flag selects (flag == nullptr: standard).
 //   standard: (cos, sin) with the orientation folded into the sine; `factor` (reverse sweep only) receives the
@@ -229,10 +242,7 @@ __global__ void coef_table_kernel(int n, const T *__restrict__ theta, const int 
         typename Pair2<T>::type out;
         double fac = orient;
         if (form == kFormStandard) {
-            double s, c;
-            sincos(th, &s, &c);
-            out.x = (T)c;
-            out.y = (T)(orient * s);
+            out = standard_entry<T>(th, orient);
         } else {
             const double da = (double)D[(long long)k * n + p], db = (double)D[(long long)k * n + (n - 1 - p)]; // before this block
             fac = orient * da * db;

@@ -5,16 +5,19 @@
 // the split of its result took 11 us more in a forward call and, with the sums, 23 in a backward one, eight launches of 3 to 8
 // us that leave the chip empty.  Here a workgroup makes the coefficients in LDS, sweeps eight columns of the identity and cuts
 // them into pieces, as a kernel of its own in the forward call and beside the contraction in the backward one, whose own sweep
-// runs beside the product.  n = 64, B = 65536, both calls: 48.5 us, 60.7 with a launch for each part.
+// runs beside the product.  n = 64, B = 65536, both calls: 48.5 us, 60.7 with a launch for each part.  Entries of the table and the
+// arithmetic of a column and of a sum are those of the kernels that this stands for: the calls that keep them (prepared, not
+// allocating, dX not wanted or in the place of G) give the same bits.
 #pragma once
 #include "carousel_kernels.hpp"
 #include "coef_kernels.hpp"
 #include "gram_kernels.hpp"
 #include "product_kernels.hpp"
-#include "small_trig.hpp"
 
 namespace givens {
 
+// The contraction's result and a column block of the product are one tile of 64 x 64 each, and the table takes 16 KB of LDS beside the
+// contraction's 26; at n = 128 it would be four tiles and 65 KB, which leaves one workgroup per compute unit (not tried).
 constexpr int kWideSmallMaxN = 64;
 constexpr int kWideSmallCols = 8;      // of a workgroup: four wavefronts of two, an octet of the split matrix
 
@@ -32,8 +35,7 @@ __device__ __forceinline__ float2 small_coefs(const SmallMatrixArgs &a, int mirr
 {
     const int H = a.n >> 1, k = e / H, p = e - k * H;
     *orient = rr_label(a.n, k, p) < rr_label(a.n, k, a.n - 1 - p) ? 1.f : -1.f;
-    const double2 cs = tile_sincos((double)theta_at(a.theta, a.map, mirror, a.n, (long long)e));
-    return make_float2((float)cs.x, *orient * (float)cs.y);
+    return standard_entry<float>((double)theta_at(a.theta, a.map, mirror, a.n, (long long)e), *orient);
 }
 // Columns 8 block + 2 wave and the next one into `cols`.
 typedef float SmallColumns[kWideSmallMaxN][kWideSmallCols + 1];

@@ -55,6 +55,25 @@ def test_batches_and_restricted(n, m, B):
     check(n, m, B)
 
 
+# calls that take the kernels of the other sizes: without allocations, on prepared tables, dX in the place of G, no dX
+@pytest.mark.parametrize("n,m,B", [(n, n - 1, B) for n in range(16, 65) for B in (2 * n + 2, 2048 + 11 * n)] +
+                         [(64, 20, 700), (63, 5, 4000), (33, 8, 30000), (48, 47, 24577)])
+def test_every_way_to_a_result_gives_the_same_bits(n, m, B):
+    th, x, g = problem(n, m, B, 7 * n + B)
+    y = binding.givens_forward_restricted(th, x, m)
+    dx, dth = binding.givens_backward_restricted(th, y, g, m)
+    token = binding.givens_prepare(th, n, m, binding.PREPARE_FORWARD | binding.PREPARE_BACKWARD_WIDE, batch=B)
+    assert torch.equal(binding.givens_forward_prepared(token, x), y)
+    pdx, pdth = binding.givens_backward_prepared(token, y, g, th.numel())
+    assert torch.equal(pdx, dx) and torch.equal(pdth, dth)
+    buf = g.clone()
+    idx, idth = binding.givens_backward_restricted(th, y, buf, m, dX=buf)
+    assert torch.equal(idx, dx) and torch.equal(idth, dth)
+    assert torch.equal(binding.givens_backward_restricted(th, y, g, m, want_dx=False)[1], dth)
+    if n % 2 == 0 and m == n - 1:
+        assert torch.equal(binding.givens_forward_noalloc(th, x, torch.empty_like(x)), y)
+
+
 def test_gram_form_chosen_for_a_narrow_batch():
     th, x, g = problem(40, 39, 7, 5)
     want_y = binding.givens_forward(th.double(), x.double())
