@@ -2108,8 +2108,14 @@ int givens_prepare_pays(int n, int m, int64_t B)
     Families fam;
     if (opt.kernel == GIVENS_KERNEL_TILES) return 0;
     if (pick_forward_family<float>(padded, B, opt.kernel, &fam)) return 1;   // (the calls themselves will say so)
-    return wants_tiles(opt, padded, swept_columns<float>(fam, n, B), false) ||
-           wants_tiles(opt, padded, wants_gram<float>(padded, B, opt.reduction) ? n : B, true) ? 0 : 1;
+    const bool gram = wants_gram<float>(padded, B, opt.reduction);
+    const long long swept = swept_columns<float>(fam, n, B);
+    if (wants_tiles(opt, padded, swept, false) || wants_tiles(opt, padded, gram ? n : B, true)) return 0;
+    // plain calls with kernels of their own, or a table in the order of the lanes.  Autograd, both calls in us, prepared and plain:
+    // n = 48, B = 512 65 / 56, n = 64, B = 2048 72 / 57; n = 528, B = 64 (not turned) 246 / 245, 520 318 / 290, n = 768, B = 2100
+    // 707 / 666, n = 2048, B = 512 2077 / 2049, n = 3072, B = 512 3689 / 3390.
+    if (gram && wide_small(fam, padded)) return 0;
+    return forward_slots<float>(fam, padded, swept) ? 0 : 1;
 }
 
 int64_t givens_packed_bytes(int n)

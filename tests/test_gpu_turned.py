@@ -67,3 +67,20 @@ def test_unitary_forward(n, B):
         assert torch.equal(binding.givens_unitary_forward(th, ph, last), y[:, -min(B, 3):])
     few = x[:, -min(B, 70):].to(torch.complex128).contiguous()
     assert rel(y[:, -min(B, 70):].to(torch.complex128), binding.givens_unitary_forward(th.double(), ph.double(), few)) <= 1e-5
+
+
+# through autograd: sizes whose plain calls are turned take those
+@pytest.mark.parametrize("n,B", [(528, 520), (528, 64), (768, 1600)])
+def test_autograd(n, B):
+    from paper_2106_00003_amd import layer
+    gen = torch.Generator(device="cuda").manual_seed(n * B)
+    th = ((torch.rand(n * (n - 1) // 2, device="cuda", generator=gen) * 2 - 1) * 3).requires_grad_(True)
+    x, g = torch.randn(n, B, device="cuda", generator=gen).requires_grad_(True), torch.randn(n, B, device="cuda", generator=gen)
+    with torch.no_grad():
+        y = binding.givens_forward(th.detach(), x.detach())
+        dx, dth = binding.givens_backward(th.detach(), y, g)
+    before = binding.givens_prepare(th.detach(), n)
+    out = layer.givens_apply(th, x)
+    out.backward(g)
+    assert binding.givens_prepare(th.detach(), n) == before + (1 if B > 512 else 2)
+    assert torch.equal(out.detach(), y) and torch.equal(x.grad, dx) and torch.equal(th.grad, dth)

@@ -109,3 +109,18 @@ def test_transposed_and_recorded(n, B):
         got = [t.clone() for t in (y, dx, dth)]
         step()
         assert all(torch.equal(a, b) for a, b in zip(got, (y, dx, dth)))
+
+
+# through autograd: the plain calls, which are the faster ones here
+@pytest.mark.parametrize("n,m,B", [(40, None, 3000), (64, None, 130), (33, 8, 2500)])
+def test_autograd_takes_the_plain_calls(n, m, B):
+    from paper_2106_00003_amd import layer
+    th, x, g = problem(n, n - 1 if m is None else m, B, n + B)
+    y = binding.givens_forward_restricted(th, x, n - 1 if m is None else m)
+    dx, dth = binding.givens_backward_restricted(th, y, g, n - 1 if m is None else m)
+    thg, xg = th.clone().requires_grad_(True), x.clone().requires_grad_(True)
+    before = binding.givens_prepare(th, n, m)                      # (tokens count the calls)
+    out = layer.givens_apply(thg, xg, m)
+    out.backward(g)
+    assert binding.givens_prepare(th, n, m) == before + 1
+    assert torch.equal(out.detach(), y) and torch.equal(xg.grad, dx) and torch.equal(thg.grad, dth)

@@ -124,3 +124,15 @@ def test_packed_matrices_must_be_aligned():
     assert L.givens_kept_changed(0) == 1
     assert L.givens_apply_kept(10 ** 9, 8, 7, 1, p, p, p, ctypes.c_void_p(at + 16), None) == -8
     assert L.givens_kept_bytes(1, 1) == -1 and L.givens_kept_bytes(8, 8) == -7 and L.givens_kept_bytes(40000, 5) == -5
+
+
+# Prepared tables pay unless the plain calls have kernels of their own: smallest matrices on wide batches (dX and dtheta by the Gram
+# form), tables in the order of the lanes, tiles.  (n, m, B): both sides of every line.
+@pytest.mark.parametrize("n,m,B,pays", [
+    (14, None, 4096, True), (16, None, 31, True), (16, None, 32, False), (40, None, 79, True), (40, None, 80, False),
+    (33, 5, 67, True), (33, 5, 68, False), (64, None, 127, True), (64, None, 65536, False), (66, None, 65536, True),
+    (256, None, 1100, True), (512, None, 2048, True), (528, None, 512, True), (528, None, 513, False), (528, None, 1025, True),
+    (528, None, 2048, False), (768, None, 4096, False), (767, 300, 4096, False), (3072, None, 512, False), (2048, None, 2048, True),
+    (1006, None, 1100, False)])
+def test_where_prepared_tables_pay(n, m, B, pays):
+    assert bool(binding.givens_prepare_pays(n, m, B)) == pays
