@@ -128,7 +128,8 @@ def _check(rc: int, where: str):
 
 def current_stream_key():
     """The current device and the address of its current stream (torch.cuda.current_stream() makes a Python object of it, which
-    takes longer than the rest of a call's marshalling)."""
+    takes longer than the rest of a call's marshalling).  The two functions are PyTorch's own and not documented: its
+    compiled code calls them, and tests/test_gpu_evaluation.py runs on other streams than the default one."""
     global _raw_stream, _current_device
     if _raw_stream is None:
         import torch

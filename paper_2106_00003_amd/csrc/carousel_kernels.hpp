@@ -138,15 +138,6 @@ __device__ __forceinline__ void lds_load_row(float (&dst)[W], const float *src)
     }
 }
 
-// Between a wavefront's stores to LDS and its other lanes' loads from there, or the other way round: its LDS operations run in order,
-// so this only holds the compiler to it.
-__device__ __forceinline__ void wavefront_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // FORM 0: standard rotation (2 MUL + 2 FMA per update, table holds cos and sin).
 // FORM 1: scaled rotation (2 FMA per update on values kept divided by their accumulated cosines,
 //         table holds alpha and beta, renormalisation every kRenormPeriod blocks; coef_kernels.hpp).

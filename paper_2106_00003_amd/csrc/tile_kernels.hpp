@@ -28,6 +28,7 @@
 #include "small_trig.hpp"
 #include "split_bf16.hpp"
 #include "tile_host.hpp"
+#include "wave_order.hpp"
 
 namespace givens {
 
@@ -800,14 +801,6 @@ __device__ __forceinline__ void tile_load_held_column(const TileTwoSidedArgs &a,
         v[1][3] = wave == 3 && row == kTileHalf - 1 ? 0.f : -held;
     }
 }
-// Between stores to LDS by a wavefront's lanes and loads of the same places by others of them, or the other way round.  A
-// wavefront's LDS operations run in order, so this only holds the compiler to it.
-__device__ __forceinline__ void tile_wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 // Rows 32 wave .. + 31 and columns 32 part .. + 31 of a result R as the matrix instructions leave it: to (x, y), turned in LDS
 // (`turn` is this wavefront's), and as it stands, negated, to (y, x)
 typedef float TileTurn[32][36];
@@ -843,7 +836,7 @@ __device__ __forceinline__ void tile_store_both(const TileTwoSidedArgs &a, const
         for (int w = 0; w < 4; ++w) four[w] = R[v + w];
         *reinterpret_cast<f32x4 *>(&turn[l32][8 * (v >> 2) + 4 * half]) = four;
     }
-    tile_wave_order();
+    wavefront_order();
     float *to = a.out + tile_s_block(g, i, j) + (wave & 1) * 2048 + (part & 1) * 1024 + lane * 8;
 #pragma unroll
     for (int f = 0; f < 2; ++f)
@@ -854,7 +847,7 @@ __device__ __forceinline__ void tile_store_both(const TileTwoSidedArgs &a, const
             for (int w = 0; w < 4; ++w) four[w] = turn[16 * f + tile_k(half, 4 * q + w)][l32];
             *reinterpret_cast<f32x4 *>(to + 512 * f + 4 * q) = four;
         }
-    tile_wave_order();   // the next result is turned in the same place
+    wavefront_order();   // the next result is turned in the same place
 }
 
 // One stage of S <- A S A^T: a workgroup per pair of tiles (x, y), x <= y, in place.  First V = S A_y^T, a wavefront taking

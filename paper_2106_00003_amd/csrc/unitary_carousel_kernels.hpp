@@ -39,6 +39,7 @@
 #include <utility>
 
 #include "carousel_kernels.hpp"
+#include "wave_order.hpp"
 
 namespace givens {
 
@@ -92,7 +93,7 @@ struct UnitaryCarouselFwd {
     static_assert(W % 2 == 0, "a lane holds whole complex numbers");
     static constexpr int kLastU = (2 * M - 2) % M;
     typedef unsigned Words __attribute__((ext_vector_type(4)));
-    static constexpr bool kTurned = WAVES == 1;   // strips of one wavefront: tables in the order of turned_place, workgroups of several strips
+    static constexpr bool kTurned = WAVES == 1;   // strips of one wavefront: tables in the order of turned_place, workgroups of one or four strips (unitary_fwd_strips)
 
     float top[M][W];
     float bot[M][W];

@@ -114,6 +114,31 @@ def test_infinities_and_nan_in_the_backward_call(n, B):
     assert not torch.isfinite(dth).all() and torch.equal(again, want) and torch.isfinite(plain).all()
 
 
+# ... with restricted parametrisations, where most pairs of tiles have one that does not rotate: an angle's gradient is finite only where
+# the float64 sweep's is
+@pytest.mark.parametrize("n,m,B", [(401, 60, 90), (700, 90, 40), (1001, 200, 2100), (2901, 100, 33)])
+def test_infinities_and_nan_in_restricted_backward_calls(n, m, B):
+    print(f"[tiles] infinities n={n} m={m} B={B}", flush=True)
+    data = inputs.make_restricted(n, m, B, seed=3650 + n)
+    th, y, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    for row, value in ((1, float("nan")), (n - 1, float("inf")), (n // 2, -float("inf"))):
+        bad = g.clone()
+        bad[row, B // 2] = value
+        clean = torch.ones(B, dtype=torch.bool, device="cuda")
+        clean[B // 2] = False
+        try:
+            binding.set_kernel(binding.KERNEL_TILES)
+            want, plain = binding.givens_backward_restricted(th, y, g, m)
+            dx, dth = binding.givens_backward_restricted(th, y, bad, m)
+            again, plain_again = binding.givens_backward_restricted(th, y, g, m)
+        finally:
+            binding.set_kernel(binding.KERNEL_AUTO)
+        wide = binding.givens_backward_restricted(th.double(), y.double(), bad.double(), m)[1]
+        assert torch.equal(dx[:, clean], want[:, clean]) and not torch.isfinite(dx[:, B // 2]).all()
+        assert not (torch.isfinite(dth) & ~torch.isfinite(wide)).any() and not torch.isfinite(dth).all()
+        assert torch.equal(again, want) and torch.equal(plain_again, plain) and torch.isfinite(plain).all()
+
+
 def test_calls_that_tiles_do_not_take():
     th = torch.zeros(15, device="cuda")
     try:

@@ -74,6 +74,32 @@ def test_every_way_to_a_result_gives_the_same_bits(n, m, B):
         assert torch.equal(binding.givens_forward_noalloc(th, x, torch.empty_like(x)), y)
 
 
+# infinities and NaN in the upstream gradient, and in an angle: the other columns of dX do not change, and what the float64 sweep
+# cannot tell is not finite here
+@pytest.mark.parametrize("n,m,B", [(64, 63, 3000), (40, 39, 24600), (33, 32, 130), (16, 15, 5000), (63, 9, 2500)])
+def test_infinities_and_nan_in_the_backward_call(n, m, B):
+    th, x, g = problem(n, m, B, 13 * n)
+    y = binding.givens_forward_restricted(th, x, m)
+    want, plain = binding.givens_backward_restricted(th, y, g, m)
+    for row, value in ((1, float("nan")), (n - 1, float("inf")), (n // 2, -float("inf"))):
+        bad = g.clone()
+        bad[row, B // 2] = value
+        clean = torch.ones(B, dtype=torch.bool, device="cuda")
+        clean[B // 2] = False
+        dx, dth = binding.givens_backward_restricted(th, y, bad, m)
+        wide = binding.givens_backward_restricted(th.double(), y.double(), bad.double(), m)[1]
+        assert torch.equal(dx[:, clean], want[:, clean]) and not torch.isfinite(dx[:, B // 2]).all()
+        assert not (torch.isfinite(dth) & ~torch.isfinite(wide)).any() and not torch.isfinite(dth).all()
+    for value in (float("nan"), float("inf")):
+        bad = th.clone()
+        bad[th.numel() // 2] = value
+        got = binding.givens_forward_restricted(bad, x, m), *binding.givens_backward_restricted(bad, y, g, m)
+        wide = binding.givens_forward_restricted(bad.double(), x.double(), m), *binding.givens_backward_restricted(bad.double(), y.double(), g.double(), m)
+        assert all(not (torch.isfinite(a) & ~torch.isfinite(b)).any() for a, b in zip(got, wide))
+    again = binding.givens_backward_restricted(th, y, g, m)
+    assert torch.equal(again[0], want) and torch.equal(again[1], plain) and torch.isfinite(plain).all()
+
+
 def test_gram_form_chosen_for_a_narrow_batch():
     th, x, g = problem(40, 39, 7, 5)
     want_y = binding.givens_forward(th.double(), x.double())
