@@ -50,29 +50,12 @@ constexpr TileCost kProductComplexCost[kProductComplexTiles] = {
     {64, 64, 4, 2.7, 1.98, 4, {{0.92, 1.06}, {1.36, 1.53}, {1.84, 2.06}, {2.33, 2.49}}},
     {128, 64, 2, 2.9, 1.69, 4, {{1.19, 1.53}, {1.99, 2.12}, {2.84, 2.84}, {3.61, 3.74}}},
     {128, 128, 2, 4.2, 3.06, 4, {{1.99, 2.71}, {3.28, 3.59}, {4.78, 4.80}, {6.76, 6.76}}}};
-// Whether the pieces of a tiled product with a contraction over k indices may be fp16: from where that is no less exact on.
-// Relative error against float64, fp16 / bf16: k = 64 1.10e-7 / 1.12e-7, 128 1.47e-7 / 1.60e-7, 256 1.9e-7 / 2.4e-7, 1024
-// 3.7e-7 / 5.0e-7, 4096 7.0e-7 / 9.8e-7.  (Up to 64 memory bounds a product, whatever the pieces.)
-constexpr bool product_half_k(long long k) { return k > 64; }
-// Their tiles, fitted to 150 real products and 90 complex ones of n = 34 ... 3800: the choice is 0.4 % slower than the best on average
-// and 9 % at most.  Times in us, bf16 / fp16 pieces, best tile of each: n = 256, B = 65536 54 / 37, n = 512, B = 9856 43 / 29, n = 1002,
-// B = 3001 51 / 39, n = 1024, B = 4096 60 / 42, n = 2048, B = 4096 206 / 112, B = 65536 2580 / 1577 (349 TFLOP/s), n = 4096, B = 8192
-// 1260 / 772.  A tile of 256 x 256 with eight wavefronts took 1666 and 809 us in the last two.
-constexpr TileCost kProductHalfCost[kProductTiles] = {
-    {64, 64, 4, 3.9, 1.30, 4, {{0.44, 0.53}, {0.71, 0.84}, {1.02, 1.18}, {1.33, 1.53}}},
-    {128, 64, 3, 5.4, 1.59, 3, {{0.47, 0.66}, {0.94, 1.34}, {1.62, 1.67}}},
-    {128, 128, 2, 7.3, 1.91, 2, {{0.75, 1.25}, {1.66, 1.96}}},
-    {256, 128, 2, 9.4, 2.88, 2, {{1.23, 1.73}, {2.33, 2.95}}}};
-constexpr TileCost kProductHalfComplexCost[kProductComplexTiles] = {
-    {64, 64, 6, 3.3, 2.22, 6, {{0.79, 0.92}, {1.08, 1.26}, {1.45, 1.59}, {1.96, 2.19}, {2.19, 2.70}, {2.70, 2.85}}},
-    {128, 64, 4, 3.6, 2.20, 4, {{0.86, 0.99}, {1.31, 1.60}, {1.86, 2.12}, {2.58, 2.58}}},
-    {128, 128, 3, 5.2, 3.15, 3, {{1.38, 1.66}, {2.36, 2.71}, {3.30, 3.47}}}};
-inline int product_tile(int m, int k, long long B, int compute_units, bool cplx, bool half = false)
+inline int product_tile(int m, int k, long long B, int compute_units, bool cplx)
 {
     int best = 0;
     double least = 0.0;
     for (int i = 0; i < (cplx ? kProductComplexTiles : kProductTiles); ++i) {
-        const TileCost &t = cplx ? (half ? kProductHalfComplexCost : kProductComplexCost)[i] : (half ? kProductHalfCost : kProductCost)[i];
+        const TileCost &t = cplx ? kProductComplexCost[i] : kProductCost[i];
         // (an XCD has whole blocks of columns: product_kernel)
         const long long groups = (long long)((m + t.bm - 1) / t.bm) * (((B + t.bn - 1) / t.bn + 7) / 8);
         const double us = tile_time(t, groups, (k + kProductStep - 1) / kProductStep, compute_units);

@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256, 2) void wide_small_product_kernel(ProductArgs 
     if (blockIdx.x < sweeps)
         small_sweep(s);
     else
-        product_tiled<2, 2, 1, 1, 1, false, false>(p, blockIdx.x - sweeps);
+        product_tiled<2, 2, 1, 1, 1, false>(p, blockIdx.x - sweeps);
 }
 __global__ __launch_bounds__(64 * kNarrowWaves, 1) void wide_small_narrow_kernel(ProductArgs p, SmallSweepArgs s, unsigned sweeps)
 {

@@ -1,0 +1,198 @@
+"""Products of wide batches with the library's own U or U^T: what an element of the result keeps where a rotation leaves it alone or
+is small beside the rest of its column, the product by itself, and columns of every size and range."""
+import numpy as np
+import pytest
+
+from paper_2106_00003_amd import binding, inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+    yield
+    binding.release()
+
+
+@pytest.fixture(autouse=True)
+def _library_defaults(_forms_by_range):
+    binding.set_rotation_form(binding.FORM_AUTO)
+
+
+# A product by itself, of k indices: pieces that are left out are 2^-24 of it at most, and its 3 k / 8 sums round by half of 2^-23 at most, as
+# often up as down, of partial sums that grow as a walk (measured: 1.6e-7 at k = 128, 2.4e-7 at 256, 5.0e-7 at 1024, 0.55 to 0.65 of this).
+def product_bound(k):
+    return 2.0 ** -24 * (1 + (3 * k / 16) ** 0.5)
+
+
+# ... and U, each of whose n - 1 blocks rounds by 2^-24 at most
+def bound(n):
+    return product_bound(n) + 2.0 ** -24 * n ** 0.5
+
+
+def rel(got, want):
+    return float((got.to(want.dtype) - want).norm() / want.norm())
+
+
+def worst_column(got, want):
+    err, norm = (got.to(want.dtype) - want).norm(dim=0), want.norm(dim=0)
+    assert float(got.abs()[:, norm == 0].sum()) == 0.0
+    return float((err[norm > 0] / norm[norm > 0]).max())
+
+
+# each tile, contractions of no whole step, columns of no whole tile; few enough results for the narrow kernel (n = 384)
+SHAPES = [(66, 33003), (96, 24000), (130, 20001), (256, 65536), (384, 2909), (384, 4000), (514, 9857), (1002, 3001), (2050, 8199)]
+COMPLEX = [(34, 20001), (160, 8000), (320, 4100)]
+
+
+def zero_angles(n):
+    return torch.zeros(n * (n - 1) // 2, device="cuda")
+
+
+# U = I: every bit of an element comes back, whatever stands beside it in its column
+@pytest.mark.parametrize("n,B", SHAPES)
+def test_no_rotation_gives_the_operand_back(n, B):
+    th = zero_angles(n)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, B, device="cuda", generator=gen)
+    x[33::5] *= 1e-9
+    x[34::5] *= 1e12
+    y = binding.givens_forward(th, x)
+    assert binding.last_product() and torch.equal(y, x)
+    assert torch.equal(binding.givens_forward_transposed(th, x), x)
+    assert torch.equal(binding.givens_backward(th, y, x)[0], x)
+    assert torch.equal(binding.givens_forward(th, y, Y=y), x)
+
+
+@pytest.mark.parametrize("n,B", COMPLEX)
+def test_no_complex_rotation_gives_the_operand_back(n, B):
+    th = zero_angles(n)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, B, device="cuda", dtype=torch.complex64, generator=gen)
+    x[33::5] *= 1e-9
+    assert torch.equal(binding.givens_unitary_forward(th, th, x), x) and binding.last_product()
+    assert torch.equal(binding.givens_unitary_backward(th, th, x, x)[0], x)
+
+
+# Few rotations and elements of every size: each result against the sum of the magnitudes that it is made of.  An element of U has gone through
+# eight rotations of at most three roundings, all of the same few terms: 2^-19 with the product.
+@pytest.mark.parametrize("n,B", SHAPES)
+def test_elements_far_below_their_column(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(5050 + n)
+    th = zero_angles(n)
+    th[torch.randint(0, th.numel(), (8,), device="cuda", generator=gen)] = torch.rand(8, device="cuda", generator=gen) + 0.3
+    x = torch.randn(n, B, device="cuda", generator=gen) * 10.0 ** -(torch.arange(n, device="cuda") % 13.0)[:, None]
+    x[:32] = 1.0
+    for apply, transposed in ((binding.givens_forward, False), (binding.givens_forward_transposed, True)):
+        u = binding.givens_build(th.double(), n)
+        u = u.t().contiguous() if transposed else u
+        got, want, size = apply(th, x), u @ x.double(), u.abs() @ x.double().abs()
+        assert bool(((got.double() - want).abs() <= 2.0 ** -19 * size).all())
+
+
+@pytest.mark.parametrize("std", [0.1, 3.0])
+@pytest.mark.parametrize("n,B", SHAPES)
+def test_the_product_by_itself(n, B, std):
+    gen = torch.Generator(device="cuda").manual_seed(5070 + n)
+    th = torch.randn(n * (n - 1) // 2, device="cuda", generator=gen) * std
+    x = torch.randn(n, B, device="cuda", generator=gen)
+    u = binding.givens_build(th, n)
+    assert rel(binding.givens_forward(th, x), u.double() @ x.double()) <= product_bound(n)
+    assert binding.last_product()
+
+
+@pytest.mark.parametrize("n,B", COMPLEX)
+def test_the_complex_product_by_itself(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(5080 + n)
+    th, ph = (torch.randn(n * (n - 1) // 2, device="cuda", generator=gen) for _ in range(2))
+    x = torch.randn(n, B, dtype=torch.complex64, device="cuda", generator=gen)
+    u = binding.givens_unitary_build(th, ph, n)
+    wide = u.to(torch.complex128) @ x.to(torch.complex128)
+    assert rel(binding.givens_unitary_forward(th, ph, x), wide) <= product_bound(2 * n)
+    assert binding.last_product()
+
+
+@pytest.mark.parametrize("n,B", SHAPES)
+def test_columns_of_every_range(n, B):
+    data = inputs.make_custom(n, B, seed=5100 + n)
+    th, x = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X"))
+    plain = binding.givens_forward(th, x)
+    assert binding.last_product()
+    want = binding.givens_forward(th.double(), x.double())
+    most = 3 * bound(n)                                # (of the worst of thousands of columns)
+    assert worst_column(plain, want) <= most
+    odd = x.clone()
+    changed = torch.zeros(B, dtype=torch.bool, device="cuda")
+
+    def change(first, f):
+        columns = torch.arange(first, B, 61, device="cuda")
+        odd[:, columns] = f(odd[:, columns].clone())
+        changed[columns] = True
+
+    def rows(v, at, by):
+        v[at] *= by
+        return v
+
+    change(0, lambda v: rows(v, slice(0, 32), 0.0))                    # nothing in the first rows, the others of the size of 1
+    change(1, lambda v: rows(v, slice(0, 32), 0.0) * 1e-9)             # ... or far from it
+    change(2, lambda v: rows(v, slice(0, 32), 0.0) * 1e9)
+    change(3, lambda v: rows(v, slice(0, 32), 1e-6))                   # later elements far larger than the first
+    change(4, lambda v: rows(v, n - 1, 1e5))
+    change(5, lambda v: rows(v, n - 1, 200.0))                         # ... and somewhat
+    change(6, lambda v: v * 0.0)
+    change(7, lambda v: v * 1e-38)                                     # down to the numbers that are not normal
+    change(8, lambda v: rows(v, slice(0, 32), 0.0) * 1e37)
+    got = binding.givens_forward(th, odd)
+    want = binding.givens_forward(th.double(), odd.double())
+    normal = odd.abs().amax(dim=0) > 1e-36
+    assert worst_column(got[:, normal], want[:, normal]) <= most
+    tiny = ~normal                                     # (results that are not normal numbers: to 2^-149)
+    assert float((got[:, tiny].double() - want[:, tiny]).abs().max()) <= 2.0 ** -126 * most * n ** 0.5 + 2.0 ** -148
+    assert torch.equal(got[:, ~changed], plain[:, ~changed])           # a column does not depend on its neighbours
+
+
+@pytest.mark.parametrize("n,B", [(96, 24000), (514, 9857)])
+def test_infinities_and_nan_stay_in_their_columns(n, B):
+    data = inputs.make_custom(n, B, seed=5200 + n)
+    th, x = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X"))
+    plain = binding.givens_forward(th, x)
+    for at in (3, n - 1):                              # in the first step and in the last
+        bad = x.clone()
+        bad[at, 5], bad[at, 70], bad[at, 200] = float("inf"), float("nan"), float("-inf")
+        got = binding.givens_forward(th, bad)
+        hit = torch.zeros(B, dtype=torch.bool, device="cuda")
+        hit[torch.tensor([5, 70, 200], device="cuda")] = True
+        assert not bool(torch.isfinite(got[:, hit]).any())
+        assert torch.equal(got[:, ~hit], plain[:, ~hit])
+
+
+# in place (columns at work are copied), transposed, the backward call's product, and complex operands
+@pytest.mark.parametrize("n,B", [(130, 20001), (1002, 3001)])
+def test_every_call_that_multiplies(n, B):
+    data = inputs.make_custom(n, B, seed=5300 + n)
+    th, x, g = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X", "G"))
+    y = binding.givens_forward(th, x)
+    buf = x.clone()
+    assert torch.equal(binding.givens_forward(th, buf, Y=buf), y)
+    most = 3 * bound(n)
+    assert worst_column(binding.givens_forward_transposed(th, x), binding.givens_forward_transposed(th.double(), x.double())) <= most
+    dx, _ = binding.givens_backward(th, y, g)
+    want, _ = binding.givens_backward(th.double(), y.double(), g.double())
+    assert worst_column(dx, want) <= most
+
+
+@pytest.mark.parametrize("n,B", [(34, 20001), (160, 8000)])
+def test_complex_operands(n, B):
+    gen = torch.Generator(device="cuda").manual_seed(5400 + n)
+    th, ph = ((torch.rand(n * (n - 1) // 2, device="cuda", generator=gen) * 2 - 1) * np.pi for _ in range(2))
+    x = torch.randn(n, B, dtype=torch.complex64, device="cuda", generator=gen)
+    x[:, 1::61] *= 1e-20
+    x[:16, 2::61] = 0.0
+    x[n - 1, 3::61] *= 1e6
+    got = binding.givens_unitary_forward(th, ph, x)
+    want = binding.givens_unitary_forward(th.double(), ph.double(), x.to(torch.complex128))
+    assert worst_column(got, want) <= 6 * bound(n)     # (a complex rotation rounds three real ones)
