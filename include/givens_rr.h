@@ -219,8 +219,8 @@ int givens_build_prepared(int64_t token, float *U, void *stream);
 int givens_backward_prepared(int64_t token, int64_t B, const float *Y, const float *G, float *dX, float *dtheta,
                              void *stream);
 
-/* 1 when a forward and a backward call on B columns gain by prepared tables or lose nothing, 0 when they are faster as plain
- * calls (which run as tiles on the matrix cores, in fewer kernels for n <= 64 and B >= 2 n, or on a table in the order of
+/* 1 when a forward and a backward call on B columns gain by prepared tables or lose nothing, 0 when they are as fast or faster as
+ * plain calls (which run as tiles on the matrix cores, in fewer kernels for n <= 64 and B >= 2 n, or on a table in the order of
  * the lanes, which prepared ones are not), or a negative error code. */
 int givens_prepare_pays(int n, int m, int64_t B);
 

@@ -312,20 +312,17 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 }
 
 // With eight slots per lane a wavefront's part of a row of the table is 4 KB, which every strip reads.  Strips of one wavefront: one that
-// has its compute unit, or nearly, to itself does well with a lane's slots side by side, and so does one of two columns with up to two
-// others; beyond that the loads set the time, unless the table is turned (turned_place in rr_index.h).  From four strips per
-// compute unit on they are one workgroup, whose wavefronts stay close enough to find their rows in the unit's L1.  Forward sweep and
-// table in us, as they were (single columns up to 512, then two) and turned, with single columns in workgroups of one and of four
-// strips and with two columns in workgroups of four: n = 528, B = 512 63 / 68, 528 92 / 65, 77, 792 96 / 81, 79; n = 768, B = 512 94 / 97,
-// 768 137 / 100, 104, 1528 139 / 169, 198, 148; n = 1024, B = 1024 182 / 149, 143, 1536 198 / 233, 265, 201, 2040 295 / 355, 314,
-// 209.  (Four slots per lane gain nothing: n = B = 512 38 / 45.)  Single columns have since taken the staged kernel (carousel_staged).
+// has its compute unit, or nearly, to itself does well with a lane's slots side by side; from there on the staged sweep brings the rows
+// (carousel_staged), and does so a little faster where they are turned (turned_place in rr_index.h).  Forward sweep and table in us, as they
+// are and turned: n = 1024, B = 440 113.0 / 112.7, 768 120.8 / 120.4, 1030 146.8 / 143.6, 1536 156.4 / 152.7, 2040 197.0 / 191.1, n = 896, B = 512
+// 101.9 / 100.4, 1300 130.3 / 128.0, n = 768, B = 1030 108.6 / 107.3, n = 528, B = 513 60.9 / 60.7, 1030 75.0 / 74.0.  (Four slots per lane gain
+// nothing: n = B = 512 38 / 45.)
 // Strips of two to eight wavefronts, one or two columns wide, are faster turned from the first column on: n = 1040, B = 1 237 / 231, 512 251 /
 // 238, n = 2048, B = 1 499 / 457, 512 510 / 473, 2000 994 / 682, n = 3072, B = 512 1041 / 766, n = 4096, B = 1 1228 / 1043, 512
 // 1322 / 1198.  Not those of two columns and two wavefronts, the second of them short, while up to three have a compute unit: n = 1040,
 // B = 1200 292 / 307, 1536 298 / 310, 1560 375 / 314, n = 1168, B = 1400 333 / 346, 1536 383 / 368, n = 1264, B = 1025 361 / 343, 1200 366 / 371,
 // 1400 414 / 393, n = 1328, B = 1100 390 / 392, 1200 436 / 411.  Wider ones have enough arithmetic per row (n = B = 2048 730 / 784).
 constexpr int kTurnedSlots = 8;
-constexpr long long kTurnedSingleB = 1024;
 // Strips of one column and eight slots: the table by way of LDS, in workgroups of four strips (carousel_forward_staged_kernel), in either order
 // of its rows.  Forward calls in us, before (each strip's own loads, of one column up to 512, then two, turned from 1537 on) and with staged
 // rows: n = 1024, B = 450 128 / 115, 512 130 / 119, 1024 138 / 121, 1100 189 / 148, 1536 197 / 159, n = 528, B = 1030 104 / 74, 1536 97 / 81,
@@ -339,7 +336,7 @@ inline bool carousel_turned(int n, long long B)
 {
     CarouselPlan p;
     if (!carousel_fwd_plan(n, B, &p) || p.s.M != kTurnedSlots) return false;
-    if (p.wave) return (B > 512 && B <= kTurnedSingleB) || (B > 1536 && B <= 2048);
+    if (p.wave) return carousel_staged(p, n, B);
     if (p.W > 2 || p.s.WAVES > 8) return false;
     return !(p.W == 2 && p.s.WAVES == 2 && n <= 1232 && B > 1024 && B <= 1536 && n * B < 1700000);
 }

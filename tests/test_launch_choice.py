@@ -46,11 +46,11 @@ def test_float64_rows_of_sums(choice, n, B, one, four):
     assert {1: one, 4: four}[choice.wave64_strips(n, ctypes.c_longlong(B))] <= 1.03 * min(one, four)
 
 
-# Forward sweeps with eight slots per lane in us, with the table in the order of the angles and turned; strips of one wavefront, then of
-# several, of which n = 1040 to 1232 with two columns and up to three strips per compute unit are up to 6 % slower turned.
+# Forward sweeps with eight slots per lane in us, with the table in the order of the angles and turned; strips of one wavefront (the staged
+# sweep, which takes either), then of several, of which n = 1040 to 1232 with two columns and up to three strips per compute unit are up to 6 % slower turned.
 @pytest.mark.parametrize("n,B,plain,turned", [
-    (528, 512, 62.8, 63.5), (528, 513, 90.1, 64.3), (640, 768, 125.1, 80.8), (768, 1024, 141.2, 105.3), (768, 1025, 142.0, 145.6),
-    (896, 1536, 164.7, 174.8), (896, 1537, 202.0, 173.2), (1024, 2040, 261.3, 198.6), (1024, 400, 127.4, 126.8),
+    (1024, 440, 113.0, 112.7), (1024, 512, 118.0, 117.9), (528, 513, 60.9, 60.7), (768, 1024, 92.3, 92.1), (768, 1030, 108.6, 107.3),
+    (1024, 1030, 146.8, 143.6), (896, 1536, 135.5, 133.7), (1024, 1536, 156.4, 152.7), (896, 1600, 131.9, 129.4), (1024, 2040, 197.0, 191.1),
     (1040, 1, 237.2, 230.5), (1040, 640, 281.7, 235.5), (1040, 1200, 291.6, 306.8), (1040, 1536, 298.2, 309.8), (1040, 1560, 375.1, 314.1),
     (1072, 1400, 299.6, 316.6), (1104, 1100, 306.3, 324.6), (1104, 1536, 318.7, 327.5), (1104, 1700, 446.6, 359.2),
     (1168, 1400, 333.5, 346.3), (1168, 1536, 383.5, 368.1), (1232, 1200, 356.1, 364.2), (1232, 1400, 402.0, 385.8),
@@ -61,9 +61,9 @@ def test_turned_tables(choice, n, B, plain, turned):
 
 
 # which of the sizes of tests/test_gpu_turned.py are turned, on both sides of every line
-@pytest.mark.parametrize("n,B,expected", [(528, 512, 0), (528, 513, 1), (528, 768, 1), (528, 771, 1), (1024, 1021, 1), (1024, 1024, 1),
-                                          (1024, 1025, 0), (1024, 1537, 1), (768, 1535, 0), (1008, 2007, 1), (1040, 1041, 0),
-                                          (1040, 1561, 1), (1536, 30, 1), (3072, 257, 1), (4096, 131, 1)])
+@pytest.mark.parametrize("n,B,expected", [(528, 512, 0), (528, 513, 1), (528, 768, 1), (528, 771, 1), (1024, 439, 0), (1024, 440, 1),
+                                          (1024, 1021, 1), (1024, 1024, 1), (1024, 1025, 1), (1024, 1537, 1), (768, 1535, 1), (1008, 2007, 1),
+                                          (1024, 2048, 1), (1024, 2049, 0), (1040, 1041, 0), (1040, 1561, 1), (1536, 30, 1), (3072, 257, 1), (4096, 131, 1)])
 def test_sizes_that_are_turned(choice, n, B, expected):
     assert choice.turned(n, ctypes.c_longlong(B)) == expected
 

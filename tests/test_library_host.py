@@ -131,7 +131,7 @@ def test_packed_matrices_must_be_aligned():
 @pytest.mark.parametrize("n,m,B,pays", [
     (14, None, 4096, True), (16, None, 31, True), (16, None, 32, False), (40, None, 79, True), (40, None, 80, False),
     (33, 5, 67, True), (33, 5, 68, False), (64, None, 127, True), (64, None, 65536, False), (66, None, 65536, True),
-    (256, None, 1100, True), (512, None, 2048, True), (528, None, 512, True), (528, None, 513, False), (528, None, 1025, True),
+    (256, None, 1100, True), (512, None, 2048, True), (528, None, 512, True), (528, None, 513, False), (528, None, 1025, False),
     (528, None, 2048, False), (768, None, 4096, False), (767, 300, 4096, False), (3072, None, 512, False), (2048, None, 2048, True),
     (1006, None, 1100, False)])
 def test_where_prepared_tables_pay(n, m, B, pays):
