@@ -214,6 +214,7 @@ inline int unitary_fwd_width(long long Breal, int waves)
     return W < 2 ? 2 : W;
 }
 constexpr int kTurnedStrips = 4;
+constexpr int kTurnedSlots = 8;   // slots per lane of the forward sweeps whose tables may be turned
 inline int unitary_fwd_strips(long long strips) { return strips <= 512 || (strips > 1024 && strips <= 1536) ? 1 : kTurnedStrips; }
 struct UnitaryCarouselFwdArgs {
     int n;
@@ -293,7 +294,8 @@ int carousel_backward_wave(const CarouselBwdArgs &a, int M, int W);
 // exchange over n = 256 .. 1024 and B = 64 .. 262144 it is 1.5 to 3.2 times faster with 2 or 4 slots per lane (the
 // LDS shapes of those n leave lanes idle) and 1.0 to 1.7 times with 8.  Its strips are single columns while the
 // batch gives each SIMD at most one wavefront, then 2, 4 and 8 columns: every wavefront reads the whole coefficient
-// table, and beyond about a thousand wavefronts that traffic (L2) sets the time.
+// table, and beyond about a thousand wavefronts that traffic (L2) sets the time.  With eight slots single columns share it from
+// some 500 on (carousel_staged) and stay the faster ones up to 2048.
 inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 {
     p->wave = false;
@@ -305,8 +307,10 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
         return false;
     }
     if (carousel_wave_shape_for(n, 8, &ws)) {
-        const long long single = ws.M == 8 ? 512 : 1024;     // widest batch of single-column strips
-        *p = {ws, B <= single ? 1 : B <= 4 * single ? 2 : B <= 16 * single ? 4 : 8, true};
+        if (ws.M == kTurnedSlots)
+            *p = {ws, B <= 2048 ? 1 : B <= 8192 ? 4 : 8, true};
+        else
+            *p = {ws, B <= 1024 ? 1 : B <= 4096 ? 2 : B <= 16384 ? 4 : 8, true};
     }
     return true;
 }
@@ -322,7 +326,6 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 // 1322 / 1198.  Not those of two columns and two wavefronts, the second of them short, while up to three have a compute unit: n = 1040,
 // B = 1200 292 / 307, 1536 298 / 310, 1560 375 / 314, n = 1168, B = 1400 333 / 346, 1536 383 / 368, n = 1264, B = 1025 361 / 343, 1200 366 / 371,
 // 1400 414 / 393, n = 1328, B = 1100 390 / 392, 1200 436 / 411.  Wider ones have enough arithmetic per row (n = B = 2048 730 / 784).
-constexpr int kTurnedSlots = 8;
 // Strips of one column and eight slots: the table by way of LDS, in workgroups of four strips (carousel_forward_staged_kernel), in either order
 // of its rows.  Forward calls in us, before (each strip's own loads, of one column up to 512, then two, turned from 1537 on) and with staged
 // rows: n = 1024, B = 450 128 / 115, 512 130 / 119, 1024 138 / 121, 1100 189 / 148, 1536 197 / 159, n = 528, B = 1030 104 / 74, 1536 97 / 81,
@@ -330,7 +333,7 @@ constexpr int kTurnedSlots = 8;
 // n = 768, B = 500 87 / 90.  Up to two workgroups, 64 KB of LDS each, share a compute unit.
 inline bool carousel_staged(const CarouselPlan &p, int n, long long B)
 {
-    return p.wave && p.s.M == kTurnedSlots && B <= 2048 && (B > 512 || n * B > 450000);
+    return p.wave && p.s.M == kTurnedSlots && p.W == 1 && (B > 512 || n * B > 450000);
 }
 inline bool carousel_turned(int n, long long B)
 {
@@ -352,7 +355,7 @@ inline int carousel_forward(int n, int rows, long long B, const CarouselCoefs &c
                          (identity || reinterpret_cast<uintptr_t>(X) % 16 == 0);
     const CarouselFwdArgs a{n, rows, B, coefs, X, Y, identity, aligned ? 1 : 0, mirror, stream};
     if (carousel_staged(plan, n, B)) return carousel_forward_staged(a);
-    if (coefs.turned) return plan.wave ? GIVENS_ERR_UNSUPPORTED : carousel_forward_turned_lds(a, s.WAVES, W);
+    if (coefs.turned) return carousel_forward_turned_lds(a, s.WAVES, W);
     if (plan.wave) return carousel_forward_wave(a, s.M, W);
     switch (s.M) {
     case 7: return carousel_forward_m7(a, s.WAVES, W);

@@ -266,21 +266,11 @@ struct CarouselFwd {
 #pragma unroll
                 for (int r = 0; r < M; ++r) dst[r] = tab_lane[(long long)k * H + r];
             } else {
-                const int row = k * H * (int)sizeof(float2);
-                if constexpr (TURNED) {
+                static_assert(!TURNED, "turned rows are read from LDS (load_staged)");
+                float v[2 * M];
+                tab.load(v, tab_bytes[0], k * H * (int)sizeof(float2));
 #pragma unroll
-                    for (int r = 0; r < M / 2; ++r) {
-                        float v[4];
-                        tab.load(v, tab_bytes[r], row);
-                        dst[2 * r] = make_float2(v[0], v[1]);
-                        dst[2 * r + 1] = make_float2(v[2], v[3]);
-                    }
-                } else {
-                    float v[2 * M];
-                    tab.load(v, tab_bytes[0], row);
-#pragma unroll
-                    for (int r = 0; r < M; ++r) dst[r] = make_float2(v[2 * r], v[2 * r + 1]);
-                }
+                for (int r = 0; r < M; ++r) dst[r] = make_float2(v[2 * r], v[2 * r + 1]);
             }
         } else {
             load_row_of<TURNED>(tab_lane, k, dst);
@@ -706,10 +696,9 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
 {
     using State = CarouselFwd<M, W, WAVES, FORM, EX, TURNED>;
     State st;
-    constexpr bool kStrips = TURNED && EX == kExchangeWave;   // as many strips in a workgroup as it has wavefronts
     const int L = n / (2 * M);                  // lanes that hold slots; the rest of the last wavefront idles
     st.lanes = L;
-    const int tid = kStrips ? (int)threadIdx.x & 63 : (int)threadIdx.x;
+    const int tid = threadIdx.x;
     const bool idle = tid >= L;
     const int coef_lane = idle ? 0 : tid;
     const int my_rows = idle ? 0 : rows;        // an idle lane loads zeros and stores nothing
@@ -718,8 +707,7 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
     st.H = n >> 1;      // (table_of_lane takes both)
     st.tid = tid;
     st.lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    st.wave = kStrips ? 0 : wave;
+    st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     st.table_of_lane(table, coef_lane);
     if constexpr (EX == kExchangeLds) {
         constexpr int LMAX = 64 * WAVES;
@@ -732,8 +720,7 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
         st.in_bot = (t > 0) ? b.bot_out.lane(t - 1) : b.top_out.lane(LMAX);      // near end: top[1] -> bot[0]
     }
 
-    const long long b0 = (kStrips ? (long long)blockIdx.x * (blockDim.x >> 6) + wave : (long long)blockIdx.x) * W;
-    if (kStrips && b0 >= B) return;
+    const long long b0 = (long long)blockIdx.x * W;
     if (EX == kExchangeWave && idle) return;    // (switched off: lane_from_next)
     const int wv = (B - b0) < W ? (int)(B - b0) : W;
     const bool vec = vec_ok && wv == W;
@@ -806,61 +793,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void carousel_forward_turned_kernel(
         carousel_forward_body<M, W, WAVES, kFormLifted, kExchangeLds, true>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror);
     else
         carousel_forward_body<M, W, WAVES, kFormStandard, kExchangeLds, true>(sh, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror);
-}
-
-// Eight slots per lane, one wavefront per strip: the table, turned, by way of LDS (CarouselFwd::staged_sweep).  A wavefront's part of a row is
-// 4 KB, so where each strip reads it by itself the loads set the time, 256 cycles of a compute unit's L1 for the four strips of n = B =
-// 1024, whose arithmetic takes 190.
-template <int W, int FORM>
-__device__ __forceinline__ void carousel_staged_body(StagedRows &staged, int n, int rows, long long B, const float2 *__restrict__ table,
-                                                     const float2 *__restrict__ renorm, const float *X, float *Y, int identity,
-                                                     int vec_ok, int mirror, int turned)
-{
-    constexpr int M = kTurnedSlots;
-    using State = CarouselFwd<M, W, 1, FORM, kExchangeWave, true, kTableStaged>;
-    State st;
-    const int L = n / (2 * M), lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (lane >= L) return;                               // (switched off: lane_from_next)
-    st.n = n;
-    st.H = n >> 1;
-    st.lanes = L;
-    st.lane = st.tid = lane;
-    st.wave = 0;
-    st.table_of_lane(table, lane);
-    st.tab_lane = table;
-    st.rn_lane = renorm + (long long)lane * M;
-    // (a strip that is not there is swept all the same, as zeros, since its wavefront brings a part of the rows)
-    const long long b0 = ((long long)blockIdx.x * kTurnedStrips + wave) * W;
-    const int wv = B - b0 < W ? (int)(B - b0) : W, my_rows = wv > 0 ? rows : 0;
-    const bool vec = vec_ok && wv == W;
-#pragma unroll
-    for (int r = 0; r < M; ++r) {
-        const int p = lane * M + r;
-        load_row<W>(st.top[r], X, B, mirrored_row(n, rr_label(n, n - 2, p), mirror), my_rows, b0, wv, vec, identity);
-        load_row<W>(st.bot[r], X, B, mirrored_row(n, rr_label(n, n - 2, n - 1 - p), mirror), my_rows, b0, wv, vec, identity);
-    }
-    st.staged_sweep(staged, turned != 0);
-    constexpr int UL = State::kLastU;
-#pragma unroll
-    for (int r = 0; r < M; ++r) {
-        const int p = lane * M + r;
-        store_row<W>(st.top[(r + UL) % M], Y, B, mirrored_row(n, p, mirror), my_rows, b0, wv, vec);
-        store_row<W>(st.bot[(r - UL + M) % M], Y, B, mirrored_row(n, n - 1 - p, mirror), my_rows, b0, wv, vec);
-    }
-}
-template <int W>
-__global__ __launch_bounds__(64 * kTurnedStrips, 2) void carousel_forward_staged_kernel(
-    int n, int rows, long long B, const float2 *__restrict__ table, const float2 *__restrict__ renorm,
-    const unsigned *flag, float scaled_max, const float *X, float *Y, int identity, int vec_ok, int mirror, int turned)
-{
-    __shared__ StagedRows staged;
-    const int form = __builtin_amdgcn_readfirstlane(selected_form(flag, scaled_max));
-    if (form == kFormScaled)
-        carousel_staged_body<W, kFormScaled>(staged, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror, turned);
-    else if (form == kFormLifted)
-        carousel_staged_body<W, kFormLifted>(staged, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror, turned);
-    else
-        carousel_staged_body<W, kFormStandard>(staged, n, rows, B, table, renorm, X, Y, identity, vec_ok, mirror, turned);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1725,20 +1657,15 @@ inline int carousel_forward_wave_slots(const CarouselFwdArgs &a, int W)
     switch (W) {
     case 8: carousel_launch_fwd_wave<M, 8>(a); return GIVENS_OK;
     case 4: carousel_launch_fwd_wave<M, 4>(a); return GIVENS_OK;
-    case 2: carousel_launch_fwd_wave<M, 2>(a); return GIVENS_OK;
+    case 2:
+        if constexpr (M == kTurnedSlots) return GIVENS_ERR_UNSUPPORTED;   // (staged single columns instead)
+        else carousel_launch_fwd_wave<M, 2>(a);
+        return GIVENS_OK;
     case 1: carousel_launch_fwd_wave<M, 1>(a); return GIVENS_OK;
     default: return GIVENS_ERR_UNSUPPORTED;
     }
 }
-// turned tables: strips of one or two columns
-template <int W>
-inline void carousel_launch_fwd_staged(const CarouselFwdArgs &a)
-{
-    const long long columns = (long long)W * kTurnedStrips, groups = (a.B + columns - 1) / columns;
-    hipLaunchKernelGGL(carousel_forward_staged_kernel<W>, dim3((unsigned)groups), dim3(64 * kTurnedStrips), 0, a.stream, a.n, a.rows, a.B,
-                       a.coefs.table, a.coefs.renorm, a.coefs.flag, a.coefs.scaled_max, a.X, a.Y, a.identity, a.vec_ok, a.mirror,
-                       a.coefs.turned ? 1 : 0);
-}
+// turned tables, strips of several wavefronts and one or two columns
 template <int W, int WAVES>
 inline void carousel_launch_fwd_turned(const CarouselFwdArgs &a)
 {
