@@ -122,9 +122,9 @@ def test_columns_of_every_range(n, B):
     th, x = (torch.from_numpy(data[k]).cuda() for k in ("theta", "X"))
     plain = binding.givens_forward(th, x)
     assert binding.last_product()
-    want = binding.givens_forward(th.double(), x.double())
-    most = 3 * bound(n)                                # (of the worst of thousands of columns)
-    assert worst_column(plain, want) <= most
+    u = binding.givens_build(th, n).double()
+    most = 2 * product_bound(n)                        # (of the worst of thousands of columns)
+    assert worst_column(plain, u @ x.double()) <= most
     odd = x.clone()
     changed = torch.zeros(B, dtype=torch.bool, device="cuda")
 
@@ -147,7 +147,7 @@ def test_columns_of_every_range(n, B):
     change(7, lambda v: v * 1e-38)                                     # down to the numbers that are not normal
     change(8, lambda v: rows(v, slice(0, 32), 0.0) * 1e37)
     got = binding.givens_forward(th, odd)
-    want = binding.givens_forward(th.double(), odd.double())
+    want = u @ odd.double()
     normal = odd.abs().amax(dim=0) > 1e-36
     assert worst_column(got[:, normal], want[:, normal]) <= most
     tiny = ~normal                                     # (results that are not normal numbers: to 2^-149)
