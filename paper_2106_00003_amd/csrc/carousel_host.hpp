@@ -327,10 +327,10 @@ inline bool carousel_fwd_plan(int n, long long B, CarouselPlan *p)
 // B = 1200 292 / 307, 1536 298 / 310, 1560 375 / 314, n = 1168, B = 1400 333 / 346, 1536 383 / 368, n = 1264, B = 1025 361 / 343, 1200 366 / 371,
 // 1400 414 / 393, n = 1328, B = 1100 390 / 392, 1200 436 / 411.  Wider ones have enough arithmetic per row (n = B = 2048 730 / 784).
 // Strips of one column and eight slots: the table by way of LDS, in workgroups of four strips (carousel_forward_staged_kernel), in either order
-// of its rows.  Forward calls in us, before (each strip's own loads, of one column up to 512, then two, turned from 1537 on) and with staged
-// rows: n = 1024, B = 450 128 / 115, 512 130 / 119, 1024 138 / 121, 1100 189 / 148, 1536 197 / 159, n = 528, B = 1030 104 / 74, 1536 97 / 81,
-// n = 768, B = 1500 139 / 112.  With two strips on a compute unit, and short rows, the loads are not what bounds a block: n = 528, B = 512 57 / 60,
-// n = 768, B = 500 87 / 90.  Up to two workgroups, 64 KB of LDS each, share a compute unit.
+// of its rows.  Forward calls in us, before (each strip's own loads, of one column up to 512, then two, turned from 1537 on) and with staged,
+// turned rows: n = 1024, B = 450 128 / 115, 512 130 / 118, 1024 138 / 121, 1100 189 / 145, 1536 197 / 153, n = 528, B = 1030 104 / 74, 1536
+// 97 / 78, n = 768, B = 1500 139 / 110.  With two strips on a compute unit, and short rows, the loads are not what bounds a block: n = 528,
+// B = 512 57 / 60, n = 768, B = 500 87 / 90.  Up to two workgroups, 64 KB of LDS each, share a compute unit.
 inline bool carousel_staged(const CarouselPlan &p, int n, long long B)
 {
     return p.wave && p.s.M == kTurnedSlots && p.W == 1 && (B > 512 || n * B > 450000);

@@ -44,7 +44,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 //   kExchangeLds:  through LDS, for every lane (any number of wavefronts); one barrier per block.
 //   kExchangeWave: with DPP wavefront shifts, for workgroups of one wavefront.  No LDS, no barrier, and a chain of
 //                  a few cycles from one block to the next instead of an LDS write, a barrier and an LDS read.
-//                  Each move costs VALU issue slots (two shifts and one or two selects per column), so it is
+//                  Each move costs VALU issue slots (two shifts and a select per column), so it is
 //                  the choice where a sweep is bound by that chain and not by arithmetic: few, narrow strips.
 enum { kExchangeLds = 0, kExchangeWave = 1 };
 // Coefficients (and the reverse sweep's earlier sums) are fetched ahead into a ring of registers: one block ahead
@@ -342,7 +342,8 @@ struct CarouselFwd {
 #pragma unroll
         for (int x = 0; x < W; ++x) asm volatile("" : "+v"(top[it][x]), "+v"(bot[ib][x]));
     }
-    // Phase PHASE of the rotation of slot R (the same results as rotate_slot's), what the phases hand on in p and q.
+    // Phase PHASE of the rotation of slot R (the same results as rotate_slot's), what the phases hand on in p and q.  (A function of its
+    // own: a slot's columns one after the other, as rotate_slot has them, are another schedule in every kernel of the LDS exchange.)
     static constexpr int kPhases = FORM == 0 ? 2 : FORM == 1 ? 1 : 3;
     template <int U, int R, bool RN, int PHASE>
     __device__ __forceinline__ void rotate_phase(const float2 (&cur)[M], const float2 (&rn)[M], float (&p)[M][W], float (&q)[M][W])
@@ -1215,15 +1216,15 @@ struct CarouselBwd {
                 move_in_wavefront<U>(gt, gb);
             }
         } else {
-        __builtin_amdgcn_s_setprio(2);   // the exchange slots are the block's critical path (see the forward kernel)
-        sums[0] = sweep_slot<U, 0, RN>(cur, rn);
-        if constexpr (M > 1) sums[M - 1] = sweep_slot<U, M - 1, RN>(cur, rn);
-        if constexpr (!LAST && EX == kExchangeLds) {
-            publish<U, PAR, 0>(zt, zb);
-            publish<U, PAR, 1>(gt, gb);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        if constexpr (kInner > 0) sweep_inner<U, RN, 1>(cur, rn, sums, std::make_integer_sequence<int, kInner>{});
+            __builtin_amdgcn_s_setprio(2);   // the exchange slots are the block's critical path (see the forward kernel)
+            sums[0] = sweep_slot<U, 0, RN>(cur, rn);
+            if constexpr (M > 1) sums[M - 1] = sweep_slot<U, M - 1, RN>(cur, rn);
+            if constexpr (!LAST) {
+                publish<U, PAR, 0>(zt, zb);
+                publish<U, PAR, 1>(gt, gb);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            if constexpr (kInner > 0) sweep_inner<U, RN, 1>(cur, rn, sums, std::make_integer_sequence<int, kInner>{});
         }
         {
             float *dst = part_lane + (long long)k * H;
