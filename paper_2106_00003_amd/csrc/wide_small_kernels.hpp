@@ -61,7 +61,7 @@ __device__ __forceinline__ void small_columns(const SmallMatrixArgs &a, int bloc
     };
     unit(st.top[0], idle ? 0 : rr_label(n, n - 2, lane));
     unit(st.bot[0], idle ? 0 : rr_label(n, n - 2, n - 1 - lane));
-    if (!idle) {                       // (the others are switched off: lane_from_next)
+    if (!lane_is_off(lane, L)) {
         st.lead_in();
 #pragma unroll
         for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(n - 2 - st.leading_blocks() - d, st.cs[d]);
@@ -69,6 +69,7 @@ __device__ __forceinline__ void small_columns(const SmallMatrixArgs &a, int bloc
         const int rt = mirrored_row(n, lane, a.mirror), rb = mirrored_row(n, n - 1 - lane, a.mirror);
 #pragma unroll
         for (int x = 0; x < W; ++x) {
+            if (idle) break;
             cols[rt][wave * W + x] = st.top[0][x];
             cols[rb][wave * W + x] = st.bot[0][x];
         }

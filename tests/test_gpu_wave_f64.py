@@ -70,6 +70,24 @@ def test_strip_widths_against_the_lds_kernels(n, B):
     assert torch.equal(binding.givens_backward(th, got[0], buf, dX=buf)[0], got[1])
 
 
+# wavefronts of eight lanes with slots and fewer, whose other lanes stay on but one; nine, where none does: batches past the ones that
+# take one kernel per call, strips of every width.  Beyond it the rows of other strips, sums and angles are as they should be.
+@pytest.mark.parametrize("n,B", [(n, B) for n in (10, 12, 14, 16, 18) for B in (1025, 2049, 4099)] + [(16, 9001), (13, 3000), (15, 5000)])
+def test_few_lanes_with_slots(n, B):
+    data = inputs.make_restricted(n, n - 1, B, seed=4250 + n)
+    th, x, g = (dev(data[k]).double() for k in ("theta", "X", "G"))
+
+    def run():
+        y = binding.givens_forward_restricted(th, x, n - 1)
+        return (y, *binding.givens_backward_restricted(th, y, g, n - 1))
+
+    got = run()
+    binding.set_kernel(binding.KERNEL_LDS)
+    want = run()
+    binding.set_kernel(binding.KERNEL_AUTO)
+    assert all(far(a, b) <= TOL for a, b in zip(got, want))
+
+
 # one kernel per call: strips that end with the batch, just past it and far before it, the largest batch and the next; both sides of
 # the sizes that take it.  Angles of 0 among the free ones, bypassed pairs, and odd sizes.  No more than some hundred roundings of
 # 1.1e-16 lie between the two, so 1e-12 has room.
