@@ -62,8 +62,12 @@ constexpr int wave_ring_depth_fwd(int M, int W, int form, bool turned)
 }
 constexpr int wave_ring_depth_bwd(int M, int W, int form)
 {
-    return M == 1 ? 8 : M == 2 ? (form == 0 ? 16 : 8) : form == 0 && W == 1 ? 8 : 4;
+    return M <= 2 || (form == 0 && W == 1) ? 8 : 4;
 }
+// The reverse sweep of two slots has a ring of 16 (standard form) where n is a multiple of that.  At other n eight blocks would stand before the
+// unrolled groups, fetched and done before the ring fills; those have a ring of 8: B = 100, with 16 and 8, n = 136 17.2 / 15.6 us, 152 19.0 /
+// 17.5, 200 24.0 / 23.0; n = 256 (16 and 8) B = 300 26.0 / 26.2, 1500 25.5 / 26.7.
+constexpr int kDeepRing = 16;
 // Slots that run in phases together: where a slot has few columns.  (Wide ones have results enough by themselves.)
 constexpr bool phases_together(int W) { return W <= 2; }
 constexpr int carousel_lcm(int a, int b)
@@ -841,7 +845,8 @@ constexpr int kChainSlack = 0;
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8; others: no wait)
 constexpr int waitcnt_vm(int vmcnt) { return (vmcnt & 15) | ((vmcnt >> 4) << 14) | (7 << 4) | (15 << 8); }
 
-template <int M, int W, int WAVES, int FORM, int EX = kExchangeLds, int CHAIN = 0>
+template <int M, int W, int WAVES, int FORM, int EX = kExchangeLds, int CHAIN = 0,
+          int RING = EX == kExchangeWave ? wave_ring_depth_bwd(M, W, FORM) : 2>
 struct CarouselBwd {
     static_assert(EX == kExchangeLds || WAVES == 1, "the DPP exchange stays inside one wavefront");
     static_assert(!CHAIN || (EX == kExchangeLds && M % 4 == 0), "chained rows: LDS exchange, 4 or 8 slots per lane");
@@ -850,7 +855,7 @@ struct CarouselBwd {
     // off by a strip's share; invalidating the L1 every block, buffer_inv sc1, made the sweep 13 times slower).
     // From 5 wavefronts on a workgroup has its compute unit to itself (registers and LDS leave no room for two).
     static_assert(!CHAIN || WAVES >= 5, "chained rows: one workgroup per compute unit");
-    static constexpr int kDepth = EX == kExchangeWave ? wave_ring_depth_bwd(M, W, FORM) : 2; // as in the forward kernel
+    static constexpr int kDepth = RING;        // as in the forward kernel
     static constexpr int kUnroll = carousel_lcm(M, kDepth);
     static_assert(FORM == 0 || kRenormPeriod % kUnroll == 0,
                   "renormalisation must fall on the last copy of an unrolled group");
@@ -1279,27 +1284,17 @@ struct CarouselBwd {
         (step<Cs, Cs == kUnroll - 2, false, (kUnroll - 2 - Cs >= kDepth - 1)>(k_first + Cs), ...);
     }
 
-    // as in the forward kernel
-    static constexpr bool kLeads = EX == kExchangeWave && FORM == 0 && kDepth == kUnroll;
-    __device__ __forceinline__ int leading_blocks() const { return kLeads ? n % kUnroll : 0; }
-    template <int... Cs>
-    __device__ __forceinline__ void lead_group(int lead, std::integer_sequence<int, Cs...>)
-    {
-        ((Cs < lead ? load_coefs(Cs, cs[Cs % kDepth]) : (void)0), ...);
-        ((Cs < lead ? load_prior(Cs, prior[Cs % kDepth]) : (void)0), ...);
-        ((Cs < lead ? step<Cs, false, false, false>(Cs) : (void)0), ...);
-    }
+    // one slot per lane: n is even and no more, so the first n mod kUnroll blocks go before the unrolled groups, by one copy of the body
+    // (with a copy for each there is more to fetch: n = 64 0.7 us of 13.6)
+    __device__ __forceinline__ int leading_blocks() const { return M == 1 ? n % kUnroll : 0; }
     __device__ __forceinline__ void lead_in()
     {
-        if constexpr (kLeads && M == 1) {       // (short sweeps: one copy of the body takes less to fetch; n = 64 0.7 us of 13.6)
+        if constexpr (M == 1)
             for (int k = 0; k < leading_blocks(); ++k) {
                 load_coefs(k, cs[0]);
                 load_prior(k, prior[0]);
                 step<0, false, false, false>(k);
             }
-        } else if constexpr (kLeads) {
-            if (const int lead = leading_blocks()) lead_group(lead, std::make_integer_sequence<int, kUnroll - 1>{});
-        }
     }
 
     // the other n-1 blocks in the order b_1, b_2, ...: whole groups, then the tail of kUnroll - 1
@@ -1341,7 +1336,8 @@ struct CarouselBwd {
 // out), the error word is set and the second stage poisons the result instead of returning sums that may have
 // been read from a stale L2.
 
-template <int M, int W, int WAVES, int FORM, int EX, int CHAIN, typename Exchange>
+template <int M, int W, int WAVES, int FORM, int EX, int CHAIN, int RING = EX == kExchangeWave ? wave_ring_depth_bwd(M, W, FORM) : 2,
+          typename Exchange>
 __device__ __forceinline__ void carousel_backward_body(Exchange &sh, int n, int rows, long long B,
                                                        long long strip0, long long nstrips,
                                                        const float2 *__restrict__ table,
@@ -1350,7 +1346,7 @@ __device__ __forceinline__ void carousel_backward_body(Exchange &sh, int n, int 
                                                        const float *__restrict__ zeros, float *sink, int vec_ok,
                                                        int g_identity, const CarouselChainArgs &chain)
 {
-    using State = CarouselBwd<M, W, WAVES, FORM, EX, CHAIN>;
+    using State = CarouselBwd<M, W, WAVES, FORM, EX, CHAIN, RING>;
     State st;
     const int L = n / (2 * M);                  // lanes that hold slots; the rest of the last wavefront idles
     const bool idle = (int)threadIdx.x >= L;
@@ -1489,6 +1485,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES > 8 ? 1 : 2) void carousel_backwa
                                                                   CarouselChainArgs{});
     } else {
         const int form = __builtin_amdgcn_readfirstlane(selected_form(flag, scaled_max));
+        if constexpr (EX == kExchangeWave && M == 2)
+            if (form != kFormScaled && form != kFormLifted && n % kDeepRing == 0) {
+                carousel_backward_body<M, W, WAVES, kFormStandard, EX, 0, kDeepRing>(
+                    sh, n, rows, B, strip0, nstrips, table, renorm, Yin, G, dX, partial, zeros, sink, vec_ok, g_identity,
+                    CarouselChainArgs{});
+                return;
+            }
         if (form == kFormScaled)
             carousel_backward_body<M, W, WAVES, kFormScaled, EX, 0>(sh, n, rows, B, strip0, nstrips, table, renorm,
                                                                     Yin, G, dX, partial, zeros, sink, vec_ok,
