@@ -16,7 +16,7 @@ __device__ __forceinline__ void carousel_staged_body(StagedRows &staged, int n, 
     using State = CarouselFwd<M, W, 1, FORM, kExchangeWave, true, kTableStaged>;
     State st;
     const int L = n / (2 * M), lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (lane_is_off(lane, L)) return;
+    if (lane_is_off<M>(lane, L)) return;
     st.n = n;
     st.H = n >> 1;
     st.lanes = L;

@@ -139,7 +139,9 @@ struct RowBuffer {
 // those without slots, but where eight or fewer have any only the one that would be the source.  With at most eight lanes on every
 // block takes longer, for a reason not known (float64, n = 16, B = 4000, forward and backward sweep 8.9 and 16.2 us, this way 5.0 and 7.7; n =
 // 18, nine lanes, 5.5 and 8.3; how the table is read makes no difference), so the lanes beyond go along, with zeros.
-__device__ __forceinline__ bool lane_is_off(int lane, int lanes) { return lanes > 8 ? lane >= lanes : lane == lanes; }
+// (With M > 1 slots per lane there are always more.)
+template <int M>
+__device__ __forceinline__ bool lane_is_off(int lane, int lanes) { return M > 1 || lanes > 8 ? lane >= lanes : lane == lanes; }
 
 // lane l receives the value of lane l+1; the last lane (no source, or one that is switched off) keeps `incoming`
 __device__ __forceinline__ float lane_from_next(float incoming, float v)
@@ -732,7 +734,7 @@ __device__ __forceinline__ void carousel_forward_body(Exchange &sh, int n, int r
     }
 
     const long long b0 = (long long)blockIdx.x * W;
-    if (EX == kExchangeWave && lane_is_off(st.lane, L)) return;
+    if (EX == kExchangeWave && lane_is_off<M>(st.lane, L)) return;
     const int wv = (B - b0) < W ? (int)(B - b0) : W;
     const bool vec = vec_ok && wv == W;
 
@@ -1360,8 +1362,8 @@ __device__ __forceinline__ void carousel_backward_body(Exchange &sh, int n, int 
     st.lane = threadIdx.x & 63;
     st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     st.tab_lane = table + (long long)coef_lane * M;
-    if (EX == kExchangeWave && lane_is_off(st.lane, L)) return;
-    st.slot0 = idle ? State::kNoSlot : threadIdx.x * M;
+    if (EX == kExchangeWave && lane_is_off<M>(st.lane, L)) return;
+    st.slot0 = M == 1 && idle ? State::kNoSlot : threadIdx.x * M;
     // (LDS exchange) an idle lane's sums (all zero) go to the sink: N + 8192 floats nobody reads
     const long long N = (long long)(n - 1) * (n >> 1);
     st.part_lane = idle ? sink + (long long)threadIdx.x * M

@@ -71,20 +71,18 @@ struct Wave64Coefs {
     double2 cs[DEPTH][M];
     RowBuffer table;
     const double2 *first;   // of this lane's slots
-    int bytes;              // to them in a row
     __device__ __forceinline__ void init(const double2 *base, int n, int lane)
     {
         table = RowBuffer::of(base, (long long)(n - 1) * (1024 * M));
         first = base + lane;
-        bytes = lane * 16;
     }
-    __device__ __forceinline__ void load(int k, int slot)
+    __device__ __forceinline__ void load(int k, int lane, int slot)
     {
         const double2 *src = first + (long long)k * (64 * M);
 #pragma unroll
         for (int r = 0; r < M; ++r) {
             if constexpr (ALONE) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(table.r, bytes + 1024 * r, k * (1024 * M), 0);
+                const auto v = __builtin_amdgcn_raw_buffer_load_b128(table.r, lane * 16 + 1024 * r, k * (1024 * M), 0);
                 cs[slot][r] = make_double2(__hiloint2double((int)v[1], (int)v[0]), __hiloint2double((int)v[3], (int)v[2]));
             } else {
                 cs[slot][r] = src[64 * r];
@@ -93,7 +91,8 @@ struct Wave64Coefs {
     }
 };
 
-// Lanes without slots are switched off before the sweep (lane_is_off).  Those that are not take lane 0's coefficients and zeros.
+// Lanes without slots are switched off before the sweep (lane_is_off).  Those that are not bring zeros and read what stands in their places of
+// the table's rows, which are 64 lanes wide; nothing of theirs reaches a lane with slots or is stored.
 template <int M, int W, bool SHARED>
 struct Wave64Fwd {
     static constexpr bool kPhases = wave64_in_phases(M, W, SHARED);
@@ -140,7 +139,7 @@ struct Wave64Fwd {
     __device__ __forceinline__ void step(int k)
     {
         constexpr int U = C % M;
-        if constexpr (AHEAD) co.load(k - (kDepth - 1), (C + kDepth - 1) % kDepth);
+        if constexpr (AHEAD) co.load(k - (kDepth - 1), lane, (C + kDepth - 1) % kDepth);
         rotate_groups<C>(std::make_integer_sequence<int, M / kTogether>{});
         if constexpr (!LAST) {
             constexpr int q = U % M, qb = (M - 1 - U + M) % M, q1 = (1 + U) % M;
@@ -174,7 +173,7 @@ struct Wave64Fwd {
     template <int... Cs>
     __device__ __forceinline__ void lead(int k, int count, std::integer_sequence<int, Cs...>)
     {
-        ((Cs < count ? co.load(k - Cs, Cs) : (void)0), ...);
+        ((Cs < count ? co.load(k - Cs, lane, Cs) : (void)0), ...);
         ((Cs < count ? step<Cs, false, false>(k - Cs) : (void)0), ...);
     }
     __device__ __forceinline__ void sweep(int n)
@@ -187,7 +186,7 @@ struct Wave64Fwd {
         }
 #pragma unroll
         for (int d = 0; d < kDepth - 1; ++d)
-            if (!wave64_asks(M, W) || k - d >= 0) co.load(k - d, d);
+            if (!wave64_asks(M, W) || k - d >= 0) co.load(k - d, lane, d);
         for (; k >= kUnroll - 1; k -= kUnroll) group(k, std::make_integer_sequence<int, kUnroll>{});
         tail(std::make_integer_sequence<int, kUnroll - 1>{});
     }
@@ -202,11 +201,11 @@ __global__ __launch_bounds__(64 * kWave64Strips, 1) void wave64_forward_kernel(i
     using State = Wave64Fwd<M, W, SHARED>;
     State st;
     const int l = threadIdx.x & 63, L = n / (2 * M);
-    const bool idle = l >= L;
+    const bool idle = M == 1 && l >= L;
     st.lane = l;
-    st.co.init(table, n, idle ? 0 : l);
+    st.co.init(table, n, l);
     const long long b0 = ((long long)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * W;
-    if (b0 >= B || lane_is_off(l, L)) return;
+    if (b0 >= B || lane_is_off<M>(l, L)) return;
     auto place = [&](int label) { return (mirror && label) ? n - label : label; };
     auto bring = [&](double(&v)[W], int row) {
 #pragma unroll
@@ -246,7 +245,7 @@ struct Wave64Bwd {
     double zt[M][W], zb[M][W], gt[M][W], gb[M][W];
     Wave64Coefs<M, kDepth, wave64_alone(M, W, STRIPS > 1)> co;
     int lane, wave, H;
-    bool idle;        // (false with more than one slot: those have more than eight lanes)
+    bool idle;        // (one slot per lane: no slot)
     RowBuffer part;   // this workgroup's row of partial sums
     struct Sums {
         double of[kWave64Depth][STRIPS][M][64];
@@ -311,7 +310,7 @@ struct Wave64Bwd {
     __device__ __forceinline__ void step(int k, int place = C % kWave64Depth)
     {
         constexpr int U = C % M;
-        if constexpr (AHEAD) co.load(k + (kDepth - 1), (C + kDepth - 1) % kDepth);
+        if constexpr (AHEAD) co.load(k + (kDepth - 1), lane, (C + kDepth - 1) % kDepth);
         double sums[M];
 #pragma unroll
         for (int r = 0; r < M; ++r) {
@@ -364,14 +363,14 @@ struct Wave64Bwd {
         int k = 0;
         if constexpr (M == 1) {
             for (; k < n % kUnroll; ++k) {   // (three blocks at most)
-                co.load(k, 0);
+                co.load(k, lane, 0);
                 step<0, false, false>(k, k);
             }
             if (k) flush(0, k);
         }
 #pragma unroll
         for (int d = 0; d < kDepth - 1; ++d)
-            if (!wave64_asks(M, W) || k + d <= n - 2) co.load(k + d, d);
+            if (!wave64_asks(M, W) || k + d <= n - 2) co.load(k + d, lane, d);
         for (; k + kUnroll <= n - 1; k += kUnroll) group(k, std::make_integer_sequence<int, kUnroll>{});
         tail(k, std::make_integer_sequence<int, kUnroll - 1>{});
     }
@@ -390,12 +389,12 @@ __global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, 
     st.turn = 0;
     st.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = threadIdx.x & 63, L = n / (2 * M);
-    if (lane_is_off(l, L)) return;
-    const bool idle = l >= L;
+    if (lane_is_off<M>(l, L)) return;
+    const bool idle = M == 1 && l >= L;
     st.lane = l;
     st.idle = idle;
     st.H = n >> 1;
-    st.co.init(table, n, idle ? 0 : l);
+    st.co.init(table, n, l);
     const long long sums_of_all = (long long)(n - 1) * (n >> 1);
     st.part = RowBuffer::of(partial + blockIdx.x * sums_of_all, sums_of_all * 8);
     const long long b0 = ((group0 + blockIdx.x) * STRIPS + st.wave) * W;   // (past the end: zeros)

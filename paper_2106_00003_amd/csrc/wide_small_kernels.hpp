@@ -61,7 +61,7 @@ __device__ __forceinline__ void small_columns(const SmallMatrixArgs &a, int bloc
     };
     unit(st.top[0], idle ? 0 : rr_label(n, n - 2, lane));
     unit(st.bot[0], idle ? 0 : rr_label(n, n - 2, n - 1 - lane));
-    if (!lane_is_off(lane, L)) {
+    if (!lane_is_off<1>(lane, L)) {
         st.lead_in();
 #pragma unroll
         for (int d = 0; d < State::kDepth - 1; ++d) st.load_coefs(n - 2 - st.leading_blocks() - d, st.cs[d]);
