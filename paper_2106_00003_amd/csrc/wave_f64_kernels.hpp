@@ -247,6 +247,11 @@ struct Wave64Bwd {
     int lane, wave, H;
     bool idle;        // (one slot per lane: no slot)
     RowBuffer part;   // this workgroup's row of partial sums
+    double *sums_row; // ... and this lane's slots in it
+    // Whether a sum is stored before the next one is read.  Eight slots and single columns: all sums and then the stores n = 784, B = 300, 512
+    // and 768 317, 382 and 427 us, one by one 316, 350 and 374; n = 1024 457, 531 and 593, 433, 483 and 532.  Others are the slower for it: four
+    // slots and two columns n = 512, B = 2000 187 and 198, eight and two n = 784, B = 1024 468 and 485.
+    static constexpr bool kOneByOne = M == 8 && W == 1 && STRIPS > 1;
     struct Sums {
         double of[kWave64Depth][STRIPS][M][64];
     };
@@ -278,14 +283,25 @@ struct Wave64Bwd {
         const auto &s = sums_of[turn].of;
         turn ^= 1;
         if (wave >= count || (M == 1 && idle)) return;
-        double v[M];
+        if constexpr (kOneByOne) {
+            double *dst = sums_row + (long long)(k0 + wave) * H;
 #pragma unroll
-        for (int r = 0; r < M; ++r) {
-            v[r] = s[wave][0][r][lane];
+            for (int r = 0; r < M; ++r) {
+                double v = s[wave][0][r][lane];
 #pragma unroll
-            for (int w = 1; w < STRIPS; ++w) v[r] += s[wave][w][r][lane];
+                for (int w = 1; w < STRIPS; ++w) v += s[wave][w][r][lane];
+                dst[r] = v;
+            }
+        } else {
+            double v[M];
+#pragma unroll
+            for (int r = 0; r < M; ++r) {
+                v[r] = s[wave][0][r][lane];
+#pragma unroll
+                for (int w = 1; w < STRIPS; ++w) v[r] += s[wave][w][r][lane];
+            }
+            store(v, k0 + wave);
         }
-        store(v, k0 + wave);
     }
     template <int U>
     __device__ __forceinline__ void move(double (&t)[M][W], double (&b)[M][W])
@@ -397,6 +413,7 @@ __global__ __launch_bounds__(64 * STRIPS, 1) void wave64_backward_kernel(int n, 
     st.co.init(table, n, l);
     const long long sums_of_all = (long long)(n - 1) * (n >> 1);
     st.part = RowBuffer::of(partial + blockIdx.x * sums_of_all, sums_of_all * 8);
+    if constexpr (State::kOneByOne) st.sums_row = partial + blockIdx.x * sums_of_all + l * M;
     const long long b0 = ((group0 + blockIdx.x) * STRIPS + st.wave) * W;   // (past the end: zeros)
     auto bring = [&](double(&v)[W], const double *src, int row) {
 #pragma unroll
